@@ -1,4 +1,4 @@
-"""Thin ctypes binding of libsrigl.so: argument marshalling only.
+"""Thin binding of libsrigl.so: argument marshalling only (ctypes, and the _front module for the calls a program repeats).
 
 Function names and argument order follow include/srigl.h.  Every array argument is a
 torch tensor on the GPU (PyTorch is used for device memory and streams, nothing else);
@@ -131,6 +131,10 @@ def _load() -> ctypes.CDLL:
 
 lib = _load()
 
+from . import _front  # noqa: E402  (the repeated calls without ctypes; needs torch and libsrigl.so loaded)
+
+_front.set_error(SriglError)
+
 
 def status_str(status: int) -> str:
     return lib.srigl_status_str(int(status)).decode()
@@ -229,6 +233,9 @@ def srigl_condensed_linear_fwd(x, B, d_in, W_c, idx, active, n_active, K, bias, 
     """algo None: the library's own entry point; otherwise the forced-algorithm entry point; act: the entry point with an
     activation in the epilogue (ACT_* codes); idx in a 16-bit container: the narrow-index entry point (no streaming copy);
     packed: the streaming copy of W_c / idx."""
+    if algo is None and tuning is None and y is not None:
+        _front.linear_fwd(x, B, d_in, W_c, idx, active, n_active, K, bias, d_out, y, seg, packed, act or ACT_NONE)
+        return
     tn = _tuning(tuning)
     tn_ref = ctypes.byref(tn) if tn is not None else None
     head = (_ptr(x), _dtype_code(x), int(B), int(d_in), _ptr(W_c), _dtype_code(W_c), _ptr(idx), _ptr(active), int(n_active), int(K),
@@ -240,8 +247,6 @@ def srigl_condensed_linear_fwd(x, B, d_in, W_c, idx, active, n_active, K, bias, 
     elif act is not None:
         _check(lib.srigl_condensed_linear_fwd_act(*head, _ptr(packed), int(act), int(algo or FWD_AUTO), tn_ref, _stream()),
                "srigl_condensed_linear_fwd_act")
-    elif algo is None and tuning is None:
-        _check(lib.srigl_condensed_linear_fwd(*head, _ptr(packed), _stream()), "srigl_condensed_linear_fwd")
     else:
         _check(lib.srigl_condensed_linear_fwd_algo(*head, _ptr(packed), int(algo or FWD_AUTO), tn_ref, _stream()),
                "srigl_condensed_linear_fwd_algo")
@@ -345,10 +350,7 @@ def srigl_mask_update_workspace_bytes(d_out: int, d_in: int) -> int:
 
 def srigl_mask_update(W, mask, grad, d_out, d_in, k, K_upd, gamma_percent, budget, mask_out, W_out, workspace, report):
     """report: int64[4] device tensor -> {k', remaining neurons, ablated by this update, pruned in step 6}."""
-    st = lib.srigl_mask_update(_ptr(W), _ptr(mask), _ptr(grad), int(d_out), int(d_in), int(k), int(K_upd), int(gamma_percent),
-                               int(budget), _ptr(mask_out), _ptr(W_out), _ptr(workspace),
-                               0 if workspace is None else workspace.numel() * workspace.element_size(), _ptr(report), _stream())
-    _check(st, "srigl_mask_update")
+    _front.mask_update(W, mask, grad, d_out, d_in, k, K_upd, gamma_percent, budget, mask_out, W_out, workspace, report)
 
 
 def srigl_launch_empty():

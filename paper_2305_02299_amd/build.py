@@ -1,4 +1,4 @@
-"""Builds libsrigl.so (the C-ABI library) in-tree with hipcc for gfx950."""
+"""Builds libsrigl.so (the C-ABI library) in-tree with hipcc for gfx950, and the CPython module in front of it with g++."""
 from __future__ import annotations
 
 import os
@@ -8,6 +8,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libsrigl.so")
+FRONT = os.path.join(PKG, "_front.so")
 SOURCES = ["condense.hip", "fwd.hip", "fwd_rowlane_f32.hip", "fwd_rowlane_bf16.hip", "fwd_rowlane_f32_i16.hip", "fwd_rowlane_bf16_i16.hip", "fwd_rowloop.hip", "structured.hip", "mlp.hip", "update.hip", "csr.hip"]
 
 HIPCC_FLAGS = [
@@ -33,17 +34,50 @@ def build(verbose: bool = False, defines=(), out: str = LIB) -> str:
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((obj, cmd, subprocess.Popen(cmd)))
+    if out == LIB:
+        procs.append(start_front(objdir, verbose))
     objs = []
     for obj, cmd, pr in procs:
         if pr.wait() != 0:
             raise subprocess.CalledProcessError(pr.returncode, cmd)
         objs.append(obj)
+    front = objs.pop() if out == LIB else None
     tmp = out + ".tmp.%d" % os.getpid()
     subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs)
     os.replace(tmp, out)
+    if front:
+        link_front(front)
+        objs.append(front)
     for o in objs:
         os.remove(o)
     return out
+
+
+def start_front(objdir: str, verbose: bool = False):
+    """Starts the compiler on the CPython module between torch tensors and libsrigl.so (host code only)."""
+    import sysconfig
+
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    obj = os.path.join(objdir, "front.%d.o" % os.getpid())
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", os.path.join(ROOT, "include")]
+    for inc in (os.path.join(tdir, "include"), os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+                os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_paths()["include"]):
+        cmd += ["-isystem", inc]
+    cmd += ["-c", os.path.join(CSRC, "front.cpp"), "-o", obj]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    return obj, cmd, subprocess.Popen(cmd)
+
+
+def link_front(obj: str) -> None:
+    import torch
+    tmp = FRONT + ".tmp.%d" % os.getpid()
+    subprocess.check_call(["g++", "-shared", "-o", tmp, obj, "-L", PKG, "-l:libsrigl.so", "-L",
+                           os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
+                           "-Wl,-rpath,$ORIGIN"])
+    os.replace(tmp, FRONT)
 
 
 if __name__ == "__main__":

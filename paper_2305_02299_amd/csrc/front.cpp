@@ -1,0 +1,243 @@
+// _front: the calls a program repeats (forward passes, condensing, connectivity updates) from Python into libsrigl without
+// ctypes.  A call on a small layer runs 3-4 us on the GPU; through ctypes its 17 arguments, the stream object and the output
+// allocation cost 10 us of host time, which was then what a stream of such calls ran at.  Here an argument is a pointer read
+// out of the tensor object, the stream comes from the thread's current one, and the output is allocated next to the launch.
+// Same names, argument order and checks as binding.py; all arithmetic stays in libsrigl.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <ATen/core/Tensor.h>
+#include <ATen/ops/empty.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include "srigl.h"
+
+namespace {
+
+PyObject* g_error = nullptr;   // SriglError(status, where)
+
+struct Failed {};              // a Python exception is set
+
+[[noreturn]] void fail(PyObject* type, const char* what) {
+    PyErr_SetString(type, what);
+    throw Failed{};
+}
+
+void check(srigl_status st, const char* where) {
+    if (st == SRIGL_OK) return;
+    PyObject* e = PyObject_CallFunction(g_error, "is", (int)st, where);
+    if (e) {
+        PyErr_SetObject(g_error, e);
+        Py_DECREF(e);
+    }
+    throw Failed{};
+}
+
+// The tensor in an argument, or null for None.
+const at::Tensor* tensor(PyObject* o) {
+    if (o == Py_None) return nullptr;
+    if (!THPVariable_Check(o)) fail(PyExc_TypeError, "a tensor is expected");
+    const at::Tensor& t = THPVariable_Unpack(o);
+    if (!t.is_cuda() || !t.is_contiguous()) fail(PyExc_AssertionError, "device-resident contiguous tensors only");
+    return &t;
+}
+template <typename T = void>
+T* pointer(PyObject* o) {
+    const at::Tensor* t = tensor(o);
+    return t ? static_cast<T*>(t->data_ptr()) : nullptr;
+}
+size_t bytes_of(PyObject* o) {
+    const at::Tensor* t = tensor(o);
+    return t ? (size_t)t->numel() * t->element_size() : 0;
+}
+long long integer(PyObject* o) {
+    const long long v = PyLong_AsLongLong(o);
+    if (v == -1 && PyErr_Occurred()) throw Failed{};
+    return v;
+}
+int32_t int32(PyObject* o) {
+    const long long v = integer(o);
+    if (v != (int32_t)v) fail(PyExc_OverflowError, "a 32-bit integer is expected");
+    return (int32_t)v;
+}
+// 16-bit containers carry bf16 bit patterns
+srigl_dtype dtype_of(const at::Tensor& t) {
+    const auto s = t.scalar_type();
+    if (s == at::kFloat) return SRIGL_F32;
+    if (s == at::kBFloat16 || s == at::kUInt16 || s == at::kShort) return SRIGL_BF16;
+    fail(PyExc_TypeError, "unsupported element type");
+}
+void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
+
+void need(Py_ssize_t n, Py_ssize_t want) {
+    if (n != want) fail(PyExc_TypeError, "wrong number of arguments");
+}
+
+// The tensor y names, or a new one [B, d_out] fp32 where x is; `out` becomes the reference to return.
+float* output(PyObject* y, const at::Tensor& x, int32_t B, int32_t d_out, PyObject*& out) {
+    if (y != Py_None) {
+        float* p = pointer<float>(y);
+        Py_INCREF(y);
+        out = y;
+        return p;
+    }
+    at::Tensor t = at::empty({B, d_out}, x.options().dtype(at::kFloat).requires_grad(false));
+    float* p = static_cast<float*>(t.data_ptr());
+    out = THPVariable_Wrap(std::move(t));
+    if (!out) throw Failed{};
+    return p;
+}
+
+// The rows of x, which must be [rows, d_in].
+int32_t rows_of(const at::Tensor& x, int32_t d_in) {
+    if (x.dim() != 2 || x.size(1) != d_in) fail(PyExc_AssertionError, "x is [batch, d_in]");
+    if (x.size(0) > INT32_MAX) fail(PyExc_OverflowError, "batch");
+    return (int32_t)x.size(0);
+}
+
+template <typename Body>
+PyObject* guarded(Body body) {
+    PyObject* out = nullptr;
+    try {
+        body(out);
+        return out;
+    } catch (const Failed&) {
+    } catch (const std::exception& e) {
+        if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());
+    }
+    Py_XDECREF(out);
+    return nullptr;
+}
+
+PyObject* set_error(PyObject*, PyObject* type) {
+    Py_XDECREF(g_error);
+    Py_INCREF(type);
+    g_error = type;
+    Py_RETURN_NONE;
+}
+
+// linear_fwd(x, B, d_in, W_c, idx, active, n_active, K, bias, d_out, y, seg, packed, act) -> y
+// B < 0: the rows of x, which must be [rows, d_in]; y None: allocated; idx in a 16-bit container: the narrow-index call.
+PyObject* linear_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    return guarded([&](PyObject*& out) {
+        need(n, 14);
+        const at::Tensor* x = tensor(a[0]);
+        const at::Tensor* W_c = tensor(a[3]);
+        const at::Tensor* idx = tensor(a[4]);
+        if (!x || !W_c || !idx) fail(PyExc_TypeError, "x, W_c and idx are tensors");
+        int32_t B = int32(a[1]);
+        const int32_t d_in = int32(a[2]), n_active = int32(a[6]), K = int32(a[7]), d_out = int32(a[9]);
+        if (B < 0) B = rows_of(*x, d_in);
+        const int32_t* active = pointer<int32_t>(a[5]);
+        const float* bias = pointer<float>(a[8]);
+        const uint16_t* seg = pointer<uint16_t>(a[11]);
+        const void* packed = pointer(a[12]);
+        const srigl_activation act = (srigl_activation)int32(a[13]);
+        float* y = output(a[10], *x, B, d_out, out);
+        const srigl_dtype xt = dtype_of(*x), wt = dtype_of(*W_c);
+        const void *xp = x->data_ptr(), *wp = W_c->data_ptr(), *ip = idx->data_ptr();
+        const bool narrow = idx->scalar_type() != at::kInt;
+        if (narrow && packed) fail(PyExc_AssertionError, "16-bit indices have no streaming copy");
+        void* st = stream();
+        srigl_status rc;
+        Py_BEGIN_ALLOW_THREADS
+        rc = narrow ? srigl_condensed_linear_fwd_idx16(xp, xt, B, d_in, wp, wt, static_cast<const uint16_t*>(ip), active, n_active, K, bias, d_out, y,
+                                                       seg, act, SRIGL_FWD_AUTO, nullptr, st)
+                    : srigl_condensed_linear_fwd_act(xp, xt, B, d_in, wp, wt, static_cast<const int32_t*>(ip), active, n_active, K, bias, d_out, y,
+                                                     seg, packed, act, SRIGL_FWD_AUTO, nullptr, st);
+        Py_END_ALLOW_THREADS
+        check(rc, narrow ? "srigl_condensed_linear_fwd_idx16" : "srigl_condensed_linear_fwd");
+    });
+}
+
+// structured_fwd(x, d_in, Wd, active, n_active, bias, d_out, y, workspace) -> y, in the library's tile and parts of d_in
+PyObject* structured_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    return guarded([&](PyObject*& out) {
+        need(n, 9);
+        const at::Tensor* x = tensor(a[0]);
+        const at::Tensor* Wd = tensor(a[2]);
+        if (!x || !Wd) fail(PyExc_TypeError, "x and Wd are tensors");
+        const int32_t d_in = int32(a[1]), n_active = int32(a[4]), d_out = int32(a[6]);
+        const int32_t B = rows_of(*x, d_in);
+        const int32_t* active = pointer<int32_t>(a[3]);
+        const float* bias = pointer<float>(a[5]);
+        void* ws = pointer(a[8]);
+        const size_t ws_bytes = bytes_of(a[8]);
+        float* y = output(a[7], *x, B, d_out, out);
+        const srigl_dtype xt = dtype_of(*x), wt = dtype_of(*Wd);
+        const void *xp = x->data_ptr(), *wp = Wd->data_ptr();
+        void* st = stream();
+        srigl_status rc;
+        Py_BEGIN_ALLOW_THREADS
+        rc = srigl_structured_linear_fwd_split(xp, xt, B, d_in, wp, wt, active, n_active, bias, d_out, y, SRIGL_TILE_AUTO, 0, ws, ws_bytes, st);
+        Py_END_ALLOW_THREADS
+        check(rc, "srigl_structured_linear_fwd_split");
+    });
+}
+
+// choose(x, d_in, n_active, K, d_out, W_c) -> whether the structured-only form is expected to be faster for the rows of x
+PyObject* choose(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    return guarded([&](PyObject*& out) {
+        need(n, 6);
+        const at::Tensor *x = tensor(a[0]), *W_c = tensor(a[5]);
+        if (!x || !W_c) fail(PyExc_TypeError, "x and W_c are tensors");
+        const int32_t d_in = int32(a[1]);
+        const bool s = srigl_choose_representation(rows_of(*x, d_in), d_in, int32(a[2]), int32(a[3]), int32(a[4]), dtype_of(*W_c), nullptr, nullptr) ==
+                       SRIGL_REPR_STRUCTURED;
+        out = PyBool_FromLong(s);
+    });
+}
+
+// split_bytes(x, d_in, n_active, d_out, W_c) -> workspace bytes structured_fwd needs for the rows of x
+PyObject* split_bytes(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    return guarded([&](PyObject*& out) {
+        need(n, 5);
+        const at::Tensor *x = tensor(a[0]), *W_c = tensor(a[4]);
+        if (!x || !W_c) fail(PyExc_TypeError, "x and W_c are tensors");
+        const int32_t d_in = int32(a[1]);
+        size_t bytes = 0;
+        check(srigl_structured_split_plan(rows_of(*x, d_in), d_in, int32(a[2]), int32(a[3]), dtype_of(*W_c), nullptr, &bytes),
+              "srigl_structured_split_plan");
+        out = PyLong_FromSize_t(bytes);
+    });
+}
+
+// mask_update(W, mask, grad, d_out, d_in, k, K_upd, gamma_percent, budget, mask_out, W_out, workspace, report)
+PyObject* mask_update(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    return guarded([&](PyObject*& out) {
+        need(n, 13);
+        const float* W = pointer<float>(a[0]);
+        const uint8_t* mask = pointer<uint8_t>(a[1]);
+        const float* grad = pointer<float>(a[2]);
+        const int32_t d_out = int32(a[3]), d_in = int32(a[4]), k = int32(a[5]), gamma = int32(a[7]);
+        const int64_t K_upd = integer(a[6]), budget = integer(a[8]);
+        uint8_t* mask_out = pointer<uint8_t>(a[9]);
+        float* W_out = pointer<float>(a[10]);
+        void* ws = pointer(a[11]);
+        const size_t ws_bytes = bytes_of(a[11]);
+        int64_t* report = pointer<int64_t>(a[12]);
+        void* st = stream();
+        srigl_status rc;
+        Py_BEGIN_ALLOW_THREADS
+        rc = srigl_mask_update(W, mask, grad, d_out, d_in, k, K_upd, gamma, budget, mask_out, W_out, ws, ws_bytes, report, st);
+        Py_END_ALLOW_THREADS
+        check(rc, "srigl_mask_update");
+        Py_INCREF(Py_None);
+        out = Py_None;
+    });
+}
+
+PyMethodDef methods[] = {
+    {"set_error", set_error, METH_O, "the exception type of a failed call"},
+    {"linear_fwd", (PyCFunction)(void (*)(void))linear_fwd, METH_FASTCALL, "srigl_condensed_linear_fwd"},
+    {"structured_fwd", (PyCFunction)(void (*)(void))structured_fwd, METH_FASTCALL, "srigl_structured_linear_fwd_split"},
+    {"choose", (PyCFunction)(void (*)(void))choose, METH_FASTCALL, "srigl_choose_representation"},
+    {"split_bytes", (PyCFunction)(void (*)(void))split_bytes, METH_FASTCALL, "srigl_structured_split_plan"},
+    {"mask_update", (PyCFunction)(void (*)(void))mask_update, METH_FASTCALL, "srigl_mask_update"},
+    {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_front", "calls into libsrigl", -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__front() { return PyModule_Create(&module); }

@@ -372,8 +372,6 @@ static srigl_status launch_klane_packed_t(const FwdArgs& a, int log2L, int rows_
     return hip_ok(hipGetLastError());
 }
 
-// Launch shape of the small-batch kernel, decided on the host.
-struct KlanePlan { int L, RB, rows_per_wg, direct; long long workgroups; bool ok; };
 static KlanePlan plan_klane(const FwdArgs& a, const srigl_fwd_tuning* t) {
     KlanePlan p{};
     p.ok = false;
@@ -414,11 +412,8 @@ static KlanePlan plan_klane(const FwdArgs& a, const srigl_fwd_tuning* t) {
     return p;
 }
 
-srigl_status launch_fwd_klane(const FwdArgs& a, const srigl_fwd_tuning* t, hipStream_t st) {
-    const int n_slots = a.active ? a.n_active + 1 : a.n_active;
-    if (a.B == 0 || n_slots == 0) return SRIGL_OK;
-    const KlanePlan kp = plan_klane(a, t);
-    if (!kp.ok || (t && (t->terms_from_copy < 0 || t->terms_from_copy > 1))) return SRIGL_ERR_UNSUPPORTED;
+static srigl_status launch_klane_plan(const FwdArgs& a, const KlanePlan& kp, const srigl_fwd_tuning* t, hipStream_t st) {
+    if (!kp.ok) return SRIGL_ERR_UNSUPPORTED;
     const int RB = kp.RB, rows_per_wg = kp.rows_per_wg, direct = kp.direct;
     const int log2L = ilog2_floor(kp.L);
     // The streaming copy (same launch shape, a lane's four terms in one unit) when a workgroup holds one batch row: there it
@@ -460,6 +455,12 @@ srigl_status launch_fwd_klane(const FwdArgs& a, const srigl_fwd_tuning* t, hipSt
     }
 #undef SRIGL_KLANE_G
 #undef SRIGL_KLANE
+}
+
+srigl_status launch_fwd_klane(const FwdArgs& a, const srigl_fwd_tuning* t, hipStream_t st) {
+    if (a.B == 0 || (a.active ? a.n_active + 1 : a.n_active) == 0) return SRIGL_OK;
+    if (t && (t->terms_from_copy < 0 || t->terms_from_copy > 1)) return SRIGL_ERR_UNSUPPORTED;
+    return launch_klane_plan(a, plan_klane(a, t), t, st);
 }
 
 constexpr int kRowlaneTwoRowsMinK = 32;
@@ -774,10 +775,13 @@ static RowlanePlan plan_rowlane(const FwdArgs& a, const srigl_fwd_tuning* t) {
 
 bool rowlane_supported(const FwdArgs& a, const srigl_fwd_tuning* t) { return plan_rowlane(a, t).ok; }
 
+static srigl_status launch_rowlane_plan(const FwdArgs& a, const RowlanePlan& p, hipStream_t st);
 srigl_status launch_fwd_rowlane(const FwdArgs& a, const srigl_fwd_tuning* t, hipStream_t st) {
     const int n_slots = a.active ? a.n_active + 1 : a.n_active;
     if (a.B == 0 || n_slots == 0) return SRIGL_OK;
-    const RowlanePlan p = plan_rowlane(a, t);
+    return launch_rowlane_plan(a, plan_rowlane(a, t), st);
+}
+static srigl_status launch_rowlane_plan(const FwdArgs& a, const RowlanePlan& p, hipStream_t st) {
     if (!p.ok) return SRIGL_ERR_UNSUPPORTED;
     if (a.idx_u16) return a.x_bf16 ? launch_rowlane_bf16_i16(a, p, st) : launch_rowlane_f32_i16(a, p, st);
     return a.x_bf16 ? launch_rowlane_bf16(a, p, st) : launch_rowlane_f32(a, p, st);
@@ -825,6 +829,30 @@ srigl_fwd_algo choose_fwd_algo(const FwdArgs& a) {
     const double rl = rowloop_estimate_us(a);
     if (rl >= 1e29) return base;
     return rl * kRowloopMargin < chunked_or_small_estimate_us(a) ? SRIGL_FWD_ROWLOOP : base;
+}
+
+// The library's own choice for a call: the kernel and its launch shape, remembered per thread for the sizes, types and
+// alignments they depend on.
+struct FwdDecision {
+    srigl_fwd_algo algo;
+    KlanePlan klane;
+    RowlanePlan rowlane;
+    RowloopPlan rowloop;
+};
+static const FwdDecision& decide_fwd(const FwdArgs& a) {
+    struct Key { int32_t B, d_in, n_active, K, d_out, flags; };
+    static thread_local DecisionCache<Key, FwdDecision, 64> cache;
+    const Key k = {a.B, a.d_in, a.n_active, a.K, a.d_out,
+                   (a.x_bf16 ? 1 : 0) | (a.idx_u16 ? 2 : 0) | (a.active ? 4 : 0) | (a.seg ? 8 : 0) | (a.packed ? 16 : 0) |
+                       (int)((reinterpret_cast<uintptr_t>(a.x) & 15) << 8) | (int)((reinterpret_cast<uintptr_t>(a.idx) & 3) << 12)};
+    return cache.get(k, [&] {
+        FwdDecision d{};
+        d.algo = choose_fwd_algo(a);
+        if (d.algo == SRIGL_FWD_KLANE) d.klane = plan_klane(a, nullptr);
+        if (d.algo == SRIGL_FWD_ROWLANE) d.rowlane = plan_rowlane(a, nullptr);
+        if (d.algo == SRIGL_FWD_ROWLOOP) d.rowloop = plan_rowloop(a, nullptr);
+        return d;
+    });
 }
 
 // stand-ins for the device arrays of a call of these sizes: the planner looks at their alignment and at which ones are
@@ -893,10 +921,11 @@ static srigl_status fwd_core(const void* x, srigl_dtype x_dtype, int32_t B, int3
         case SRIGL_FWD_AUTO: break;
         default: return SRIGL_ERR_INVALID_ARG;
     }
-    switch (choose_fwd_algo(a)) {
-        case SRIGL_FWD_ROWLANE: return launch_fwd_rowlane(a, nullptr, st);
-        case SRIGL_FWD_ROWLOOP: return launch_fwd_rowloop(a, nullptr, st);
-        case SRIGL_FWD_KLANE: return launch_fwd_klane(a, nullptr, st);
+    const FwdDecision& d = decide_fwd(a);
+    switch (d.algo) {
+        case SRIGL_FWD_ROWLANE: return launch_rowlane_plan(a, d.rowlane, st);
+        case SRIGL_FWD_ROWLOOP: return launch_rowloop_plan(a, d.rowloop, st);
+        case SRIGL_FWD_KLANE: return launch_klane_plan(a, d.klane, nullptr, st);
         default: return launch_fwd_generic(a, st);
     }
 }

@@ -18,12 +18,6 @@
 namespace srigl {
 
 constexpr int kRowloopReadAhead = 2;   // groups of LDS reads in flight ahead of the multiply-adds (walk_groups)
-struct RowloopPlan {
-    int H, NW, NG, KPRE, n_btiles, n_groups, out_off, span_cap, bt_major;
-    int rounds;
-    size_t lds;
-    bool ok;
-};
 
 template <int R, int H, int KPRE, typename XT, typename IT>
 __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, int B, int d_in, const XT* __restrict__ W_c,
@@ -319,7 +313,7 @@ static double rowloop_compare_us(const FwdArgs& a, const RowloopPlan& p) {
            1.75e-6 * a.B * a.d_out + (terms > 1.5e6 ? 0.29e-6 * terms : 0.0);
 }
 
-static RowloopPlan plan_rowloop(const FwdArgs& a, const srigl_fwd_tuning* t) {
+RowloopPlan plan_rowloop(const FwdArgs& a, const srigl_fwd_tuning* t) {
     RowloopPlan p{};
     p.ok = false;
     if (a.B <= 0 || a.n_active <= 0 || a.K <= 0) return p;
@@ -435,7 +429,10 @@ bool rowloop_plan_query(const FwdArgs& a, const srigl_fwd_tuning* t, srigl_fwd_p
 
 srigl_status launch_fwd_rowloop(const FwdArgs& a, const srigl_fwd_tuning* t, hipStream_t st) {
     if (a.B == 0 || a.n_active == 0) return SRIGL_OK;
-    const RowloopPlan p = plan_rowloop(a, t);
+    return launch_rowloop_plan(a, plan_rowloop(a, t), st);
+}
+
+srigl_status launch_rowloop_plan(const FwdArgs& a, const RowloopPlan& p, hipStream_t st) {
     if (!p.ok) return SRIGL_ERR_UNSUPPORTED;
     if (a.idx_u16) return a.x_bf16 ? launch_rowloop_x<uint16_t, uint16_t>(a, p, st) : launch_rowloop_x<float, uint16_t>(a, p, st);
     return a.x_bf16 ? launch_rowloop_x<uint16_t, int32_t>(a, p, st) : launch_rowloop_x<float, int32_t>(a, p, st);

@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <cstring>
 #include <stdint.h>
 
 #include "srigl.h"
@@ -135,6 +136,40 @@ srigl_status launch_rowlane_bf16(const FwdArgs& a, const RowlanePlan& p, hipStre
 srigl_status launch_rowlane_f32_i16(const FwdArgs& a, const RowlanePlan& p, hipStream_t st);
 srigl_status launch_rowlane_bf16_i16(const FwdArgs& a, const RowlanePlan& p, hipStream_t st);
 
+// Launch shape of the small-batch kernel, decided on the host.
+struct KlanePlan { int L, RB, rows_per_wg, direct; long long workgroups; bool ok; };
+// Launch shape of the whole-input batched kernel, decided on the host.
+struct RowloopPlan {
+    int H, NW, NG, KPRE, n_btiles, n_groups, out_off, span_cap, bt_major;
+    int rounds;
+    size_t lds;
+    bool ok;
+};
+
+// A small per-thread memory of host decisions (which kernel, which launch shape): walking the candidate shapes costs 1-9 us,
+// as much as the kernels of small layers run, and a caller repeats the same sizes.  Key: a struct of int32 fields without
+// padding.  Direct-mapped, N entries per thread, nothing allocated; a decision depends on its key only.
+template <typename Key, typename Value, int N>
+struct DecisionCache {
+    struct Entry { Key key; Value value; bool used; };
+    Entry entry[N] = {};
+    template <typename Decide>
+    const Value& get(const Key& k, Decide decide) {
+        static_assert(sizeof(Key) % 4 == 0, "a key is int32 fields");
+        uint32_t words[sizeof(Key) / 4], h = 0x9e3779b9u;
+        std::memcpy(words, &k, sizeof(Key));
+        for (uint32_t w : words) h = (h ^ w) * 0x85ebca6bu, h ^= h >> 15;
+        Entry& e = entry[h % N];
+        if (!e.used || std::memcmp(&e.key, &k, sizeof(Key)) != 0) {
+            e.used = false;
+            e.value = decide();
+            e.key = k;
+            e.used = true;
+        }
+        return e.value;
+    }
+};
+
 // Each returns SRIGL_OK, SRIGL_ERR_UNSUPPORTED (cannot run these sizes) or SRIGL_ERR_HIP.
 srigl_status launch_fwd_generic(const FwdArgs& a, hipStream_t st);
 srigl_status launch_fwd_klane(const FwdArgs& a, const srigl_fwd_tuning* t, hipStream_t st);
@@ -146,6 +181,8 @@ srigl_status launch_fwd_rowloop(const FwdArgs& a, const srigl_fwd_tuning* t, hip
 bool rowloop_supported(const FwdArgs& a, const srigl_fwd_tuning* t);
 double rowloop_estimate_us(const FwdArgs& a);
 bool rowloop_plan_query(const FwdArgs& a, const srigl_fwd_tuning* t, srigl_fwd_plan* plan);
+RowloopPlan plan_rowloop(const FwdArgs& a, const srigl_fwd_tuning* t);
+srigl_status launch_rowloop_plan(const FwdArgs& a, const RowloopPlan& p, hipStream_t st);
 srigl_fwd_algo choose_fwd_algo(const FwdArgs& a);
 // Estimated time (us) of the condensed forward call of these sizes in the kernel the library's own choice takes.
 double condensed_estimate_us(int B, int d_in, int n_active, int K, int d_out, bool bf16, bool has_active);

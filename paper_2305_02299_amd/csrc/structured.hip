@@ -562,15 +562,21 @@ srigl_status srigl_densify(const void* W_c, srigl_dtype w_dtype, const int32_t* 
 //                  + 4 B d_out / 4.5e6              (writing the result at HBM speed)
 srigl_representation srigl_choose_representation(int32_t B, int32_t d_in, int32_t n_active, int32_t K, int32_t d_out,
                                                  srigl_dtype dtype, float* est_condensed_us, float* est_structured_us) {
-    const double cond = condensed_estimate_us(B, d_in, n_active, K, d_out, dtype == SRIGL_BF16, n_active < d_out);
-    const bool f32 = dtype == SRIGL_F32;
-    const int elem = f32 ? 4 : 2;
-    double stru = 0.0;
-    choose_tile_and_split(B > 0 ? B : 1, n_active > 0 ? n_active : 1, d_in, d_out, f32, nullptr, nullptr, &stru);
-    if ((d_in * elem) % 16 != 0) stru = 1e30;   // the matrix-core kernel needs rows of whole 16-byte pieces
-    if (est_condensed_us) *est_condensed_us = (float)cond;
-    if (est_structured_us) *est_structured_us = (float)stru;
-    return stru < cond ? SRIGL_REPR_STRUCTURED : SRIGL_REPR_CONDENSED;
+    struct Key { int32_t B, d_in, n_active, K, d_out, dtype; };
+    struct Estimates { double cond, stru; };
+    static thread_local DecisionCache<Key, Estimates, 64> cache;
+    const Estimates e = cache.get(Key{B, d_in, n_active, K, d_out, (int32_t)dtype}, [&] {
+        Estimates v;
+        v.cond = condensed_estimate_us(B, d_in, n_active, K, d_out, dtype == SRIGL_BF16, n_active < d_out);
+        const bool f32 = dtype == SRIGL_F32;
+        v.stru = 0.0;
+        choose_tile_and_split(B > 0 ? B : 1, n_active > 0 ? n_active : 1, d_in, d_out, f32, nullptr, nullptr, &v.stru);
+        if ((d_in * (f32 ? 4 : 2)) % 16 != 0) v.stru = 1e30;   // the matrix-core kernel needs rows of whole 16-byte pieces
+        return v;
+    });
+    if (est_condensed_us) *est_condensed_us = (float)e.cond;
+    if (est_structured_us) *est_structured_us = (float)e.stru;
+    return e.stru < e.cond ? SRIGL_REPR_STRUCTURED : SRIGL_REPR_CONDENSED;
 }
 
 static srigl_status structured_core(const void* x, srigl_dtype x_dtype, int32_t B, int32_t d_in, const void* Wd, srigl_dtype w_dtype,

@@ -6,6 +6,7 @@ from dataclasses import dataclass
 import torch
 
 from . import binding as B_
+from . import _front
 
 
 @dataclass
@@ -48,23 +49,24 @@ class CondensedLinear:
     def forward(self, x: torch.Tensor, y: torch.Tensor | None = None, algo=None, tuning=None,
                 representation: str = "condensed") -> torch.Tensor:
         """representation: "condensed", "structured", or "auto" (the library's estimate for this batch size)."""
-        assert x.dim() == 2 and x.shape[1] == self.d_in
-        Bn = x.shape[0]
-        if y is None:
-            y = torch.empty((Bn, self.d_out), dtype=torch.float32, device=x.device)
         if representation == "auto":
-            representation = "structured" if self.choose(Bn) == B_.REPR_STRUCTURED else "condensed"
+            representation = "structured" if _front.choose(x, self.d_in, self.n_active, self.K, self.d_out, self.W_c) else "condensed"
         if representation == "structured":
-            _, need = B_.srigl_structured_split_plan(Bn, self.d_in, self.n_active, self.d_out, B_._dtype_code(self.W_c))
+            need = _front.split_bytes(x, self.d_in, self.n_active, self.d_out, self.W_c)
             if need and (self.split_ws is None or self.split_ws.numel() < need):
                 self.split_ws = torch.empty((need,), dtype=torch.uint8, device=x.device)
-            B_.srigl_structured_linear_fwd_split(x, Bn, self.d_in, self.dense_rows(), self.active, self.n_active, self.bias, self.d_out, y,
-                                                 self.split_ws if need else None)
-            return y
+            return _front.structured_fwd(x, self.d_in, self.dense_rows(), self.active, self.n_active, self.bias, self.d_out, y,
+                                         self.split_ws if need else None)
         assert representation == "condensed"
-        B_.srigl_condensed_linear_fwd(x, Bn, self.d_in, self.W_c, self.idx, self.active, self.n_active, self.K, self.bias,
-                                      self.d_out, y, self.seg, algo=algo, tuning=tuning,
-                                      packed=self.packed if self.idx.dtype == torch.int32 else None)
+        packed = self.packed if self.idx.dtype == torch.int32 else None
+        if algo is None and tuning is None:
+            return _front.linear_fwd(x, -1, self.d_in, self.W_c, self.idx, self.active, self.n_active, self.K, self.bias, self.d_out, y, self.seg,
+                                     packed, B_.ACT_NONE)
+        assert x.dim() == 2 and x.shape[1] == self.d_in
+        if y is None:
+            y = torch.empty((x.shape[0], self.d_out), dtype=torch.float32, device=x.device)
+        B_.srigl_condensed_linear_fwd(x, x.shape[0], self.d_in, self.W_c, self.idx, self.active, self.n_active, self.K, self.bias,
+                                      self.d_out, y, self.seg, algo=algo, tuning=tuning, packed=packed)
         return y
 
 
@@ -105,21 +107,18 @@ class CondensedMLP:
 
     def forward(self, x: torch.Tensor, y: torch.Tensor | None = None, hidden: torch.Tensor | None = None,
                 fused: bool | None = None) -> torch.Tensor:
-        Bn = x.shape[0]
         f, s = self.first, self.second
-        if hidden is None:
-            hidden = torch.empty((Bn, f.d_out), dtype=torch.float32, device=x.device)
-        if y is None:
-            y = torch.empty((Bn, s.d_out), dtype=torch.float32, device=x.device)
         if fused:      # both layers in one launch (batches up to 8; measured slower than two launches on MI355X: not the default)
+            Bn = x.shape[0]
+            if hidden is None:
+                hidden = torch.empty((Bn, f.d_out), dtype=torch.float32, device=x.device)
+            if y is None:
+                y = torch.empty((Bn, s.d_out), dtype=torch.float32, device=x.device)
             B_.srigl_condensed_mlp_fwd(x, Bn, f.d_in, f.packed, f.active, f.n_active, f.K, f.bias, f.d_out, self.act, hidden, s.packed,
                                        s.active, s.n_active, s.K, s.bias, s.d_out, y)
             return y
-        B_.srigl_condensed_linear_fwd(x, Bn, f.d_in, f.W_c, f.idx, f.active, f.n_active, f.K, f.bias, f.d_out, hidden, f.seg, act=self.act,
-                                      packed=f.packed)
-        B_.srigl_condensed_linear_fwd(hidden, Bn, s.d_in, s.W_c, s.idx, s.active, s.n_active, s.K, s.bias, s.d_out, y, s.seg,
-                                      packed=s.packed)
-        return y
+        hidden = _front.linear_fwd(x, -1, f.d_in, f.W_c, f.idx, f.active, f.n_active, f.K, f.bias, f.d_out, hidden, f.seg, f.packed, self.act)
+        return _front.linear_fwd(hidden, -1, s.d_in, s.W_c, s.idx, s.active, s.n_active, s.K, s.bias, s.d_out, y, s.seg, s.packed, B_.ACT_NONE)
 
 
 def fold_mlp(layer1: CondensedLinear, layer2: CondensedLinear, act: int) -> CondensedMLP:
