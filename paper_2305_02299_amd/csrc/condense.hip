@@ -4,10 +4,9 @@
 // ablated keeps exactly K incoming weights).  Condensed form: App. E (an [n][k] array of values and
 // an [n][k] array of column indices), with ablated neurons dropped (Sec. 4.4).
 //
-// All three steps are bandwidth work over the mask (1 byte per weight) and, for the compaction, the
-// dense weights: one wavefront owns one row, lanes read 4 consecutive mask bytes each so that a
-// wavefront covers 256 contiguous columns per iteration, and positions inside the row come from
-// ballots and prefix popcounts (no LDS, no atomics).
+// All steps are bandwidth work over the mask (1 byte per weight) and, for the compaction, the dense
+// weights: one wavefront owns one row, lanes read consecutive mask bytes, and positions inside the row
+// come from ballots and prefix popcounts (no atomics).
 #include "srigl_internal.h"
 
 #include <mutex>
@@ -91,17 +90,16 @@ __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_check_idx(const int32_
     for (int c = last + lane; c < seg_stride; c += kWave) sg[c] = (uint16_t)K;
 }
 
-// One workgroup.  Reads counts[], decides K, numbers the stored rows, writes slot[], active[], report.
+// One workgroup.  Reads counts[], decides K, writes the report of a check.
 // index_mode: counts hold K (valid) or -1 (bad); every valid row is "stored" even when K == 0.
 __global__ __launch_bounds__(1024) void k_scan_rows(const int32_t* __restrict__ counts, int n_rows, int K_expected,
-                                                    int index_mode, int cap_rows, int32_t* __restrict__ slot,
-                                                    int32_t* __restrict__ active, srigl_report* __restrict__ report) {
-    __shared__ int s_wave[16];
-    __shared__ int s_k, s_base, s_min;
+                                                    int index_mode, srigl_report* __restrict__ report) {
+    __shared__ int s_wave[16], s_wave_bad[16];
+    __shared__ int s_k, s_min;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
     const int nthreads = blockDim.x, nwaves = nthreads >> 6;
 
-    if (tid == 0) { s_min = 0x7fffffff; s_base = 0; }
+    if (tid == 0) s_min = 0x7fffffff;
     __syncthreads();
     int K = K_expected;
     if (K_expected < 0) {   // fan-in of the first non-empty row
@@ -118,127 +116,273 @@ __global__ __launch_bounds__(1024) void k_scan_rows(const int32_t* __restrict__ 
         if (tid == 0) s_min = 0x7fffffff;
         __syncthreads();
     }
-
-    // Every thread takes a run of consecutive rows: it counts its stored rows, the workgroup turns the counts into each thread's
-    // first slot (one scan inside every wavefront, one over the 16 wavefront totals), and the thread numbers its rows from there.
-    int n_bad = 0, first_bad = 0x7fffffff;
-    const int per_thread = (n_rows + nthreads - 1) / nthreads;
-    const int r0 = tid * per_thread, r1 = min(n_rows, r0 + per_thread);
-    auto classify = [&](int r, bool& stored, bool& bad) {
+    int n_stored = 0, n_bad = 0, first_bad = 0x7fffffff;
+    for (int r = tid; r < n_rows; r += nthreads) {
         const int c = counts[r];
-        if (index_mode) { stored = (c == K); bad = (c != K); }
-        else            { stored = (c == K) && (c > 0); bad = (c != 0) && (c != K); }
-    };
-    int mine = 0;
-    for (int r = r0; r < r1; ++r) {
-        bool stored, bad;
-        classify(r, stored, bad);
-        mine += stored ? 1 : 0;
+        const bool bad = index_mode ? c != K : (c != 0 && c != K);
+        n_stored += (c == K && (index_mode || c > 0)) ? 1 : 0;
         if (bad) { ++n_bad; first_bad = min(first_bad, r); }
     }
-    int incl = mine;   // inclusive scan over the lanes of this wavefront
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int up = __shfl_up(incl, off, kWave);
-        if (lane >= off) incl += up;
-    }
-    if (lane == kWave - 1) s_wave[wv] = incl;
-    __syncthreads();
-    int my = incl - mine;
-    for (int w = 0; w < wv; ++w) my += s_wave[w];
-    if (tid == nthreads - 1) s_base = my + mine;   // the last thread's end is the number of stored rows
-    for (int r = r0; r < r1; ++r) {
-        bool stored, bad;
-        classify(r, stored, bad);
-        if (slot) slot[r] = stored ? my : -1;
-        if (stored && active && my < cap_rows) active[my] = r;
-        my += stored ? 1 : 0;
-    }
-    __syncthreads();
     for (int off = 32; off > 0; off >>= 1) {
+        n_stored += __shfl_xor(n_stored, off, kWave);
         n_bad += __shfl_xor(n_bad, off, kWave);
         first_bad = min(first_bad, __shfl_xor(first_bad, off, kWave));
     }
-    if (lane == 0) s_wave[wv] = n_bad;
-    if (lane == 0 && first_bad != 0x7fffffff) atomicMin(&s_min, first_bad);
+    if (lane == 0) {
+        s_wave[wv] = n_stored;
+        s_wave_bad[wv] = n_bad;
+        if (first_bad != 0x7fffffff) atomicMin(&s_min, first_bad);
+    }
     __syncthreads();
     if (tid == 0) {
-        int t = 0;
-        for (int w = 0; w < nwaves; ++w) t += s_wave[w];
+        int n = 0, t = 0;
+        for (int w = 0; w < nwaves; ++w) { n += s_wave[w]; t += s_wave_bad[w]; }
         report->K = K;
-        report->n_active = s_base;
+        report->n_active = n;
         report->n_bad_rows = t;
         report->first_bad_row = (s_min == 0x7fffffff) ? -1 : s_min;
-        int st = SRIGL_OK;
-        if (t > 0) st = index_mode ? SRIGL_ERR_INDEX_RANGE : SRIGL_ERR_FANIN;
-        else if (active && s_base > cap_rows) st = SRIGL_ERR_CAPACITY;
-        report->status = st;
+        report->status = t > 0 ? (index_mode ? SRIGL_ERR_INDEX_RANGE : SRIGL_ERR_FANIN) : SRIGL_OK;
         report->reserved[0] = report->reserved[1] = report->reserved[2] = 0;
     }
 }
 
-// One wavefront per row: ordered stream compaction of the kept columns.
-// T = bit container of one weight (uint32_t for fp32, uint16_t for bf16).
-// With `packed` the same pass also writes the streaming copy (see PackedLayout): term `pos` of stored row s next to its
-// index, and the places behind the K-th term up to the next multiple of four get weight bits 0 and index 0.
+// ---- condense: two launches ----
+// k_row_flags reads the mask once and leaves two bits per row (stored: K kept weights; bad: neither 0 nor K).  k_compact_rows
+// numbers its rows from those bits by itself (a row's slot is the number of stored rows in front of it: 2 KB of bits for
+// 16384 rows, read beside the row's mask), so no launch of one workgroup stands between the two passes over the mask: that
+// scan took 5 us at 3072 rows and 31 us at 16384, 128 and 16 times what its bytes need.
+constexpr int kFlagRows = 8;       // rows (wavefronts) per workgroup of k_row_flags: one byte of each bit array
+constexpr int kMaskCols = 16;      // mask bytes per lane and load
+constexpr int kBatchCols = 4 * kWave * kMaskCols;   // columns whose mask bytes a wavefront has in flight
+
+// Kept columns among the kMaskCols columns this lane looks at: `first` (the first of them) and a bit per column.  Rows of any
+// alignment: the last lane with columns of the row reads the row's last 16 bytes and drops the ones its neighbour has.
+struct MaskPiece {
+    uint4 v;
+    int first, drop;   // drop: leading columns that are not this lane's (>= 16: none is)
+};
+__device__ __forceinline__ MaskPiece load_piece(const uint8_t* __restrict__ m, int col, int d_in) {
+    MaskPiece p;
+    p.first = min(col, d_in - kMaskCols);
+    p.drop = col - p.first;
+    __builtin_memcpy(&p.v, m + p.first, kMaskCols);   // one 16-byte load at any alignment
+    return p;
+}
+__device__ __forceinline__ uint32_t kept_bits(const MaskPiece& p) {
+    // bit 7 of each byte -> four adjacent bits
+    auto four = [](uint32_t w) { return ((nonzero_bytes(w) >> 7) * 0x10204080u) >> 28; };
+    const uint32_t all = four(p.v.x) | (four(p.v.y) << 4) | (four(p.v.z) << 8) | (four(p.v.w) << 12);
+    return p.drop >= kMaskCols ? 0u : (all >> p.drop) << p.drop;
+}
+// rows shorter than one piece
+__device__ __forceinline__ uint32_t kept_bits_short(const uint8_t* __restrict__ m, int col, int d_in) {
+    uint32_t b = 0;
+    if (col == 0)
+        for (int c = 0; c < d_in; ++c) b |= (m[c] != 0 ? 1u : 0u) << c;
+    return b;
+}
+
+__global__ __launch_bounds__(kFlagRows* kWave) void k_row_flags(const uint8_t* __restrict__ mask, int n_rows, int d_in, int K,
+                                                              uint8_t* __restrict__ stored, uint8_t* __restrict__ bad) {
+    __shared__ int cnt[kFlagRows];
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
+    const int r = blockIdx.x * kFlagRows + wv;
+    int c = 0;
+    if (r < n_rows) {
+        const uint8_t* m = mask + (size_t)r * d_in;
+        if (d_in >= kMaskCols) {
+            for (int col0 = 0; col0 < d_in; col0 += kBatchCols) {
+                MaskPiece p[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (col0 + u * kWave * kMaskCols < d_in) p[u] = load_piece(m, col0 + (u * kWave + lane) * kMaskCols, d_in);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (col0 + u * kWave * kMaskCols < d_in) c += __popc(kept_bits(p[u]));
+            }
+        } else {
+            c = __popc(kept_bits_short(m, lane, d_in));
+        }
+        for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, kWave);
+    }
+    if (lane == 0) cnt[wv] = r < n_rows ? c : 0;
+    __syncthreads();
+    if (threadIdx.x < kWave) {
+        const int n = lane < kFlagRows ? cnt[lane] : 0;
+        const uint64_t is_stored = __ballot(n > 0 && n == K), is_bad = __ballot(n != 0 && n != K);
+        if (lane == 0) {
+            stored[blockIdx.x] = (uint8_t)is_stored;
+            bad[blockIdx.x] = (uint8_t)is_bad;
+        }
+    }
+}
+
+// One wavefront per row: ordered stream compaction of the kept columns.  T = bit container of one weight (uint32_t for fp32,
+// uint16_t for bf16).  The row's kept columns are listed in LDS first (a lane's columns go to consecutive places behind those
+// of the lanes below it), then the lanes take the list's entries in turn, so that idx, W_c, the streaming copy (see
+// PackedLayout; places behind the K-th term up to the next multiple of four get weight bits 0 and index 0) and the weights'
+// gather all run over consecutive terms: three store instructions per 64 terms, where a lane storing its own columns issued
+// three per column position.  What bounds it: the mask a second time and the 128-byte lines of W that hold a kept weight (at
+// 5 % density nearly all of W).  4096 x 16384 bf16, 20 % of the rows ablated: 161 us for the whole call on the GPU before.
+// Workgroup 0 also writes the report.
 template <typename T>
 __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_compact_rows(const T* __restrict__ W, const uint8_t* __restrict__ mask,
                                                                      int d_out, int d_in, int K, int cap_rows,
-                                                                     const int32_t* __restrict__ slot, T* __restrict__ W_c,
-                                                                     int32_t* __restrict__ idx, uint16_t* __restrict__ seg,
-                                                                     int seg_stride, unsigned char* __restrict__ packed, PackedLayout pl) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int r = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
-    if (r >= d_out) return;
-    const int s = slot[r];
-    if (s < 0 || s >= cap_rows) return;   // ablated, invalid, or no room
-    const uint8_t* m = mask + (size_t)r * d_in;
-    const T* w = W + (size_t)r * d_in;
-    const bool aligned4 = ((reinterpret_cast<uintptr_t>(m) & 3) == 0);
-    T* wc = W_c + (size_t)s * K;
-    int32_t* ix = idx + (size_t)s * K;
-    uint16_t* sg = seg ? seg + (size_t)s * seg_stride : nullptr;
-    unsigned char* pk = packed ? packed + (size_t)s * pl.row_bytes() : nullptr;
+                                                                     const uint8_t* __restrict__ stored, const uint8_t* __restrict__ bad,
+                                                                     T* __restrict__ W_c, int32_t* __restrict__ idx, int32_t* __restrict__ active,
+                                                                     uint16_t* __restrict__ seg, int seg_stride,
+                                                                     unsigned char* __restrict__ packed, PackedLayout pl, int rows_per_block,
+                                                                     int list_cap, srigl_report* __restrict__ report) {
+    extern __shared__ uint16_t lists[];   // [kRowsPerBlock][list_cap]: kept columns of a row, counted from the batch's first column
+    __shared__ int part[kRowsPerBlock], part_bad[kRowsPerBlock], part_first[kRowsPerBlock];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid >> 6;
+    const int row0 = blockIdx.x * rows_per_block;
+    const uint32_t* const stored_w = reinterpret_cast<const uint32_t*>(stored);
+    const uint32_t* const bad_w = reinterpret_cast<const uint32_t*>(bad);
+    const int n_words = (d_out + 31) / 32;
 
-    int base = 0;   // kept columns seen in earlier iterations (same in every lane)
-    int chunk = 0;  // index of the next seg entry; one iteration covers 256 columns = 4 entries
-    for (int col0 = 0; col0 < d_in; col0 += kWave * 4, chunk += 4) {
-        const int col = col0 + lane * 4;
-        const uint32_t nz = (col < d_in) ? nonzero_bytes(load_mask4(m, col, d_in, aligned4)) : 0u;
-        uint64_t bal[4];
-        int before = 0, total = 0;
+    // the first row's mask goes out before the bits are waited for
+    MaskPiece ahead[4];
+    const bool pieces = d_in >= kMaskCols;
+    if (pieces && row0 + wv < d_out) {
+        const uint8_t* m = mask + (size_t)(row0 + wv) * d_in;
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            bal[p] = __ballot((nz >> (8 * p + 7)) & 1u);
-            before += (int)lanes_below(bal[p]);
-            total += __popcll(bal[p]);
-        }
-        if (sg && lane < 4 && chunk + lane < seg_stride) {
-            // entry for columns col0 + 64*lane ...: kept columns in the 16*lane lanes before it
-            const uint64_t lo = (lane == 0) ? 0ull : ((1ull << (16 * lane)) - 1ull);
-            int cnt = 0;
-#pragma unroll
-            for (int p = 0; p < 4; ++p) cnt += __popcll(bal[p] & lo);
-            sg[chunk + lane] = (uint16_t)(base + cnt);
-        }
-        int pos = base + before;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            if ((nz >> (8 * p + 7)) & 1u) {
-                if (pos < K) {
-                    const T wbits = w[col + p];
-                    ix[pos] = col + p;
-                    wc[pos] = wbits;
-                    if (pk) pl.store(pk, pos, (uint32_t)wbits, col + p);
-                }
-                ++pos;
-            }
-        }
-        base += total;
+        for (int u = 0; u < 4; ++u)
+            if (u * kWave * kMaskCols < d_in) ahead[u] = load_piece(m, (u * kWave + lane) * kMaskCols, d_in);
     }
-    if (sg)
-        for (int c = chunk + lane; c < seg_stride; c += kWave) sg[c] = (uint16_t)base;
-    if (pk)
-        for (int t = K + lane; t < pl.terms; t += kWave) pl.store(pk, t, 0u, 0);
+
+    // (a workgroup's four rows share a byte)
+    const uint32_t own_byte = row0 < d_out ? stored[row0 >> 3] : 0u;
+    auto stored_byte = [&](int r) { return (r >> 3) == (row0 >> 3) ? own_byte : (uint32_t)stored[r >> 3]; };
+
+    // bits of the rows [0, row0); workgroup 0 counts all rows, and the bad ones, for the report
+    const bool reports = blockIdx.x == 0;
+    const int upto = reports ? n_words : (row0 + 31) / 32;
+    int below = 0, n_bad = 0, first_bad = 0x7fffffff;
+    for (int w = tid; w < upto; w += kRowsPerBlock * kWave) {
+        uint32_t b = stored_w[w];
+        const int left = (reports ? d_out : row0) - 32 * w;   // rows of this word that count
+        if (left < 32) b &= (1u << left) - 1u;
+        below += __popc(b);
+        if (reports) {
+            uint32_t q = bad_w[w];
+            if (left < 32) q &= (1u << left) - 1u;
+            n_bad += __popc(q);
+            if (q != 0 && first_bad == 0x7fffffff) first_bad = 32 * w + __ffs(q) - 1;
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) below += __shfl_xor(below, off, kWave);
+    if (reports) {
+        for (int off = 32; off > 0; off >>= 1) {
+            n_bad += __shfl_xor(n_bad, off, kWave);
+            first_bad = min(first_bad, __shfl_xor(first_bad, off, kWave));
+        }
+    }
+    if (lane == 0) { part[wv] = below; part_bad[wv] = n_bad; part_first[wv] = first_bad; }
+    __syncthreads();
+    int base_slot = part[0] + part[1] + part[2] + part[3];
+    static_assert(kRowsPerBlock == 4, "four parts");
+    if (reports) {
+        if (tid == 0) {
+            const int nb = part_bad[0] + part_bad[1] + part_bad[2] + part_bad[3];
+            const int fb = min(min(part_first[0], part_first[1]), min(part_first[2], part_first[3]));
+            report->K = K;
+            report->n_active = base_slot;
+            report->n_bad_rows = nb;
+            report->first_bad_row = nb ? fb : -1;
+            report->reserved[0] = report->reserved[1] = report->reserved[2] = 0;
+            // (the status goes last: a caller with the report in host memory may be waiting for it)
+            const int st = nb > 0 ? SRIGL_ERR_FANIN : (active && base_slot > cap_rows ? SRIGL_ERR_CAPACITY : SRIGL_OK);
+            __hip_atomic_store(&report->status, st, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        base_slot = 0;
+    }
+    if (K == 0 || cap_rows == 0) return;
+
+    uint16_t* const list = lists + wv * list_cap;
+    for (int i = wv; i < rows_per_block; i += kRowsPerBlock) {
+        const int r = row0 + i;
+        if (r >= d_out) return;
+        if (((stored_byte(r) >> (r & 7)) & 1) == 0) continue;   // ablated or invalid
+        // stored rows among the workgroup's first i
+        int s = base_slot;
+        for (int q = row0; q < r; q += 8 - (q & 7)) {
+            const uint32_t b = stored_byte(q) >> (q & 7);
+            const int n = min(8 - (q & 7), r - q);
+            s += __popc(b & ((1u << n) - 1u));
+        }
+        if (s >= cap_rows) continue;   // no room
+        if (lane == 0) active[s] = r;
+        const uint8_t* m = mask + (size_t)r * d_in;
+        const T* w = W + (size_t)r * d_in;
+        T* wc = W_c + (size_t)s * K;
+        int32_t* ix = idx + (size_t)s * K;
+        uint16_t* sg = seg ? seg + (size_t)s * seg_stride : nullptr;
+        unsigned char* pk = packed ? packed + (size_t)s * pl.row_bytes() : nullptr;
+
+        int base = 0;   // kept columns of the batches before (same in every lane)
+        for (int col0 = 0; col0 < d_in; col0 += kBatchCols) {
+            if (pieces && (i != wv || col0 != 0)) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (col0 + u * kWave * kMaskCols < d_in) ahead[u] = load_piece(m, col0 + (u * kWave + lane) * kMaskCols, d_in);
+            }
+            int in_batch = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int col = col0 + (u * kWave + lane) * kMaskCols;
+                if (col0 + u * kWave * kMaskCols >= d_in) break;
+                uint32_t bits = pieces ? kept_bits(ahead[u]) : kept_bits_short(m, col, d_in);
+                const int first = (pieces ? ahead[u].first : 0) - col0;
+                // kept columns in the lanes below, and in all lanes: bit planes of the lanes' counts (0..16)
+                const uint32_t n = __popc(bits);
+                int before = 0, total = 0;
+#pragma unroll
+                for (int p = 0; p < 5; ++p) {
+                    const uint64_t bal = __ballot((n >> p) & 1u);
+                    before += (int)lanes_below(bal) << p;
+                    total += __popcll(bal) << p;
+                }
+                // every fourth lane starts a 64-column segment
+                const int entry = col / kSegCols;
+                if (sg && (lane & 3) == 0 && entry < seg_stride) sg[entry] = (uint16_t)(base + in_batch + before);
+                int pos = in_batch + before;
+                while (bits) {
+                    if (base + pos < K && pos < list_cap) list[pos] = (uint16_t)(first + __ffs(bits) - 1);
+                    ++pos;
+                    bits &= bits - 1;
+                }
+                in_batch += total;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const int n_list = min(min(in_batch, K - base), list_cap);
+            for (int t0 = 0; t0 < n_list; t0 += 4 * kWave) {
+                int col[4];
+                T v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) col[u] = col0 + list[min(t0 + u * kWave + lane, n_list - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = w[col[u]];   // (places past the end re-read the last column)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int t = t0 + u * kWave + lane;
+                    if (t < n_list) {
+                        ix[base + t] = col[u];
+                        wc[base + t] = v[u];
+                        if (pk) pl.store(pk, base + t, (uint32_t)v[u], col[u]);
+                    }
+                }
+            }
+            base += in_batch;
+            __builtin_amdgcn_wave_barrier();   // the list is rewritten by the next batch
+        }
+        if (sg)   // entries behind the last lane that had columns
+            for (int c = (d_in + kMaskCols * kWave - 1) / (kMaskCols * kWave) * (kMaskCols * kWave) / kSegCols + lane; c < seg_stride; c += kWave) sg[c] = (uint16_t)base;
+        if (pk)
+            for (int t = K + lane; t < pl.terms; t += kWave) pl.store(pk, t, 0u, 0);
+    }
 }
 
 // The streaming copy from the canonical arrays: one thread per term, padding included.
@@ -299,8 +443,7 @@ srigl_status srigl_check_fanin(const uint8_t* mask, const int32_t* idx, int32_t 
         if (mask) hipLaunchKernelGGL(k_row_count, dim3(blocks), dim3(kRowsPerBlock * kWave), 0, st, mask, n_rows, d_in, counts);
         else      hipLaunchKernelGGL(k_check_idx, dim3(blocks), dim3(kRowsPerBlock * kWave), 0, st, idx, n_rows, K_expected, d_in, counts, seg, srigl_seg_stride(d_in));
     }
-    hipLaunchKernelGGL(k_scan_rows, dim3(1), dim3(1024), 0, st, counts, n_rows, K_expected, idx ? 1 : 0, n_rows,
-                       (int32_t*)nullptr, (int32_t*)nullptr, report_dev);
+    hipLaunchKernelGGL(k_scan_rows, dim3(1), dim3(1024), 0, st, counts, n_rows, K_expected, idx ? 1 : 0, report_dev);
     return hip_ok(hipGetLastError());
 }
 
@@ -318,22 +461,26 @@ static srigl_status condense_core(const void* W, srigl_dtype w_dtype, const uint
         if (reinterpret_cast<uintptr_t>(packed) % 16 != 0) return SRIGL_ERR_INVALID_ARG;
         if (packed_bytes < srigl_packed_bytes(cap_rows, K, d_in, w_dtype)) return SRIGL_ERR_CAPACITY;
     }
-    int32_t* counts = static_cast<int32_t*>(workspace);
-    int32_t* slot = counts + d_out;
-    const int blocks = (d_out + kRowsPerBlock - 1) / kRowsPerBlock;
-    if (d_out > 0) hipLaunchKernelGGL(k_row_count, dim3(blocks), dim3(kRowsPerBlock * kWave), 0, st, mask, d_out, d_in, counts);
-    hipLaunchKernelGGL(k_scan_rows, dim3(1), dim3(1024), 0, st, counts, d_out, K, 0, cap_rows, slot, active, report_dev);
-    if (d_out > 0 && cap_rows > 0 && K > 0) {
-        const int ss = srigl_seg_stride(d_in);
-        if (w_dtype == SRIGL_F32)
-            hipLaunchKernelGGL(k_compact_rows<uint32_t>, dim3(blocks), dim3(kRowsPerBlock * kWave), 0, st,
-                               static_cast<const uint32_t*>(W), mask, d_out, d_in, K, cap_rows, slot,
-                               static_cast<uint32_t*>(W_c), idx, seg, ss, static_cast<unsigned char*>(packed), pl);
-        else
-            hipLaunchKernelGGL(k_compact_rows<uint16_t>, dim3(blocks), dim3(kRowsPerBlock * kWave), 0, st,
-                               static_cast<const uint16_t*>(W), mask, d_out, d_in, K, cap_rows, slot,
-                               static_cast<uint16_t*>(W_c), idx, seg, ss, static_cast<unsigned char*>(packed), pl);
-    }
+    // two bits per row in the workspace (8 bytes per row of room)
+    uint8_t* stored = static_cast<uint8_t*>(workspace);
+    uint8_t* bad = stored ? stored + (size_t)(d_out + 127) / 128 * 16 : nullptr;
+    const int flag_blocks = (d_out + kFlagRows - 1) / kFlagRows;
+    if (d_out > 0) hipLaunchKernelGGL(k_row_flags, dim3(flag_blocks), dim3(kFlagRows * kWave), 0, st, mask, d_out, d_in, K, stored, bad);
+    // one row per wavefront; layers of more than 131072 rows several, so that the bits every workgroup reads stay a small part
+    int rows_per_block = kRowsPerBlock;
+    while ((d_out + rows_per_block - 1) / rows_per_block > 32768) rows_per_block *= 2;
+    const int blocks = d_out > 0 ? (d_out + rows_per_block - 1) / rows_per_block : 1;   // (no rows: workgroup 0 writes the report)
+    const int list_cap = (K < kBatchCols ? K : kBatchCols) + 1;
+    const size_t lds = sizeof(uint16_t) * kRowsPerBlock * (size_t)list_cap;
+    const int ss = srigl_seg_stride(d_in);
+    if (w_dtype == SRIGL_F32)
+        hipLaunchKernelGGL(k_compact_rows<uint32_t>, dim3(blocks), dim3(kRowsPerBlock * kWave), lds, st, static_cast<const uint32_t*>(W), mask, d_out,
+                           d_in, K, cap_rows, stored, bad, static_cast<uint32_t*>(W_c), idx, active, seg, ss,
+                           static_cast<unsigned char*>(packed), pl, rows_per_block, list_cap, report_dev);
+    else
+        hipLaunchKernelGGL(k_compact_rows<uint16_t>, dim3(blocks), dim3(kRowsPerBlock * kWave), lds, st, static_cast<const uint16_t*>(W), mask, d_out,
+                           d_in, K, cap_rows, stored, bad, static_cast<uint16_t*>(W_c), idx, active, seg, ss,
+                           static_cast<unsigned char*>(packed), pl, rows_per_block, list_cap, report_dev);
     return hip_ok(hipGetLastError());
 }
 

@@ -6,6 +6,8 @@
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
+#include <cstdio>
+
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
@@ -228,12 +230,77 @@ PyObject* mask_update(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
+// condense(W, mask, K, want_seg, want_packed) -> (n_active, W_c, idx, active, seg, packed), every array cut to the stored rows
+// (active: None when no neuron is ablated).  Waits for the report only, which the kernels write straight into pinned host
+// memory (no copy launch, no stream synchronisation); the arrays are complete in stream order like any other result.
+PyObject* condense(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
+    return guarded([&](PyObject*& out) {
+        need(n_args, 5);
+        const at::Tensor *W = tensor(a[0]), *mask = tensor(a[1]);
+        if (!W || !mask || mask->dim() != 2) fail(PyExc_TypeError, "W and a two-dimensional mask");
+        if (mask->size(0) > INT32_MAX || mask->size(1) > INT32_MAX) fail(PyExc_OverflowError, "mask");
+        const int32_t d_out = (int32_t)mask->size(0), d_in = (int32_t)mask->size(1), K = int32(a[2]);
+        const bool want_seg = PyObject_IsTrue(a[3]) == 1, want_packed = PyObject_IsTrue(a[4]) == 1;
+        const srigl_dtype wt = dtype_of(*W);
+        const auto like = W->options().requires_grad(false);
+        const int64_t k = K > 0 ? K : 0;
+        at::Tensor W_c = at::empty({d_out, k}, like), idx = at::empty({d_out, k}, like.dtype(at::kInt)), active = at::empty({d_out}, like.dtype(at::kInt));
+        at::Tensor seg, packed;
+        if (want_seg) seg = at::empty({d_out, srigl_seg_stride(d_in)}, like.dtype(at::kShort));
+        const size_t packed_bytes = srigl_packed_bytes(d_out, K, d_in, wt);
+        if (want_packed) packed = at::empty({(int64_t)(packed_bytes > 16 ? packed_bytes : 16)}, like.dtype(at::kByte));
+        const size_t ws_bytes = srigl_workspace_bytes(d_out);
+        at::Tensor ws = at::empty({(int64_t)ws_bytes}, like.dtype(at::kByte));
+        at::Tensor report = at::empty({(int64_t)sizeof(srigl_report)}, at::TensorOptions().dtype(at::kByte).pinned_memory(true));
+        srigl_report* rep = static_cast<srigl_report*>(report.data_ptr());
+        constexpr int32_t kPending = -7;
+        __atomic_store_n(&rep->status, kPending, __ATOMIC_RELEASE);
+        const c10::hip::HIPStream st = c10::hip::getCurrentHIPStream();
+        void *wcp = W_c.data_ptr(), *sgp = want_seg ? seg.data_ptr() : nullptr, *pkp = want_packed ? packed.data_ptr() : nullptr;
+        srigl_status rc;
+        int32_t status = kPending;
+        Py_BEGIN_ALLOW_THREADS
+        rc = srigl_condense(W->data_ptr(), wt, static_cast<const uint8_t*>(mask->data_ptr()), d_out, d_in, K, d_out, wcp,
+                            static_cast<int32_t*>(idx.data_ptr()), static_cast<int32_t*>(active.data_ptr()), static_cast<uint16_t*>(sgp), pkp,
+                            want_packed ? (size_t)packed.numel() : 0, ws.data_ptr(), ws_bytes, rep, st.stream());
+        // (the stream is asked now and then, so that the wait ends whatever happened to the launches)
+        for (unsigned polls = 1; rc == SRIGL_OK; ++polls) {
+            status = __atomic_load_n(&rep->status, __ATOMIC_ACQUIRE);
+            if (status != kPending) break;
+            bool idle = false;
+            if (polls % 1024 == 0) {
+                try { idle = st.query(); } catch (...) { rc = SRIGL_ERR_HIP; }
+            }
+            if (idle) {
+                status = __atomic_load_n(&rep->status, __ATOMIC_ACQUIRE);
+                if (status == kPending) rc = SRIGL_ERR_HIP;
+                break;
+            }
+        }
+        Py_END_ALLOW_THREADS
+        check(rc, "srigl_condense");
+        if (status != SRIGL_OK) {
+            char where[64];
+            snprintf(where, sizeof(where), "srigl_condense (first bad row %d)", (int)rep->first_bad_row);
+            check((srigl_status)status, where);
+        }
+        const int64_t n = rep->n_active;
+        auto cut = [&](at::Tensor& t, int64_t rows) { return THPVariable_Wrap(rows == t.size(0) ? std::move(t) : t.narrow(0, 0, rows)); };
+        auto none = [] { Py_INCREF(Py_None); return Py_None; };
+        PyObject* parts[5] = {cut(W_c, n), cut(idx, n), n == d_out ? none() : cut(active, n), want_seg ? cut(seg, n) : none(),
+                              want_packed && n && K ? cut(packed, (int64_t)srigl_packed_bytes((int32_t)n, K, d_in, wt)) : none()};
+        out = Py_BuildValue("(LNNNNN)", (long long)n, parts[0], parts[1], parts[2], parts[3], parts[4]);
+        if (!out) throw Failed{};
+    });
+}
+
 PyMethodDef methods[] = {
     {"set_error", set_error, METH_O, "the exception type of a failed call"},
     {"linear_fwd", (PyCFunction)(void (*)(void))linear_fwd, METH_FASTCALL, "srigl_condensed_linear_fwd"},
     {"structured_fwd", (PyCFunction)(void (*)(void))structured_fwd, METH_FASTCALL, "srigl_structured_linear_fwd_split"},
     {"choose", (PyCFunction)(void (*)(void))choose, METH_FASTCALL, "srigl_choose_representation"},
     {"split_bytes", (PyCFunction)(void (*)(void))split_bytes, METH_FASTCALL, "srigl_structured_split_plan"},
+    {"condense", (PyCFunction)(void (*)(void))condense, METH_FASTCALL, "srigl_condense into new tensors"},
     {"mask_update", (PyCFunction)(void (*)(void))mask_update, METH_FASTCALL, "srigl_mask_update"},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_front", "calls into libsrigl", -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -72,27 +72,9 @@ class CondensedLinear:
 
 def condense_layer(W: torch.Tensor, mask: torch.Tensor, K: int, bias: torch.Tensor | None = None,
                    want_seg: bool = True, want_packed: bool = True) -> CondensedLinear:
-    """srigl_condense on device tensors; reads the report back (one synchronisation) to size the result."""
-    d_out, d_in = mask.shape
-    dev = W.device
-    W_c = torch.empty((d_out, K), dtype=W.dtype, device=dev)
-    idx = torch.empty((d_out, K), dtype=torch.int32, device=dev)
-    active = torch.empty((d_out,), dtype=torch.int32, device=dev)
-    ss = B_.srigl_seg_stride(d_in)
-    seg = torch.empty((d_out, ss), dtype=torch.int16, device=dev) if want_seg else None
-    ws = B_.new_workspace(d_out, dev)
-    rep = B_.new_report(dev)
-    code = B_._dtype_code(W)
-    packed = torch.empty((max(B_.srigl_packed_bytes(d_out, K, d_in, code), 16),), dtype=torch.uint8, device=dev) if want_packed else None
-    B_.srigl_condense(W, mask, d_out, d_in, K, d_out, W_c, idx, active, seg, ws, rep, packed=packed)
-    r = B_.read_report(rep)
-    if r["status"] != B_.OK:
-        raise B_.SriglError(r["status"], "srigl_condense (first bad row %d)" % r["first_bad_row"])
-    n = r["n_active"]
-    return CondensedLinear(d_in, d_out, K, n, W_c[:n].contiguous(), idx[:n].contiguous(),
-                           None if n == d_out else active[:n].contiguous(), bias,
-                           seg[:n].contiguous() if want_seg else None,
-                           packed=packed[:B_.srigl_packed_bytes(n, K, d_in, code)] if want_packed and n and K else None)
+    """srigl_condense on device tensors; waits for the report (how many rows are stored) to size the result."""
+    n, W_c, idx, active, seg, packed = _front.condense(W, mask, K, want_seg, want_packed)
+    return CondensedLinear(mask.shape[1], mask.shape[0], K, n, W_c, idx, active, bias, seg, packed=packed)
 
 
 @dataclass
