@@ -233,7 +233,7 @@ def srigl_condensed_linear_fwd(x, B, d_in, W_c, idx, active, n_active, K, bias, 
     """algo None: the library's own entry point; otherwise the forced-algorithm entry point; act: the entry point with an
     activation in the epilogue (ACT_* codes); idx in a 16-bit container: the narrow-index entry point (no streaming copy);
     packed: the streaming copy of W_c / idx."""
-    if algo is None and tuning is None and y is not None:
+    if algo is None and tuning is None and y is not None and (packed is None or idx.dtype == torch.int32):
         _front.linear_fwd(x, B, d_in, W_c, idx, active, n_active, K, bias, d_out, y, seg, packed, act or ACT_NONE)
         return
     tn = _tuning(tuning)

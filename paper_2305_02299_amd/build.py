@@ -75,7 +75,7 @@ def link_front(obj: str) -> None:
     import torch
     tmp = FRONT + ".tmp.%d" % os.getpid()
     subprocess.check_call(["g++", "-shared", "-o", tmp, obj, "-L", PKG, "-l:libsrigl.so", "-L",
-                           os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
+                           os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python", "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip",
                            "-Wl,-rpath,$ORIGIN"])
     os.replace(tmp, FRONT)
 

@@ -9,6 +9,7 @@
 #include <cstdio>
 
 #include <ATen/core/Tensor.h>
+#include <ATen/hip/EmptyTensor.h>
 #include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -76,6 +77,11 @@ void need(Py_ssize_t n, Py_ssize_t want) {
     if (n != want) fail(PyExc_TypeError, "wrong number of arguments");
 }
 
+// A new tensor where `like` is, straight from the caching allocator (the dispatcher's way costs another 0.3 us).
+at::Tensor fresh(at::IntArrayRef size, at::ScalarType type, const at::Tensor& like) {
+    return at::Tensor(at::detail::empty_cuda(size, type, like.device(), std::nullopt));
+}
+
 // The tensor y names, or a new one [B, d_out] fp32 where x is; `out` becomes the reference to return.
 float* output(PyObject* y, const at::Tensor& x, int32_t B, int32_t d_out, PyObject*& out) {
     if (y != Py_None) {
@@ -84,7 +90,7 @@ float* output(PyObject* y, const at::Tensor& x, int32_t B, int32_t d_out, PyObje
         out = y;
         return p;
     }
-    at::Tensor t = at::empty({B, d_out}, x.options().dtype(at::kFloat).requires_grad(false));
+    at::Tensor t = fresh({B, d_out}, at::kFloat, x);
     float* p = static_cast<float*>(t.data_ptr());
     out = THPVariable_Wrap(std::move(t));
     if (!out) throw Failed{};
@@ -139,8 +145,7 @@ PyObject* linear_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         float* y = output(a[10], *x, B, d_out, out);
         const srigl_dtype xt = dtype_of(*x), wt = dtype_of(*W_c);
         const void *xp = x->data_ptr(), *wp = W_c->data_ptr(), *ip = idx->data_ptr();
-        const bool narrow = idx->scalar_type() != at::kInt;
-        if (narrow && packed) fail(PyExc_AssertionError, "16-bit indices have no streaming copy");
+        const bool narrow = idx->scalar_type() != at::kInt;   // (16-bit indices are read without the streaming copy)
         void* st = stream();
         srigl_status rc;
         Py_BEGIN_ALLOW_THREADS
@@ -242,15 +247,14 @@ PyObject* condense(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
         const int32_t d_out = (int32_t)mask->size(0), d_in = (int32_t)mask->size(1), K = int32(a[2]);
         const bool want_seg = PyObject_IsTrue(a[3]) == 1, want_packed = PyObject_IsTrue(a[4]) == 1;
         const srigl_dtype wt = dtype_of(*W);
-        const auto like = W->options().requires_grad(false);
         const int64_t k = K > 0 ? K : 0;
-        at::Tensor W_c = at::empty({d_out, k}, like), idx = at::empty({d_out, k}, like.dtype(at::kInt)), active = at::empty({d_out}, like.dtype(at::kInt));
+        at::Tensor W_c = fresh({d_out, k}, W->scalar_type(), *W), idx = fresh({d_out, k}, at::kInt, *W), active = fresh({d_out}, at::kInt, *W);
         at::Tensor seg, packed;
-        if (want_seg) seg = at::empty({d_out, srigl_seg_stride(d_in)}, like.dtype(at::kShort));
+        if (want_seg) seg = fresh({d_out, srigl_seg_stride(d_in)}, at::kShort, *W);
         const size_t packed_bytes = srigl_packed_bytes(d_out, K, d_in, wt);
-        if (want_packed) packed = at::empty({(int64_t)(packed_bytes > 16 ? packed_bytes : 16)}, like.dtype(at::kByte));
+        if (want_packed) packed = fresh({(int64_t)(packed_bytes > 16 ? packed_bytes : 16)}, at::kByte, *W);
         const size_t ws_bytes = srigl_workspace_bytes(d_out);
-        at::Tensor ws = at::empty({(int64_t)ws_bytes}, like.dtype(at::kByte));
+        at::Tensor ws = fresh({(int64_t)ws_bytes}, at::kByte, *W);
         at::Tensor report = at::empty({(int64_t)sizeof(srigl_report)}, at::TensorOptions().dtype(at::kByte).pinned_memory(true));
         srigl_report* rep = static_cast<srigl_report*>(report.data_ptr());
         constexpr int32_t kPending = -7;
