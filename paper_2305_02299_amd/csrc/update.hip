@@ -4,55 +4,53 @@
 // include/srigl.h next to srigl_mask_update.
 //
 // Every ranking is a selection of the K largest of unique 64-bit keys, (magnitude bits, position): equal magnitudes are
-// ordered by position, so the selected set is unique and no sort is needed.  Layer-wide selections (steps 3 and 6) find the
-// K-th largest key by a most-significant-digit-first radix walk: passes of (histogram of one digit over the elements that
-// match the prefix found so far, then the digit that holds the K-th key), ended as soon as every key of the chosen digit is
-// wanted.  The top bit of every key is zero, so the digits are bits 62-55, 54-47, ..., 14-7 and 6-0: two passes fix the
-// exponent and 8 mantissa bits of the threshold; the third pass also copies the keys that match those 16 bits (a fraction
-// of a percent of a layer with real-valued contents) into a candidate list, and the remaining passes read that list
-// instead of the layer (a list that would overflow is dropped and the passes stay on the layer).  The two selections of step 3 share their passes, and every workgroup of a pass picks the previous pass's byte for
-// itself from that pass's own counters (no pick launches, no device-wide fences); step 6 reuses step 3's answer when no
-// neuron was ablated.  Row-wise selections (step 7) do the same walk inside one workgroup per row, on keys held in registers.
+// ordered by position, so the selected set is unique and no sort is needed.
+//
+// Layer-wide selections (steps 3 and 6).  The top bit of a key is zero; its next 12 bits (exponent and 4 mantissa bits) are
+// the first digit.  k_hist counts the digits of the whole layer, k_collect lists the keys of the digit that holds the K-th
+// (about a percent of a layer with real-valued contents), k_final finishes the walk on that list in one workgroup.  So the
+// layer is read twice per selection pair, and both selections of step 3 share the reads (an element belongs to exactly one).
+// Contents with more keys in that digit than the list has room for (a layer of constant magnitudes) are finished by reading
+// the layer instead, in that one workgroup.  Step 6 ranks the weights of the neurons that remain: the per-neuron kernel takes
+// the ablated neurons' keys out of step 3's counts, so step 6 starts at k_collect, and with no neuron ablated it is step 3's
+// answer.  Row-wise selections (step 7) are a search for the threshold by its bits, one wavefront per row, keys in registers,
+// counts from ballots: no LDS, no barrier.
+//
+// Eight launches.  768 x 3072, 90 % sparse: the walk by 8-bit digits through 19 launches took 98 us, 48 of them for three
+// passes whose LDS counters met in one bank, 19 for the row-wise radix walk.
 #include "srigl_internal.h"
+#include <cstddef>
 
 namespace srigl {
 
 struct SelState {
-    unsigned long long prefix;      // the bytes of the K-th largest key found so far (right-aligned); at the end: the key itself
+    unsigned long long prefix;      // the leading bits of the K-th largest key found so far (right-aligned); at the end: the key itself
     unsigned long long k_rem;       // how many of the keys with this prefix are still wanted
     unsigned long long total;       // number of candidate keys
+    unsigned int in_bin;            // keys with this prefix
     int done;                       // the threshold is final (nothing wanted: ~0; everything wanted: 0; or the walk has ended)
-    int pad;
 };
+
+constexpr int kDigitBits = 12, kDigits = 1 << kDigitBits, kDigitShift = 63 - kDigitBits;   // the first digit of a key
+constexpr int kCoarse = 256, kFine = kDigits / kCoarse;   // the digit is found among 256 coarse counts first, then among 16
+// Copies of the layer-wide counters (a workgroup adds into copy w % 8: one per die), and of the neuron counters: a launch ends
+// with one atomic per non-empty digit and workgroup, and atomics on one address take turns.
+constexpr int kHistCopies = 8;
+constexpr int kCountCopies = 64;
 
 // Head of the workspace.  Selections: 0 = smallest kept weights of the layer, 1 = largest gradients at pruned positions,
-// 2 = smallest kept weights of the remaining neurons.  Pass p of a walk adds into hist[sel][p]; the launch of pass p + 1
-// reads it (every workgroup picks the byte of pass p for itself), so no launch reads and clears the same counters, and no
-// device-wide fence is needed (on this multi-die GPU such a fence costs about 0.1 ms per launch).
-// slot[sel][p & 1] = the walk's state before pass p (written by workgroup 0 of the launch of pass p, read by the next launch).
-// The launch after a walk's eighth pass takes the last digit for itself (finished_walk): select key >= its prefix.
-// Copies of every layer-wide histogram: a pass ends with one atomic per non-empty digit and workgroup, and 2048 workgroups
-// adding to the same 256 counters took longer than reading a 2.4-million-element layer (43 us of a 167 us update).  Every
-// workgroup of the next pass reads all copies, which costs too: 4 copies measured best (1, 2, 8: 2-5 % slower; 32: 50 %).
-constexpr int kHistCopies = 4;
-constexpr int kCountCopies = 64;
+// 2 = smallest kept weights of the remaining neurons (counted in hist[0] once the ablated neurons are out of it).
 struct UpdateScratch {
-    unsigned int hist[3][8][kHistCopies][256];   // workgroup w adds into copy w % kHistCopies
-    SelState slot[3][2];
-    SelState fin[2];                    // the finished selections of step 3 (written by k_row_salient for the launches after it)
-    // steps 4-5: neurons that stay / are ablated now (sums of the copies: one per lane of the wavefront that reads them; a
-    // workgroup of the per-neuron kernel adds into copy w % 64, so a 16384-row layer sends 64 atomics to an address, not 1024)
-    unsigned int cnt_remaining[kCountCopies], cnt_ablated[kCountCopies];
-    unsigned long long cand_count[3];   // keys in the selection's candidate list; above the capacity: the list is not valid
+    unsigned int hist[2][kHistCopies][kDigits];
+    unsigned int coarse[2][kHistCopies][kCoarse];
+    unsigned int cnt_remaining[kCountCopies], cnt_ablated[kCountCopies];   // steps 4-5: neurons that stay / are ablated now
+    unsigned long long cand_count[3];   // keys in the selection's list; above the capacity: the list is not valid
+    SelState picked[3];                 // after the first digit (written by k_collect)
+    SelState fin[3];                    // the finished selections (k_final)
+    unsigned long long t_prune;         // step 6's threshold and the new fan-in (k_final of step 6)
+    long long k_new;
 };
-
-// Pass p of a walk decides `pass_bits(p)` bits of the key, found at `pass_shift(p)`; before pass p the top
-// `bits_done(p)` bits are fixed (the always-zero top bit counts as fixed from the start).
-__host__ __device__ constexpr int pass_shift(int p) { return p < 7 ? 55 - 8 * p : 0; }
-__host__ __device__ constexpr int pass_bits(int p) { return p < 7 ? 8 : 7; }
-__host__ __device__ constexpr int bits_done(int p) { return p < 8 ? 1 + 8 * p : 64; }
-constexpr int kCompactPass = 2;      // the pass that also writes the candidate lists
-constexpr int kBlockList = 1024;     // candidate keys a workgroup collects in LDS before it appends them
+constexpr size_t kZeroWords = (offsetof(UpdateScratch, picked) + 15) / 16;   // 16-byte pieces cleared before an update
 
 __device__ __forceinline__ unsigned int mag_bits(float v) { return __float_as_uint(v) & 0x7fffffffu; }
 // larger key = smaller magnitude, then lower position
@@ -63,113 +61,145 @@ __device__ __forceinline__ unsigned long long key_small_first(unsigned int mag, 
 __device__ __forceinline__ unsigned long long key_large_first(unsigned int mag, unsigned int pos) {
     return ((unsigned long long)mag << 32) | (0xffffffffu - pos);
 }
+__device__ __forceinline__ unsigned int digit_small_first(unsigned int mag) { return (0x7fffffffu - mag) >> (kDigitShift - 32); }
+__device__ __forceinline__ unsigned int digit_large_first(unsigned int mag) { return mag >> (kDigitShift - 32); }
 
-__global__ __launch_bounds__(256) void k_update_init(UpdateScratch* s, long long K_upd) {
-    const int t = threadIdx.x;
-    const int n = 3 * 8 * kHistCopies * 256;
-    for (int i = blockIdx.x * 256 + t; i < n; i += gridDim.x * 256) (&s->hist[0][0][0][0])[i] = 0;
-    if (blockIdx.x == 0 && t < 3) {
-        SelState z;
-        z.prefix = 0; z.k_rem = (unsigned long long)K_upd; z.total = 0; z.done = 0; z.pad = 0;
-        s->slot[t][0] = z;
-        s->slot[t][1] = z;
-        if (t < 2) s->fin[t] = z;
-        s->cand_count[t] = 0;
-    }
-    if (blockIdx.x == 0 && t < kCountCopies) { s->cnt_remaining[t] = 0; s->cnt_ablated[t] = 0; }
+__global__ __launch_bounds__(256) void k_update_init(uint4* __restrict__ head) {
+    const uint4 z = {0u, 0u, 0u, 0u};
+    for (size_t i = blockIdx.x * 256 + threadIdx.x; i < kZeroWords; i += (size_t)gridDim.x * 256) head[i] = z;
 }
 
-// From a 256-bin histogram (lane l reads bins 4l .. 4l + 3), for one wavefront: the byte d with suffix(d) >= want >
-// suffix(d + 1), suffix(d) = number of keys whose byte is >= d; `above` = suffix(d + 1), `in_bin` = keys with byte d, `total`
-// = suffix(0).  The results are the same on every lane.
-__device__ __forceinline__ void pick_from(const unsigned long long (&v)[4], unsigned long long want, int lane, unsigned long long& digit,
-                                          unsigned long long& above, unsigned long long& in_bin, unsigned long long& total) {
-    unsigned long long part[5];
-    part[4] = 0;
+// Four consecutive elements of the flat layer.
+struct Quad {
+    uint32_t m;
+    float4 w, g;
+};
+// What a workgroup of k_hist / k_collect works on: a run of quads, kQuads per thread in flight.
+constexpr int kScanThreads = 1024, kQuads = 4;
+template <bool GRAD>
+__device__ __forceinline__ void load_quads(Quad (&q)[kQuads], const float* __restrict__ W, const uint8_t* __restrict__ mask,
+                                           const float* __restrict__ grad, unsigned int first, unsigned int end) {
 #pragma unroll
-    for (int j = 3; j >= 0; --j) part[j] = part[j + 1] + v[j];
-    unsigned long long incl = part[0];   // becomes the sum over this lane and the lanes above it
+    for (int u = 0; u < kQuads; ++u) {
+        const unsigned int i = min(first + u * kScanThreads + threadIdx.x, end - 1);   // (past the end: re-read and dropped)
+        q[u].m = reinterpret_cast<const uint32_t*>(mask)[i];
+        q[u].w = reinterpret_cast<const float4*>(W)[i];
+        if (GRAD) q[u].g = reinterpret_cast<const float4*>(grad)[i];
+    }
+}
+// The elements of a quad, or of the layer's last ones (fewer than four, or all of them when the arrays are not 16-byte aligned).
+template <typename Element>
+__device__ __forceinline__ void each_of_quad(const Quad& q, unsigned int base, Element element) {
+    element(base + 0, q.m & 0xffu, q.w.x, q.g.x);
+    element(base + 1, (q.m >> 8) & 0xffu, q.w.y, q.g.y);
+    element(base + 2, (q.m >> 16) & 0xffu, q.w.z, q.g.z);
+    element(base + 3, q.m >> 24, q.w.w, q.g.w);
+}
+
+// Counts the first digits of both selections of step 3.  n4 quads, then the elements [4 n4, N) one by one.  LDS counters: the
+// digits of one wavefront's values spread over some fifty of the 4096, so its adds meet at most a few times per address.
+__global__ __launch_bounds__(kScanThreads) void k_hist(const float* __restrict__ W, const uint8_t* __restrict__ mask, const float* __restrict__ grad,
+                                                       unsigned int N, unsigned int n4, UpdateScratch* __restrict__ s) {
+    __shared__ unsigned int h[2][kDigits];
+    const int t = threadIdx.x;
+    const unsigned int per = (n4 + gridDim.x - 1) / gridDim.x, q0 = min(blockIdx.x * per, n4), q1 = min(q0 + per, n4);
+    Quad q[kQuads];
+    if (q0 < q1) load_quads<true>(q, W, mask, grad, q0, q1);
+    for (int i = t; i < 2 * kDigits / 4; i += kScanThreads) reinterpret_cast<uint4*>(&h[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    auto element = [&](unsigned int, unsigned int m, float w, float g) {
+        const unsigned int d = m ? digit_small_first(mag_bits(w)) : digit_large_first(mag_bits(g));
+        atomicAdd(&h[m ? 0 : 1][d], 1u);
+    };
+    for (unsigned int b = q0; b < q1; b += kQuads * kScanThreads) {
+        if (b != q0) load_quads<true>(q, W, mask, grad, b, q1);
+#pragma unroll
+        for (int u = 0; u < kQuads; ++u)
+            if (b + u * kScanThreads + t < q1) each_of_quad(q[u], 0, element);
+    }
+    for (unsigned int i = 4 * n4 + blockIdx.x * kScanThreads + t; i < N; i += gridDim.x * kScanThreads) element(i, mask[i], W[i], grad[i]);
+    __syncthreads();
+    const int copy = blockIdx.x % kHistCopies;
+#pragma unroll
+    for (int sel = 0; sel < 2; ++sel) {
+        const uint4 v = reinterpret_cast<const uint4*>(h[sel])[t];   // digits 4t .. 4t + 3
+        unsigned int* dst = &s->hist[sel][copy][4 * t];
+        if (v.x) atomicAdd(dst, v.x);
+        if (v.y) atomicAdd(dst + 1, v.y);
+        if (v.z) atomicAdd(dst + 2, v.z);
+        if (v.w) atomicAdd(dst + 3, v.w);
+        unsigned int c = v.x + v.y + v.z + v.w;
+        c += __shfl_xor(c, 1, 64);
+        c += __shfl_xor(c, 2, 64);
+        if ((t & 3) == 0 && c) atomicAdd(&s->coarse[sel][copy][t >> 2], c);
+    }
+}
+static_assert(kFine == 16 && kDigits == 4 * kScanThreads, "four digits per thread, sixteen per coarse count");
+
+// With n[l] keys in bin l of this wavefront's lane l: the bin d with suffix(d) >= want > suffix(d + 1), suffix(d) = keys in
+// bins d and above; `above` = suffix(d + 1), `in_bin` = n[d], `total` = suffix(0).  The results are the same on every lane.
+__device__ __forceinline__ void pick_lane(unsigned long long n, unsigned long long want, int lane, int& bin, unsigned long long& above,
+                                          unsigned long long& in_bin, unsigned long long& total) {
+    unsigned long long incl = n;   // becomes the sum over this lane and the lanes above it
     for (int off = 1; off < 64; off <<= 1) {
         const unsigned long long up = __shfl_down(incl, off, 64);
         if (lane + off < 64) incl += up;
     }
-    const unsigned long long excl = incl - part[0];
     total = __shfl(incl, 0, 64);
-    bool found = false;
-    digit = 0; above = 0; in_bin = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        if (excl + part[j] >= want && excl + part[j + 1] < want) {
-            found = true;
-            digit = 4 * lane + j;
-            above = excl + part[j + 1];
-            in_bin = v[j];
-        }
-    }
-    const unsigned long long owner = __ballot(found);
-    const int src = owner ? __builtin_ctzll(owner) : 0;
-    digit = __shfl(digit, src, 64);
-    above = __shfl(above, src, 64);
-    in_bin = __shfl(in_bin, src, 64);
-}
-// Over the sum of COPIES sub-histograms (lane l reads bins 4l .. 4l + 3 of each); copy c keeps the count of digit d at index (d + TURN * c) mod 256 (in LDS a
-// turn of kCopyTurn puts equal digits of different copies in different banks)
-constexpr int kCopyTurn = 16;
-template <int COPIES, int TURN>
-__device__ __forceinline__ void sum_byte_copies(const unsigned int (*h)[256], int lane, unsigned long long (&v)[4]) {
-    v[0] = v[1] = v[2] = v[3] = 0;
-#pragma unroll
-    for (int c = 0; c < COPIES; ++c) {
-        const uint4 q = *reinterpret_cast<const uint4*>(&h[c][(4 * lane + TURN * c) & 255]);
-        v[0] += q.x; v[1] += q.y; v[2] += q.z; v[3] += q.w;
-    }
-}
-template <int COPIES, int TURN>
-__device__ __forceinline__ void pick_byte_copies(const unsigned int (*h)[256], unsigned long long want, int lane, unsigned long long& digit,
-                                                 unsigned long long& above, unsigned long long& in_bin, unsigned long long& total) {
-    unsigned long long v[4];
-    sum_byte_copies<COPIES, TURN>(h, lane, v);
-    pick_from(v, want, lane, digit, above, in_bin, total);
+    const unsigned long long owner = __ballot(incl >= want && incl - n < want);
+    bin = owner ? __builtin_ctzll(owner) : 0;
+    above = __shfl(incl - n, bin, 64);
+    in_bin = __shfl(n, bin, 64);
 }
 
-// The state of a layer-wide walk before pass `pass` (1..8), from the state before pass - 1 and the histogram of pass - 1.
-// Called by one whole wavefront; the result is the same on every lane.
-// advance_from: with the counters of pass - 1 already summed (lane l holds digits 4l .. 4l + 3); advance requests them
-// before the state is looked at, so that the two reads from memory do not wait for each other.
-__device__ SelState advance_from(const SelState& before, const unsigned long long (&v)[4], int pass, int lane) {
-    SelState st = before;
-    if (st.done) return st;
-    unsigned long long digit, above, in_bin, total;
-    pick_from(v, st.k_rem == 0 ? 1 : st.k_rem, lane, digit, above, in_bin, total);
-    if (pass == 1) {
-        st.total = total;
-        if (st.k_rem == 0 || total < st.k_rem) {
-            st.prefix = (st.k_rem == 0) ? ~0ull : 0ull;   // nothing / everything
-            st.done = 1;
-            return st;
-        }
+// The state of a selection after its first digit, from the layer-wide counters.  One whole wavefront; the same on every lane.
+__device__ SelState pick_first(const UpdateScratch* __restrict__ s, int hist, unsigned long long K, int lane) {
+    unsigned int v[4] = {0u, 0u, 0u, 0u};   // coarse counts 4 lane .. 4 lane + 3
+#pragma unroll
+    for (int c = 0; c < kHistCopies; ++c) {
+        const uint4 q = reinterpret_cast<const uint4*>(s->coarse[hist][c])[lane];
+        v[0] += q.x; v[1] += q.y; v[2] += q.z; v[3] += q.w;
     }
-    st.prefix = (st.prefix << pass_bits(pass - 1)) | digit;
+    SelState st;
+    st.prefix = 0; st.k_rem = K; st.in_bin = 0; st.done = 0;
+    int group;
+    unsigned long long above, in_bin, total;
+    pick_lane((unsigned long long)v[0] + v[1] + v[2] + v[3], K == 0 ? 1 : K, lane, group, above, in_bin, total);
+    st.total = total;
+    if (K == 0 || total < K) {
+        st.prefix = K == 0 ? ~0ull : 0ull;   // nothing / everything
+        st.done = 1;
+        return st;
+    }
     st.k_rem -= above;
-    // every key of the chosen digit is wanted (always so once the keys under the prefix are down to one): the walk is over,
-    // the threshold is the smallest key with this prefix
-    if (pass == 8 || st.k_rem == in_bin) {
-        if (pass < 8) st.prefix <<= 64 - bits_done(pass);
+    // the coarse digit inside the chosen group of four, then the digit inside the coarse one
+    unsigned long long mine = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const unsigned int x = __shfl(v[j], group, 64);
+        if (lane == j) mine = x;
+    }
+    int sub;
+    pick_lane(mine, st.k_rem, lane, sub, above, in_bin, total);
+    st.k_rem -= above;
+    const int coarse = 4 * group + sub;
+    unsigned int n = 0;
+#pragma unroll
+    for (int c = 0; c < kHistCopies; c += 4) n += s->hist[hist][c + (lane >> 4)][coarse * kFine + (lane & 15)];
+    n += __shfl_xor(n, 16, 64);
+    n += __shfl_xor(n, 32, 64);
+    int fine;
+    pick_lane(lane < kFine ? n : 0, st.k_rem, lane, fine, above, in_bin, total);
+    st.k_rem -= above;
+    st.prefix = coarse * kFine + fine;
+    st.in_bin = (unsigned int)in_bin;
+    if (st.k_rem == in_bin) {   // every key of the digit is wanted: the threshold is the smallest key with this prefix
+        st.prefix <<= kDigitShift;
         st.done = 1;
     }
     return st;
 }
-__device__ SelState advance(const SelState& before, const unsigned int (*hist_prev)[256], int pass, int lane) {
-    unsigned long long v[4];
-    sum_byte_copies<kHistCopies, 0>(hist_prev, lane, v);
-    return advance_from(before, v, pass, lane);
-}
 
-// The finished selection `sel` for the launch that follows its eighth pass: the last digit from that pass's counters.
-// Called by one whole wavefront; the result is the same on every lane.
-__device__ __forceinline__ SelState finished_walk(const UpdateScratch* __restrict__ s, int sel, int lane) {
-    return advance(s->slot[sel][1], s->hist[sel][7], 8, lane);
-}
 // Sum of the 64 copies of a neuron counter.  Called by one whole wavefront; the result is the same on every lane.
 __device__ __forceinline__ unsigned int sum_copies(const unsigned int (&c)[kCountCopies], int lane) {
     unsigned int n = c[lane];
@@ -177,161 +207,248 @@ __device__ __forceinline__ unsigned int sum_copies(const unsigned int (&c)[kCoun
     return n;
 }
 
-// One pass of the walk.  PAIR: selections 0 (kept weights, smallest first) and 1 (pruned positions, largest gradient first)
-// together: every element belongs to exactly one of them, so one read of the layer serves both.  Otherwise selection 2
-// (kept weights of the remaining neurons).  kCopies sub-histograms spread the LDS atomics of equal digits.
-// COMPACT (the launch of pass kCompactPass): every key that matches the prefix is also appended to the selection's candidate
-// list (collected per workgroup in LDS, one counter update per workgroup); a workgroup that meets more than kBlockList of
-// them, or a list longer than `cap`, leaves the counter above `cap`, and the later passes then keep reading the layer.
-// VEC (d_in a multiple of 4, 16-byte aligned arrays): four consecutive elements per thread and step, moved with one 4-byte
-// and two 16-byte loads that do not wait for each other (a line of W or grad is fetched for almost every run of 32 elements
-// anyway, so reading both arrays in full costs no extra traffic).
-constexpr int kCopies = 8;
-constexpr int kPassThreads = 256;   // threads per workgroup of a layer-wide pass (512 and 1024 measured no faster)
-template <bool PAIR, bool COMPACT, bool VEC>
-__global__ __launch_bounds__(kPassThreads) void k_layer_hist(const float* __restrict__ W, const uint8_t* __restrict__ mask,
-                                                    const float* __restrict__ grad, const int* __restrict__ remains, unsigned int N,
-                                                    int d_in, int pass, UpdateScratch* __restrict__ s,
-                                                    unsigned long long* __restrict__ candA, unsigned long long* __restrict__ candB,
-                                                    unsigned long long cap) {
-    __shared__ unsigned int h[2][kCopies][256];
+// Lists the keys of the first digit that holds the K-th key.  PAIR: selections 0 and 1 together, otherwise selection 2 (kept
+// weights of the remaining neurons; nothing to do when no neuron was ablated).  A workgroup collects up to kStage keys per
+// selection in LDS and appends them with one update of the list's length; what does not fit goes out one by one.
+constexpr int kStage = 2048;
+template <bool PAIR>
+__global__ __launch_bounds__(kScanThreads) void k_collect(const float* __restrict__ W, const uint8_t* __restrict__ mask,
+                                                          const float* __restrict__ grad, const int* __restrict__ remains, unsigned int N,
+                                                          unsigned int n4, int d_in, unsigned long long K, UpdateScratch* __restrict__ s,
+                                                          unsigned long long* __restrict__ candA, unsigned long long* __restrict__ candB,
+                                                          unsigned long long cap) {
+    __shared__ unsigned long long stage[PAIR ? 2 : 1][kStage];
     __shared__ SelState cur[2];
-    __shared__ unsigned long long keep[COMPACT ? 2 : 1][COMPACT ? kBlockList : 1];
-    __shared__ unsigned int keep_n[2];
-    __shared__ unsigned long long keep_base[2];
+    __shared__ unsigned int n_staged[2];
+    __shared__ unsigned long long base[2];
     const int t = threadIdx.x;
-    const int selA = PAIR ? 0 : 2;
-    const SelState before_a = s->slot[selA][(pass + 1) & 1], before_b = s->slot[1][(pass + 1) & 1];
-    // walks that had ended before the previous pass: nothing to count
-    if (pass > 0 && before_a.done != 0 && (!PAIR || before_b.done != 0)) {
-        if (blockIdx.x == 0 && t == 0) {
-            s->slot[selA][pass & 1] = before_a;
-            if (PAIR) s->slot[1][pass & 1] = before_b;
+    constexpr int selA = PAIR ? 0 : 2;
+    const unsigned int per = (n4 + gridDim.x - 1) / gridDim.x, q0 = min(blockIdx.x * per, n4), q1 = min(q0 + per, n4);
+    Quad q[kQuads];
+    if (!PAIR && sum_copies(s->cnt_ablated, t & 63) == 0) return;
+    if (q0 < q1) load_quads<PAIR>(q, W, mask, grad, q0, q1);   // (before the counters are waited for)
+    if (t < (PAIR ? 128 : 64)) {
+        const int k = t >> 6;
+        const SelState st = pick_first(s, k, K, t & 63);
+        if ((t & 63) == 0) {
+            cur[k] = st;
+            n_staged[k] = 0;
+            if (blockIdx.x == 0) s->picked[k == 0 ? selA : 1] = st;
         }
-        return;
     }
-    if (t < 64) {
-        SelState a = before_a, b = before_b;
-        if (pass > 0) {
-            a = advance(a, s->hist[selA][pass - 1], pass, t);
-            if (PAIR) b = advance(b, s->hist[1][pass - 1], pass, t);
-            if (blockIdx.x == 0 && t == 0) {
-                s->slot[selA][pass & 1] = a;
-                if (PAIR) s->slot[1][pass & 1] = b;
-            }
-        } else {
-            a = s->slot[selA][0];
-            b = s->slot[1][0];
-            // step 6 with no neuron ablated in step 4: same candidates, same count, so step 3's walk already has the answer
-            if (!PAIR && sum_copies(s->cnt_ablated, t) == 0) {
-                a = s->fin[0];
-                if (blockIdx.x == 0 && t == 0) s->slot[2][0] = a;
-            }
-        }
-        if (t == 0) { cur[0] = a; cur[1] = b; }
-    }
-    for (int i = t; i < 2 * kCopies * 256; i += kPassThreads) (&h[0][0][0])[i] = 0;
-    if (t < 2) keep_n[t] = 0;
     __syncthreads();
-    const bool doneA = cur[0].done != 0, doneB = PAIR ? cur[1].done != 0 : true;
-    if (doneA && doneB) return;
-    const int shift = pass_shift(pass);
-    const unsigned int dmask = (1u << pass_bits(pass)) - 1u;
-    const int pshift = 64 - bits_done(pass);   // pass > 0: a key is still in the walk iff key >> pshift == prefix
-    const unsigned long long prefixA = cur[0].prefix, prefixB = cur[1].prefix;
-    const int copy = t & (kCopies - 1);
-    const bool lists = !COMPACT && pass > kCompactPass && cap > 0;
-    const unsigned long long countA = lists ? s->cand_count[selA] : 0, countB = (lists && PAIR) ? s->cand_count[1] : 0;
-    const bool listA = lists && countA <= cap, listB = lists && PAIR && countB <= cap;
-    const bool scanA = !doneA && !listA, scanB = PAIR && !doneB && !listB;
-    // one element: position ii, mask byte m, weight w, gradient g, whether its neuron remains (selection 2 only)
-    auto element = [&](unsigned int ii, unsigned int m, float w, float g, bool rem) {
-        if (m != 0) {
-            if (!scanA || (!PAIR && !rem)) return;
-            const unsigned long long key = key_small_first(mag_bits(w), ii);
-            if (pass > 0 && (key >> pshift) != prefixA) return;
-            atomicAdd(&h[0][copy][(unsigned int)(key >> shift) & dmask], 1u);
-            if (COMPACT) {
-                const unsigned int slot = atomicAdd(&keep_n[0], 1u);
-                if (slot < (unsigned)kBlockList) keep[0][slot] = key;
-            }
-        } else if (scanB) {
-            const unsigned long long key = key_large_first(mag_bits(g), ii);
-            if (pass > 0 && (key >> pshift) != prefixB) return;
-            atomicAdd(&h[1][copy][(unsigned int)(key >> shift) & dmask], 1u);
-            if (COMPACT) {
-                const unsigned int slot = atomicAdd(&keep_n[1], 1u);
-                if (slot < (unsigned)kBlockList) keep[1][slot] = key;
-            }
+    const bool liveA = !cur[0].done && cur[0].in_bin <= cap, liveB = PAIR && !cur[1].done && cur[1].in_bin <= cap;
+    if (!liveA && !liveB) return;
+    const unsigned int digA = liveA ? (unsigned int)cur[0].prefix : ~0u, digB = liveB ? (unsigned int)cur[1].prefix : ~0u;
+    auto put = [&](int k, unsigned long long key) {
+        const unsigned int slot = atomicAdd(&n_staged[k], 1u);
+        if (slot < (unsigned)kStage) {
+            stage[k][slot] = key;
+        } else {
+            const unsigned long long at = atomicAdd(&s->cand_count[k == 0 ? selA : 1], 1ull);
+            if (at < cap) (k == 0 ? candA : candB)[at] = key;
         }
     };
-    if ((scanA || scanB) && VEC) {
-        const unsigned int N4 = N / 4;   // d_in is a multiple of 4, so N is, and a run of 4 stays inside one row
-        for (unsigned long long i = (unsigned long long)blockIdx.x * kPassThreads + t; i < N4; i += (unsigned long long)gridDim.x * kPassThreads) {
-            const unsigned int base = 4u * (unsigned int)i;
-            const uint32_t m4 = *reinterpret_cast<const uint32_t*>(mask + base);
-            float4 w4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), g4 = w4;
-            if (scanA) w4 = *reinterpret_cast<const float4*>(W + base);
-            if (scanB) g4 = *reinterpret_cast<const float4*>(grad + base);
-            const bool rem = (PAIR || m4 == 0) ? true : remains[base / (unsigned)d_in] != 0;
-            element(base + 0, m4 & 0xffu, w4.x, g4.x, rem);
-            element(base + 1, (m4 >> 8) & 0xffu, w4.y, g4.y, rem);
-            element(base + 2, (m4 >> 16) & 0xffu, w4.z, g4.z, rem);
-            element(base + 3, m4 >> 24, w4.w, g4.w, rem);
+    auto element = [&](unsigned int i, unsigned int m, float w, float g) {
+        if (m) {
+            const unsigned int mag = mag_bits(w);
+            if (digit_small_first(mag) == digA && (PAIR || remains[i / (unsigned)d_in] != 0)) put(0, key_small_first(mag, i));
+        } else if (PAIR) {
+            const unsigned int mag = mag_bits(g);
+            if (digit_large_first(mag) == digB) put(1, key_large_first(mag, i));
         }
-    } else if (scanA || scanB) {
-        for (unsigned long long i = (unsigned long long)blockIdx.x * kPassThreads + t; i < N; i += (unsigned long long)gridDim.x * kPassThreads) {
-            const unsigned int ii = (unsigned int)i;
-            const unsigned int m = mask[ii];
-            if (m != 0) {
-                if (scanA) element(ii, m, W[ii], 0.0f, PAIR ? true : remains[ii / (unsigned)d_in] != 0);
-            } else if (scanB) {
-                element(ii, 0u, 0.0f, grad[ii], true);
-            }
-        }
-    }
-    if (!doneA && listA) {
-        for (unsigned long long i = (unsigned long long)blockIdx.x * kPassThreads + t; i < countA; i += (unsigned long long)gridDim.x * kPassThreads) {
-            const unsigned long long key = candA[i];
-            if ((key >> pshift) == prefixA) atomicAdd(&h[0][copy][(unsigned int)(key >> shift) & dmask], 1u);
-        }
-    }
-    if (PAIR && !doneB && listB) {
-        for (unsigned long long i = (unsigned long long)blockIdx.x * kPassThreads + t; i < countB; i += (unsigned long long)gridDim.x * kPassThreads) {
-            const unsigned long long key = candB[i];
-            if ((key >> pshift) == prefixB) atomicAdd(&h[1][copy][(unsigned int)(key >> shift) & dmask], 1u);
-        }
-    }
-    __syncthreads();
-    unsigned int a = 0, b = 0;
-    if (t < 256) {
-#pragma unroll
-        for (int c = 0; c < kCopies; ++c) { a += h[0][c][t]; b += h[1][c][t]; }
-        if (a) atomicAdd(&s->hist[selA][pass][blockIdx.x % kHistCopies][t], a);
-        if (PAIR && b) atomicAdd(&s->hist[1][pass][blockIdx.x % kHistCopies][t], b);
-    }
-    if (COMPACT) {
-        if (t < 2) {
-            const unsigned int n = keep_n[t];
-            // more keys than the workgroup can hold: the counter goes past `cap` for good, the list is not used
-            keep_base[t] = n ? atomicAdd(&s->cand_count[t == 0 ? selA : 1], n > (unsigned)kBlockList ? cap + 1ull : (unsigned long long)n) : 0ull;
+    };
+    auto flush = [&] {
+        __syncthreads();
+        if (t < (PAIR ? 2 : 1)) {
+            const unsigned int n = min(n_staged[t], (unsigned)kStage);
+            base[t] = n ? atomicAdd(&s->cand_count[t == 0 ? selA : 1], (unsigned long long)n) : 0ull;
         }
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const unsigned int n = keep_n[q];
-            unsigned long long* __restrict__ dst = q == 0 ? candA : candB;
-            if (n == 0 || n > (unsigned)kBlockList || keep_base[q] + n > cap) continue;
-            for (unsigned int e = t; e < n; e += kPassThreads) dst[keep_base[q] + e] = keep[q][e];
+        for (int k = 0; k < (PAIR ? 2 : 1); ++k) {
+            const unsigned int n = min(n_staged[k], (unsigned)kStage);
+            for (unsigned int e = t; e < n; e += kScanThreads)
+                if (base[k] + e < cap) (k == 0 ? candA : candB)[base[k] + e] = stage[k][e];
+        }
+        __syncthreads();
+        if (t < 2) n_staged[t] = 0;
+        __syncthreads();
+    };
+    for (unsigned int b = q0; b < q1; b += kQuads * kScanThreads) {
+        if (b != q0) load_quads<PAIR>(q, W, mask, grad, b, q1);
+#pragma unroll
+        for (int u = 0; u < kQuads; ++u) {
+            const unsigned int i = b + u * kScanThreads + t;
+            if (i < q1) each_of_quad(q[u], 4 * i, element);
+        }
+        if (b + kQuads * kScanThreads < q1) flush();
+    }
+    for (unsigned int i = 4 * n4 + blockIdx.x * kScanThreads + t; i < N; i += gridDim.x * kScanThreads)
+        element(i, mask[i], W[i], PAIR ? grad[i] : 0.0f);
+    flush();
+}
+
+// The end of a selection: workgroup b takes selection b (PAIR) or 2.  The keys come from the list (held in registers up to
+// kHeld per thread), or from the layer when there is no valid list.  12-bit digits until at most kDirect keys share the
+// prefix (one pass on real-valued contents), which are then ranked against each other.
+// Step 6's workgroup also takes the new fan-in from the neuron counters (step 5) and writes the report.
+constexpr int kHeld = 32, kDirect = 256;
+template <bool PAIR>
+__global__ __launch_bounds__(kScanThreads) void k_final(const float* __restrict__ W, const uint8_t* __restrict__ mask, const float* __restrict__ grad,
+                                                        const int* __restrict__ remains, unsigned int N, int d_in, UpdateScratch* __restrict__ s,
+                                                        const unsigned long long* __restrict__ candA, const unsigned long long* __restrict__ candB,
+                                                        unsigned long long cap, unsigned long long K, long long budget,
+                                                        long long* __restrict__ report) {
+    __shared__ unsigned int h[kDigits];
+    __shared__ unsigned int group_sum[64];
+    __shared__ SelState cur;
+    __shared__ unsigned long long direct[kDirect];
+    __shared__ unsigned int n_direct;
+    const int t = threadIdx.x, lane = t & 63;
+    const int sel = PAIR ? (int)blockIdx.x : 2;
+    SelState st;
+    if (!PAIR) {
+        const unsigned int n_remaining = sum_copies(s->cnt_remaining, lane), n_ablated = sum_copies(s->cnt_ablated, lane);
+        st = n_ablated == 0 ? s->fin[0] : s->picked[2];   // no neuron ablated: the same candidates and count as in step 3
+        if (t == 0) {
+            long long k = n_remaining > 0 ? budget / (long long)n_remaining : 0;
+            if (k > d_in) k = d_in;
+            s->k_new = k;
+            report[0] = k;
+            report[1] = n_remaining;
+            report[2] = n_ablated;
+            report[3] = (long long)(K < st.total ? K : st.total);
+        }
+    } else {
+        st = s->picked[sel];
+    }
+    auto finish = [&] {
+        if (t == 0) {
+            s->fin[sel] = st;
+            if (!PAIR) s->t_prune = st.prefix;
+        }
+    };
+    if (st.done) { finish(); return; }
+    const unsigned long long n_list = st.in_bin;   // (every key of the digit is in the list, or there is none)
+    const bool listed = n_list <= cap;
+    const unsigned long long* const list = sel == 1 ? candB : candA;
+    const bool held = listed && n_list <= (unsigned long long)kHeld * kScanThreads;
+    unsigned long long key[kHeld];
+    if (held) {
+#pragma unroll
+        for (int j = 0; j < kHeld; ++j) {
+            const unsigned int i = j * kScanThreads + t;
+            key[j] = i < n_list ? list[i] : 0ull;
         }
     }
+    auto each = [&](auto f) {
+        if (held) {
+#pragma unroll
+            for (int j = 0; j < kHeld; ++j)
+                if (j * kScanThreads + t < (int)n_list) f(key[j]);
+        } else if (listed) {
+            for (unsigned long long i = t; i < n_list; i += kScanThreads) f(list[i]);
+        } else {
+            for (unsigned long long i = t; i < N; i += kScanThreads) {
+                const unsigned int ii = (unsigned int)i;
+                const bool kept = mask[ii] != 0;
+                if (kept != (sel != 1)) continue;
+                if (sel == 2 && remains[ii / (unsigned)d_in] == 0) continue;
+                f(sel == 1 ? key_large_first(mag_bits(grad[ii]), ii) : key_small_first(mag_bits(W[ii]), ii));
+            }
+        }
+    };
+    int shift = kDigitShift;   // key >> shift == st.prefix: still in the walk
+    for (;;) {
+        if (st.in_bin <= (unsigned)kDirect) {
+            if (t == 0) n_direct = 0;
+            __syncthreads();
+            each([&](unsigned long long k) {
+                if ((k >> shift) == st.prefix) direct[min(atomicAdd(&n_direct, 1u), (unsigned)kDirect - 1)] = k;
+            });
+            __syncthreads();
+            const unsigned int n = min(n_direct, (unsigned)kDirect);
+            if (t < (int)n) {   // the k_rem-th largest
+                const unsigned long long mine = direct[t];
+                unsigned int larger = 0;
+                for (unsigned int j = 0; j < n; ++j) larger += direct[j] > mine ? 1u : 0u;
+                if (larger + 1 == st.k_rem) cur.prefix = mine;
+            }
+            __syncthreads();
+            st.prefix = cur.prefix;
+            st.done = 1;
+            finish();
+            return;
+        }
+        const int bits = min(kDigitBits, shift), next = shift - bits;
+        for (int i = t; i < kDigits; i += kScanThreads) h[i] = 0;
+        __syncthreads();
+        each([&](unsigned long long k) {
+            if ((k >> shift) == st.prefix) atomicAdd(&h[(unsigned int)(k >> next) & ((1u << bits) - 1u)], 1u);
+        });
+        __syncthreads();
+        for (int g = t >> 6; g < kDigits / 64; g += kScanThreads / 64) {   // 64 groups of 64 digits
+            unsigned int n = h[64 * g + lane];
+            for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off, 64);
+            if (lane == 0) group_sum[g] = n;
+        }
+        __syncthreads();
+        if (t < 64) {
+            int group, bin;
+            unsigned long long above, in_bin, total;
+            SelState c = st;
+            pick_lane(group_sum[lane], c.k_rem, lane, group, above, in_bin, total);
+            c.k_rem -= above;
+            pick_lane(h[64 * group + lane], c.k_rem, lane, bin, above, in_bin, total);
+            c.k_rem -= above;
+            c.prefix = (c.prefix << bits) | (unsigned)(64 * group + bin);
+            c.in_bin = (unsigned int)in_bin;
+            if (c.k_rem == in_bin || next == 0) {
+                c.prefix <<= next;
+                c.done = 1;
+            }
+            if (lane == 0) cur = c;
+        }
+        __syncthreads();
+        st = cur;
+        shift = next;
+        __syncthreads();   // (cur is written again by the next pass)
+        if (st.done) { finish(); return; }
+    }
+}
+static_assert(kDigits == 64 * 64, "two picks among 64");
+
+// Four consecutive columns of a row, at any alignment of the row: the last group of a row that does not end on a group
+// boundary reads the row's last four columns and owns only those its neighbour does not have.
+struct RowQuad {
+    uint32_t m;
+    float4 w, g;
+};
+__device__ __forceinline__ int quad_first(int c0, int d_in) { return min(c0, d_in - 4); }
+__device__ __forceinline__ void load_row_quad(RowQuad& q, const float* __restrict__ W, const uint8_t* __restrict__ mask,
+                                              const float* __restrict__ grad, size_t at) {
+    __builtin_memcpy(&q.m, mask + at, 4);
+    struct __attribute__((packed, aligned(4))) F4 { float x, y, z, w; };
+    const F4 w = *reinterpret_cast<const F4*>(W + at), g = *reinterpret_cast<const F4*>(grad + at);
+    q.w = make_float4(w.x, w.y, w.z, w.w);
+    q.g = make_float4(g.x, g.y, g.z, g.w);
+}
+// rows of fewer than four columns
+__device__ __forceinline__ void load_row_short(RowQuad& q, const float* __restrict__ W, const uint8_t* __restrict__ mask,
+                                               const float* __restrict__ grad, size_t at, int n) {
+    auto w = [&](int j) { return j < n ? W[at + j] : 0.0f; };
+    auto g = [&](int j) { return j < n ? grad[at + j] : 0.0f; };
+    auto m = [&](int j) { return j < n ? (uint32_t)mask[at + j] << (8 * j) : 0u; };
+    q.m = m(0) | m(1) | m(2) | m(3);
+    q.w = make_float4(w(0), w(1), w(2), w(3));
+    q.g = make_float4(g(0), g(1), g(2), g(3));
 }
 
 // Steps 3 to 5 up to the counts: per neuron, how many weights it holds and how many salient ones, whether it stays
 // (remains[r]; a neuron without weights stays ablated), and the layer's numbers of staying and newly ablated neurons (one
-// atomic per workgroup and counter, spread over copies; read by the launches after this one).  One wavefront per row.
-// VEC as in k_layer_hist: a lane takes runs of 4 columns.
-template <bool VEC>
+// atomic per workgroup and counter, spread over copies; read by the launches after this one).  One wavefront per row.  An
+// ablated neuron's weights leave the counts of selection 0.
 __global__ __launch_bounds__(256) void k_row_salient(const float* __restrict__ W, const uint8_t* __restrict__ mask,
                                                      const float* __restrict__ grad, int d_out, int d_in, int k, int gamma_percent,
                                                      UpdateScratch* __restrict__ s, int* __restrict__ remains) {
@@ -339,26 +456,22 @@ __global__ __launch_bounds__(256) void k_row_salient(const float* __restrict__ W
     const int lane = threadIdx.x & 63;
     const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (threadIdx.x == 0) { wg_stay = 0; wg_ablated = 0; }
+    const size_t row0 = (size_t)r * d_in;
+    const bool quads = d_in >= 4;
     // the row's first kAhead steps are requested before the thresholds are (they do not depend on them)
-    constexpr int kAhead = 2;
-    uint32_t pm[kAhead];
-    float4 pw[kAhead], pg[kAhead];
-    if (VEC && r < d_out) {
+    constexpr int kAhead = 4;
+    RowQuad p[kAhead];
+    if (r < d_out && quads) {
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            const int c = 4 * lane + 256 * u;
-            const unsigned int i = (unsigned int)r * d_in + (c < d_in ? c : 0);
-            pm[u] = *reinterpret_cast<const uint32_t*>(mask + i);
-            pw[u] = *reinterpret_cast<const float4*>(W + i);
-            pg[u] = *reinterpret_cast<const float4*>(grad + i);
-        }
+        for (int u = 0; u < kAhead; ++u)
+            if (256 * u < d_in) load_row_quad(p[u], W, mask, grad, row0 + quad_first(4 * lane + 256 * u, d_in));
     }
-    const SelState fa = finished_walk(s, 0, lane), fb = finished_walk(s, 1, lane);
-    if (blockIdx.x == 0 && threadIdx.x == 0) { s->fin[0] = fa; s->fin[1] = fb; }
+    const unsigned long long t_small = s->fin[0].prefix, t_grad = s->fin[1].prefix;
     __syncthreads();
-    const unsigned long long t_small = fa.prefix, t_grad = fb.prefix;
     int h = 0, sal = 0;
-    auto element = [&](unsigned int i, unsigned int m, float w, float g) {
+    auto element = [&](int c, int own, unsigned int m, float w, float g) {   // columns below `own` belong to the neighbour
+        if (c < own || c >= d_in) return;
+        const unsigned int i = (unsigned int)row0 + c;
         if (m) {
             ++h;
             if (key_small_first(mag_bits(w), i) < t_small) ++sal;    // survives the layer-wide pruning
@@ -366,43 +479,42 @@ __global__ __launch_bounds__(256) void k_row_salient(const float* __restrict__ W
             ++sal;                                                    // would be grown
         }
     };
+    auto quad = [&](const RowQuad& q, int first, int own) {
+        element(first + 0, own, q.m & 0xffu, q.w.x, q.g.x);
+        element(first + 1, own, (q.m >> 8) & 0xffu, q.w.y, q.g.y);
+        element(first + 2, own, (q.m >> 16) & 0xffu, q.w.z, q.g.z);
+        element(first + 3, own, q.m >> 24, q.w.w, q.g.w);
+    };
     if (r < d_out) {
-        if (VEC) {
+        if (quads) {
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                const int c = 4 * lane + 256 * u;
-                if (c >= d_in) break;
-                const unsigned int i = (unsigned int)r * d_in + c;
-                element(i + 0, pm[u] & 0xffu, pw[u].x, pg[u].x);
-                element(i + 1, (pm[u] >> 8) & 0xffu, pw[u].y, pg[u].y);
-                element(i + 2, (pm[u] >> 16) & 0xffu, pw[u].z, pg[u].z);
-                element(i + 3, pm[u] >> 24, pw[u].w, pg[u].w);
-            }
+            for (int u = 0; u < kAhead; ++u)
+                if (256 * u < d_in) quad(p[u], quad_first(4 * lane + 256 * u, d_in), 4 * lane + 256 * u);
             for (int c = 4 * lane + 256 * kAhead; c < d_in; c += 256) {
-                const unsigned int i = (unsigned int)r * d_in + c;
-                const uint32_t m4 = *reinterpret_cast<const uint32_t*>(mask + i);
-                const float4 w4 = *reinterpret_cast<const float4*>(W + i);
-                const float4 g4 = *reinterpret_cast<const float4*>(grad + i);
-                element(i + 0, m4 & 0xffu, w4.x, g4.x);
-                element(i + 1, (m4 >> 8) & 0xffu, w4.y, g4.y);
-                element(i + 2, (m4 >> 16) & 0xffu, w4.z, g4.z);
-                element(i + 3, m4 >> 24, w4.w, g4.w);
+                RowQuad q;
+                load_row_quad(q, W, mask, grad, row0 + quad_first(c, d_in));
+                quad(q, quad_first(c, d_in), c);
             }
-        } else {
-            for (int c = lane; c < d_in; c += 64) {
-                const unsigned int i = (unsigned int)r * d_in + c;
-                const unsigned int m = mask[i];
-                element(i, m, m ? W[i] : 0.0f, m ? 0.0f : grad[i]);
-            }
+        } else if (lane == 0) {
+            RowQuad q;
+            load_row_short(q, W, mask, grad, row0, d_in);
+            quad(q, 0, 0);
         }
         for (int off = 32; off > 0; off >>= 1) { h += __shfl_xor(h, off, 64); sal += __shfl_xor(sal, off, 64); }
+        const bool ablated = h > 0 && (sal < 1 || (long long)sal * 100 < (long long)gamma_percent * k);
         if (lane == 0) {
-            int stays = 0;
-            if (h > 0) {
-                const bool too_few = sal < 1 || (long long)sal * 100 < (long long)gamma_percent * k;
-                if (too_few) atomicAdd(&wg_ablated, 1); else { stays = 1; atomicAdd(&wg_stay, 1); }
+            if (ablated) atomicAdd(&wg_ablated, 1);
+            if (h > 0 && !ablated) atomicAdd(&wg_stay, 1);
+            remains[r] = h > 0 && !ablated ? 1 : 0;
+        }
+        if (ablated) {
+            const int copy = blockIdx.x % kHistCopies;
+            for (int c = lane; c < d_in; c += 64) {
+                if (mask[row0 + c] == 0) continue;
+                const unsigned int d = digit_small_first(mag_bits(W[row0 + c]));
+                atomicSub(&s->hist[0][copy][d], 1u);   // (modulo 2^32 per copy: the copies' sum is what counts)
+                atomicSub(&s->coarse[0][copy][d / kFine], 1u);
             }
-            remains[r] = stays;
         }
     }
     __syncthreads();
@@ -412,193 +524,148 @@ __global__ __launch_bounds__(256) void k_row_salient(const float* __restrict__ W
     }
 }
 
-// Radix walk inside one workgroup of 256 threads: the threshold of the `want` largest keys among the row's candidates.
-// key_of(j, key): whether the thread's j-th column is a candidate, and its key.  1 <= want <= number of candidates.
-// Same digits as the layer-wide walk (the top bit of a key is zero).  One barrier per pass: the histograms rotate through
-// three buffers (a pass adds into one, clears the next; the one before may still be read by a wavefront that is late), and
-// every wavefront sums the kRowCopies sub-histograms and picks the digit for itself, so nothing is handed round.
-constexpr int kRowCopies = 4;
-template <int CPT, typename KeyOf>
-__device__ unsigned long long row_select(unsigned long long want, KeyOf key_of, unsigned int (*h)[kRowCopies][256]) {
-    const int t = threadIdx.x, lane = t & 63;
-    const int copy = t & (kRowCopies - 1);
-    unsigned long long prefix = 0;
-#pragma unroll
-    for (int c = 0; c < kRowCopies; ++c) h[0][c][t] = 0;
-    __syncthreads();
-#pragma unroll 1
-    for (int pass = 0; pass < 8; ++pass) {
-        const int cur = pass % 3, nxt = (pass + 1) % 3;
-        const int shift = pass_shift(pass);
-        const unsigned int dmask = (1u << pass_bits(pass)) - 1u;
-        const int pshift = 64 - bits_done(pass);
-#pragma unroll
-        for (int c = 0; c < kRowCopies; ++c) h[nxt][c][t] = 0;
-#pragma unroll
-        for (int j = 0; j < CPT; ++j) {
-            unsigned long long key;
-            if (!key_of(j, key)) continue;
-            if (pass > 0 && (key >> pshift) != prefix) continue;
-            atomicAdd(&h[cur][copy][(((unsigned int)(key >> shift) & dmask) + kCopyTurn * copy) & 255u], 1u);
-        }
-        __syncthreads();
-        unsigned long long digit, above, in_bin, total;
-        pick_byte_copies<kRowCopies, kCopyTurn>(h[cur], want, lane, digit, above, in_bin, total);
-        prefix = (prefix << pass_bits(pass)) | digit;
-        want -= above;
-        // every key of this digit is wanted: the walk is over, the threshold is the smallest key with this prefix
-        if (want == in_bin && pass < 7) return prefix << (64 - bits_done(pass + 1));
-    }
-    return prefix;
-}
+// Steps 6 (applied) and 7.  One wavefront per row; lane l holds columns 4 (l + 64 q) .. + 3, q < NQ (d_in <= 256 NQ).  A column
+// is ranked by one number (its weight's magnitude if it survives step 6, else its gradient's), equal numbers by column.  The
+// `want`-th largest among the row's candidates is searched bit by bit: NQ x 4 compares, their ballots counted by scalar
+// instructions, per bit, until a threshold splits off exactly `want` (about 20 of 31 bits on real-valued contents).
+template <int NQ>
+__global__ __launch_bounds__(256) void k_row_update(const float* __restrict__ W, const uint8_t* __restrict__ mask, const float* __restrict__ grad,
+                                                    int d_out, int d_in, const int* __restrict__ remains, const UpdateScratch* __restrict__ s,
+                                                    uint8_t* __restrict__ mask_out, float* __restrict__ W_out) {
+    constexpr int N = 4 * NQ;
+    constexpr bool HOLD = NQ <= 4;   // the weights stay in registers (else they are read again where they are kept)
+    const int lane = threadIdx.x & 63;
+    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (r >= d_out) return;
+    const size_t row0 = (size_t)r * d_in;
+    const bool quads = NQ > 1 || d_in >= 4;
+    struct __attribute__((packed, aligned(4))) F4 { float x, y, z, w; };
+    auto col0 = [&](int q) { return 4 * (lane + 64 * q); };
 
-// Steps 6 (applied) and 7.  One workgroup of 256 threads per row; a thread holds CPT columns of the row (d_in <= 256 CPT):
-// whether the weight survives step 6, and the one key the column can be ranked by (its weight magnitude if it survives,
-// else its gradient magnitude), so the walks read registers only.  VEC (d_in a multiple of 4, 16-byte aligned arrays): a
-// thread's columns are runs of 4, moved with 16-byte loads and stores; otherwise column t + 256 j, one element at a time.
-template <int CPT, bool VEC>
-__global__ __launch_bounds__(256, CPT <= 16 ? 5 : 2) void k_row_update(const float* __restrict__ W, const uint8_t* __restrict__ mask,
-                                                    const float* __restrict__ grad, int d_in, const int* __restrict__ remains,
-                                                    const UpdateScratch* __restrict__ s, long long K_upd, long long budget,
-                                                    uint8_t* __restrict__ mask_out, float* __restrict__ W_out,
-                                                    long long* __restrict__ report) {
-    __shared__ __align__(16) unsigned int h[3][kRowCopies][256];
-    __shared__ int n_kept;
-    __shared__ unsigned long long prune_threshold;
-    __shared__ long long new_fan_in;
-    const int r = blockIdx.x, t = threadIdx.x;
-    const unsigned int row0 = (unsigned int)r * d_in;
-    // rows of up to 4096 columns: the thread's columns are requested before the selection's state is (neither waits for the other)
-    constexpr bool kEarly = VEC && CPT <= 16;
-    float4 pw[kEarly ? CPT / 4 : 1], pg[kEarly ? CPT / 4 : 1];
-    uint32_t pm[kEarly ? CPT / 4 : 1];
-    if (kEarly) {
+    int rank[N];             // magnitude bits (below 2^31), or -1: not a column of the row
+    uint32_t surv[(N + 31) / 32];
 #pragma unroll
-        for (int q = 0; q < CPT / 4; ++q) {
-            const int c0 = 4 * (t + 256 * q);
-            const unsigned int i = row0 + (c0 < d_in ? c0 : 0);
-            pw[q] = *reinterpret_cast<const float4*>(W + i);
-            pg[q] = *reinterpret_cast<const float4*>(grad + i);
-            pm[q] = *reinterpret_cast<const uint32_t*>(mask + i);
-        }
-    }
-    // step 5: the new fan-in from the count of staying neurons; step 6's finished selection (its last digit is taken here)
-    if (t < 64) {
-        const long long n_remaining = sum_copies(s->cnt_remaining, t);
-        const long long n_ablated = sum_copies(s->cnt_ablated, t);
-        long long k = n_remaining > 0 ? budget / n_remaining : 0;
-        if (k > d_in) k = d_in;
-        const SelState f2 = finished_walk(s, 2, t);
-        if (t == 0) {
-            prune_threshold = f2.prefix;
-            new_fan_in = k;
-            if (r == 0) {
-                report[0] = k;
-                report[1] = n_remaining;
-                report[2] = n_ablated;
-                report[3] = (long long)((unsigned long long)K_upd < f2.total ? (unsigned long long)K_upd : f2.total);
+    for (int i = 0; i < (N + 31) / 32; ++i) surv[i] = 0u;
+    float4 held[HOLD ? NQ : 1];
+    const unsigned long long t_prune = s->t_prune;
+    const long long k_new = s->k_new;
+    const bool stays = remains[r] != 0;
+    constexpr int STEP = NQ <= 6 ? NQ : 4;   // groups in flight
+#pragma unroll
+    for (int q0 = 0; q0 < NQ; q0 += STEP) {
+        RowQuad in[STEP];
+#pragma unroll
+        for (int u = 0; u < STEP; ++u) {
+            if (q0 + u < NQ && stays) {
+                if (quads) load_row_quad(in[u], W, mask, grad, row0 + quad_first(col0(q0 + u), d_in));
+                else load_row_short(in[u], W, mask, grad, row0, d_in);
             }
         }
+#pragma unroll
+        for (int u = 0; u < STEP; ++u) {
+            const int q = q0 + u;
+            if (q >= NQ) break;
+            const int own = col0(q), first = quads ? quad_first(own, d_in) : 0;
+            auto take = [&](int j, unsigned int m, float w, float g) {
+                const int c = first + j;
+                const bool valid = stays && c >= own && c < d_in;
+                const bool sv = valid && m != 0 && key_small_first(mag_bits(w), (unsigned int)row0 + c) < t_prune;
+                rank[4 * q + j] = valid ? (int)mag_bits(sv ? w : g) : -1;
+                if (sv) surv[(4 * q + j) / 32] |= 1u << ((4 * q + j) % 32);
+            };
+            take(0, in[u].m & 0xffu, in[u].w.x, in[u].g.x);
+            take(1, (in[u].m >> 8) & 0xffu, in[u].w.y, in[u].g.y);
+            take(2, (in[u].m >> 16) & 0xffu, in[u].w.z, in[u].g.z);
+            take(3, in[u].m >> 24, in[u].w.w, in[u].g.w);
+            if (HOLD) held[q] = in[u].w;
+        }
     }
-    // column of the thread's j-th element
-    auto col_of = [&](int j) { return VEC ? 4 * (t + 256 * (j >> 2)) + (j & 3) : t + 256 * j; };
-    if (!remains[r]) {
-        if (VEC) {
-            for (int c = 4 * t; c < d_in; c += 1024) {
-                *reinterpret_cast<uint32_t*>(mask_out + row0 + c) = 0u;
-                *reinterpret_cast<float4*>(W_out + row0 + c) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            }
+    auto survives = [&](int e) { return ((surv[e / 32] >> (e % 32)) & 1u) != 0; };
+
+    int kept = 0;
+    {
+        int mine = 0;
+#pragma unroll
+        for (int i = 0; i < (N + 31) / 32; ++i) mine += __popc(surv[i]);
+        for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off, 64);
+        kept = __builtin_amdgcn_readfirstlane(mine);
+    }
+    const int target = (int)k_new;   // at most d_in
+    // trim: the row keeps its `target` largest surviving weights; grow: the `target - kept` largest gradients among its free positions
+    const bool trim = kept > target;
+    const int want = trim ? target : target - kept;
+    int T = 0, last_col = d_in;      // a candidate is chosen if its rank is above T, or T and its column at most last_col
+    if (stays && want > 0) {
+#pragma unroll
+        for (int e = 0; e < N; ++e)
+            if (survives(e) != trim) rank[e] = -1 - (rank[e] >= 0 ? 1 : 0);   // not a candidate (-2: a column all the same)
+        auto count = [&](int thr) {
+            int n = 0;
+#pragma unroll
+            for (int e = 0; e < N; ++e) n += __popcll(__ballot(rank[e] >= thr));
+            return n;
+        };
+        int at_T = -1;
+#pragma unroll 1
+        for (int bit = 30; bit >= 0; --bit) {
+            const int probe = T | (1 << bit);
+            const int n = count(probe);
+            if (n >= want) { T = probe; at_T = n; }
+            if (n == want) break;
+        }
+        if (at_T != want) {   // equal ranks on both sides of the border (or T = 0): the lowest columns of them
+            const int r_eq = want - count(T + 1);
+            auto eq_below = [&](int col) {
+                int n = 0;
+#pragma unroll
+                for (int e = 0; e < N; ++e) {
+                    const int own = col0(e / 4), c = (quads ? quad_first(own, d_in) : 0) + e % 4;
+                    n += __popcll(__ballot(rank[e] == T && c < col));
+                }
+                return n;
+            };
+            int c = 0;            // the largest column with fewer than r_eq equal ranks in front of it
+            for (int bit = 13; bit >= 0; --bit)
+                if (c + (1 << bit) <= d_in && eq_below(c + (1 << bit)) < r_eq) c += 1 << bit;
+            last_col = c;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int own = col0(q), first = quads ? quad_first(own, d_in) : 0;
+        if (own >= d_in) continue;
+        bool keep[4], grow[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int e = 4 * q + j, c = first + j;
+            const bool sv = survives(e);
+            const bool chosen = want > 0 && rank[e] >= 0 && (rank[e] > T || (rank[e] == T && c <= last_col));
+            keep[j] = stays && sv && (!trim || chosen);
+            grow[j] = stays && !sv && !trim && chosen;
+        }
+        float4 w = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (HOLD) {
+            if (stays) w = held[q];
+        } else if (keep[0] || keep[1] || keep[2] || keep[3]) {
+            const F4 v = *reinterpret_cast<const F4*>(W + row0 + first);   // (rows this long have whole groups)
+            w = make_float4(v.x, v.y, v.z, v.w);
+        }
+        const F4 o = {keep[0] ? w.x : 0.0f, keep[1] ? w.y : 0.0f, keep[2] ? w.z : 0.0f, keep[3] ? w.w : 0.0f};
+        const uint32_t m = (uint32_t)(keep[0] || grow[0]) | ((uint32_t)(keep[1] || grow[1]) << 8) | ((uint32_t)(keep[2] || grow[2]) << 16) |
+                           ((uint32_t)(keep[3] || grow[3]) << 24);
+        if (quads && first == own) {
+            __builtin_memcpy(mask_out + row0 + first, &m, 4);
+            *reinterpret_cast<F4*>(W_out + row0 + first) = o;
         } else {
-            for (int c = t; c < d_in; c += 256) { mask_out[row0 + c] = 0; W_out[row0 + c] = 0.0f; }
-        }
-        return;
-    }
-    unsigned long long key[CPT];
-    unsigned int survives = 0, valid = 0;   // bit j: the thread's j-th column
-    if (t == 0) n_kept = 0;
-    __syncthreads();
-    const unsigned long long t_prune = prune_threshold;
-    const long long k_new = new_fan_in;
-    auto take = [&](int j, int c, float w, float g, uint8_t m) {
-        valid |= 1u << j;
-        const unsigned int i = row0 + c;
-        if (m != 0 && key_small_first(mag_bits(w), i) < t_prune) {
-            survives |= 1u << j;
-            key[j] = key_large_first(mag_bits(w), (unsigned int)c);
-        } else {
-            key[j] = key_large_first(mag_bits(g), (unsigned int)c);
-        }
-    };
+            const float of[4] = {o.x, o.y, o.z, o.w};
 #pragma unroll
-    for (int j = 0; j < CPT; ++j) key[j] = 0;
-    if (VEC) {
-#pragma unroll
-        for (int q = 0; q < CPT / 4; ++q) {
-            const int c0 = 4 * (t + 256 * q);
-            if (c0 < d_in) {
-                // all three loads go out at once (the lines are fetched either way)
-                const float4 w4 = kEarly ? pw[kEarly ? q : 0] : *reinterpret_cast<const float4*>(W + row0 + c0);
-                const float4 g4 = kEarly ? pg[kEarly ? q : 0] : *reinterpret_cast<const float4*>(grad + row0 + c0);
-                const uint32_t m4 = kEarly ? pm[kEarly ? q : 0] : *reinterpret_cast<const uint32_t*>(mask + row0 + c0);
-                take(4 * q + 0, c0 + 0, w4.x, g4.x, (uint8_t)(m4 & 0xffu));
-                take(4 * q + 1, c0 + 1, w4.y, g4.y, (uint8_t)((m4 >> 8) & 0xffu));
-                take(4 * q + 2, c0 + 2, w4.z, g4.z, (uint8_t)((m4 >> 16) & 0xffu));
-                take(4 * q + 3, c0 + 3, w4.w, g4.w, (uint8_t)(m4 >> 24));
+            for (int j = 0; j < 4; ++j) {
+                const int c = first + j;
+                if (c >= own && c < d_in) {
+                    mask_out[row0 + c] = (uint8_t)(m >> (8 * j));
+                    W_out[row0 + c] = of[j];
+                }
             }
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < CPT; ++j) {
-            const int c = t + 256 * j;
-            if (c < d_in) {
-                const unsigned int i = row0 + c;
-                const float w = W[i], g = grad[i];
-                const uint8_t m = mask[i];
-                take(j, c, w, g, m);
-            }
-        }
-    }
-    if (survives) atomicAdd(&n_kept, __popc(survives));
-    __syncthreads();
-    const long long kept = n_kept;
-    unsigned long long t_keep = 0;       // keep a surviving weight iff its key >= t_keep
-    unsigned long long t_grow = ~0ull;   // grow a free position iff its key >= t_grow
-    if (kept > k_new) {
-        if (k_new == 0) t_keep = ~0ull;
-        else t_keep = row_select<CPT>((unsigned long long)k_new, [&](int j, unsigned long long& k_out) {
-            k_out = key[j];
-            return ((survives >> j) & 1u) != 0;
-        }, h);
-    } else if (kept < k_new) {
-        t_grow = row_select<CPT>((unsigned long long)(k_new - kept), [&](int j, unsigned long long& k_out) {
-            k_out = key[j];
-            return ((valid >> j) & 1u) != 0 && ((survives >> j) & 1u) == 0;
-        }, h);
-    }
-    // column j of the thread: kept (its weight is copied), grown (weight zero) or free
-    auto kept_j = [&](int j) { return ((survives >> j) & 1u) != 0 && key[j] >= t_keep; };
-    auto grown_j = [&](int j) { return ((valid >> j) & 1u) != 0 && ((survives >> j) & 1u) == 0 && key[j] >= t_grow; };
-    if (VEC) {
-#pragma unroll
-        for (int q = 0; q < CPT / 4; ++q) {
-            const int c0 = 4 * (t + 256 * q);
-            if (c0 >= d_in) continue;
-            const bool k0 = kept_j(4 * q), k1 = kept_j(4 * q + 1), k2 = kept_j(4 * q + 2), k3 = kept_j(4 * q + 3);
-            float4 w4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (k0 || k1 || k2 || k3) w4 = *reinterpret_cast<const float4*>(W + row0 + c0);
-            const uint32_t m4 = (uint32_t)(k0 || grown_j(4 * q)) | ((uint32_t)(k1 || grown_j(4 * q + 1)) << 8) |
-                                ((uint32_t)(k2 || grown_j(4 * q + 2)) << 16) | ((uint32_t)(k3 || grown_j(4 * q + 3)) << 24);
-            *reinterpret_cast<uint32_t*>(mask_out + row0 + c0) = m4;
-            *reinterpret_cast<float4*>(W_out + row0 + c0) = make_float4(k0 ? w4.x : 0.0f, k1 ? w4.y : 0.0f, k2 ? w4.z : 0.0f, k3 ? w4.w : 0.0f);
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < CPT; ++j) {
-            const int c = t + 256 * j;
-            if (c >= d_in) continue;
-            const bool kj = kept_j(j);
-            mask_out[row0 + c] = (uint8_t)(kj || grown_j(j));
-            W_out[row0 + c] = kj ? W[row0 + c] : 0.0f;
         }
     }
 }
@@ -608,29 +675,8 @@ __global__ void k_update_report_empty(long long* __restrict__ report) {
     if (threadIdx.x < 4) report[threadIdx.x] = 0;
 }
 
-template <bool PAIR>
-static void layer_select(const float* W, const uint8_t* mask, const float* grad, const int* remains, unsigned int N, int d_in,
-                         UpdateScratch* s, unsigned long long* candA, unsigned long long* candB, unsigned long long cap, hipStream_t st) {
-    const bool vec = d_in % 4 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0 && reinterpret_cast<uintptr_t>(grad) % 16 == 0 &&
-                     reinterpret_cast<uintptr_t>(mask) % 4 == 0;
-    // a thread takes 1 or 4 elements per step and at least 8 steps (every workgroup ends with up to 512 atomics), at most
-    // four workgroups per compute unit
-    const unsigned int per_step = (vec ? 4u : 1u) * kPassThreads;
-    unsigned int blocks = (N / 8 + per_step - 1) / per_step;
-    if (blocks > 1024) blocks = 1024;
-    if (blocks == 0) blocks = 1;
-#define SRIGL_HIST(COMPACT, VEC)                                                                                                   \
-    hipLaunchKernelGGL((k_layer_hist<PAIR, COMPACT, VEC>), dim3(blocks), dim3(kPassThreads), 0, st, W, mask, grad, remains, N, d_in, pass, s, \
-                       candA, candB, cap)
-    for (int pass = 0; pass < 8; ++pass) {
-        if (pass == kCompactPass && cap > 0) { if (vec) SRIGL_HIST(true, true); else SRIGL_HIST(true, false); }
-        else { if (vec) SRIGL_HIST(false, true); else SRIGL_HIST(false, false); }
-    }
-#undef SRIGL_HIST
-}
-
-// Keys per candidate list: a sixteenth of the layer, at least 4096 (a list holds the keys that share 16 leading bits with
-// the threshold: a fraction of a percent of real-valued contents; constant contents overflow it and do without).
+// Keys per candidate list: a sixteenth of the layer, at least 4096 (a list holds the keys that share the threshold's first
+// digit: about a percent of real-valued contents, three at most; constant contents do without).
 static size_t cand_capacity(int32_t d_out, int32_t d_in) {
     const size_t n = (d_out > 0 && d_in > 0) ? (size_t)d_out * (size_t)d_in : 0;
     const size_t c = n / 16;
@@ -658,7 +704,7 @@ srigl_status srigl_mask_update(const float* W, const uint8_t* mask, const float*
     if (d_out < 0 || d_in < 0 || k < 0 || k > d_in || K_upd < 0 || gamma_percent < 0 || budget < 0 || report_dev == nullptr)
         return SRIGL_ERR_INVALID_ARG;
     if ((long long)d_out * d_in >= (1ll << 32)) return SRIGL_ERR_UNSUPPORTED;   // positions are ranked as 32-bit numbers
-    if (d_in > 8192) return SRIGL_ERR_UNSUPPORTED;                              // a row is held in the registers of one workgroup
+    if (d_in > 8192) return SRIGL_ERR_UNSUPPORTED;                              // a row is held in the registers of one wavefront
     if (workspace == nullptr) return SRIGL_ERR_INVALID_ARG;
     if (workspace_bytes < srigl_mask_update_workspace_bytes(d_out, d_in)) return SRIGL_ERR_CAPACITY;
     const unsigned int N = (unsigned int)((long long)d_out * d_in);
@@ -673,25 +719,37 @@ srigl_status srigl_mask_update(const float* W, const uint8_t* mask, const float*
         hipLaunchKernelGGL(k_update_report_empty, dim3(1), dim3(64), 0, st, report);
         return hip_ok(hipGetLastError());
     }
-    // 19 launches, each reading what the one before it counted: the state, 8 passes of steps 1-3, the per-neuron counts of
-    // steps 3-5, 8 passes of step 6, and step 7 (which also writes the report)
-    hipLaunchKernelGGL(k_update_init, dim3(48), dim3(256), 0, st, s, (long long)K_upd);
-    layer_select<true>(W, mask, grad, remains, N, d_in, s, candA, candB, cap, st);
-    const bool vec_in = d_in % 4 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0 && reinterpret_cast<uintptr_t>(grad) % 16 == 0 &&
-                        reinterpret_cast<uintptr_t>(mask) % 4 == 0;
-    if (vec_in) hipLaunchKernelGGL(k_row_salient<true>, dim3((d_out + 3) / 4), dim3(256), 0, st, W, mask, grad, d_out, d_in, k, gamma_percent, s, remains);
-    else hipLaunchKernelGGL(k_row_salient<false>, dim3((d_out + 3) / 4), dim3(256), 0, st, W, mask, grad, d_out, d_in, k, gamma_percent, s, remains);
-    layer_select<false>(W, mask, grad, remains, N, d_in, s, candA, candB, cap, st);
-    // 16-byte moves need rows that start on 16-byte (mask: 4-byte) boundaries
-    const bool vec = vec_in && reinterpret_cast<uintptr_t>(W_out) % 16 == 0 && reinterpret_cast<uintptr_t>(mask_out) % 4 == 0;
-#define SRIGL_ROW_UPDATE(CPT)                                                                                                      \
-    if (vec) hipLaunchKernelGGL((k_row_update<CPT, true>), dim3(d_out), dim3(256), 0, st, W, mask, grad, d_in, remains, s,         \
-                                (long long)K_upd, (long long)budget, mask_out, W_out, report);                                     \
-    else hipLaunchKernelGGL((k_row_update<CPT, false>), dim3(d_out), dim3(256), 0, st, W, mask, grad, d_in, remains, s,            \
-                            (long long)K_upd, (long long)budget, mask_out, W_out, report)
-    if (d_in <= 1024) { SRIGL_ROW_UPDATE(4); }
-    else if (d_in <= 4096) { SRIGL_ROW_UPDATE(16); }
-    else { SRIGL_ROW_UPDATE(32); }
+    // eight launches, each reading what the ones before it counted
+    hipLaunchKernelGGL(k_update_init, dim3(64), dim3(256), 0, st, reinterpret_cast<uint4*>(s));
+    // quads of the flat layer (16-byte moves need aligned arrays; rows of any length); at most one workgroup per compute unit
+    const bool vec = reinterpret_cast<uintptr_t>(W) % 16 == 0 && reinterpret_cast<uintptr_t>(grad) % 16 == 0 && reinterpret_cast<uintptr_t>(mask) % 4 == 0;
+    const unsigned int n4 = vec ? N / 4 : 0;
+    unsigned int blocks = (unsigned int)(((unsigned long long)N + 4 * kScanThreads - 1) / (4 * kScanThreads));
+    if (blocks > 256) blocks = 256;
+    hipLaunchKernelGGL(k_hist, dim3(blocks), dim3(kScanThreads), 0, st, W, mask, grad, N, n4, s);
+    hipLaunchKernelGGL(k_collect<true>, dim3(blocks), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, n4, d_in, (unsigned long long)K_upd, s,
+                       candA, candB, cap);
+    hipLaunchKernelGGL(k_final<true>, dim3(2), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, d_in, s, candA, candB, cap,
+                       (unsigned long long)K_upd, (long long)budget, report);
+    const dim3 row_grid((unsigned)((d_out + 3) / 4));
+    hipLaunchKernelGGL(k_row_salient, row_grid, dim3(256), 0, st, W, mask, grad, d_out, d_in, k, gamma_percent, s, remains);
+    hipLaunchKernelGGL(k_collect<false>, dim3(blocks), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, n4, d_in, (unsigned long long)K_upd, s,
+                       candA, candB, cap);
+    hipLaunchKernelGGL(k_final<false>, dim3(1), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, d_in, s, candA, candB, cap,
+                       (unsigned long long)K_upd, (long long)budget, report);
+#define SRIGL_ROW_UPDATE(NQ) \
+    hipLaunchKernelGGL(k_row_update<NQ>, row_grid, dim3(256), 0, st, W, mask, grad, d_out, d_in, remains, s, mask_out, W_out)
+    const int nq = (d_in + 255) / 256;
+    if (nq <= 1) SRIGL_ROW_UPDATE(1);
+    else if (nq <= 2) SRIGL_ROW_UPDATE(2);
+    else if (nq <= 3) SRIGL_ROW_UPDATE(3);
+    else if (nq <= 4) SRIGL_ROW_UPDATE(4);
+    else if (nq <= 6) SRIGL_ROW_UPDATE(6);
+    else if (nq <= 8) SRIGL_ROW_UPDATE(8);
+    else if (nq <= 12) SRIGL_ROW_UPDATE(12);
+    else if (nq <= 16) SRIGL_ROW_UPDATE(16);
+    else if (nq <= 24) SRIGL_ROW_UPDATE(24);
+    else SRIGL_ROW_UPDATE(32);
 #undef SRIGL_ROW_UPDATE
     return hip_ok(hipGetLastError());
 }
