@@ -100,7 +100,7 @@ __device__ __forceinline__ void each_of_quad(const Quad& q, unsigned int base, E
 // digits of one wavefront's values spread over some fifty of the 4096, so its adds meet at most a few times per address.
 __global__ __launch_bounds__(kScanThreads) void k_hist(const float* __restrict__ W, const uint8_t* __restrict__ mask, const float* __restrict__ grad,
                                                        unsigned int N, unsigned int n4, UpdateScratch* __restrict__ s) {
-    __shared__ unsigned int h[2][kDigits];
+    __shared__ __align__(16) unsigned int h[2][kDigits];
     const int t = threadIdx.x;
     const unsigned int per = (n4 + gridDim.x - 1) / gridDim.x, q0 = min(blockIdx.x * per, n4), q1 = min(q0 + per, n4);
     Quad q[kQuads];
@@ -119,37 +119,53 @@ __global__ __launch_bounds__(kScanThreads) void k_hist(const float* __restrict__
     }
     for (unsigned int i = 4 * n4 + blockIdx.x * kScanThreads + t; i < N; i += gridDim.x * kScanThreads) element(i, mask[i], W[i], grad[i]);
     __syncthreads();
+    // neighbouring lanes add to neighbouring digits (an atomic instruction costs by the lines it touches: with four digits in a
+    // row per thread the flush took half of the kernel's 11 us)
     const int copy = blockIdx.x % kHistCopies;
 #pragma unroll
     for (int sel = 0; sel < 2; ++sel) {
-        const uint4 v = reinterpret_cast<const uint4*>(h[sel])[t];   // digits 4t .. 4t + 3
-        unsigned int* dst = &s->hist[sel][copy][4 * t];
-        if (v.x) atomicAdd(dst, v.x);
-        if (v.y) atomicAdd(dst + 1, v.y);
-        if (v.z) atomicAdd(dst + 2, v.z);
-        if (v.w) atomicAdd(dst + 3, v.w);
-        unsigned int c = v.x + v.y + v.z + v.w;
-        c += __shfl_xor(c, 1, 64);
-        c += __shfl_xor(c, 2, 64);
-        if ((t & 3) == 0 && c) atomicAdd(&s->coarse[sel][copy][t >> 2], c);
+#pragma unroll
+        for (int j = 0; j < kDigits / kScanThreads; ++j) {
+            const unsigned int n = h[sel][t + j * kScanThreads];
+            if (n) atomicAdd(&s->hist[sel][copy][t + j * kScanThreads], n);
+        }
+    }
+    if (t < 2 * kCoarse) {
+        const int sel = t / kCoarse, c = t % kCoarse;
+        unsigned int n = 0;
+#pragma unroll
+        for (int j = 0; j < kFine / 4; ++j) {
+            const uint4 v = reinterpret_cast<const uint4*>(&h[sel][c * kFine])[j];
+            n += v.x + v.y + v.z + v.w;
+        }
+        if (n) atomicAdd(&s->coarse[sel][copy][c], n);
     }
 }
-static_assert(kFine == 16 && kDigits == 4 * kScanThreads, "four digits per thread, sixteen per coarse count");
+static_assert(kFine == 16 && kDigits == 4 * kScanThreads, "sixteen digits per coarse count, four per thread");
 
-// With n[l] keys in bin l of this wavefront's lane l: the bin d with suffix(d) >= want > suffix(d + 1), suffix(d) = keys in
-// bins d and above; `above` = suffix(d + 1), `in_bin` = n[d], `total` = suffix(0).  The results are the same on every lane.
-__device__ __forceinline__ void pick_lane(unsigned long long n, unsigned long long want, int lane, int& bin, unsigned long long& above,
-                                          unsigned long long& in_bin, unsigned long long& total) {
-    unsigned long long incl = n;   // becomes the sum over this lane and the lanes above it
-    for (int off = 1; off < 64; off <<= 1) {
-        const unsigned long long up = __shfl_down(incl, off, 64);
-        if (lane + off < 64) incl += up;
-    }
-    total = __shfl(incl, 0, 64);
-    const unsigned long long owner = __ballot(incl >= want && incl - n < want);
+// Sum of v over this lane and the lanes below it (DPP: a cross-lane read through the LDS network costs some sixty clocks).
+__device__ __forceinline__ unsigned int wave_prefix(unsigned int v) {
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);   // row_shr:1
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+    return v;
+}
+__device__ __forceinline__ unsigned int wave_total(unsigned int v) { return (unsigned)__builtin_amdgcn_readlane((int)wave_prefix(v), 63); }
+
+// With n keys in this lane's bin: the bin d with suffix(d) >= want > suffix(d + 1), suffix(d) = keys in bins d and above;
+// `above` = suffix(d + 1), `in_bin` = the bin's keys, `total` = suffix(0).  The results are the same on every lane.
+__device__ __forceinline__ void pick_lane(unsigned int n, unsigned int want, int& bin, unsigned int& above, unsigned int& in_bin,
+                                          unsigned int& total) {
+    const unsigned int incl = wave_prefix(n);
+    total = (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
+    const unsigned int beyond = total - incl;   // keys in the bins above this lane's
+    const uint64_t owner = __ballot(beyond < want && beyond + n >= want);
     bin = owner ? __builtin_ctzll(owner) : 0;
-    above = __shfl(incl - n, bin, 64);
-    in_bin = __shfl(n, bin, 64);
+    above = (unsigned)__builtin_amdgcn_readlane((int)beyond, bin);
+    in_bin = (unsigned)__builtin_amdgcn_readlane((int)n, bin);
 }
 
 // The state of a selection after its first digit, from the layer-wide counters.  One whole wavefront; the same on every lane.
@@ -162,37 +178,35 @@ __device__ SelState pick_first(const UpdateScratch* __restrict__ s, int hist, un
     }
     SelState st;
     st.prefix = 0; st.k_rem = K; st.in_bin = 0; st.done = 0;
-    int group;
-    unsigned long long above, in_bin, total;
-    pick_lane((unsigned long long)v[0] + v[1] + v[2] + v[3], K == 0 ? 1 : K, lane, group, above, in_bin, total);
+    int group, sub, fine;
+    unsigned int above, in_bin, total;
+    pick_lane(v[0] + v[1] + v[2] + v[3], K == 0 ? 1u : (unsigned)min(K, 0xffffffffull), group, above, in_bin, total);
     st.total = total;
     if (K == 0 || total < K) {
         st.prefix = K == 0 ? ~0ull : 0ull;   // nothing / everything
         st.done = 1;
         return st;
     }
-    st.k_rem -= above;
+    unsigned int want = (unsigned)K - above;
     // the coarse digit inside the chosen group of four, then the digit inside the coarse one
-    unsigned long long mine = 0;
+    unsigned int mine = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const unsigned int x = __shfl(v[j], group, 64);
+        const unsigned int x = (unsigned)__builtin_amdgcn_readlane((int)v[j], group);
         if (lane == j) mine = x;
     }
-    int sub;
-    pick_lane(mine, st.k_rem, lane, sub, above, in_bin, total);
-    st.k_rem -= above;
+    pick_lane(mine, want, sub, above, in_bin, total);
+    want -= above;
     const int coarse = 4 * group + sub;
     unsigned int n = 0;
 #pragma unroll
     for (int c = 0; c < kHistCopies; c += 4) n += s->hist[hist][c + (lane >> 4)][coarse * kFine + (lane & 15)];
     n += __shfl_xor(n, 16, 64);
     n += __shfl_xor(n, 32, 64);
-    int fine;
-    pick_lane(lane < kFine ? n : 0, st.k_rem, lane, fine, above, in_bin, total);
-    st.k_rem -= above;
+    pick_lane(lane < kFine ? n : 0u, want, fine, above, in_bin, total);
+    st.k_rem = want - above;
     st.prefix = coarse * kFine + fine;
-    st.in_bin = (unsigned int)in_bin;
+    st.in_bin = in_bin;
     if (st.k_rem == in_bin) {   // every key of the digit is wanted: the threshold is the smallest key with this prefix
         st.prefix <<= kDigitShift;
         st.done = 1;
@@ -202,9 +216,7 @@ __device__ SelState pick_first(const UpdateScratch* __restrict__ s, int hist, un
 
 // Sum of the 64 copies of a neuron counter.  Called by one whole wavefront; the result is the same on every lane.
 __device__ __forceinline__ unsigned int sum_copies(const unsigned int (&c)[kCountCopies], int lane) {
-    unsigned int n = c[lane];
-    for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off, 64);
-    return n;
+    return wave_total(c[lane]);
 }
 
 // Lists the keys of the first digit that holds the K-th key.  PAIR: selections 0 and 1 together, otherwise selection 2 (kept
@@ -275,6 +287,7 @@ __global__ __launch_bounds__(kScanThreads) void k_collect(const float* __restric
         if (t < 2) n_staged[t] = 0;
         __syncthreads();
     };
+    int batches = 0;
     for (unsigned int b = q0; b < q1; b += kQuads * kScanThreads) {
         if (b != q0) load_quads<PAIR>(q, W, mask, grad, b, q1);
 #pragma unroll
@@ -282,26 +295,27 @@ __global__ __launch_bounds__(kScanThreads) void k_collect(const float* __restric
             const unsigned int i = b + u * kScanThreads + t;
             if (i < q1) each_of_quad(q[u], 4 * i, element);
         }
-        if (b + kQuads * kScanThreads < q1) flush();
+        if (++batches % 4 == 0 && b + kQuads * kScanThreads < q1) flush();   // (65536 elements, three percent of which the stage holds)
     }
     for (unsigned int i = 4 * n4 + blockIdx.x * kScanThreads + t; i < N; i += gridDim.x * kScanThreads)
         element(i, mask[i], W[i], PAIR ? grad[i] : 0.0f);
     flush();
 }
 
-// The end of a selection: workgroup b takes selection b (PAIR) or 2.  The keys come from the list (held in registers up to
-// kHeld per thread), or from the layer when there is no valid list.  12-bit digits until at most kDirect keys share the
+// The end of a selection: workgroup b takes selection b (PAIR) or 2.  The keys come from the list, or from the layer when there
+// is no valid list.  One workgroup runs this code once, so its length counts: with the list held in registers and every loop
+// unrolled over it, fetching the instructions took most of 10 us.  12-bit digits until at most kDirect keys share the
 // prefix (one pass on real-valued contents), which are then ranked against each other.
 // Step 6's workgroup also takes the new fan-in from the neuron counters (step 5) and writes the report.
-constexpr int kHeld = 32, kDirect = 256;
+constexpr int kAhead = 8, kDirect = 256;
 template <bool PAIR>
 __global__ __launch_bounds__(kScanThreads) void k_final(const float* __restrict__ W, const uint8_t* __restrict__ mask, const float* __restrict__ grad,
                                                         const int* __restrict__ remains, unsigned int N, int d_in, UpdateScratch* __restrict__ s,
                                                         const unsigned long long* __restrict__ candA, const unsigned long long* __restrict__ candB,
                                                         unsigned long long cap, unsigned long long K, long long budget,
                                                         long long* __restrict__ report) {
-    __shared__ unsigned int h[kDigits];
-    __shared__ unsigned int group_sum[64];
+    __shared__ __align__(16) unsigned int h[kDigits];
+    __shared__ unsigned int wave_sum[kScanThreads / 64];
     __shared__ SelState cur;
     __shared__ unsigned long long direct[kDirect];
     __shared__ unsigned int n_direct;
@@ -330,25 +344,23 @@ __global__ __launch_bounds__(kScanThreads) void k_final(const float* __restrict_
         }
     };
     if (st.done) { finish(); return; }
-    const unsigned long long n_list = st.in_bin;   // (every key of the digit is in the list, or there is none)
-    const bool listed = n_list <= cap;
+    const unsigned int n = st.in_bin;   // (every key of the digit is in the list, or there is none)
+    const bool listed = n <= cap;
     const unsigned long long* const list = sel == 1 ? candB : candA;
-    const bool held = listed && n_list <= (unsigned long long)kHeld * kScanThreads;
-    unsigned long long key[kHeld];
-    if (held) {
-#pragma unroll
-        for (int j = 0; j < kHeld; ++j) {
-            const unsigned int i = j * kScanThreads + t;
-            key[j] = i < n_list ? list[i] : 0ull;
-        }
-    }
     auto each = [&](auto f) {
-        if (held) {
+        if (listed) {
+#pragma unroll 1
+            for (unsigned int i0 = t; 2 * i0 < n; i0 += kAhead * kScanThreads) {   // two keys per load
+                ulonglong2 key[kAhead];
 #pragma unroll
-            for (int j = 0; j < kHeld; ++j)
-                if (j * kScanThreads + t < (int)n_list) f(key[j]);
-        } else if (listed) {
-            for (unsigned long long i = t; i < n_list; i += kScanThreads) f(list[i]);
+                for (int j = 0; j < kAhead; ++j) key[j] = reinterpret_cast<const ulonglong2*>(list)[min(i0 + j * kScanThreads, (n - 1u) / 2u)];
+#pragma unroll
+                for (int j = 0; j < kAhead; ++j) {
+                    const unsigned int i = 2 * (i0 + j * kScanThreads);
+                    if (i < n) f(key[j].x);
+                    if (i + 1 < n) f(key[j].y);
+                }
+            }
         } else {
             for (unsigned long long i = t; i < N; i += kScanThreads) {
                 const unsigned int ii = (unsigned int)i;
@@ -368,11 +380,11 @@ __global__ __launch_bounds__(kScanThreads) void k_final(const float* __restrict_
                 if ((k >> shift) == st.prefix) direct[min(atomicAdd(&n_direct, 1u), (unsigned)kDirect - 1)] = k;
             });
             __syncthreads();
-            const unsigned int n = min(n_direct, (unsigned)kDirect);
-            if (t < (int)n) {   // the k_rem-th largest
+            const unsigned int n_here = min(n_direct, (unsigned)kDirect);
+            if (t < (int)n_here) {   // the k_rem-th largest
                 const unsigned long long mine = direct[t];
                 unsigned int larger = 0;
-                for (unsigned int j = 0; j < n; ++j) larger += direct[j] > mine ? 1u : 0u;
+                for (unsigned int j = 0; j < n_here; ++j) larger += direct[j] > mine ? 1u : 0u;
                 if (larger + 1 == st.k_rem) cur.prefix = mine;
             }
             __syncthreads();
@@ -388,27 +400,29 @@ __global__ __launch_bounds__(kScanThreads) void k_final(const float* __restrict_
             if ((k >> shift) == st.prefix) atomicAdd(&h[(unsigned int)(k >> next) & ((1u << bits) - 1u)], 1u);
         });
         __syncthreads();
-        for (int g = t >> 6; g < kDigits / 64; g += kScanThreads / 64) {   // 64 groups of 64 digits
-            unsigned int n = h[64 * g + lane];
-            for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off, 64);
-            if (lane == 0) group_sum[g] = n;
-        }
+        // thread t has digits 4t .. 4t + 3; keys in the digits above a thread's: in its wavefront's higher lanes and the higher wavefronts
+        const uint4 c4 = reinterpret_cast<const uint4*>(h)[t];
+        const unsigned int mine = c4.x + c4.y + c4.z + c4.w, incl = wave_prefix(mine);
+        if (lane == 63) wave_sum[t >> 6] = incl;
         __syncthreads();
-        if (t < 64) {
-            int group, bin;
-            unsigned long long above, in_bin, total;
+        unsigned int beyond = (unsigned)__builtin_amdgcn_readlane((int)incl, 63) - incl;
+        for (int w = kScanThreads / 64 - 1; w > (t >> 6); --w) beyond += wave_sum[w];
+        const unsigned int want = (unsigned)st.k_rem;
+        if (beyond < want && beyond + mine >= want) {
+            unsigned int above = beyond, in_bin = c4.w;
+            int digit = 4 * t + 3;
+            if (above + in_bin < want) { above += c4.w; in_bin = c4.z; --digit; }
+            if (digit == 4 * t + 2 && above + in_bin < want) { above += c4.z; in_bin = c4.y; --digit; }
+            if (digit == 4 * t + 1 && above + in_bin < want) { above += c4.y; in_bin = c4.x; --digit; }
             SelState c = st;
-            pick_lane(group_sum[lane], c.k_rem, lane, group, above, in_bin, total);
-            c.k_rem -= above;
-            pick_lane(h[64 * group + lane], c.k_rem, lane, bin, above, in_bin, total);
-            c.k_rem -= above;
-            c.prefix = (c.prefix << bits) | (unsigned)(64 * group + bin);
-            c.in_bin = (unsigned int)in_bin;
+            c.k_rem = want - above;
+            c.prefix = (c.prefix << bits) | (unsigned)digit;
+            c.in_bin = in_bin;
             if (c.k_rem == in_bin || next == 0) {
                 c.prefix <<= next;
                 c.done = 1;
             }
-            if (lane == 0) cur = c;
+            cur = c;
         }
         __syncthreads();
         st = cur;
@@ -417,7 +431,7 @@ __global__ __launch_bounds__(kScanThreads) void k_final(const float* __restrict_
         if (st.done) { finish(); return; }
     }
 }
-static_assert(kDigits == 64 * 64, "two picks among 64");
+static_assert(kDigits == 4 * kScanThreads, "four digits per thread");
 
 // Four consecutive columns of a row, at any alignment of the row: the last group of a row that does not end on a group
 // boundary reads the row's last four columns and owns only those its neighbour does not have.
@@ -500,7 +514,8 @@ __global__ __launch_bounds__(256) void k_row_salient(const float* __restrict__ W
             load_row_short(q, W, mask, grad, row0, d_in);
             quad(q, 0, 0);
         }
-        for (int off = 32; off > 0; off >>= 1) { h += __shfl_xor(h, off, 64); sal += __shfl_xor(sal, off, 64); }
+        h = (int)wave_total((unsigned)h);
+        sal = (int)wave_total((unsigned)sal);
         const bool ablated = h > 0 && (sal < 1 || (long long)sal * 100 < (long long)gamma_percent * k);
         if (lane == 0) {
             if (ablated) atomicAdd(&wg_ablated, 1);
@@ -526,8 +541,8 @@ __global__ __launch_bounds__(256) void k_row_salient(const float* __restrict__ W
 
 // Steps 6 (applied) and 7.  One wavefront per row; lane l holds columns 4 (l + 64 q) .. + 3, q < NQ (d_in <= 256 NQ).  A column
 // is ranked by one number (its weight's magnitude if it survives step 6, else its gradient's), equal numbers by column.  The
-// `want`-th largest among the row's candidates is searched bit by bit: NQ x 4 compares, their ballots counted by scalar
-// instructions, per bit, until a threshold splits off exactly `want` (about 20 of 31 bits on real-valued contents).
+// `want`-th largest among the row's candidates is searched by counting (NQ x 4 compares, their ballots counted by scalar
+// instructions) until a threshold splits off exactly `want`.
 template <int NQ>
 __global__ __launch_bounds__(256) void k_row_update(const float* __restrict__ W, const uint8_t* __restrict__ mask, const float* __restrict__ grad,
                                                     int d_out, int d_in, const int* __restrict__ remains, const UpdateScratch* __restrict__ s,
@@ -587,8 +602,7 @@ __global__ __launch_bounds__(256) void k_row_update(const float* __restrict__ W,
         int mine = 0;
 #pragma unroll
         for (int i = 0; i < (N + 31) / 32; ++i) mine += __popc(surv[i]);
-        for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off, 64);
-        kept = __builtin_amdgcn_readfirstlane(mine);
+        kept = (int)wave_total((unsigned)mine);
     }
     const int target = (int)k_new;   // at most d_in
     // trim: the row keeps its `target` largest surviving weights; grow: the `target - kept` largest gradients among its free positions
@@ -605,16 +619,40 @@ __global__ __launch_bounds__(256) void k_row_update(const float* __restrict__ W,
             for (int e = 0; e < N; ++e) n += __popcll(__ballot(rank[e] >= thr));
             return n;
         };
-        int at_T = -1;
-#pragma unroll 1
-        for (int bit = 30; bit >= 0; --bit) {
-            const int probe = T | (1 << bit);
-            const int n = count(probe);
-            if (n >= want) { T = probe; at_T = n; }
-            if (n == want) break;
+        // count(T) >= want > count(hi).  Rows regrow close to the layer-wide gradient threshold of step 3, so the walk starts
+        // there with steps that double, and halves the interval it lands in: about 8 counts on real-valued contents, where
+        // the 31 bits one after the other took 22 (768 columns 12.1 -> 9.6 us, 2048 31.4 -> 24).
+        int at_T = -1, hi = 0x7fffffff;
+        if (!trim) {
+            const unsigned int near = (unsigned int)(s->fin[1].prefix >> 32);
+            int g = (int)min(max(near, 1u), 0x7ffffffeu), step = 1 << 20;   // (an eighth of an octave)
+            const int n = count(g);
+            if (n >= want) {
+                T = g; at_T = n;
+                while (at_T != want && step <= 0x7ffffffe - T) {
+                    const int m = count(T + step);
+                    if (m < want) { hi = T + step; break; }
+                    T += step; at_T = m; step *= 2;
+                }
+            } else {
+                hi = g;
+                while (step < hi) {
+                    const int m = count(hi - step);
+                    if (m >= want) { T = hi - step; at_T = m; break; }
+                    hi -= step; step *= 2;
+                }
+            }
+        }
+        while (at_T != want && hi - T > 1) {
+            const int mid = T + (hi - T) / 2, n = count(mid);
+            if (n >= want) { T = mid; at_T = n; } else hi = mid;
+        }
+        if (at_T != want && hi == 0x7fffffff && T == hi - 1) {   // (the one magnitude the walk leaves out)
+            const int n = count(hi);
+            if (n >= want) { T = hi; at_T = n; }
         }
         if (at_T != want) {   // equal ranks on both sides of the border (or T = 0): the lowest columns of them
-            const int r_eq = want - count(T + 1);
+            const int r_eq = want - (T == 0x7fffffff ? 0 : count(T + 1));
             auto eq_below = [&](int col) {
                 int n = 0;
 #pragma unroll
@@ -680,7 +718,7 @@ __global__ void k_update_report_empty(long long* __restrict__ report) {
 static size_t cand_capacity(int32_t d_out, int32_t d_in) {
     const size_t n = (d_out > 0 && d_in > 0) ? (size_t)d_out * (size_t)d_in : 0;
     const size_t c = n / 16;
-    return c < 4096 ? 4096 : c;
+    return c < 4096 ? 4096 : c / 2 * 2;   // (even: the second list is 16-byte aligned too)
 }
 static size_t update_head_bytes(int32_t d_out) {
     const size_t rows = d_out > 0 ? (size_t)d_out : 0;
