@@ -500,7 +500,8 @@ static RowlanePlan plan_rowlane_with(const FwdArgs& a, const srigl_fwd_tuning* t
     p.R = t && t->rows_per_lane ? t->rows_per_lane : 1;
     p.H = t && t->term_slices ? t->term_slices : 0;
     if (p.R != 1 && p.R != 2 && p.R != 4) return p;
-    // fast staging: whole 16-column units, rows aligned for 4-element vector loads
+    // aligned staging: whole 16-column units, rows aligned for 4-element vector loads (else: the same shapes on rows of any
+    // alignment, except four rows per lane)
     const size_t xal = (a.x_bf16 ? 2 : 4) * 4;
     p.fast = (a.d_in % 16 == 0) && ((reinterpret_cast<uintptr_t>(a.x) % xal) == 0);
     if (p.H == 0) {
@@ -508,10 +509,10 @@ static RowlanePlan plan_rowlane_with(const FwdArgs& a, const srigl_fwd_tuning* t
         // staging outweighs the arithmetic of the few stored rows a workgroup gets, so the tile gets fewer rows
         // (more term slices); measured on 768- and 3072-wide layers.  Large batches amortise it: 64-row tiles.
         p.H = 1;
-        if (p.fast && p.R == 1 && a.B <= 512) p.H = a.d_in <= 1024 ? 1 : (a.d_in <= 2048 ? 2 : 4);
+        if (p.R == 1 && a.B <= 512) p.H = a.d_in <= 1024 ? 1 : (a.d_in <= 2048 ? 2 : 4);
         // batches below one 64-row tile: a tile no taller than the batch keeps every lane on real rows
         // (and up to one 64-row tile two 32-row tiles run faster: twice the workgroups, half the terms per lane)
-        if (p.fast && p.R == 1) {
+        if (p.R == 1) {
             int hb = a.B <= 16 ? 4 : (a.B <= 64 ? 2 : 1);
             // inputs wider than 1024: 16-row tiles stay ahead up to a batch of 32, and up to 64 when the layer
             // has too few stored rows to fill the GPU otherwise (measured on 1536- and 2048-wide inputs)
@@ -522,7 +523,7 @@ static RowlanePlan plan_rowlane_with(const FwdArgs& a, const srigl_fwd_tuning* t
     if (p.H != 1 && p.H != 2 && p.H != 4) return p;
     if (p.R == 2 && p.H != 1 && p.H != 2 && p.H != 4) return p;
     if (p.R == 4 && p.H != 2 && p.H != 4) return p;   // four rows per lane: 128- or 64-row tiles (whole 64-row groups per term slice)
-    if (!p.fast && (p.R != 1 || p.H != 1)) return p;
+    if (!p.fast && p.R == 4) return p;
     const int BT = kWave * p.R / p.H, S = rowlane_row_stride(BT, p.H, p.R);
     if ((long long)(BT + 1) * a.d_in * 4 >= (1LL << 32)) return p;   // a lane's byte offset inside its batch tile is 32-bit
     p.n_btiles = (a.B + BT - 1) / BT;
@@ -798,7 +799,7 @@ static srigl_fwd_algo choose_chunked_or_small(const FwdArgs& a) {
         if (klane_few_lanes_staged(B, d_in, n_active, K, &few_L, &few_RB) && plan_klane(a, nullptr).ok) return SRIGL_FWD_KLANE;
     }
     bool batched = B > 16;
-    if (B > 1 && B <= 2048 && d_in % 16 == 0) {
+    if (B > 1 && B <= 2048) {
         static_assert(kKlaneTerms == 4, "klane_estimate_us assumes 4 terms per lane and request");
         const RowlanePlan rp = plan_rowlane_by_estimate(a, nullptr);   // (the comparison was fitted with this shape and estimate)
         batched = rp.ok && rowlane_estimate_us(a, rp, true) < klane_estimate_us(B, d_in, n_active, K);

@@ -91,6 +91,43 @@ __device__ __forceinline__ void load4(const uint16_t* __restrict__ p, bool vec_o
     }
 }
 
+// The same for rows at any alignment (FAST = false: rows whose length is not a multiple of 16 elements, or an unaligned x): one
+// vector load at element alignment, from element e of the tile's rows on, which hold `total` elements.  A load that would
+// run past the last one starts as many elements earlier (`ragged_shift`), and the values are moved up when they are stored.
+// What a load brings from beyond its own row's end lies in columns no index names.  (Element by element behind branches, as
+// these rows were staged before, the loads went out one round trip after the other: 1000 -> 777 at batch 37 20.6 us.)
+__device__ __forceinline__ int ragged_shift(unsigned e, int total) { return max((int)e - (total - 4), 0); }
+__device__ __forceinline__ void load4_ragged(const float* __restrict__ p, unsigned e, int total, Staged4<float>& out) {
+    struct __attribute__((packed, aligned(4))) F4 { float x, y, z, w; };
+    if (total >= 4) {
+        const F4 v = *reinterpret_cast<const F4*>(p + min((int)e, total - 4));
+        out.v[0] = v.x; out.v[1] = v.y; out.v[2] = v.z; out.v[3] = v.w;
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out.v[i] = p[min((int)e + i, total - 1)];
+    }
+}
+__device__ __forceinline__ void load4_ragged(const uint16_t* __restrict__ p, unsigned e, int total, Staged4<uint16_t>& out) {
+    struct __attribute__((packed, aligned(2))) U2 { uint32_t x, y; };
+    if (total >= 4) {
+        const U2 v = *reinterpret_cast<const U2*>(p + min((int)e, total - 4));
+        out.w[0] = v.x; out.w[1] = v.y;
+    } else {
+        out.w[0] = (uint32_t)p[min((int)e, total - 1)] | ((uint32_t)p[min((int)e + 1, total - 1)] << 16);
+        out.w[1] = (uint32_t)p[min((int)e + 2, total - 1)];
+    }
+}
+// (values moved up by `sh` places; a tile of fewer than four elements was loaded in place)
+__device__ __forceinline__ void shift4(Staged4<float>& s, int sh) {
+    if (sh & 2) { s.v[0] = s.v[2]; s.v[1] = s.v[3]; }
+    if (sh & 1) { s.v[0] = s.v[1]; s.v[1] = s.v[2]; s.v[2] = s.v[3]; }
+}
+__device__ __forceinline__ void shift4(Staged4<uint16_t>& s, int sh) {
+    const uint64_t v = (((uint64_t)s.w[1] << 32) | s.w[0]) >> (16 * sh);
+    s.w[0] = (uint32_t)v;
+    s.w[1] = (uint32_t)(v >> 32);
+}
+
 // lane n of each 16-lane row, seen by every lane of that row (folds into the consuming VALU instruction)
 template <int N>
 __device__ __forceinline__ int row_bcast(int v) {
@@ -375,6 +412,7 @@ __global__ __launch_bounds__(rowlane_max_threads(R)) void k_fwd_rowlane(const XT
     static_assert(RT == 1 || RT == 2 || RT == 4 || RT == 8, "batch tile of 16 .. 128 rows");
     // this lane's bytes are addressed from the tile's first row (a wave-uniform base) with 32-bit offsets: BT rows of x
     const char* const xtile = reinterpret_cast<const char*>(x + (size_t)b0 * d_in);
+    const int tile_total = (B - b0) * d_in;               // elements of x from the tile's first on (B * d_in < 2^31: host)
     unsigned g_off[kStageUnits];                          // byte offset from xtile of this lane's 4 columns (chunk 0)
     int l_off[kStageUnits];                               // word offset into the LDS tile
     int u_col[kStageUnits];                               // first column of the unit (wave-uniform)
@@ -407,17 +445,21 @@ __global__ __launch_bounds__(rowlane_max_threads(R)) void k_fwd_rowlane(const XT
                 const bool in_ = (live) && c0_ + u_col[u_] < d_in;                                              \
                 if (UNC) load4(reinterpret_cast<const XT*>(xtile + (in_ ? g_off[u_] + (unsigned)c0_ * (unsigned)sizeof(XT) : 0u)), true, 4, st[u_]); \
                 else if (in_) load4(reinterpret_cast<const XT*>(xtile + (g_off[u_] + (unsigned)c0_ * (unsigned)sizeof(XT))), true, 4, st[u_]); \
-            } else if (live) {                                                                                            \
-                st[u_].clear();                                                                                 \
-                const int nv = min(4, d_in - (c0_ + u_col[u_] + dq * 4));                                       \
-                if (u_col[u_] < C && nv > 0) load4(reinterpret_cast<const XT*>(xtile + (g_off[u_] + (unsigned)c0_ * (unsigned)sizeof(XT))), false, nv, st[u_]); \
+            } else {                                                                                            \
+                const bool in_ = (live) && c0_ + u_col[u_] < d_in;                                              \
+                if (UNC) load4_ragged(reinterpret_cast<const XT*>(xtile), in_ ? g_off[u_] / (unsigned)sizeof(XT) + (unsigned)c0_ : 0u, tile_total, st[u_]); \
+                else if (in_) load4_ragged(reinterpret_cast<const XT*>(xtile), g_off[u_] / (unsigned)sizeof(XT) + (unsigned)c0_, tile_total, st[u_]); \
             }                                                                                                   \
         }                                                                                                       \
     }
 #define SRIGL_STAGE_LOAD(c) SRIGL_STAGE_LOAD_UNITS(true, c, 0, kStageUnits)
-#define SRIGL_STAGE_STORE()                                                                                     \
+#define SRIGL_STAGE_STORE(c)                                                                                    \
     _Pragma("unroll") for (int i = 0; i < kStageUnits; ++i) {                                                   \
         if (u_col[i] < C) {                                                                                     \
+            if (!FAST) {   /* only the last row of x ends behind the last place a load can start at */          \
+                const int sh_ = ragged_shift(g_off[i] / (unsigned)sizeof(XT) + (unsigned)((c) * C), tile_total); \
+                if (tile_total >= 4 && __ballot(sh_ > 0) != 0) shift4(st[i], min(sh_, 3));                       \
+            }                                                                                                   \
             float* d_ = lds + l_off[i];                                                                         \
             if (H == 4 && R == 1) {   /* stride 16: odd column quads write their pairs in the other order (banks 16 apart) */ \
                 const bool odd_ = (dq & 1) != 0;                                                                \
@@ -534,7 +576,7 @@ __global__ __launch_bounds__(rowlane_max_threads(R)) void k_fwd_rowlane(const XT
             request_terms<XT, IT, PKB>(W_c, idx, pk, slot_of(i) * KS + p * TB, MERGE ? lane : lofs, t_last, rw[i][p], ri[i][p]);
     SRIGL_LOAD_BOUNDS()
     for (int t = tid; t < S; t += blockDim.x) lds[C * S + t] = 0.0f;   // the all-zero column
-    SRIGL_STAGE_STORE()
+    SRIGL_STAGE_STORE(0)
     __syncthreads();
 
     const int lanepart = rowl * (R * 4);
@@ -581,7 +623,7 @@ __global__ __launch_bounds__(rowlane_max_threads(R)) void k_fwd_rowlane(const XT
         }
         if (more) {
             __syncthreads();                              // every wavefront is done reading chunk c
-            SRIGL_STAGE_STORE()
+            SRIGL_STAGE_STORE(c + 1)
             __syncthreads();
         }
     }
@@ -735,6 +777,7 @@ static srigl_status launch_rowlane_k(const FwdArgs& a, const RowlanePlan& p, hip
     if constexpr (H > 1 && !(R == 2 && H == 2) && KPRE > 1) {
         // short rows: one preloaded block of 32 or 64 terms per stored row and chunk (the host's choice, by fan-in)
         if (p.KPRE == 1) {
+            if constexpr (R != 4) { if (!p.fast) return launch_rowlane_f<R, H, NPW, 1, XT, false, IT>(a, p, st); }
             if (!p.fast) return SRIGL_ERR_UNSUPPORTED;
             if constexpr (PKB != 0) { if (pk) return launch_rowlane_f<R, H, NPW, 1, XT, true, IT, PKB>(a, p, st); }
             return launch_rowlane_f<R, H, NPW, 1, XT, true, IT>(a, p, st);
@@ -742,8 +785,8 @@ static srigl_status launch_rowlane_k(const FwdArgs& a, const RowlanePlan& p, hip
     }
     if constexpr (PKB != 0) { if (pk) return launch_rowlane_f<R, H, NPW, KPRE, XT, true, IT, PKB>(a, p, st); }
     if (p.fast) return launch_rowlane_f<R, H, NPW, KPRE, XT, true, IT>(a, p, st);
-    if constexpr (R == 1 && H == 1) return launch_rowlane_f<R, H, NPW, KPRE, XT, false, IT>(a, p, st);
-    return SRIGL_ERR_UNSUPPORTED;   // the planner keeps R = 1, H = 1 when the fast staging does not apply
+    if constexpr (R != 4) return launch_rowlane_f<R, H, NPW, KPRE, XT, false, IT>(a, p, st);
+    return SRIGL_ERR_UNSUPPORTED;
 }
 
 template <int R, int H, typename XT, typename IT>
