@@ -303,6 +303,34 @@ srigl_status srigl_condensed_linear_fwd_idx16(const void* x, srigl_dtype x_dtype
                                               const uint16_t* seg, srigl_activation act, srigl_fwd_algo algo,
                                               const srigl_fwd_tuning* tuning, void* stream);
 
+/* ---- blocked copy: the condensed layer on the matrix cores -------------------------------------------------
+ * Alg. 1 for bf16 storage at larger batches: the terms of 64 columns at a time are written into a weight tile in LDS and
+ * multiplied there with the staged columns of x (bf16 products are exact in fp32; the sums run in fp32 as in the other forward
+ * calls).  The terms come from a copy of W_c / idx in blocks of 32 stored rows x 64 columns, 4 bytes a term; the layout belongs
+ * to the library.  A value of x that is not finite reaches only the neurons that name its column, as in the other calls.
+ *
+ * srigl_blocked_bytes: bytes of the copy of n_rows stored rows (0 when any size is not positive).
+ * srigl_block_terms: writes it.  W_c bf16, idx of idx_bits (32 or 16) bits, seg as written for these idx (rows ascending); blocked
+ * 16-byte aligned.  SRIGL_ERR_UNSUPPORTED for d_in < 8 or > 65536.
+ * srigl_blocked_tile: the tile the library would take for B rows of x, or 0 where srigl_condensed_linear_fwd is expected to be
+ * faster or the sizes are not supported.  Host arithmetic on sizes.
+ * srigl_blocked_linear_fwd: the forward call; x[B][d_in] bf16, the copy and the W_c / idx it was made from (read again for sums that are
+ * not finite), everything else as in srigl_condensed_linear_fwd_act.  tile 0: the tile of smallest expected time.
+ * srigl_fwd_plan_query describes the calls that read W_c / idx (or the streaming copy), not this one.  Device pointers,
+ * asynchronous on `stream`. */
+typedef enum { SRIGL_BLOCKED_64 = 1, SRIGL_BLOCKED_128 = 2, SRIGL_BLOCKED_256 = 3 } srigl_blocked_tile_t;   /* batch rows = stored rows */
+
+size_t srigl_blocked_bytes(int32_t n_rows, int32_t K, int32_t d_in);
+
+srigl_status srigl_block_terms(const void* W_c, const void* idx, int32_t idx_bits, const uint16_t* seg, int32_t n_rows, int32_t K,
+                               int32_t d_in, void* blocked, size_t blocked_bytes, void* stream);
+
+int32_t srigl_blocked_tile(int32_t B, int32_t d_in, int32_t n_active, int32_t K, int32_t d_out);
+
+srigl_status srigl_blocked_linear_fwd(const void* x, int32_t B, int32_t d_in, const void* blocked, const void* W_c, const void* idx,
+                                      int32_t idx_bits, const int32_t* active, int32_t n_active, int32_t K, const float* bias,
+                                      int32_t d_out, float* y, srigl_activation act, int32_t tile, void* stream);
+
 /* ---- unstructured comparison: the same weights in compressed sparse row form ------------------------------
  * Sec. 4.4 / Fig. 4 and App. H time the condensed layer against the layer's kept weights held as an unstructured sparse
  * matrix.  srigl_csr_linear_fwd is that comparison on this GPU, built like the small-batch condensed kernel:

@@ -22,6 +22,7 @@ REPR_CONDENSED, REPR_STRUCTURED = 0, 1
 ACT_NONE, ACT_RELU, ACT_GELU = 0, 1, 2
 FWD_AUTO, FWD_GENERIC, FWD_KLANE, FWD_ROWLANE, FWD_ROWLOOP = range(5)
 TILE_AUTO, TILE_256x256, TILE_256x256_H, TILE_256x128_W4, TILE_256x128, TILE_128x128, TILE_64x64 = range(7)
+BLOCKED_64, BLOCKED_128, BLOCKED_256 = 1, 2, 3
 TILES = {"256x256": TILE_256x256, "256x256_h": TILE_256x256_H, "256x128_w4": TILE_256x128_W4, "256x128": TILE_256x128,
          "128x128": TILE_128x128, "64x64": TILE_64x64}
 
@@ -33,6 +34,7 @@ EXPORTS = (
     "srigl_structured_linear_fwd_tile", "srigl_structured_split_plan", "srigl_structured_linear_fwd_split", "srigl_choose_representation",
     "srigl_condensed_linear_fwd_act", "srigl_fold_ablated_inputs", "srigl_mask_update_workspace_bytes", "srigl_mask_update",
     "srigl_compact_hidden_layer", "srigl_condensed_mlp_fwd", "srigl_narrow_idx", "srigl_condensed_linear_fwd_idx16", "srigl_csr_linear_fwd", "srigl_fwd_plan_query", "srigl_fwd_plan_query_algo",
+    "srigl_blocked_bytes", "srigl_block_terms", "srigl_blocked_tile", "srigl_blocked_linear_fwd",
 )
 
 
@@ -120,6 +122,14 @@ def _load() -> ctypes.CDLL:
     lib.srigl_fwd_plan_query_algo.restype = ctypes.c_int
     lib.srigl_fwd_plan_query_algo.argtypes = [i32, i32, i32, i32, i32, ctypes.c_int, i32, i32, ctypes.c_int, ctypes.POINTER(FwdTuning),
                                               ctypes.POINTER(FwdPlan)]
+    lib.srigl_blocked_bytes.restype = sz
+    lib.srigl_blocked_bytes.argtypes = [i32, i32, i32]
+    lib.srigl_block_terms.restype = ctypes.c_int
+    lib.srigl_block_terms.argtypes = [vp, vp, i32, vp, i32, i32, i32, vp, sz, vp]
+    lib.srigl_blocked_tile.restype = i32
+    lib.srigl_blocked_tile.argtypes = [i32, i32, i32, i32, i32]
+    lib.srigl_blocked_linear_fwd.restype = ctypes.c_int
+    lib.srigl_blocked_linear_fwd.argtypes = [vp, i32, i32, vp, vp, vp, i32, vp, i32, i32, vp, i32, vp, ctypes.c_int, i32, vp]
     lib.srigl_launch_empty.restype = ctypes.c_int
     lib.srigl_launch_empty.argtypes = [vp]
     lib.srigl_copy_bytes.restype = ctypes.c_int
@@ -279,6 +289,28 @@ def srigl_fwd_plan_query(B, d_in, n_active, K, d_out, dtype_code=F32, has_active
                                          int(bool(has_seg)), int(algo or FWD_AUTO), ctypes.byref(tn) if tn is not None else None,
                                          ctypes.byref(p)), "srigl_fwd_plan_query_algo")
     return {name: int(getattr(p, name)) for name, _ in FwdPlan._fields_}
+
+
+def srigl_blocked_bytes(n_rows: int, K: int, d_in: int) -> int:
+    return int(lib.srigl_blocked_bytes(int(n_rows), int(K), int(d_in)))
+
+
+def srigl_block_terms(W_c, idx, seg, n_rows, K, d_in, blocked):
+    """W_c / idx (32- or 16-bit) / seg of bf16 rows -> the blocked copy, a byte tensor of srigl_blocked_bytes."""
+    _check(lib.srigl_block_terms(_ptr(W_c), _ptr(idx), 8 * idx.element_size(), _ptr(seg), int(n_rows), int(K), int(d_in), _ptr(blocked),
+                                 _nbytes(blocked), _stream()), "srigl_block_terms")
+
+
+def srigl_blocked_tile(B: int, d_in: int, n_active: int, K: int, d_out: int) -> int:
+    """BLOCKED_* code of the tile the library would take, 0 where it would not take the matrix-core form."""
+    return int(lib.srigl_blocked_tile(int(B), int(d_in), int(n_active), int(K), int(d_out)))
+
+
+def srigl_blocked_linear_fwd(x, B, d_in, blocked, W_c, idx, active, n_active, K, bias, d_out, y, act=None, tile=0):
+    """The forward call on the matrix cores; tile 0: the library's choice."""
+    _check(lib.srigl_blocked_linear_fwd(_ptr(x), int(B), int(d_in), _ptr(blocked), _ptr(W_c), _ptr(idx), 8 * idx.element_size(), _ptr(active),
+                                        int(n_active), int(K), _ptr(bias), int(d_out), _ptr(y), int(act or ACT_NONE), int(tile), _stream()),
+           "srigl_blocked_linear_fwd")
 
 
 def srigl_densify(W_c, idx, n_active, K, d_in, Wd):

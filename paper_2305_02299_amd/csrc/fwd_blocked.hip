@@ -1,0 +1,500 @@
+// BLOCKED forward kernel (gfx950, bf16 storage): Alg. 1 of arXiv 2305.02299 on the matrix cores, from a blocked copy of the
+// condensed rows.
+//
+//     y[b][active[s]] = act(bias[active[s]] + sum_k W_c[s][k] * x[b][idx[s][k]])
+//
+// The gathering kernels read one word of x from LDS per term and batch row, which the LDS serves at 128 bytes per clock and
+// compute unit whatever the batch; from a few dozen batch rows on the matrix cores get through the multiplications by the
+// pruned positions faster than that.  Nothing dense is kept in memory: a workgroup owns BM batch rows x BN stored rows and
+// walks d_in 64 columns at a time; for each piece it clears a BN x 64 weight tile in LDS, writes the piece's terms into it and
+// multiplies it with the staged piece of x.  Products of bf16 values are exact in fp32 and the sums run in fp32, as in the
+// gathering kernels.
+//
+// The blocked copy (srigl_block_terms) holds the terms of 32 stored rows x 64 columns next to each other, each as the weight
+// beside its place in the LDS tile: 64 lanes fetch up to 256 of them with one 16-byte load each and store them with four 2-byte
+// LDS writes each.  (From the row-major copies the same kernel needed 327 us instead of 251 on 4096 -> 16384, 13108 stored
+// rows, K = 205, 2048 batch rows: every row's few terms of a piece were a cache line and a lane's predicated writes of their own.)
+//
+// Pipeline (an iteration is CC pieces of 64 columns): x of the next iteration goes from memory straight into the other of two LDS
+// stages while this one is multiplied, and the terms one iteration further ahead into a slot of each wavefront's own.  The weight
+// tile of it + 1 is built while the tile of it is multiplied; half of the wavefronts of a 256 x 256 tile build before they
+// multiply, the other half after it, so that a SIMD's two wavefronts do different things.
+// LDS layout of a stage: sub-tiles of 64 columns, a row 128 bytes, its 16-byte piece q in slot q ^ ((row >> 1) & 7), as in
+// structured.hip.  A wavefront clears and fills whole blocks: no barrier between the two, the LDS serves one wavefront's requests
+// in order.
+//
+// A stored zero times an activation that is not finite is not a term of the layer.  A sum that is not finite is therefore
+// computed again from the row's own terms when it is stored; finite sums cannot have met such an activation.
+#include "mma_tile.h"
+#include <algorithm>
+#include <cmath>
+
+namespace srigl {
+
+constexpr int kBlockRows = 32;   // stored rows of a block (of kSegCols columns)
+
+// The blocked copy: first the table offs[groups][chunks + 1], in units of four terms from the lists' start, then the lists.  A
+// group's lists lie behind each other in chunk order from group * units_per_group on; each is padded to whole units with copies
+// of its last term.  A term: weight bits (low half), byte offset in the block's 32 x 128-byte LDS tile (high half).
+struct BlockedLayout {
+    int groups, chunks, units_per_group;
+    size_t table_bytes, bytes;
+};
+static BlockedLayout blocked_layout(int n_rows, int K, int d_in) {
+    BlockedLayout l;
+    l.groups = (n_rows + kBlockRows - 1) / kBlockRows;
+    l.chunks = (d_in + kSegCols - 1) / kSegCols;
+    l.units_per_group = (kBlockRows * K + 3 * l.chunks) / 4 + 1;
+    l.table_bytes = ((size_t)l.groups * (l.chunks + 1) * 4 + 15) / 16 * 16;
+    l.bytes = l.table_bytes + (size_t)l.groups * l.units_per_group * 16;
+    return l;
+}
+
+// byte offset of column c (0..63) of row r (0..31) in a block's LDS tile
+__device__ __forceinline__ uint32_t block_place(int r, int c) { return (uint32_t)(r * 128) + (((uint32_t)c * 2u) ^ (((uint32_t)(r >> 1) & 7u) << 4)); }
+
+// One workgroup per group of 32 rows.  The counts per (row, chunk) come from the seg table; their running sums down the rows of a
+// chunk, and along the chunks, give every term its place without another pass.  Bound by the latency of its few dependent
+// steps (4096 -> 16384, 13108 stored rows, K = 205: 15.5 us; with 256 threads and the divisions of a flat loop 29.6).
+constexpr int kBuildThreads = 1024;
+__global__ __launch_bounds__(kBuildThreads) void k_block_terms(const uint16_t* __restrict__ W_c, const void* __restrict__ idx, int idx_u16,
+                                                               const uint16_t* __restrict__ seg, int seg_stride, int n_rows, int K, int chunks,
+                                                               int units_per_group, uint32_t* __restrict__ table, uint4* __restrict__ lists) {
+    extern __shared__ uint32_t sh[];
+    uint32_t* offs = sh;                                        // [chunks + 1]: where the lists begin, in units
+    uint32_t* count = offs + chunks + 1;                        // [chunks]: terms of the lists
+    int* place = reinterpret_cast<int*>(count + chunks);        // [32][chunks]: place of term 0 of the row if it were in this chunk's list
+    const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r0 = g * kBlockRows;
+    const int rows = min(kBlockRows, n_rows - r0);
+    for (int i = tid; i < rows * chunks; i += kBuildThreads) {
+        const int r = i / chunks, c = i - r * chunks;
+        const uint16_t* s = seg + (size_t)(r0 + r) * seg_stride + c;
+        place[i] = max((int)s[1] - (int)s[0], 0) | ((int)s[0] << 16);   // count, terms before the chunk
+    }
+    __syncthreads();
+    for (int c = tid; c < chunks; c += kBuildThreads) {
+        int n = 0;
+        for (int r = 0; r < rows; ++r) {
+            const uint32_t v = (uint32_t)place[r * chunks + c];
+            place[r * chunks + c] = n - (int)(v >> 16);
+            n += (int)(v & 0xffffu);
+        }
+        count[c] = (uint32_t)n;
+        offs[c] = (uint32_t)(n + 3) / 4;
+    }
+    __syncthreads();
+    if (wv == 0) {   // exclusive sums along the chunks
+        uint32_t base = (uint32_t)g * (uint32_t)units_per_group;
+        for (int c0 = 0; c0 < chunks; c0 += 64) {
+            const int c = c0 + lane;
+            const uint32_t n = c < chunks ? offs[c] : 0u;
+            uint32_t sum = n;
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t up = __shfl_up(sum, d, 64);
+                if (lane >= d) sum += up;
+            }
+            if (c < chunks) offs[c] = base + sum - n;
+            base += __shfl(sum, 63, 64);
+        }
+        if (lane == 0) offs[chunks] = base;
+    }
+    __syncthreads();
+    for (int c = tid; c <= chunks; c += kBuildThreads) table[(size_t)g * (chunks + 1) + c] = offs[c];
+    uint32_t* out = reinterpret_cast<uint32_t*>(lists);
+    for (int r = wv; r < rows; r += kBuildThreads / 64) {
+        const size_t first = (size_t)(r0 + r) * K;
+        for (int k = lane; k < K; k += 64) {
+            const uint32_t col = idx_u16 ? static_cast<const uint16_t*>(idx)[first + k] : static_cast<const uint32_t*>(idx)[first + k];
+            const uint32_t term = (uint32_t)W_c[first + k] | (block_place(r, (int)(col & 63u)) << 16);
+            const int c = min((int)(col >> 6), chunks - 1);
+            const uint32_t at = (uint32_t)(place[r * chunks + c] + k);     // within the list
+            const uint32_t room = 4u * (offs[c + 1] - offs[c]);
+            if (at >= room) continue;                                       // (an idx that its seg table does not describe)
+            uint32_t* list = out + 4u * (size_t)offs[c];
+            list[at] = term;
+            if (at + 1u == count[c])   // padding: copies of the last term
+                for (uint32_t i = at + 1u; i < room; ++i) list[i] = term;
+        }
+    }
+}
+
+struct BlockedArgs {
+    const uint16_t* x;
+    const uint32_t* table;
+    const unsigned char* lists;
+    const uint16_t* W_c;           // W_c / idx: for sums that are not finite
+    const void* idx;
+    const int32_t* active;
+    const float* bias;
+    float* y;
+    int B, d_in, n_active, K, d_out, idx_u16, act, tiles_m, tiles_n;
+};
+
+// The sum of one output from its own terms.
+__device__ __forceinline__ float sum_terms(const BlockedArgs& p, int m, int s) {
+    const uint16_t* xr = p.x + (size_t)m * p.d_in;
+    float acc = 0.0f;
+    for (int k = 0; k < p.K; ++k) {
+        const size_t at = (size_t)s * p.K + k;
+        const uint32_t c = p.idx_u16 ? static_cast<const uint16_t*>(p.idx)[at] : static_cast<const uint32_t*>(p.idx)[at];
+        acc = fmaf(bf16_bits_to_float(p.W_c[at]), bf16_bits_to_float(xr[min(c, (uint32_t)p.d_in - 1)]), acc);
+    }
+    return acc;
+}
+
+// what store_tile writes
+struct Finish {
+    const BlockedArgs& p;
+    static constexpr bool kRepairs = true;
+    __device__ float stored(float sum, float bv) const { return apply_act(sum + bv, p.act); }
+    __device__ float repaired(int m, int s) const { return sum_terms(p, m, s); }
+    __device__ float ablated(float bv) const { return apply_act(bv, p.act); }
+};
+
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+struct __attribute__((packed, aligned(2))) Half4 { uint32_t a, b; };
+
+// LDS: two stages of x, two of the weight tile, the lists, all of it reused by the epilogue's tile; behind it the epilogue's table
+template <int UA, int BM, int BN, int WGM, int WGN, int CC>
+constexpr size_t blocked_table_at() {
+    constexpr size_t stages = (size_t)CC * 128 * 2 * (BM + BN) + (size_t)WGM * WGN * UA * 1024, tile = EpiLayout<BM, BN, WGM>::TILE_BYTES;
+    return stages > tile ? stages : tile;
+}
+
+// UA: loads of 256 terms a block's list gets ahead of time (longer lists: the rest is fetched when it is needed)
+template <int UA, bool DIRECT, int BM, int BN, int WGM, int WGN, int CC>
+__global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArgs p) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    constexpr int NWAVES = WGM * WGN;
+    constexpr int WTM = BM / WGM, WTN = BN / WGN, TM = WTM / 32, TN = WTN / 32;
+    constexpr int XSTAGE = CC * BM * 128, WSTAGE = CC * BN * 128;
+    constexpr int XP = CC * BM / 8 / NWAVES;   // 1 KB pieces of the x stage per wavefront (8 rows of 128 bytes each)
+    constexpr int KSTEPS = 4 * CC;             // MFMA steps of 16 columns per iteration
+    static_assert(CC * BN == kBlockRows * NWAVES, "one block per wavefront and iteration");
+    static_assert(CC * BM % (8 * NWAVES) == 0 && WTM % 32 == 0 && WTN % 32 == 0 && BM % 16 == 0, "tile shape");
+    unsigned char* const wstages = smem + 2 * XSTAGE;
+    unsigned char* const lstages = wstages + 2 * WSTAGE;
+    unsigned char* const table = smem + blocked_table_at<UA, BM, BN, WGM, WGN, CC>();
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wv / WGN, wn = wv % WGN;
+    const int d_in = p.d_in;
+    int tile_m, tile_n;
+    if (!tile_of_workgroup(blockIdx.x, p.tiles_m, p.tiles_n, &tile_m, &tile_n)) return;
+    const int m0 = tile_m * BM, n0 = tile_n * BN;
+    const int n_chunks = (d_in + 63) >> 6, n_it = (n_chunks + CC - 1) / CC;
+
+    // ---- x: a lane brings 16 bytes per pass; rows past the batch re-read the last one (never stored), pieces past the end of
+    // the rows come from zeros (DIRECT) or from whatever lies there (they meet zero weights only)
+    uint32_t xoff[XP];   // element offset from the tile's first row, chunk 0 of the iteration
+    int xcol[XP];
+#pragma unroll
+    for (int q = 0; q < XP; ++q) {
+        const int row = 8 * (q * NWAVES + wv) + (lane >> 3);   // row of the stage: sub-tile row / BM
+        xcol[q] = (row / BM) * 64 + (((lane & 7) ^ ((row >> 1) & 7)) << 3);
+        xoff[q] = (uint32_t)min(row % BM, p.B - 1 - m0) * (uint32_t)d_in + (uint32_t)xcol[q];
+    }
+    const uint16_t* const xtile = p.x + (size_t)m0 * d_in;
+    const uint32_t xtotal = (uint32_t)min(p.B - m0, BM) * (uint32_t)d_in;
+    Half4 xr[DIRECT ? 1 : XP][2];
+    auto issue_x = [&](int it) {
+        const int c0 = it * CC * 64;
+        if (DIRECT) {
+            unsigned char* stage = smem + (it & 1) * XSTAGE + 1024 * wv;
+#pragma unroll
+            for (int q = 0; q < XP; ++q) {
+                const void* g = xtile + xoff[q] + c0;
+                if (c0 + xcol[q] >= d_in) g = &g_zero16;   // (d_in is a multiple of 8: a piece is whole or absent)
+                __builtin_amdgcn_global_load_lds((gptr_t)g, (lptr_t)(stage + 1024 * NWAVES * q), 16, 0, 0);
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < XP; ++q) {
+                const uint16_t* g = xtile + min(xoff[q] + (uint32_t)c0, xtotal - 8u);   // (d_in >= 8: host)
+                xr[q][0] = *reinterpret_cast<const Half4*>(g);
+                xr[q][1] = *reinterpret_cast<const Half4*>(g + 4);
+            }
+        }
+    };
+    auto store_x = [&](int it) {   // !DIRECT
+        unsigned char* stage = smem + (it & 1) * XSTAGE + 1024 * wv + 16 * lane;
+        const int c0 = it * CC * 64;
+#pragma unroll
+        for (int q = 0; q < XP; ++q) {
+            uint32_t v[4] = {xr[q][0].a, xr[q][0].b, xr[q][1].a, xr[q][1].b};
+            // a load that would have run past the tile's last element started up to 8 elements early
+            const int sh = min(max((int)(xoff[q] + (uint32_t)c0) - (int)(xtotal - 8u), 0), 7);
+            if (__any(sh != 0)) {
+                if (sh & 4) { v[0] = v[2]; v[1] = v[3]; v[2] = v[3] = 0; }
+                if (sh & 2) { v[0] = v[1]; v[1] = v[2]; v[2] = v[3]; v[3] = 0; }
+                if (sh & 1) {
+                    v[0] = __builtin_amdgcn_alignbyte(v[1], v[0], 2);
+                    v[1] = __builtin_amdgcn_alignbyte(v[2], v[1], 2);
+                    v[2] = __builtin_amdgcn_alignbyte(v[3], v[2], 2);
+                    v[3] >>= 16;
+                }
+            }
+            *reinterpret_cast<uint4*>(stage + 1024 * NWAVES * q) = make_uint4(v[0], v[1], v[2], v[3]);
+        }
+    };
+
+    // ---- terms: wavefront wv builds the block of rows 32 * (wv % (BN / 32)) of the tile, sub-tile wv / (BN / 32)
+    const int group = n0 / kBlockRows + wv % (BN / kBlockRows), sub = wv / (BN / kBlockRows);
+    const bool has_rows = group * kBlockRows < p.n_active;
+    const uint32_t* const offs = p.table + (size_t)(has_rows ? group : 0) * (n_chunks + 1);
+    // lane l: where the lists of iterations 64 i + l begin and end, for even and for odd i
+    uint32_t even_lo = 0, even_hi = 0, odd_lo = 0, odd_hi = 0;
+    auto load_offsets = [&](int it0) {
+        const int c = (it0 + lane) * CC + sub;
+        const bool in = has_rows && c < n_chunks;
+        const uint32_t lo = offs[in ? c : 0], hi = in ? offs[c + 1] : lo;
+        wait_loads<0>();
+        if (it0 & 64) { odd_lo = lo; odd_hi = hi; } else { even_lo = lo; even_hi = hi; }
+    };
+    auto list_of = [&](int it, uint32_t* lo, uint32_t* n) {
+        const bool odd = it & 64;
+        *lo = (uint32_t)__builtin_amdgcn_readlane((int)(odd ? odd_lo : even_lo), it & 63);
+        *n = (uint32_t)__builtin_amdgcn_readlane((int)(odd ? odd_hi : even_hi), it & 63) - *lo;
+    };
+    unsigned char* const list_slot = lstages + wv * UA * 1024;
+    auto fetch_units = [&](uint32_t lo, uint32_t n) {
+#pragma unroll
+        for (int i = 0; i < UA; ++i) {
+            const uint32_t u = 64u * i + (uint32_t)lane;   // (lanes past the list share one address)
+            __builtin_amdgcn_global_load_lds((gptr_t)(p.lists + (size_t)(lo + (u < n ? u : 0u)) * 16), (lptr_t)(list_slot + 1024 * i), 16, 0, 0);
+        }
+    };
+    // (past the last iteration the last list is fetched again: the number of loads in flight at each wait is fixed)
+    auto issue_list = [&](int it) {
+        if ((it & 63) == 0 && it < n_it) load_offsets(it);
+        uint32_t lo, n;
+        list_of(min(it, n_it - 1), &lo, &n);
+        fetch_units(lo, n);
+    };
+    // (LDS instructions by hand: the compiler would have a write wait for every load into LDS that is in flight)
+    auto lds_at = [](const unsigned char* q) { return (uint32_t)(uintptr_t)(lptr_t)q; };
+    auto put4 = [&](uint32_t block, u32x4_t v) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) asm volatile("ds_write_b16 %0, %1" ::"v"(block + (v[t] >> 16)), "v"(v[t]) : "memory");
+    };
+    // A block is built from its list, which has landed: the terms into registers, the tile cleared, the terms to their places; the
+    // next list is requested into the slot that this one leaves.
+    auto build = [&](int it) {
+        const uint32_t block = lds_at(wstages + (it & 1) * WSTAGE + wv * 4096), clear = block + (uint32_t)lane * 16u;
+        const uint32_t slot = lds_at(list_slot + lane * 16);
+        const u32x4_t zero = {0u, 0u, 0u, 0u};
+        u32x4_t terms[UA];
+        // (one piece, so that nothing touches the registers before the reads have returned; the zeros may still be on their way)
+        if constexpr (UA == 1)
+            asm volatile("ds_read_b128 %0, %1\n\tds_write_b128 %2, %3\n\tds_write_b128 %2, %3 offset:1024\n\tds_write_b128 %2, %3 offset:2048\n\t"
+                         "ds_write_b128 %2, %3 offset:3072\n\ts_waitcnt lgkmcnt(4)"
+                         : "=&v"(terms[0]) : "v"(slot), "v"(clear), "v"(zero) : "memory");
+        else
+            asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:1024\n\tds_write_b128 %3, %4\n\tds_write_b128 %3, %4 offset:1024\n\t"
+                         "ds_write_b128 %3, %4 offset:2048\n\tds_write_b128 %3, %4 offset:3072\n\ts_waitcnt lgkmcnt(4)"
+                         : "=&v"(terms[0]), "=&v"(terms[UA - 1]) : "v"(slot), "v"(clear), "v"(zero) : "memory");
+        uint32_t lo, n;
+        list_of(it, &lo, &n);
+        issue_list(it + 1);
+#pragma unroll
+        for (int i = 0; i < UA; ++i)
+            if (64u * i + (uint32_t)lane < n) put4(block, terms[i]);
+        for (uint32_t u = 64u * UA; u < n; u += 64u)
+            if (u + (uint32_t)lane < n) {
+                const u32x4_t more = *reinterpret_cast<const u32x4_t*>(p.lists + (size_t)(lo + u + (uint32_t)lane) * 16);
+                put4(block, more);
+            }
+    };
+
+    f32x16_t acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+
+    const int swz = ((lane & 31) >> 1) & 7;
+    int frag_off[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) frag_off[kk] = (lane & 31) * 128 + (((2 * kk + (lane >> 5)) ^ swz) * 16);
+    auto x_frag = [&](int it, int kk, int i) {
+        return *reinterpret_cast<const bf16x8_t*>(smem + (it & 1) * XSTAGE + (kk >> 2) * (BM * 128) + (wm * WTM + i * 32) * 128 + frag_off[kk & 3]);
+    };
+    auto w_frag = [&](int it, int kk, int j) {
+        return *reinterpret_cast<const bf16x8_t*>(wstages + (it & 1) * WSTAGE + (kk >> 2) * (BN * 128) + (wn * WTN + j * 32) * 128 + frag_off[kk & 3]);
+    };
+
+    // ---- prologue (what the epilogue needs from memory is fetched here too, beside the first requests)
+    const TileColumns cols = tile_columns(n0, BN, p.active, p.n_active, p.d_out);
+    issue_list(0);
+    issue_x(0);
+    fill_table<NWAVES * 64>(table, cols.lo, cols, n0, p.active, p.bias);
+    if (!DIRECT) store_x(0);
+    wait_loads<0>();
+    build(0);
+    lds_barrier();
+
+    // The build of it + 1 stands before or behind the multiplications of it.
+    bf16x8_t a[2][TM], b[2][TN];
+    auto read_frags = [&](int it, int kk, int set) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) a[set][i] = x_frag(it, kk, i);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) b[set][j] = w_frag(it, kk, j);
+    };
+    read_frags(0, 0, 0);
+    const bool early = NWAVES > 4 && wv < NWAVES / 2;
+    for (int it = 0; it < n_it; ++it) {
+        const bool next = it + 1 < n_it;
+        if (early && next) {
+            wait_loads<0>();   // the list (the last iteration has waited for it, the prologue has not)
+            build(it + 1);
+        }
+        if (next) issue_x(it + 1);
+#pragma unroll
+        for (int kk = 0; kk < KSTEPS; ++kk) {
+            __builtin_amdgcn_s_waitcnt(kLgkm0);   // this step's fragments, requested a step ago, before the next one's are
+            if (kk + 1 < KSTEPS) {
+                read_frags(it, kk + 1, (kk + 1) & 1);
+            } else if (next) {
+                if (!DIRECT) store_x(it + 1);
+                wait_loads<0>();   // x of it + 1; the list
+                if (!early) build(it + 1);
+                lds_barrier();   // stage it + 1 is complete, every fragment of stage it is in registers
+                read_frags(it + 1, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // a step's fragments are requested a whole step ahead
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk & 1][i], b[kk & 1][j], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
+    wait_loads<0>();   // the repeated last list may still be landing
+    lds_barrier();
+    store_tile<BM, BN, WGM, WGN>(smem, table, true, acc, cols, m0, n0, p.B, p.active, p.bias, p.d_out, p.y, Finish{p});
+}
+
+template <int UA, bool DIRECT, int BM, int BN, int WGM, int WGN, int CC>
+static srigl_status launch_tile(const BlockedArgs& args, hipStream_t st) {
+    auto kern = k_fwd_blocked<UA, DIRECT, BM, BN, WGM, WGN, CC>;
+    constexpr size_t lds = blocked_table_at<UA, BM, BN, WGM, WGN, CC>() + kTableBytes;
+    static_assert(lds <= kLdsMax, "LDS");
+    static LdsLimit lds_limit;
+    if (lds_limit.ensure(kern, lds) != SRIGL_OK) return SRIGL_ERR_HIP;
+    BlockedArgs p = args;
+    p.tiles_m = (p.B + BM - 1) / BM;
+    p.tiles_n = (p.n_active + BN - 1) / BN;
+    const long long n_wg = ((long long)p.tiles_m * p.tiles_n + kXcds - 1) / kXcds * kXcds;
+    if (n_wg > 0x7fffffffLL) return SRIGL_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(kern, dim3((unsigned)n_wg), dim3(WGM * WGN * 64), lds, st, p);
+    return hip_ok(hipGetLastError());
+}
+
+template <int UA, bool DIRECT>
+static srigl_status launch_shape(const BlockedArgs& p, int tile, hipStream_t st) {
+    switch (tile) {
+        case SRIGL_BLOCKED_256: return launch_tile<UA, DIRECT, 256, 256, 2, 4, 1>(p, st);
+        case SRIGL_BLOCKED_128: return launch_tile<UA, DIRECT, 128, 128, 2, 2, 1>(p, st);
+        case SRIGL_BLOCKED_64: return launch_tile<UA, DIRECT, 64, 64, 2, 2, 2>(p, st);
+        default: return SRIGL_ERR_INVALID_ARG;
+    }
+}
+
+// Estimated time (us) in each tile, and the tile of smallest estimate (0: these sizes cannot run).  Fits of measurements on 13
+// layers (200..4096 wide, 300..16192 stored rows, 80-98 % sparse) at batches of 32 to 2048: a workgroup costs a fixed part (prologue,
+// epilogue) and a part per iteration; a compute unit holds one 256 x 256 workgroup, or two of the others, which then run slower each.
+static int choose_blocked_tile(int B, int d_in, int n_active, double* us) {
+    const int chunks = (d_in + kSegCols - 1) / kSegCols;
+    auto workgroups = [&](int t) { return (double)((B + t - 1) / t) * ((n_active + t - 1) / t); };
+    const double w64 = workgroups(64), w128 = workgroups(128), w256 = workgroups(256), it64 = (chunks + 1) / 2;
+    const double t64 = 3.0 + (w64 <= 256 ? 0.8 * it64 + 3.2 : std::ceil(w64 / 512) * (1.02 * it64 + 3.5));
+    const double t128 = w128 <= 256 ? 8.0 + 0.9 * chunks : 3.0 + std::ceil(w128 / 512) * (9.0 + 1.02 * chunks);
+    const double t256 = 3.0 + std::ceil(w256 / 256) * (15.0 + 1.6 * chunks);
+    *us = std::min(t64, std::min(t128, t256));
+    return *us == t64 ? SRIGL_BLOCKED_64 : (*us == t128 ? SRIGL_BLOCKED_128 : SRIGL_BLOCKED_256);
+}
+
+// Taken where its estimate is this far ahead of the gathering kernels' (both estimates are good to about 10 %; no measured
+// point was then slower, and the copy has to be built once per layer)
+constexpr double kBlockedMargin = 0.85;
+
+static bool blocked_fits(int n_active, int K, int d_in) {
+    if (n_active <= 0 || K <= 0 || d_in < 8 || d_in > 65536) return false;
+    const BlockedLayout l = blocked_layout(n_active, K, d_in);
+    return (long long)l.groups * l.units_per_group < (1LL << 30);   // places of terms in 32 bits
+}
+
+}  // namespace srigl
+
+using namespace srigl;
+
+extern "C" {
+
+size_t srigl_blocked_bytes(int32_t n_rows, int32_t K, int32_t d_in) {
+    if (n_rows <= 0 || K <= 0 || d_in <= 0) return 0;
+    return blocked_layout(n_rows, K, d_in).bytes;
+}
+
+int32_t srigl_blocked_tile(int32_t B, int32_t d_in, int32_t n_active, int32_t K, int32_t d_out) {
+    if (B <= 0 || n_active > d_out || K > d_in || !blocked_fits(n_active, K, d_in)) return 0;
+    struct Key { int32_t B, d_in, n_active, K, d_out; };
+    static thread_local DecisionCache<Key, int, 64> cache;
+    return cache.get(Key{B, d_in, n_active, K, d_out}, [&] {
+        double us;
+        const int tile = choose_blocked_tile(B, d_in, n_active, &us);
+        return us < kBlockedMargin * condensed_estimate_us(B, d_in, n_active, K, d_out, true, n_active < d_out) ? tile : 0;
+    });
+}
+
+srigl_status srigl_block_terms(const void* W_c, const void* idx, int32_t idx_bits, const uint16_t* seg, int32_t n_rows, int32_t K,
+                               int32_t d_in, void* blocked, size_t blocked_bytes, void* stream) {
+    if (n_rows < 0 || K < 0 || d_in < 0 || K > d_in || (idx_bits != 32 && idx_bits != 16)) return SRIGL_ERR_INVALID_ARG;
+    if (n_rows == 0 || K == 0) return SRIGL_OK;
+    if (W_c == nullptr || idx == nullptr || seg == nullptr || blocked == nullptr || reinterpret_cast<uintptr_t>(blocked) % 16 != 0)
+        return SRIGL_ERR_INVALID_ARG;
+    if (!blocked_fits(n_rows, K, d_in)) return SRIGL_ERR_UNSUPPORTED;
+    const BlockedLayout l = blocked_layout(n_rows, K, d_in);
+    if (blocked_bytes < l.bytes) return SRIGL_ERR_CAPACITY;
+    const size_t lds = (size_t)(2 * l.chunks + 1) * 4 + (size_t)kBlockRows * l.chunks * 4;
+    static LdsLimit lds_limit;
+    if (lds_limit.ensure(k_block_terms, lds) != SRIGL_OK) return SRIGL_ERR_HIP;
+    unsigned char* base = static_cast<unsigned char*>(blocked);
+    hipLaunchKernelGGL(k_block_terms, dim3((unsigned)l.groups), dim3(kBuildThreads), lds, static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(W_c),
+                       idx, idx_bits == 16 ? 1 : 0, seg, srigl_seg_stride(d_in), n_rows, K, l.chunks, l.units_per_group,
+                       reinterpret_cast<uint32_t*>(base), reinterpret_cast<uint4*>(base + l.table_bytes));
+    return hip_ok(hipGetLastError());
+}
+
+srigl_status srigl_blocked_linear_fwd(const void* x, int32_t B, int32_t d_in, const void* blocked, const void* W_c, const void* idx,
+                                           int32_t idx_bits, const int32_t* active, int32_t n_active, int32_t K, const float* bias,
+                                           int32_t d_out, float* y, srigl_activation act, int32_t tile, void* stream) {
+    if (act != SRIGL_ACT_NONE && act != SRIGL_ACT_RELU && act != SRIGL_ACT_GELU) return SRIGL_ERR_INVALID_ARG;
+    if (B < 0 || d_in < 0 || n_active < 0 || K < 0 || d_out < 0 || K > d_in || n_active > d_out || (idx_bits != 32 && idx_bits != 16))
+        return SRIGL_ERR_INVALID_ARG;
+    if (active == nullptr && n_active != d_out) return SRIGL_ERR_INVALID_ARG;
+    if (!blocked_fits(n_active, K, d_in)) return SRIGL_ERR_UNSUPPORTED;
+    if (B == 0) return SRIGL_OK;
+    if (x == nullptr || blocked == nullptr || W_c == nullptr || idx == nullptr || y == nullptr || reinterpret_cast<uintptr_t>(blocked) % 16 != 0)
+        return SRIGL_ERR_INVALID_ARG;
+    const BlockedLayout l = blocked_layout(n_active, K, d_in);
+    BlockedArgs p;
+    const unsigned char* base = static_cast<const unsigned char*>(blocked);
+    p.x = static_cast<const uint16_t*>(x); p.table = reinterpret_cast<const uint32_t*>(base); p.lists = base + l.table_bytes;
+    p.W_c = static_cast<const uint16_t*>(W_c); p.idx = idx; p.active = active; p.bias = bias; p.y = y;
+    p.B = B; p.d_in = d_in; p.n_active = n_active; p.K = K; p.d_out = d_out; p.idx_u16 = idx_bits == 16; p.act = (int)act;
+    const bool direct = d_in % 8 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
+    // a block's mean number of terms against the 256 a load brings
+    const bool two = 2048.0 * K / d_in > 180.0;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    double us;
+    if (tile == 0) tile = choose_blocked_tile(B, d_in, n_active, &us);
+    if (direct) return two ? launch_shape<2, true>(p, tile, st) : launch_shape<1, true>(p, tile, st);
+    return two ? launch_shape<2, false>(p, tile, st) : launch_shape<1, false>(p, tile, st);
+}
+
+}  // extern "C"

@@ -16,21 +16,11 @@
 //   fp32: v_mfma_f32_32x32x2_f32, lane l holds row l%32, k = l/32; the lane's 16-byte piece carries 4 k, used by 4
 //         successive MFMAs (both operands use the same k-to-slot map, so the sum runs over matching k).
 // Result block layout: accumulator register e of lane l is row 8*(e/4) + 4*(l/32) + e%4, column l%32.
-#include "srigl_internal.h"
+#include "mma_tile.h"
 
 namespace srigl {
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
-
-constexpr int kXcds = 8;                  // dies with an L2 of their own; workgroup id % 8 selects the die
-#ifndef SRIGL_PANEL_N
-#define SRIGL_PANEL_N 8
-#endif
-constexpr int kPanelN = SRIGL_PANEL_N;    // tile columns per panel of the tile order
 constexpr int kSlabBytes = 128;   // bytes of K per row and slab = LDS row pitch
-
-__device__ uint4 g_zero16 = {0u, 0u, 0u, 0u};   // source of the pieces past the end of a row
 
 // zero fill, then scatter: two launches so that no ordering inside a wavefront is relied on
 __global__ __launch_bounds__(256) void k_fill_zero16(uint4* __restrict__ p, size_t n16) {
@@ -147,20 +137,12 @@ __device__ __forceinline__ void mma_block(f32x16_t& acc, const float4& a, const 
     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
 }
 
-// s_waitcnt immediate that waits for the vector-memory counter only (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
-constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
-
-using gptr_t = const __attribute__((address_space(1))) void*;
-using lptr_t = __attribute__((address_space(3))) void*;
-
-// LDS use of the epilogue: the column table with its bias values and an fp32 tile (pitch BN + 4) of all BM rows when
-// that fits, else of the rows of one wavefront row at a time
-template <int BM, int BN, int WGM>
-struct EpiLayout {
-    static constexpr int PITCH = BN + 4;
-    static constexpr int TCAP = 1024;   // columns of y per pass
-    static constexpr int PHASES = ((size_t)BM * PITCH * 4 + (size_t)TCAP * 8 <= kLdsMax) ? 1 : WGM;
-    static constexpr size_t BYTES = (size_t)(BM / PHASES) * PITCH * 4 + (size_t)TCAP * 8;
+// what store_tile writes: the sum plus the bias; the bias of an ablated neuron
+struct Plain {
+    static constexpr bool kRepairs = false;
+    __device__ float stored(float sum, float b) const { return sum + b; }
+    __device__ float repaired(int, int) const { return 0.0f; }
+    __device__ float ablated(float b) const { return b; }
 };
 
 // BM x BN output tile per workgroup of WGM x WGN wavefronts; NS >= 2 LDS stages of SLAB (128 or 64) bytes of K per row.
@@ -195,24 +177,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_structured_gemm(const T* __r
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront index as a scalar
     const int wm = wv / WGN, wn = wv % WGN;
-    // Workgroup -> tile.  Consecutive workgroup ids go round-robin to the 8 XCDs, each with its own L2.  The tiles are put
-    // in an order in which neighbours share operands (panels of kPanelN tile columns, row by row inside a panel), that order
-    // is cut into 8 equal runs, and XCD c walks run c: the 32 tiles it holds at a time cover about 4 x 8 tiles, which
-    // share their rows of x and of Wd through that L2, and every XCD gets the same number of tiles.
     int tile_m, tile_n;
-    {
-        const int tiles_m = (B + BM - 1) / BM, tiles_n = (n_active + BN - 1) / BN;
-        const int total = tiles_m * tiles_n;
-        const int per_xcd = (total + kXcds - 1) / kXcds;
-        const int id = blockIdx.x;
-        const int q = (id % kXcds) * per_xcd + id / kXcds;
-        if (id / kXcds >= per_xcd || q >= total) return;   // padding of the last run
-        const int full_panel = tiles_m * kPanelN;
-        const int panel = q / full_panel, r = q - panel * full_panel;
-        const int width = min(kPanelN, tiles_n - panel * kPanelN);
-        tile_m = r / width;
-        tile_n = panel * kPanelN + r - tile_m * width;
-    }
+    if (!tile_of_workgroup(blockIdx.x, (B + BM - 1) / BM, (n_active + BN - 1) / BN, &tile_m, &tile_n)) return;
     const int m0 = tile_m * BM, n0 = tile_n * BN;
 
     // loader: pass p of wavefront wv fills rows RPL * (p * NWAVES + wv) .. + RPL - 1; lane -> (row + lane / PIECES, slot lane % PIECES).
@@ -348,57 +314,10 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_structured_gemm(const T* __r
         return;
     }
 
-    // Epilogue with an active list.  The stored neurons of this tile and the ablated ones between them cover one contiguous
-    // range of columns of y, [c_lo, c_hi].  The range is written row by row with neighbouring lanes on neighbouring columns:
-    // a table in LDS says, for each column of the range, which stored neuron of the tile it is (or none: the column is its
-    // bias), and the accumulators pass through an LDS tile.  No column of y is touched twice and none is left out.
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // the re-issued last stages may still be landing in the ring
     __syncthreads();
-    using EL = EpiLayout<BM, BN, WGM>;
-    constexpr int NT = NWAVES * 64;
-    constexpr int PITCH = EL::PITCH, TCAP = EL::TCAP, EPH = EL::PHASES, PROWS = BM / EPH, WPP = WGM / EPH;
-    float* tile = reinterpret_cast<float*>(smem);                         // [PROWS][PITCH]
-    int* table = reinterpret_cast<int*>(smem + PROWS * PITCH * 4);        // [TCAP] stored neuron within the tile, or -1
-    float* tbias = reinterpret_cast<float*>(table + TCAP);                // [TCAP]
-    const int s_cnt = min(BN, n_active - n0);
-    const int c_lo = max((n0 > 0) ? active[n0 - 1] + 1 : 0, 0);
-    const int c_hi = min((n0 + s_cnt == n_active) ? d_out - 1 : active[n0 + s_cnt - 1], d_out - 1);
-    for (int cc = c_lo; cc <= c_hi; cc += TCAP) {
-        const int wc = min(TCAP, c_hi - cc + 1);
-        if (cc != c_lo) __syncthreads();   // the previous pass is done with the table
-        for (int k = tid; k < wc; k += NT) {
-            tbias[k] = bias ? bias[cc + k] : 0.0f;
-            table[k] = -1;
-        }
-        __syncthreads();
-        for (int s = tid; s < s_cnt; s += NT) {
-            const int col = active[n0 + s] - cc;
-            if (col >= 0 && col < wc) table[col] = s;
-        }
-#pragma unroll
-        for (int ph = 0; ph < EPH; ++ph) {
-            if (ph > 0 || cc != c_lo) __syncthreads();   // tile free again
-            if (wm / WPP == ph) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e)
-                            tile[((wm % WPP) * WTM + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)) * PITCH + wn * WTN + j * 32 + (lane & 31)] =
-                                acc[i][j][e];
-            }
-            __syncthreads();   // tile, table and bias values complete
-            const int rows = min(PROWS, B - (m0 + ph * PROWS));
-            for (int r = wv; r < rows; r += NWAVES) {
-                float* yr = y + (size_t)(m0 + ph * PROWS + r) * d_out + cc;
-                for (int k = lane; k < wc; k += 64) {
-                    const int tix = table[k];
-                    __builtin_nontemporal_store((tix >= 0 ? tile[r * PITCH + tix] : 0.0f) + tbias[k], &yr[k]);
-                }
-            }
-        }
-    }
+    store_tile<BM, BN, WGM, WGN>(smem, smem + EpiLayout<BM, BN, WGM>::TILE_BYTES, false, acc, tile_columns(n0, BN, active, n_active, d_out), m0, n0, B,
+                                    active, bias, d_out, y, Plain());
 }
 
 template <typename T, int BM, int BN, int WGM, int WGN, int NS, int SLAB, bool RAGGED>

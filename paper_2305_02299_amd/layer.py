@@ -1,13 +1,13 @@
 """Device-buffer holder around the three library calls (no arithmetic here)."""
 from __future__ import annotations
 
-from dataclasses import dataclass
+from dataclasses import dataclass, field
 
 import torch
 
 from . import binding as B_
 from . import _front
-from ._front import linear_fwd as _linear_fwd   # (x, batch or -1, d_in, W_c, idx, ..., packed, activation) -> y
+from ._front import linear_fwd as _linear_fwd   # (x, batch or -1, d_in, W_c, idx, ..., packed, activation, owner) -> y
 
 
 @dataclass
@@ -28,6 +28,8 @@ class CondensedLinear:
     idx_wide: torch.Tensor | None = None   # the int32 indices when idx holds the 16-bit copy
     packed: torch.Tensor | None = None     # the streaming copy of W_c / idx (bytes), read by the kernels that can stream it
     split_ws: torch.Tensor | None = None   # partial sums of the structured-only product when it cuts d_in into parts (grown on demand)
+    # what the forward call keeps of the blocked copy of W_c / idx that the matrix-core form reads (bf16 storage; made on first use)
+    _blocked: tuple | None = field(default=None, repr=False, compare=False)
 
     def narrow(self) -> "CondensedLinear":
         """The same layer with 16-bit column indices (d_in <= 65536); weights, active, bias and seg are shared."""
@@ -52,7 +54,7 @@ class CondensedLinear:
         """representation: "condensed", "structured", or "auto" (the library's estimate for this batch size)."""
         if algo is None and tuning is None and representation == "condensed":
             return _linear_fwd(x, -1, self.d_in, self.W_c, self.idx, self.active, self.n_active, self.K, self.bias, self.d_out, y, self.seg,
-                               self.packed, 0)
+                               self.packed, 0, self)
         if representation == "auto":
             representation = "structured" if _front.choose(x, self.d_in, self.n_active, self.K, self.d_out, self.W_c) else "condensed"
         if representation == "structured":
@@ -65,7 +67,7 @@ class CondensedLinear:
         packed = self.packed if self.idx.dtype == torch.int32 else None
         if algo is None and tuning is None:
             return _linear_fwd(x, -1, self.d_in, self.W_c, self.idx, self.active, self.n_active, self.K, self.bias, self.d_out, y, self.seg,
-                               packed, 0)
+                               packed, 0, self)
         assert x.dim() == 2 and x.shape[1] == self.d_in
         if y is None:
             y = torch.empty((x.shape[0], self.d_out), dtype=torch.float32, device=x.device)
