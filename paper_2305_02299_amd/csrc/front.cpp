@@ -295,13 +295,13 @@ PyObject* condense(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
         const bool want_seg = PyObject_IsTrue(a[3]) == 1, want_packed = PyObject_IsTrue(a[4]) == 1;
         const srigl_dtype wt = dtype_of(*W);
         const int64_t k = K > 0 ? K : 0;
-        at::Tensor W_c = fresh({d_out, k}, W->scalar_type(), *W), idx = fresh({d_out, k}, at::kInt, *W), active = fresh({d_out}, at::kInt, *W);
+        const size_t ws_bytes = srigl_workspace_bytes(d_out);
+        at::Tensor W_c = fresh({d_out, k}, W->scalar_type(), *W), idx = fresh({d_out, k}, at::kInt, *W);
+        at::Tensor active = fresh({d_out + (int64_t)(ws_bytes + 3) / 4}, at::kInt, *W);   // (with the workspace behind it)
         at::Tensor seg, packed;
         if (want_seg) seg = fresh({d_out, srigl_seg_stride(d_in)}, at::kShort, *W);
         const size_t packed_bytes = srigl_packed_bytes(d_out, K, d_in, wt);
         if (want_packed) packed = fresh({(int64_t)(packed_bytes > 16 ? packed_bytes : 16)}, at::kByte, *W);
-        const size_t ws_bytes = srigl_workspace_bytes(d_out);
-        at::Tensor ws = fresh({(int64_t)ws_bytes}, at::kByte, *W);
         at::Tensor report = at::empty({(int64_t)sizeof(srigl_report)}, at::TensorOptions().dtype(at::kByte).pinned_memory(true));
         srigl_report* rep = static_cast<srigl_report*>(report.data_ptr());
         constexpr int32_t kPending = -7;
@@ -313,13 +313,14 @@ PyObject* condense(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
         Py_BEGIN_ALLOW_THREADS
         rc = srigl_condense(W->data_ptr(), wt, static_cast<const uint8_t*>(mask->data_ptr()), d_out, d_in, K, d_out, wcp,
                             static_cast<int32_t*>(idx.data_ptr()), static_cast<int32_t*>(active.data_ptr()), static_cast<uint16_t*>(sgp), pkp,
-                            want_packed ? (size_t)packed.numel() : 0, ws.data_ptr(), ws_bytes, rep, st.stream());
-        // (the stream is asked now and then, so that the wait ends whatever happened to the launches)
+                            want_packed ? (size_t)packed.numel() : 0, static_cast<int32_t*>(active.data_ptr()) + d_out, ws_bytes, rep, st.stream());
+        // (the stream is asked now and then, so that the wait ends whatever happened to the launches; asked every 1024 polls it took
+        // 6 us of a call's 22)
         for (unsigned polls = 1; rc == SRIGL_OK; ++polls) {
             status = __atomic_load_n(&rep->status, __ATOMIC_ACQUIRE);
             if (status != kPending) break;
             bool idle = false;
-            if (polls % 1024 == 0) {
+            if (polls % 65536 == 0) {
                 try { idle = st.query(); } catch (...) { rc = SRIGL_ERR_HIP; }
             }
             if (idle) {
