@@ -539,23 +539,38 @@ __global__ __launch_bounds__(256) void k_row_salient(const float* __restrict__ W
     }
 }
 
-// Steps 6 (applied) and 7.  One wavefront per row; lane l holds columns 4 (l + 64 q) .. + 3, q < NQ (d_in <= 256 NQ).  A column
+// Steps 6 (applied) and 7.  WPR wavefronts per row (1, four rows to a workgroup, or 4); lane l of them holds columns
+// 4 (l + 64 WPR q) .. + 3, q < NQ (d_in <= 256 WPR NQ).  Rows of more than 1024 columns take four wavefronts: with one, a wavefront's
+// hundreds of instructions per count ran one after the other on two thirds of a machine that few rows fill (2240 x 1896
+// 27 -> 18 us, 4096 x 1953 41 -> 25; shorter rows would pay for the barrier behind every count).  A column
 // is ranked by one number (its weight's magnitude if it survives step 6, else its gradient's), equal numbers by column.  The
 // `want`-th largest among the row's candidates is searched by counting (NQ x 4 compares, their ballots counted by scalar
 // instructions) until a threshold splits off exactly `want`.
-template <int NQ>
+template <int NQ, int WPR>
 __global__ __launch_bounds__(256) void k_row_update(const float* __restrict__ W, const uint8_t* __restrict__ mask, const float* __restrict__ grad,
                                                     int d_out, int d_in, const int* __restrict__ remains, const UpdateScratch* __restrict__ s,
                                                     uint8_t* __restrict__ mask_out, float* __restrict__ W_out) {
     constexpr int N = 4 * NQ;
     constexpr bool HOLD = NQ <= 4;   // the weights stay in registers (else they are read again where they are kept)
-    const int lane = threadIdx.x & 63;
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+    static_assert(WPR == 1 || WPR == 4, "the workgroup's barrier is the row's");
+    __shared__ int part[2][4];
+    const int lane = WPR == 1 ? threadIdx.x & 63 : threadIdx.x;
+    const int r = WPR == 1 ? blockIdx.x * 4 + (threadIdx.x >> 6) : blockIdx.x;
     if (r >= d_out) return;
     const size_t row0 = (size_t)r * d_in;
-    const bool quads = NQ > 1 || d_in >= 4;
+    const bool quads = NQ > 1 || WPR > 1 || d_in >= 4;
     struct __attribute__((packed, aligned(4))) F4 { float x, y, z, w; };
-    auto col0 = [&](int q) { return 4 * (lane + 64 * q); };
+    auto col0 = [&](int q) { return 4 * (lane + 64 * WPR * q); };
+    // a number of each of the row's wavefronts, summed (two places in turn: one barrier per sum)
+    int turn = 0;
+    auto row_sum = [&](int n) {
+        if (WPR == 1) return n;
+        if ((threadIdx.x & 63) == 0) part[turn][threadIdx.x >> 6] = n;
+        __syncthreads();
+        const int total = part[turn][0] + part[turn][1] + part[turn][2] + part[turn][3];
+        turn ^= 1;
+        return __builtin_amdgcn_readfirstlane(total);
+    };
 
     int rank[N];             // magnitude bits (below 2^31), or -1: not a column of the row
     uint32_t surv[(N + 31) / 32];
@@ -602,7 +617,7 @@ __global__ __launch_bounds__(256) void k_row_update(const float* __restrict__ W,
         int mine = 0;
 #pragma unroll
         for (int i = 0; i < (N + 31) / 32; ++i) mine += __popc(surv[i]);
-        kept = (int)wave_total((unsigned)mine);
+        kept = row_sum((int)wave_total((unsigned)mine));
     }
     const int target = (int)k_new;   // at most d_in
     // trim: the row keeps its `target` largest surviving weights; grow: the `target - kept` largest gradients among its free positions
@@ -617,7 +632,7 @@ __global__ __launch_bounds__(256) void k_row_update(const float* __restrict__ W,
             int n = 0;
 #pragma unroll
             for (int e = 0; e < N; ++e) n += __popcll(__ballot(rank[e] >= thr));
-            return n;
+            return row_sum(n);
         };
         // count(T) >= want > count(hi).  Rows regrow close to the layer-wide gradient threshold of step 3, so the walk starts
         // there with steps that double, and halves the interval it lands in: about 8 counts on real-valued contents, where
@@ -660,7 +675,7 @@ __global__ __launch_bounds__(256) void k_row_update(const float* __restrict__ W,
                     const int own = col0(e / 4), c = (quads ? quad_first(own, d_in) : 0) + e % 4;
                     n += __popcll(__ballot(rank[e] == T && c < col));
                 }
-                return n;
+                return row_sum(n);
             };
             int c = 0;            // the largest column with fewer than r_eq equal ranks in front of it
             for (int bit = 13; bit >= 0; --bit)
@@ -771,23 +786,24 @@ srigl_status srigl_mask_update(const float* W, const uint8_t* mask, const float*
                        (unsigned long long)K_upd, (long long)budget, report);
     const dim3 row_grid((unsigned)((d_out + 3) / 4));
     hipLaunchKernelGGL(k_row_salient, row_grid, dim3(256), 0, st, W, mask, grad, d_out, d_in, k, gamma_percent, s, remains);
-    hipLaunchKernelGGL(k_collect<false>, dim3(blocks), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, n4, d_in, (unsigned long long)K_upd, s,
+    // (most updates ablate nothing and this launch returns at once: it takes few workgroups, whose start is then all it costs)
+    hipLaunchKernelGGL(k_collect<false>, dim3(std::min(blocks, 64u)), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, n4, d_in, (unsigned long long)K_upd, s,
                        candA, candB, cap);
     hipLaunchKernelGGL(k_final<false>, dim3(1), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, d_in, s, candA, candB, cap,
                        (unsigned long long)K_upd, (long long)budget, report);
-#define SRIGL_ROW_UPDATE(NQ) \
-    hipLaunchKernelGGL(k_row_update<NQ>, row_grid, dim3(256), 0, st, W, mask, grad, d_out, d_in, remains, s, mask_out, W_out)
+#define SRIGL_ROW_UPDATE(NQ, WPR)                                                                                                      \
+    hipLaunchKernelGGL((k_row_update<NQ, WPR>), WPR == 1 ? row_grid : dim3((unsigned)d_out), dim3(256), 0, st, W, mask, grad, d_out, d_in, remains, \
+                       s, mask_out, W_out)
     const int nq = (d_in + 255) / 256;
-    if (nq <= 1) SRIGL_ROW_UPDATE(1);
-    else if (nq <= 2) SRIGL_ROW_UPDATE(2);
-    else if (nq <= 3) SRIGL_ROW_UPDATE(3);
-    else if (nq <= 4) SRIGL_ROW_UPDATE(4);
-    else if (nq <= 6) SRIGL_ROW_UPDATE(6);
-    else if (nq <= 8) SRIGL_ROW_UPDATE(8);
-    else if (nq <= 12) SRIGL_ROW_UPDATE(12);
-    else if (nq <= 16) SRIGL_ROW_UPDATE(16);
-    else if (nq <= 24) SRIGL_ROW_UPDATE(24);
-    else SRIGL_ROW_UPDATE(32);
+    if (nq <= 1) SRIGL_ROW_UPDATE(1, 1);
+    else if (nq <= 2) SRIGL_ROW_UPDATE(2, 1);
+    else if (nq <= 3) SRIGL_ROW_UPDATE(3, 1);
+    else if (nq <= 4) SRIGL_ROW_UPDATE(4, 1);
+    else if (nq <= 8) SRIGL_ROW_UPDATE(2, 4);
+    else if (nq <= 12) SRIGL_ROW_UPDATE(3, 4);
+    else if (nq <= 16) SRIGL_ROW_UPDATE(4, 4);
+    else if (nq <= 24) SRIGL_ROW_UPDATE(6, 4);
+    else SRIGL_ROW_UPDATE(8, 4);
 #undef SRIGL_ROW_UPDATE
     return hip_ok(hipGetLastError());
 }
