@@ -12,7 +12,7 @@
 //
 // The blocked copy (srigl_block_terms) holds the terms of 32 stored rows x 64 columns next to each other, each as the weight
 // beside its place in the LDS tile: 64 lanes fetch up to 256 of them with one 16-byte load each and store them with four 2-byte
-// LDS writes each.  (From the row-major copies the same kernel needed 327 us instead of 251 on 4096 -> 16384, 13108 stored
+// LDS writes each.  (From the row-major copies the same kernel needed 327 us instead of 251 (245 by now) on 4096 -> 16384, 13108 stored
 // rows, K = 205, 2048 batch rows: every row's few terms of a piece were a cache line and a lane's predicated writes of their own.)
 //
 // Pipeline (an iteration is CC pieces of 64 columns): x of the next iteration goes from memory straight into the other of two LDS
@@ -146,9 +146,8 @@ __device__ __forceinline__ float sum_terms(const BlockedArgs& p, int m, int s) {
 struct Finish {
     const BlockedArgs& p;
     static constexpr bool kRepairs = true;
-    __device__ float stored(float sum, float bv) const { return apply_act(sum + bv, p.act); }
+    __device__ int activation() const { return p.act; }
     __device__ float repaired(int m, int s) const { return sum_terms(p, m, s); }
-    __device__ float ablated(float bv) const { return apply_act(bv, p.act); }
 };
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
@@ -157,7 +156,7 @@ struct __attribute__((packed, aligned(2))) Half4 { uint32_t a, b; };
 // LDS: two stages of x, two of the weight tile, the lists, all of it reused by the epilogue's tile; behind it the epilogue's table
 template <int UA, int BM, int BN, int WGM, int WGN, int CC>
 constexpr size_t blocked_table_at() {
-    constexpr size_t stages = (size_t)CC * 128 * 2 * (BM + BN) + (size_t)WGM * WGN * UA * 1024, tile = EpiLayout<BM, BN, WGM>::TILE_BYTES;
+    constexpr size_t stages = (size_t)CC * 128 * 2 * (BM + BN) + (size_t)WGM * WGN * UA * 1024, tile = EpiLayout<BN, WGM>::TILE_BYTES;
     return stages > tile ? stages : tile;
 }
 
@@ -329,7 +328,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
     const TileColumns cols = tile_columns(n0, BN, p.active, p.n_active, p.d_out);
     issue_list(0);
     issue_x(0);
-    fill_table<NWAVES * 64>(table, cols.lo, cols, n0, p.active, p.bias);
+    fill_table<BN, WGM, NWAVES * 64>(table, cols.lo, cols, n0, p.active, p.bias);
     if (!DIRECT) store_x(0);
     wait_loads<0>();
     build(0);
@@ -382,7 +381,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
 template <int UA, bool DIRECT, int BM, int BN, int WGM, int WGN, int CC>
 static srigl_status launch_tile(const BlockedArgs& args, hipStream_t st) {
     auto kern = k_fwd_blocked<UA, DIRECT, BM, BN, WGM, WGN, CC>;
-    constexpr size_t lds = blocked_table_at<UA, BM, BN, WGM, WGN, CC>() + kTableBytes;
+    constexpr size_t lds = blocked_table_at<UA, BM, BN, WGM, WGN, CC>() + EpiLayout<BN, WGM>::TABLE_BYTES;
     static_assert(lds <= kLdsMax, "LDS");
     static LdsLimit lds_limit;
     if (lds_limit.ensure(kern, lds) != SRIGL_OK) return SRIGL_ERR_HIP;
@@ -412,9 +411,9 @@ static int choose_blocked_tile(int B, int d_in, int n_active, double* us) {
     const int chunks = (d_in + kSegCols - 1) / kSegCols;
     auto workgroups = [&](int t) { return (double)((B + t - 1) / t) * ((n_active + t - 1) / t); };
     const double w64 = workgroups(64), w128 = workgroups(128), w256 = workgroups(256), it64 = (chunks + 1) / 2;
-    const double t64 = 3.0 + (w64 <= 256 ? 0.8 * it64 + 3.2 : std::ceil(w64 / 512) * (1.02 * it64 + 3.5));
-    const double t128 = w128 <= 256 ? 8.0 + 0.9 * chunks : 3.0 + std::ceil(w128 / 512) * (9.0 + 1.02 * chunks);
-    const double t256 = 3.0 + std::ceil(w256 / 256) * (15.0 + 1.6 * chunks);
+    const double t64 = 3.0 + (w64 <= 256 ? 0.8 * it64 + 1.7 : std::ceil(w64 / 512) * (1.05 * it64 + 2.5));
+    const double t128 = w128 <= 256 ? 7.5 + 0.85 * chunks : 3.0 + std::ceil(w128 / 512) * (7.0 + 1.1 * chunks);
+    const double t256 = 3.0 + std::ceil(w256 / 256) * (11.0 + 1.6 * chunks);
     *us = std::min(t64, std::min(t128, t256));
     return *us == t64 ? SRIGL_BLOCKED_64 : (*us == t128 ? SRIGL_BLOCKED_128 : SRIGL_BLOCKED_256);
 }

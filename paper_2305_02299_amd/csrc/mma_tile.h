@@ -57,18 +57,7 @@ __device__ __forceinline__ bool tile_of_workgroup(int id, int tiles_m, int tiles
     return true;
 }
 
-// LDS use of the epilogue: an fp32 tile (pitch BN + 4) of all BM rows when that fits, else of the rows of one wavefront row at
-// a time, and the column table with its bias values.
-constexpr int kTableCols = 1024;   // columns of y per pass over the tile
-constexpr size_t kTableBytes = (size_t)kTableCols * 8;
-template <int BM, int BN, int WGM>
-struct EpiLayout {
-    static constexpr int PITCH = BN + 4;
-    static constexpr int PHASES = ((size_t)BM * PITCH * 4 + kTableBytes <= kLdsMax) ? 1 : WGM;
-    static constexpr size_t TILE_BYTES = (size_t)(BM / PHASES) * PITCH * 4;
-    static constexpr size_t BYTES = TILE_BYTES + kTableBytes;
-};
-
+// ---- epilogue: a tile's sums to their columns of y ----
 // The columns of y that the tile at stored neuron n0 writes: its stored neurons and the ablated ones in front of them (behind the
 // last one too in the last tile) are one contiguous range.
 struct TileColumns { int lo, hi, stored; };
@@ -78,17 +67,34 @@ __device__ __forceinline__ TileColumns tile_columns(int n0, int bn, const int32_
     return {max((n0 > 0) ? active[n0 - 1] + 1 : 0, 0), min((n0 + cnt == n_active) ? d_out - 1 : active[n0 + cnt - 1], d_out - 1), cnt};
 }
 
-// The table of columns cc .. cc + kTableCols - 1 of that range: table[k] = the stored neuron of the tile that column cc + k is, or -1
-// (the column is its bias); bias values behind it.  A stored neuron's thread marks the gap in front of it too.  No barrier.
-template <int NT>
+// LDS of the epilogue: one 32-row part of each wavefront row's tile at a time, at the rows' final columns (a window of COLS of them;
+// most ranges fit one), and the tables: the stored neurons' places in the range, for the window's columns which neuron
+// they are (-1: ablated) and their bias.
+template <int BN, int WGM>
+struct EpiLayout {
+    static constexpr int COLS = BN >= 256 ? 512 : 256, ROWS = 32 * WGM, PITCH = COLS + 4;
+    static constexpr size_t TILE_BYTES = (size_t)ROWS * PITCH * 4, TABLE_BYTES = (size_t)BN * 4 + (size_t)COLS * 8;
+    static constexpr size_t BYTES = TILE_BYTES + TABLE_BYTES;
+};
+
+// Fills the tables for the window from column cc on (the places only with the first window).  No barrier: a stored neuron's thread
+// marks the gap in front of it too.
+template <int BN, int WGM, int NT>
 __device__ __forceinline__ void fill_table(unsigned char* at, int cc, const TileColumns& c, int n0, const int32_t* active, const float* bias) {
-    int* table = reinterpret_cast<int*>(at);
-    float* tbias = reinterpret_cast<float*>(at + kTableCols * 4);
-    const int tid = threadIdx.x, wc = min(kTableCols, c.hi - cc + 1);
+    constexpr int COLS = EpiLayout<BN, WGM>::COLS;
+    int* const place = reinterpret_cast<int*>(at);
+    int* const table = place + BN;
+    float* const tbias = reinterpret_cast<float*>(table + COLS);
+    const int tid = threadIdx.x, wc = min(COLS, c.hi - cc + 1);
     for (int k = tid; k < wc; k += NT) tbias[k] = bias ? bias[cc + k] : 0.0f;
-    for (int s = tid; s < c.stored; s += NT) {
+    for (int s = tid; s < BN; s += NT) {
+        if (s >= c.stored) {
+            place[s] = -1;
+            continue;
+        }
         const int col = active ? active[n0 + s] : n0 + s;
         const int prev = s == 0 ? c.lo - 1 : (active ? active[n0 + s - 1] : n0 + s - 1);
+        place[s] = col >= c.lo && col <= c.hi ? col - c.lo : -1;
         for (int k = max(prev + 1 - cc, 0); k < min(col - cc, wc); ++k) table[k] = -1;
         if (col >= cc && col - cc < wc) table[col - cc] = s;
         if (s == c.stored - 1)
@@ -97,96 +103,128 @@ __device__ __forceinline__ void fill_table(unsigned char* at, int cc, const Tile
 }
 
 // Epilogue of a BM x BN tile at batch row m0, stored neuron n0, held as 32x32 blocks (accumulator register e of lane l is row
-// 8*(e/4) + 4*(l/32) + e%4, column l%32).  The tile's columns of y are written row by row with neighbouring lanes on neighbouring
-// columns: the table says which stored neuron of the tile a column is, and the accumulators pass through an LDS tile at smem.
-// No column of y is touched twice and none is left out.  The LDS must be free (the caller has waited for its own loads into it and
-// passed a barrier); have_table: the first columns' table stands there already.
-// finish.stored(sum, bias) and finish.ablated(bias) give the values to write; finish.repaired(m, s) the sum to use where one is not
-// finite (Finish::kRepairs).
+// 8*(e/4) + 4*(l/32) + e%4, column l%32).  Every wavefront puts 32 of its rows at a time into LDS, sums plus bias at their final columns,
+// and the rows are then read and written 4 columns per lane and 4 rows at a time, ablated columns from registers.  No column
+// of y is touched twice and none is left out.  (A 256 x 256 tile's epilogue took 28 us with one value at a time, each behind a read of
+// a column table and one of the tile, and 10 with 4-way bank conflicts of lanes that gathered four columns each.)
+// The LDS must be free (the caller has waited for its own loads into it and passed a barrier); have_table: the first window's tables
+// stand at table_at already.  finish.repaired(m, s): the sum to use where one is not finite (Finish::kRepairs); finish.activation():
+// an activation applied to every value, or SRIGL_ACT_NONE.  Both are rare or slow paths and written once, as loops over values in
+// LDS: inlined for each of a lane's 16 values they made the epilogue kilobytes of code that every workgroup fetched anew.
+// With that and the float4 rows a 768 -> 3072 layer in 256 x 256 tiles went from 36.4 to 32.3 us, 4096 -> 16384 at batch 2048 from 297 to
+// 279 in 128 x 128 tiles.  Narrow tiles put 2 or 4 rows into one LDS request (16 or 32 lanes each): with 64 lanes on a row 64 x 64
+// tiles took 11.5 us instead of 9.4 on 768 -> 3072 at batch 128.
 template <int BM, int BN, int WGM, int WGN, int TM, int TN, typename Finish>
 __device__ __forceinline__ void store_tile(unsigned char* smem, unsigned char* table_at, bool have_table, const f32x16_t (&acc)[TM][TN],
                                            const TileColumns& cols, int m0, int n0, int B, const int32_t* active, const float* bias,
                                            int d_out, float* y, const Finish& finish) {
-    using EL = EpiLayout<BM, BN, WGM>;
-    constexpr int NWAVES = WGM * WGN, NT = NWAVES * 64, WTM = BM / WGM, WTN = BN / WGN;
-    constexpr int PITCH = EL::PITCH, EPH = EL::PHASES, PROWS = BM / EPH, WPP = WGM / EPH;
-    // A lane keeps NJ neighbouring columns of a run of 64 NJ in registers and takes NI rows at a time: 16 outputs' LDS reads in
-    // flight, then NI stores of NJ values.  (One value at a time, each behind a read of the table and then one of the tile, a
-    // 256 x 256 tile's epilogue took 28 us; with 4-byte stores 12.)
-    constexpr int NJ = BN >= 256 ? 4 : BN / 64, NI = 16 / NJ;
-    typedef float Run __attribute__((ext_vector_type(NJ == 1 ? 2 : NJ), aligned(4)));
+    using EL = EpiLayout<BN, WGM>;
+    constexpr int NWAVES = WGM * WGN, WTM = BM / WGM, WTN = BN / WGN, PITCH = EL::PITCH;
+    // lanes that share a row (four columns each), rows per LDS request, runs of columns of a window
+    constexpr int LR = BN >= 256 ? 64 : BN / 4, RPI = 64 / LR, RUN = 4 * LR, RUNS = EL::COLS / RUN;
+    typedef float float4_t __attribute__((ext_vector_type(4)));
+    typedef float float4_at4_t __attribute__((ext_vector_type(4), aligned(4)));
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wv / WGN, wn = wv % WGN;
-    float* tile = reinterpret_cast<float*>(smem);                         // [PROWS][PITCH]
-    const int* table = reinterpret_cast<const int*>(table_at);
-    const float* tbias = reinterpret_cast<const float*>(table_at + kTableCols * 4);
-    for (int cc = cols.lo; cc <= cols.hi; cc += kTableCols) {
-        const int wc = min(kTableCols, cols.hi - cc + 1);
-        if (cc != cols.lo) __syncthreads();   // the previous pass is done with the table
-        if (cc != cols.lo || !have_table) fill_table<NT>(table_at, cc, cols, n0, active, bias);
+    float* const tile = reinterpret_cast<float*>(smem);
+    const int* const place = reinterpret_cast<const int*>(table_at);
+    const int* const table = place + BN;
+    float* const tbias = reinterpret_cast<float*>(table_at + (size_t)(BN + EL::COLS) * 4);
+    if (!have_table) {
+        fill_table<BN, WGM, NWAVES * 64>(table_at, cols.lo, cols, n0, active, bias);
+        __syncthreads();
+    }
+    for (int cc = cols.lo; cc <= cols.hi; cc += EL::COLS) {
+        const int wc = min(EL::COLS, cols.hi - cc + 1);
+        if (cc != cols.lo) {
+            __syncthreads();   // the previous window is done with the tables
+            fill_table<BN, WGM, NWAVES * 64>(table_at, cc, cols, n0, active, bias);
+            __syncthreads();
+        }
+        if (finish.activation() != SRIGL_ACT_NONE) {
+            __syncthreads();
+            for (int k = tid; k < wc; k += NWAVES * 64)
+                if (table[k] < 0) tbias[k] = apply_act(tbias[k], finish.activation());
+            __syncthreads();
+        }
+        int at[TN];        // this lane's columns in the window
+        float badd[TN];
 #pragma unroll
-        for (int ph = 0; ph < EPH; ++ph) {
-            if (ph > 0) __syncthreads();   // tile free again
-            if (wm / WPP == ph) {
+        for (int j = 0; j < TN; ++j) {
+            const int q = place[wn * WTN + j * 32 + (lane & 31)];
+            at[j] = q < 0 ? -1 : q - (cc - cols.lo);
+            if (at[j] >= wc) at[j] = -1;
+            badd[j] = tbias[max(at[j], 0)];
+        }
+        float flat[RUNS][4];
+        int gaps = 0;      // bit 4 run + j: an ablated column, or none of the window
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
+        for (int run = 0; run < RUNS; ++run)
 #pragma unroll
-                    for (int j = 0; j < TN; ++j)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e)
-                            tile[((wm % WPP) * WTM + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)) * PITCH + wn * WTN + j * 32 + (lane & 31)] =
-                                acc[i][j][e];
+            for (int j = 0; j < 4; ++j) {
+                const int k = RUN * run + 4 * (lane % LR) + j, in = min(k, wc - 1);
+                flat[run][j] = tbias[in];
+                if (k >= wc || table[in] < 0) gaps |= 1 << (4 * run + j);
             }
-            __syncthreads();   // tile, table and bias values complete
-            const int rows = min(PROWS, B - (m0 + ph * PROWS));
-            for (int kb = 0; kb < wc; kb += 64 * NJ) {
-                const int k0 = kb + NJ * lane;   // this lane's first column
-                int tix[NJ];
-                float bv[NJ], flat[NJ];
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    const int k = min(k0 + j, wc - 1);
-                    tix[j] = table[k];
-                    bv[j] = tbias[k];
-                    flat[j] = finish.ablated(bv[j]);
+        for (int i = 0; i < TM; ++i) {
+            if (i > 0 || cc != cols.lo) __syncthreads();   // the rows before have been read
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                if (at[j] >= 0) {
+                    float* const t = tile + (wm * 32 + 4 * (lane >> 5)) * PITCH + at[j];
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) t[(8 * (e >> 2) + (e & 3)) * PITCH] = acc[i][j][e] + badd[j];
                 }
-                for (int r = NI * wv; r < rows; r += NI * NWAVES) {
-                    float v[NI][NJ];
+            }
+            __syncthreads();
+            for (int r0 = 4 * RPI * wv; r0 < EL::ROWS; r0 += 4 * RPI * NWAVES) {   // 4 RPI rows of one wavefront row
+                const int row = r0 + lane / LR, m = m0 + (r0 >> 5) * WTM + i * 32 + (row & 31);   // this lane's rows: every RPI-th from here
+                if (m - lane / LR >= B) continue;
+#pragma unroll
+                for (int run = 0; run < RUNS; ++run) {
+                    if (RUN * run >= wc) break;
+                    const int k0 = RUN * run + 4 * (lane % LR);
+                    float* const t0 = tile + row * PITCH + k0;
+                    float4_t v[4];
                     bool finite = true;
 #pragma unroll
-                    for (int i = 0; i < NI; ++i)
+                    for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const float4_t*>(t0 + u * RPI * PITCH);
 #pragma unroll
-                        for (int j = 0; j < NJ; ++j) {
-                            v[i][j] = tile[min(r + i, PROWS - 1) * PITCH + max(tix[j], 0)];
-                            if (Finish::kRepairs) finite = finite && fabsf(v[i][j]) <= 3.4028234e38f;
+                    for (int u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            if ((gaps >> (4 * run + j)) & 1) v[u][j] = 0.0f;
+                            else if (Finish::kRepairs) finite = finite && fabsf(v[u][j]) <= 3.4028234e38f;
                         }
-                    if (Finish::kRepairs && __any(!finite)) {
+                    if ((Finish::kRepairs && __any(!finite)) || finish.activation() != SRIGL_ACT_NONE) {
 #pragma unroll 1
-                        for (int e = 0; e < NI * NJ; ++e) {
-                            const int row = r + e / NJ, t = table[min(k0 + e % NJ, wc - 1)];
-                            if (t >= 0 && row < rows && !(fabsf(tile[row * PITCH + t]) <= 3.4028234e38f))
-                                tile[row * PITCH + t] = finish.repaired(m0 + ph * PROWS + row, n0 + t);
+                        for (int q = 0; q < 16; ++q) {
+                            const int k = k0 + (q & 3), mq = m + (q >> 2) * RPI;
+                            float* const at_q = t0 + (q >> 2) * RPI * PITCH + (q & 3);
+                            if (k >= wc || table[k] < 0 || mq >= B) continue;
+                            float f = *at_q;
+                            if (Finish::kRepairs && !(fabsf(f) <= 3.4028234e38f)) f = finish.repaired(mq, n0 + table[k]) + tbias[k];
+                            *at_q = apply_act(f, finish.activation());
                         }
 #pragma unroll
-                        for (int i = 0; i < NI; ++i)
-#pragma unroll
-                            for (int j = 0; j < NJ; ++j) v[i][j] = tile[min(r + i, PROWS - 1) * PITCH + max(tix[j], 0)];
+                        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const float4_t*>(t0 + u * RPI * PITCH);
                     }
-                    float* yr = y + (size_t)(m0 + ph * PROWS + r) * d_out + cc + k0;
+                    float* const yr = y + (size_t)m * d_out + cc + k0;
 #pragma unroll
-                    for (int i = 0; i < NI; ++i) {
-                        if (r + i >= rows) break;
-                        Run run;
+                    for (int u = 0; u < 4; ++u) {
 #pragma unroll
-                        for (int j = 0; j < NJ; ++j) run[j] = tix[j] >= 0 ? finish.stored(v[i][j], bv[j]) : flat[j];
-                        if (k0 + NJ <= wc) {
-                            if constexpr (NJ == 1) __builtin_nontemporal_store(run[0], yr + (size_t)i * d_out);
-                            else __builtin_nontemporal_store(run, reinterpret_cast<Run*>(yr + (size_t)i * d_out));
-                        } else {
+                        for (int j = 0; j < 4; ++j) v[u][j] = (gaps >> (4 * run + j)) & 1 ? flat[run][j] : v[u][j];
+                        float* const yu = yr + (size_t)(u * RPI) * d_out;
+                        if (m + u * RPI < B) {
+                            if (k0 + 4 <= wc) {
+                                __builtin_nontemporal_store(v[u], reinterpret_cast<float4_at4_t*>(yu));
+                            } else {
 #pragma unroll
-                            for (int j = 0; j + 1 < NJ; ++j)
-                                if (k0 + j < wc) yr[(size_t)i * d_out + j] = run[j];
+                                for (int j = 0; j < 3; ++j)
+                                    if (k0 + j < wc) yu[j] = v[u][j];
+                            }
                         }
                     }
                 }

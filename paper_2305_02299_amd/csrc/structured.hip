@@ -140,9 +140,8 @@ __device__ __forceinline__ void mma_block(f32x16_t& acc, const float4& a, const 
 // what store_tile writes: the sum plus the bias; the bias of an ablated neuron
 struct Plain {
     static constexpr bool kRepairs = false;
-    __device__ float stored(float sum, float b) const { return sum + b; }
+    __device__ constexpr int activation() const { return SRIGL_ACT_NONE; }
     __device__ float repaired(int, int) const { return 0.0f; }
-    __device__ float ablated(float b) const { return b; }
 };
 
 // BM x BN output tile per workgroup of WGM x WGN wavefronts; NS >= 2 LDS stages of SLAB (128 or 64) bytes of K per row.
@@ -316,7 +315,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_structured_gemm(const T* __r
 
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // the re-issued last stages may still be landing in the ring
     __syncthreads();
-    store_tile<BM, BN, WGM, WGN>(smem, smem + EpiLayout<BM, BN, WGM>::TILE_BYTES, false, acc, tile_columns(n0, BN, active, n_active, d_out), m0, n0, B,
+    store_tile<BM, BN, WGM, WGN>(smem, smem + EpiLayout<BN, WGM>::TILE_BYTES, false, acc, tile_columns(n0, BN, active, n_active, d_out), m0, n0, B,
                                     active, bias, d_out, y, Plain());
 }
 
@@ -324,7 +323,7 @@ template <typename T, int BM, int BN, int WGM, int WGN, int NS, int SLAB, bool R
 static srigl_status launch_gemm_r(const void* x, int B, int d_in, const void* Wd, const int32_t* active, int n_active, const float* bias,
                                 int d_out, float* y, int splits, float* part, hipStream_t st) {
     auto kern = k_structured_gemm<T, BM, BN, WGM, WGN, NS, SLAB, RAGGED>;
-    constexpr size_t ring = (size_t)NS * (BM + BN) * SLAB, epi = EpiLayout<BM, BN, WGM>::BYTES;
+    constexpr size_t ring = (size_t)NS * (BM + BN) * SLAB, epi = EpiLayout<BN, WGM>::BYTES;
     constexpr size_t lds = ring > epi ? ring : epi;
     static_assert(lds <= kLdsMax, "LDS");
     static LdsLimit lds_limit;
