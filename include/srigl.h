@@ -313,12 +313,14 @@ srigl_status srigl_condensed_linear_fwd_idx16(const void* x, srigl_dtype x_dtype
  * srigl_block_terms: writes it.  W_c bf16, idx of idx_bits (32 or 16) bits, seg as written for these idx (rows ascending); blocked
  * 16-byte aligned.  SRIGL_ERR_UNSUPPORTED for d_in < 8 or > 65536.
  * srigl_blocked_tile: the tile the library would take for B rows of x, or 0 where srigl_condensed_linear_fwd is expected to be
- * faster or the sizes are not supported.  Host arithmetic on sizes.
+ * faster or the sizes are not supported: a srigl_blocked_tile_t, or first | second << 4 | columns << 8 for stored rows split in two launches,
+ * `columns` tile columns in the first shape and the rest in the second.  Host arithmetic on sizes.
  * srigl_blocked_linear_fwd: the forward call; x[B][d_in] bf16, the copy and the W_c / idx it was made from (read again for sums that are
  * not finite), everything else as in srigl_condensed_linear_fwd_act.  tile 0: the tile of smallest expected time.
  * srigl_fwd_plan_query describes the calls that read W_c / idx (or the streaming copy), not this one.  Device pointers,
  * asynchronous on `stream`. */
-typedef enum { SRIGL_BLOCKED_64 = 1, SRIGL_BLOCKED_128 = 2, SRIGL_BLOCKED_256 = 3 } srigl_blocked_tile_t;   /* batch rows = stored rows */
+/* 64 x 64, 128 x 128, 256 x 256 batch rows x stored rows; 256 batch rows x 192 stored rows */
+typedef enum { SRIGL_BLOCKED_64 = 1, SRIGL_BLOCKED_128 = 2, SRIGL_BLOCKED_256 = 3, SRIGL_BLOCKED_192 = 4 } srigl_blocked_tile_t;
 
 size_t srigl_blocked_bytes(int32_t n_rows, int32_t K, int32_t d_in);
 

@@ -22,7 +22,7 @@ REPR_CONDENSED, REPR_STRUCTURED = 0, 1
 ACT_NONE, ACT_RELU, ACT_GELU = 0, 1, 2
 FWD_AUTO, FWD_GENERIC, FWD_KLANE, FWD_ROWLANE, FWD_ROWLOOP = range(5)
 TILE_AUTO, TILE_256x256, TILE_256x256_H, TILE_256x128_W4, TILE_256x128, TILE_128x128, TILE_64x64 = range(7)
-BLOCKED_64, BLOCKED_128, BLOCKED_256 = 1, 2, 3
+BLOCKED_64, BLOCKED_128, BLOCKED_256, BLOCKED_192 = 1, 2, 3, 4
 TILES = {"256x256": TILE_256x256, "256x256_h": TILE_256x256_H, "256x128_w4": TILE_256x128_W4, "256x128": TILE_256x128,
          "128x128": TILE_128x128, "64x64": TILE_64x64}
 
@@ -302,7 +302,7 @@ def srigl_block_terms(W_c, idx, seg, n_rows, K, d_in, blocked):
 
 
 def srigl_blocked_tile(B: int, d_in: int, n_active: int, K: int, d_out: int) -> int:
-    """BLOCKED_* code of the tile the library would take, 0 where it would not take the matrix-core form."""
+    """Code of the tile the library would take (BLOCKED_*, or two of them and where the rows are split: see srigl.h), 0 where it would not take the matrix-core form."""
     return int(lib.srigl_blocked_tile(int(B), int(d_in), int(n_active), int(K), int(d_out)))
 
 

@@ -12,7 +12,7 @@
 //
 // The blocked copy (srigl_block_terms) holds the terms of 32 stored rows x 64 columns next to each other, each as the weight
 // beside its place in the LDS tile: 64 lanes fetch up to 256 of them with one 16-byte load each and store them with four 2-byte
-// LDS writes each.  (From the row-major copies the same kernel needed 327 us instead of 251 (245 by now) on 4096 -> 16384, 13108 stored
+// LDS writes each.  (From the row-major copies the same kernel needed 327 us instead of 251 (233 by now) on 4096 -> 16384, 13108 stored
 // rows, K = 205, 2048 batch rows: every row's few terms of a piece were a cache line and a lane's predicated writes of their own.)
 //
 // Pipeline (an iteration is CC pieces of 64 columns): x of the next iteration goes from memory straight into the other of two LDS
@@ -127,7 +127,8 @@ struct BlockedArgs {
     const int32_t* active;
     const float* bias;
     float* y;
-    int B, d_in, n_active, K, d_out, idx_u16, act, tiles_m, tiles_n;
+    int B, d_in, n_active, K, d_out, idx_u16, act;
+    int n_base, tiles_m, tiles_n;   // of the launch: its first stored row, its tiles
 };
 
 // The sum of one output from its own terms.
@@ -169,7 +170,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
     constexpr int XSTAGE = CC * BM * 128, WSTAGE = CC * BN * 128;
     constexpr int XP = CC * BM / 8 / NWAVES;   // 1 KB pieces of the x stage per wavefront (8 rows of 128 bytes each)
     constexpr int KSTEPS = 4 * CC;             // MFMA steps of 16 columns per iteration
-    static_assert(CC * BN == kBlockRows * NWAVES, "one block per wavefront and iteration");
+    constexpr int BLOCKS = CC * BN / kBlockRows;   // of an iteration, one per wavefront
+    static_assert(BLOCKS <= NWAVES && (CC == 1 || BLOCKS == NWAVES), "one block per wavefront and iteration");
     static_assert(CC * BM % (8 * NWAVES) == 0 && WTM % 32 == 0 && WTN % 32 == 0 && BM % 16 == 0, "tile shape");
     unsigned char* const wstages = smem + 2 * XSTAGE;
     unsigned char* const lstages = wstages + 2 * WSTAGE;
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
     const int d_in = p.d_in;
     int tile_m, tile_n;
     if (!tile_of_workgroup(blockIdx.x, p.tiles_m, p.tiles_n, &tile_m, &tile_n)) return;
-    const int m0 = tile_m * BM, n0 = tile_n * BN;
+    const int m0 = tile_m * BM, n0 = p.n_base + tile_n * BN;
     const int n_chunks = (d_in + 63) >> 6, n_it = (n_chunks + CC - 1) / CC;
 
     // ---- x: a lane brings 16 bytes per pass; rows past the batch re-read the last one (never stored), pieces past the end of
@@ -239,7 +241,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
 
     // ---- terms: wavefront wv builds the block of rows 32 * (wv % (BN / 32)) of the tile, sub-tile wv / (BN / 32)
     const int group = n0 / kBlockRows + wv % (BN / kBlockRows), sub = wv / (BN / kBlockRows);
-    const bool has_rows = group * kBlockRows < p.n_active;
+    const bool builds = BLOCKS == NWAVES || wv < BLOCKS;
+    const bool has_rows = builds && group * kBlockRows < p.n_active;
     const uint32_t* const offs = p.table + (size_t)(has_rows ? group : 0) * (n_chunks + 1);
     // lane l: where the lists of iterations 64 i + l begin and end, for even and for odd i
     uint32_t even_lo = 0, even_hi = 0, odd_lo = 0, odd_hi = 0;
@@ -265,6 +268,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
     };
     // (past the last iteration the last list is fetched again: the number of loads in flight at each wait is fixed)
     auto issue_list = [&](int it) {
+        if (!builds) return;
         if ((it & 63) == 0 && it < n_it) load_offsets(it);
         uint32_t lo, n;
         list_of(min(it, n_it - 1), &lo, &n);
@@ -279,6 +283,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
     // A block is built from its list, which has landed: the terms into registers, the tile cleared, the terms to their places; the
     // next list is requested into the slot that this one leaves.
     auto build = [&](int it) {
+        if (!builds) return;
         const uint32_t block = lds_at(wstages + (it & 1) * WSTAGE + wv * 4096), clear = block + (uint32_t)lane * 16u;
         const uint32_t slot = lds_at(list_slot + lane * 16);
         const u32x4_t zero = {0u, 0u, 0u, 0u};
@@ -379,7 +384,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
 }
 
 template <int UA, bool DIRECT, int BM, int BN, int WGM, int WGN, int CC>
-static srigl_status launch_tile(const BlockedArgs& args, hipStream_t st) {
+static srigl_status launch_tile(const BlockedArgs& args, int n_rows, hipStream_t st) {
     auto kern = k_fwd_blocked<UA, DIRECT, BM, BN, WGM, WGN, CC>;
     constexpr size_t lds = blocked_table_at<UA, BM, BN, WGM, WGN, CC>() + EpiLayout<BN, WGM>::TABLE_BYTES;
     static_assert(lds <= kLdsMax, "LDS");
@@ -387,35 +392,79 @@ static srigl_status launch_tile(const BlockedArgs& args, hipStream_t st) {
     if (lds_limit.ensure(kern, lds) != SRIGL_OK) return SRIGL_ERR_HIP;
     BlockedArgs p = args;
     p.tiles_m = (p.B + BM - 1) / BM;
-    p.tiles_n = (p.n_active + BN - 1) / BN;
+    p.tiles_n = (n_rows + BN - 1) / BN;
     const long long n_wg = ((long long)p.tiles_m * p.tiles_n + kXcds - 1) / kXcds * kXcds;
     if (n_wg > 0x7fffffffLL) return SRIGL_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(kern, dim3((unsigned)n_wg), dim3(WGM * WGN * 64), lds, st, p);
     return hip_ok(hipGetLastError());
 }
 
+// stored rows [p.n_base, p.n_base + n_rows) in one tile shape
 template <int UA, bool DIRECT>
-static srigl_status launch_shape(const BlockedArgs& p, int tile, hipStream_t st) {
+static srigl_status launch_shape(const BlockedArgs& p, int tile, int n_rows, hipStream_t st) {
     switch (tile) {
-        case SRIGL_BLOCKED_256: return launch_tile<UA, DIRECT, 256, 256, 2, 4, 1>(p, st);
-        case SRIGL_BLOCKED_128: return launch_tile<UA, DIRECT, 128, 128, 2, 2, 1>(p, st);
-        case SRIGL_BLOCKED_64: return launch_tile<UA, DIRECT, 64, 64, 2, 2, 2>(p, st);
+        case SRIGL_BLOCKED_256: return launch_tile<UA, DIRECT, 256, 256, 2, 4, 1>(p, n_rows, st);
+        case SRIGL_BLOCKED_192: return launch_tile<UA, DIRECT, 256, 192, 4, 2, 1>(p, n_rows, st);
+        case SRIGL_BLOCKED_128: return launch_tile<UA, DIRECT, 128, 128, 2, 2, 1>(p, n_rows, st);
+        case SRIGL_BLOCKED_64: return launch_tile<UA, DIRECT, 64, 64, 2, 2, 2>(p, n_rows, st);
         default: return SRIGL_ERR_INVALID_ARG;
     }
 }
+static int blocked_tile_rows(int tile) { return tile == SRIGL_BLOCKED_64 ? 64 : tile == SRIGL_BLOCKED_128 ? 128 : tile == SRIGL_BLOCKED_192 ? 192 : 256; }
 
-// Estimated time (us) in each tile, and the tile of smallest estimate (0: these sizes cannot run).  Fits of measurements on 13
-// layers (200..4096 wide, 300..16192 stored rows, 80-98 % sparse) at batches of 32 to 2048: a workgroup costs a fixed part (prologue,
-// epilogue) and a part per iteration; a compute unit holds one 256 x 256 workgroup, or two of the others, which then run slower each.
+// A tile code names the shape in its low four bits; with a second shape in the next four, the stored rows are split: the first `code >>
+// 8` tile columns in the first shape, the others in the second.
+template <int UA, bool DIRECT>
+static srigl_status launch_plan(BlockedArgs& p, int code, hipStream_t st) {
+    const int first = code & 15, second = (code >> 4) & 15;
+    const long long split = (long long)(code >> 8) * blocked_tile_rows(first);
+    p.n_base = 0;
+    if (second == 0) return code >> 8 ? SRIGL_ERR_INVALID_ARG : launch_shape<UA, DIRECT>(p, first, p.n_active, st);
+    if (code < 0 || split <= 0 || split >= p.n_active || second > SRIGL_BLOCKED_192) return SRIGL_ERR_INVALID_ARG;
+    if (const srigl_status rc = launch_shape<UA, DIRECT>(p, first, (int)split, st)) return rc;
+    p.n_base = (int)split;
+    return launch_shape<UA, DIRECT>(p, second, p.n_active - (int)split, st);
+}
+
+// Estimated time (us) of n stored rows in a tile shape.  Fits of measurements on 13 layers (200..4096 wide, 300..16192 stored rows,
+// 80-98 % sparse) at batches of 32 to 2048: a workgroup costs a fixed part (prologue, epilogue) and a part per iteration; a compute
+// unit holds one workgroup of the two large shapes, or two of the others, which then run slower each.
+static double blocked_tile_us(int tile, int B, int n, int chunks) {
+    const int bn = blocked_tile_rows(tile), bm = bn == 192 ? 256 : bn;
+    const double w = (double)((B + bm - 1) / bm) * ((n + bn - 1) / bn), it64 = (chunks + 1) / 2;
+    switch (tile) {
+        case SRIGL_BLOCKED_64: return 3.0 + (w <= 256 ? 0.8 * it64 + 1.7 : std::ceil(w / 512) * (1.05 * it64 + 2.5));
+        case SRIGL_BLOCKED_128: return 3.0 + (w <= 256 ? 4.5 + 0.85 * chunks : std::ceil(w / 512) * (7.0 + 1.1 * chunks));
+        case SRIGL_BLOCKED_192: return 3.0 + std::ceil(w / 256) * (10.0 + 1.3 * chunks);
+        default: return 3.0 + std::ceil(w / 256) * (11.0 + 1.6 * chunks);
+    }
+}
+
+// The tile code of smallest estimate.  Tiles of 256 x 256 are the most efficient ones, but 416 of them (13108 stored rows, batch 2048)
+// keep 256 compute units busy for two whole rounds where 1.6 would do.  So the large shapes are also tried for their full rounds
+// only, with the stored rows that are left in the shape that suits those.  Measured: that layer 240 -> 233 us (a part-filled round
+// runs faster than a full one, so less than the count of rounds promises); 546 -> 16192 at batch 606 in 256 x 192 tiles 26 us, 28 in
+// 256 x 256, 34 in 128 x 128.
 static int choose_blocked_tile(int B, int d_in, int n_active, double* us) {
     const int chunks = (d_in + kSegCols - 1) / kSegCols;
-    auto workgroups = [&](int t) { return (double)((B + t - 1) / t) * ((n_active + t - 1) / t); };
-    const double w64 = workgroups(64), w128 = workgroups(128), w256 = workgroups(256), it64 = (chunks + 1) / 2;
-    const double t64 = 3.0 + (w64 <= 256 ? 0.8 * it64 + 1.7 : std::ceil(w64 / 512) * (1.05 * it64 + 2.5));
-    const double t128 = w128 <= 256 ? 7.5 + 0.85 * chunks : 3.0 + std::ceil(w128 / 512) * (7.0 + 1.1 * chunks);
-    const double t256 = 3.0 + std::ceil(w256 / 256) * (11.0 + 1.6 * chunks);
-    *us = std::min(t64, std::min(t128, t256));
-    return *us == t64 ? SRIGL_BLOCKED_64 : (*us == t128 ? SRIGL_BLOCKED_128 : SRIGL_BLOCKED_256);
+    constexpr int kShapes[] = {SRIGL_BLOCKED_64, SRIGL_BLOCKED_128, SRIGL_BLOCKED_192, SRIGL_BLOCKED_256};
+    int best = 0;
+    *us = 0.0;
+    auto consider = [&](int code, double t) {
+        if (best == 0 || t < *us) { best = code; *us = t; }
+    };
+    for (int s : kShapes) consider(s, blocked_tile_us(s, B, n_active, chunks));
+    for (int first : {SRIGL_BLOCKED_256, SRIGL_BLOCKED_192}) {
+        const int bn = blocked_tile_rows(first);
+        const long long tiles_m = (B + 255) / 256, tiles_n = (n_active + bn - 1) / bn, rounds = tiles_m * tiles_n / 256;
+        const long long columns = rounds * 256 / tiles_m;
+        if (columns < 1 || columns >= tiles_n || columns >= (1 << 23)) continue;
+        const int done = (int)columns * bn;
+        const double head = blocked_tile_us(first, B, done, chunks);
+        for (int s : kShapes)
+            if (s != first) consider(first | s << 4 | (int)columns << 8, head + blocked_tile_us(s, B, n_active - done, chunks) - 1.0);
+    }
+    return best;
 }
 
 // Taken where its estimate is this far ahead of the gathering kernels' (both estimates are good to about 10 %; no measured
@@ -492,8 +541,8 @@ srigl_status srigl_blocked_linear_fwd(const void* x, int32_t B, int32_t d_in, co
     hipStream_t st = static_cast<hipStream_t>(stream);
     double us;
     if (tile == 0) tile = choose_blocked_tile(B, d_in, n_active, &us);
-    if (direct) return two ? launch_shape<2, true>(p, tile, st) : launch_shape<1, true>(p, tile, st);
-    return two ? launch_shape<2, false>(p, tile, st) : launch_shape<1, false>(p, tile, st);
+    if (direct) return two ? launch_plan<2, true>(p, tile, st) : launch_plan<1, true>(p, tile, st);
+    return two ? launch_plan<2, false>(p, tile, st) : launch_plan<1, false>(p, tile, st);
 }
 
 }  // extern "C"

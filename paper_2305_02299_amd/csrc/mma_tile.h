@@ -121,7 +121,7 @@ __device__ __forceinline__ void store_tile(unsigned char* smem, unsigned char* t
     using EL = EpiLayout<BN, WGM>;
     constexpr int NWAVES = WGM * WGN, WTM = BM / WGM, WTN = BN / WGN, PITCH = EL::PITCH;
     // lanes that share a row (four columns each), rows per LDS request, runs of columns of a window
-    constexpr int LR = BN >= 256 ? 64 : BN / 4, RPI = 64 / LR, RUN = 4 * LR, RUNS = EL::COLS / RUN;
+    constexpr int LR = BN >= 256 ? 64 : (BN >= 128 ? 32 : 16), RPI = 64 / LR, RUN = 4 * LR, RUNS = EL::COLS / RUN;
     typedef float float4_t __attribute__((ext_vector_type(4)));
     typedef float float4_at4_t __attribute__((ext_vector_type(4), aligned(4)));
     const int tid = threadIdx.x, lane = tid & 63;

@@ -12,7 +12,7 @@ from paper_2305_02299_amd import condense_layer
 
 pytestmark = pytest.mark.gpu
 
-TILES = {64: B_.BLOCKED_64, 128: B_.BLOCKED_128, 256: B_.BLOCKED_256}
+TILES = {64: B_.BLOCKED_64, 128: B_.BLOCKED_128, 256: B_.BLOCKED_256, 192: B_.BLOCKED_192}
 SHAPES = [   # d_in, d_out, K, B, ablated
     (64, 33, 5, 3, 0.0), (8, 40, 8, 65, 0.0), (65, 1, 4, 1, 0.0), (129, 300, 30, 64, 0.3), (1000, 257, 50, 129, 0.1), (546, 130, 98, 257, 0.0),
     (768, 513, 8, 70, 0.98), (4160, 70, 300, 66, 0.2), (200, 96, 200, 33, 0.5), (9000, 64, 40, 40, 0.0), (1024, 1500, 11, 20, 0.995)]
@@ -93,3 +93,27 @@ def test_layer_object_keeps_the_copy_and_renews_it():
     layer.W_c.mul_(2)
     gate(host(layer.forward(x)), (y_ref - L.bias) * 2 + L.bias, 2 * S, TOL_BF16)
     assert layer._blocked is not kept
+
+
+@pytest.mark.parametrize("first,second,columns", [(B_.BLOCKED_256, B_.BLOCKED_192, 2), (B_.BLOCKED_192, B_.BLOCKED_64, 3), (B_.BLOCKED_64, B_.BLOCKED_256, 1),
+                                                  (B_.BLOCKED_128, B_.BLOCKED_128, 4)])
+@pytest.mark.parametrize("abl", [0.0, 0.3])
+def test_split_rows(first, second, columns, abl):
+    """Stored rows in two launches of different tile shapes: every column written once, ablated ones at the seam included."""
+    d_in, d_out, K, B = 200, 900, 30, 300
+    L = si.make_layer(d_in, d_out, K, B, ablate_frac=abl, dtype="bf16", seed=columns)
+    W_c, idx, active = oracle_condensed(L)
+    n = len(active)
+    y_ref, S = oracle.fwd(L.x_bf16, W_c, idx, active, L.bias, d_out, want_scale=True)
+    Wd, ix, act = dev(W_c), dev(idx), dev(active) if n < d_out else None
+    blk = blocked(Wd, ix, dev(oracle_seg(idx, d_in)), d_in)
+    y = torch.full((B, d_out), float("nan"), device="cuda")
+    args = (dev(L.x_bf16), B, d_in, blk, Wd, ix, act, n, K, dev(L.bias), d_out, y)
+    B_.srigl_blocked_linear_fwd(*args, tile=first | second << 4 | columns << 8)
+    yh = host(y)
+    gate(yh, y_ref, S, TOL_BF16)
+    gone = np.setdiff1d(np.arange(d_out), active)
+    assert np.array_equal(yh[:, gone].view(np.uint32), np.tile(L.bias[gone], (B, 1)).view(np.uint32))
+    for bad in (first | second << 4, first | second << 4 | 100 << 8, first | columns << 8, 5):
+        with pytest.raises(B_.SriglError):
+            B_.srigl_blocked_linear_fwd(*args, tile=bad)
