@@ -18,6 +18,7 @@
 //
 // Eight launches.  768 x 3072, 90 % sparse: the walk by 8-bit digits through 19 launches took 98 us, 48 of them for three
 // passes whose LDS counters met in one bank, 19 for the row-wise radix walk.
+#include "scan_tail.h"
 #include "srigl_internal.h"
 #include <cstddef>
 
@@ -119,7 +120,7 @@ __global__ __launch_bounds__(kScanThreads) void k_hist(const float* __restrict__
         for (int u = 0; u < kQuads; ++u)
             if (b + u * kScanThreads + t < q1) each_of_quad(q[u], 0, element);
     }
-    for (unsigned int i = 4 * n4 + blockIdx.x * kScanThreads + t; i < N; i += gridDim.x * kScanThreads) element(i, mask[i], W[i], grad[i]);
+    each_of_tail(N, n4, blockIdx.x * kScanThreads + t, gridDim.x * kScanThreads, [&](unsigned int i) { element(i, mask[i], W[i], grad[i]); });
     __syncthreads();
     // neighbouring lanes add to neighbouring digits (an atomic instruction costs by the lines it touches: with four digits in a
     // row per thread the flush took half of the kernel's 11 us)
@@ -309,8 +310,8 @@ __global__ __launch_bounds__(kScanThreads) void k_collect(const float* __restric
         }
         if (++batches % 4 == 0 && b + kQuads * kScanThreads < q1) flush();   // (65536 elements, three percent of which the stage holds)
     }
-    for (unsigned int i = 4 * n4 + blockIdx.x * kScanThreads + t; i < N; i += gridDim.x * kScanThreads)
-        element(i, mask[i], W[i], PAIR ? grad[i] : 0.0f);
+    each_of_tail(N, n4, blockIdx.x * kScanThreads + t, gridDim.x * kScanThreads,
+                 [&](unsigned int i) { element(i, mask[i], W[i], PAIR ? grad[i] : 0.0f); });
     flush();
 }
 
