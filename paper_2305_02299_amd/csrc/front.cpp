@@ -163,7 +163,7 @@ const void* blocked_copy(PyObject* owner, PyObject* W_obj, PyObject* idx_obj, co
 }
 
 // linear_fwd(x, B, d_in, W_c, idx, active, n_active, K, bias, d_out, y, seg, packed, act[, owner]) -> y
-// B < 0: the rows of x, which must be [rows, d_in]; y None: allocated; idx in a 16-bit container: the narrow-index call.
+// B None: the rows of x, which must be [rows, d_in]; y None (with B None only): allocated; idx in a 16-bit container: the narrow-index call.
 // owner: an object whose attribute _blocked may hold the blocked copy of these rows; with it the library may take the matrix cores.
 PyObject* linear_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded([&](PyObject*& out) {
@@ -172,9 +172,9 @@ PyObject* linear_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const at::Tensor* W_c = tensor(a[3]);
         const at::Tensor* idx = tensor(a[4]);
         if (!x || !W_c || !idx) fail(PyExc_TypeError, "x, W_c and idx are tensors");
-        int32_t B = int32(a[1]);
         const int32_t d_in = int32(a[2]), n_active = int32(a[6]), K = int32(a[7]), d_out = int32(a[9]);
-        if (B < 0) B = rows_of(*x, d_in);
+        const int32_t B = a[1] == Py_None ? rows_of(*x, d_in) : int32(a[1]);
+        if (a[1] != Py_None && a[10] == Py_None) fail(PyExc_TypeError, "y is a tensor");
         const int32_t* active = pointer<int32_t>(a[5]);
         const float* bias = pointer<float>(a[8]);
         const uint16_t* seg = pointer<uint16_t>(a[11]);

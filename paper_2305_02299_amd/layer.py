@@ -7,7 +7,7 @@ import torch
 
 from . import binding as B_
 from . import _front
-from ._front import linear_fwd as _linear_fwd   # (x, batch or -1, d_in, W_c, idx, ..., packed, activation, owner) -> y
+from ._front import linear_fwd as _linear_fwd   # (x, batch or None, d_in, W_c, idx, ..., packed, activation, owner) -> y
 
 
 @dataclass
@@ -53,7 +53,7 @@ class CondensedLinear:
                 representation: str = "condensed") -> torch.Tensor:
         """representation: "condensed", "structured", or "auto" (the library's estimate for this batch size)."""
         if algo is None and tuning is None and representation == "condensed":
-            return _linear_fwd(x, -1, self.d_in, self.W_c, self.idx, self.active, self.n_active, self.K, self.bias, self.d_out, y, self.seg,
+            return _linear_fwd(x, None, self.d_in, self.W_c, self.idx, self.active, self.n_active, self.K, self.bias, self.d_out, y, self.seg,
                                self.packed, 0, self)
         if representation == "auto":
             representation = "structured" if _front.choose(x, self.d_in, self.n_active, self.K, self.d_out, self.W_c) else "condensed"
@@ -66,7 +66,7 @@ class CondensedLinear:
         assert representation == "condensed"
         packed = self.packed if self.idx.dtype == torch.int32 else None
         if algo is None and tuning is None:
-            return _linear_fwd(x, -1, self.d_in, self.W_c, self.idx, self.active, self.n_active, self.K, self.bias, self.d_out, y, self.seg,
+            return _linear_fwd(x, None, self.d_in, self.W_c, self.idx, self.active, self.n_active, self.K, self.bias, self.d_out, y, self.seg,
                                packed, 0, self)
         assert x.dim() == 2 and x.shape[1] == self.d_in
         if y is None:
@@ -105,8 +105,8 @@ class CondensedMLP:
             B_.srigl_condensed_mlp_fwd(x, Bn, f.d_in, f.packed, f.active, f.n_active, f.K, f.bias, f.d_out, self.act, hidden, s.packed,
                                        s.active, s.n_active, s.K, s.bias, s.d_out, y)
             return y
-        hidden = _linear_fwd(x, -1, f.d_in, f.W_c, f.idx, f.active, f.n_active, f.K, f.bias, f.d_out, hidden, f.seg, f.packed, self.act)
-        return _linear_fwd(hidden, -1, s.d_in, s.W_c, s.idx, s.active, s.n_active, s.K, s.bias, s.d_out, y, s.seg, s.packed, B_.ACT_NONE)
+        hidden = _linear_fwd(x, None, f.d_in, f.W_c, f.idx, f.active, f.n_active, f.K, f.bias, f.d_out, hidden, f.seg, f.packed, self.act)
+        return _linear_fwd(hidden, None, s.d_in, s.W_c, s.idx, s.active, s.n_active, s.K, s.bias, s.d_out, y, s.seg, s.packed, B_.ACT_NONE)
 
 
 def fold_mlp(layer1: CondensedLinear, layer2: CondensedLinear, act: int) -> CondensedMLP:
