@@ -163,7 +163,7 @@ const void* blocked_copy(PyObject* owner, PyObject* W_obj, PyObject* idx_obj, co
 }
 
 // linear_fwd(x, B, d_in, W_c, idx, active, n_active, K, bias, d_out, y, seg, packed, act[, owner]) -> y
-// B None: the rows of x, which must be [rows, d_in]; y None (with B None only): allocated; idx in a 16-bit container: the narrow-index call.
+// B None: the rows of x, which must be [rows, d_in]; y None: allocated; idx in a 16-bit container: the narrow-index call.
 // owner: an object whose attribute _blocked may hold the blocked copy of these rows; with it the library may take the matrix cores.
 PyObject* linear_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded([&](PyObject*& out) {
@@ -174,7 +174,7 @@ PyObject* linear_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         if (!x || !W_c || !idx) fail(PyExc_TypeError, "x, W_c and idx are tensors");
         const int32_t d_in = int32(a[2]), n_active = int32(a[6]), K = int32(a[7]), d_out = int32(a[9]);
         const int32_t B = a[1] == Py_None ? rows_of(*x, d_in) : int32(a[1]);
-        if (a[1] != Py_None && a[10] == Py_None) fail(PyExc_TypeError, "y is a tensor");
+        if (B < 0 && a[10] == Py_None) fail(PyExc_ValueError, "a negative batch");
         const int32_t* active = pointer<int32_t>(a[5]);
         const float* bias = pointer<float>(a[8]);
         const uint16_t* seg = pointer<uint16_t>(a[11]);

@@ -96,8 +96,8 @@ class CondensedMLP:
     def forward(self, x: torch.Tensor, y: torch.Tensor | None = None, hidden: torch.Tensor | None = None,
                 fused: bool | None = None) -> torch.Tensor:
         f, s = self.first, self.second
+        Bn = x.shape[0]   # (hidden and y may be buffers of a larger batch)
         if fused:      # both layers in one launch (batches up to 8; measured slower than two launches on MI355X: not the default)
-            Bn = x.shape[0]
             if hidden is None:
                 hidden = torch.empty((Bn, f.d_out), dtype=torch.float32, device=x.device)
             if y is None:
@@ -105,8 +105,8 @@ class CondensedMLP:
             B_.srigl_condensed_mlp_fwd(x, Bn, f.d_in, f.packed, f.active, f.n_active, f.K, f.bias, f.d_out, self.act, hidden, s.packed,
                                        s.active, s.n_active, s.K, s.bias, s.d_out, y)
             return y
-        hidden = _linear_fwd(x, None, f.d_in, f.W_c, f.idx, f.active, f.n_active, f.K, f.bias, f.d_out, hidden, f.seg, f.packed, self.act)
-        return _linear_fwd(hidden, None, s.d_in, s.W_c, s.idx, s.active, s.n_active, s.K, s.bias, s.d_out, y, s.seg, s.packed, B_.ACT_NONE)
+        hidden = _linear_fwd(x, Bn, f.d_in, f.W_c, f.idx, f.active, f.n_active, f.K, f.bias, f.d_out, hidden, f.seg, f.packed, self.act)
+        return _linear_fwd(hidden, Bn, s.d_in, s.W_c, s.idx, s.active, s.n_active, s.K, s.bias, s.d_out, y, s.seg, s.packed, B_.ACT_NONE)
 
 
 def fold_mlp(layer1: CondensedLinear, layer2: CondensedLinear, act: int) -> CondensedMLP:

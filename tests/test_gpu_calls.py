@@ -22,3 +22,22 @@ def test_negative_sizes_are_refused(bits, packed):
             B_.srigl_condensed_linear_fwd(x, B, d_in, W, ix, None, n, K, None, d_out, y, packed=torch.zeros(1024, dtype=torch.uint8, device="cuda") if packed and bits == 32 else None)
         assert e.value.status == B_.ERR_INVALID_ARG
     assert (y == 7.0).all()
+
+
+@pytest.mark.parametrize("given", ["hidden", "both", "none"])
+def test_block_runs_the_rows_of_its_input(given):
+    """Both layers of a block run on as many rows as x has: buffers of a larger batch are filled as far as x goes, and x may have any shape of that many rows."""
+    from paper_2305_02299_amd import condense_layer, fold_mlp
+    L1, L2 = si.make_layer(96, 200, 10, 8, ablate_frac=0.3, seed=1), si.make_layer(200, 96, 20, 8, seed=2)
+    block = fold_mlp(condense_layer(dev(L1.W), dev(L1.mask), 10, dev(L1.bias)), condense_layer(dev(L2.W), dev(L2.mask), 20, dev(L2.bias)), B_.ACT_GELU)
+    x = dev(L1.x)
+    want = block.forward(x)
+    hidden = torch.full((8, block.first.d_out), 5.0, device="cuda") if given != "none" else None
+    room = torch.full((8, 96), 7.0, device="cuda")
+    y = block.forward(x[:3].reshape(3, 1, 96), room if given == "both" else None, hidden)
+    if given == "both":
+        assert y is room and (room[3:] == 7.0).all()
+    else:
+        assert y.shape == (3, 96)
+    np.testing.assert_allclose(y[:3].cpu(), want[:3].cpu(), rtol=0, atol=1e-5)
+    assert hidden is None or (hidden[3:] == 5.0).all()
