@@ -54,8 +54,12 @@ size_t bytes_of(PyObject* o) {
     const at::Tensor* t = tensor(o);
     return t ? (size_t)t->numel() * t->element_size() : 0;
 }
+// What int() accepts (a float of a schedule, a numpy number, a tensor of one element), as in the ctypes calls.
 long long integer(PyObject* o) {
-    const long long v = PyLong_AsLongLong(o);
+    PyObject* made = PyLong_Check(o) ? nullptr : PyNumber_Long(o);
+    if (!made && !PyLong_Check(o)) throw Failed{};
+    const long long v = PyLong_AsLongLong(made ? made : o);
+    Py_XDECREF(made);
     if (v == -1 && PyErr_Occurred()) throw Failed{};
     return v;
 }

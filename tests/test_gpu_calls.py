@@ -41,3 +41,26 @@ def test_block_runs_the_rows_of_its_input(given):
         assert y.shape == (3, 96)
     np.testing.assert_allclose(y[:3].cpu(), want[:3].cpu(), rtol=0, atol=1e-5)
     assert hidden is None or (hidden[3:] == 5.0).all()
+
+
+def test_sizes_in_any_form_that_int_takes():
+    L = si.make_layer(64, 12, 5, 3, seed=45)
+    W_c, idx, _ = oracle_condensed(L)
+    x, W, ix = dev(L.x), dev(W_c), dev(idx)
+    want, y = torch.empty((3, 12), device="cuda"), torch.empty((3, 12), device="cuda")
+    B_.srigl_condensed_linear_fwd(x, 3, 64, W, ix, None, 12, 5, None, 12, want)
+    for form in (float, np.int64, np.float32, torch.tensor):
+        B_.srigl_condensed_linear_fwd(x, form(3), form(64), W, ix, None, form(12), form(5), None, form(12), y.fill_(0))
+        assert torch.equal(y, want)
+    for wrong in (None, "many", [3]):
+        with pytest.raises((TypeError, ValueError)):
+            B_.srigl_condensed_linear_fwd(x, 3, 64, W, ix, None, 12, wrong, None, 12, y)
+    Wm, mask, g = dev(np.where(L.mask != 0, L.W, 0).astype(np.float32)), dev(L.mask), dev(L.W)
+    ws = torch.empty(B_.srigl_mask_update_workspace_bytes(12, 64), dtype=torch.uint8, device="cuda")
+    outs = []
+    for form in (int, float, np.int32):
+        mo, Wo, rep = torch.empty_like(mask), torch.empty_like(Wm), torch.empty(4, dtype=torch.int64, device="cuda")
+        B_.srigl_mask_update(Wm, mask, g, form(12), form(64), form(5), form(0.3 * 60), form(30), form(60), mo, Wo, ws, rep)
+        outs.append((mo, Wo, rep))
+    for other in outs[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(outs[0], other))
