@@ -315,6 +315,7 @@ srigl_status srigl_condensed_linear_fwd_idx16(const void* x, srigl_dtype x_dtype
  * srigl_blocked_tile: the tile the library would take for B rows of x, or 0 where srigl_condensed_linear_fwd is expected to be
  * faster or the sizes are not supported: a srigl_blocked_tile_t, or first | second << 4 | columns << 8 for stored rows split in two launches,
  * `columns` tile columns in the first shape and the rest in the second.  Host arithmetic on sizes.
+ * srigl_blocked_tile_with_copy: the same for a call that makes the copy first (srigl_block_terms, then srigl_blocked_linear_fwd).
  * srigl_blocked_linear_fwd: the forward call; x[B][d_in] bf16, the copy and the W_c / idx it was made from (read again for sums that are
  * not finite), everything else as in srigl_condensed_linear_fwd_act.  tile 0: the tile of smallest expected time.
  * srigl_fwd_plan_query describes the calls that read W_c / idx (or the streaming copy), not this one.  Device pointers,
@@ -328,6 +329,8 @@ srigl_status srigl_block_terms(const void* W_c, const void* idx, int32_t idx_bit
                                int32_t d_in, void* blocked, size_t blocked_bytes, void* stream);
 
 int32_t srigl_blocked_tile(int32_t B, int32_t d_in, int32_t n_active, int32_t K, int32_t d_out);
+
+int32_t srigl_blocked_tile_with_copy(int32_t B, int32_t d_in, int32_t n_active, int32_t K, int32_t d_out);
 
 srigl_status srigl_blocked_linear_fwd(const void* x, int32_t B, int32_t d_in, const void* blocked, const void* W_c, const void* idx,
                                       int32_t idx_bits, const int32_t* active, int32_t n_active, int32_t K, const float* bias,

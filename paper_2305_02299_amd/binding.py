@@ -34,7 +34,7 @@ EXPORTS = (
     "srigl_structured_linear_fwd_tile", "srigl_structured_split_plan", "srigl_structured_linear_fwd_split", "srigl_choose_representation",
     "srigl_condensed_linear_fwd_act", "srigl_fold_ablated_inputs", "srigl_mask_update_workspace_bytes", "srigl_mask_update",
     "srigl_compact_hidden_layer", "srigl_condensed_mlp_fwd", "srigl_narrow_idx", "srigl_condensed_linear_fwd_idx16", "srigl_csr_linear_fwd", "srigl_fwd_plan_query", "srigl_fwd_plan_query_algo",
-    "srigl_blocked_bytes", "srigl_block_terms", "srigl_blocked_tile", "srigl_blocked_linear_fwd",
+    "srigl_blocked_bytes", "srigl_block_terms", "srigl_blocked_tile", "srigl_blocked_tile_with_copy", "srigl_blocked_linear_fwd",
 )
 
 
@@ -128,6 +128,8 @@ def _load() -> ctypes.CDLL:
     lib.srigl_block_terms.argtypes = [vp, vp, i32, vp, i32, i32, i32, vp, sz, vp]
     lib.srigl_blocked_tile.restype = i32
     lib.srigl_blocked_tile.argtypes = [i32, i32, i32, i32, i32]
+    lib.srigl_blocked_tile_with_copy.restype = i32
+    lib.srigl_blocked_tile_with_copy.argtypes = [i32, i32, i32, i32, i32]
     lib.srigl_blocked_linear_fwd.restype = ctypes.c_int
     lib.srigl_blocked_linear_fwd.argtypes = [vp, i32, i32, vp, vp, vp, i32, vp, i32, i32, vp, i32, vp, ctypes.c_int, i32, vp]
     lib.srigl_launch_empty.restype = ctypes.c_int
@@ -304,6 +306,11 @@ def srigl_block_terms(W_c, idx, seg, n_rows, K, d_in, blocked):
 def srigl_blocked_tile(B: int, d_in: int, n_active: int, K: int, d_out: int) -> int:
     """Code of the tile the library would take (BLOCKED_*, or two of them and where the rows are split: see srigl.h), 0 where it would not take the matrix-core form."""
     return int(lib.srigl_blocked_tile(int(B), int(d_in), int(n_active), int(K), int(d_out)))
+
+
+def srigl_blocked_tile_with_copy(B: int, d_in: int, n_active: int, K: int, d_out: int) -> int:
+    """The same for a call that first makes the copy."""
+    return int(lib.srigl_blocked_tile_with_copy(int(B), int(d_in), int(n_active), int(K), int(d_out)))
 
 
 def srigl_blocked_linear_fwd(x, B, d_in, blocked, W_c, idx, active, n_active, K, bias, d_out, y, act=None, tile=0):

@@ -129,46 +129,23 @@ PyObject* set_error(PyObject*, PyObject* type) {
     Py_RETURN_NONE;
 }
 
-PyObject* g_blocked = nullptr;   // "_blocked"
-
-int64_t version_of(const at::Tensor& t) { return t.is_inference() ? 0 : (int64_t)t._version(); }
-
-// The blocked copy of owner's rows (read by the matrix-core form of the forward call): made on first use and kept in
-// owner._blocked as (copy, W_c, its version, idx, its version), so that other tensors, or the same ones written in place,
-// get a new one.  Null while the stream is being captured and there is none yet (the caller takes the form that needs none: a copy
-// made inside a graph would be valid after a replay only).  The making is waited for, once: any stream may use the copy.
-const void* blocked_copy(PyObject* owner, PyObject* W_obj, PyObject* idx_obj, const at::Tensor& W_c, const at::Tensor& idx, const uint16_t* seg,
-                         int32_t n_active, int32_t K, int32_t d_in) {
-    PyObject* held = PyObject_GetAttr(owner, g_blocked);
-    if (!held) throw Failed{};
-    const void* found = nullptr;
-    if (PyTuple_Check(held) && PyTuple_GET_SIZE(held) == 5 && PyTuple_GET_ITEM(held, 1) == W_obj && PyTuple_GET_ITEM(held, 3) == idx_obj &&
-        PyLong_AsLongLong(PyTuple_GET_ITEM(held, 2)) == version_of(W_c) && PyLong_AsLongLong(PyTuple_GET_ITEM(held, 4)) == version_of(idx))
-        found = THPVariable_Unpack(PyTuple_GET_ITEM(held, 0)).data_ptr();
-    Py_DECREF(held);
-    if (found) return found;
-    const c10::hip::HIPStream st = c10::hip::getCurrentHIPStream();
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st.stream(), &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) return nullptr;
-    const size_t bytes = srigl_blocked_bytes(n_active, K, d_in);
-    at::Tensor copy = fresh({(int64_t)bytes}, at::kByte, W_c);
-    const void* made = copy.data_ptr();
-    check(srigl_block_terms(W_c.data_ptr(), idx.data_ptr(), 8 * (int)idx.element_size(), seg, n_active, K, d_in, copy.data_ptr(), bytes, st.stream()),
-          "srigl_block_terms");
-    Py_BEGIN_ALLOW_THREADS
-    st.synchronize();
-    Py_END_ALLOW_THREADS
-    PyObject* keep = Py_BuildValue("(NOLOL)", THPVariable_Wrap(std::move(copy)), W_obj, (long long)version_of(W_c), idx_obj, (long long)version_of(idx));
-    if (!keep) throw Failed{};
-    const int rc = PyObject_SetAttr(owner, g_blocked, keep);
-    Py_DECREF(keep);
-    if (rc != 0) throw Failed{};
-    return made;
+// Device memory for the blocked copy of a call's terms, or an undefined tensor where there is none to be had (the call then takes the
+// form that needs none) or where the current stream is another device's.  Given back to the allocator when the call returns, in the
+// order of the current stream, on which the call has put its work.
+at::Tensor scratch(size_t bytes, const at::Tensor& like) {
+    if (like.device().index() != c10::hip::getCurrentHIPStream().device_index()) return at::Tensor();
+    try {
+        return fresh({(int64_t)bytes}, at::kByte, like);
+    } catch (const c10::OutOfMemoryError&) {
+        return at::Tensor();
+    }
 }
 
-// linear_fwd(x, B, d_in, W_c, idx, active, n_active, K, bias, d_out, y, seg, packed, act[, owner]) -> y
+// linear_fwd(x, B, d_in, W_c, idx, active, n_active, K, bias, d_out, y, seg, packed, act[, blocked]) -> y
 // B None: the rows of x, which must be [rows, d_in]; y None: allocated; idx in a 16-bit container: the narrow-index call.
-// owner: an object whose attribute _blocked may hold the blocked copy of these rows; with it the library may take the matrix cores.
+// blocked: the call may take the matrix cores, from this copy of the terms, or with None from one that it makes for itself, in the same
+// stream and from what the arrays hold then.  Nothing is kept: 4096 -> 16384 (13108 rows stored, K = 205) at batch 2048 pays 15 us of
+// 240 for it, and weights that changed since, in whatever way, are the weights that count.
 PyObject* linear_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded([&](PyObject*& out) {
         if (n != 15) need(n, 14);
@@ -190,13 +167,23 @@ PyObject* linear_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const bool narrow = idx->scalar_type() != at::kInt;   // (16-bit indices are read without the streaming copy)
         void* st = stream();
         srigl_status rc;
-        if (n == 15 && xt == SRIGL_BF16 && wt == SRIGL_BF16 && seg && srigl_blocked_tile(B, d_in, n_active, K, d_out) != 0) {
-            if (const void* blocked = blocked_copy(a[14], a[3], a[4], *W_c, *idx, seg, n_active, K, d_in)) {
-                Py_BEGIN_ALLOW_THREADS
-                rc = srigl_blocked_linear_fwd(xp, B, d_in, blocked, wp, ip, narrow ? 16 : 32, active, n_active, K, bias, d_out, y, act, 0, st);
-                Py_END_ALLOW_THREADS
-                check(rc, "srigl_blocked_linear_fwd");
-                return;
+        if (n == 15 && xt == SRIGL_BF16 && wt == SRIGL_BF16 && seg) {
+            const at::Tensor* copy = tensor(a[14]);
+            if ((copy ? srigl_blocked_tile : srigl_blocked_tile_with_copy)(B, d_in, n_active, K, d_out) != 0) {
+                const size_t bytes = srigl_blocked_bytes(n_active, K, d_in);
+                if (copy && bytes_of(a[14]) < bytes) fail(PyExc_ValueError, "a blocked copy of other rows");
+                const at::Tensor made = copy ? at::Tensor() : scratch(bytes, *W_c);
+                void* blocked = copy ? copy->data_ptr() : made.defined() ? made.data_ptr() : nullptr;
+                if (blocked) {
+                    rc = SRIGL_OK;
+                    Py_BEGIN_ALLOW_THREADS
+                    if (!copy) rc = srigl_block_terms(wp, ip, narrow ? 16 : 32, seg, n_active, K, d_in, blocked, bytes, st);
+                    if (rc == SRIGL_OK)
+                        rc = srigl_blocked_linear_fwd(xp, B, d_in, blocked, wp, ip, narrow ? 16 : 32, active, n_active, K, bias, d_out, y, act, 0, st);
+                    Py_END_ALLOW_THREADS
+                    check(rc, "srigl_blocked_linear_fwd");
+                    return;
+                }
             }
         }
         Py_BEGIN_ALLOW_THREADS
@@ -363,8 +350,4 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_front", "calls into libsrigl", -1
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__front() {
-    g_blocked = PyUnicode_InternFromString("_blocked");
-    if (!g_blocked) return nullptr;
-    return PyModule_Create(&module);
-}
+PyMODINIT_FUNC PyInit__front() { return PyModule_Create(&module); }

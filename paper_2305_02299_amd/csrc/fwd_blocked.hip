@@ -468,8 +468,11 @@ static int choose_blocked_tile(int B, int d_in, int n_active, double* us) {
 }
 
 // Taken where its estimate is this far ahead of the gathering kernels' (both estimates are good to about 10 %; no measured
-// point was then slower, and the copy has to be built once per layer)
+// point was then slower)
 constexpr double kBlockedMargin = 0.85;
+
+// What making the copy adds to a call (us)
+static double block_terms_us(int n, int K) { return 6.0 + 2.5e-6 * n * (double)K; }
 
 static bool blocked_fits(int n_active, int K, int d_in) {
     if (n_active <= 0 || K <= 0 || d_in < 8 || d_in > 65536) return false;
@@ -488,15 +491,22 @@ size_t srigl_blocked_bytes(int32_t n_rows, int32_t K, int32_t d_in) {
     return blocked_layout(n_rows, K, d_in).bytes;
 }
 
-int32_t srigl_blocked_tile(int32_t B, int32_t d_in, int32_t n_active, int32_t K, int32_t d_out) {
+static int32_t blocked_tile(int32_t B, int32_t d_in, int32_t n_active, int32_t K, int32_t d_out, bool with_copy) {
     if (B <= 0 || n_active > d_out || K > d_in || !blocked_fits(n_active, K, d_in)) return 0;
-    struct Key { int32_t B, d_in, n_active, K, d_out; };
+    struct Key { int32_t B, d_in, n_active, K, d_out, with_copy; };
     static thread_local DecisionCache<Key, int, 64> cache;
-    return cache.get(Key{B, d_in, n_active, K, d_out}, [&] {
+    return cache.get(Key{B, d_in, n_active, K, d_out, with_copy}, [&] {
         double us;
         const int tile = choose_blocked_tile(B, d_in, n_active, &us);
+        if (with_copy) us += block_terms_us(n_active, K);
         return us < kBlockedMargin * condensed_estimate_us(B, d_in, n_active, K, d_out, true, n_active < d_out) ? tile : 0;
     });
+}
+int32_t srigl_blocked_tile(int32_t B, int32_t d_in, int32_t n_active, int32_t K, int32_t d_out) {
+    return blocked_tile(B, d_in, n_active, K, d_out, false);
+}
+int32_t srigl_blocked_tile_with_copy(int32_t B, int32_t d_in, int32_t n_active, int32_t K, int32_t d_out) {
+    return blocked_tile(B, d_in, n_active, K, d_out, true);
 }
 
 srigl_status srigl_block_terms(const void* W_c, const void* idx, int32_t idx_bits, const uint16_t* seg, int32_t n_rows, int32_t K,

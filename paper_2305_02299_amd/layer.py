@@ -1,13 +1,13 @@
 """Device-buffer holder around the three library calls (no arithmetic here)."""
 from __future__ import annotations
 
-from dataclasses import dataclass, field
+from dataclasses import dataclass
 
 import torch
 
 from . import binding as B_
 from . import _front
-from ._front import linear_fwd as _linear_fwd   # (x, batch or None, d_in, W_c, idx, ..., packed, activation, owner) -> y
+from ._front import linear_fwd as _linear_fwd   # (x, batch or None, d_in, W_c, idx, ..., packed, activation, blocked) -> y
 
 
 @dataclass
@@ -28,8 +28,7 @@ class CondensedLinear:
     idx_wide: torch.Tensor | None = None   # the int32 indices when idx holds the 16-bit copy
     packed: torch.Tensor | None = None     # the streaming copy of W_c / idx (bytes), read by the kernels that can stream it
     split_ws: torch.Tensor | None = None   # partial sums of the structured-only product when it cuts d_in into parts (grown on demand)
-    # what the forward call keeps of the blocked copy of W_c / idx that the matrix-core form reads (bf16 storage; made on first use)
-    _blocked: tuple | None = field(default=None, repr=False, compare=False)
+    blocked: torch.Tensor | None = None    # the blocked copy of W_c / idx (bytes) that prepare() makes, read by the matrix-core form (bf16 storage)
 
     def narrow(self) -> "CondensedLinear":
         """The same layer with 16-bit column indices (d_in <= 65536); weights, active, bias and seg are shared."""
@@ -38,7 +37,19 @@ class CondensedLinear:
         idx16 = torch.empty(self.idx.shape, dtype=torch.int16, device=self.idx.device)
         B_.srigl_narrow_idx(self.idx, self.d_in, idx16)
         return CondensedLinear(self.d_in, self.d_out, self.K, self.n_active, self.W_c, idx16, self.active, self.bias, self.seg,
-                               self.Wd, self.idx)
+                               self.Wd, self.idx, blocked=self.blocked)
+
+    def prepare(self) -> "CondensedLinear":
+        """For programs that run many large batches on bf16 weights that stay as they are: makes the blocked copy of W_c / idx once
+        (4 bytes per stored weight and some), in the order of the current stream, where forward would make one of its own in each call
+        that is better off with it.  After W_c or idx was written it has to be called again; the copy stays at its address, so that
+        captured calls follow.  Nothing to do for fp32 weights, or without seg."""
+        if self.seg is not None and B_._dtype_code(self.W_c) == B_.BF16 and 8 <= self.d_in <= 65536 and self.n_active and self.K:
+            if self.blocked is None:
+                need = B_.srigl_blocked_bytes(self.n_active, self.K, self.d_in)
+                self.blocked = torch.empty((need,), dtype=torch.uint8, device=self.W_c.device)
+            B_.srigl_block_terms(self.W_c, self.idx, self.seg, self.n_active, self.K, self.d_in, self.blocked)
+        return self
 
     def dense_rows(self) -> torch.Tensor:
         if self.Wd is None:
@@ -51,10 +62,12 @@ class CondensedLinear:
 
     def forward(self, x: torch.Tensor, y: torch.Tensor | None = None, algo=None, tuning=None,
                 representation: str = "condensed") -> torch.Tensor:
-        """representation: "condensed", "structured", or "auto" (the library's estimate for this batch size)."""
+        """representation: "condensed", "structured", or "auto" (the library's estimate for this batch size).  The condensed form reads
+        W_c / idx / seg as they are when the call runs on the stream (and `packed`, the blocked copy of prepare(), and for "structured" the dense rows,
+        which are copies that whoever writes the arrays renews).  Results and scratch come from torch's allocator."""
         if algo is None and tuning is None and representation == "condensed":
             return _linear_fwd(x, None, self.d_in, self.W_c, self.idx, self.active, self.n_active, self.K, self.bias, self.d_out, y, self.seg,
-                               self.packed, 0, self)
+                               self.packed, 0, self.blocked)
         if representation == "auto":
             representation = "structured" if _front.choose(x, self.d_in, self.n_active, self.K, self.d_out, self.W_c) else "condensed"
         if representation == "structured":
@@ -67,7 +80,7 @@ class CondensedLinear:
         packed = self.packed if self.idx.dtype == torch.int32 else None
         if algo is None and tuning is None:
             return _linear_fwd(x, None, self.d_in, self.W_c, self.idx, self.active, self.n_active, self.K, self.bias, self.d_out, y, self.seg,
-                               packed, 0, self)
+                               packed, 0, self.blocked)
         assert x.dim() == 2 and x.shape[1] == self.d_in
         if y is None:
             y = torch.empty((x.shape[0], self.d_out), dtype=torch.float32, device=x.device)

@@ -64,35 +64,113 @@ def test_non_finite_activations_reach_only_the_neurons_that_name_them(tile, d_in
     gate(np.where(clean, yh, 0), np.where(clean, y_ref[:, active], 0), S[:, active], TOL_BF16)
 
 
-def test_layer_object_keeps_the_copy_and_renews_it():
-    """The layer's own call takes the matrix cores where the library expects them faster, in eager calls and in captured ones, and
-    follows weights that are written in place."""
-    d_in, d_out, K, B = 512, 2048, 100, 1024
-    assert B_.srigl_blocked_tile(B, d_in, d_out, K, d_out) != 0 and B_.srigl_blocked_tile(1, d_in, d_out, K, d_out) == 0
-    L = si.make_layer(d_in, d_out, K, B, dtype="bf16", seed=9)
+D_IN, D_OUT, K_, B_ROWS = 512, 2048, 100, 1024   # the layer's own call takes the matrix cores here
+
+
+def bf16_layer(seed):
+    """A synthetic layer, its arrays as the layer object takes them, and the oracle's result and scale."""
+    L = si.make_layer(D_IN, D_OUT, K_, B_ROWS, dtype="bf16", seed=seed)
     W_c, idx, active = oracle_condensed(L)
-    y_ref, S = oracle.fwd(L.x_bf16, W_c, idx, active, L.bias, d_out, want_scale=True)
-    layer = condense_layer(dev(L.W_bf16).view(torch.bfloat16), dev(L.mask), K, dev(L.bias))
+    return L, dev(L.W_bf16).view(torch.bfloat16), dev(L.mask), *oracle.fwd(L.x_bf16, W_c, idx, active, L.bias, D_OUT, want_scale=True)
+
+
+def test_layer_call_takes_the_matrix_cores_and_reads_what_the_arrays_hold():
+    """Every way of changing a layer in place shows in the next call: writes through torch, condensing again into the same buffers (raw
+    pointers, no version counter), inference tensors (which have none)."""
+    assert B_.srigl_blocked_tile_with_copy(B_ROWS, D_IN, D_OUT, K_, D_OUT) != 0 and B_.srigl_blocked_tile_with_copy(1, D_IN, D_OUT, K_, D_OUT) == 0
+    L, W, mask, y_ref, S = bf16_layer(9)
+    layer = condense_layer(W, mask, K_, dev(L.bias))
     x = dev(L.x_bf16).view(torch.bfloat16)
-    y = torch.empty((B, d_out), device="cuda")
-    layer.forward(x[:1])
-    graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph):      # no copy yet: the captured call takes a form that needs none
-        layer.forward(x, y)
-    assert layer._blocked is None
-    gate(host(layer.forward(x)), y_ref, S, TOL_BF16)
-    kept = layer._blocked
-    assert kept is not None
-    with torch.cuda.graph(graph2 := torch.cuda.CUDAGraph()):
-        layer.forward(x, y)
-    for g in (graph, graph2, graph, graph2):
-        y.fill_(float("nan"))
-        g.replay()
-        gate(host(y), y_ref, S, TOL_BF16)
-        assert layer._blocked is kept and torch.isfinite(layer.narrow().forward(x)).all()
+    first = layer.forward(x)
+    gate(host(first), y_ref, S, 2e-6)
+    assert torch.equal(layer.forward(x), first) and torch.equal(layer.narrow().forward(x), first)
+    forced = torch.empty_like(first)     # the same form with a copy made by hand
+    B_.srigl_blocked_linear_fwd(x, B_ROWS, D_IN, blocked(layer.W_c, layer.idx, layer.seg, D_IN), layer.W_c, layer.idx, None, D_OUT, K_, layer.bias, D_OUT, forced)
+    assert torch.equal(forced, first)
     layer.W_c.mul_(2)
-    gate(host(layer.forward(x)), (y_ref - L.bias) * 2 + L.bias, 2 * S, TOL_BF16)
-    assert layer._blocked is not kept
+    gate(host(layer.forward(x)), (y_ref - L.bias) * 2 + L.bias, 2 * S, 2e-6)
+    L2, W2, mask2, y2_ref, S2 = bf16_layer(10)
+    y2_ref, S2 = oracle.fwd(L.x_bf16, *oracle_condensed(L2), L.bias, D_OUT, want_scale=True)
+    B_.srigl_condense(W2, mask2, D_OUT, D_IN, K_, D_OUT, layer.W_c, layer.idx, torch.empty(D_OUT, dtype=torch.int32, device="cuda"), layer.seg,
+                      B_.new_workspace(D_OUT), B_.new_report(), packed=layer.packed)
+    gate(host(layer.forward(x)), y2_ref, S2, 2e-6)
+    with torch.inference_mode():
+        inferred = condense_layer(W.clone(), mask, K_, dev(L.bias))
+        assert inferred.W_c.is_inference()
+        gate(host(inferred.forward(x)), y_ref, S, 2e-6)
+        inferred.W_c.mul_(2)
+        gate(host(inferred.forward(x)), (y_ref - L.bias) * 2 + L.bias, 2 * S, 2e-6)
+
+
+@pytest.mark.parametrize("prepared", [False, True])
+def test_captured_layer_calls(prepared):
+    """A call captured before any other runs the same kernels as the eager one; replays follow weights that are written in place, with eager calls
+    and other allocations between them."""
+    L, W, mask, y_ref, S = bf16_layer(9)
+    layer = condense_layer(W, mask, K_, dev(L.bias))
+    if prepared:
+        at = layer.prepare().blocked.data_ptr()
+    x = dev(L.x_bf16).view(torch.bfloat16)
+    y = torch.empty((B_ROWS, D_OUT), device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        layer.forward(x, y)
+    eager = layer.forward(x)
+    gate(host(eager), y_ref, S, 2e-6)
+    for turn in range(6):
+        if turn == 3:
+            layer.W_c.mul_(2)
+            y_ref, S = (y_ref - L.bias) * 2 + L.bias, 2 * S
+            if prepared:
+                assert layer.prepare().blocked.data_ptr() == at
+        y.fill_(float("nan"))
+        junk = [torch.full((4 << 20,), -1, dtype=torch.int32, device="cuda") for _ in range(3)]
+        graph.replay()
+        torch.cuda.synchronize()
+        del junk
+        gate(host(y), y_ref, S, 2e-6)
+        assert torch.equal(layer.forward(x), y)
+        torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("prepared", [False, True])
+def test_first_calls_from_several_threads_and_streams(prepared):
+    import threading
+    L, W, mask, y_ref, S = bf16_layer(9)
+    layer = condense_layer(W, mask, K_, dev(L.bias))
+    if prepared:
+        layer.prepare()
+    x = dev(L.x_bf16).view(torch.bfloat16)
+    torch.cuda.synchronize()
+    results, start = [None] * 4, threading.Barrier(4)
+
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            start.wait()
+            results[i] = [layer.forward(x) for _ in range(8)]
+            torch.cuda.current_stream().synchronize()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    gate(host(results[0][0]), y_ref, S, 2e-6)
+    assert all(torch.equal(y, results[0][0]) for r in results for y in r)
+
+
+def test_prepare_is_what_the_call_reads_and_other_layers_need_none():
+    L, W, mask, y_ref, S = bf16_layer(9)
+    layer = condense_layer(W, mask, K_, dev(L.bias))
+    x = dev(L.x_bf16).view(torch.bfloat16)
+    want = layer.forward(x)
+    assert torch.equal(layer.prepare().forward(x), want) and layer.narrow().blocked is layer.blocked
+    assert layer.blocked.numel() == B_.srigl_blocked_bytes(D_OUT, K_, D_IN)
+    layer.blocked = layer.blocked[:-16].clone()
+    with pytest.raises(ValueError):
+        layer.forward(x)
+    plain = condense_layer(dev(L.W), mask, K_)      # fp32
+    assert plain.prepare().blocked is None and condense_layer(W, mask, K_, want_seg=False).prepare().blocked is None
 
 
 @pytest.mark.parametrize("first,second,columns", [(B_.BLOCKED_256, B_.BLOCKED_192, 2), (B_.BLOCKED_192, B_.BLOCKED_64, 3), (B_.BLOCKED_64, B_.BLOCKED_256, 1),
