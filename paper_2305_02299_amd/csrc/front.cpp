@@ -144,8 +144,8 @@ at::Tensor scratch(size_t bytes, const at::Tensor& like) {
 // linear_fwd(x, B, d_in, W_c, idx, active, n_active, K, bias, d_out, y, seg, packed, act[, blocked]) -> y
 // B None: the rows of x, which must be [rows, d_in]; y None: allocated; idx in a 16-bit container: the narrow-index call.
 // blocked: the call may take the matrix cores, from this copy of the terms, or with None from one that it makes for itself, in the same
-// stream and from what the arrays hold then.  Nothing is kept: 4096 -> 16384 (13108 rows stored, K = 205) at batch 2048 pays 15 us of
-// 240 for it, and weights that changed since, in whatever way, are the weights that count.
+// stream and from what the arrays hold then.  Nothing is kept: 4096 -> 16384 (13108 rows stored, K = 205) at batch 2048 pays 10 us of
+// 237 for it, and weights that changed since, in whatever way, are the weights that count.
 PyObject* linear_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded([&](PyObject*& out) {
         if (n != 15) need(n, 14);

@@ -53,68 +53,97 @@ static BlockedLayout blocked_layout(int n_rows, int K, int d_in) {
 // byte offset of column c (0..63) of row r (0..31) in a block's LDS tile
 __device__ __forceinline__ uint32_t block_place(int r, int c) { return (uint32_t)(r * 128) + (((uint32_t)c * 2u) ^ (((uint32_t)(r >> 1) & 7u) << 4)); }
 
-// One workgroup per group of 32 rows.  The counts per (row, chunk) come from the seg table; their running sums down the rows of a
-// chunk, and along the chunks, give every term its place without another pass.  Bound by the latency of its few dependent
-// steps (4096 -> 16384, 13108 stored rows, K = 205: 15.5 us; with 256 threads and the divisions of a flat loop 29.6).
-constexpr int kBuildThreads = 1024;
-__global__ __launch_bounds__(kBuildThreads) void k_block_terms(const uint16_t* __restrict__ W_c, const void* __restrict__ idx, int idx_u16,
+// One workgroup per group of 32 rows, two rows to a wavefront.  The counts per (row, chunk) come from the seg table, lane l having
+// chunk l of the wavefront's rows; their sums over the wavefronts below, and along the chunks (which every wavefront sums for itself),
+// give each term its place without another pass.  The terms are requested before the table is waited for, and a list is put together in LDS
+// (STAGED: where it fits) so that it leaves in whole lines.  A call that brings no copy pays for this in front of its product.  On small
+// layers the chain of dependent steps bounds it (200 -> 300 adds 4.2 us to a call, 512 -> 2048 with K = 100 4.9), on large ones the
+// terms' way in and out (4096 -> 16384, K = 205, 37 MB: 10.3 us; with the terms fetched behind the sums, each list stored from where its
+// terms' lanes were and the sums down the rows by one lane per chunk 15.1).  Eight loads ahead instead of four need more registers than
+// two workgroups per compute unit leave (14 us).
+constexpr int kBuildThreads = 1024, kBuildWaves = kBuildThreads / 64, kBuildAhead = 4;   // loads of 64 terms per row in flight
+static_assert(kBlockRows == 2 * kBuildWaves, "two rows per wavefront");
+template <typename IT, bool STAGED>
+__global__ __launch_bounds__(kBuildThreads, 8) void k_block_terms(const uint16_t* __restrict__ W_c, const IT* __restrict__ idx,
                                                                const uint16_t* __restrict__ seg, int seg_stride, int n_rows, int K, int chunks,
                                                                int units_per_group, uint32_t* __restrict__ table, uint4* __restrict__ lists) {
-    extern __shared__ uint32_t sh[];
-    uint32_t* offs = sh;                                        // [chunks + 1]: where the lists begin, in units
-    uint32_t* count = offs + chunks + 1;                        // [chunks]: terms of the lists
-    int* place = reinterpret_cast<int*>(count + chunks);        // [32][chunks]: place of term 0 of the row if it were in this chunk's list
-    const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r0 = g * kBlockRows;
-    const int rows = min(kBlockRows, n_rows - r0);
-    for (int i = tid; i < rows * chunks; i += kBuildThreads) {
-        const int r = i / chunks, c = i - r * chunks;
-        const uint16_t* s = seg + (size_t)(r0 + r) * seg_stride + c;
-        place[i] = max((int)s[1] - (int)s[0], 0) | ((int)s[0] << 16);   // count, terms before the chunk
-    }
-    __syncthreads();
-    for (int c = tid; c < chunks; c += kBuildThreads) {
-        int n = 0;
-        for (int r = 0; r < rows; ++r) {
-            const uint32_t v = (uint32_t)place[r * chunks + c];
-            place[r * chunks + c] = n - (int)(v >> 16);
-            n += (int)(v & 0xffffu);
+    extern __shared__ __attribute__((aligned(16))) uint32_t sh[];
+    uint32_t* const stage = sh;                                                   // STAGED: the group's lists
+    uint2* const span = reinterpret_cast<uint2*>(sh + (STAGED ? 4 * (size_t)units_per_group : 0));   // [chunks + 1]: the lists' first places, their terms
+    uint32_t* const place = reinterpret_cast<uint32_t*>(span + chunks + 1);       // [32][chunks]: place of term 0 of the row if it were in this chunk's list
+    uint32_t* const part = place + kBlockRows * chunks;                           // [2][wavefronts][64]: terms per chunk of the wavefront's rows
+    const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r0 = g * kBlockRows + 2 * wv;
+    const int rows = min(max(n_rows - r0, 0), 2);   // of this wavefront
+    uint32_t w[2][kBuildAhead], col[2][kBuildAhead];
+    auto load = [&](int r, int k0) {
+#pragma unroll
+        for (int u = 0; u < kBuildAhead; ++u) {
+            const size_t at = (size_t)(r0 + r) * K + min(k0 + 64 * u + lane, K - 1);
+            if (k0 + 64 * u < K) { w[r][u] = W_c[at]; col[r][u] = (uint32_t)idx[at]; }
         }
-        count[c] = (uint32_t)n;
-        offs[c] = (uint32_t)(n + 3) / 4;
-    }
-    __syncthreads();
-    if (wv == 0) {   // exclusive sums along the chunks
-        uint32_t base = (uint32_t)g * (uint32_t)units_per_group;
-        for (int c0 = 0; c0 < chunks; c0 += 64) {
-            const int c = c0 + lane;
-            const uint32_t n = c < chunks ? offs[c] : 0u;
-            uint32_t sum = n;
-            for (int d = 1; d < 64; d <<= 1) {
-                const uint32_t up = __shfl_up(sum, d, 64);
-                if (lane >= d) sum += up;
+    };
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+        if (r < rows) load(r, 0);
+    uint32_t base = 0;   // units of the chunks before
+    for (int c0 = 0; c0 < chunks; c0 += 64) {
+        const int c = c0 + lane;
+        uint32_t s0[2] = {0u, 0u}, n[2] = {0u, 0u};
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+            if (r < rows && c < chunks) {
+                const uint16_t* s = seg + (size_t)(r0 + r) * seg_stride + c;
+                s0[r] = s[0];
+                n[r] = (uint32_t)max((int)s[1] - (int)s0[r], 0);
             }
-            if (c < chunks) offs[c] = base + sum - n;
-            base += __shfl(sum, 63, 64);
+        uint32_t* const p = part + (c0 & 64) * kBuildWaves;   // (two places in turn: one barrier)
+        p[wv * 64 + lane] = n[0] + n[1];
+        __syncthreads();
+        uint32_t below = 0, total = 0;
+#pragma unroll
+        for (int v = 0; v < kBuildWaves; ++v) {
+            const uint32_t m = p[v * 64 + lane];
+            below += v < wv ? m : 0u;
+            total += m;
         }
-        if (lane == 0) offs[chunks] = base;
+        const uint32_t units = (total + 3) / 4, incl = wave_prefix(units), first = min(base + incl - units, (uint32_t)units_per_group);
+        base += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        if (c < chunks) {
+            place[2 * wv * chunks + c] = 4 * first + below - s0[0];
+            place[(2 * wv + 1) * chunks + c] = 4 * first + below + n[0] - s0[1];
+            if (wv == 0) span[c] = make_uint2(4 * first, min(total, 4 * ((uint32_t)units_per_group - first)));
+        }
     }
+    if (tid == 0) span[chunks] = make_uint2(4 * min(base, (uint32_t)units_per_group), 0u);
     __syncthreads();
-    for (int c = tid; c <= chunks; c += kBuildThreads) table[(size_t)g * (chunks + 1) + c] = offs[c];
-    uint32_t* out = reinterpret_cast<uint32_t*>(lists);
-    for (int r = wv; r < rows; r += kBuildThreads / 64) {
-        const size_t first = (size_t)(r0 + r) * K;
-        for (int k = lane; k < K; k += 64) {
-            const uint32_t col = idx_u16 ? static_cast<const uint16_t*>(idx)[first + k] : static_cast<const uint32_t*>(idx)[first + k];
-            const uint32_t term = (uint32_t)W_c[first + k] | (block_place(r, (int)(col & 63u)) << 16);
-            const int c = min((int)(col >> 6), chunks - 1);
-            const uint32_t at = (uint32_t)(place[r * chunks + c] + k);     // within the list
-            const uint32_t room = 4u * (offs[c + 1] - offs[c]);
-            if (at >= room) continue;                                       // (an idx that its seg table does not describe)
-            uint32_t* list = out + 4u * (size_t)offs[c];
-            list[at] = term;
-            if (at + 1u == count[c])   // padding: copies of the last term
-                for (uint32_t i = at + 1u; i < room; ++i) list[i] = term;
+    const uint32_t group0 = (uint32_t)g * (uint32_t)units_per_group;
+    for (int c = tid; c <= chunks; c += kBuildThreads) table[(size_t)g * (chunks + 1) + c] = group0 + span[c].x / 4;
+    uint32_t* const out = STAGED ? stage : reinterpret_cast<uint32_t*>(lists + group0);
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+        for (int k0 = 0; r < rows && k0 < K; k0 += 64 * kBuildAhead) {
+            if (k0 != 0) load(r, k0);
+            uint32_t at[kBuildAhead];
+            uint2 list[kBuildAhead];
+#pragma unroll
+            for (int u = 0; u < kBuildAhead; ++u)   // (every place is read before the first term is written: LDS answers take a hundred clocks)
+                if (k0 + 64 * u < K) {
+                    const int c = (int)min(col[r][u] >> 6, (uint32_t)chunks - 1u);
+                    list[u] = span[c];
+                    at[u] = place[(2 * wv + r) * chunks + c] + (uint32_t)(k0 + 64 * u + lane) - list[u].x;   // within the list
+                }
+#pragma unroll
+            for (int u = 0; u < kBuildAhead; ++u)
+                if (k0 + 64 * u + lane < K && at[u] < list[u].y) {   // (else an idx that its seg table does not describe)
+                    const uint32_t term = w[r][u] | (block_place(2 * wv + r, (int)(col[r][u] & 63u)) << 16);
+                    out[list[u].x + at[u]] = term;
+                    if (at[u] + 1u == list[u].y)   // padding: copies of the last term
+                        for (uint32_t i = at[u] + 1u; i % 4 != 0; ++i) out[list[u].x + i] = term;
+                }
         }
+    if (STAGED) {
+        __syncthreads();
+        for (uint32_t u = tid; u < span[chunks].x / 4; u += kBuildThreads) lists[group0 + u] = reinterpret_cast<const uint4*>(stage)[u];
     }
 }
 
@@ -467,12 +496,13 @@ static int choose_blocked_tile(int B, int d_in, int n_active, double* us) {
     return best;
 }
 
-// Taken where its estimate is this far ahead of the gathering kernels' (both estimates are good to about 10 %; no measured
-// point was then slower)
-constexpr double kBlockedMargin = 0.85;
+// Taken where its estimate is this far ahead of the gathering kernels'.  On 168 measured points (21 layers at batches of 16 to 2048, both
+// kinds of call) 0.95 takes one point that is behind by more than 2 % (4 %), and a call is 0.2 % slower on average than with the faster
+// of the two forms throughout; 0.85 leaves out points where the gathering kernel is up to 26 % behind, 1.0 takes some that are 14 % behind.
+constexpr double kBlockedMargin = 0.95;
 
-// What making the copy adds to a call (us)
-static double block_terms_us(int n, int K) { return 6.0 + 2.5e-6 * n * (double)K; }
+// What making the copy adds to a call (us): between 4.1 (200 -> 300) and 14 (4096 -> 16384, K = 205) on those layers
+static double block_terms_us(int n, int K) { return 4.3 + 2.9e-6 * n * (double)K; }
 
 static bool blocked_fits(int n_active, int K, int d_in) {
     if (n_active <= 0 || K <= 0 || d_in < 8 || d_in > 65536) return false;
@@ -518,14 +548,21 @@ srigl_status srigl_block_terms(const void* W_c, const void* idx, int32_t idx_bit
     if (!blocked_fits(n_rows, K, d_in)) return SRIGL_ERR_UNSUPPORTED;
     const BlockedLayout l = blocked_layout(n_rows, K, d_in);
     if (blocked_bytes < l.bytes) return SRIGL_ERR_CAPACITY;
-    const size_t lds = (size_t)(2 * l.chunks + 1) * 4 + (size_t)kBlockRows * l.chunks * 4;
-    static LdsLimit lds_limit;
-    if (lds_limit.ensure(k_block_terms, lds) != SRIGL_OK) return SRIGL_ERR_HIP;
     unsigned char* base = static_cast<unsigned char*>(blocked);
-    hipLaunchKernelGGL(k_block_terms, dim3((unsigned)l.groups), dim3(kBuildThreads), lds, static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(W_c),
-                       idx, idx_bits == 16 ? 1 : 0, seg, srigl_seg_stride(d_in), n_rows, K, l.chunks, l.units_per_group,
-                       reinterpret_cast<uint32_t*>(base), reinterpret_cast<uint4*>(base + l.table_bytes));
-    return hip_ok(hipGetLastError());
+    auto launch = [&](auto kern, LdsLimit& lds_limit, size_t lds, auto* columns) {
+        if (lds_limit.ensure(kern, lds) != SRIGL_OK) return SRIGL_ERR_HIP;
+        hipLaunchKernelGGL(kern, dim3((unsigned)l.groups), dim3(kBuildThreads), lds, static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(W_c),
+                           columns, seg, srigl_seg_stride(d_in), n_rows, K, l.chunks, l.units_per_group, reinterpret_cast<uint32_t*>(base),
+                           reinterpret_cast<uint4*>(base + l.table_bytes));
+        return hip_ok(hipGetLastError());
+    };
+    const size_t tables = ((size_t)2 * (l.chunks + 1) + (size_t)kBlockRows * l.chunks + 2 * 64 * kBuildWaves) * 4, staged = tables + 16 * (size_t)l.units_per_group;
+    static LdsLimit limit[4];
+    const int32_t* wide = static_cast<const int32_t*>(idx);
+    const uint16_t* narrow = static_cast<const uint16_t*>(idx);
+    if (staged <= kLdsMax)
+        return idx_bits == 32 ? launch(k_block_terms<int32_t, true>, limit[0], staged, wide) : launch(k_block_terms<uint16_t, true>, limit[1], staged, narrow);
+    return idx_bits == 32 ? launch(k_block_terms<int32_t, false>, limit[2], tables, wide) : launch(k_block_terms<uint16_t, false>, limit[3], tables, narrow);
 }
 
 srigl_status srigl_blocked_linear_fwd(const void* x, int32_t B, int32_t d_in, const void* blocked, const void* W_c, const void* idx,

@@ -283,6 +283,17 @@ struct LdsLimit {
 
 __device__ __forceinline__ float bf16_bits_to_float(uint32_t b) { return __uint_as_float(b << 16); }
 
+// Sum of v over this lane and the lanes below it (DPP: a cross-lane read through the LDS network costs some sixty clocks).
+__device__ __forceinline__ unsigned int wave_prefix(unsigned int v) {
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);   // row_shr:1
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
 // Activation between the two linear layers of an MLP block: identity, max(v, 0), or v * Phi(v) with the normal
 // distribution function Phi (the exact, erf-based GELU).
 __device__ __forceinline__ float apply_act(float v, int act) {

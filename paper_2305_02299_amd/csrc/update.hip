@@ -146,16 +146,6 @@ __global__ __launch_bounds__(kScanThreads) void k_hist(const float* __restrict__
 }
 static_assert(kFine == 16 && kDigits == 4 * kScanThreads, "sixteen digits per coarse count, four per thread");
 
-// Sum of v over this lane and the lanes below it (DPP: a cross-lane read through the LDS network costs some sixty clocks).
-__device__ __forceinline__ unsigned int wave_prefix(unsigned int v) {
-    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);   // row_shr:1
-    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
-    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
-    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
-    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
-    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
-    return v;
-}
 __device__ __forceinline__ unsigned int wave_total(unsigned int v) { return (unsigned)__builtin_amdgcn_readlane((int)wave_prefix(v), 63); }
 
 // With n keys in this lane's bin: the bin d with suffix(d) >= want > suffix(d + 1), suffix(d) = keys in bins d and above;
