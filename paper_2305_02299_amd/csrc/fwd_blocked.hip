@@ -473,7 +473,10 @@ static double blocked_tile_us(int tile, int B, int n, int chunks) {
 // keep 256 compute units busy for two whole rounds where 1.6 would do.  So the large shapes are also tried for their full rounds
 // only, with the stored rows that are left in the shape that suits those.  Measured: that layer 240 -> 233 us (a part-filled round
 // runs faster than a full one, so less than the count of rounds promises); 546 -> 16192 at batch 606 in 256 x 192 tiles 26 us, 28 in
-// 256 x 256, 34 in 128 x 128.
+// 256 x 256, 34 in 128 x 128.  kSplitUs: what the second launch adds (its estimate counts a start of its own; the first one's last workgroups
+// and its power draw cost more).  Of 128 points (768- to 4096-wide, 2560 to 16000 stored rows, batches 600 to 2048) the shape taken is on
+// average 0.4 % behind the fastest of up to 12, at worst 8 %; with -1 in its place 11 %.
+constexpr double kSplitUs = 4.0;
 static int choose_blocked_tile(int B, int d_in, int n_active, double* us) {
     const int chunks = (d_in + kSegCols - 1) / kSegCols;
     constexpr int kShapes[] = {SRIGL_BLOCKED_64, SRIGL_BLOCKED_128, SRIGL_BLOCKED_192, SRIGL_BLOCKED_256};
@@ -491,7 +494,7 @@ static int choose_blocked_tile(int B, int d_in, int n_active, double* us) {
         const int done = (int)columns * bn;
         const double head = blocked_tile_us(first, B, done, chunks);
         for (int s : kShapes)
-            if (s != first) consider(first | s << 4 | (int)columns << 8, head + blocked_tile_us(s, B, n_active - done, chunks) - 1.0);
+            if (s != first) consider(first | s << 4 | (int)columns << 8, head + blocked_tile_us(s, B, n_active - done, chunks) + kSplitUs);
     }
     return best;
 }
@@ -508,6 +511,13 @@ static bool blocked_fits(int n_active, int K, int d_in) {
     if (n_active <= 0 || K <= 0 || d_in < 8 || d_in > 65536) return false;
     const BlockedLayout l = blocked_layout(n_active, K, d_in);
     return (long long)l.groups * l.units_per_group < (1LL << 30);   // places of terms in 32 bits
+}
+
+double blocked_estimate_us(int B, int d_in, int n_active, int K, int d_out) {
+    if (B <= 0 || n_active > d_out || K > d_in || !blocked_fits(n_active, K, d_in)) return 1e30;
+    double us;
+    choose_blocked_tile(B, d_in, n_active, &us);
+    return us + block_terms_us(n_active, K);
 }
 
 }  // namespace srigl

@@ -186,6 +186,8 @@ srigl_status launch_rowloop_plan(const FwdArgs& a, const RowloopPlan& p, hipStre
 srigl_fwd_algo choose_fwd_algo(const FwdArgs& a);
 // Estimated time (us) of the condensed forward call of these sizes in the kernel the library's own choice takes.
 double condensed_estimate_us(int B, int d_in, int n_active, int K, int d_out, bool bf16, bool has_active);
+// ... and on the matrix cores, the blocked copy made in the call (bf16 storage; 1e30 where the sizes do not allow it).
+double blocked_estimate_us(int B, int d_in, int n_active, int K, int d_out);
 
 // The small-batch forward kernel takes its activations either from global memory through the vector caches (a gather:
 // no staging pass, no barrier, any d_in) or from rows of x staged in LDS.  Estimated times (us) of both: least-squares

@@ -17,6 +17,8 @@
 //         successive MFMAs (both operands use the same k-to-slot map, so the sum runs over matching k).
 // Result block layout: accumulator register e of lane l is row 8*(e/4) + 4*(l/32) + e%4, column l%32.
 #include "mma_tile.h"
+#include <algorithm>
+#include <cmath>
 
 namespace srigl {
 
@@ -420,6 +422,26 @@ static void choose_tile_and_split(int B, int n_active, int d_in, int d_out, bool
     if (est_us_out) *est_us_out = 3.5 + best_us + 4.0 * (double)B * d_out / 4.5e6;
 }
 
+// Time (us) of the bf16 product in the tile and parts chosen above, for the choice between the forms: refitted to the kernel as it is (the
+// constants above rank its tiles, and are 15 to 25 % high on 4096-wide layers since the epilogue writes whole rows).  A round of tiles
+// costs a fixed part and a part per element of d_in; two 64 x 64 tiles share a compute unit.  On 144 measured points (18 layers, 200- to
+// 4096-wide, batches of 16 to 2048) the deviation is 7 % (root of the mean square), 10 % where d_in is cut.
+static double structured_bf16_us(srigl_gemm_tile tile, int splits, int B, int d_in, int n_active, int d_out) {
+    const double d = d_in * 1e-3 / splits;
+    auto groups = [&](int bm, int bn) {
+        const long long tiles = (long long)((B + bm - 1) / bm) * ((n_active + bn - 1) / bn);
+        return (double)(splits > 1 ? (tiles + kXcds - 1) / kXcds * kXcds * splits : tiles);
+    };
+    double us = 3.5 + 4.0 * (double)B * d_out / 4.5e6;
+    if (tile == SRIGL_TILE_64x64) us += groups(64, 64) <= 256 ? 0.8 + 4.15 * d : std::ceil(groups(64, 64) / 512) * (0.2 + 5.85 * d);
+    else if (tile == SRIGL_TILE_128x128) us += std::ceil(groups(128, 128) / 256) * (3.3 + 8.5 * d);
+    else if (tile == SRIGL_TILE_256x128) us += std::ceil(groups(256, 128) / 256) * (2.6 + 13.3 * d);
+    else us += std::ceil(groups(256, 256) / 256) * (2.0 + 22.5 * d);
+    if (splits > 1) us += 2.5 + 8.0 * splits * (double)B * n_active / 4.5e6;
+    else if (n_active < d_out) us += 1.0;   // (the tables of the epilogue)
+    return us;
+}
+
 template <typename T>
 static srigl_status launch_structured(int tile, const void* x, int B, int d_in, const void* Wd, const int32_t* active, int n_active,
                                       const float* bias, int d_out, float* y, int splits, float* part, hipStream_t st) {
@@ -474,12 +496,16 @@ srigl_status srigl_densify(const void* W_c, srigl_dtype w_dtype, const int32_t* 
 
 // Estimates in microseconds, calibrated on MI355X measurements of both forms (fp32 and bf16 storage, batches 1..2048,
 // 512- to 4096-wide layers, 80-99 % sparsity):
-//   condensed  = the estimate of the forward kernel the library's own choice takes for these sizes (condensed_estimate_us)
-//   structured ~ 3.5 + d_in x (rounds of tiles x nanoseconds per element of d_in of the chosen tile) / 1000 / parts of d_in
+//   condensed  = the estimate of the forward kernel the library's own choice takes for these sizes (condensed_estimate_us); bf16: or of the
+//                matrix-core form with its copy made in the call, whichever is faster
+//   structured = structured_bf16_us; fp32:
+//              ~ 3.5 + d_in x (rounds of tiles x nanoseconds per element of d_in of the chosen tile) / 1000 / parts of d_in
 //                  + the second launch when d_in is cut into parts (srigl_structured_linear_fwd_split)
 //                  + 4 B d_out / 4.5e6              (writing the result at HBM speed)
 srigl_representation srigl_choose_representation(int32_t B, int32_t d_in, int32_t n_active, int32_t K, int32_t d_out,
                                                  srigl_dtype dtype, float* est_condensed_us, float* est_structured_us) {
+    // On the same points (bf16) the form taken is 0.2 % slower than the faster one on average, at worst 6 %.  (While the condensed estimate
+    // was the gathering kernels' alone: up to 20 %, and a dense copy of 107 MB on 4096 -> 16384 for what the estimate called 2.7 times.)
     struct Key { int32_t B, d_in, n_active, K, d_out, dtype; };
     struct Estimates { double cond, stru; };
     static thread_local DecisionCache<Key, Estimates, 64> cache;
@@ -488,7 +514,15 @@ srigl_representation srigl_choose_representation(int32_t B, int32_t d_in, int32_
         v.cond = condensed_estimate_us(B, d_in, n_active, K, d_out, dtype == SRIGL_BF16, n_active < d_out);
         const bool f32 = dtype == SRIGL_F32;
         v.stru = 0.0;
-        choose_tile_and_split(B > 0 ? B : 1, n_active > 0 ? n_active : 1, d_in, d_out, f32, nullptr, nullptr, &v.stru);
+        if (f32) {
+            choose_tile_and_split(B > 0 ? B : 1, n_active > 0 ? n_active : 1, d_in, d_out, f32, nullptr, nullptr, &v.stru);
+        } else {
+            srigl_gemm_tile tile;
+            int splits;
+            choose_tile_and_split(B > 0 ? B : 1, n_active > 0 ? n_active : 1, d_in, d_out, f32, &tile, &splits, nullptr);
+            v.stru = structured_bf16_us(tile, splits, B > 0 ? B : 1, d_in, n_active > 0 ? n_active : 1, d_out);
+            v.cond = std::min(v.cond, blocked_estimate_us(B, d_in, n_active, K, d_out));
+        }
         if ((d_in * (f32 ? 4 : 2)) % 16 != 0) v.stru = 1e30;   // the matrix-core kernel needs rows of whole 16-byte pieces
         return v;
     });

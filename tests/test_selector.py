@@ -73,3 +73,17 @@ def test_parts_of_d_in_for_the_structured_only_product(B_):
             assert 1 <= parts <= max(1, min(16, stages // 4))
             assert need == (parts * B * n_active * 4 if parts > 1 else 0)
     assert B_.srigl_structured_split_plan(0, 768, 0, 3072, B_.F32) == (1, 0)
+
+
+def test_the_condensed_estimate_is_that_of_the_form_the_call_takes(B_):
+    """bf16 at sizes where the layer's call goes to the matrix cores: the choice compares that form, not the gathering kernels (measured, with its
+    copy made in the call: 4096 -> 16384 with 13108 stored 237 us at batch 2048, 130 at 1024; the gathering kernels need 782 and 447)."""
+    for (B, d_in, n, K, d_out, condensed, structured) in ((2048, 4096, 13108, 205, 16384, 237.2, 219.5), (1024, 4096, 13108, 205, 16384, 129.7, 114.8),
+                                                         (2048, 4096, 16384, 205, 16384, 236.9, 223.4), (512, 4096, 4096, 410, 4096, 48.2, 29.5),
+                                                         (1024, 768, 3072, 77, 3072, 23.0, 16.9), (512, 1024, 4096, 102, 4096, 19.7, 11.4)):
+        assert B_.srigl_blocked_tile_with_copy(B, d_in, n, K, d_out) != 0
+        r, c, s = B_.srigl_choose_representation(B, d_in, n, K, d_out, B_.BF16)
+        assert abs(c / condensed - 1) < 0.15 and abs(s / structured - 1) < 0.15
+    # rows the structured form cannot hold: the estimate is still the matrix-core form's
+    r, c, s = B_.srigl_choose_representation(1024, 546, 16192, 98, 16192, B_.BF16)
+    assert r == B_.REPR_CONDENSED and abs(c / 40.9 - 1) < 0.15
