@@ -357,7 +357,7 @@ srigl_status srigl_csr_linear_fwd(const void* x, srigl_dtype x_dtype, int32_t B,
  * weights copied, everything else zero: grown weights start at zero), report_dev[4] = {k', neurons that remain, neurons
  * ablated by this update, weights pruned in step 6}.  All buffers are device memory, caller-owned; outputs must not alias
  * inputs; workspace of srigl_mask_update_workspace_bytes(d_out, d_in) bytes (counters, three integers per neuron and two
- * candidate lists of d_out * d_in / 16 eight-byte keys each, at least 4096), 256-byte aligned.  Asynchronous on `stream`.
+ * candidate lists of d_out * d_in / 32 eight-byte keys each, at least 4096), 256-byte aligned.  Asynchronous on `stream`.
  * Readings: a kept weight is salient if it is not among the K_upd smallest-magnitude kept weights of the layer, a pruned
  * position if its gradient is among the K_upd largest at pruned positions; a neuron is ablated if it holds weights and
  * its salient count is below max(gamma k, 1); a neuron without weights stays ablated; k' = min(d_in, budget / remaining

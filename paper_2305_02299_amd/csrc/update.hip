@@ -10,8 +10,9 @@
 // the first digit.  k_hist counts the digits of the whole layer, k_collect lists the keys of the digit that holds the K-th
 // (about a percent of a layer with real-valued contents), k_final finishes the walk on that list in one workgroup.  So the
 // layer is read twice per selection pair, and both selections of step 3 share the reads (an element belongs to exactly one).
-// Contents with more keys in that digit than the list has room for (a layer of constant magnitudes) are finished by reading
-// the layer instead, in that one workgroup.  Step 6 ranks the weights of the neurons that remain: the per-neuron kernel takes
+// Contents with more keys in that digit than the list has room for (few distinct magnitudes: gradients that are zero, quantised or signed
+// weights) go without a list: k_collect counts the next 12 bits instead, and k_final's launch, which has a workgroup per compute unit
+// or so standing by for that, counts the last 7 bits of the magnitude in one pass (finish_wide).  Step 6 ranks the weights of the neurons that remain: the per-neuron kernel takes
 // the ablated neurons' keys out of step 3's counts, so step 6 starts at k_collect, and with no neuron ablated it is step 3's
 // answer.  Row-wise selections (step 7) are a search for the threshold by its bits, one wavefront per row, keys in registers,
 // counts from ballots: no LDS, no barrier.
@@ -39,20 +40,26 @@ constexpr int kCoarse = 256, kFine = kDigits / kCoarse;   // the digit is found 
 constexpr int kHistCopies = 8;
 constexpr int kCountCopies = 64;
 constexpr int kNextCopies = 4;   // of the counters of step 3's second digits (a hundredth as many adds)
+constexpr int kWideParts = 256;  // parts of the layer in finish_wide, at most
 
 // Head of the workspace.  Selections: 0 = smallest kept weights of the layer, 1 = largest gradients at pruned positions,
 // 2 = smallest kept weights of the remaining neurons (counted in hist[0] once the ablated neurons are out of it).
 struct UpdateScratch {
     unsigned int hist[2][kHistCopies][kDigits];
     unsigned int coarse[2][kHistCopies][kCoarse];
-    unsigned int next[2][kNextCopies][kDigits];   // second digits of the listed keys of selections 0 and 1
+    // second digits of the keys with the picked first one: selections 0 and 1 always (copies), selection 2 (one) where it has no list
+    unsigned int next[2 * kNextCopies + 1][kDigits];
     unsigned int cnt_remaining[kCountCopies], cnt_ablated[kCountCopies];   // steps 4-5: neurons that stay / are ablated now
-    unsigned long long cand_count[3];   // keys in the selection's list; above the capacity: the list is not valid
+    unsigned long long cand_count[3];   // keys in the selection's list
+    unsigned int arrived[4];            // finish_wide: parts of the selection that have been counted
     SelState picked[3];                 // after the first digit (written by k_collect)
     SelState fin[3];                    // the finished selections (k_final)
     unsigned long long t_prune;         // step 6's threshold and the new fan-in (k_final of step 6)
     long long k_new;
 };
+__device__ __forceinline__ unsigned int* next_digits(UpdateScratch* s, int sel, int copy) {
+    return s->next[sel == 2 ? 2 * kNextCopies : sel * kNextCopies + copy % kNextCopies];
+}
 constexpr size_t kZeroWords = (offsetof(UpdateScratch, picked) + 15) / 16;   // 16-byte pieces cleared before an update
 
 __device__ __forceinline__ unsigned int mag_bits(float v) { return __float_as_uint(v) & 0x7fffffffu; }
@@ -207,6 +214,19 @@ __device__ SelState pick_first(const UpdateScratch* __restrict__ s, int hist, un
     return st;
 }
 
+// add(d, n) for the lanes that are `on`: those with the first one's digit add together, the others for themselves (contents of few magnitudes
+// have whole wavefronts on one counter, whose atomics take turns).
+template <typename Add>
+__device__ __forceinline__ void add_by_digit(bool on, unsigned int d, Add add) {
+    const uint64_t any = __ballot(on);
+    if (any == 0) return;
+    const int lead = __builtin_ctzll(any);
+    const unsigned int first = (unsigned)__builtin_amdgcn_readlane((int)d, lead);
+    const uint64_t same = __ballot(on && d == first);
+    if (on && d != first) add(d, 1u);
+    if ((int)(threadIdx.x & 63) == lead) add(first, (unsigned)__popcll(same));
+}
+
 // Sum of the 64 copies of a neuron counter.  Called by one whole wavefront; the result is the same on every lane.
 __device__ __forceinline__ unsigned int sum_copies(const unsigned int (&c)[kCountCopies], int lane) {
     return wave_total(c[lane]);
@@ -217,7 +237,8 @@ __device__ __forceinline__ unsigned int sum_copies(const unsigned int (&c)[kCoun
 // selection in LDS and appends them with one update of the list's length; what does not fit goes out one by one.  PAIR also counts the
 // next 12 bits of the keys it lists, so that k_final, one workgroup on its own, goes through the list once instead of twice (768 x 3072,
 // 23000 keys: 9.5 -> 5.6 us there for 0.7 here).  Counting a neuron's salient elements here and in k_final, to spare k_row_salient the
-// layer, cost k_final more than k_row_salient saved.
+// layer, cost k_final more than k_row_salient saved.  A selection whose digit holds more keys than a list has room for gets the next 12 bits
+// of its keys counted instead (in LDS, in the place of the collected keys).
 constexpr int kStage = 2048;
 template <bool PAIR>
 __global__ __launch_bounds__(kScanThreads) void k_collect(const float* __restrict__ W, const uint8_t* __restrict__ mask,
@@ -225,7 +246,7 @@ __global__ __launch_bounds__(kScanThreads) void k_collect(const float* __restric
                                                           unsigned int n4, int d_in, unsigned long long K, UpdateScratch* __restrict__ s,
                                                           unsigned long long* __restrict__ candA, unsigned long long* __restrict__ candB,
                                                           unsigned long long cap) {
-    __shared__ unsigned long long stage[PAIR ? 2 : 1][kStage];
+    __shared__ __align__(16) unsigned long long stage[PAIR ? 2 : 1][kStage];
     __shared__ SelState cur[2];
     __shared__ unsigned int n_staged[2];
     __shared__ unsigned long long base[2];
@@ -245,13 +266,26 @@ __global__ __launch_bounds__(kScanThreads) void k_collect(const float* __restric
         }
     }
     __syncthreads();
-    const bool liveA = !cur[0].done && cur[0].in_bin <= cap, liveB = PAIR && !cur[1].done && cur[1].in_bin <= cap;
-    if (!liveA && !liveB) return;
-    const unsigned int digA = liveA ? (unsigned int)cur[0].prefix : ~0u, digB = liveB ? (unsigned int)cur[1].prefix : ~0u;
+    const bool openA = !cur[0].done, openB = PAIR && !cur[1].done;
+    if (!openA && !openB) return;
+    const bool wideA = openA && cur[0].in_bin > cap, wideB = openB && cur[1].in_bin > cap;
+    const unsigned int digA = openA ? (unsigned int)cur[0].prefix : ~0u, digB = openB ? (unsigned int)cur[1].prefix : ~0u;
+    if (wideA || wideB) {
+        for (int i = t; i < kStage; i += kScanThreads) {
+            if (wideA) stage[0][i] = 0ull;
+            if (wideB) stage[PAIR ? 1 : 0][i] = 0ull;
+        }
+        __syncthreads();
+    }
+    auto second_digit = [](unsigned long long key) { return (unsigned int)(key >> (kDigitShift - kDigitBits)) & (kDigits - 1); };
     auto count_next = [&](int k, unsigned long long key) {
-        atomicAdd(&s->next[k][blockIdx.x % kNextCopies][(unsigned int)(key >> (kDigitShift - kDigitBits)) & (kDigits - 1)], 1u);
+        add_by_digit(true, second_digit(key), [&](unsigned int d, unsigned int n) { atomicAdd(next_digits(s, k, blockIdx.x) + d, n); });
     };
     auto put = [&](int k, unsigned long long key) {
+        if (k == 0 ? wideA : wideB) {
+            atomicAdd(reinterpret_cast<unsigned int*>(stage[PAIR ? k : 0]) + second_digit(key), 1u);
+            return;
+        }
         const unsigned int slot = atomicAdd(&n_staged[k], 1u);
         if (slot < (unsigned)kStage) {
             stage[k][slot] = key;
@@ -272,7 +306,7 @@ __global__ __launch_bounds__(kScanThreads) void k_collect(const float* __restric
     };
     auto flush = [&] {
         __syncthreads();
-        if (t < (PAIR ? 2 : 1)) {
+        if (t < (PAIR ? 2 : 1)) {   // (nothing was put in place of a selection that counts)
             const unsigned int n = min(n_staged[t], (unsigned)kStage);
             base[t] = n ? atomicAdd(&s->cand_count[t == 0 ? selA : 1], (unsigned long long)n) : 0ull;
         }
@@ -303,40 +337,223 @@ __global__ __launch_bounds__(kScanThreads) void k_collect(const float* __restric
     each_of_tail(N, n4, blockIdx.x * kScanThreads + t, gridDim.x * kScanThreads,
                  [&](unsigned int i) { element(i, mask[i], W[i], PAIR ? grad[i] : 0.0f); });
     flush();
+#pragma unroll
+    for (int k = 0; k < (PAIR ? 2 : 1); ++k) {
+        if (!(k == 0 ? wideA : wideB)) continue;
+#pragma unroll
+        for (int j = 0; j < kDigits / kScanThreads; ++j) {
+            const unsigned int d = t + j * kScanThreads, n = reinterpret_cast<const unsigned int*>(stage[k])[d];
+            if (n) atomicAdd(next_digits(s, k == 0 ? selA : 1, blockIdx.x) + d, n);
+        }
+    }
+}
+static_assert(2 * kStage == kDigits, "the counters take the place of the collected keys");
+
+// With c4 keys in the digits 4t .. 4t + 3 of thread t (c4.x in the lowest): the digit with the k_rem-th key becomes part of `st`, whose prefix
+// grows by `bits`; `left` bits of the key follow.  The whole workgroup; the same on every thread.  wave_sum, cur: its LDS.
+__device__ __forceinline__ void pick_next(SelState& st, const uint4 c4, int bits, int left, unsigned int (&wave_sum)[kScanThreads / 64], SelState& cur) {
+    const int t = threadIdx.x, lane = t & 63;
+    // keys in the digits above a thread's: in its wavefront's higher lanes and the higher wavefronts
+    const unsigned int mine = c4.x + c4.y + c4.z + c4.w, incl = wave_prefix(mine);
+    if (lane == 63) wave_sum[t >> 6] = incl;
+    __syncthreads();
+    unsigned int beyond = (unsigned)__builtin_amdgcn_readlane((int)incl, 63) - incl;
+    for (int w = kScanThreads / 64 - 1; w > (t >> 6); --w) beyond += wave_sum[w];
+    const unsigned int want = (unsigned)st.k_rem;
+    if (beyond < want && beyond + mine >= want) {
+        unsigned int above = beyond, in_bin = c4.w;
+        int digit = 4 * t + 3;
+        if (above + in_bin < want) { above += c4.w; in_bin = c4.z; --digit; }
+        if (digit == 4 * t + 2 && above + in_bin < want) { above += c4.z; in_bin = c4.y; --digit; }
+        if (digit == 4 * t + 1 && above + in_bin < want) { above += c4.y; in_bin = c4.x; --digit; }
+        SelState c = st;
+        c.k_rem = want - above;
+        c.prefix = (c.prefix << bits) | (unsigned)digit;
+        c.in_bin = in_bin;
+        if (c.k_rem == in_bin || left == 0) {
+            c.prefix <<= left;
+            c.done = 1;
+        }
+        cur = c;
+    }
+    __syncthreads();
+    st = cur;
+    __syncthreads();   // (cur is written again by the next pick)
+}
+static_assert(kDigits == 4 * kScanThreads, "four digits per thread");
+
+// The end of a selection without a list, after its second digit: the magnitudes still open differ in their last 7 bits.  Every workgroup
+// of the selection counts them over a part of the layer; the last one to arrive finds the magnitude, the part in which the k_rem-th of
+// its positions lies, and that position.  Two passes over the layer in all, by many workgroups, and one over a part.  (One workgroup that
+// walked the layer digit by digit took 8.6 ms on 768 x 3072 with zero gradients, 55 on 1953 x 4096 with signed weights; the whole update takes
+// 79 and 335 us now, with a fence per wavefront instead of one 108 and 376.)
+// `count`: [parts][128] in the place of the list.  false: another workgroup finishes.
+constexpr int kLastBits = kDigitShift - kDigitBits - 32, kLast = 1 << kLastBits;
+static_assert(kLast == 128, "two values per lane");
+__device__ bool finish_wide(SelState& st, int sel, int part, int parts, const float* __restrict__ W, const uint8_t* __restrict__ mask,
+                            const float* __restrict__ grad, const int* __restrict__ remains, unsigned int N, int d_in, unsigned int* arrived,
+                            unsigned int* __restrict__ count, unsigned int* sh) {
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    constexpr int U = 4, WAVES = kScanThreads / 64;
+    unsigned int* const total = sh;                // [kLast]
+    unsigned int* const found = sh + kLast;        // magnitude value, keys wanted of it, part, keys wanted in the part
+    unsigned int* const wave_n = found + 4;        // [WAVES]
+    unsigned int* const of_part = wave_n + WAVES;  // [kWideParts]
+    const float* const src = sel == 1 ? grad : W;
+    const unsigned long long prefix = st.prefix;   // the two digits
+    const unsigned int per = (unsigned int)(((unsigned long long)N + parts - 1) / parts);
+    auto part_begin = [&](int p) { return (unsigned int)min((unsigned long long)p * per, (unsigned long long)N); };
+    // Visits [lo, hi) in steps of U x `width` elements, `at` of them this thread's first; f(position, value or ~0) with all lanes of the wavefront.
+    auto visit = [&](unsigned int lo, unsigned int hi, unsigned int at, unsigned int width, auto f) {
+        for (unsigned long long b = lo; b < hi; b += (unsigned long long)U * width) {
+            unsigned int m[U], i[U];
+            float v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                i[u] = (unsigned int)min(b + (unsigned long long)u * width + at, (unsigned long long)N - 1);
+                m[u] = mask[i[u]];
+                v[u] = src[i[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const unsigned long long key = sel == 1 ? key_large_first(mag_bits(v[u]), i[u]) : key_small_first(mag_bits(v[u]), i[u]);
+                bool in = b + (unsigned long long)u * width + at < hi && (m[u] != 0) == (sel != 1) && (key >> (32 + kLastBits)) == prefix;
+                if (sel == 2) in = in && remains[i[u] / (unsigned)d_in] != 0;
+                if (!f(i[u], in ? (unsigned int)(key >> 32) & (kLast - 1) : ~0u)) return;
+            }
+        }
+    };
+    for (int i = t; i < kLast; i += kScanThreads) total[i] = 0;
+    __syncthreads();
+    visit(part_begin(part), part_begin(part + 1), t, kScanThreads, [&](unsigned int, unsigned int v) {
+        add_by_digit(v != ~0u, v, [&](unsigned int d, unsigned int n) { atomicAdd(&total[d], n); });
+        return true;
+    });
+    __syncthreads();
+    for (int i = t; i < kLast; i += kScanThreads) count[part * kLast + i] = total[i];
+    __syncthreads();
+    if (t == 0) {   // (one wavefront's fences: behind and in front of the workgroup's barriers they stand for all of it)
+        __threadfence();
+        found[0] = atomicAdd(arrived, 1u);
+        __threadfence();
+    }
+    __syncthreads();
+    if (found[0] != (unsigned)parts - 1) return false;
+    __syncthreads();
+    // ---- the magnitude
+    for (int i = t; i < kLast; i += kScanThreads) total[i] = 0;
+    __syncthreads();
+    {
+        unsigned int n = 0;
+        for (int p = t / kLast; p < parts; p += kScanThreads / kLast) n += __hip_atomic_load(&count[p * kLast + t % kLast], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (n) atomicAdd(&total[t % kLast], n);
+    }
+    __syncthreads();
+    if (wv == 0) {
+        const unsigned int lo = total[2 * lane], hi = total[2 * lane + 1];
+        int pair;
+        unsigned int above, in_pair, all;
+        pick_lane(lo + hi, (unsigned)st.k_rem, pair, above, in_pair, all);
+        const unsigned int top = (unsigned)__builtin_amdgcn_readlane((int)hi, pair), want = (unsigned)st.k_rem - above;
+        if (lane == 0) {
+            found[0] = 2 * pair + (want <= top ? 1 : 0);
+            found[1] = want <= top ? want : want - top;
+        }
+    }
+    __syncthreads();
+    const unsigned int value = found[0];
+    st.k_rem = found[1];
+    st.in_bin = total[value];
+    st.prefix = (prefix << kLastBits) | value;
+    st.done = 1;
+    if (st.k_rem == st.in_bin) {   // every position of the magnitude: the smallest key with it
+        st.prefix <<= 32;
+        return true;
+    }
+    // ---- the part, lower positions first
+    for (int p = t; p < parts; p += kScanThreads) of_part[p] = __hip_atomic_load(&count[p * kLast + value], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    // the group of 64 entries (or the entry) in which the want-th lies; want becomes its number in there
+    auto walk = [&](const unsigned int* n, int entries, unsigned int want) {
+        for (int e0 = 0; e0 < entries; e0 += 64) {
+            const unsigned int mine = e0 + lane < entries ? n[e0 + lane] : 0u, incl = wave_prefix(mine);
+            const uint64_t owner = __ballot(incl >= want && incl - mine < want);
+            if (owner) {
+                const int l = __builtin_ctzll(owner);
+                if (lane == 0) {
+                    found[2] = e0 + l;
+                    found[3] = want - ((unsigned)__builtin_amdgcn_readlane((int)incl, l) - (unsigned)__builtin_amdgcn_readlane((int)mine, l));
+                }
+                return;
+            }
+            want -= (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
+        }
+    };
+    if (wv == 0) walk(of_part, parts, (unsigned)st.k_rem);
+    __syncthreads();
+    // ---- the position: a run of the part per wavefront, counted; then the run that holds it once more
+    const unsigned int lo = part_begin(found[2]), hi = part_begin(found[2] + 1), want = found[3], run = (hi - lo + WAVES - 1) / WAVES;
+    auto run_begin = [&](int w) { return lo + min((unsigned)w * run, hi - lo); };
+    unsigned int n = 0;
+    visit(run_begin(wv), run_begin(wv + 1), lane, 64, [&](unsigned int, unsigned int v) {
+        n += (unsigned)__popcll(__ballot(v == value));
+        return true;
+    });
+    if (lane == 0) wave_n[wv] = n;
+    __syncthreads();
+    if (wv == 0) walk(wave_n, WAVES, want);
+    __syncthreads();
+    if (wv == (int)found[2]) {
+        unsigned int left = found[3];
+        visit(run_begin(wv), run_begin(wv + 1), lane, 64, [&](unsigned int i, unsigned int v) {
+            const uint64_t here = __ballot(v == value);
+            const unsigned int c = (unsigned)__popcll(here);
+            if (left > c) { left -= c; return true; }
+            const unsigned int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(here >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)here, 0u));
+            if (v == value && rank + 1 == left) found[0] = 0xffffffffu - i;
+            return false;
+        });
+    }
+    __syncthreads();
+    st.prefix = (st.prefix << 32) | found[0];
+    return true;
 }
 
-// The end of a selection: workgroup b takes selection b (PAIR) or 2.  The keys come from the list, or from the layer when there
-// is no valid list.  One workgroup runs this code once, so its length counts: with the list held in registers and every loop
-// unrolled over it, fetching the instructions took most of 10 us.  12-bit digits until at most kDirect keys share the
-// prefix (step 3: the first of them from k_collect's counters, which is enough on real-valued contents), which are then ranked
-// against each other.
-// Step 6's workgroup also takes the new fan-in from the neuron counters (step 5) and writes the report.
+// The end of a selection: workgroups of selection 0 and 1 in turn (PAIR), or of selection 2.  With a list the selection's first workgroup does
+// it all and the others return at once; without one they share the work (finish_wide).  One workgroup runs the code for a list once, so its
+// length counts: with the list held in registers and every loop unrolled over it, fetching the instructions took most of 10 us.  12-bit
+// digits until at most kDirect keys share the prefix (step 3: the first of them from k_collect's counters, which is enough on
+// real-valued contents), which are then ranked against each other.
+// Step 6's first workgroup also takes the new fan-in from the neuron counters (step 5) and writes the report.
 constexpr int kAhead = 8, kDirect = 256;
 template <bool PAIR>
 __global__ __launch_bounds__(kScanThreads) void k_final(const float* __restrict__ W, const uint8_t* __restrict__ mask, const float* __restrict__ grad,
                                                         const int* __restrict__ remains, unsigned int N, int d_in, UpdateScratch* __restrict__ s,
-                                                        const unsigned long long* __restrict__ candA, const unsigned long long* __restrict__ candB,
-                                                        unsigned long long cap, unsigned long long K, long long budget,
-                                                        long long* __restrict__ report) {
+                                                        unsigned long long* candA, unsigned long long* candB, unsigned long long cap,
+                                                        unsigned long long K, long long budget, long long* __restrict__ report) {
     __shared__ __align__(16) unsigned int h[kDigits];
     __shared__ unsigned int wave_sum[kScanThreads / 64];
     __shared__ SelState cur;
     __shared__ unsigned long long direct[kDirect];
     __shared__ unsigned int n_direct;
     const int t = threadIdx.x, lane = t & 63;
-    const int sel = PAIR ? (int)blockIdx.x : 2;
+    const int sel = PAIR ? (int)blockIdx.x & 1 : 2, part = PAIR ? (int)blockIdx.x >> 1 : (int)blockIdx.x, parts = PAIR ? (int)gridDim.x / 2 : (int)gridDim.x;
     SelState st;
     if (!PAIR) {
-        const unsigned int n_remaining = sum_copies(s->cnt_remaining, lane), n_ablated = sum_copies(s->cnt_ablated, lane);
+        const unsigned int n_ablated = sum_copies(s->cnt_ablated, lane);
+        if (part != 0 && n_ablated == 0) return;
         st = n_ablated == 0 ? s->fin[0] : s->picked[2];   // no neuron ablated: the same candidates and count as in step 3
-        if (t == 0) {
-            long long k = n_remaining > 0 ? budget / (long long)n_remaining : 0;
-            if (k > d_in) k = d_in;
-            s->k_new = k;
-            report[0] = k;
-            report[1] = n_remaining;
-            report[2] = n_ablated;
-            report[3] = (long long)(K < st.total ? K : st.total);
+        if (part == 0) {
+            const unsigned int n_remaining = sum_copies(s->cnt_remaining, lane);
+            if (t == 0) {
+                long long k = n_remaining > 0 ? budget / (long long)n_remaining : 0;
+                if (k > d_in) k = d_in;
+                s->k_new = k;
+                report[0] = k;
+                report[1] = n_remaining;
+                report[2] = n_ablated;
+                report[3] = (long long)(K < st.total ? K : st.total);
+            }
         }
     } else {
         st = s->picked[sel];
@@ -347,31 +564,38 @@ __global__ __launch_bounds__(kScanThreads) void k_final(const float* __restrict_
             if (!PAIR) s->t_prune = st.prefix;
         }
     };
+    const bool wide = !st.done && st.in_bin > cap;
+    if (part != 0 && !wide) return;
     if (st.done) { finish(); return; }
-    const unsigned int n = st.in_bin;   // (every key of the digit is in the list, or there is none)
-    const bool listed = n <= cap;
+    auto counted_where_listed = [&] {
+        uint4 c4 = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int c = 0; c < (PAIR ? kNextCopies : 1); ++c) {
+            const uint4 v = reinterpret_cast<const uint4*>(next_digits(s, sel, c))[t];
+            c4.x += v.x; c4.y += v.y; c4.z += v.z; c4.w += v.w;
+        }
+        return c4;
+    };
+    if (wide) {
+        pick_next(st, counted_where_listed(), kDigitBits, kDigitShift - kDigitBits, wave_sum, cur);
+        if (st.done ? part == 0 : finish_wide(st, sel, part, parts, W, mask, grad, remains, N, d_in, &s->arrived[sel],
+                                              reinterpret_cast<unsigned int*>(sel == 1 ? candB : candA), h))
+            finish();
+        return;
+    }
+    const unsigned int n = st.in_bin;   // every key of the digit is in the list
     const unsigned long long* const list = sel == 1 ? candB : candA;
     auto each = [&](auto f) {
-        if (listed) {
 #pragma unroll 1
-            for (unsigned int i0 = t; 2 * i0 < n; i0 += kAhead * kScanThreads) {   // two keys per load
-                ulonglong2 key[kAhead];
+        for (unsigned int i0 = t; 2 * i0 < n; i0 += kAhead * kScanThreads) {   // two keys per load
+            ulonglong2 key[kAhead];
 #pragma unroll
-                for (int j = 0; j < kAhead; ++j) key[j] = reinterpret_cast<const ulonglong2*>(list)[min(i0 + j * kScanThreads, (n - 1u) / 2u)];
+            for (int j = 0; j < kAhead; ++j) key[j] = reinterpret_cast<const ulonglong2*>(list)[min(i0 + j * kScanThreads, (n - 1u) / 2u)];
 #pragma unroll
-                for (int j = 0; j < kAhead; ++j) {
-                    const unsigned int i = 2 * (i0 + j * kScanThreads);
-                    if (i < n) f(key[j].x);
-                    if (i + 1 < n) f(key[j].y);
-                }
-            }
-        } else {
-            for (unsigned long long i = t; i < N; i += kScanThreads) {
-                const unsigned int ii = (unsigned int)i;
-                const bool kept = mask[ii] != 0;
-                if (kept != (sel != 1)) continue;
-                if (sel == 2 && remains[ii / (unsigned)d_in] == 0) continue;
-                f(sel == 1 ? key_large_first(mag_bits(grad[ii]), ii) : key_small_first(mag_bits(W[ii]), ii));
+            for (int j = 0; j < kAhead; ++j) {
+                const unsigned int i = 2 * (i0 + j * kScanThreads);
+                if (i < n) f(key[j].x);
+                if (i + 1 < n) f(key[j].y);
             }
         }
     };
@@ -398,53 +622,25 @@ __global__ __launch_bounds__(kScanThreads) void k_final(const float* __restrict_
             return;
         }
         const int bits = min(kDigitBits, shift), next = shift - bits;
-        uint4 c4 = {0u, 0u, 0u, 0u};   // thread t has digits 4t .. 4t + 3
-        if (PAIR && listed && shift == kDigitShift) {   // counted where the list was made
-#pragma unroll
-            for (int c = 0; c < kNextCopies; ++c) {
-                const uint4 v = reinterpret_cast<const uint4*>(s->next[sel][c])[t];
-                c4.x += v.x; c4.y += v.y; c4.z += v.z; c4.w += v.w;
-            }
+        uint4 c4;
+        if (PAIR && shift == kDigitShift) {   // counted where the list was made
+            c4 = counted_where_listed();
         } else {
             for (int i = t; i < kDigits; i += kScanThreads) h[i] = 0;
             __syncthreads();
             each([&](unsigned long long k) {
-                if ((k >> shift) == st.prefix) atomicAdd(&h[(unsigned int)(k >> next) & ((1u << bits) - 1u)], 1u);
+                add_by_digit((k >> shift) == st.prefix, (unsigned int)(k >> next) & ((1u << bits) - 1u),
+                             [&](unsigned int d, unsigned int c) { atomicAdd(&h[d], c); });
             });
             __syncthreads();
             c4 = reinterpret_cast<const uint4*>(h)[t];
         }
-        // keys in the digits above a thread's: in its wavefront's higher lanes and the higher wavefronts
-        const unsigned int mine = c4.x + c4.y + c4.z + c4.w, incl = wave_prefix(mine);
-        if (lane == 63) wave_sum[t >> 6] = incl;
-        __syncthreads();
-        unsigned int beyond = (unsigned)__builtin_amdgcn_readlane((int)incl, 63) - incl;
-        for (int w = kScanThreads / 64 - 1; w > (t >> 6); --w) beyond += wave_sum[w];
-        const unsigned int want = (unsigned)st.k_rem;
-        if (beyond < want && beyond + mine >= want) {
-            unsigned int above = beyond, in_bin = c4.w;
-            int digit = 4 * t + 3;
-            if (above + in_bin < want) { above += c4.w; in_bin = c4.z; --digit; }
-            if (digit == 4 * t + 2 && above + in_bin < want) { above += c4.z; in_bin = c4.y; --digit; }
-            if (digit == 4 * t + 1 && above + in_bin < want) { above += c4.y; in_bin = c4.x; --digit; }
-            SelState c = st;
-            c.k_rem = want - above;
-            c.prefix = (c.prefix << bits) | (unsigned)digit;
-            c.in_bin = in_bin;
-            if (c.k_rem == in_bin || next == 0) {
-                c.prefix <<= next;
-                c.done = 1;
-            }
-            cur = c;
-        }
-        __syncthreads();
-        st = cur;
+        pick_next(st, c4, bits, next, wave_sum, cur);
         shift = next;
-        __syncthreads();   // (cur is written again by the next pass)
         if (st.done) { finish(); return; }
     }
 }
-static_assert(kDigits == 4 * kScanThreads, "four digits per thread");
+static_assert((kLast + 4 + kScanThreads / 64 + kWideParts) <= kDigits, "finish_wide's LDS");
 
 // Four consecutive columns of a row, at any alignment of the row: the last group of a row that does not end on a group
 // boundary reads the row's last four columns and owns only those its neighbour does not have.
@@ -480,6 +676,8 @@ __global__ __launch_bounds__(256) void k_row_salient(const float* __restrict__ W
                                                      const float* __restrict__ grad, int d_out, int d_in, int k, int gamma_percent,
                                                      UpdateScratch* __restrict__ s, int* __restrict__ remains) {
     __shared__ int wg_stay, wg_ablated;
+    __shared__ __align__(16) unsigned int gone[kDigits];
+    bool ablates = false;
     const int lane = threadIdx.x & 63;
     const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (threadIdx.x == 0) { wg_stay = 0; wg_ablated = 0; }
@@ -535,21 +733,36 @@ __global__ __launch_bounds__(256) void k_row_salient(const float* __restrict__ W
             if (h > 0 && !ablated) atomicAdd(&wg_stay, 1);
             remains[r] = h > 0 && !ablated ? 1 : 0;
         }
-        if (ablated) {
-            const int copy = blockIdx.x % kHistCopies;
-            for (int c = lane; c < d_in; c += 64) {
-                if (mask[row0 + c] == 0) continue;
-                const unsigned int d = digit_small_first(mag_bits(W[row0 + c]));
-                atomicSub(&s->hist[0][copy][d], 1u);   // (modulo 2^32 per copy: the copies' sum is what counts)
-                atomicSub(&s->coarse[0][copy][d / kFine], 1u);
-            }
-        }
+        ablates = ablated;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         if (wg_stay) atomicAdd(&s->cnt_remaining[blockIdx.x % kCountCopies], (unsigned int)wg_stay);
         if (wg_ablated) atomicAdd(&s->cnt_ablated[blockIdx.x % kCountCopies], (unsigned int)wg_ablated);
     }
+    if (wg_ablated == 0) return;
+    // The ablated rows' digits are counted in LDS first: an atomic in memory for every kept weight of theirs (and one for the coarse
+    // digit) was most of the update where many neurons go (768 x 3072: 887 of 3072 ablated 104 us, 2969 of them 283).
+    for (int i = threadIdx.x; i < kDigits / 4; i += 256) reinterpret_cast<uint4*>(gone)[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    if (ablates)
+        for (int c = lane; c < d_in; c += 64)
+            if (mask[row0 + c] != 0) atomicAdd(&gone[digit_small_first(mag_bits(W[row0 + c]))], 1u);
+    __syncthreads();
+    const int copy = blockIdx.x % kHistCopies;   // (modulo 2^32 per copy: the copies' sum is what counts)
+#pragma unroll
+    for (int j = 0; j < kDigits / 256; ++j) {
+        const unsigned int n = gone[threadIdx.x + 256 * j];
+        if (n) atomicSub(&s->hist[0][copy][threadIdx.x + 256 * j], n);
+    }
+    static_assert(kCoarse == 256, "a coarse count per thread");
+    unsigned int n = 0;
+#pragma unroll
+    for (int j = 0; j < kFine / 4; ++j) {
+        const uint4 v = reinterpret_cast<const uint4*>(gone)[threadIdx.x * (kFine / 4) + j];
+        n += v.x + v.y + v.z + v.w;
+    }
+    if (n) atomicSub(&s->coarse[0][copy][threadIdx.x], n);
 }
 
 // Steps 6 (applied) and 7.  WPR wavefronts per row (1, four rows to a workgroup, or 4); lane l of them holds columns
@@ -741,11 +954,12 @@ __global__ void k_update_report_empty(long long* __restrict__ report) {
     if (threadIdx.x < 4) report[threadIdx.x] = 0;
 }
 
-// Keys per candidate list: a sixteenth of the layer, at least 4096 (a list holds the keys that share the threshold's first
-// digit: about a percent of real-valued contents, three at most; constant contents do without).
+// Keys per candidate list: a thirty-second of the layer, at least 4096.  A list holds the keys that share the threshold's first digit: about
+// a percent of real-valued contents, three at most; more are contents of few magnitudes, which do better without a list (7 levels of
+// weights and gradients on 768 x 3072, 5 % of the layer in one digit: 749 us with a list).
 static size_t cand_capacity(int32_t d_out, int32_t d_in) {
     const size_t n = (d_out > 0 && d_in > 0) ? (size_t)d_out * (size_t)d_in : 0;
-    const size_t c = n / 16;
+    const size_t c = n / 32;
     return c < 4096 ? 4096 : c / 2 * 2;   // (even: the second list is 16-byte aligned too)
 }
 static size_t update_head_bytes(int32_t d_out) {
@@ -795,14 +1009,18 @@ srigl_status srigl_mask_update(const float* W, const uint8_t* mask, const float*
     hipLaunchKernelGGL(k_hist, dim3(blocks), dim3(kScanThreads), 0, st, W, mask, grad, N, n4, s);
     hipLaunchKernelGGL(k_collect<true>, dim3(blocks), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, n4, d_in, (unsigned long long)K_upd, s,
                        candA, candB, cap);
-    hipLaunchKernelGGL(k_final<true>, dim3(2), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, d_in, s, candA, candB, cap,
+    // Workgroups of k_final that stand by for a selection without a list (otherwise their start is all they cost: 45.0 us with 64, 44.7 with
+    // none on 768 x 3072).  With 16 / 32 / 64 of them an update of that layer with zero gradients takes 127 / 92 / 79 us; on 4096 x 4097 64 take
+    // 330 us and 256 285, on smaller layers 256 have too little to do each (1953 x 4096: 276, with 64 212).
+    const unsigned int parts = N < (1u << 24) ? std::min(blocks, 64u) : (unsigned)kWideParts;
+    hipLaunchKernelGGL(k_final<true>, dim3(2 * parts), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, d_in, s, candA, candB, cap,
                        (unsigned long long)K_upd, (long long)budget, report);
     const dim3 row_grid((unsigned)((d_out + 3) / 4));
     hipLaunchKernelGGL(k_row_salient, row_grid, dim3(256), 0, st, W, mask, grad, d_out, d_in, k, gamma_percent, s, remains);
     // (most updates ablate nothing and this launch returns at once: it takes few workgroups, whose start is then all it costs)
     hipLaunchKernelGGL(k_collect<false>, dim3(std::min(blocks, 64u)), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, n4, d_in, (unsigned long long)K_upd, s,
                        candA, candB, cap);
-    hipLaunchKernelGGL(k_final<false>, dim3(1), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, d_in, s, candA, candB, cap,
+    hipLaunchKernelGGL(k_final<false>, dim3(parts), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, d_in, s, candA, candB, cap,
                        (unsigned long long)K_upd, (long long)budget, report);
 #define SRIGL_ROW_UPDATE(NQ, WPR)                                                                                                      \
     hipLaunchKernelGGL((k_row_update<NQ, WPR>), WPR == 1 ? row_grid : dim3((unsigned)d_out), dim3(256), 0, st, W, mask, grad, d_out, d_in, remains, \
