@@ -23,8 +23,8 @@
 // structured.hip.  A wavefront clears and fills whole blocks: no barrier between the two, the LDS serves one wavefront's requests
 // in order.
 //
-// A stored zero times an activation that is not finite is not a term of the layer.  A sum that is not finite is therefore
-// computed again from the row's own terms when it is stored; finite sums cannot have met such an activation.
+// A stored zero times an activation that is not finite is not a term of the layer, but spoils the sum.  The rows of a tile with a sum that is
+// not finite are therefore computed again from the terms (mend_rows); finite sums cannot have met such an activation.
 #include "mma_tile.h"
 #include <algorithm>
 #include <cmath>
@@ -160,25 +160,106 @@ struct BlockedArgs {
     int n_base, tiles_m, tiles_n;   // of the launch: its first stored row, its tiles
 };
 
-// The sum of one output from its own terms.
-__device__ __forceinline__ float sum_terms(const BlockedArgs& p, int m, int s) {
-    const uint16_t* xr = p.x + (size_t)m * p.d_in;
-    float acc = 0.0f;
-    for (int k = 0; k < p.K; ++k) {
-        const size_t at = (size_t)s * p.K + k;
-        const uint32_t c = p.idx_u16 ? static_cast<const uint16_t*>(p.idx)[at] : static_cast<const uint32_t*>(p.idx)[at];
-        acc = fmaf(bf16_bits_to_float(p.W_c[at]), bf16_bits_to_float(xr[min(c, (uint32_t)p.d_in - 1)]), acc);
+// The rows of a tile whose bits are set in `spoiled`, computed again from the neurons' own terms: eight rows of x at a time stand in LDS,
+// interleaved, so that a term's eight factors come with one 16-byte read; a wavefront takes a neuron, its lanes the terms.  `area` bytes of
+// LDS at smem are free (inputs wider than area / 16 columns go through it in runs, the sums so far waiting at `sums`, [bn][8]).
+// 4096 -> 16384 (13108 stored, K = 205) at batch 2048: 245 us as it is, 320 with one NaN in the batch, 3.4 ms with one in every row, whatever
+// else (the gathering kernel: 0.85 ms); with every sum added up by one lane, term after term from memory, 1.3 ms and 23 ms.  (Rewritten
+// operands through the matrix cores once more, four passes, took 2.8 ms for either, and its registers 3 to 7 % of every call.)
+constexpr int kMendRows = 8, kMendAhead = 4;   // rows at a time; loads of 64 terms in flight, for two neurons
+__device__ __forceinline__ void mend_rows(const BlockedArgs& p, unsigned char* smem, int area, float* sums, const uint32_t* spoiled, int bm, int bn, int m0, int n0) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), waves = blockDim.x >> 6;
+    const int stored = min(bn, p.n_active - n0), width = area / (2 * kMendRows) / 64 * 64;
+    const int g = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);   // the row whose sum ends up in this lane
+    for (int done = 0;; done += kMendRows) {
+        // the next rows: number `done` and on of the set bits
+        int rows[kMendRows], n = 0, seen = 0;
+        for (int w = 0; w < bm / 32; ++w)
+            for (uint32_t bits = spoiled[w]; bits; bits &= bits - 1) {
+                if (seen >= done && n < kMendRows) {
+                    const int r = m0 + 32 * w + __ffs(bits) - 1;
+#pragma unroll
+                    for (int q = 0; q < kMendRows; ++q) rows[q] = q >= n ? r : rows[q];   // (rows that are missing repeat the last one)
+                    ++n;
+                }
+                ++seen;
+            }
+        if (n == 0) return;
+        for (int c0 = 0; c0 < p.d_in; c0 += width) {
+            const int cols = min(width, p.d_in - c0);
+            __syncthreads();   // the run before has been read (at first: the tile)
+            for (int c = tid; c < cols; c += blockDim.x) {
+                uint32_t h[kMendRows];
+#pragma unroll
+                for (int q = 0; q < kMendRows; ++q) h[q] = p.x[(size_t)rows[q] * p.d_in + c0 + c];
+                *reinterpret_cast<uint4*>(smem + 16 * (size_t)c) = make_uint4(h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16);
+            }
+            __syncthreads();
+            for (int s0 = 2 * wv; s0 < stored; s0 += 2 * waves) {
+                float acc[2][kMendRows];
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int q = 0; q < kMendRows; ++q) acc[t][q] = 0.0f;
+                for (int k0 = 0; k0 < p.K; k0 += 64 * kMendAhead) {
+                    float w[2][kMendAhead];
+                    int col[2][kMendAhead];
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int u = 0; u < kMendAhead; ++u) {
+                            const int k = k0 + 64 * u + lane;
+                            const size_t at = (size_t)(n0 + min(s0 + t, stored - 1)) * p.K + min(k, p.K - 1);
+                            w[t][u] = bf16_bits_to_float(p.W_c[at]);
+                            const uint32_t c = p.idx_u16 ? static_cast<const uint16_t*>(p.idx)[at] : static_cast<const uint32_t*>(p.idx)[at];
+                            col[t][u] = k < p.K ? (int)min(c, (uint32_t)p.d_in - 1u) - c0 : -1;
+                        }
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int u = 0; u < kMendAhead; ++u)
+                            if (col[t][u] >= 0 && col[t][u] < cols) {
+                                const uint4 v = *reinterpret_cast<const uint4*>(smem + 16 * (size_t)col[t][u]);
+                                const uint32_t pair[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                                for (int q = 0; q < 4; ++q) {
+                                    acc[t][2 * q] = fmaf(w[t][u], __uint_as_float(pair[q] << 16), acc[t][2 * q]);
+                                    acc[t][2 * q + 1] = fmaf(w[t][u], __uint_as_float(pair[q] & 0xffff0000u), acc[t][2 * q + 1]);
+                                }
+                            }
+                }
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    float(&v)[kMendRows] = acc[t];
+#pragma unroll
+                    for (int half = kMendRows / 2, d = 32; half >= 1; half /= 2, d /= 2)   // half of the rows to the upper lanes, half to the lower
+#pragma unroll
+                        for (int q = 0; q < half; ++q) {
+                            const bool up = (lane & d) != 0;
+                            v[q] = (up ? v[q + half] : v[q]) + __shfl_xor(up ? v[q] : v[q + half], d, 64);
+                        }
+                    float sum = v[0];
+#pragma unroll
+                    for (int d = 4; d >= 1; d /= 2) sum += __shfl_xor(sum, d, 64);
+                    const int s = s0 + t;
+                    if (s >= stored || (lane & 7) != 0) continue;
+                    if (c0 > 0) sum += sums[s * kMendRows + g];
+                    if (c0 + cols < p.d_in) {
+                        sums[s * kMendRows + g] = sum;
+                        continue;
+                    }
+                    const int out = p.active ? p.active[n0 + s] : n0 + s;
+                    if (g < n && out >= 0 && out < p.d_out) {
+                        int row = rows[0];
+#pragma unroll
+                        for (int q = 1; q < kMendRows; ++q) row = q == g ? rows[q] : row;
+                        p.y[(size_t)row * p.d_out + out] = apply_act(sum + (p.bias ? p.bias[out] : 0.0f), p.act);
+                    }
+                }
+            }
+        }
     }
-    return acc;
 }
-
-// what store_tile writes
-struct Finish {
-    const BlockedArgs& p;
-    static constexpr bool kRepairs = true;
-    __device__ int activation() const { return p.act; }
-    __device__ float repaired(int m, int s) const { return sum_terms(p, m, s); }
-};
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 struct __attribute__((packed, aligned(2))) Half4 { uint32_t a, b; };
@@ -358,6 +439,9 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
         return *reinterpret_cast<const bf16x8_t*>(wstages + (it & 1) * WSTAGE + (kk >> 2) * (BN * 128) + (wn * WTN + j * 32) * 128 + frag_off[kk & 3]);
     };
 
+    uint32_t* const spoiled = reinterpret_cast<uint32_t*>(table + EpiLayout<BN, WGM>::TABLE_BYTES);
+    if (tid < BM / 32) spoiled[tid] = 0u;
+
     // ---- prologue (what the epilogue needs from memory is fetched here too, beside the first requests)
     const TileColumns cols = tile_columns(n0, BN, p.active, p.n_active, p.d_out);
     issue_list(0);
@@ -409,13 +493,21 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
 
     wait_loads<0>();   // the repeated last list may still be landing
     lds_barrier();
-    store_tile<BM, BN, WGM, WGN>(smem, table, true, acc, cols, m0, n0, p.B, p.active, p.bias, p.d_out, p.y, Finish{p});
+    store_tile<BM, BN, WGM, WGN, true>(smem, table, true, acc, cols, m0, n0, p.B, p.active, p.bias, p.d_out, p.y, p.act, spoiled);
+    lds_barrier();
+    uint32_t any = 0;
+#pragma unroll
+    for (int w = 0; w < BM / 32; ++w) any |= spoiled[w];
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)any) != 0, 0)) {
+        constexpr int SUMS = BN * kMendRows * 4, AREA = (int)blocked_table_at<UA, BM, BN, WGM, WGN, CC>() - SUMS;
+        mend_rows(p, smem, AREA, reinterpret_cast<float*>(smem + AREA), spoiled, BM, BN, m0, n0);   // (its barriers wait for the stores above)
+    }
 }
 
 template <int UA, bool DIRECT, int BM, int BN, int WGM, int WGN, int CC>
 static srigl_status launch_tile(const BlockedArgs& args, int n_rows, hipStream_t st) {
     auto kern = k_fwd_blocked<UA, DIRECT, BM, BN, WGM, WGN, CC>;
-    constexpr size_t lds = blocked_table_at<UA, BM, BN, WGM, WGN, CC>() + EpiLayout<BN, WGM>::TABLE_BYTES;
+    constexpr size_t lds = blocked_table_at<UA, BM, BN, WGM, WGN, CC>() + EpiLayout<BN, WGM>::TABLE_BYTES + BM / 8;
     static_assert(lds <= kLdsMax, "LDS");
     static LdsLimit lds_limit;
     if (lds_limit.ensure(kern, lds) != SRIGL_OK) return SRIGL_ERR_HIP;

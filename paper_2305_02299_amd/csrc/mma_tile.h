@@ -108,16 +108,16 @@ __device__ __forceinline__ void fill_table(unsigned char* at, int cc, const Tile
 // of y is touched twice and none is left out.  (A 256 x 256 tile's epilogue took 28 us with one value at a time, each behind a read of
 // a column table and one of the tile, and 10 with 4-way bank conflicts of lanes that gathered four columns each.)
 // The LDS must be free (the caller has waited for its own loads into it and passed a barrier); have_table: the first window's tables
-// stand at table_at already.  finish.repaired(m, s): the sum to use where one is not finite (Finish::kRepairs); finish.activation():
-// an activation applied to every value, or SRIGL_ACT_NONE.  Both are rare or slow paths and written once, as loops over values in
-// LDS: inlined for each of a lane's 16 values they made the epilogue kilobytes of code that every workgroup fetched anew.
+// stand at table_at already.  act: the activation applied to every value, written once, as a loop over values in LDS: inlined for each of
+// a lane's 16 values it made the epilogue kilobytes of code that every workgroup fetched anew.  SPOILED: the tile's rows with a sum
+// that is not finite get their bits set in `spoiled` (BM of them, in LDS); what is written for them is up to the caller to mend.
 // With that and the float4 rows a 768 -> 3072 layer in 256 x 256 tiles went from 36.4 to 32.3 us, 4096 -> 16384 at batch 2048 from 297 to
 // 279 in 128 x 128 tiles.  Narrow tiles put 2 or 4 rows into one LDS request (16 or 32 lanes each): with 64 lanes on a row 64 x 64
 // tiles took 11.5 us instead of 9.4 on 768 -> 3072 at batch 128.
-template <int BM, int BN, int WGM, int WGN, int TM, int TN, typename Finish>
+template <int BM, int BN, int WGM, int WGN, bool SPOILED, int TM, int TN>
 __device__ __forceinline__ void store_tile(unsigned char* smem, unsigned char* table_at, bool have_table, const f32x16_t (&acc)[TM][TN],
                                            const TileColumns& cols, int m0, int n0, int B, const int32_t* active, const float* bias,
-                                           int d_out, float* y, const Finish& finish) {
+                                           int d_out, float* y, int act, uint32_t* spoiled) {
     using EL = EpiLayout<BN, WGM>;
     constexpr int NWAVES = WGM * WGN, WTM = BM / WGM, WTN = BN / WGN, PITCH = EL::PITCH;
     // lanes that share a row (four columns each), rows per LDS request, runs of columns of a window
@@ -142,10 +142,10 @@ __device__ __forceinline__ void store_tile(unsigned char* smem, unsigned char* t
             fill_table<BN, WGM, NWAVES * 64>(table_at, cc, cols, n0, active, bias);
             __syncthreads();
         }
-        if (finish.activation() != SRIGL_ACT_NONE) {
+        if (act != SRIGL_ACT_NONE) {
             __syncthreads();
             for (int k = tid; k < wc; k += NWAVES * 64)
-                if (table[k] < 0) tbias[k] = apply_act(tbias[k], finish.activation());
+                if (table[k] < 0) tbias[k] = apply_act(tbias[k], act);
             __syncthreads();
         }
         int at[TN];        // this lane's columns in the window
@@ -196,17 +196,22 @@ __device__ __forceinline__ void store_tile(unsigned char* smem, unsigned char* t
 #pragma unroll
                         for (int j = 0; j < 4; ++j) {
                             if ((gaps >> (4 * run + j)) & 1) v[u][j] = 0.0f;
-                            else if (Finish::kRepairs) finite = finite && fabsf(v[u][j]) <= 3.4028234e38f;
+                            else if (SPOILED) finite = finite && fabsf(v[u][j]) <= 3.4028234e38f;
                         }
-                    if ((Finish::kRepairs && __any(!finite)) || finish.activation() != SRIGL_ACT_NONE) {
+                    if (SPOILED && __any(!finite)) {
+#pragma unroll 1
+                        for (int q = 0; q < 16; ++q) {
+                            const int k = k0 + (q & 3), mq = m + (q >> 2) * RPI, r = mq - m0;
+                            if (k < wc && table[k] >= 0 && mq < B && !(fabsf(t0[(q >> 2) * RPI * PITCH + (q & 3)]) <= 3.4028234e38f))
+                                atomicOr(&spoiled[r >> 5], 1u << (r & 31));
+                        }
+                    }
+                    if (act != SRIGL_ACT_NONE) {
 #pragma unroll 1
                         for (int q = 0; q < 16; ++q) {
                             const int k = k0 + (q & 3), mq = m + (q >> 2) * RPI;
                             float* const at_q = t0 + (q >> 2) * RPI * PITCH + (q & 3);
-                            if (k >= wc || table[k] < 0 || mq >= B) continue;
-                            float f = *at_q;
-                            if (Finish::kRepairs && !(fabsf(f) <= 3.4028234e38f)) f = finish.repaired(mq, n0 + table[k]) + tbias[k];
-                            *at_q = apply_act(f, finish.activation());
+                            if (k < wc && table[k] >= 0 && mq < B) *at_q = apply_act(*at_q, act);
                         }
 #pragma unroll
                         for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const float4_t*>(t0 + u * RPI * PITCH);

@@ -139,13 +139,6 @@ __device__ __forceinline__ void mma_block(f32x16_t& acc, const float4& a, const 
     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
 }
 
-// what store_tile writes: the sum plus the bias; the bias of an ablated neuron
-struct Plain {
-    static constexpr bool kRepairs = false;
-    __device__ constexpr int activation() const { return SRIGL_ACT_NONE; }
-    __device__ float repaired(int, int) const { return 0.0f; }
-};
-
 // BM x BN output tile per workgroup of WGM x WGN wavefronts; NS >= 2 LDS stages of SLAB (128 or 64) bytes of K per row.
 //
 // Schedule of one stage h (KSTEPS = SLAB / 32 MFMA steps): the fragments of step kk + 1 are requested before the MFMAs of
@@ -317,8 +310,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_structured_gemm(const T* __r
 
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // the re-issued last stages may still be landing in the ring
     __syncthreads();
-    store_tile<BM, BN, WGM, WGN>(smem, smem + EpiLayout<BN, WGM>::TILE_BYTES, false, acc, tile_columns(n0, BN, active, n_active, d_out), m0, n0, B,
-                                    active, bias, d_out, y, Plain());
+    store_tile<BM, BN, WGM, WGN, false>(smem, smem + EpiLayout<BN, WGM>::TILE_BYTES, false, acc, tile_columns(n0, BN, active, n_active, d_out), m0, n0, B,
+                                    active, bias, d_out, y, SRIGL_ACT_NONE, nullptr);
 }
 
 template <typename T, int BM, int BN, int WGM, int WGN, int NS, int SLAB, bool RAGGED>

@@ -195,3 +195,50 @@ def test_split_rows(first, second, columns, abl):
     for bad in (first | second << 4, first | second << 4 | 100 << 8, first | columns << 8, 5):
         with pytest.raises(B_.SriglError):
             B_.srigl_blocked_linear_fwd(*args, tile=bad)
+
+
+@pytest.mark.parametrize("tile", list(TILES))
+@pytest.mark.parametrize("d_in,d_out,K,B,abl", [(768, 300, 20, 300, 0.1), (770, 70, 300, 70, 0.0), (9001, 200, 130, 40, 0.2), (64, 700, 5, 9, 0.0)])
+def test_rows_with_sums_that_are_not_finite(d_in, d_out, K, B, abl, tile):
+    """Infinities of either sign, NaN, stored zeros and infinite weights, from one row to all of them: every sum is what its own terms give in
+    64 bits (the same infinity or a NaN, or the finite sum), others untouched; also behind an activation."""
+    L = si.make_layer(d_in, d_out, K, B, ablate_frac=abl, dtype="bf16", seed=d_in + 1)
+    W_c, idx, active = oracle_condensed(L)
+    n = len(active)
+    rng = np.random.default_rng(K)
+    W_c = W_c.copy()
+    W_c[rng.integers(0, n, 6), rng.integers(0, K, 6)] = [0, 0x8000, 0, 0x7f80, 0xff80, 0x7fc0]
+    W_c[-1, :] = 0
+    ix, Wd, act = dev(idx.astype(np.uint16)) if d_in == 768 else dev(idx), dev(W_c), dev(active) if n < d_out else None
+    blk = blocked(Wd, ix, dev(oracle_seg(idx, d_in)), d_in)
+    wide = lambda bits: (bits.astype(np.uint32) << 16).view(np.float32).astype(np.float64)   # noqa: E731
+    w64 = wide(W_c)
+    for name in ("one", "nine rows", "a column", "every value", "none"):
+        x = L.x_bf16.copy()
+        bad = np.array([0x7f80, 0xff80, 0x7fc0, 0x7f80], np.uint16)
+        if name == "one":
+            x[B - 1, d_in // 2] = 0x7f80
+        elif name == "nine rows":
+            for r in range(0, min(B, 9)):
+                x[r * (B // 9), rng.integers(0, d_in, 4)] = bad
+        elif name == "a column":
+            x[:, idx[0, 0]] = 0x7f80
+        elif name == "every value":
+            x[:] = np.where(rng.random(x.shape) < 0.01, 0x7fc0, 0x7f80)
+        x64 = wide(x)
+        with np.errstate(all="ignore"):
+            want = np.stack([(w64[s] * x64[:, idx[s]]).sum(axis=1) for s in range(n)], axis=1) + L.bias[active].astype(np.float64)
+            scale = np.stack([np.abs(np.where(np.isfinite(w64[s] * x64[:, idx[s]]), w64[s] * x64[:, idx[s]], 0)).sum(axis=1) for s in range(n)], axis=1) + 1
+        for fn in (B_.ACT_NONE, B_.ACT_RELU):
+            y = torch.full((B, d_out), 5.0, device="cuda")
+            B_.srigl_blocked_linear_fwd(dev(x), B, d_in, blk, Wd, ix, act, n, K, dev(L.bias), d_out, y, act=fn, tile=TILES[tile])
+            yh = host(y).astype(np.float64)
+            ref = want if fn == B_.ACT_NONE else np.fmax(want, 0)   # (the activation of a NaN is 0)
+            got = yh[:, active]
+            assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref)), (name, fn)
+            assert (np.sign(got[np.isinf(ref)]) == np.sign(ref[np.isinf(ref)])).all()
+            ok = np.isfinite(ref)
+            assert (np.abs(got[ok] - ref[ok]) <= 2e-6 * scale[ok]).all()   # exact products, fp32 sums of at most 300
+            gone = np.setdiff1d(np.arange(d_out), active)
+            flat = L.bias[gone] if fn == B_.ACT_NONE else np.maximum(L.bias[gone], 0)
+            assert np.array_equal(host(y)[:, gone], np.tile(flat, (B, 1)))
