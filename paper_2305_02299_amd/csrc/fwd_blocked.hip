@@ -500,7 +500,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
     for (int w = 0; w < BM / 32; ++w) any |= spoiled[w];
     if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)any) != 0, 0)) {
         constexpr int SUMS = BN * kMendRows * 4, AREA = (int)blocked_table_at<UA, BM, BN, WGM, WGN, CC>() - SUMS;
-        mend_rows(p, smem, AREA, reinterpret_cast<float*>(smem + AREA), spoiled, BM, BN, m0, n0);   // (its barriers wait for the stores above)
+        wait_loads<0>();   // the stores above have reached memory; the function starts with a barrier
+        mend_rows(p, smem, AREA, reinterpret_cast<float*>(smem + AREA), spoiled, BM, BN, m0, n0);
     }
 }
 

@@ -109,11 +109,12 @@ __device__ __forceinline__ void fill_table(unsigned char* at, int cc, const Tile
 // a column table and one of the tile, and 10 with 4-way bank conflicts of lanes that gathered four columns each.)
 // The LDS must be free (the caller has waited for its own loads into it and passed a barrier); have_table: the first window's tables
 // stand at table_at already.  act: the activation applied to every value, written once, as a loop over values in LDS: inlined for each of
-// a lane's 16 values it made the epilogue kilobytes of code that every workgroup fetched anew.  SPOILED: the tile's rows with a sum
-// that is not finite get their bits set in `spoiled` (BM of them, in LDS); what is written for them is up to the caller to mend.
+// a lane's 16 values it made the epilogue kilobytes of code that every workgroup fetched anew.
 // With that and the float4 rows a 768 -> 3072 layer in 256 x 256 tiles went from 36.4 to 32.3 us, 4096 -> 16384 at batch 2048 from 297 to
 // 279 in 128 x 128 tiles.  Narrow tiles put 2 or 4 rows into one LDS request (16 or 32 lanes each): with 64 lanes on a row 64 x 64
 // tiles took 11.5 us instead of 9.4 on 768 -> 3072 at batch 128.
+// SPOILED: the tile's rows with a sum that is not finite get their bits set in `spoiled` (BM of them, in LDS); what has been written for
+// them is up to the caller to mend.
 template <int BM, int BN, int WGM, int WGN, bool SPOILED, int TM, int TN>
 __device__ __forceinline__ void store_tile(unsigned char* smem, unsigned char* table_at, bool have_table, const f32x16_t (&acc)[TM][TN],
                                            const TileColumns& cols, int m0, int n0, int B, const int32_t* active, const float* bias,
