@@ -150,7 +150,18 @@ def test_rowlane_launch_shapes(tuning):
                                      (768, 40, 8, 17, 0.0), (1024, 50, 615, 33, 0.2)):
         L = si.make_layer(d_in, d_out, K, B, ablate_frac=abl, seed=77)
         ran = check_layer(L, B_.FWD_ROWLANE, tuning, unsupported_ok=True)
-        assert ran is not None or d_in % 16 != 0     # only the ragged-width layer may be refused (slow staging: H = R = 1)
+        # rows of any length in every shape but the 16-byte reads of four rows per lane, which need whole 16-column units
+        assert (ran is not None) == (d_in % 16 == 0 or tuning.get("rows_per_lane") != 4)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(1, 1), (1, 2), (1, 4), (2, 1), (2, 2), (2, 4)])
+@pytest.mark.parametrize("d_in,B", [(1000, 37), (3001, 70), (2047, 257), (97, 33), (1, 5), (7, 130), (1023, 64)])
+def test_rowlane_rows_of_any_length_and_alignment(d_in, B, shape, dtype):
+    """Rows that are no whole staging units and start at any element: the last columns, and batches whose last tile is part empty."""
+    L = si.make_layer(d_in, 90, max(1, d_in // 12), B, ablate_frac=0.1, dtype=dtype, seed=d_in + B)
+    for tuning in ({}, {"waves": 5, "neurons_per_wave": 3, "chunk_cols": 64}, {"waves": 16, "neurons_per_wave": 1, "chunk_cols": 192}):
+        assert check_layer(L, B_.FWD_ROWLANE, dict(tuning, rows_per_lane=shape[0], term_slices=shape[1]), unsupported_ok=True) is not None
 
 
 @pytest.mark.parametrize("tuning", [

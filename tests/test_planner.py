@@ -219,3 +219,20 @@ def test_every_plan_is_one_the_kernels_accept():
         q = B_.srigl_fwd_plan_query(B, d_in, n_active, K, d_out, dtype_code=dtype, has_active=(n_active != d_out), algo=p["algo"],
                                     tuning=forced)
         assert q == p, (B, d_in, d_out, n_active, K, p, q)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_batched_tile_shapes_take_rows_of_any_length(dtype):
+    """Every shape of one or two rows per lane is planned at any width; four rows per lane only where rows are whole units of 16 columns."""
+    for d_in in (1, 3, 15, 16, 17, 97, 100, 777, 1000, 1023, 2047, 3001, 4095):
+        for rows_per_lane in (1, 2, 4):
+            for term_slices in (1, 2, 4) if rows_per_lane < 4 else (2, 4):
+                tuning = dict(rows_per_lane=rows_per_lane, term_slices=term_slices)
+                plan = lambda: B_.srigl_fwd_plan_query(70, d_in, 90, max(1, d_in // 12), 100, dtype, True, True, algo=B_.FWD_ROWLANE, tuning=tuning)   # noqa: E731
+                if rows_per_lane == 4 and d_in % 16:
+                    with pytest.raises(B_.SriglError) as e:
+                        plan()
+                    assert e.value.status == B_.ERR_UNSUPPORTED
+                else:
+                    p = plan()
+                    assert p["algo"] == B_.FWD_ROWLANE and (p["rows_per_lane"], p["term_slices"]) == (rows_per_lane, term_slices)
