@@ -285,6 +285,10 @@ PyObject* condense(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
         const int32_t d_out = (int32_t)mask->size(0), d_in = (int32_t)mask->size(1), K = int32(a[2]);
         const bool want_seg = PyObject_IsTrue(a[3]) == 1, want_packed = PyObject_IsTrue(a[4]) == 1;
         const srigl_dtype wt = dtype_of(*W);
+        const c10::hip::HIPStream st = c10::hip::getCurrentHIPStream();
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st.stream(), &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)
+            fail(PyExc_RuntimeError, "the report is waited for, which a captured stream cannot be (srigl_condense can)");
         const int64_t k = K > 0 ? K : 0;
         const size_t ws_bytes = srigl_workspace_bytes(d_out);
         at::Tensor W_c = fresh({d_out, k}, W->scalar_type(), *W), idx = fresh({d_out, k}, at::kInt, *W);
@@ -297,7 +301,6 @@ PyObject* condense(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
         srigl_report* rep = static_cast<srigl_report*>(report.data_ptr());
         constexpr int32_t kPending = -7;
         __atomic_store_n(&rep->status, kPending, __ATOMIC_RELEASE);
-        const c10::hip::HIPStream st = c10::hip::getCurrentHIPStream();
         void *wcp = W_c.data_ptr(), *sgp = want_seg ? seg.data_ptr() : nullptr, *pkp = want_packed ? packed.data_ptr() : nullptr;
         srigl_status rc;
         int32_t status = kPending;

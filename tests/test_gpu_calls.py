@@ -64,3 +64,20 @@ def test_sizes_in_any_form_that_int_takes():
         outs.append((mo, Wo, rep))
     for other in outs[1:]:
         assert all(torch.equal(a, b) for a, b in zip(outs[0], other))
+
+
+def test_condensing_refuses_a_captured_stream():
+    """The call waits for its report: under capture it says so, before it has put anything into the graph."""
+    from paper_2305_02299_amd import condense_layer
+    L = si.make_layer(64, 12, 5, 3, seed=45)
+    W, mask = dev(L.W), dev(L.mask)
+    y = torch.zeros(4, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        y.add_(1)
+        with pytest.raises(RuntimeError, match="captured"):
+            condense_layer(W, mask, 5)
+    for _ in range(3):
+        graph.replay()
+    torch.cuda.synchronize()
+    assert (y == 3).all() and condense_layer(W, mask, 5).n_active == 12
