@@ -242,3 +242,36 @@ def test_rows_with_sums_that_are_not_finite(d_in, d_out, K, B, abl, tile):
             gone = np.setdiff1d(np.arange(d_out), active)
             flat = L.bias[gone] if fn == B_.ACT_NONE else np.maximum(L.bias[gone], 0)
             assert np.array_equal(host(y)[:, gone], np.tile(flat, (B, 1)))
+
+
+def test_layer_call_without_memory_for_the_copy():
+    """The layer's call needs 4 bytes per stored weight for itself where it takes the matrix cores; with no memory to be had it takes the kernel that
+    needs none."""
+    d_in, d_out, K, B = 1024, 8192, 200, 512
+    assert B_.srigl_blocked_tile_with_copy(B, d_in, d_out, K, d_out) != 0
+    L = si.make_layer(d_in, d_out, K, 8, dtype="bf16", seed=3)
+    layer = condense_layer(dev(L.W_bf16).view(torch.bfloat16), dev(L.mask), K, dev(L.bias))
+    x = dev(L.x_bf16).view(torch.bfloat16).repeat(B // 8, 1)
+    y, want = torch.empty((B, d_out), device="cuda"), layer.forward(x)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    eaten = []
+    try:
+        torch.cuda.set_per_process_memory_fraction(torch.cuda.memory_reserved() / total)
+        for size in (8 << 20, 1 << 20, 1 << 18):
+            while True:
+                try:
+                    eaten.append(torch.empty((size,), dtype=torch.uint8, device="cuda"))
+                except torch.cuda.OutOfMemoryError:
+                    break
+        with pytest.raises(torch.cuda.OutOfMemoryError):
+            torch.empty((B_.srigl_blocked_bytes(d_out, K, d_in),), dtype=torch.uint8, device="cuda")
+        layer.forward(x, y)
+        torch.cuda.synchronize()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+        del eaten
+    y_ref, S = oracle.fwd(L.x_bf16, *oracle_condensed(L), L.bias, d_out, want_scale=True)
+    gate(host(y[:8]), y_ref, S, TOL_BF16)
+    gate(host(y), host(want), np.tile(S, (B // 8, 1)), 4e-6)
