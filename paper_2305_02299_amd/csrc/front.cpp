@@ -56,10 +56,14 @@ size_t bytes_of(PyObject* o) {
 }
 // What int() accepts (a float of a schedule, a numpy number, a tensor of one element), as in the ctypes calls.
 long long integer(PyObject* o) {
-    PyObject* made = PyLong_Check(o) ? nullptr : PyNumber_Long(o);
-    if (!made && !PyLong_Check(o)) throw Failed{};
-    const long long v = PyLong_AsLongLong(made ? made : o);
-    Py_XDECREF(made);
+    long long v = PyLong_AsLongLong(o);
+    if (v != -1 || !PyErr_Occurred()) return v;
+    if (!PyErr_ExceptionMatches(PyExc_TypeError)) throw Failed{};
+    PyErr_Clear();
+    PyObject* made = PyNumber_Long(o);
+    if (!made) throw Failed{};
+    v = PyLong_AsLongLong(made);
+    Py_DECREF(made);
     if (v == -1 && PyErr_Occurred()) throw Failed{};
     return v;
 }
