@@ -131,7 +131,7 @@ srigl_status srigl_pack_terms(const void* W_c, srigl_dtype w_dtype, const int32_
 
 /* srigl_condense for callers that cannot allocate device memory or pass scratch of their own: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and errors as srigl_condense
- * without `workspace`: the per-row counts and slots live in an array inside the library (8 bytes per row of W,
+ * without `workspace`: the rows' bits live in an array inside the library (8 bytes per row of W,
  * SRIGL_STATIC_MAX_ROWS rows: 512 KiB per GPU, held until the process ends).  d_out > SRIGL_STATIC_MAX_ROWS returns
  * SRIGL_ERR_CAPACITY and launches nothing.  The call allocates and frees nothing (the first call on a device looks the
  * array's address up, which is not an allocation).  Every call on a GPU uses that GPU's one array: calls that may

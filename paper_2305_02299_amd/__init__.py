@@ -1,7 +1,7 @@
 """Condensed constant fan-in sparse linear layer (SRigL inference hot path) for AMD MI355X.
 
 The product is libsrigl.so, a C-ABI library of hand-written gfx950 kernels declared in
-include/srigl.h; `binding` is its ctypes front end and `layer` a small convenience
+include/srigl.h; `binding` is its front end and `layer` a small convenience
 holder of the device buffers.  Importing the package loads the library and fails if it
 has not been built.
 """

@@ -11,8 +11,8 @@
 
 #include <mutex>
 
-// Scratch of srigl_condense_static (the condense call for callers that cannot allocate): the per-row counts and slots that
-// srigl_condense takes from its workspace argument.  One copy per GPU, held until the process ends.  The name is a host-side
+// Scratch of srigl_condense_static (the condense call for callers that cannot allocate): the rows' bits that srigl_condense
+// keeps in its workspace argument.  One copy per GPU, held until the process ends.  The name is a host-side
 // stand-in: kernels get the device address that hipGetSymbolAddress returns for the current device.
 static __device__ __align__(256) unsigned char scratch[2 * sizeof(int32_t) * (size_t)SRIGL_STATIC_MAX_ROWS + 256];
 
@@ -518,8 +518,8 @@ srigl_status srigl_condense_static(const void* W, srigl_dtype w_dtype, const uin
     void* ws = nullptr;
     const srigl_status st = scratch_on_current_device(&ws);
     if (st != SRIGL_OK) return st;
-    // every count and slot of rows [0, d_out) is written by the first two kernels before anything reads it, so what an
-    // earlier call left in the scratch is never seen and nothing has to be cleared
+    // every bit of rows [0, d_out) is written by the first kernel before the second reads it, so what an earlier call left in
+    // the scratch is never seen and nothing has to be cleared
     return condense_core(W, w_dtype, mask, d_out, d_in, K, cap_rows, W_c, idx, active, seg, packed, packed_bytes, ws, report_dev,
                          static_cast<hipStream_t>(stream));
 }

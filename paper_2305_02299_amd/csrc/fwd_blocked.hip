@@ -12,7 +12,7 @@
 //
 // The blocked copy (srigl_block_terms) holds the terms of 32 stored rows x 64 columns next to each other, each as the weight
 // beside its place in the LDS tile: 64 lanes fetch up to 256 of them with one 16-byte load each and store them with four 2-byte
-// LDS writes each.  (From the row-major copies the same kernel needed 327 us instead of 251 (233 by now) on 4096 -> 16384, 13108 stored
+// LDS writes each.  (From the row-major copies the same kernel needed 327 us instead of 251 (228 by now) on 4096 -> 16384, 13108 stored
 // rows, K = 205, 2048 batch rows: every row's few terms of a piece were a cache line and a lane's predicated writes of their own.)
 //
 // Pipeline (an iteration is CC pieces of 64 columns): x of the next iteration goes from memory straight into the other of two LDS
@@ -550,7 +550,8 @@ static srigl_status launch_plan(BlockedArgs& p, int code, hipStream_t st) {
 
 // Estimated time (us) of n stored rows in a tile shape.  Fits of measurements on 13 layers (200..4096 wide, 300..16192 stored rows,
 // 80-98 % sparse) at batches of 32 to 2048: a workgroup costs a fixed part (prologue, epilogue) and a part per iteration; a compute
-// unit holds one workgroup of the two large shapes, or two of the others, which then run slower each.
+// unit holds one workgroup of the two large shapes, or two of the others, which then run slower each.  On 168 later points (21 layers,
+// batches of 16 to 2048) the root mean square of the deviation is 9 to 12 % by shape, 2 % on average for the shape taken.
 static double blocked_tile_us(int tile, int B, int n, int chunks) {
     const int bn = blocked_tile_rows(tile), bm = bn == 192 ? 256 : bn;
     const double w = (double)((B + bm - 1) / bm) * ((n + bn - 1) / bn), it64 = (chunks + 1) / 2;
@@ -564,7 +565,7 @@ static double blocked_tile_us(int tile, int B, int n, int chunks) {
 
 // The tile code of smallest estimate.  Tiles of 256 x 256 are the most efficient ones, but 416 of them (13108 stored rows, batch 2048)
 // keep 256 compute units busy for two whole rounds where 1.6 would do.  So the large shapes are also tried for their full rounds
-// only, with the stored rows that are left in the shape that suits those.  Measured: that layer 240 -> 233 us (a part-filled round
+// only, with the stored rows that are left in the shape that suits those.  Measured: that layer 236 -> 228 us (a part-filled round
 // runs faster than a full one, so less than the count of rounds promises); 546 -> 16192 at batch 606 in 256 x 192 tiles 26 us, 28 in
 // 256 x 256, 34 in 128 x 128.  kSplitUs: what the second launch adds (its estimate counts a start of its own; the first one's last workgroups
 // and its power draw cost more).  Of 128 points (768- to 4096-wide, 2560 to 16000 stored rows, batches 600 to 2048) the shape taken is on

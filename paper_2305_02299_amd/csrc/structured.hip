@@ -497,7 +497,7 @@ srigl_status srigl_densify(const void* W_c, srigl_dtype w_dtype, const int32_t* 
 //                  + 4 B d_out / 4.5e6              (writing the result at HBM speed)
 srigl_representation srigl_choose_representation(int32_t B, int32_t d_in, int32_t n_active, int32_t K, int32_t d_out,
                                                  srigl_dtype dtype, float* est_condensed_us, float* est_structured_us) {
-    // On the same points (bf16) the form taken is 0.2 % slower than the faster one on average, at worst 6 %.  (While the condensed estimate
+    // On the same points (bf16) the form taken is 0.2 % slower than the faster one on average, at worst 7 %.  (While the condensed estimate
     // was the gathering kernels' alone: up to 20 %, and a dense copy of 107 MB on 4096 -> 16384 for what the estimate called 2.7 times.)
     struct Key { int32_t B, d_in, n_active, K, d_out, dtype; };
     struct Estimates { double cond, stru; };
