@@ -45,8 +45,8 @@ class CondensedLinear:
         that is better off with it.  After W_c or idx was written it has to be called again; the copy stays at its address, so that
         captured calls follow.  Nothing to do for fp32 weights, or without seg."""
         if self.seg is not None and B_._dtype_code(self.W_c) == B_.BF16 and 8 <= self.d_in <= 65536 and self.n_active and self.K:
-            if self.blocked is None:
-                need = B_.srigl_blocked_bytes(self.n_active, self.K, self.d_in)
+            need = B_.srigl_blocked_bytes(self.n_active, self.K, self.d_in)
+            if self.blocked is None or self.blocked.numel() < need:   # (more rows than it was made for: the one case of a new address)
                 self.blocked = torch.empty((need,), dtype=torch.uint8, device=self.W_c.device)
             B_.srigl_block_terms(self.W_c, self.idx, self.seg, self.n_active, self.K, self.d_in, self.blocked)
         return self

@@ -169,6 +169,7 @@ def test_prepare_is_what_the_call_reads_and_other_layers_need_none():
     layer.blocked = layer.blocked[:-16].clone()
     with pytest.raises(ValueError):
         layer.forward(x)
+    assert torch.equal(layer.prepare().forward(x), want) and layer.blocked.numel() == B_.srigl_blocked_bytes(D_OUT, K_, D_IN)
     plain = condense_layer(dev(L.W), mask, K_)      # fp32
     assert plain.prepare().blocked is None and condense_layer(W, mask, K_, want_seg=False).prepare().blocked is None
 
