@@ -34,6 +34,7 @@ EXPORTS = (
     "srigl_structured_linear_fwd_tile", "srigl_structured_split_plan", "srigl_structured_linear_fwd_split", "srigl_choose_representation",
     "srigl_condensed_linear_fwd_act", "srigl_fold_ablated_inputs", "srigl_mask_update_workspace_bytes", "srigl_mask_update",
     "srigl_compact_hidden_layer", "srigl_condensed_mlp_fwd", "srigl_narrow_idx", "srigl_condensed_linear_fwd_idx16", "srigl_csr_linear_fwd", "srigl_fwd_plan_query", "srigl_fwd_plan_query_algo",
+    "srigl_condensed_linear_fwd_tile", "srigl_fwd_tile_query",
     "srigl_blocked_bytes", "srigl_block_terms", "srigl_blocked_tile", "srigl_blocked_tile_with_copy", "srigl_blocked_linear_fwd",
 )
 
@@ -122,6 +123,11 @@ def _load() -> ctypes.CDLL:
     lib.srigl_fwd_plan_query_algo.restype = ctypes.c_int
     lib.srigl_fwd_plan_query_algo.argtypes = [i32, i32, i32, i32, i32, ctypes.c_int, i32, i32, ctypes.c_int, ctypes.POINTER(FwdTuning),
                                               ctypes.POINTER(FwdPlan)]
+    lib.srigl_condensed_linear_fwd_tile.restype = ctypes.c_int
+    lib.srigl_condensed_linear_fwd_tile.argtypes = [vp, ctypes.c_int, i32, i32, vp, ctypes.c_int, vp, i32, vp, i32, i32, vp, i32, vp,
+                                                    ctypes.c_int, i32, i32, i32, vp]
+    lib.srigl_fwd_tile_query.restype = i32
+    lib.srigl_fwd_tile_query.argtypes = [i32, i32, i32, i32, i32, ctypes.c_int, i32, i32, i32, ctypes.POINTER(i32)]
     lib.srigl_blocked_bytes.restype = sz
     lib.srigl_blocked_bytes.argtypes = [i32, i32, i32]
     lib.srigl_block_terms.restype = ctypes.c_int
@@ -291,6 +297,22 @@ def srigl_fwd_plan_query(B, d_in, n_active, K, d_out, dtype_code=F32, has_active
                                          int(bool(has_seg)), int(algo or FWD_AUTO), ctypes.byref(tn) if tn is not None else None,
                                          ctypes.byref(p)), "srigl_fwd_plan_query_algo")
     return {name: int(getattr(p, name)) for name, _ in FwdPlan._fields_}
+
+
+def srigl_condensed_linear_fwd_tile(x, B, d_in, W_c, idx, active, n_active, K, bias, d_out, y, act=None, tile_rows=0, rows_per_wave=0, xcd_order=0):
+    """The forward call in the whole-input batched kernel, in a tile of 16, 32 or 64 batch rows (0: the library's choice)."""
+    _check(lib.srigl_condensed_linear_fwd_tile(_ptr(x), _dtype_code(x), int(B), int(d_in), _ptr(W_c), _dtype_code(W_c), _ptr(idx),
+                                               32 if idx.dtype == torch.int32 else 16, _ptr(active), int(n_active), int(K), _ptr(bias), int(d_out),
+                                               _ptr(y), int(act or ACT_NONE), int(tile_rows), int(rows_per_wave), int(xcd_order), _stream()),
+           "srigl_condensed_linear_fwd_tile")
+
+
+def srigl_fwd_tile_query(B, d_in, n_active, K, d_out, dtype_code=F32, idx_bits=32, has_active=False, has_seg=True) -> tuple[int, int]:
+    """(tile rows, stored rows per wavefront) of the whole-input batched kernel where the library's own choice takes it, (0, 0) where not."""
+    rows = ctypes.c_int32(0)
+    tile = lib.srigl_fwd_tile_query(int(B), int(d_in), int(n_active), int(K), int(d_out), int(dtype_code), int(idx_bits), int(bool(has_active)),
+                                    int(bool(has_seg)), ctypes.byref(rows))
+    return int(tile), int(rows.value)
 
 
 def srigl_blocked_bytes(n_rows: int, K: int, d_in: int) -> int:

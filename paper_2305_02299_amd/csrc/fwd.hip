@@ -810,26 +810,31 @@ static srigl_fwd_algo choose_chunked_or_small(const FwdArgs& a) {
     return can_batch ? SRIGL_FWD_ROWLANE : SRIGL_FWD_GENERIC;
 }
 
-// Estimate (us) of the faster of the small-batch and the chunked batched kernel (above 2048 rows: of the batched one).
-static double chunked_or_small_estimate_us(const FwdArgs& a) {
+// Estimates (us) of the chunked batched kernel and of the small-batch kernel (1e30 where one does not run, or above 2048 rows).
+struct OtherEstimates { double batched, small; };
+static OtherEstimates other_estimates(const FwdArgs& a) {
     const RowlanePlan rp = plan_rowlane_by_estimate(a, nullptr);
-    const double batched = rp.ok ? rowlane_estimate_us(a, rp, true) : 1e30;
-    if (a.B > 2048 && rp.ok) return batched;
-    return std::min(batched, klane_estimate_us(a.B, a.d_in, a.n_active, a.K));
+    return {rp.ok ? rowlane_estimate_us(a, rp, true) : 1e30, a.B > 2048 && rp.ok ? 1e30 : klane_estimate_us(a.B, a.d_in, a.n_active, a.K)};
 }
-// The whole-input batched kernel is taken where its estimate is ahead of that one's (5 % behind still counts: over the
-// 238 launches its estimate was fitted to, that threshold left the least time on the table, 0.9 % against 7.5 % without
-// this kernel); below 32 batch rows never against the staged few-lanes shape of the small-batch kernel, which was placed by
-// measurement (at 32 rows this kernel measured ahead of it on rows of 77 terms, 6.1 / 5.4 against 7.5 / 6.4 us, and level on shorter ones).
-constexpr double kRowloopMargin = 0.95;
-srigl_fwd_algo choose_fwd_algo(const FwdArgs& a) {
+// The whole-input batched kernel is taken where its estimate is ahead of theirs, 5 % in its favour against the chunked kernel: over 304 points
+// (67 layers 112 to 2400 wide, fan-ins 6 to 384, both types, batches 8 to 2048) the call is then 0.8 % behind the fastest of the
+// three kernels on average; 1.0 % with 5 % against both, 1.1 % with none, 0.9 % with 10 % against the chunked one.  Below 32 batch rows it is
+// never taken against the staged few-lanes shape of the small-batch kernel, which was placed by measurement.  any_tile: in whatever tile runs
+// (plan_tile), else only in those that a caller can ask for as SRIGL_FWD_ROWLOOP.
+static bool tile_ahead(const FwdArgs& a, double us, bool any_tile) {
+    const OtherEstimates o = other_estimates(a);
+    // (beyond 2304 columns a tile leaves room for nine stored rows to a wavefront and less: 2400 -> 12000, K = 48 at batch 800 143 us, chunked 134)
+    return us * (any_tile ? (a.d_in > 2304 ? 1.0 : 0.95) : 1.02) < o.batched && us * (any_tile ? 1.0 : 1.02) < o.small;
+}
+static srigl_fwd_algo choose_fwd_algo(const FwdArgs& a, bool any_tile, RowloopPlan* tile) {
     const srigl_fwd_algo base = choose_chunked_or_small(a);
-    if (base == SRIGL_FWD_GENERIC || a.B < 2) return base;
+    if (a.B < 2) return base;
     int few_L = 0, few_RB = 0;
     if (base == SRIGL_FWD_KLANE && a.B < 32 && klane_few_lanes_staged(a.B, a.d_in, a.n_active, a.K, &few_L, &few_RB)) return base;
-    const double rl = rowloop_estimate_us(a);
-    if (rl >= 1e29) return base;
-    return rl * kRowloopMargin < chunked_or_small_estimate_us(a) ? SRIGL_FWD_ROWLOOP : base;
+    double us = 0.0;
+    *tile = any_tile ? plan_tile(a, 0, 0, 0, &us) : plan_rowloop(a, nullptr, &us);
+    if (!tile->ok || (base == SRIGL_FWD_GENERIC && !any_tile)) return base;
+    return base == SRIGL_FWD_GENERIC || tile_ahead(a, us, any_tile) ? SRIGL_FWD_ROWLOOP : base;
 }
 
 // The library's own choice for a call: the kernel and its launch shape, remembered per thread for the sizes, types and
@@ -838,7 +843,7 @@ struct FwdDecision {
     srigl_fwd_algo algo;
     KlanePlan klane;
     RowlanePlan rowlane;
-    RowloopPlan rowloop;
+    RowloopPlan rowloop;   // (not the caller's SRIGL_FWD_ROWLOOP alone: tiles of 16 rows and rows of any length too)
 };
 static const FwdDecision& decide_fwd(const FwdArgs& a) {
     struct Key { int32_t B, d_in, n_active, K, d_out, flags; };
@@ -848,10 +853,9 @@ static const FwdDecision& decide_fwd(const FwdArgs& a) {
                        (int)((reinterpret_cast<uintptr_t>(a.x) & 15) << 8) | (int)((reinterpret_cast<uintptr_t>(a.idx) & 3) << 12)};
     return cache.get(k, [&] {
         FwdDecision d{};
-        d.algo = choose_fwd_algo(a);
+        d.algo = choose_fwd_algo(a, true, &d.rowloop);
         if (d.algo == SRIGL_FWD_KLANE) d.klane = plan_klane(a, nullptr);
         if (d.algo == SRIGL_FWD_ROWLANE) d.rowlane = plan_rowlane(a, nullptr);
-        if (d.algo == SRIGL_FWD_ROWLOOP) d.rowloop = plan_rowloop(a, nullptr);
         return d;
     });
 }
@@ -874,8 +878,10 @@ static FwdArgs standin_args(int B, int d_in, int n_active, int K, int d_out, boo
 double condensed_estimate_us(int B, int d_in, int n_active, int K, int d_out, bool bf16, bool has_active) {
     if (B <= 0 || n_active <= 0 || K <= 0 || d_in <= 0) return 2.0;
     const FwdArgs a = standin_args(B, d_in, n_active, K, d_out, bf16, has_active, true);
-    const double other = chunked_or_small_estimate_us(a), rl = rowloop_estimate_us(a);
-    return rl * kRowloopMargin < other ? rl : other;
+    double us = 0.0;
+    if (plan_tile(a, 0, 0, 0, &us).ok && tile_ahead(a, us, true)) return us;
+    const OtherEstimates o = other_estimates(a);
+    return std::min(o.batched, o.small);
 }
 
 }  // namespace srigl
@@ -888,7 +894,7 @@ extern "C" {
 static srigl_status fwd_core(const void* x, srigl_dtype x_dtype, int32_t B, int32_t d_in, const void* W_c, srigl_dtype w_dtype,
                              const void* idx, bool idx_u16, const int32_t* active, int32_t n_active, int32_t K, const float* bias,
                              int32_t d_out, float* y, const uint16_t* seg, const void* packed, srigl_fwd_algo algo,
-                             const srigl_fwd_tuning* tuning, srigl_activation act, void* stream) {
+                             const srigl_fwd_tuning* tuning, srigl_activation act, void* stream, const int32_t* tile = nullptr) {
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (act != SRIGL_ACT_NONE && act != SRIGL_ACT_RELU && act != SRIGL_ACT_GELU) return SRIGL_ERR_INVALID_ARG;
     if (B < 0 || d_in < 0 || n_active < 0 || K < 0 || d_out < 0 || K > d_in || n_active > d_out) return SRIGL_ERR_INVALID_ARG;
@@ -914,6 +920,10 @@ static srigl_status fwd_core(const void* x, srigl_dtype x_dtype, int32_t B, int3
         hipLaunchKernelGGL(k_bias_broadcast, dim3((unsigned)blocks), dim3(256), 0, st, bias, B, d_out, y, a.act);
         return hip_ok(hipGetLastError());
     }
+    if (tile) {   // rows of the tile, stored rows per wavefront, which workgroups share an XCD
+        double us = 0.0;
+        return launch_rowloop_plan(a, plan_tile(a, tile[0], tile[1], tile[2], &us), st);
+    }
     switch (algo) {
         case SRIGL_FWD_GENERIC: return launch_fwd_generic(a, st);
         case SRIGL_FWD_KLANE: return launch_fwd_klane(a, tuning, st);
@@ -929,6 +939,30 @@ static srigl_status fwd_core(const void* x, srigl_dtype x_dtype, int32_t B, int3
         case SRIGL_FWD_KLANE: return launch_klane_plan(a, d.klane, nullptr, st);
         default: return launch_fwd_generic(a, st);
     }
+}
+
+srigl_status srigl_condensed_linear_fwd_tile(const void* x, srigl_dtype x_dtype, int32_t B, int32_t d_in, const void* W_c, srigl_dtype w_dtype,
+                                             const void* idx, int32_t idx_bits, const int32_t* active, int32_t n_active, int32_t K,
+                                             const float* bias, int32_t d_out, float* y, srigl_activation act, int32_t tile_rows,
+                                             int32_t rows_per_wave, int32_t xcd_order, void* stream) {
+    if (idx_bits != 16 && idx_bits != 32) return SRIGL_ERR_INVALID_ARG;
+    if ((tile_rows != 0 && tile_rows != 16 && tile_rows != 32 && tile_rows != 64) || rows_per_wave < 0 || xcd_order < 0 || xcd_order > 2)
+        return SRIGL_ERR_INVALID_ARG;
+    const int32_t tile[3] = {tile_rows, rows_per_wave, xcd_order};
+    return fwd_core(x, x_dtype, B, d_in, W_c, w_dtype, idx, idx_bits == 16, active, n_active, K, bias, d_out, y, nullptr, nullptr, SRIGL_FWD_AUTO, nullptr,
+                    act, stream, tile);
+}
+
+int32_t srigl_fwd_tile_query(int32_t B, int32_t d_in, int32_t n_active, int32_t K, int32_t d_out, srigl_dtype dtype, int32_t idx_bits,
+                             int32_t has_active, int32_t has_seg, int32_t* rows_per_wave) {
+    if (rows_per_wave) *rows_per_wave = 0;
+    if (B <= 0 || d_in <= 0 || n_active <= 0 || K <= 0 || d_out <= 0 || K > d_in || n_active > d_out) return 0;
+    FwdArgs a = standin_args(B, d_in, n_active, K, d_out, dtype == SRIGL_BF16, has_active != 0, has_seg != 0);
+    a.idx_u16 = idx_bits == 16;
+    RowloopPlan p{};
+    if (choose_fwd_algo(a, true, &p) != SRIGL_FWD_ROWLOOP) return 0;
+    if (rows_per_wave) *rows_per_wave = (p.NG + p.NW - 1) / p.NW;
+    return p.BT;
 }
 
 srigl_status srigl_condensed_linear_fwd_algo(const void* x, srigl_dtype x_dtype, int32_t B, int32_t d_in,
@@ -1008,7 +1042,8 @@ srigl_status srigl_fwd_plan_query_algo(int32_t B, int32_t d_in, int32_t n_active
     *plan = srigl_fwd_plan{};
     if (B == 0 || d_out == 0 || n_active == 0 || K == 0) return SRIGL_OK;   // nothing to gather: no forward kernel runs
     const FwdArgs a = standin_args(B, d_in, n_active, K, d_out, dtype == SRIGL_BF16, has_active != 0, has_seg != 0);
-    const srigl_fwd_algo algo = forced == SRIGL_FWD_AUTO ? choose_fwd_algo(a) : forced;
+    RowloopPlan unused{};
+    const srigl_fwd_algo algo = forced == SRIGL_FWD_AUTO ? choose_fwd_algo(a, false, &unused) : forced;
     plan->algo = (int32_t)algo;
     if (algo == SRIGL_FWD_ROWLANE) {
         const RowlanePlan p = plan_rowlane(a, tuning);

@@ -593,10 +593,10 @@ static int choose_blocked_tile(int B, int d_in, int n_active, double* us) {
     return best;
 }
 
-// Taken where its estimate is this far ahead of the gathering kernels'.  On 168 measured points (21 layers at batches of 16 to 2048, both
-// kinds of call) 0.95 takes one point that is behind by more than 2 % (4 %), and a call is 0.2 % slower on average than with the faster
-// of the two forms throughout; 0.85 leaves out points where the gathering kernel is up to 26 % behind, 1.0 takes some that are 14 % behind.
-constexpr double kBlockedMargin = 0.95;
+// Taken where its estimate is level with the gathering kernels' or ahead.  On 92 points (23 layers 155 to 2368 wide, 80 to 99 % sparse,
+// batches of 24 to 2048) a call is then 0.06 % slower on average than with the faster of the two forms throughout, 4 % at worst, with 1.0
+// or 1.05 in its place alike; with 0.95 0.12 % (9 %), with 1.1 0.5 % (9 %).
+constexpr double kBlockedMargin = 1.02;
 
 // What making the copy adds to a call (us): between 4.1 (200 -> 300) and 14 (4096 -> 16384, K = 205) on those layers
 static double block_terms_us(int n, int K) { return 4.3 + 2.9e-6 * n * (double)K; }

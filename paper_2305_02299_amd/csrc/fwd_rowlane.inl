@@ -97,21 +97,27 @@ __device__ __forceinline__ void load4(const uint16_t* __restrict__ p, bool vec_o
 // What a load brings from beyond its own row's end lies in columns no index names.  (Element by element behind branches, as
 // these rows were staged before, the loads went out one round trip after the other: 1000 -> 777 at batch 37 20.6 us.)
 __device__ __forceinline__ int ragged_shift(unsigned e, int total) { return max((int)e - (total - 4), 0); }
-__device__ __forceinline__ void load4_ragged(const float* __restrict__ p, unsigned e, int total, Staged4<float>& out) {
+__device__ __forceinline__ void load4_at_element(const float* __restrict__ p, Staged4<float>& out) {
     struct __attribute__((packed, aligned(4))) F4 { float x, y, z, w; };
+    const F4 v = *reinterpret_cast<const F4*>(p);
+    out.v[0] = v.x; out.v[1] = v.y; out.v[2] = v.z; out.v[3] = v.w;
+}
+__device__ __forceinline__ void load4_at_element(const uint16_t* __restrict__ p, Staged4<uint16_t>& out) {
+    struct __attribute__((packed, aligned(2))) U2 { uint32_t x, y; };
+    const U2 v = *reinterpret_cast<const U2*>(p);
+    out.w[0] = v.x; out.w[1] = v.y;
+}
+__device__ __forceinline__ void load4_ragged(const float* __restrict__ p, unsigned e, int total, Staged4<float>& out) {
     if (total >= 4) {
-        const F4 v = *reinterpret_cast<const F4*>(p + min((int)e, total - 4));
-        out.v[0] = v.x; out.v[1] = v.y; out.v[2] = v.z; out.v[3] = v.w;
+        load4_at_element(p + min((int)e, total - 4), out);
     } else {
 #pragma unroll
         for (int i = 0; i < 4; ++i) out.v[i] = p[min((int)e + i, total - 1)];
     }
 }
 __device__ __forceinline__ void load4_ragged(const uint16_t* __restrict__ p, unsigned e, int total, Staged4<uint16_t>& out) {
-    struct __attribute__((packed, aligned(2))) U2 { uint32_t x, y; };
     if (total >= 4) {
-        const U2 v = *reinterpret_cast<const U2*>(p + min((int)e, total - 4));
-        out.w[0] = v.x; out.w[1] = v.y;
+        load4_at_element(p + min((int)e, total - 4), out);
     } else {
         out.w[0] = (uint32_t)p[min((int)e, total - 1)] | ((uint32_t)p[min((int)e + 1, total - 1)] << 16);
         out.w[1] = (uint32_t)p[min((int)e + 2, total - 1)];

@@ -140,7 +140,7 @@ srigl_status launch_rowlane_bf16_i16(const FwdArgs& a, const RowlanePlan& p, hip
 struct KlanePlan { int L, RB, rows_per_wg, direct; long long workgroups; bool ok; };
 // Launch shape of the whole-input batched kernel, decided on the host.
 struct RowloopPlan {
-    int H, NW, NG, KPRE, n_btiles, n_groups, out_off, span_cap, bt_major;
+    int BT, NW, NG, ST, n_btiles, n_groups, out_off, span_cap, bt_major;
     int rounds;
     size_t lds;
     bool ok;
@@ -179,11 +179,14 @@ bool rowlane_supported(const FwdArgs& a, const srigl_fwd_tuning* t);
 // the launch shape for srigl_fwd_plan_query
 srigl_status launch_fwd_rowloop(const FwdArgs& a, const srigl_fwd_tuning* t, hipStream_t st);
 bool rowloop_supported(const FwdArgs& a, const srigl_fwd_tuning* t);
-double rowloop_estimate_us(const FwdArgs& a);
 bool rowloop_plan_query(const FwdArgs& a, const srigl_fwd_tuning* t, srigl_fwd_plan* plan);
-RowloopPlan plan_rowloop(const FwdArgs& a, const srigl_fwd_tuning* t);
+RowloopPlan plan_rowloop(const FwdArgs& a, const srigl_fwd_tuning* t, double* us);
+srigl_status launch_rowloop_f32(const FwdArgs& a, const RowloopPlan& p, hipStream_t st);
+srigl_status launch_rowloop_bf16(const FwdArgs& a, const RowloopPlan& p, hipStream_t st);
+srigl_status launch_rowloop_f32_i16(const FwdArgs& a, const RowloopPlan& p, hipStream_t st);
+srigl_status launch_rowloop_bf16_i16(const FwdArgs& a, const RowloopPlan& p, hipStream_t st);
+RowloopPlan plan_tile(const FwdArgs& a, int tile_rows, int rows_per_wave, int xcd_order, double* us);
 srigl_status launch_rowloop_plan(const FwdArgs& a, const RowloopPlan& p, hipStream_t st);
-srigl_fwd_algo choose_fwd_algo(const FwdArgs& a);
 // Estimated time (us) of the condensed forward call of these sizes in the kernel the library's own choice takes.
 double condensed_estimate_us(int B, int d_in, int n_active, int K, int d_out, bool bf16, bool has_active);
 // ... and on the matrix cores, the blocked copy made in the call (bf16 storage; 1e30 where the sizes do not allow it).

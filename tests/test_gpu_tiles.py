@@ -1,0 +1,115 @@
+"""GPU parity of the whole-input batched kernel in every tile it runs in (16, 32 and 64 batch rows): rows of every number of 16-term steps it
+has code for, rows of any length and alignment, last tiles and groups that are not full, both index widths."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth_inputs as si
+from gpu_util import TOL_BF16, TOL_F32, dev, gate, oracle_condensed
+from paper_2305_02299_amd import binding as B_
+
+pytestmark = pytest.mark.gpu
+WIDEST = {16: 2528, 32: 1248, 64: 608}     # columns (whole units of 16) with which 16 result rows still fit the LDS
+GUARD = 1 << 12
+
+
+def run_tile(L, tile_rows, rows_per_wave=0, xcd_order=0, narrow=False, x=None, offset=0, act=0):
+    W_c, idx, active = oracle_condensed(L)
+    xs = dev(L.x_bf16 if L.dtype == "bf16" else L.x) if x is None else dev(x)
+    if offset:    # the same rows at an address that is a multiple of the element size only
+        flat = torch.zeros((xs.numel() + offset,), dtype=xs.dtype, device="cuda")
+        flat[offset:] = xs.flatten()
+        xs = flat[offset:].view(xs.shape)
+    idx_d = dev(idx)
+    if narrow:
+        idx16 = torch.empty(idx_d.shape, dtype=torch.int16, device="cuda")
+        B_.srigl_narrow_idx(idx_d, L.d_in, idx16)
+        idx_d = idx16
+    Bn = xs.shape[0]
+    flat = torch.full((Bn * L.d_out + 2 * GUARD,), 777.0, dtype=torch.float32, device="cuda")
+    y = flat[GUARD:GUARD + Bn * L.d_out].view(Bn, L.d_out)
+    B_.srigl_condensed_linear_fwd_tile(xs, Bn, L.d_in, dev(W_c), idx_d, None if len(active) == L.d_out else dev(active), len(active), L.K, dev(L.bias),
+                                       L.d_out, y, act=act, tile_rows=tile_rows, rows_per_wave=rows_per_wave, xcd_order=xcd_order)
+    torch.cuda.synchronize()
+    out = flat.cpu().numpy()
+    assert (out[:GUARD] == 777.0).all() and (out[GUARD + Bn * L.d_out:] == 777.0).all(), "write outside y"
+    return out[GUARD:GUARD + Bn * L.d_out].reshape(Bn, L.d_out).copy()
+
+
+def check(L, tile_rows, **kw):
+    W_c, idx, active = oracle_condensed(L)
+    y_ref, S = oracle.fwd(L.x_bf16 if L.dtype == "bf16" else L.x, W_c, idx, active, L.bias, L.d_out, want_scale=True)
+    y = run_tile(L, tile_rows, **kw)
+    # sums of at most 600 fp32 terms in 16 or more partial sums: well inside 2e-6 of the summed magnitudes, whatever the storage type
+    assert gate(y, y_ref, S, TOL_BF16 if L.dtype == "bf16" else TOL_F32) < 2e-6
+    return y
+
+
+@pytest.mark.parametrize("tile_rows", [16, 32, 64])
+@pytest.mark.parametrize("K", [1, 15, 16, 17, 33, 63, 64, 65, 77, 96, 112, 113, 128, 129, 144, 177, 200, 240, 241, 256, 257, 320, 333, 600])
+def test_rows_of_every_number_of_steps(tile_rows, K):
+    d_in = 605 if K % 2 else 608                    # rows of whole 16-column units, and others
+    L = si.make_layer(d_in, 75, K, tile_rows + 3, dtype="bf16" if K % 3 == 0 else "f32", ablate_frac=0.2 if K % 4 else 0.0, seed=300 + K)
+    check(L, tile_rows)
+
+
+@pytest.mark.parametrize("tile_rows", [16, 32, 64])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_widths_alignments_and_index_types(tile_rows, dtype):
+    for d_in, B, abl, offset, rows_per_wave in ((16, 1, 0.0, 0, 0), (17, 2, 0.3, 1, 1), (31, tile_rows, 0.0, 3, 2), (33, tile_rows - 1, 0.5, 0, 0),
+                                                (100, 2 * tile_rows + 1, 0.0, 1, 3), (255, 5, 0.9, 2, 1), (WIDEST[tile_rows], 40, 0.1, 0, 1),
+                                                (WIDEST[tile_rows] - 7, 40, 0.0, 1, 1)):
+        L = si.make_layer(d_in, 133, max(1, d_in // 9), B, dtype=dtype, ablate_frac=abl, seed=400 + d_in)
+        wide = check(L, tile_rows, rows_per_wave=rows_per_wave, offset=offset, xcd_order=1 + d_in % 2)
+        narrow = check(L, tile_rows, rows_per_wave=rows_per_wave, offset=offset, narrow=True)
+        assert np.array_equal(wide.view(np.uint32), narrow.view(np.uint32))
+
+
+@pytest.mark.parametrize("tile_rows", [16, 32, 64])
+def test_columns_no_row_names_do_not_matter(tile_rows):
+    """NaN and infinities in columns that no stored row reads (padding terms point at an all-zero column of the tile), at the end of rows
+    whose length is not a multiple of 16 among them."""
+    for d_in, K in ((600, 70), (208, 5)):
+        L = si.make_layer(d_in, 60, K, tile_rows + 5, seed=500 + K)
+        mask = L.mask.copy()
+        keep = np.setdiff1d(np.arange(d_in), [0, 7, 16, d_in - 1])
+        rng = np.random.RandomState(3)
+        mask[:] = 0
+        for r in range(mask.shape[0]):
+            mask[r, rng.choice(keep, K, replace=False)] = 1
+        L.mask = mask
+        L.W = np.where(mask > 0, rng.randn(*mask.shape).astype(np.float32), 0).astype(np.float32)
+        clean = run_tile(L, tile_rows)
+        x = L.x.copy()
+        x[:, 0], x[:, 7], x[:, 16], x[:, d_in - 1] = np.nan, np.inf, -np.inf, np.nan
+        assert np.array_equal(run_tile(L, tile_rows, x=x).view(np.uint32), clean.view(np.uint32))
+        # a named column carries its non-finite value into exactly the neurons that read it
+        c = int(keep[3])
+        x = L.x.copy()
+        x[2, c] = np.inf
+        y = run_tile(L, tile_rows, x=x)
+        hit = np.zeros(y.shape, bool)
+        hit[2, mask[:, c] > 0] = True
+        assert np.array_equal(~np.isfinite(y), hit)
+
+
+def test_what_does_not_fit_is_refused():
+    for tile_rows, d_in in ((16, 2560), (32, 1280), (64, 640), (16, 15)):
+        L = si.make_layer(d_in, 40, 5, 20, seed=600)
+        with pytest.raises(B_.SriglError) as e:
+            run_tile(L, tile_rows)
+        assert e.value.status == B_.ERR_UNSUPPORTED, (tile_rows, d_in)
+    L = si.make_layer(256, 40, 5, 20, seed=600)
+    for kw in (dict(tile_rows=8), dict(tile_rows=16, rows_per_wave=-1), dict(tile_rows=16, xcd_order=3)):
+        with pytest.raises(B_.SriglError):
+            run_tile(L, **kw)
+
+
+@pytest.mark.parametrize("act", [B_.ACT_RELU, B_.ACT_GELU])
+def test_activation_in_the_epilogue(act):
+    L = si.make_layer(300, 90, 25, 37, ablate_frac=0.3, seed=700)
+    plain = run_tile(L, 16).astype(np.float64)
+    got = run_tile(L, 16, act=act)
+    want = np.maximum(plain, 0) if act == B_.ACT_RELU else torch.nn.functional.gelu(torch.from_numpy(plain)).numpy()
+    assert np.abs(got - want).max() <= 2e-6 * max(1.0, np.abs(want).max())    # the activation of the same fp32 sums
