@@ -215,11 +215,11 @@ __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, 
     float e_bias[TP];
     int e_col[TP];
 
-    // A pass stages kStageUnits units per wavefront.  Every load of a pass is unconditional (a unit, row or entry past the
-    // end re-reads the last one and is dropped afterwards) and the first pass, which is the only one with 16 wavefronts, is
-    // straight-line code: with loads under branches, or in a loop whose registers a load of the last turn may still own, the
-    // compiler waits for every load in flight before the next one is issued (measured on the staging of this kernel: the
-    // six tile loads of a wavefront went out one round trip after the other).
+    // A pass stages kStageUnits units per wavefront, 16 columns of all rows under one wave-uniform branch (a lane's row past the end
+    // re-reads the last one and is dropped afterwards), and the first pass, the only one on inputs up to 2048 columns wide with 16
+    // wavefronts, is straight-line code: in a loop whose registers a load of the last turn may still own, or with a branch on every
+    // load's lanes, the compiler waits for every load in flight before the next one is issued (measured on the staging of this
+    // kernel: the six tile loads of a wavefront went out one round trip after the other).
     const float* const bias_src = bias ? bias : reinterpret_cast<const float*>(x);   // never used: entries are 0 without a bias
     unsigned x_lane[RT];                       // element of x the lane loads of column 0, per 16 rows (past B: row B - 1 again, never stored)
 #pragma unroll
@@ -232,10 +232,12 @@ __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, 
         Staged4<XT> st[CPP][RT];
 #pragma unroll
         for (int i = 0; i < CPP; ++i) {
-            const int ct = min(cb + wv_id + i * nw, n_ct - 1);
+            const int ct = cb + wv_id + i * nw;
+            if (ct < n_ct) {
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-                load4_at_element(xtile + min(x_lane[rt] + (unsigned)(ct * 16), (unsigned)(tile_total - 4)), st[i][rt]);
+                for (int rt = 0; rt < RT; ++rt)
+                    load4_at_element(xtile + min(x_lane[rt] + (unsigned)(ct * 16), (unsigned)(tile_total - 4)), st[i][rt]);
+            }
         }
         if constexpr (decltype(first)::value) {
             // behind the tile's first requests: the first rows' terms (vector loads return in order, and the tile's stores
@@ -369,14 +371,20 @@ __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, 
         if constexpr (RL == 4) v += row_ror<4>(v);
         if ((p16 & 3) < RL / 4) out[out_row * OS + j] = v;
     };
+    __builtin_amdgcn_s_setprio(3);
+    const int third = ng / 3;
     int j = wv_id;
     for (; j + (D - 1) * nw < ng; j += D * nw) {   // whole turns of the D buffers: straight-line
 #pragma unroll
         for (int d = 0; d < D; ++d) walk_row(j + d * nw, rw[d], ri[d]);
+        if (j >= 2 * third) __builtin_amdgcn_s_setprio(0);
+        else if (j >= third) __builtin_amdgcn_s_setprio(1);
+        else __builtin_amdgcn_s_setprio(2);
     }
 #pragma unroll
     for (int d = 0; d < D - 1; ++d)                 // the rows of a last, partial turn
         if (j + d * nw < ng) walk_row(j + d * nw, rw[d], ri[d]);
+    __builtin_amdgcn_s_setprio(0);
     __syncthreads();
 
     // ---- results: row-contiguous stores of the workgroup's run of columns ----
