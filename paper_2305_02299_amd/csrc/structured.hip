@@ -127,12 +127,13 @@ __global__ __launch_bounds__(256) void k_sum_parts(const float* __restrict__ par
 
 template <typename T> struct Frag;
 template <> struct Frag<uint16_t> { using type = bf16x8_t; };
-template <> struct Frag<float> { using type = float4; };
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+template <> struct Frag<float> { using type = f32x4_t; };
 
 __device__ __forceinline__ void mma_block(f32x16_t& acc, const bf16x8_t& a, const bf16x8_t& b) {
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
 }
-__device__ __forceinline__ void mma_block(f32x16_t& acc, const float4& a, const float4& b) {
+__device__ __forceinline__ void mma_block(f32x16_t& acc, const f32x4_t& a, const f32x4_t& b) {
     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
@@ -141,11 +142,17 @@ __device__ __forceinline__ void mma_block(f32x16_t& acc, const float4& a, const 
 
 // BM x BN output tile per workgroup of WGM x WGN wavefronts; NS >= 2 LDS stages of SLAB (128 or 64) bytes of K per row.
 //
-// Schedule of one stage h (KSTEPS = SLAB / 32 MFMA steps): the fragments of step kk + 1 are requested before the MFMAs of
-// step kk; before the last step the wavefront waits until its own loads of stage h + 1 have landed and its own reads of
-// stage h have returned, meets the others at the barrier (after which stage h + 1 is complete and the slot of stage h is
-// free), refills that slot with stage h + NS and requests the first fragments of stage h + 1.  The MFMAs right after
-// the barrier have their operands in registers already, so the matrix pipe does not drain at the barrier.
+// Schedule of one stage h (KSTEPS = SLAB / 32 MFMA steps): the fragments of step kk + 1 are requested between the MFMAs of
+// step kk, the first ones before the first of them; before the last step the wavefront waits until its own loads of stage h + 1 have
+// landed and its own reads of stage h have returned, meets the others at the barrier (after which stage h + 1 is complete and the slot of
+// stage h is free), and requests the first fragments of stage h + 1 and, between the MFMAs of this step and of the next stage's first
+// one, the pieces of stage h + NS.  The MFMAs right after the barrier have their operands in registers already, so the matrix pipe does
+// not drain at the barrier.
+// What bounds it: the matrix units' rate at the clock that the card holds (4096 -> 16384 at batch 2048: 1.4 PFLOP/s, 1.2 to 1.75 for a
+// library product on the same cards) and the fp32 result.  Everything of a step in one block, and loaded where the
+// compiler wanted it, just before its use: the matrix pipe was busy 42 % of the time, and in 256 x 256 tiles two stages of 128 bytes took
+// longer than five of 64.  Before -> now (bf16, us): 16384 stored at batch 2048, d_in 4096, 240 -> 215; 5023 at 1696, 1136, 53 -> 36; 13569 at
+// 1816, 1040, 128 -> 78; fp32 538 at 256, 3072, in one part 86 -> 59; 64 x 64 tiles on small products 5.9 -> 5.8.
 template <typename T, int BM, int BN, int WGM, int WGN, int NS, int SLAB, bool RAGGED>
 __global__ __launch_bounds__(WGM * WGN * 64) void k_structured_gemm(const T* __restrict__ x, int B, int d_in, const T* __restrict__ Wd,
                                                                    const int32_t* __restrict__ active, int n_active,
@@ -193,26 +200,25 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_structured_gemm(const T* __r
     // Part blockIdx.y of d_in (splits parts of whole stages, sizes one stage apart at most): stages h_first .. h_first + n_st - 1
     // of the row.  With one part the tile's sums are complete and go to y; with several they go to part[blockIdx.y][B][n_active].
     const int n_st_row = (d_in + EPS - 1) / EPS;
-    const int h_first = (int)(((long long)blockIdx.y * n_st_row) / splits);
-    const int n_st = (int)(((long long)(blockIdx.y + 1) * n_st_row) / splits) - h_first;
+    // (32 bits hold it: at most kMaxSplits parts of 2^26 stages; 64-bit divisions were a third of the instructions before the first request)
+    const unsigned n_parts = (unsigned)splits, part_no = blockIdx.y;
+    const int h_first = n_parts == 1 ? 0 : (int)(part_no * (unsigned)n_st_row / n_parts);
+    const int n_st = n_parts == 1 ? n_st_row : (int)((part_no + 1) * (unsigned)n_st_row / n_parts) - h_first;
     // RAGGED: d_in is not a multiple of EPS; the pieces of the last stage that lie past the end of the rows come from zeros.
     // A stage index past the end re-issues the last stage (into a slot nobody reads again): the loop body has no branches
     // and the number of loads in flight at each wait is fixed.
-    auto issue_stage = [&](int h_unclamped) {
+    auto issue_piece = [&](int p, int h_unclamped, int slot) {   // slot: byte offset of the stage's place in the ring
         const int h = h_first + min(h_unclamped, n_st - 1);
-        unsigned char* stage = smem + (h_unclamped % NS) * STAGE + 1024 * wv;
-        const unsigned char* xs = xbase + (size_t)h * SLAB;
-        const unsigned char* ws = wbase + (size_t)h * SLAB;
-#pragma unroll
-        for (int p = 0; p < PASSES; ++p) {
-            const unsigned char* g = ((p < XP) ? xs : ws) + voff[p];
-            if (RAGGED) {
-                const int row = RPL * (p * NWAVES + wv) + lane / PIECES;
-                const int piece = (lane % PIECES) ^ ((row >> SWZ_SHIFT) & (PIECES - 1));
-                if (h * EPS + piece * EPP >= d_in) g = reinterpret_cast<const unsigned char*>(&g_zero16);   // a piece is whole or absent
-            }
-            __builtin_amdgcn_global_load_lds((gptr_t)g, (lptr_t)(stage + 1024 * NWAVES * p), 16, 0, 0);
+        const unsigned char* const rows = ((p < XP) ? xbase : wbase) + (size_t)h * SLAB;
+        uint32_t off = voff[p];
+        asm("" : "+v"(off));   // (a lane offset from a scalar base: seen to be 32 bits only next to the load)
+        const unsigned char* g = rows + off;
+        if (RAGGED) {
+            const int row = RPL * (p * NWAVES + wv) + lane / PIECES;
+            const int piece = (lane % PIECES) ^ ((row >> SWZ_SHIFT) & (PIECES - 1));
+            if (h * EPS + piece * EPP >= d_in) g = reinterpret_cast<const unsigned char*>(&g_zero16);   // a piece is whole or absent
         }
+        __builtin_amdgcn_global_load_lds((gptr_t)g, (lptr_t)(smem + slot + 1024 * wv + 1024 * NWAVES * p), 16, 0, 0);
     };
 
     f32x16_t acc[TM][TN];
@@ -223,9 +229,12 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_structured_gemm(const T* __r
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
+    constexpr int EARLY = TM * TN == 1 ? PASSES : PASSES / 2;   // pieces of a stage that are requested right behind the barrier, the others a step later
     if (n_st > 0) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) issue_stage(s);
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int p = 0; p < (s < NS - 1 ? PASSES : EARLY); ++p) issue_piece(p, s, s * STAGE);
     }
 
     // reader: row l%32 of a block, piece 2*kk + l/32; the swizzle term only depends on the lane (block rows start at multiples of 32)
@@ -235,37 +244,61 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_structured_gemm(const T* __r
     for (int kk = 0; kk < KSTEPS; ++kk) frag_off[kk] = (lane & 31) * SLAB + (((2 * kk + (lane >> 5)) ^ swz) * 16);
 
     F a[2][TM], b[2][TN];
-    auto read_frags = [&](int h, int kk, int set) {
-        const unsigned char* buf = smem + (h % NS) * STAGE;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) a[set][i] = *reinterpret_cast<const F*>(buf + (wm * WTM + i * 32) * SLAB + frag_off[kk]);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) b[set][j] = *reinterpret_cast<const F*>(buf + (BM + wn * WTN + j * 32) * SLAB + frag_off[kk]);
+    // fragment f of a step, in the order the products take them: a[0], the b's, the other a's
+    auto read_frag = [&](int f, int slot, int kk, int set) {
+        const unsigned char* buf = smem + slot + frag_off[kk];
+        if (f >= 1 && f <= TN) b[set][f - 1] = *reinterpret_cast<const F*>(buf + (BM + wn * WTN + (f - 1) * 32) * SLAB);
+        else a[set][f ? f - TN : 0] = *reinterpret_cast<const F*>(buf + (wm * WTM + (f ? f - TN : 0) * 32) * SLAB);
     };
 
     if (n_st > 0) {
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 1) * PASSES));
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 2) * PASSES + EARLY));
         __syncthreads();
-        read_frags(0, 0, 0);
+#pragma unroll
+        for (int f = 0; f < TM + TN; ++f) read_frag(f, 0, 0, 0);
+        // (opaque: a value that is a load here and in the loop is loaded where it is used, behind everything that was to hide it)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(a[0][i]));
+#pragma unroll
+        for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(b[0][j]));
     }
+    int slot = 0, before = (NS - 1) * STAGE;   // of stage h and of the one before it
     for (int h = 0; h < n_st; ++h) {
+        const int after = slot == (NS - 1) * STAGE ? 0 : slot + STAGE;
 #pragma unroll
         for (int kk = 0; kk < KSTEPS; ++kk) {
-            if (kk + 1 < KSTEPS) {
-                read_frags(h, kk + 1, (kk + 1) & 1);
-            } else {
+            constexpr int N_MMA = TM * TN, N_FRAG = TM + TN, N_READ = N_MMA > N_FRAG ? N_FRAG : (N_MMA + 1) / 2;
+            const bool last = kk + 1 == KSTEPS;
+            if (last) {
+                __builtin_amdgcn_s_waitcnt(kLgkm0);
                 // stages up to h + NS - 1 are on their way; stage h + 1 must have landed.  Every fragment of stage h is in
-                // registers by now (the wait before the barrier covers the reads above), so its slot is refilled right away.
+                // registers by now, so its slot is refilled right away.
                 __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 2) * PASSES));
-                __syncthreads();
-                issue_stage(h + NS);
-                read_frags(min(h + 1, n_st - 1), 0, 0);
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
             }
+            // The next step's fragments and this step's share of the stage requested ahead go out between the multiplications
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int m = 0; m < N_MMA; ++m) {
 #pragma unroll
-                for (int j = 0; j < TN; ++j) mma_block(acc[i][j], a[kk & 1][i], b[kk & 1][j]);
+                for (int f = m * N_FRAG / N_READ; f < (m + 1) * N_FRAG / N_READ && f < N_FRAG; ++f)
+                    read_frag(f, last ? after : slot, last ? 0 : kk + 1, (kk + 1) & 1);
+                if (N_MMA > 1) mma_block(acc[m / TN][m % TN], a[kk & 1][m / TN], b[kk & 1][m % TN]);
+                if (last) {
+#pragma unroll
+                    for (int p = m * EARLY / N_MMA; p < (m + 1) * EARLY / N_MMA; ++p) issue_piece(p, h + NS, slot);
+                }
+                if (kk == 0) {
+#pragma unroll
+                    for (int p = EARLY + m * (PASSES - EARLY) / N_MMA; p < EARLY + (m + 1) * (PASSES - EARLY) / N_MMA; ++p) issue_piece(p, h + NS - 1, before);
+                }
+                if (N_MMA == 1) mma_block(acc[0][0], a[kk & 1][0], b[kk & 1][0]);   // (it waits for the one before: requests first)
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
+        before = slot;
+        slot = after;
     }
 
     // One part of several: the partial sums of the tile, stored neuron s in column s of this part's [B][n_active] array
@@ -288,9 +321,11 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_structured_gemm(const T* __r
         return;
     }
 
-    // Epilogue without an active list: stored neuron s is column s; every lane writes its accumulators where they belong
-    // (32 neighbouring lanes cover 128 contiguous bytes of a row).
-    if (active == nullptr) {
+    // Epilogue of 64 x 64 tiles without an active list: stored neuron s is column s; every lane writes its accumulators where they belong
+    // (32 neighbouring lanes cover 128 contiguous bytes of a row).  Larger tiles go through the LDS below here too, which writes whole
+    // rows of the tile: 13108 columns at batch 2048, d_in 4096, in 256 x 256 tiles 221 us -> 180, 9000 at 1024, d_in 2048, 55 -> 47, 3000 at
+    // 2048, d_in 1024, in 256 x 128 tiles 24 -> 20; in 64 x 64 tiles 28 -> 29.
+    if (TM * TN == 1 && active == nullptr) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int col = n0 + wn * WTN + j * 32 + (lane & 31);
@@ -327,7 +362,7 @@ static srigl_status launch_gemm_r(const void* x, int B, int d_in, const void* Wd
     const long long n_wg = ((tiles_m * tiles_n + kXcds - 1) / kXcds) * kXcds;   // 8 equal runs of tiles, one per XCD
     if (n_wg > 0x7fffffffLL) return SRIGL_ERR_UNSUPPORTED;
     // every part holds at least one stage
-    if (splits < 1 || splits > 65535 || (splits > 1 && (part == nullptr || splits > (d_in * (int)sizeof(T) + SLAB - 1) / SLAB)))
+    if (splits < 1 || splits > kMaxSplits || (splits > 1 && (part == nullptr || splits > (d_in * (int)sizeof(T) + SLAB - 1) / SLAB)))
         return SRIGL_ERR_INVALID_ARG;
     if (splits > 1 && B > 65535) return SRIGL_ERR_UNSUPPORTED;   // the sum's grid has one row of workgroups per batch row
     const dim3 grid((unsigned)n_wg, (unsigned)splits);
@@ -351,94 +386,120 @@ static srigl_status launch_gemm(const void* x, int B, int d_in, const void* Wd, 
 }
 
 // Tile choice and time estimate: a workgroup needs about ns_per_k nanoseconds per element of d_in for its tile (measured on
-// MI355X with every compute unit busy; 64x64 fp32 tiles run slower when a compute unit holds a single workgroup), and the
-// tiles take ceil(tiles / 256) rounds over the 256 compute units.
-struct TileModel { srigl_gemm_tile tile; int bm, bn; float ns_per_k_bf16, ns_per_k_f32, ns_per_k_f32_single_round; };
+// MI355X with every compute unit busy), and the tiles take ceil(tiles / 256) rounds over the 256 compute units.  fp32, and either type
+// where the caller forces the parts of d_in.
+struct TileModel { srigl_gemm_tile tile; int bm, bn; float ns_per_k_bf16, ns_per_k_f32; };
 static const TileModel kTileModels[] = {
-    {SRIGL_TILE_256x256_H, 256, 256, 28.0f, 233.0f, 233.0f},
-    {SRIGL_TILE_256x128, 256, 128, 18.0f, 125.0f, 125.0f},
-    {SRIGL_TILE_128x128, 128, 128, 12.0f, 70.0f, 70.0f},
-    {SRIGL_TILE_64x64, 64, 64, 3.8f, 19.0f, 26.0f},
+    {SRIGL_TILE_256x256_H, 256, 256, 28.0f, 233.0f},
+    {SRIGL_TILE_256x128, 256, 128, 18.0f, 125.0f},
+    {SRIGL_TILE_128x128, 128, 128, 12.0f, 70.0f},
+    {SRIGL_TILE_64x64, 64, 64, 3.8f, 19.0f},
 };
-
-// ns_per_k_out: nanoseconds per element of d_in for the whole product with the chosen tile
-static srigl_gemm_tile choose_tile(int B, int n_active, bool f32, double* ns_per_k_out = nullptr) {
+static srigl_gemm_tile choose_tile(int B, int n_active, bool f32) {
     srigl_gemm_tile best = SRIGL_TILE_64x64;
     double best_cost = 0.0;
     for (const TileModel& m : kTileModels) {
         const long long tiles = (long long)((B + m.bm - 1) / m.bm) * ((n_active + m.bn - 1) / m.bn);
         const long long rounds = (tiles + 255) / 256;
-        const double cost = (double)rounds * (f32 ? (rounds == 1 ? m.ns_per_k_f32_single_round : m.ns_per_k_f32) : m.ns_per_k_bf16);
+        const double cost = (double)rounds * (f32 ? m.ns_per_k_f32 : m.ns_per_k_bf16);
         if (best_cost == 0.0 || cost < best_cost) { best_cost = cost; best = m.tile; }
     }
-    if (ns_per_k_out) *ns_per_k_out = best_cost;
     return best;
 }
 
-// The same choice with d_in cut into parts (the parts' tiles run side by side; their partial sums pass through a workspace
-// and a second launch adds them): worth it when the tiles alone reach a fraction of the 256 compute units.  Parts: as many
-// as keep the workgroups (8 runs of tiles, padded) within 256, or within 480 for 64x64 tiles, two of which share a compute
-// unit and then run about 1.6 times longer each; at most 16, at least 4 stages of 128 bytes each.  Measured on MI355X
-// (3072 -> 768 fp32, 538 stored neurons): batch 256 88 us in one part, 21 us in 12; batch 64 69 us and 12 us in 16.
-static void choose_tile_and_split(int B, int n_active, int d_in, int d_out, bool f32, srigl_gemm_tile* tile_out, int* splits_out,
-                                  double* est_us_out) {
+// bf16: a round of tiles costs a part of its own, a part per 1000 elements of d_in and another that follows how full the rounds are;
+// two 64 x 64 tiles share a compute unit.  Least squares on 79 products with 5 to 20 % of the weights present (200 to 16384 stored
+// rows, batches 48 to 2048, 128- to 4096-wide, half of them with ablated neurons): 7 to 9 % per shape, and the tile of smallest time 0.3 %
+// behind the fastest on average.  (256 x 192 tiles: 9000 rows at batch 2048, d_in 4096, 155 us, 157 in 256 x 128 and 180 in 256 x 256; 5023 at
+// 1696, 1136, 35.7, 48 and 36.)
+constexpr int kTile256x192 = 7;   // 8 wavefronts of 64x96, 2 LDS stages of 128 bytes; only the library's choice takes it
+struct Bf16TileModel { int tile, bm, bn; float fixed, round, per_k, per_k_full; };
+static const Bf16TileModel kBf16TileModels[] = {
+    {SRIGL_TILE_256x256, 256, 256, 2.0f, 7.14f, 16.67f, 2.35f},
+    {kTile256x192, 256, 192, 0.1f, 8.24f, 12.88f, 5.28f},
+    {SRIGL_TILE_256x128, 256, 128, 0.7f, 6.74f, 9.90f, 0.41f},
+    {SRIGL_TILE_128x128, 128, 128, 3.3f, 3.88f, 6.74f, 0.0f},
+    {SRIGL_TILE_64x64, 64, 64, 2.0f, 2.42f, 5.67f, 0.0f},
+};
+// Time (us) of `splits` parts of the product in a shape, without the bytes of y.
+static double bf16_tiles_us(const Bf16TileModel& m, int splits, int B, int d_in, int n_active) {
+    const double d = d_in * 1e-3 / splits;
+    const long long tiles = (long long)((B + m.bm - 1) / m.bm) * ((n_active + m.bn - 1) / m.bn);
+    const double groups = (double)(splits > 1 ? (tiles + kXcds - 1) / kXcds * kXcds * splits : tiles);
+    if (m.bm == 64) return groups <= 256 ? 5.1 + 4.44 * d : m.fixed + std::ceil(groups / 512) * (m.round + m.per_k * d);
+    return m.fixed + std::ceil(groups / 256) * (m.round + m.per_k * d) + groups / 256 * m.per_k_full * d;
+}
+
+struct GemmChoice { int tile, splits; double us; };
+
+// Several parts of d_in run side by side; their partial sums pass through a workspace and a second launch adds them: worth it
+// when the tiles alone reach a fraction of the 256 compute units.  Parts: as many as keep the workgroups (8 runs of tiles,
+// padded) within 256, or within 480 for 64x64 tiles, two of which share a compute unit and then run 1.3 (bf16) to 1.85 (fp32) times
+// longer each; at most 16, at least 4 stages of 128 bytes each.  Measured on MI355X (3072 -> 768 fp32, 538 stored neurons): batch 256
+// 59 us in one part, 18 us in 12; batch 64 57 us and 11 us in 16.
+static int parts_of(int B, int n_active, int d_in, bool f32, int bm, int bn) {
     const int stages = (d_in * (f32 ? 4 : 2) + kSlabBytes - 1) / kSlabBytes;
-    srigl_gemm_tile best = SRIGL_TILE_64x64;
-    int best_s = 1;
-    double best_us = 0.0;
+    const long long tiles = (long long)((B + bm - 1) / bm) * ((n_active + bn - 1) / bn), padded = (tiles + kXcds - 1) / kXcds * kXcds;
+    const long long wg_cap = bm == 64 ? 480 : 256;
+    const int cap = std::max(1, std::min(stages / 4, kMaxSplits));
+    return padded >= wg_cap ? 1 : std::min((int)(wg_cap / padded), cap);
+}
+
+// The partial sums are written once and read once; the second launch and a second pipeline fill are 1 us (bf16) and 2.6 (fp32) of
+// the 2.5 and 3.5 that the estimates add, the rest is the host's second launch.  On 78 products with and without parts (64 x 64 tiles, 100 to 6000 stored
+// rows, batches 16 to 512): 4 to 6 us too high while the constants were the first kernel's (1304 rows at batch 80, d_in 1680, bf16: 12.6 us
+// in one part, 9.3 in six).
+constexpr double kPartsUs = 1.7 * 8.0 / 4.5e6;
+static GemmChoice choose_f32(int B, int n_active, int d_in, int d_out, bool may_split) {
+    GemmChoice best{};
     for (const TileModel& m : kTileModels) {
-        const long long tiles = (long long)((B + m.bm - 1) / m.bm) * ((n_active + m.bn - 1) / m.bn);
-        const long long padded = (tiles + kXcds - 1) / kXcds * kXcds;
-        const long long wg_cap = m.bm == 64 ? 480 : 256;
-        int cap = stages / 4 < kMaxSplits ? stages / 4 : kMaxSplits;
-        if (cap < 1) cap = 1;
-        int s = padded >= wg_cap ? 1 : (int)(wg_cap / padded);
-        s = s > cap ? cap : s;
+        const long long tiles = (long long)((B + m.bm - 1) / m.bm) * ((n_active + m.bn - 1) / m.bn), padded = (tiles + kXcds - 1) / kXcds * kXcds;
+        const int s = may_split ? parts_of(B, n_active, d_in, true, m.bm, m.bn) : 1;
         for (int pass = 0; pass < 2; ++pass) {   // one part, then several
             if (pass == 1 && s == 1) break;
             double us;
             if (pass == 0) {
                 const long long rounds = (tiles + 255) / 256;
-                const double ns_k = f32 ? (rounds == 1 ? m.ns_per_k_f32_single_round : m.ns_per_k_f32) : m.ns_per_k_bf16;
-                us = (double)rounds * ns_k * d_in * 1e-3;
+                us = 2.1 + (double)rounds * m.ns_per_k_f32 * d_in * 1e-3;
             } else {
-                const double ns_k = f32 ? m.ns_per_k_f32 : m.ns_per_k_bf16;
-                const double crowd = (m.bm == 64 && padded * s > 256) ? 1.6 : 1.0;
-                // 7.0: the second launch and a second pipeline fill; the partial sums are written once and read once
-                us = 7.0 + ns_k * crowd * d_in / s * 1e-3 + 8.0 * s * (double)B * n_active / 4.5e6;
+                const double crowd = (m.bm == 64 && padded * s > 256) ? 1.85 : 1.0;
+                us = 3.5 + m.ns_per_k_f32 * crowd * d_in / s * 1e-3 + kPartsUs * s * (double)B * n_active;
             }
-            if (best_us == 0.0 || us < best_us) { best_us = us; best = m.tile; best_s = pass == 0 ? 1 : s; }
+            if (best.tile == 0 || us < best.us) best = {m.tile, pass == 0 ? 1 : s, us};
         }
     }
-    if (tile_out) *tile_out = best;
-    if (splits_out) *splits_out = best_s;
-    if (est_us_out) *est_us_out = 3.5 + best_us + 4.0 * (double)B * d_out / 4.5e6;
+    best.us += 3.5 + 4.0 * (double)B * d_out / 4.5e6;
+    return best;
 }
 
-// Time (us) of the bf16 product in the tile and parts chosen above, for the choice between the forms: refitted to the kernel as it is (the
-// constants above rank its tiles, and are 15 to 25 % high on 4096-wide layers since the epilogue writes whole rows).  A round of tiles
-// costs a fixed part and a part per element of d_in; two 64 x 64 tiles share a compute unit.  On 144 measured points (18 layers, 200- to
-// 4096-wide, batches of 16 to 2048) the deviation is 7 % (root of the mean square), 10 % where d_in is cut.
-static double structured_bf16_us(srigl_gemm_tile tile, int splits, int B, int d_in, int n_active, int d_out) {
-    const double d = d_in * 1e-3 / splits;
-    auto groups = [&](int bm, int bn) {
-        const long long tiles = (long long)((B + bm - 1) / bm) * ((n_active + bn - 1) / bn);
-        return (double)(splits > 1 ? (tiles + kXcds - 1) / kXcds * kXcds * splits : tiles);
-    };
-    double us = 3.5 + 4.0 * (double)B * d_out / 4.5e6;
-    if (tile == SRIGL_TILE_64x64) us += groups(64, 64) <= 256 ? 0.8 + 4.15 * d : std::ceil(groups(64, 64) / 512) * (0.2 + 5.85 * d);
-    else if (tile == SRIGL_TILE_128x128) us += std::ceil(groups(128, 128) / 256) * (3.3 + 8.5 * d);
-    else if (tile == SRIGL_TILE_256x128) us += std::ceil(groups(256, 128) / 256) * (2.6 + 13.3 * d);
-    else us += std::ceil(groups(256, 256) / 256) * (2.0 + 22.5 * d);
-    if (splits > 1) us += 2.5 + 8.0 * splits * (double)B * n_active / 4.5e6;
-    else if (n_active < d_out) us += 1.0;   // (the tables of the epilogue)
-    return us;
+static GemmChoice choose_bf16(int B, int n_active, int d_in, int d_out, bool may_split) {
+    GemmChoice best{};
+    for (const Bf16TileModel& m : kBf16TileModels) {
+        if (m.bm > 64 && (long long)m.bm * d_in * 2 >= (1ll << 31)) continue;   // launch_gemm's byte offsets
+        const double one = bf16_tiles_us(m, 1, B, d_in, n_active);
+        if (best.tile == 0 || one < best.us) best = {m.tile, 1, one};
+        const int s = may_split ? parts_of(B, n_active, d_in, false, m.bm, m.bn) : 1;
+        if (s == 1 || m.tile == kTile256x192) continue;
+        const double several = bf16_tiles_us(m, s, B, d_in, n_active) + 2.5 + kPartsUs * s * (double)B * n_active;
+        if (several < best.us) best = {m.tile, s, several};
+    }
+    best.us += 4.0 * (double)B * d_out / 4.5e6 + (best.splits == 1 && n_active < d_out ? 1.3 : 0.0);   // (1.3: the columns' tables)
+    return best;
+}
+static GemmChoice choose_gemm(int B, int n_active, int d_in, int d_out, bool f32, bool may_split) {
+    struct Key { int32_t B, n_active, d_in, d_out, form; };
+    static thread_local DecisionCache<Key, GemmChoice, 64> cache;
+    return cache.get(Key{B, n_active, d_in, d_out, f32 * 2 + may_split}, [&] {
+        return f32 ? choose_f32(B, n_active, d_in, d_out, may_split) : choose_bf16(B, n_active, d_in, d_out, may_split);
+    });
 }
 
 template <typename T>
 static srigl_status launch_structured(int tile, const void* x, int B, int d_in, const void* Wd, const int32_t* active, int n_active,
                                       const float* bias, int d_out, float* y, int splits, float* part, hipStream_t st) {
-    if (tile == SRIGL_TILE_AUTO) tile = choose_tile(B, n_active, sizeof(T) == 4);
+    if constexpr (sizeof(T) == 2) {
+        if (tile == kTile256x192) return launch_gemm<T, 256, 192, 4, 2, 2, 128>(x, B, d_in, Wd, active, n_active, bias, d_out, y, splits, part, st);
+    }
     switch (tile) {
         case SRIGL_TILE_256x256: return launch_gemm<T, 256, 256, 2, 4, 2, 128>(x, B, d_in, Wd, active, n_active, bias, d_out, y, splits, part, st);
         case SRIGL_TILE_256x256_H: return launch_gemm<T, 256, 256, 2, 4, 5, 64>(x, B, d_in, Wd, active, n_active, bias, d_out, y, splits, part, st);
@@ -491,7 +552,7 @@ srigl_status srigl_densify(const void* W_c, srigl_dtype w_dtype, const int32_t* 
 // 512- to 4096-wide layers, 80-99 % sparsity):
 //   condensed  = the estimate of the forward kernel the library's own choice takes for these sizes (condensed_estimate_us); bf16: or of the
 //                matrix-core form with its copy made in the call, whichever is faster
-//   structured = structured_bf16_us; fp32:
+//   structured = choose_bf16; fp32:
 //              ~ 3.5 + d_in x (rounds of tiles x nanoseconds per element of d_in of the chosen tile) / 1000 / parts of d_in
 //                  + the second launch when d_in is cut into parts (srigl_structured_linear_fwd_split)
 //                  + 4 B d_out / 4.5e6              (writing the result at HBM speed)
@@ -506,16 +567,8 @@ srigl_representation srigl_choose_representation(int32_t B, int32_t d_in, int32_
         Estimates v;
         v.cond = condensed_estimate_us(B, d_in, n_active, K, d_out, dtype == SRIGL_BF16, n_active < d_out);
         const bool f32 = dtype == SRIGL_F32;
-        v.stru = 0.0;
-        if (f32) {
-            choose_tile_and_split(B > 0 ? B : 1, n_active > 0 ? n_active : 1, d_in, d_out, f32, nullptr, nullptr, &v.stru);
-        } else {
-            srigl_gemm_tile tile;
-            int splits;
-            choose_tile_and_split(B > 0 ? B : 1, n_active > 0 ? n_active : 1, d_in, d_out, f32, &tile, &splits, nullptr);
-            v.stru = structured_bf16_us(tile, splits, B > 0 ? B : 1, d_in, n_active > 0 ? n_active : 1, d_out);
-            v.cond = std::min(v.cond, blocked_estimate_us(B, d_in, n_active, K, d_out));
-        }
+        v.stru = choose_gemm(B > 0 ? B : 1, n_active > 0 ? n_active : 1, d_in, d_out, f32, true).us;
+        if (!f32) v.cond = std::min(v.cond, blocked_estimate_us(B, d_in, n_active, K, d_out));
         if ((d_in * (f32 ? 4 : 2)) % 16 != 0) v.stru = 1e30;   // the matrix-core kernel needs rows of whole 16-byte pieces
         return v;
     });
@@ -547,16 +600,19 @@ static srigl_status structured_core(const void* x, srigl_dtype x_dtype, int32_t 
         hipLaunchKernelGGL(k_fill_ablated, grid, dim3(256), 0, st, active, n_active, bias, B, d_out, y);
         return hip_ok(hipGetLastError());
     }
+    const bool tile_ok = tile >= SRIGL_TILE_AUTO && tile <= SRIGL_TILE_64x64;
     if (splits == 0) {   // the library's choice of parts (and of the tile, unless forced)
-        srigl_gemm_tile t = SRIGL_TILE_AUTO;
-        choose_tile_and_split(B, n_active, d_in, d_out, x_dtype == SRIGL_F32, &t, &splits, nullptr);
-        if (tile != SRIGL_TILE_AUTO) splits = 1;   // a forced tile keeps the whole of d_in unless the parts are forced too
-        else tile = t;
+        const GemmChoice c = choose_gemm(B, n_active, d_in, d_out, x_dtype == SRIGL_F32, true);
+        splits = tile != SRIGL_TILE_AUTO ? 1 : c.splits;   // a forced tile keeps the whole of d_in unless the parts are forced too
+        if (tile == SRIGL_TILE_AUTO) tile = c.tile;
+    } else if (tile == SRIGL_TILE_AUTO) {   // one part by choice of the entry point, or the caller's parts
+        tile = splits == 1 ? choose_gemm(B, n_active, d_in, d_out, x_dtype == SRIGL_F32, false).tile : choose_tile(B, n_active, x_dtype == SRIGL_F32);
     }
     if (splits > 1) {
         const size_t need = (size_t)splits * B * n_active * sizeof(float);
         if (workspace == nullptr || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 3) != 0) return SRIGL_ERR_CAPACITY;
     }
+    if (!tile_ok) return SRIGL_ERR_INVALID_ARG;
     float* part = static_cast<float*>(workspace);
     if (x_dtype == SRIGL_F32) return launch_structured<float>(tile, x, B, d_in, Wd, active, n_active, bias, d_out, y, splits, part, st);
     return launch_structured<uint16_t>(tile, x, B, d_in, Wd, active, n_active, bias, d_out, y, splits, part, st);
@@ -578,7 +634,7 @@ srigl_status srigl_structured_split_plan(int32_t B, int32_t d_in, int32_t n_acti
                                          size_t* workspace_bytes) {
     if (B < 0 || d_in < 0 || n_active < 0 || d_out < 0 || (dtype != SRIGL_F32 && dtype != SRIGL_BF16)) return SRIGL_ERR_INVALID_ARG;
     int s = 1;
-    if (B > 0 && d_in > 0 && n_active > 0) choose_tile_and_split(B, n_active, d_in, d_out, dtype == SRIGL_F32, nullptr, &s, nullptr);
+    if (B > 0 && d_in > 0 && n_active > 0) s = choose_gemm(B, n_active, d_in, d_out, dtype == SRIGL_F32, true).splits;
     if (splits) *splits = s;
     if (workspace_bytes) *workspace_bytes = s > 1 ? (size_t)s * B * n_active * sizeof(float) : 0;
     return SRIGL_OK;

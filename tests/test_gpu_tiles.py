@@ -113,3 +113,27 @@ def test_activation_in_the_epilogue(act):
     got = run_tile(L, 16, act=act)
     want = np.maximum(plain, 0) if act == B_.ACT_RELU else torch.nn.functional.gelu(torch.from_numpy(plain)).numpy()
     assert np.abs(got - want).max() <= 2e-6 * max(1.0, np.abs(want).max())    # the activation of the same fp32 sums
+
+
+@pytest.mark.parametrize("B,n,d_in,ablated", [
+    (520, 16121, 136, 0), (1000, 8200, 72, 333), (1500, 5401, 264, 57),      # 256 x 192 tiles: rows, columns and depth end inside a tile
+])
+def test_structured_library_choice(B, n, d_in, ablated):
+    """The shape that only the library's own choice takes, against float64: two orders of one fp32 sum of d_in products differ by at most
+    d_in * 2^-23 of the sum of the magnitudes (bf16 products are exact in fp32)."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn(B, d_in, device="cuda", generator=g).bfloat16()
+    Wd = torch.randn(n, d_in, device="cuda", generator=g).bfloat16()
+    d_out = n + ablated
+    bias = torch.randn(d_out, device="cuda", generator=g)
+    active = torch.sort(torch.randperm(d_out, device="cuda", generator=g)[:n]).values
+    flat = torch.full((B * d_out + 2 * GUARD,), 777.0, device="cuda")
+    y = flat[GUARD:GUARD + B * d_out].view(B, d_out)
+    B_.srigl_structured_linear_fwd(x.view(torch.int16), B, d_in, Wd.view(torch.int16), active.int() if ablated else None, n, bias, d_out, y)
+    ref = bias.double().repeat(B, 1)
+    ref[:, active] += x.double() @ Wd.double().t()
+    bound = bias.abs().repeat(B, 1)
+    bound[:, active] += x.float().abs() @ Wd.float().abs().t()
+    worst = ((y - ref).abs() / (bound * (d_in + 1) * 2.0 ** -23)).max().item()
+    assert worst <= 1, worst
+    assert (flat[:GUARD] == 777.0).all() and (flat[GUARD + B * d_out:] == 777.0).all()
