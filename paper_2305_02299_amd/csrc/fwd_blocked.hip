@@ -12,13 +12,21 @@
 //
 // The blocked copy (srigl_block_terms) holds the terms of 32 stored rows x 64 columns next to each other, each as the weight
 // beside its place in the LDS tile: 64 lanes fetch up to 256 of them with one 16-byte load each and store them with four 2-byte
-// LDS writes each.  (From the row-major copies the same kernel needed 327 us instead of 251 (228 by now) on 4096 -> 16384, 13108 stored
+// LDS writes each.  (From the row-major copies the same kernel needed 327 us instead of 251 (201 by now) on 4096 -> 16384, 13108 stored
 // rows, K = 205, 2048 batch rows: every row's few terms of a piece were a cache line and a lane's predicated writes of their own.)
 //
 // Pipeline (an iteration is CC pieces of 64 columns): x of the next iteration goes from memory straight into the other of two LDS
-// stages while this one is multiplied, and the terms one iteration further ahead into a slot of each wavefront's own.  The weight
-// tile of it + 1 is built while the tile of it is multiplied; half of the wavefronts of a 256 x 256 tile build before they
-// multiply, the other half after it, so that a SIMD's two wavefronts do different things.
+// stages while this one is multiplied, and the terms one iteration further ahead into registers.  The weight tile of it + 1 is built while
+// the tile of it is multiplied; half of the wavefronts of a 256 x 256 tile build before they multiply, the other half after it, so that
+// a SIMD's two wavefronts do different things; by their priorities those that build late multiply first (s_setprio: without it a SIMD's two
+// wavefronts came to the end of their multiplications together, and the matrix units waited for the late builds).  A step's fragments
+// are read and x is requested between its multiplications, the reads in their first half.
+// What bounds it: the matrix units and the build between them; 4096 -> 16384 with 13108 stored rows, batch 2048, in 256 x 256 tiles: an
+// iteration of 2048 clocks of multiplications per SIMD took 3400, of which a build 600 and the requests of x 600 (14 instructions of
+// addresses each); with the terms in registers instead of an LDS slot, one instruction of addresses per request (a column past the rows' end
+// is their last one), reads between the multiplications and the priorities: 237 -> 201 us.  256 wide tiles of other layers 70 -> 58,
+// 32.1 -> 26.9, 192 wide 65 -> 57, 128 wide 275 -> 250, 17.5 -> 15.5, 64 wide 440 -> 397, 14.5 -> 13.6.  (Requests of x a step earlier, behind the
+// barrier: 242 us, every wavefront's at the same time.)
 // LDS layout of a stage: sub-tiles of 64 columns, a row 128 bytes, its 16-byte piece q in slot q ^ ((row >> 1) & 7), as in
 // structured.hip.  A wavefront clears and fills whole blocks: no barrier between the two, the LDS serves one wavefront's requests
 // in order.
@@ -264,10 +272,10 @@ __device__ __forceinline__ void mend_rows(const BlockedArgs& p, unsigned char* s
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 struct __attribute__((packed, aligned(2))) Half4 { uint32_t a, b; };
 
-// LDS: two stages of x, two of the weight tile, the lists, all of it reused by the epilogue's tile; behind it the epilogue's table
+// LDS: two stages of x, two of the weight tile, all of it reused by the epilogue's tile; behind it the epilogue's table
 template <int UA, int BM, int BN, int WGM, int WGN, int CC>
 constexpr size_t blocked_table_at() {
-    constexpr size_t stages = (size_t)CC * 128 * 2 * (BM + BN) + (size_t)WGM * WGN * UA * 1024, tile = EpiLayout<BN, WGM>::TILE_BYTES;
+    constexpr size_t stages = (size_t)CC * 128 * 2 * (BM + BN), tile = EpiLayout<BN, WGM>::TILE_BYTES;
     return stages > tile ? stages : tile;
 }
 
@@ -284,7 +292,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
     static_assert(BLOCKS <= NWAVES && (CC == 1 || BLOCKS == NWAVES), "one block per wavefront and iteration");
     static_assert(CC * BM % (8 * NWAVES) == 0 && WTM % 32 == 0 && WTN % 32 == 0 && BM % 16 == 0, "tile shape");
     unsigned char* const wstages = smem + 2 * XSTAGE;
-    unsigned char* const lstages = wstages + 2 * WSTAGE;
     unsigned char* const table = smem + blocked_table_at<UA, BM, BN, WGM, WGN, CC>();
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -296,35 +303,30 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
     const int n_chunks = (d_in + 63) >> 6, n_it = (n_chunks + CC - 1) / CC;
 
     // ---- x: a lane brings 16 bytes per pass; rows past the batch re-read the last one (never stored), pieces past the end of
-    // the rows come from zeros (DIRECT) or from whatever lies there (they meet zero weights only)
+    // the rows come from their last columns (DIRECT) or from whatever lies there (they meet zero weights only, and what is not finite
+    // in a row spoils its sums wherever it stands)
     uint32_t xoff[XP];   // element offset from the tile's first row, chunk 0 of the iteration
     int xcol[XP];
 #pragma unroll
     for (int q = 0; q < XP; ++q) {
         const int row = 8 * (q * NWAVES + wv) + (lane >> 3);   // row of the stage: sub-tile row / BM
         xcol[q] = (row / BM) * 64 + (((lane & 7) ^ ((row >> 1) & 7)) << 3);
-        xoff[q] = (uint32_t)min(row % BM, p.B - 1 - m0) * (uint32_t)d_in + (uint32_t)xcol[q];
+        xoff[q] = (uint32_t)min(row % BM, p.B - 1 - m0) * (uint32_t)d_in + (DIRECT ? 0u : (uint32_t)xcol[q]);
     }
     const uint16_t* const xtile = p.x + (size_t)m0 * d_in;
     const uint32_t xtotal = (uint32_t)min(p.B - m0, BM) * (uint32_t)d_in;
     Half4 xr[DIRECT ? 1 : XP][2];
-    auto issue_x = [&](int it) {
+    auto issue_piece = [&](int it, int q) {
         const int c0 = it * CC * 64;
         if (DIRECT) {
             unsigned char* stage = smem + (it & 1) * XSTAGE + 1024 * wv;
-#pragma unroll
-            for (int q = 0; q < XP; ++q) {
-                const void* g = xtile + xoff[q] + c0;
-                if (c0 + xcol[q] >= d_in) g = &g_zero16;   // (d_in is a multiple of 8: a piece is whole or absent)
-                __builtin_amdgcn_global_load_lds((gptr_t)g, (lptr_t)(stage + 1024 * NWAVES * q), 16, 0, 0);
-            }
+            uint32_t off = 2 * (xoff[q] + (uint32_t)min(c0 + xcol[q], d_in - 8));   // (d_in is a multiple of 8: a piece is whole or absent)
+            asm("" : "+v"(off));   // (a lane offset from a scalar base: seen to be 32 bits only next to the load)
+            __builtin_amdgcn_global_load_lds((gptr_t)(reinterpret_cast<const unsigned char*>(xtile) + off), (lptr_t)(stage + 1024 * NWAVES * q), 16, 0, 0);
         } else {
-#pragma unroll
-            for (int q = 0; q < XP; ++q) {
-                const uint16_t* g = xtile + min(xoff[q] + (uint32_t)c0, xtotal - 8u);   // (d_in >= 8: host)
-                xr[q][0] = *reinterpret_cast<const Half4*>(g);
-                xr[q][1] = *reinterpret_cast<const Half4*>(g + 4);
-            }
+            const uint16_t* g = xtile + min(xoff[q] + (uint32_t)c0, xtotal - 8u);   // (d_in >= 8: host)
+            xr[q][0] = *reinterpret_cast<const Half4*>(g);
+            xr[q][1] = *reinterpret_cast<const Half4*>(g + 4);
         }
     };
     auto store_x = [&](int it) {   // !DIRECT
@@ -354,35 +356,28 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
     const bool builds = BLOCKS == NWAVES || wv < BLOCKS;
     const bool has_rows = builds && group * kBlockRows < p.n_active;
     const uint32_t* const offs = p.table + (size_t)(has_rows ? group : 0) * (n_chunks + 1);
-    // lane l: where the lists of iterations 64 i + l begin and end, for even and for odd i
-    uint32_t even_lo = 0, even_hi = 0, odd_lo = 0, odd_hi = 0;
+    uint32_t list_lo = 0, list_hi = 0;   // lane l: where the lists of iterations 64 i + l begin and end
     auto load_offsets = [&](int it0) {
         const int c = (it0 + lane) * CC + sub;
         const bool in = has_rows && c < n_chunks;
-        const uint32_t lo = offs[in ? c : 0], hi = in ? offs[c + 1] : lo;
+        list_lo = offs[in ? c : 0];
+        list_hi = in ? offs[c + 1] : list_lo;
         wait_loads<0>();
-        if (it0 & 64) { odd_lo = lo; odd_hi = hi; } else { even_lo = lo; even_hi = hi; }
     };
-    auto list_of = [&](int it, uint32_t* lo, uint32_t* n) {
-        const bool odd = it & 64;
-        *lo = (uint32_t)__builtin_amdgcn_readlane((int)(odd ? odd_lo : even_lo), it & 63);
-        *n = (uint32_t)__builtin_amdgcn_readlane((int)(odd ? odd_hi : even_hi), it & 63) - *lo;
-    };
-    unsigned char* const list_slot = lstages + wv * UA * 1024;
-    auto fetch_units = [&](uint32_t lo, uint32_t n) {
+    // The units of a list wait in registers for the build, one iteration ahead (past the last iteration the last list again)
+    u32x4_t terms[UA];
+    uint32_t held_lo = 0, held_n = 0;
+    auto load_list = [&](int it) {
+        if (!builds) return;
+        if ((it & 63) == 0 && it < n_it) load_offsets(it);
+        const int at = min(it, n_it - 1) & 63;
+        held_lo = (uint32_t)__builtin_amdgcn_readlane((int)list_lo, at);
+        held_n = (uint32_t)__builtin_amdgcn_readlane((int)list_hi, at) - held_lo;
 #pragma unroll
         for (int i = 0; i < UA; ++i) {
             const uint32_t u = 64u * i + (uint32_t)lane;   // (lanes past the list share one address)
-            __builtin_amdgcn_global_load_lds((gptr_t)(p.lists + (size_t)(lo + (u < n ? u : 0u)) * 16), (lptr_t)(list_slot + 1024 * i), 16, 0, 0);
+            terms[i] = *reinterpret_cast<const u32x4_t*>(p.lists + (size_t)(held_lo + (u < held_n ? u : 0u)) * 16);
         }
-    };
-    // (past the last iteration the last list is fetched again: the number of loads in flight at each wait is fixed)
-    auto issue_list = [&](int it) {
-        if (!builds) return;
-        if ((it & 63) == 0 && it < n_it) load_offsets(it);
-        uint32_t lo, n;
-        list_of(min(it, n_it - 1), &lo, &n);
-        fetch_units(lo, n);
     };
     // (LDS instructions by hand: the compiler would have a write wait for every load into LDS that is in flight)
     auto lds_at = [](const unsigned char* q) { return (uint32_t)(uintptr_t)(lptr_t)q; };
@@ -390,26 +385,15 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
 #pragma unroll
         for (int t = 0; t < 4; ++t) asm volatile("ds_write_b16 %0, %1" ::"v"(block + (v[t] >> 16)), "v"(v[t]) : "memory");
     };
-    // A block is built from its list, which has landed: the terms into registers, the tile cleared, the terms to their places; the
-    // next list is requested into the slot that this one leaves.
+    // A block is built from its list: the tile is cleared and the terms are written to their places, behind the zeros in the order of the
+    // LDS; the next list is requested into the registers that this one leaves.
     auto build = [&](int it) {
         if (!builds) return;
         const uint32_t block = lds_at(wstages + (it & 1) * WSTAGE + wv * 4096), clear = block + (uint32_t)lane * 16u;
-        const uint32_t slot = lds_at(list_slot + lane * 16);
         const u32x4_t zero = {0u, 0u, 0u, 0u};
-        u32x4_t terms[UA];
-        // (one piece, so that nothing touches the registers before the reads have returned; the zeros may still be on their way)
-        if constexpr (UA == 1)
-            asm volatile("ds_read_b128 %0, %1\n\tds_write_b128 %2, %3\n\tds_write_b128 %2, %3 offset:1024\n\tds_write_b128 %2, %3 offset:2048\n\t"
-                         "ds_write_b128 %2, %3 offset:3072\n\ts_waitcnt lgkmcnt(4)"
-                         : "=&v"(terms[0]) : "v"(slot), "v"(clear), "v"(zero) : "memory");
-        else
-            asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:1024\n\tds_write_b128 %3, %4\n\tds_write_b128 %3, %4 offset:1024\n\t"
-                         "ds_write_b128 %3, %4 offset:2048\n\tds_write_b128 %3, %4 offset:3072\n\ts_waitcnt lgkmcnt(4)"
-                         : "=&v"(terms[0]), "=&v"(terms[UA - 1]) : "v"(slot), "v"(clear), "v"(zero) : "memory");
-        uint32_t lo, n;
-        list_of(it, &lo, &n);
-        issue_list(it + 1);
+        asm volatile("ds_write_b128 %0, %1\n\tds_write_b128 %0, %1 offset:1024\n\tds_write_b128 %0, %1 offset:2048\n\t"
+                     "ds_write_b128 %0, %1 offset:3072" ::"v"(clear), "v"(zero) : "memory");
+        const uint32_t lo = held_lo, n = held_n;
 #pragma unroll
         for (int i = 0; i < UA; ++i)
             if (64u * i + (uint32_t)lane < n) put4(block, terms[i]);
@@ -418,6 +402,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
                 const u32x4_t more = *reinterpret_cast<const u32x4_t*>(p.lists + (size_t)(lo + u + (uint32_t)lane) * 16);
                 put4(block, more);
             }
+        load_list(it + 1);
     };
 
     f32x16_t acc[TM][TN];
@@ -444,8 +429,9 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
 
     // ---- prologue (what the epilogue needs from memory is fetched here too, beside the first requests)
     const TileColumns cols = tile_columns(n0, BN, p.active, p.n_active, p.d_out);
-    issue_list(0);
-    issue_x(0);
+    load_list(0);
+#pragma unroll
+    for (int q = 0; q < XP; ++q) issue_piece(0, q);
     fill_table<BN, WGM, NWAVES * 64>(table, cols.lo, cols, n0, p.active, p.bias);
     if (!DIRECT) store_x(0);
     wait_loads<0>();
@@ -454,44 +440,63 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
 
     // The build of it + 1 stands before or behind the multiplications of it.
     bf16x8_t a[2][TM], b[2][TN];
-    auto read_frags = [&](int it, int kk, int set) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i) a[set][i] = x_frag(it, kk, i);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) b[set][j] = w_frag(it, kk, j);
+    constexpr int N_MMA = TM * TN, N_FRAG = TM + TN, N_READ = (N_MMA + 1) / 2;
+    auto read_frag = [&](int f, int it, int kk, int set) {   // in the order the products take them: a[0], the b's, the other a's
+        if (f >= 1 && f <= TN) b[set][f - 1] = w_frag(it, kk, f - 1);
+        else a[set][f ? f - TN : 0] = x_frag(it, kk, f ? f - TN : 0);
     };
-    read_frags(0, 0, 0);
+#pragma unroll
+    for (int f = 0; f < N_FRAG; ++f) read_frag(f, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(a[0][i]));
+#pragma unroll
+    for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(b[0][j]));
     const bool early = NWAVES > 4 && wv < NWAVES / 2;
     for (int it = 0; it < n_it; ++it) {
         const bool next = it + 1 < n_it;
+        if (NWAVES > 4) {
+            if (early) __builtin_amdgcn_s_setprio(0); else __builtin_amdgcn_s_setprio(1);
+        }
         if (early && next) {
-            wait_loads<0>();   // the list (the last iteration has waited for it, the prologue has not)
             build(it + 1);
         }
-        if (next) issue_x(it + 1);
+        if (!DIRECT && next) {
+#pragma unroll
+            for (int q = 0; q < XP; ++q) issue_piece(it + 1, q);
+        }
 #pragma unroll
         for (int kk = 0; kk < KSTEPS; ++kk) {
-            __builtin_amdgcn_s_waitcnt(kLgkm0);   // this step's fragments, requested a step ago, before the next one's are
-            if (kk + 1 < KSTEPS) {
-                read_frags(it, kk + 1, (kk + 1) & 1);
-            } else if (next) {
-                if (!DIRECT) store_x(it + 1);
-                wait_loads<0>();   // x of it + 1; the list
-                if (!early) build(it + 1);
+            const bool last = kk + 1 == KSTEPS;
+            if (last) {
+                if (NWAVES > 4) {
+                    if (early) __builtin_amdgcn_s_setprio(1); else __builtin_amdgcn_s_setprio(0);
+                }
+                if (next) {
+                    __builtin_amdgcn_s_waitcnt(kLgkm0);
+                    if (!DIRECT) store_x(it + 1);
+                    wait_loads<0>();   // x of it + 1; the list
+                    if (!early) build(it + 1);
+                }
                 lds_barrier();   // stage it + 1 is complete, every fragment of stage it is in registers
-                read_frags(it + 1, 0, 0);
             }
-            __builtin_amdgcn_sched_barrier(0);   // a step's fragments are requested a whole step ahead
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk & 1][i], b[kk & 1][j], acc[i][j], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int m = 0; m < N_MMA; ++m) {
+#pragma unroll
+                for (int f = m * N_FRAG / N_READ; f < (m + 1) * N_FRAG / N_READ && f < N_FRAG; ++f)
+                    read_frag(f, last ? it + 1 : it, last ? 0 : kk + 1, (kk + 1) & 1);
+                if (N_MMA > 1) acc[m / TN][m % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk & 1][m / TN], b[kk & 1][m % TN], acc[m / TN][m % TN], 0, 0, 0);
+                if (DIRECT && kk == 0) {
+#pragma unroll
+                    for (int q = m * XP / N_MMA; q < (m + 1) * XP / N_MMA; ++q) issue_piece(it + 1, q);
+                }
+                if (N_MMA == 1) acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk & 1][0], b[kk & 1][0], acc[0][0], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     }
 
-    wait_loads<0>();   // the repeated last list may still be landing
+    wait_loads<0>();   // x past the last iteration
     lds_barrier();
     store_tile<BM, BN, WGM, WGN, true>(smem, table, true, acc, cols, m0, n0, p.B, p.active, p.bias, p.d_out, p.y, p.act, spoiled);
     lds_barrier();
@@ -548,47 +553,56 @@ static srigl_status launch_plan(BlockedArgs& p, int code, hipStream_t st) {
     return launch_shape<UA, DIRECT>(p, second, p.n_active - (int)split, st);
 }
 
-// Estimated time (us) of n stored rows in a tile shape.  Fits of measurements on 13 layers (200..4096 wide, 300..16192 stored rows,
-// 80-98 % sparse) at batches of 32 to 2048: a workgroup costs a fixed part (prologue, epilogue) and a part per iteration; a compute
-// unit holds one workgroup of the two large shapes, or two of the others, which then run slower each.  On 168 later points (21 layers,
-// batches of 16 to 2048) the root mean square of the deviation is 9 to 12 % by shape, 2 % on average for the shape taken.
-static double blocked_tile_us(int tile, int B, int n, int chunks) {
-    const int bn = blocked_tile_rows(tile), bm = bn == 192 ? 256 : bn;
-    const double w = (double)((B + bm - 1) / bm) * ((n + bn - 1) / bn), it64 = (chunks + 1) / 2;
-    switch (tile) {
-        case SRIGL_BLOCKED_64: return 3.0 + (w <= 256 ? 0.8 * it64 + 1.7 : std::ceil(w / 512) * (1.05 * it64 + 2.5));
-        case SRIGL_BLOCKED_128: return 3.0 + (w <= 256 ? 4.5 + 0.85 * chunks : std::ceil(w / 512) * (7.0 + 1.1 * chunks));
-        case SRIGL_BLOCKED_192: return 3.0 + std::ceil(w / 256) * (10.0 + 1.3 * chunks);
-        default: return 3.0 + std::ceil(w / 256) * (11.0 + 1.6 * chunks);
-    }
+// Estimated time (us) of n stored rows in a tile shape, their share of the result `columns` wide.  Least squares on 99 layers and batches
+// (200 to 4096 wide, 300 to 16192 stored rows, 80 to 98 % sparse, batches 64 to 2048): a round of workgroups costs a fixed part (prologue,
+// epilogue), more with ablated neurons among the columns, and a part per 64 columns of x, more where rows of x go through registers; a
+// compute unit holds one workgroup of the two large shapes, or two of the others.  The root mean square of the deviation is 4 to 5 % by shape,
+// the shape of smallest estimate 0.3 % behind the fastest on average.
+struct BlockedModel { double one, chunk_one, fixed, round, chunk, ragged, ablated, bytes; int slots; };
+static double blocked_tile_us(int tile, int B, int n, double columns, int d_in, bool ablated) {
+    static const BlockedModel kModels[] = {   // one, chunk_one: all workgroups at once, one to a compute unit
+        {6.0, 0.268, 4.8, 0.7, 0.407, 0.113, 1.2, 1.1, 512},
+        {8.5, 0.542, 6.2, 1.1, 0.885, 0.196, 3.4, 0.63, 512},
+        {11.0, 1.190, 1.8, 9.2, 1.190, 0.226, 6.5, 0.50, 256},
+        {10.6, 0.985, 2.3, 8.3, 0.985, 0.241, 1.3, 0.64, 256},
+    };
+    const BlockedModel& m = kModels[tile - 1];
+    const int bn = blocked_tile_rows(tile), bm = bn == 192 ? 256 : bn, chunks = (d_in + kSegCols - 1) / kSegCols;
+    const double w = (double)((B + bm - 1) / bm) * ((n + bn - 1) / bn), rounds = std::ceil(w / m.slots);
+    const double more = (d_in % 8 != 0 ? m.ragged * chunks : 0.0) + (ablated ? m.ablated : 0.0);
+    const double us = w <= 256 ? m.one + m.chunk_one * chunks + more : m.fixed + rounds * (m.round + m.chunk * chunks + more);
+    return us + m.bytes * 1e-6 * B * columns;
 }
 
-// The tile code of smallest estimate.  Tiles of 256 x 256 are the most efficient ones, but 416 of them (13108 stored rows, batch 2048)
-// keep 256 compute units busy for two whole rounds where 1.6 would do.  So the large shapes are also tried for their full rounds
-// only, with the stored rows that are left in the shape that suits those.  Measured: that layer 236 -> 228 us (a part-filled round
-// runs faster than a full one, so less than the count of rounds promises); 546 -> 16192 at batch 606 in 256 x 192 tiles 26 us, 28 in
-// 256 x 256, 34 in 128 x 128.  kSplitUs: what the second launch adds (its estimate counts a start of its own; the first one's last workgroups
-// and its power draw cost more).  Of 128 points (768- to 4096-wide, 2560 to 16000 stored rows, batches 600 to 2048) the shape taken is on
-// average 0.4 % behind the fastest of up to 12, at worst 8 %; with -1 in its place 11 %.
-constexpr double kSplitUs = 4.0;
-static int choose_blocked_tile(int B, int d_in, int n_active, double* us) {
-    const int chunks = (d_in + kSegCols - 1) / kSegCols;
+// The tile code of smallest estimate.  The large shapes are also tried for their full rounds of workgroups only, with the stored rows that
+// are left in the shape that suits those, and taken where that promises 8 % (3016 -> 9749 at batch 1765 in 256 and then 64 wide tiles 106 us, 135
+// in one shape; 13108 at 2048, d_in 4096, in 256 and then 192 wide ones, 7 % ahead by the estimate, 215 us against 206: the second
+// launch's start and the power that a full round draws).  On 42 points (600- to 4096-wide, 2500 to 16000 stored rows, batches 600 to 2048)
+// the code taken is 0.8 % behind the fastest of up to 10 on average, 9 % at worst; 1.8 % (28 %) with one shape only.
+constexpr double kSplitGain = 0.92;
+static int choose_blocked_tile(int B, int d_in, int n_active, int d_out, double* us) {
     constexpr int kShapes[] = {SRIGL_BLOCKED_64, SRIGL_BLOCKED_128, SRIGL_BLOCKED_192, SRIGL_BLOCKED_256};
+    const bool ablated = n_active < d_out;
+    const double per_row = (double)d_out / n_active;
     int best = 0;
     *us = 0.0;
     auto consider = [&](int code, double t) {
         if (best == 0 || t < *us) { best = code; *us = t; }
     };
-    for (int s : kShapes) consider(s, blocked_tile_us(s, B, n_active, chunks));
+    for (int s : kShapes) consider(s, blocked_tile_us(s, B, n_active, d_out, d_in, ablated));
+    const double split_below = kSplitGain * *us;
     for (int first : {SRIGL_BLOCKED_256, SRIGL_BLOCKED_192}) {
         const int bn = blocked_tile_rows(first);
         const long long tiles_m = (B + 255) / 256, tiles_n = (n_active + bn - 1) / bn, rounds = tiles_m * tiles_n / 256;
         const long long columns = rounds * 256 / tiles_m;
         if (columns < 1 || columns >= tiles_n || columns >= (1 << 23)) continue;
-        const int done = (int)columns * bn;
-        const double head = blocked_tile_us(first, B, done, chunks);
+        const int done = (int)columns * bn, left = n_active - done;
+        const double head = blocked_tile_us(first, B, done, done * per_row, d_in, ablated);
         for (int s : kShapes)
-            if (s != first) consider(first | s << 4 | (int)columns << 8, head + blocked_tile_us(s, B, n_active - done, chunks) + kSplitUs);
+            if (s != first) {
+                const double both = head + blocked_tile_us(s, B, left, left * per_row, d_in, ablated);
+                if (both < split_below) consider(first | s << 4 | (int)columns << 8, both);
+            }
     }
     return best;
 }
@@ -610,7 +624,7 @@ static bool blocked_fits(int n_active, int K, int d_in) {
 double blocked_estimate_us(int B, int d_in, int n_active, int K, int d_out) {
     if (B <= 0 || n_active > d_out || K > d_in || !blocked_fits(n_active, K, d_in)) return 1e30;
     double us;
-    choose_blocked_tile(B, d_in, n_active, &us);
+    choose_blocked_tile(B, d_in, n_active, d_out, &us);
     return us + block_terms_us(n_active, K);
 }
 
@@ -631,7 +645,7 @@ static int32_t blocked_tile(int32_t B, int32_t d_in, int32_t n_active, int32_t K
     static thread_local DecisionCache<Key, int, 64> cache;
     return cache.get(Key{B, d_in, n_active, K, d_out, with_copy}, [&] {
         double us;
-        const int tile = choose_blocked_tile(B, d_in, n_active, &us);
+        const int tile = choose_blocked_tile(B, d_in, n_active, d_out, &us);
         if (with_copy) us += block_terms_us(n_active, K);
         return us < kBlockedMargin * condensed_estimate_us(B, d_in, n_active, K, d_out, true, n_active < d_out) ? tile : 0;
     });
@@ -692,7 +706,7 @@ srigl_status srigl_blocked_linear_fwd(const void* x, int32_t B, int32_t d_in, co
     const bool two = 2048.0 * K / d_in > 240.0;
     hipStream_t st = static_cast<hipStream_t>(stream);
     double us;
-    if (tile == 0) tile = choose_blocked_tile(B, d_in, n_active, &us);
+    if (tile == 0) tile = choose_blocked_tile(B, d_in, n_active, d_out, &us);
     if (direct) return two ? launch_plan<2, true>(p, tile, st) : launch_plan<1, true>(p, tile, st);
     return two ? launch_plan<2, false>(p, tile, st) : launch_plan<1, false>(p, tile, st);
 }
