@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import synth_inputs as si
-from gpu_util import TOL_BF16, TOL_F32, dev, gate, oracle_condensed
+from gpu_util import TOL_BF16, TOL_F32, dev, gate, oracle_condensed, oracle_seg
 from paper_2305_02299_amd import binding as B_
 
 pytestmark = pytest.mark.gpu
@@ -137,3 +137,29 @@ def test_structured_library_choice(B, n, d_in, ablated):
     worst = ((y - ref).abs() / (bound * (d_in + 1) * 2.0 ** -23)).max().item()
     assert worst <= 1, worst
     assert (flat[:GUARD] == 777.0).all() and (flat[GUARD + B * d_out:] == 777.0).all()
+
+
+@pytest.mark.parametrize("tile", [B_.BLOCKED_64, B_.BLOCKED_128, B_.BLOCKED_192, B_.BLOCKED_256])
+@pytest.mark.parametrize("d_in,K", [(8, 3), (72, 20), (136, 70), (776, 60), (4104, 90), (8328, 500)])
+def test_blocked_rows_that_end_inside_a_piece(d_in, K, tile):
+    """Rows of whole 16-byte pieces that end inside a piece of 64 columns (the rest of it comes from the row's last columns and meets zero
+    weights), one to more than 64 iterations, lists of more and of fewer terms than are fetched ahead; the last columns of one row are not
+    finite and no neuron reads them."""
+    B, d_out = 70, 300
+    rng = np.random.default_rng(d_in)
+    used = max(K, d_in - 8)
+    idx = np.sort(np.argsort(rng.random((d_out, used)), axis=1)[:, :K], axis=1).astype(np.int32)
+    Wf, xf = rng.standard_normal((d_out, K)).astype(np.float32), rng.standard_normal((B, d_in)).astype(np.float32)
+    W, x = torch.from_numpy(Wf).bfloat16().cuda(), torch.from_numpy(xf).bfloat16().cuda()
+    if d_in > 8:
+        x[B - 1, -8:] = float("nan")
+    idx_d = torch.from_numpy(idx).cuda()
+    seg = dev(oracle_seg(idx, d_in))
+    blk = torch.empty(B_.srigl_blocked_bytes(d_out, K, d_in), dtype=torch.uint8, device="cuda")
+    B_.srigl_block_terms(W, idx_d, seg, d_out, K, d_in, blk)
+    y = torch.full((B, d_out), float("nan"), device="cuda")
+    B_.srigl_blocked_linear_fwd(x, B, d_in, blk, W, idx_d, None, d_out, K, None, d_out, y, tile=tile)
+    xd, Wd = x.double().cpu().numpy(), W.double().cpu().numpy()
+    want = np.stack([(Wd[s] * xd[:, idx[s]]).sum(axis=1) for s in range(d_out)], axis=1)
+    scale = np.stack([np.abs(Wd[s] * xd[:, idx[s]]).sum(axis=1) for s in range(d_out)], axis=1)
+    assert (np.abs(y.cpu().numpy() - want) <= scale * (K + 1) * 2.0 ** -23).all()   # exact products, fp32 sums of K of them
