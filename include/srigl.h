@@ -234,9 +234,9 @@ srigl_status srigl_fwd_plan_query_algo(int32_t B, int32_t d_in, int32_t n_active
  * v * Phi(v) with the normal distribution function (erf form). */
 typedef enum srigl_activation { SRIGL_ACT_NONE = 0, SRIGL_ACT_RELU = 1, SRIGL_ACT_GELU = 2 } srigl_activation;
 
-/* The forward call in the whole-input batched kernel (SRIGL_FWD_ROWLOOP) in a tile of 16, 32 or 64 batch rows (0: the library's
+/* The forward call in the whole-input batched kernel (SRIGL_FWD_ROWLOOP) in a tile of 8, 16, 32 or 64 batch rows (0: the library's
  * choice) with rows_per_wave stored rows to a wavefront (0: likewise) and xcd_order as in srigl_fwd_tuning, on rows of any length
- * that fit the LDS (up to about 2500, 1250 and 600 columns) and with 16- or 32-bit indices (idx_bits).  For tests and measurements:
+ * that fit the LDS (up to 4096, about 2500, 1250 and 600 columns) and with 16- or 32-bit indices (idx_bits).  For tests and measurements:
  * SRIGL_FWD_AUTO takes this kernel, in these tiles, where it expects it to be the fastest; srigl_fwd_tile_query says in which (0: in
  * none) and with how many stored rows to a wavefront.  srigl_fwd_plan_query describes the choice among what the algorithms above
  * can be asked for (tiles of 32 and 64 rows, d_in a multiple of 16), which is what runs where the query here says 0. */

@@ -300,7 +300,7 @@ def srigl_fwd_plan_query(B, d_in, n_active, K, d_out, dtype_code=F32, has_active
 
 
 def srigl_condensed_linear_fwd_tile(x, B, d_in, W_c, idx, active, n_active, K, bias, d_out, y, act=None, tile_rows=0, rows_per_wave=0, xcd_order=0):
-    """The forward call in the whole-input batched kernel, in a tile of 16, 32 or 64 batch rows (0: the library's choice)."""
+    """The forward call in the whole-input batched kernel, in a tile of 8, 16, 32 or 64 batch rows (0: the library's choice)."""
     _check(lib.srigl_condensed_linear_fwd_tile(_ptr(x), _dtype_code(x), int(B), int(d_in), _ptr(W_c), _dtype_code(W_c), _ptr(idx),
                                                32 if idx.dtype == torch.int32 else 16, _ptr(active), int(n_active), int(K), _ptr(bias), int(d_out),
                                                _ptr(y), int(act or ACT_NONE), int(tile_rows), int(rows_per_wave), int(xcd_order), _stream()),

@@ -843,7 +843,7 @@ struct FwdDecision {
     srigl_fwd_algo algo;
     KlanePlan klane;
     RowlanePlan rowlane;
-    RowloopPlan rowloop;   // (not the caller's SRIGL_FWD_ROWLOOP alone: tiles of 16 rows and rows of any length too)
+    RowloopPlan rowloop;   // (not the caller's SRIGL_FWD_ROWLOOP alone: tiles of 8 and 16 rows and rows of any length too)
 };
 static const FwdDecision& decide_fwd(const FwdArgs& a) {
     struct Key { int32_t B, d_in, n_active, K, d_out, flags; };
@@ -946,7 +946,7 @@ srigl_status srigl_condensed_linear_fwd_tile(const void* x, srigl_dtype x_dtype,
                                              const float* bias, int32_t d_out, float* y, srigl_activation act, int32_t tile_rows,
                                              int32_t rows_per_wave, int32_t xcd_order, void* stream) {
     if (idx_bits != 16 && idx_bits != 32) return SRIGL_ERR_INVALID_ARG;
-    if ((tile_rows != 0 && tile_rows != 16 && tile_rows != 32 && tile_rows != 64) || rows_per_wave < 0 || xcd_order < 0 || xcd_order > 2)
+    if ((tile_rows != 0 && tile_rows != 8 && tile_rows != 16 && tile_rows != 32 && tile_rows != 64) || rows_per_wave < 0 || xcd_order < 0 || xcd_order > 2)
         return SRIGL_ERR_INVALID_ARG;
     const int32_t tile[3] = {tile_rows, rows_per_wave, xcd_order};
     return fwd_core(x, x_dtype, B, d_in, W_c, w_dtype, idx, idx_bits == 16, active, n_active, K, bias, d_out, y, nullptr, nullptr, SRIGL_FWD_AUTO, nullptr,

@@ -9,24 +9,28 @@ static double term_bytes(const FwdArgs& a) { return (double)a.n_active * a.K * (
 
 // Estimated time (us) of a launch shape: per round of workgroups on the busiest XCD a constant, the tile (words staged; beyond 16 K words
 // more from the second round on, when no wavefronts start under its loads any more), and per stored row of a wavefront a step
-// per 16 terms and a constant (another where terms beyond 256 are walked in a loop); the bytes of y; the bytes the XCDs' L2 caches
+// per 16 terms (32 in 8-row tiles) and a constant (another where terms beyond 256 are walked in a loop); the bytes of y; the bytes the XCDs' L2 caches
 // fetch (all of them the one array, each its share of the other).  Non-negative least squares on the relative error of 2600 launches
 // (each tile, shapes within 1.6 times the fastest; 67 layers 112 to 2400 wide, fan-ins 6 to 384, both types, batches 8 to 2048, cached
-// operands): standard deviation 7 to 9 %.  The shape of smallest estimate was 0.6 % behind the best measured one on average over
+// operands; 8-row tiles: 2800 launches, 297 layers 700 to 4096 wide, fan-ins to 806): standard deviation 6.5 to 9 %.  The shape of smallest estimate was 0.6 % behind the best measured one on average over
 // 304 points.
 static double rowloop_us(const FwdArgs& a, const RowloopPlan& p) {
     struct Fit { double fixed, round, word, big, step, row, y, fetched, long_row; };
-    static const Fit fits[3] = {{2.231, 2.147, 0.2049e-4, 0.585e-4, 0.0545, 0.0423, 2.128e-6, 0.0585e-6, 0.2256},
+    static const Fit fits[4] = {{2.817, 2.003, 0.2907e-4, 0.292e-4, 0.0683, 0.0931, 2.549e-6, 0.0338e-6, 0.1623},
+                                {2.231, 2.147, 0.2049e-4, 0.585e-4, 0.0545, 0.0423, 2.128e-6, 0.0585e-6, 0.2256},
                                 {3.522, 1.023, 0.1370e-4, 1.2465e-4, 0.0866, 0.0701, 1.613e-6, 0.0430e-6, 0.5675},
                                 {3.131, 1.348, 0.2724e-4, 0.3693e-4, 0.1745, 0.0951, 1.378e-6, 0.0448e-6, 0.0}};
-    const Fit& f = fits[p.BT == 16 ? 0 : p.BT == 32 ? 1 : 2];
-    const int steps = p.ST < 16 || a.K <= 256 ? p.ST : 16 + 4 * ((a.K - 256 + 63) / 64);
+    const Fit& f = fits[p.BT == 8 ? 0 : p.BT == 16 ? 1 : p.BT == 32 ? 2 : 3];
+    const int steps = a.K <= 256 ? p.ST : p.BT == 8 ? 8 + 2 * ((a.K - 256 + 63) / 64) : 16 + 4 * ((a.K - 256 + 63) / 64);
     const int rows = std::min((p.NG + p.NW - 1) / p.NW, (a.n_active + p.NW - 1) / p.NW);   // of the busiest wavefront
     const double fetched = p.bt_major ? x_bytes(a) + 8 * term_bytes(a) : 8 * x_bytes(a) + term_bytes(a);
     const double words = (double)p.BT * ((a.d_in + 15) / 16 * 16);
     return f.fixed + p.rounds * (f.round + f.word * words + rows * (f.step * steps + f.row + (a.K > 256 ? f.long_row : 0.0)) * p.NW / 16.0) +
            (p.rounds - 1) * f.big * std::max(0.0, words - 16384) + f.y * a.B * a.d_out + f.fetched * fetched;
 }
+
+// Columns of a tile: whole units of its staging.
+static int tile_columns_of(const FwdArgs& a, int BT) { return BT < 16 ? (a.d_in + 31) / 32 * 32 : (a.d_in + 15) / 16 * 16; }
 
 // Rows per workgroup the result tile (and, with an active list, a column table of twice as many columns) has room for.
 static long long rowloop_room(const FwdArgs& a, size_t tile, int BT) {
@@ -38,7 +42,7 @@ static long long rowloop_room(const FwdArgs& a, size_t tile, int BT) {
 // The launch of p.BT batch rows x NG stored rows per workgroup.
 static RowloopPlan rowloop_shape(const FwdArgs& a, RowloopPlan p, int NG, int xcd_order) {
     p.NG = NG;
-    const int steps = (a.K + 15) / 16;
+    const int steps = p.BT == 8 ? std::min((a.K + 31) / 32, 8) : (a.K + 15) / 16;
     p.ST = steps <= 8 ? steps : std::min((steps + 1) / 2 * 2, 16);   // (the kernel has these; a row one step short of an even number walks one of padding)
     p.n_btiles = (a.B + p.BT - 1) / p.BT;
     p.n_groups = (a.n_active + NG - 1) / NG;
@@ -57,7 +61,7 @@ static RowloopPlan rowloop_shape(const FwdArgs& a, RowloopPlan p, int NG, int xc
 // the workgroup's columns; with an active list the bias and the column table of a run of up to span_cap columns).
 static RowloopPlan rowloop_finish(const FwdArgs& a, RowloopPlan p) {
     p.ok = false;
-    const int C = (a.d_in + 15) / 16 * 16;
+    const int C = tile_columns_of(a, p.BT);
     p.out_off = (C + 1) * p.BT;
     const size_t used = ((size_t)p.out_off + (size_t)p.BT * (p.NG | 1) + (a.active ? 0 : (size_t)p.NG)) * sizeof(float);
     if (used > kLdsMax) return p;
@@ -105,16 +109,16 @@ RowloopPlan plan_rowloop(const FwdArgs& a, const srigl_fwd_tuning* t, double* us
     return p;
 }
 
-// The library's own choice of a tile: 16, 32 or 64 batch rows, rows of any length.
+// The library's own choice of a tile: 8, 16, 32 or 64 batch rows, rows of any length.
 RowloopPlan plan_tile(const FwdArgs& a, int tile_rows, int rows_per_wave, int xcd_order, double* us) {
     RowloopPlan best{};
     if (a.B <= 0 || a.n_active <= 0 || a.K <= 0 || a.d_in < 16 || a.d_in > 4096) return best;
-    for (int BT = 16; BT <= 64; BT *= 2) {
+    for (int BT = 8; BT <= 64; BT *= 2) {
         if (tile_rows && tile_rows != BT) continue;
         RowloopPlan p{};
         p.BT = BT;
         p.NW = 16;
-        const size_t tile = (size_t)((a.d_in + 15) / 16 * 16 + 1) * BT * sizeof(float);
+        const size_t tile = (size_t)(tile_columns_of(a, BT) + 1) * BT * sizeof(float);
         double t = 0.0;
         p = rowloop_best(a, p, rowloop_room(a, tile, BT), rows_per_wave, xcd_order, &t);
         if (p.ok && (!best.ok || t < *us)) { best = p; *us = t; }

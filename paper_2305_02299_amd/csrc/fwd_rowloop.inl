@@ -9,7 +9,7 @@
 // the batch tile of x, which every workgroup of the chunked kernel stages again for every 16-128 stored rows, is staged
 // once per several hundred: at 1024 batch rows on a 768-wide input 8 groups of stored rows instead of 24.
 //
-// Tile: 16, 32 or 64 batch rows (4, 8 or 16 per lane); the 64 lanes are 16 groups of four, and every group works on a term of its
+// Tile: 8, 16, 32 or 64 batch rows (4, 4, 8 or 16 per lane); from 16 rows on the 64 lanes are 16 groups of four, and every group works on a term of its
 // own, so a step takes 16 terms of a row: one 16-byte LDS read per four batch rows of a lane, and quad_perm broadcasts put the
 // weight into the multiply-add and the column into the LDS address.  (Groups of 16 lanes with two rows per lane, four terms to a step, as this
 // kernel was built first, read 8 bytes per lane at 105 bytes per clock and compute unit and issued three vector instructions for
@@ -18,6 +18,10 @@
 // columns, K = 216 at 256, in place of the chunked kernel 13.7 -> 9.4; 1000 -> 777, K = 50 at 300 15.8 -> 7.4.)
 // What bounds it: vector instructions (the multiply-adds are half of them) and LDS reads in equal parts, behind a fixed 5 to 6 us of
 // launching 4096 wavefronts, staging the tile and writing y.
+// Inputs of 2500 to 4096 columns, which leave room for 8 batch rows: 32 groups of two lanes, 32 terms to a step, the same reads and
+// instructions per term and row.  In place of the chunked kernel 3072 -> 768, K = 307 at batch 256 16.8 -> 11.1 us, 538 stored at 64 10.6 -> 8.4,
+// 4096 -> 1024, K = 205 at 512 23.9 -> 19.1, 2816 -> 768 bf16, K = 113 at 1527 35.6 -> 27.6; on 147 points that take it 1.49 times faster on
+// average, none slower.
 // Rows of 64 tiles only pay on inputs up to about 400 columns wide, where they still leave room for a hundred stored rows.
 // Terms: 64 consecutive ones of a row to a vector load, requested two rows ahead.
 #pragma once
@@ -27,40 +31,42 @@ namespace srigl {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) f32x4 LdsF32x4;
-// acc[0..3] += w[lane Q of this group of four] * x, or = with FIRST.  (The s_nop covers the two wait states a DPP read needs after
+// acc[0..3] += w[lane Q of this group of GL lanes] * x, or = with FIRST.  (The s_nop covers the two wait states a DPP read needs after
 // a VALU write of its source: the compiler does not look into the block.)
-template <int Q, bool FIRST>
-__device__ __forceinline__ void fmac4_quad_bcast(float* acc, float w, const f32x4& x) {
-#define SRIGL_QUAD " quad_perm:[%9,%9,%9,%9] row_mask:0xf bank_mask:0xf bound_ctrl:1"
+template <int GL, int Q, bool FIRST>
+__device__ __forceinline__ void fmac4_bcast(float* acc, float w, const f32x4& x) {
+#define SRIGL_GROUP " quad_perm:[%9,%9,%10,%10] row_mask:0xf bank_mask:0xf bound_ctrl:1"
     if constexpr (FIRST)
-        asm("s_nop 1\n\tv_mul_f32_dpp %0, %4, %5" SRIGL_QUAD "\n\tv_mul_f32_dpp %1, %4, %6" SRIGL_QUAD
-            "\n\tv_mul_f32_dpp %2, %4, %7" SRIGL_QUAD "\n\tv_mul_f32_dpp %3, %4, %8" SRIGL_QUAD
+        asm("s_nop 1\n\tv_mul_f32_dpp %0, %4, %5" SRIGL_GROUP "\n\tv_mul_f32_dpp %1, %4, %6" SRIGL_GROUP
+            "\n\tv_mul_f32_dpp %2, %4, %7" SRIGL_GROUP "\n\tv_mul_f32_dpp %3, %4, %8" SRIGL_GROUP
             : "=&v"(acc[0]), "=&v"(acc[1]), "=&v"(acc[2]), "=&v"(acc[3])
-            : "v"(w), "v"(x.x), "v"(x.y), "v"(x.z), "v"(x.w), "n"(Q));
+            : "v"(w), "v"(x.x), "v"(x.y), "v"(x.z), "v"(x.w), "n"(Q), "n"(GL == 4 ? Q : Q + 2));
     else
-        asm("s_nop 1\n\tv_fmac_f32_dpp %0, %4, %5" SRIGL_QUAD "\n\tv_fmac_f32_dpp %1, %4, %6" SRIGL_QUAD
-            "\n\tv_fmac_f32_dpp %2, %4, %7" SRIGL_QUAD "\n\tv_fmac_f32_dpp %3, %4, %8" SRIGL_QUAD
+        asm("s_nop 1\n\tv_fmac_f32_dpp %0, %4, %5" SRIGL_GROUP "\n\tv_fmac_f32_dpp %1, %4, %6" SRIGL_GROUP
+            "\n\tv_fmac_f32_dpp %2, %4, %7" SRIGL_GROUP "\n\tv_fmac_f32_dpp %3, %4, %8" SRIGL_GROUP
             : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
-            : "v"(w), "v"(x.x), "v"(x.y), "v"(x.z), "v"(x.w), "n"(Q));
-#undef SRIGL_QUAD
+            : "v"(w), "v"(x.x), "v"(x.y), "v"(x.z), "v"(x.w), "n"(Q), "n"(GL == 4 ? Q : Q + 2));
+#undef SRIGL_GROUP
 }
-// (lane Q of this group of four) ^ piece: the LDS addresses of a term's pieces
-template <int Q>
-__device__ __forceinline__ void xor_quad_bcast(int ov, const int (&piece)[1], int (&at)[1]) {
-    asm("s_nop 1\n\tv_xor_b32_dpp %0, %1, %2 quad_perm:[%3,%3,%3,%3] row_mask:0xf bank_mask:0xf bound_ctrl:1" : "=v"(at[0]) : "v"(ov), "v"(piece[0]), "n"(Q));
+// (lane Q of this group) ^ piece: the LDS addresses of a term's pieces
+template <int GL, int Q>
+__device__ __forceinline__ void xor_bcast(int ov, const int (&piece)[1], int (&at)[1]) {
+    asm("s_nop 1\n\tv_xor_b32_dpp %0, %1, %2 quad_perm:[%3,%3,%4,%4] row_mask:0xf bank_mask:0xf bound_ctrl:1"
+        : "=v"(at[0]) : "v"(ov), "v"(piece[0]), "n"(Q), "n"(GL == 4 ? Q : Q + 2));
 }
-template <int Q>
-__device__ __forceinline__ void xor_quad_bcast(int ov, const int (&piece)[2], int (&at)[2]) {
+template <int GL, int Q>
+__device__ __forceinline__ void xor_bcast(int ov, const int (&piece)[2], int (&at)[2]) {
+    static_assert(GL == 4, "one piece per lane in groups of two");
     asm("s_nop 1\n\tv_xor_b32_dpp %0, %2, %3 quad_perm:[%5,%5,%5,%5] row_mask:0xf bank_mask:0xf bound_ctrl:1"
         "\n\tv_xor_b32_dpp %1, %2, %4 quad_perm:[%5,%5,%5,%5] row_mask:0xf bank_mask:0xf bound_ctrl:1"
         : "=&v"(at[0]), "=&v"(at[1]) : "v"(ov), "v"(piece[0]), "v"(piece[1]), "n"(Q));
 }
-template <int Q>
-__device__ __forceinline__ void xor_quad_bcast(int ov, const int (&piece)[4], int (&at)[4]) {
+template <int GL, int Q>
+__device__ __forceinline__ void xor_bcast(int ov, const int (&piece)[4], int (&at)[4]) {
     const int lo[2] = {piece[0], piece[1]}, hi[2] = {piece[2], piece[3]};
     int l[2], h[2];
-    xor_quad_bcast<Q>(ov, lo, l);
-    xor_quad_bcast<Q>(ov, hi, h);
+    xor_bcast<GL, Q>(ov, lo, l);
+    xor_bcast<GL, Q>(ov, hi, h);
     at[0] = l[0]; at[1] = l[1]; at[2] = h[0]; at[3] = h[1];
 }
 template <int N>
@@ -68,55 +74,55 @@ __device__ __forceinline__ float row_ror(float v) {   // the value N lanes below
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, true));
 }
 
-constexpr int kQuadBlock = 64;   // terms a wavefront's vector load of W_c / idx brings: 16 groups of lanes x 4 steps
+constexpr int kQuadBlock = 64;   // terms a wavefront's vector load of W_c / idx brings: 16 groups of lanes x 4 steps, or 32 x 2
 
-// One step: 16 terms, one per group of four lanes; RL rows per lane, read as RL / 4 pieces of 16 bytes.
+// One step: 16 (32) terms, one per group of four (two) lanes; RL rows per lane, read as RL / 4 pieces of 16 bytes.
 template <int RL> struct StepX { f32x4 v[RL / 4]; };
 template <int RL> struct Pieces { int at[RL / 4]; };   // where in a column the lane's pieces lie
-template <int RL, int Q>
+template <int GL, int RL, int Q>
 __device__ __forceinline__ void step_reads(StepX<RL>& x, int ov, const Pieces<RL>& pc) {
     int at[RL / 4];
-    xor_quad_bcast<Q>(ov, pc.at, at);
+    xor_bcast<GL, Q>(ov, pc.at, at);
 #pragma unroll
     for (int h = 0; h < RL / 4; ++h) x.v[h] = *reinterpret_cast<const LdsF32x4*>((unsigned)at[h]);
 }
-template <int RL, int Q, bool FIRST>
+template <int GL, int RL, int Q, bool FIRST>
 __device__ __forceinline__ void step_fmacs(float (&acc)[RL], float wv, const StepX<RL>& x) {
 #pragma unroll
-    for (int h = 0; h < RL / 4; ++h) fmac4_quad_bcast<Q, FIRST>(acc + 4 * h, wv, x.v[h]);
+    for (int h = 0; h < RL / 4; ++h) fmac4_bcast<GL, Q, FIRST>(acc + 4 * h, wv, x.v[h]);
 }
-// ST steps of NB = ceil(ST / 4) blocks held in registers, in straight-line code (with the number of steps a run-time value the branches
+// ST steps of NB = ceil(ST / GL) blocks held in registers, in straight-line code (with the number of steps a run-time value the branches
 // between them cost a copy of the accumulators at every exit and kept a register per address).  The reads of a step go out two steps
 // ahead of its multiply-adds.
-template <int RL, int ST, int NB, bool FIRST, int G = 0>
+template <int GL, int RL, int ST, int NB, bool FIRST, int G = 0>
 __device__ __forceinline__ void walk_steps(float (&acc)[RL], const float (&wv)[NB], const int (&ov)[NB], const Pieces<RL>& pc, StepX<RL> (&x)[3]) {
     if constexpr (G < ST) {
-        if constexpr (G + 2 < ST) step_reads<RL, (G + 2) % 4>(x[(G + 2) % 3], ov[(G + 2) / 4], pc);
-        step_fmacs<RL, G % 4, FIRST && G == 0>(acc, wv[G / 4], x[G % 3]);
-        walk_steps<RL, ST, NB, FIRST, G + 1>(acc, wv, ov, pc, x);
+        if constexpr (G + 2 < ST) step_reads<GL, RL, (G + 2) % GL>(x[(G + 2) % 3], ov[(G + 2) / GL], pc);
+        step_fmacs<GL, RL, G % GL, FIRST && G == 0>(acc, wv[G / GL], x[G % 3]);
+        walk_steps<GL, RL, ST, NB, FIRST, G + 1>(acc, wv, ov, pc, x);
     }
 }
-template <int RL, int ST, bool FIRST, int NB>
+template <int GL, int RL, int ST, bool FIRST, int NB>
 __device__ __forceinline__ void walk_terms(float (&acc)[RL], const float (&wv)[NB], const int (&ov)[NB], const Pieces<RL>& pc) {
-    static_assert(NB == (ST + 3) / 4, "blocks of four steps");
+    static_assert(NB == (ST + GL - 1) / GL, "blocks of GL steps");
     StepX<RL> x[3];
-    step_reads<RL, 0>(x[0], ov[0], pc);
-    if constexpr (ST > 1) step_reads<RL, 1>(x[1], ov[0], pc);
-    walk_steps<RL, ST, NB, FIRST>(acc, wv, ov, pc, x);
+    step_reads<GL, RL, 0>(x[0], ov[0], pc);
+    if constexpr (ST > 1) step_reads<GL, RL, 1>(x[1], ov[0], pc);
+    walk_steps<GL, RL, ST, NB, FIRST>(acc, wv, ov, pc, x);
 }
 
-// ST: steps a row's first ST * 16 terms take (rows of more than 256 terms: 16, the rest in a loop).
-template <int RL, int ST, typename XT, typename IT>
+// ST: steps a row's first terms take, 64 / GL to a step (rows of more than 256 terms: 4 GL, the rest in a loop).
+template <int GL, int RL, int ST, typename XT, typename IT>
 __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, int B, int d_in, const XT* __restrict__ W_c,
                                                       const IT* __restrict__ idx, const int32_t* __restrict__ active, int n_active,
                                                       int K, const float* __restrict__ bias, int d_out, float* __restrict__ y,
                                                       int NG, int n_btiles, int n_groups, int out_off, int span_cap, int act, int bt_major) {
     extern __shared__ float lds[];   // x tile [C + 1][S]; result tile [BT][NG | 1]; bias [NG], or bias and column table [span_cap] each
-    constexpr int BT = 4 * RL;               // batch rows per tile
+    constexpr int BT = GL * RL;              // batch rows per tile
     constexpr int S = BT;                    // words from column to column
     constexpr int S4 = S * 4;
-    constexpr int NB = (ST + 3) / 4;         // blocks of terms held in registers
-    static_assert(RL == 4 || RL == 8 || RL == 16, "tiles of 16, 32 or 64 rows");
+    constexpr int NB = (ST + GL - 1) / GL;   // blocks of terms held in registers
+    static_assert((GL == 4 && (RL == 4 || RL == 8 || RL == 16)) || (GL == 2 && RL == 4), "tiles of 8, 16, 32 or 64 rows");
 
     // consecutive workgroup ids go to different XCDs (one L2 each): either all batch tiles of a group of stored rows share an
     // XCD (its L2 fetches that group's W_c / idx once and all of x), or (bt_major) all groups of a batch tile (its own rows of
@@ -136,27 +142,28 @@ __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, 
     const int b0 = bt * BT;
     const int sg0 = g * NG;
     const int ng = min(NG, n_active - sg0);   // > 0: n_groups = ceil(n_active / NG)
-    const int C = (d_in + 15) & ~15;           // columns of the tile: whole units of 16 (what lies past a row's end is named by no index)
+    constexpr int UC = BT < 16 ? 32 : 16;      // columns of a unit
+    const int C = (d_in + UC - 1) & ~(UC - 1);   // columns of the tile: whole units (what lies past a row's end is named by no index)
     const int tile0 = (int)(unsigned)reinterpret_cast<size_t>((__attribute__((address_space(3))) float*)lds);   // (0: the kernel has no other LDS)
     const int zero_off = tile0 + C * S4;
 
-    // ---- the tile: units of 16 rows x 16 columns; a wavefront takes every nw-th 16 columns, all rows of them ----
-    const int dq = lane & 3, db = lane >> 2;
-    constexpr int RT = BT / 16;                // units to 16 columns
-    constexpr int CPP = kStageUnits / RT;      // columns / 16 a wavefront holds in registers: eight units
-    const int n_ct = C >> 4;
+    // ---- the tile: units of 16 rows x 16 columns (8 x 32); a wavefront takes every nw-th 16 (32) columns, all rows of them ----
+    const int dq = lane & 3, db = BT < 16 ? (lane >> 2) & 7 : lane >> 2, half = BT < 16 ? (lane >> 5) * 16 : 0;
+    constexpr int RT = BT < 16 ? 1 : BT / 16;  // units to UC columns
+    constexpr int CPP = kStageUnits / RT;      // columns / UC a wavefront holds in registers: eight units
+    const int n_ct = C / UC;
     const XT* const xtile = x + (size_t)b0 * d_in;
     const int n_rows = min(BT, B - b0);
     const bool last_rows = b0 + BT >= B;
     const int tile_total = n_rows * d_in + (last_rows ? 0 : 16);   // elements of x from the tile's first on that may be read (at least 16, host)
     const bool shifts = (d_in & 15) != 0 && last_rows;             // the last row of x ends inside a unit: its loads start earlier
 
-    // Terms.  A block is 64 consecutive terms of a row, one per lane and array; at step s of the block the four lanes of group p
+    // Terms.  A block is 64 consecutive terms of a row, one per lane and array; at step s of the block the GL lanes of group p
     // work on the term that lane s of the group loaded.  Whole blocks are loaded in the order of the lanes (consecutive words), the last,
-    // partial one with the term 16 s + p in lane s of group p, so that a row of K terms takes ceil(K / 16) steps.
+    // partial one with the term (64 / GL) s + p in lane s of group p, so that a row of K terms takes ceil(K GL / 64) steps.
     // D = 2 rows are in flight ahead of the one being walked.
-    const int p16 = lane >> 2, q4 = lane & 3;
-    const int t_strided = 16 * q4 + p16;
+    const int p16 = lane / GL, q4 = lane % GL;
+    const int t_strided = kWave / GL * q4 + p16;
     unsigned t_lane[NB];                       // this lane's term of each preloaded block, clamped into the row
     bool t_real[NB];
 #pragma unroll
@@ -223,11 +230,11 @@ __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, 
     const float* const bias_src = bias ? bias : reinterpret_cast<const float*>(x);   // never used: entries are 0 without a bias
     unsigned x_lane[RT];                       // element of x the lane loads of column 0, per 16 rows (past B: row B - 1 again, never stored)
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) x_lane[rt] = (unsigned)(min(rt * 16 + db, n_rows - 1) * d_in + dq * 4);
+    for (int rt = 0; rt < RT; ++rt) x_lane[rt] = (unsigned)(min(rt * 16 + db, n_rows - 1) * d_in + half + dq * 4);
     // Where the lane's four columns go.  Lanes of neighbouring column groups write different columns of their four at a time: the lanes
     // of a group of four two even and two odd ones, or (16-row tiles) each its own, and with the halves of odd pairs of column
     // groups swapped 32 consecutive lanes meet 32 different banks.
-    float* const l_lane = lds + dq * 4 * S + (RL > 4 ? db ^ ((dq & 2) << 2) : db);
+    float* const l_lane = lds + (half + dq * 4) * S + (RL > 4 ? db ^ ((dq & 2) << 2) : db);
     auto stage_pass = [&](int cb, auto first) {
         Staged4<XT> st[CPP][RT];
 #pragma unroll
@@ -236,7 +243,7 @@ __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, 
             if (ct < n_ct) {
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt)
-                    load4_at_element(xtile + min(x_lane[rt] + (unsigned)(ct * 16), (unsigned)(tile_total - 4)), st[i][rt]);
+                    load4_at_element(xtile + min(x_lane[rt] + (unsigned)(ct * UC), (unsigned)(tile_total - 4)), st[i][rt]);
             }
         }
         if constexpr (decltype(first)::value) {
@@ -260,9 +267,9 @@ __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, 
             if (ct >= n_ct) break;
             if (shifts) {
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt) shift4(st[i][rt], ragged_shift(x_lane[rt] + (unsigned)(ct * 16), tile_total));
+                for (int rt = 0; rt < RT; ++rt) shift4(st[i][rt], ragged_shift(x_lane[rt] + (unsigned)(ct * UC), tile_total));
             }
-            float* const at = l_lane + ct * 16 * S;
+            float* const at = l_lane + ct * UC * S;
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
                 float* const d = at + rt * 16;
@@ -327,7 +334,7 @@ __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, 
             i_raw = (int)*reinterpret_cast<const IT*>(reinterpret_cast<const char*>(idx + row) + t * (unsigned)sizeof(IT));
         };
         constexpr int kHeld = 4 * kQuadBlock;
-        if constexpr (ST == 16) {
+        if constexpr (ST == 4 * GL) {
             if (K > kHeld) {
                 request_block(kHeld, xw[0], xi[0]);
                 request_block(kHeld + kQuadBlock, xw[1], xi[1]);
@@ -337,21 +344,21 @@ __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, 
         // the prologue: past the workgroup's last row the last one is read again and never walked; under a branch the wait
         // for the next row's terms would become a wait for everything in flight, these included)
         request_row(min(j + D * nw, ng - 1), w, i);
-        walk_terms<RL, ST, true>(acc, pw, po, pc);
-        if constexpr (ST == 16) {
+        walk_terms<GL, RL, ST, true>(acc, pw, po, pc);
+        if constexpr (ST == 4 * GL) {
             auto block = [&](int t0, XT& w_raw, int& i_raw) {
                 float wc[1];
                 int oc[1];
                 finish(w_raw, i_raw, t0 + lane < K, wc[0], oc[0]);
                 request_block(t0 + 2 * kQuadBlock, w_raw, i_raw);
-                walk_terms<RL, 4, false>(acc, wc, oc, pc);
+                walk_terms<GL, RL, GL, false>(acc, wc, oc, pc);
             };
             for (int t0 = kHeld; t0 < K; t0 += 2 * kQuadBlock) {
                 block(t0, xw[0], xi[0]);
                 if (t0 + kQuadBlock < K) block(t0 + kQuadBlock, xw[1], xi[1]);
             }
         }
-        // The 16 groups hold partial sums of the same batch rows.  Every group of a 16-lane row collects the sums of the piece that
+        // The groups hold partial sums of the same batch rows.  Every group of a 16-lane row collects the sums of the piece that
         // it reads first; then registers are paired, lanes 0-31 of the sum taking the first and lanes 32-63 the second register's, and
         // again between the odd and even 16-lane rows.  What is left is one batch row per lane of a 64-row tile; in smaller tiles
         // groups that read the same piece first add theirs.
@@ -369,7 +376,8 @@ __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, 
         float v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
         if constexpr (RL <= 8) v += row_ror<8>(v);
         if constexpr (RL == 4) v += row_ror<4>(v);
-        if ((p16 & 3) < RL / 4) out[out_row * OS + j] = v;
+        if constexpr (GL == 2) v += row_ror<2>(v);
+        if ((p16 & (16 / GL - 1)) < RL / 4) out[out_row * OS + j] = v;
     };
     __builtin_amdgcn_s_setprio(3);
     const int third = ng / 3;
@@ -436,9 +444,9 @@ __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, 
     }
 }
 
-template <int RL, int ST, typename XT, typename IT>
+template <int GL, int RL, int ST, typename XT, typename IT>
 static srigl_status launch_rowloop_f(const FwdArgs& a, const RowloopPlan& p, hipStream_t st) {
-    auto kern = k_fwd_rowloop<RL, ST, XT, IT>;
+    auto kern = k_fwd_rowloop<GL, RL, ST, XT, IT>;
     static LdsLimit lds_limit;
     if (lds_limit.ensure(kern, p.lds) != SRIGL_OK) return SRIGL_ERR_HIP;
     const long long blocks = p.bt_major ? 8LL * ((p.n_btiles + 7) / 8) * p.n_groups : 8LL * ((p.n_groups + 7) / 8) * p.n_btiles;
@@ -448,28 +456,38 @@ static srigl_status launch_rowloop_f(const FwdArgs& a, const RowloopPlan& p, hip
     return hip_ok(hipGetLastError());
 }
 
-template <int RL, typename XT, typename IT>
+template <int GL, int RL, typename XT, typename IT>
 static srigl_status launch_rowloop_r(const FwdArgs& a, const RowloopPlan& p, hipStream_t st) {
+    if constexpr (GL == 4) {
+        switch (p.ST) {
+            case 10: return launch_rowloop_f<GL, RL, 10, XT, IT>(a, p, st);
+            case 12: return launch_rowloop_f<GL, RL, 12, XT, IT>(a, p, st);
+            case 14: return launch_rowloop_f<GL, RL, 14, XT, IT>(a, p, st);
+            case 16: return launch_rowloop_f<GL, RL, 16, XT, IT>(a, p, st);
+            default: break;
+        }
+    }
     switch (p.ST) {
-        case 1: return launch_rowloop_f<RL, 1, XT, IT>(a, p, st);
-        case 2: return launch_rowloop_f<RL, 2, XT, IT>(a, p, st);
-        case 3: return launch_rowloop_f<RL, 3, XT, IT>(a, p, st);
-        case 4: return launch_rowloop_f<RL, 4, XT, IT>(a, p, st);
-        case 5: return launch_rowloop_f<RL, 5, XT, IT>(a, p, st);
-        case 6: return launch_rowloop_f<RL, 6, XT, IT>(a, p, st);
-        case 7: return launch_rowloop_f<RL, 7, XT, IT>(a, p, st);
-        case 8: return launch_rowloop_f<RL, 8, XT, IT>(a, p, st);
-        case 10: return launch_rowloop_f<RL, 10, XT, IT>(a, p, st);
-        case 12: return launch_rowloop_f<RL, 12, XT, IT>(a, p, st);
-        case 14: return launch_rowloop_f<RL, 14, XT, IT>(a, p, st);
-        case 16: return launch_rowloop_f<RL, 16, XT, IT>(a, p, st);
+        case 1: return launch_rowloop_f<GL, RL, 1, XT, IT>(a, p, st);
+        case 2: return launch_rowloop_f<GL, RL, 2, XT, IT>(a, p, st);
+        case 3: return launch_rowloop_f<GL, RL, 3, XT, IT>(a, p, st);
+        case 4: return launch_rowloop_f<GL, RL, 4, XT, IT>(a, p, st);
+        case 5: return launch_rowloop_f<GL, RL, 5, XT, IT>(a, p, st);
+        case 6: return launch_rowloop_f<GL, RL, 6, XT, IT>(a, p, st);
+        case 7: return launch_rowloop_f<GL, RL, 7, XT, IT>(a, p, st);
+        case 8: return launch_rowloop_f<GL, RL, 8, XT, IT>(a, p, st);
         default: return SRIGL_ERR_UNSUPPORTED;
     }
 }
 
 template <typename XT, typename IT>
 static srigl_status launch_rowloop_x(const FwdArgs& a, const RowloopPlan& p, hipStream_t st) {
-    return p.BT == 16 ? launch_rowloop_r<4, XT, IT>(a, p, st) : p.BT == 32 ? launch_rowloop_r<8, XT, IT>(a, p, st) : launch_rowloop_r<16, XT, IT>(a, p, st);
+    switch (p.BT) {
+        case 8: return launch_rowloop_r<2, 4, XT, IT>(a, p, st);
+        case 16: return launch_rowloop_r<4, 4, XT, IT>(a, p, st);
+        case 32: return launch_rowloop_r<4, 8, XT, IT>(a, p, st);
+        default: return launch_rowloop_r<4, 16, XT, IT>(a, p, st);
+    }
 }
 
 }  // namespace srigl

@@ -1,4 +1,4 @@
-"""GPU parity of the whole-input batched kernel in every tile it runs in (16, 32 and 64 batch rows): rows of every number of 16-term steps it
+"""GPU parity of the whole-input batched kernel in every tile it runs in (8, 16, 32 and 64 batch rows): rows of every number of steps it
 has code for, rows of any length and alignment, last tiles and groups that are not full, both index widths."""
 import numpy as np
 import pytest
@@ -10,7 +10,7 @@ from gpu_util import TOL_BF16, TOL_F32, dev, gate, oracle_condensed, oracle_seg
 from paper_2305_02299_amd import binding as B_
 
 pytestmark = pytest.mark.gpu
-WIDEST = {16: 2528, 32: 1248, 64: 608}     # columns (whole units of 16) with which 16 result rows still fit the LDS
+WIDEST = {8: 4096, 16: 2528, 32: 1248, 64: 608}     # columns (whole units) with which 16 result rows still fit the LDS, or that the kernel takes at most
 GUARD = 1 << 12
 
 
@@ -46,7 +46,7 @@ def check(L, tile_rows, **kw):
     return y
 
 
-@pytest.mark.parametrize("tile_rows", [16, 32, 64])
+@pytest.mark.parametrize("tile_rows", [8, 16, 32, 64])
 @pytest.mark.parametrize("K", [1, 15, 16, 17, 33, 63, 64, 65, 77, 96, 112, 113, 128, 129, 144, 177, 200, 240, 241, 256, 257, 320, 333, 600])
 def test_rows_of_every_number_of_steps(tile_rows, K):
     d_in = 605 if K % 2 else 608                    # rows of whole 16-column units, and others
@@ -54,7 +54,7 @@ def test_rows_of_every_number_of_steps(tile_rows, K):
     check(L, tile_rows)
 
 
-@pytest.mark.parametrize("tile_rows", [16, 32, 64])
+@pytest.mark.parametrize("tile_rows", [8, 16, 32, 64])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_widths_alignments_and_index_types(tile_rows, dtype):
     for d_in, B, abl, offset, rows_per_wave in ((16, 1, 0.0, 0, 0), (17, 2, 0.3, 1, 1), (31, tile_rows, 0.0, 3, 2), (33, tile_rows - 1, 0.5, 0, 0),
@@ -66,7 +66,7 @@ def test_widths_alignments_and_index_types(tile_rows, dtype):
         assert np.array_equal(wide.view(np.uint32), narrow.view(np.uint32))
 
 
-@pytest.mark.parametrize("tile_rows", [16, 32, 64])
+@pytest.mark.parametrize("tile_rows", [8, 16, 32, 64])
 def test_columns_no_row_names_do_not_matter(tile_rows):
     """NaN and infinities in columns that no stored row reads (padding terms point at an all-zero column of the tile), at the end of rows
     whose length is not a multiple of 16 among them."""
@@ -95,13 +95,13 @@ def test_columns_no_row_names_do_not_matter(tile_rows):
 
 
 def test_what_does_not_fit_is_refused():
-    for tile_rows, d_in in ((16, 2560), (32, 1280), (64, 640), (16, 15)):
+    for tile_rows, d_in in ((8, 4112), (16, 2560), (32, 1280), (64, 640), (16, 15)):
         L = si.make_layer(d_in, 40, 5, 20, seed=600)
         with pytest.raises(B_.SriglError) as e:
             run_tile(L, tile_rows)
         assert e.value.status == B_.ERR_UNSUPPORTED, (tile_rows, d_in)
     L = si.make_layer(256, 40, 5, 20, seed=600)
-    for kw in (dict(tile_rows=8), dict(tile_rows=16, rows_per_wave=-1), dict(tile_rows=16, xcd_order=3)):
+    for kw in (dict(tile_rows=4), dict(tile_rows=16, rows_per_wave=-1), dict(tile_rows=16, xcd_order=3)):
         with pytest.raises(B_.SriglError):
             run_tile(L, **kw)
 

@@ -8,8 +8,9 @@ def test_tiles_of_named_layers():
     assert B_.srigl_fwd_tile_query(256, 768, 3072, 77, 3072) == (32, 6)           # one workgroup per compute unit
     assert B_.srigl_fwd_tile_query(1024, 768, 3072, 154, 3072) == (32, 24)
     assert B_.srigl_fwd_tile_query(256, 2160, 768, 216, 768)[0] == 16             # 32 rows of 2160 columns do not fit the LDS
+    assert B_.srigl_fwd_tile_query(256, 3072, 768, 307, 768) == (8, 6)             # nor do 16 rows of 3072
     assert B_.srigl_fwd_tile_query(300, 1000, 700, 50, 777, has_active=True)[0] in (16, 32)
-    for sizes in ((1, 768, 3072, 77, 3072), (16, 768, 3072, 77, 3072), (256, 3072, 768, 307, 768), (0, 768, 3072, 77, 3072), (64, 8, 3072, 4, 3072)):
+    for sizes in ((1, 768, 3072, 77, 3072), (16, 768, 3072, 77, 3072), (256, 4112, 768, 307, 768), (0, 768, 3072, 77, 3072), (64, 8, 3072, 4, 3072)):
         assert B_.srigl_fwd_tile_query(*sizes) == (0, 0), sizes                    # one row, a few rows, too wide, nothing, too narrow
 
 
@@ -24,7 +25,8 @@ def test_every_tile_taken_fits():
         assert (tile == 0) == (rows == 0)
         if tile:
             taken += 1
-            cols = -(-d_in // 16) * 16
-            assert tile in (16, 32, 64) and 16 <= d_in and B > 1
+            unit = 32 if tile == 8 else 16
+            cols = -(-d_in // unit) * unit
+            assert tile in (8, 16, 32, 64) and 16 <= d_in and B > 1
             assert ((cols + 1) * tile + tile * (16 * rows | 1)) * 4 <= 160 * 1024
     assert taken > 50
