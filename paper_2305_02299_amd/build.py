@@ -9,7 +9,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libsrigl.so")
 FRONT = os.path.join(PKG, "_front.so")
-SOURCES = ["condense.hip", "fwd.hip", "fwd_rowlane_f32.hip", "fwd_rowlane_bf16.hip", "fwd_rowlane_f32_i16.hip", "fwd_rowlane_bf16_i16.hip", "fwd_rowloop.hip", "fwd_rowloop_f32.hip", "fwd_rowloop_bf16.hip", "fwd_rowloop_f32_i16.hip", "fwd_rowloop_bf16_i16.hip", "fwd_blocked.hip", "structured.hip", "mlp.hip", "update.hip", "csr.hip"]
+SOURCES = ["condense.hip", "fwd.hip", "fwd_klane_stream.hip", "fwd_rowlane_f32.hip", "fwd_rowlane_bf16.hip", "fwd_rowlane_f32_i16.hip", "fwd_rowlane_bf16_i16.hip", "fwd_rowloop.hip", "fwd_rowloop_f32.hip", "fwd_rowloop_bf16.hip", "fwd_rowloop_f32_i16.hip", "fwd_rowloop_bf16_i16.hip", "fwd_blocked.hip", "structured.hip", "mlp.hip", "update.hip", "csr.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

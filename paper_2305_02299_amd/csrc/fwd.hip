@@ -843,6 +843,7 @@ struct FwdDecision {
     srigl_fwd_algo algo;
     KlanePlan klane;
     RowlanePlan rowlane;
+    bool stream;           // (of the small-batch kernels)
     RowloopPlan rowloop;   // (not the caller's SRIGL_FWD_ROWLOOP alone: tiles of 8 and 16 rows and rows of any length too)
 };
 static const FwdDecision& decide_fwd(const FwdArgs& a) {
@@ -854,7 +855,10 @@ static const FwdDecision& decide_fwd(const FwdArgs& a) {
     return cache.get(k, [&] {
         FwdDecision d{};
         d.algo = choose_fwd_algo(a, true, &d.rowloop);
-        if (d.algo == SRIGL_FWD_KLANE) d.klane = plan_klane(a, nullptr);
+        if (d.algo == SRIGL_FWD_KLANE) {
+            d.klane = plan_klane(a, nullptr);
+            d.stream = stream_ahead(a);
+        }
         if (d.algo == SRIGL_FWD_ROWLANE) d.rowlane = plan_rowlane(a, nullptr);
         return d;
     });
@@ -936,7 +940,7 @@ static srigl_status fwd_core(const void* x, srigl_dtype x_dtype, int32_t B, int3
     switch (d.algo) {
         case SRIGL_FWD_ROWLANE: return launch_rowlane_plan(a, d.rowlane, st);
         case SRIGL_FWD_ROWLOOP: return launch_rowloop_plan(a, d.rowloop, st);
-        case SRIGL_FWD_KLANE: return launch_klane_plan(a, d.klane, nullptr, st);
+        case SRIGL_FWD_KLANE: return d.stream ? launch_fwd_stream(a, st) : launch_klane_plan(a, d.klane, nullptr, st);
         default: return launch_fwd_generic(a, st);
     }
 }

@@ -1,0 +1,153 @@
+// KLANE for layers whose terms have to be streamed (gfx950): the small-batch formulation of fwd.hip (lanes share a stored row; Alg. 1 of
+// arXiv 2305.02299 with the bias of Sec. 4.4 and the ablated neurons of Sec. 3.1 step 4) with the activations in LDS and two workgroups of
+// eight wavefronts per compute unit, each wavefront with four stored rows of one batch row.
+//
+// The gathering form starts thousands of workgroups of four wavefronts, a stored row each, and takes x from the vector caches, which serve
+// a wavefront's 64 scattered words in about as many clocks: 4096 -> 16384 bf16 (13108 stored rows, K = 205, 10.7 MB) at one batch row
+// 7.2 us (a call 8.1).  Here a wavefront requests the terms of its four rows, 4 consecutive ones per lane and row in one load per array, before it
+// stages its share of x, and the LDS serves 64 scattered words in some ten clocks (a call 5.5).  What bounds it: the start of the wavefronts, the
+// trip to memory for the terms and the sums over the lanes, 3.6 us together, and the terms' way in.
+#include "srigl_internal.h"
+#include "fwd_rowlane.inl"
+
+namespace srigl {
+
+constexpr int kStreamWaves = 8, kStreamRows = 4, kStreamTerms = 4;   // wavefronts of a workgroup, rows of a wavefront, consecutive terms of a lane
+constexpr int kStreamChunk = kStreamTerms * kWave;
+
+template <typename T> struct Four { T v[4]; };
+__device__ __forceinline__ Four<float> load_four(const float* p) {
+    struct __attribute__((packed, aligned(4))) F4 { float v[4]; };
+    const F4 f = *reinterpret_cast<const F4*>(p);
+    return {{f.v[0], f.v[1], f.v[2], f.v[3]}};
+}
+__device__ __forceinline__ Four<int32_t> load_four(const int32_t* p) {
+    struct __attribute__((packed, aligned(4))) I4 { int32_t v[4]; };
+    const I4 f = *reinterpret_cast<const I4*>(p);
+    return {{f.v[0], f.v[1], f.v[2], f.v[3]}};
+}
+__device__ __forceinline__ Four<uint16_t> load_four(const uint16_t* p) {
+    struct __attribute__((packed, aligned(2))) U2 { uint32_t x, y; };
+    const U2 f = *reinterpret_cast<const U2*>(p);
+    return {{(uint16_t)f.x, (uint16_t)(f.x >> 16), (uint16_t)f.y, (uint16_t)(f.y >> 16)}};
+}
+
+template <int N>
+__device__ __forceinline__ float ror16(float v) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, true)); }
+
+template <typename XT, typename IT>
+__global__ __launch_bounds__(kStreamWaves* kWave) void k_fwd_klane_stream(const XT* __restrict__ x, int d_in, const XT* __restrict__ W_c,
+                                                           const IT* __restrict__ idx, const int32_t* __restrict__ active, int n_active, int K,
+                                                           const float* __restrict__ bias, int d_out, float* __restrict__ y, int act) {
+    extern __shared__ float xs[];   // the columns, then one of zeros for lanes without a term
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    constexpr int kThreads = kStreamWaves * kWave;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const XT* const xr = x + (size_t)blockIdx.y * d_in;
+    float* const yr = y + (size_t)blockIdx.y * d_out;
+    const int s0 = (blockIdx.x * kStreamWaves + wv) * kStreamRows;   // (may lie past the last row)
+    // after the sums over lanes, 16-lane group g of the wavefront holds row s0 + own (0, 2, 1, 3)
+    const int own = ((lane >> 5) | ((lane >> 3) & 2));
+
+    Four<XT> w[kStreamRows];
+    Four<IT> c[kStreamRows];
+    auto request = [&](int k0, Four<XT> (&wr)[kStreamRows], Four<IT> (&cr)[kStreamRows]) {   // terms k0 + 4 lane and on
+        const int at = min(k0 + kStreamTerms * lane, K - kStreamTerms);   // (K >= 4: host; a term of the lane before is dropped where it is used)
+#pragma unroll
+        for (int r = 0; r < kStreamRows; ++r) {
+            const size_t row = (size_t)min(s0 + r, n_active - 1) * (size_t)K;
+            wr[r] = load_four(W_c + row + at);
+            cr[r] = load_four(idx + row + at);
+        }
+    };
+    request(0, w, c);
+    const int s = min(s0 + own, n_active - 1);
+    const int col = active ? active[s] : s, prev = s > 0 ? (active ? active[s - 1] : s - 1) : -1;
+
+    // ---- x: four loads per thread in flight ----
+    for (int j0 = tid; j0 < d_in; j0 += 4 * kThreads) {
+        XT v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = xr[min(j0 + u * kThreads, d_in - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (j0 + u * kThreads < d_in) xs[j0 + u * kThreads] = rl_to_f32<XT>(v[u]);
+    }
+    if (tid == 0) xs[d_in] = 0.0f;
+    const bool stored = col >= 0 && col < d_out;
+    const float bv = bias && stored ? bias[col] : 0.0f;
+    __syncthreads();
+    if (s0 >= n_active) return;
+
+    float acc[kStreamRows] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int k0 = 0; k0 < K; k0 += kStreamChunk) {
+        Four<XT> wn[kStreamRows];
+        Four<IT> cn[kStreamRows];
+        if (k0 + kStreamChunk < K) request(k0 + kStreamChunk, wn, cn);   // on their way behind these
+        const int first = k0 + kStreamTerms * lane, at = min(first, K - kStreamTerms);
+#pragma unroll
+        for (int r = 0; r < kStreamRows; ++r)
+#pragma unroll
+            for (int u = 0; u < kStreamTerms; ++u) {
+                const bool real = at + u >= first;   // (none where first >= K)
+                const unsigned j = real ? min((unsigned)c[r].v[u], (unsigned)d_in - 1u) : (unsigned)d_in;
+                acc[r] = fmaf(real ? rl_to_f32<XT>(w[r].v[u]) : 0.0f, xs[j], acc[r]);
+            }
+#pragma unroll
+        for (int r = 0; r < kStreamRows; ++r) { w[r] = wn[r]; c[r] = cn[r]; }
+    }
+    // registers are paired, lanes 0-31 of the sum taking the first and lanes 32-63 the second register's, and again between the odd and
+    // even 16-lane rows; then the sum around each 16-lane row
+    const auto h0 = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[0]), __float_as_uint(acc[1]), false, false);
+    const auto h1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[2]), __float_as_uint(acc[3]), false, false);
+    const float u0 = __uint_as_float(h0[0]) + __uint_as_float(h0[1]), u1 = __uint_as_float(h1[0]) + __uint_as_float(h1[1]);
+    const auto h = __builtin_amdgcn_permlane16_swap(__float_as_uint(u0), __float_as_uint(u1), false, false);
+    float v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+    v += ror16<8>(v);
+    v += ror16<4>(v);
+    v += ror16<2>(v);
+    v += ror16<1>(v);
+    if (s0 + own >= n_active) return;
+    if ((lane & 15) == 0 && stored) yr[col] = act == SRIGL_ACT_NONE ? v + bv : apply_act(v + bv, act);
+    if (active == nullptr) return;
+    auto fill = [&](int from, int to) {   // ablated columns hold their bias
+        for (int q = max(from, 0) + (lane & 15); q < min(to, d_out); q += 16) {
+            const float raw = rl_bias_at(bias, q);
+            yr[q] = act == SRIGL_ACT_NONE ? raw : apply_act(raw, act);
+        }
+    };
+    fill(prev + 1, col);   // in front of the row's column, and behind the last one
+    if (s == n_active - 1) fill(col + 1, d_out);
+}
+
+template <typename XT, typename IT>
+static srigl_status launch_stream_t(const FwdArgs& a, hipStream_t st) {
+    auto kern = k_fwd_klane_stream<XT, IT>;
+    static LdsLimit lds_limit;
+    const size_t lds = (size_t)(a.d_in + 1) * sizeof(float);
+    if (lds_limit.ensure(kern, lds) != SRIGL_OK) return SRIGL_ERR_HIP;
+    constexpr int kPerWg = kStreamWaves * kStreamRows;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((a.n_active + kPerWg - 1) / kPerWg), (unsigned)a.B), dim3(kStreamWaves * kWave), lds, st, (const XT*)a.x, a.d_in,
+                       (const XT*)a.W_c, (const IT*)a.idx, a.active, a.n_active, a.K, a.bias, a.d_out, a.y, a.act);
+    return hip_ok(hipGetLastError());
+}
+
+// Taken in place of the other small-batch forms where there are terms to stream (over the batch 1.6 M, or 0.8 M per chunk of 256 terms of a
+// row, whose chunks follow one another), four workgroups to a compute unit hold all of them, and a row fills half of its wavefront's lanes
+// or more: 1.16 times faster on average on 22 of 220 points and 1.10 times on 33 of 320 others, nowhere slower by more than runs differ
+// (400 to 4096 wide, 128 to 16384 stored rows, batches 1 to 48, both types and index widths; 3142 -> 16707, K = 314 at one batch row 11.1 ->
+// 7.5 us, 3072 -> 768 with 538 stored, K = 307 at 16 6.9 -> 6.2, 4052 -> 4395 bf16, K = 202 at 3 6.6 -> 5.2).  From 1.0 M terms on some lose 9 to
+// 21 % (3912 -> 3106, K = 391 at 1; 3680 -> 1412, K = 736), with rows that fill fewer lanes 10 % (1011 -> 1884, K = 101 at 12).
+bool stream_ahead(const FwdArgs& a) {
+    if (a.B <= 0 || a.B > 64 || a.n_active <= 0 || a.K < kStreamTerms || (size_t)(a.d_in + 1) * sizeof(float) > kLdsMax / 4) return false;
+    const int chunks = (a.K + kStreamChunk - 1) / kStreamChunk;
+    const double terms = (double)a.n_active * a.K * a.B;
+    return terms >= 0.8e6 * std::max(2, chunks) && (long long)a.n_active * a.B <= 4 * 256 * kStreamWaves * kStreamRows && 2 * a.K >= chunks * kStreamChunk;
+}
+
+srigl_status launch_fwd_stream(const FwdArgs& a, hipStream_t st) {
+    if (a.idx_u16) return a.x_bf16 ? launch_stream_t<uint16_t, uint16_t>(a, st) : launch_stream_t<float, uint16_t>(a, st);
+    return a.x_bf16 ? launch_stream_t<uint16_t, int32_t>(a, st) : launch_stream_t<float, int32_t>(a, st);
+}
+
+}  // namespace srigl

@@ -186,6 +186,9 @@ srigl_status launch_rowloop_bf16(const FwdArgs& a, const RowloopPlan& p, hipStre
 srigl_status launch_rowloop_f32_i16(const FwdArgs& a, const RowloopPlan& p, hipStream_t st);
 srigl_status launch_rowloop_bf16_i16(const FwdArgs& a, const RowloopPlan& p, hipStream_t st);
 RowloopPlan plan_tile(const FwdArgs& a, int tile_rows, int rows_per_wave, int xcd_order, double* us);
+// The small-batch kernel for layers whose terms are streamed, and whether it is expected to be ahead of the other small-batch forms.
+bool stream_ahead(const FwdArgs& a);
+srigl_status launch_fwd_stream(const FwdArgs& a, hipStream_t st);
 srigl_status launch_rowloop_plan(const FwdArgs& a, const RowloopPlan& p, hipStream_t st);
 // Estimated time (us) of the condensed forward call of these sizes in the kernel the library's own choice takes.
 double condensed_estimate_us(int B, int d_in, int n_active, int K, int d_out, bool bf16, bool has_active);

@@ -163,3 +163,32 @@ def test_blocked_rows_that_end_inside_a_piece(d_in, K, tile):
     want = np.stack([(Wd[s] * xd[:, idx[s]]).sum(axis=1) for s in range(d_out)], axis=1)
     scale = np.stack([np.abs(Wd[s] * xd[:, idx[s]]).sum(axis=1) for s in range(d_out)], axis=1)
     assert (np.abs(y.cpu().numpy() - want) <= scale * (K + 1) * 2.0 ** -23).all()   # exact products, fp32 sums of K of them
+
+
+@pytest.mark.parametrize("d_in,d_out,n,K,B,dtype,narrow", [
+    (1501, 9000, 8201, 290, 1, "f32", False), (1200, 8200, 8200, 500, 1, "bf16", True), (4096, 16384, 13108, 205, 1, "bf16", True),
+    (3999, 5440, 5440, 143, 3, "f32", True), (3072, 768, 538, 307, 16, "f32", False), (700, 400, 255, 256, 63, "bf16", False),
+    (2200, 3000, 1601, 683, 8, "bf16", False),
+])
+def test_streamed_terms_against_the_general_kernel(d_in, d_out, n, K, B, dtype, narrow):
+    """The small-batch kernel for layers whose terms are streamed, at sizes where the library's own choice takes it: rows of one to three chunks of
+    256 terms that end inside a lane's four, wavefronts and workgroups with fewer rows than they have room for, both types and index widths,
+    ablated neurons in front, between and behind; activations that are not finite in a column no row reads."""
+    rng = np.random.default_rng(K)
+    active = np.sort(rng.permutation(d_out - (2 if n < d_out else 0))[:n] + (1 if n < d_out else 0)).astype(np.int32)
+    idx = np.sort(np.argsort(rng.random((n, d_in - 1)), axis=1)[:, :K], axis=1).astype(np.int32)     # (nobody reads the last column)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    W, x = torch.from_numpy(rng.standard_normal((n, K)).astype(np.float32)).to(t).cuda(), torch.from_numpy(rng.standard_normal((B, d_in)).astype(np.float32)).to(t).cuda()
+    x[:, -1] = float("nan")
+    bias, act = torch.from_numpy(rng.standard_normal(d_out).astype(np.float32)).cuda(), dev(active) if n < d_out else None
+    ix = torch.from_numpy(idx).cuda()
+    got = torch.full((B + 2, d_out), 777.0, device="cuda")
+    want = torch.full((B, d_out), 777.0, device="cuda")
+    B_.srigl_condensed_linear_fwd(x, B, d_in, W, ix.to(torch.int16) if narrow else ix, act, n, K, bias, d_out, got[1:B + 1], act=B_.ACT_RELU)
+    B_.srigl_condensed_linear_fwd(x, B, d_in, W, ix, act, n, K, bias, d_out, want, algo=B_.FWD_GENERIC)
+    scale = torch.full((B, d_out), 1.0, device="cuda") + bias.abs()
+    rows = torch.from_numpy(active).cuda().long()
+    for b in range(B):
+        scale[b, rows] += (W.float().abs() * x[b].float().abs()[ix.long()]).sum(1)
+    assert ((got[1:B + 1] - want.clamp(min=0)).abs() <= scale * (K + 1) * 2.0 ** -23).all()       # two orders of one fp32 sum of K products
+    assert (got[0] == 777.0).all() and (got[B + 1] == 777.0).all()
