@@ -66,8 +66,7 @@ typedef struct {
     int32_t reserved[3];
 } srigl_report;
 
-/* Bytes of device scratch that check_fanin / condense need for n_rows rows.  With 128 bytes more per row and 1024 columns or part of
- * them (behind the next multiple of 16 bytes) condense keeps the mask's bits there and reads the mask once instead of twice. */
+/* Bytes of device scratch that check_fanin / condense need for n_rows rows. */
 size_t srigl_workspace_bytes(int32_t n_rows);
 
 /* Number of uint16 entries per stored row in the optional `seg` table: d_in/64 rounded up, plus 1. */

@@ -182,15 +182,8 @@ __device__ __forceinline__ uint32_t kept_bits_short(const uint8_t* __restrict__ 
     return b;
 }
 
-// Where the workspace has room the kept columns' bits stay there, 16 to a lane and load, for k_compact_rows, which reads an eighth of the
-// mask's bytes then (rows of fewer than 16 columns have none).  Both kernels: 4096 -> 16384 bf16 44.6 us without, 41.2 with them,
-// 2048 -> 8192 bf16 21.2 and 19.2, 4096 -> 4096 fp32 22.1 and 20.4, 768 -> 3072 fp32 8.5 and 8.3.
-__host__ __device__ inline size_t row_bit_words(int d_in) { return (size_t)((d_in + kMaskCols * kWave - 1) / (kMaskCols * kWave)) * kWave; }
-
-template <bool BITS>
 __global__ __launch_bounds__(kFlagRows* kWave) void k_row_flags(const uint8_t* __restrict__ mask, int n_rows, int d_in, int K,
-                                                              uint8_t* __restrict__ stored, uint8_t* __restrict__ bad,
-                                                              uint16_t* __restrict__ kept) {
+                                                              uint8_t* __restrict__ stored, uint8_t* __restrict__ bad) {
     __shared__ int cnt[kFlagRows];
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
     const int r = blockIdx.x * kFlagRows + wv;
@@ -205,13 +198,7 @@ __global__ __launch_bounds__(kFlagRows* kWave) void k_row_flags(const uint8_t* _
                     if (col0 + u * kWave * kMaskCols < d_in) p[u] = load_piece(m, col0 + (u * kWave + lane) * kMaskCols, d_in);
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    if (col0 + u * kWave * kMaskCols < d_in) {
-                        const uint32_t bits = kept_bits(p[u]);
-                        c += __popc(bits);
-                        if (BITS)
-                            kept[(size_t)r * row_bit_words(d_in) + (col0 / kMaskCols + u * kWave + lane)] =
-                                (uint16_t)(p[u].drop >= kMaskCols ? 0u : bits >> p[u].drop);
-                    }
+                    if (col0 + u * kWave * kMaskCols < d_in) c += __popc(kept_bits(p[u]));
             }
         } else {
             c = __popc(kept_bits_short(m, lane, d_in));
@@ -235,14 +222,14 @@ __global__ __launch_bounds__(kFlagRows* kWave) void k_row_flags(const uint8_t* _
 // of the lanes below it), then the lanes take the list's entries in turn, so that idx, W_c, the streaming copy (see
 // PackedLayout; places behind the K-th term up to the next multiple of four get weight bits 0 and index 0) and the weights'
 // gather all run over consecutive terms: three store instructions per 64 terms, where a lane storing its own columns issued
-// three per column position.  What bounds it: the mask's bits (or the mask a second time) and the 128-byte lines of W that hold a kept
-// weight (at 5 % density nearly all of W).  4096 x 16384 bf16, 20 % of the rows ablated: 161 us for the whole call on the GPU before.
+// three per column position.  What bounds it: the mask a second time and the 128-byte lines of W that hold a kept weight (at
+// 5 % density nearly all of W).  4096 x 16384 bf16, 20 % of the rows ablated: 161 us for the whole call on the GPU before.
 // Workgroup 0 also writes the report.
-template <typename T, bool BITS>
+template <typename T>
 __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_compact_rows(const T* __restrict__ W, const uint8_t* __restrict__ mask,
                                                                      int d_out, int d_in, int K, int cap_rows,
                                                                      const uint8_t* __restrict__ stored, const uint8_t* __restrict__ bad,
-                                                                     const uint16_t* __restrict__ kept, T* __restrict__ W_c, int32_t* __restrict__ idx, int32_t* __restrict__ active,
+                                                                     T* __restrict__ W_c, int32_t* __restrict__ idx, int32_t* __restrict__ active,
                                                                      uint16_t* __restrict__ seg, int seg_stride,
                                                                      unsigned char* __restrict__ packed, PackedLayout pl, int rows_per_block,
                                                                      int list_cap, srigl_report* __restrict__ report) {
@@ -255,18 +242,14 @@ __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_compact_rows(const T* 
     const int n_words = (d_out + 31) / 32;
 
     // the first row's mask goes out before the bits are waited for
-    MaskPiece ahead[BITS ? 1 : 4];
-    uint16_t ahead_bits[4];
-    const bool pieces = BITS || d_in >= kMaskCols;
-    auto load_batch = [&](int r, int col0) {
+    MaskPiece ahead[4];
+    const bool pieces = d_in >= kMaskCols;
+    if (pieces && row0 + wv < d_out) {
+        const uint8_t* m = mask + (size_t)(row0 + wv) * d_in;
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (col0 + u * kWave * kMaskCols < d_in) {
-                if (BITS) ahead_bits[u] = kept[(size_t)r * row_bit_words(d_in) + (col0 / kMaskCols + u * kWave + lane)];
-                else ahead[BITS ? 0 : u] = load_piece(mask + (size_t)r * d_in, col0 + (u * kWave + lane) * kMaskCols, d_in);
-            }
-    };
-    if (pieces && row0 + wv < d_out) load_batch(row0 + wv, 0);
+            if (u * kWave * kMaskCols < d_in) ahead[u] = load_piece(m, (u * kWave + lane) * kMaskCols, d_in);
+    }
 
     // (a workgroup's four rows share a byte)
     const uint32_t own_byte = row0 < d_out ? stored[row0 >> 3] : 0u;
@@ -330,6 +313,7 @@ __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_compact_rows(const T* 
         }
         if (s >= cap_rows) continue;   // no room
         if (lane == 0) active[s] = r;
+        const uint8_t* m = mask + (size_t)r * d_in;
         const T* w = W + (size_t)r * d_in;
         T* wc = W_c + (size_t)s * K;
         int32_t* ix = idx + (size_t)s * K;
@@ -338,14 +322,18 @@ __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_compact_rows(const T* 
 
         int base = 0;   // kept columns of the batches before (same in every lane)
         for (int col0 = 0; col0 < d_in; col0 += kBatchCols) {
-            if (pieces && (i != wv || col0 != 0)) load_batch(r, col0);
+            if (pieces && (i != wv || col0 != 0)) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (col0 + u * kWave * kMaskCols < d_in) ahead[u] = load_piece(m, col0 + (u * kWave + lane) * kMaskCols, d_in);
+            }
             int in_batch = 0;
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int col = col0 + (u * kWave + lane) * kMaskCols;
                 if (col0 + u * kWave * kMaskCols >= d_in) break;
-                uint32_t bits = BITS ? ahead_bits[u] : pieces ? kept_bits(ahead[BITS ? 0 : u]) : kept_bits_short(mask + (size_t)r * d_in, col, d_in);
-                const int first = (BITS ? col : pieces ? ahead[BITS ? 0 : u].first : 0) - col0;
+                uint32_t bits = pieces ? kept_bits(ahead[u]) : kept_bits_short(m, col, d_in);
+                const int first = (pieces ? ahead[u].first : 0) - col0;
                 // kept columns in the lanes below, and in all lanes: bit planes of the lanes' counts (0..16)
                 const uint32_t n = __popc(bits);
                 int before = 0, total = 0;
@@ -461,7 +449,7 @@ srigl_status srigl_check_fanin(const uint8_t* mask, const int32_t* idx, int32_t 
 
 static srigl_status condense_core(const void* W, srigl_dtype w_dtype, const uint8_t* mask, int32_t d_out, int32_t d_in, int32_t K,
                                   int32_t cap_rows, void* W_c, int32_t* idx, int32_t* active, uint16_t* seg, void* packed,
-                                  size_t packed_bytes, void* workspace, size_t workspace_bytes, srigl_report* report_dev, hipStream_t st) {
+                                  size_t packed_bytes, void* workspace, srigl_report* report_dev, hipStream_t st) {
     if (d_out < 0 || d_in < 0 || K < 0 || K > d_in || cap_rows < 0 || report_dev == nullptr) return SRIGL_ERR_INVALID_ARG;
     if (w_dtype != SRIGL_F32 && w_dtype != SRIGL_BF16) return SRIGL_ERR_INVALID_ARG;
     if (d_out > 0 && d_in > 0 && (W == nullptr || mask == nullptr)) return SRIGL_ERR_INVALID_ARG;
@@ -477,12 +465,7 @@ static srigl_status condense_core(const void* W, srigl_dtype w_dtype, const uint
     uint8_t* stored = static_cast<uint8_t*>(workspace);
     uint8_t* bad = stored ? stored + (size_t)(d_out + 127) / 128 * 16 : nullptr;
     const int flag_blocks = (d_out + kFlagRows - 1) / kFlagRows;
-    const size_t plain = d_out > 0 ? (srigl_workspace_bytes(d_out) + 15) / 16 * 16 : 0;
-    const bool bits = d_out > 0 && d_in >= kMaskCols && workspace_bytes >= plain + (size_t)d_out * row_bit_words(d_in) * sizeof(uint16_t) &&
-                      (reinterpret_cast<uintptr_t>(workspace) & 1) == 0;
-    uint16_t* const kept = bits ? reinterpret_cast<uint16_t*>(stored + plain) : nullptr;
-    if (d_out > 0)
-        hipLaunchKernelGGL(bits ? k_row_flags<true> : k_row_flags<false>, dim3(flag_blocks), dim3(kFlagRows * kWave), 0, st, mask, d_out, d_in, K, stored, bad, kept);
+    if (d_out > 0) hipLaunchKernelGGL(k_row_flags, dim3(flag_blocks), dim3(kFlagRows * kWave), 0, st, mask, d_out, d_in, K, stored, bad);
     // one row per wavefront; layers of more than 131072 rows several, so that the bits every workgroup reads stay a small part
     int rows_per_block = kRowsPerBlock;
     while ((d_out + rows_per_block - 1) / rows_per_block > 32768) rows_per_block *= 2;
@@ -491,12 +474,12 @@ static srigl_status condense_core(const void* W, srigl_dtype w_dtype, const uint
     const size_t lds = sizeof(uint16_t) * kRowsPerBlock * (size_t)list_cap;
     const int ss = srigl_seg_stride(d_in);
     if (w_dtype == SRIGL_F32)
-        hipLaunchKernelGGL((bits ? k_compact_rows<uint32_t, true> : k_compact_rows<uint32_t, false>), dim3(blocks), dim3(kRowsPerBlock * kWave), lds, st, static_cast<const uint32_t*>(W), mask, d_out,
-                           d_in, K, cap_rows, stored, bad, kept, static_cast<uint32_t*>(W_c), idx, active, seg, ss,
+        hipLaunchKernelGGL(k_compact_rows<uint32_t>, dim3(blocks), dim3(kRowsPerBlock * kWave), lds, st, static_cast<const uint32_t*>(W), mask, d_out,
+                           d_in, K, cap_rows, stored, bad, static_cast<uint32_t*>(W_c), idx, active, seg, ss,
                            static_cast<unsigned char*>(packed), pl, rows_per_block, list_cap, report_dev);
     else
-        hipLaunchKernelGGL((bits ? k_compact_rows<uint16_t, true> : k_compact_rows<uint16_t, false>), dim3(blocks), dim3(kRowsPerBlock * kWave), lds, st, static_cast<const uint16_t*>(W), mask, d_out,
-                           d_in, K, cap_rows, stored, bad, kept, static_cast<uint16_t*>(W_c), idx, active, seg, ss,
+        hipLaunchKernelGGL(k_compact_rows<uint16_t>, dim3(blocks), dim3(kRowsPerBlock * kWave), lds, st, static_cast<const uint16_t*>(W), mask, d_out,
+                           d_in, K, cap_rows, stored, bad, static_cast<uint16_t*>(W_c), idx, active, seg, ss,
                            static_cast<unsigned char*>(packed), pl, rows_per_block, list_cap, report_dev);
     return hip_ok(hipGetLastError());
 }
@@ -507,7 +490,7 @@ srigl_status srigl_condense(const void* W, srigl_dtype w_dtype, const uint8_t* m
                             size_t workspace_bytes, srigl_report* report_dev, void* stream) {
     if (d_out >= 0 && workspace_bytes < srigl_workspace_bytes(d_out)) return SRIGL_ERR_CAPACITY;
     return condense_core(W, w_dtype, mask, d_out, d_in, K, cap_rows, W_c, idx, active, seg, packed, packed_bytes, workspace,
-                         workspace_bytes, report_dev, static_cast<hipStream_t>(stream));
+                         report_dev, static_cast<hipStream_t>(stream));
 }
 
 // Device address of `scratch` on the current device, looked up once per device.
@@ -537,7 +520,7 @@ srigl_status srigl_condense_static(const void* W, srigl_dtype w_dtype, const uin
     if (st != SRIGL_OK) return st;
     // every bit of rows [0, d_out) is written by the first kernel before the second reads it, so what an earlier call left in
     // the scratch is never seen and nothing has to be cleared
-    return condense_core(W, w_dtype, mask, d_out, d_in, K, cap_rows, W_c, idx, active, seg, packed, packed_bytes, ws, 0, report_dev,
+    return condense_core(W, w_dtype, mask, d_out, d_in, K, cap_rows, W_c, idx, active, seg, packed, packed_bytes, ws, report_dev,
                          static_cast<hipStream_t>(stream));
 }
 

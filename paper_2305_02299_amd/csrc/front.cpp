@@ -149,7 +149,7 @@ at::Tensor scratch(size_t bytes, const at::Tensor& like) {
 // B None: the rows of x, which must be [rows, d_in]; y None: allocated; idx in a 16-bit container: the narrow-index call.
 // blocked: the call may take the matrix cores, from this copy of the terms, or with None from one that it makes for itself, in the same
 // stream and from what the arrays hold then.  Nothing is kept: 4096 -> 16384 (13108 rows stored, K = 205) at batch 2048 pays 10 us of
-// 237 for it, and weights that changed since, in whatever way, are the weights that count.
+// 210 for it, and weights that changed since, in whatever way, are the weights that count.
 PyObject* linear_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded([&](PyObject*& out) {
         if (n != 15) need(n, 14);
@@ -294,15 +294,9 @@ PyObject* condense(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
         if (hipStreamIsCapturing(st.stream(), &capture) != hipSuccess || capture != hipStreamCaptureStatusNone)
             fail(PyExc_RuntimeError, "the report is waited for, which a captured stream cannot be (srigl_condense can)");
         const int64_t k = K > 0 ? K : 0;
-        // Where the mask is large its bits are kept between the kernels' two passes, beside the workspace (4096 -> 16384: 3.4 us less; below
-        // 8 MB less than the allocation costs), in memory that goes back in the order of the stream.
-        const size_t ws_small = srigl_workspace_bytes(d_out), mask_bytes = (size_t)d_out * (size_t)d_in;
-        const bool bits = mask_bytes >= (size_t)8 << 20;
-        const size_t ws_bytes = bits ? (ws_small + 15) / 16 * 16 + (size_t)d_out * (((size_t)d_in + 1023) / 1024 * 128) : ws_small;
+        const size_t ws_bytes = srigl_workspace_bytes(d_out);
         at::Tensor W_c = fresh({d_out, k}, W->scalar_type(), *W), idx = fresh({d_out, k}, at::kInt, *W);
-        at::Tensor active = fresh({d_out + (bits ? 0 : (int64_t)(ws_bytes + 3) / 4)}, at::kInt, *W);   // (with a small workspace behind it)
-        const at::Tensor work = bits ? fresh({(int64_t)ws_bytes}, at::kByte, *W) : at::Tensor();
-        void* const wsp = bits ? work.data_ptr() : static_cast<int32_t*>(active.data_ptr()) + d_out;
+        at::Tensor active = fresh({d_out + (int64_t)(ws_bytes + 3) / 4}, at::kInt, *W);   // (with the workspace behind it)
         at::Tensor seg, packed;
         if (want_seg) seg = fresh({d_out, srigl_seg_stride(d_in)}, at::kShort, *W);
         const size_t packed_bytes = srigl_packed_bytes(d_out, K, d_in, wt);
@@ -317,7 +311,7 @@ PyObject* condense(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
         Py_BEGIN_ALLOW_THREADS
         rc = srigl_condense(W->data_ptr(), wt, static_cast<const uint8_t*>(mask->data_ptr()), d_out, d_in, K, d_out, wcp,
                             static_cast<int32_t*>(idx.data_ptr()), static_cast<int32_t*>(active.data_ptr()), static_cast<uint16_t*>(sgp), pkp,
-                            want_packed ? (size_t)packed.numel() : 0, wsp, ws_bytes, rep, st.stream());
+                            want_packed ? (size_t)packed.numel() : 0, static_cast<int32_t*>(active.data_ptr()) + d_out, ws_bytes, rep, st.stream());
         // (the stream is asked now and then, so that the wait ends whatever happened to the launches; asked every 1024 polls it took
         // 6 us of a call's 22)
         for (unsigned polls = 1; rc == SRIGL_OK; ++polls) {

@@ -171,7 +171,7 @@ struct BlockedArgs {
 // The rows of a tile whose bits are set in `spoiled`, computed again from the neurons' own terms: eight rows of x at a time stand in LDS,
 // interleaved, so that a term's eight factors come with one 16-byte read; a wavefront takes a neuron, its lanes the terms.  `area` bytes of
 // LDS at smem are free (inputs wider than area / 16 columns go through it in runs, the sums so far waiting at `sums`, [bn][8]).
-// 4096 -> 16384 (13108 stored, K = 205) at batch 2048: 245 us as it is, 320 with one NaN in the batch, 3.4 ms with one in every row, whatever
+// 4096 -> 16384 (13108 stored, K = 205) at batch 2048: 245 us as it was, 320 with one NaN in the batch, 3.4 ms with one in every row, whatever
 // else (the gathering kernel: 0.85 ms); with every sum added up by one lane, term after term from memory, 1.3 ms and 23 ms.  (Rewritten
 // operands through the matrix cores once more, four passes, took 2.8 ms for either, and its registers 3 to 7 % of every call.)
 constexpr int kMendRows = 8, kMendAhead = 4;   // rows at a time; loads of 64 terms in flight, for two neurons

@@ -208,31 +208,3 @@ def test_host_side_argument_errors():
     with pytest.raises(B_.SriglError) as e:
         B_.srigl_condense(W, m, 4, 8, 9, 4, W, i, i, None, ws, rep)
     assert e.value.status == B_.ERR_INVALID_ARG
-
-
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("d_in,d_out,K", [(16, 9, 3), (17, 40, 17), (1023, 70, 60), (1024, 33, 0), (1040, 12, 400), (4097, 21, 333), (8200, 10, 5000)])
-def test_workspace_with_room_for_the_masks_bits(d_in, d_out, K, dtype):
-    """The same arrays, streaming copy and report with the mask's bits kept as with a second pass over the mask, at every edge of a lane's 16
-    columns, a load's 1024 and a batch's 4096; a byte less than the room takes the second pass."""
-    g = torch.Generator(device="cuda").manual_seed(d_in + K)
-    W = torch.randn(d_out, d_in, device="cuda", generator=g).to(torch.float32 if dtype == "f32" else torch.bfloat16)
-    mask = torch.zeros(d_out, d_in, dtype=torch.uint8, device="cuda")
-    mask.scatter_(1, torch.rand(d_out, d_in, device="cuda", generator=g).topk(K, 1).indices, 0x80)
-    mask[::5] = 0
-    code, small = B_.F32 if dtype == "f32" else B_.BF16, B_.lib.srigl_workspace_bytes(d_out)
-    room = (small + 15) // 16 * 16 + d_out * ((d_in + 1023) // 1024) * 128
-    results = []
-    for nbytes in (small, room - 1, room):
-        ws = torch.full((nbytes,), 0xa5, dtype=torch.uint8, device="cuda")
-        W_c, idx = torch.zeros(d_out, K, dtype=W.dtype, device="cuda"), torch.zeros(d_out, K, dtype=torch.int32, device="cuda")
-        active, rep = torch.zeros(d_out, dtype=torch.int32, device="cuda"), B_.new_report("cuda")
-        seg = torch.zeros(d_out, B_.srigl_seg_stride(d_in), dtype=torch.int16, device="cuda")
-        packed = torch.zeros(max(16, B_.srigl_packed_bytes(d_out, K, d_in, code)), dtype=torch.uint8, device="cuda")
-        B_.srigl_condense(W, mask, d_out, d_in, K, d_out, W_c, idx, active, seg, ws, rep, packed)
-        results.append([t.cpu() for t in (W_c.view(torch.int32 if dtype == "f32" else torch.int16), idx, active, seg, packed)] + [B_.read_report(rep)])
-    for other in results[1:]:
-        assert all(torch.equal(a, b) for a, b in zip(results[0][:-1], other[:-1])) and results[0][-1] == other[-1]
-    if K:
-        rows = torch.arange(d_out)[torch.arange(d_out) % 5 != 0]
-        assert torch.equal(results[2][1][:len(rows)], torch.stack([mask[r].cpu().nonzero().flatten() for r in rows]).int())
