@@ -301,8 +301,9 @@ PyObject* condense(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
         if (want_seg) seg = fresh({d_out, srigl_seg_stride(d_in)}, at::kShort, *W);
         const size_t packed_bytes = srigl_packed_bytes(d_out, K, d_in, wt);
         if (want_packed) packed = fresh({(int64_t)(packed_bytes > 16 ? packed_bytes : 16)}, at::kByte, *W);
-        at::Tensor report = at::empty({(int64_t)sizeof(srigl_report)}, at::TensorOptions().dtype(at::kByte).pinned_memory(true));
-        srigl_report* rep = static_cast<srigl_report*>(report.data_ptr());
+        // (from the allocator that pinned tensors come from, without the tensor: 768 -> 3072 16.3 -> 16.1 us a call)
+        const at::DataPtr report = at::globalContext().getPinnedMemoryAllocator(at::kCUDA)->allocate(sizeof(srigl_report));
+        srigl_report* rep = static_cast<srigl_report*>(report.get());
         constexpr int32_t kPending = -7;
         __atomic_store_n(&rep->status, kPending, __ATOMIC_RELEASE);
         void *wcp = W_c.data_ptr(), *sgp = want_seg ? seg.data_ptr() : nullptr, *pkp = want_packed ? packed.data_ptr() : nullptr;
