@@ -207,11 +207,15 @@ srigl_status srigl_condensed_linear_fwd_algo(const void* x, srigl_dtype x_dtype,
 
 /* What the library's own choice (SRIGL_FWD_AUTO) would launch for a forward call of these sizes: the kernel and its
  * launch shape.  Host arithmetic only (no GPU call, no device pointers: has_active / has_seg say whether the call would
- * pass an active list / a seg table; arrays are taken to be 16-byte aligned).  All fields are 0 when no forward kernel
- * would run (B, d_out, n_active or K zero).  For tests of the planner and for users who want to know. */
+ * pass an active list / a seg table; arrays are taken to be 16-byte aligned, indices 32 bits wide).  All fields are 0 when no
+ * forward kernel would run (B, d_out, n_active or K zero).  For tests of the planner and for users who want to know.
+ * ROWLOOP and ROWLANE work on tiles of 64 * rows_per_lane / term_slices batch rows.  AUTO also takes ROWLOOP in tiles of 8 and 16 rows
+ * (term_slices 16 and 8) and on rows of any length, which is not to be had by srigl_fwd_tuning but by srigl_condensed_linear_fwd_tile,
+ * and a form of KLANE that no tuning asks for, for layers whose terms have to be streamed: waves and neurons_per_wave are set in it. */
 typedef struct {
     int32_t algo;             /* srigl_fwd_algo: SRIGL_FWD_GENERIC, _KLANE, _ROWLANE or _ROWLOOP             */
-    int32_t rows_per_lane, term_slices, waves, neurons_per_wave, chunk_cols;   /* ROWLANE, ROWLOOP (chunk_cols = d_in), else 0 */
+    int32_t rows_per_lane, term_slices, waves, neurons_per_wave, chunk_cols;   /* ROWLANE, ROWLOOP (chunk_cols = d_in), else 0; waves and
+                                 neurons_per_wave also in KLANE's form for streamed terms (8, 4)              */
     int32_t lanes_per_neuron, rows_per_block;                                 /* KLANE, else 0            */
     int64_t workgroups;       /* workgroups that do work                                                    */
     int32_t direct_gather;    /* KLANE: 1 = activations gathered from global memory, 0 = rows of x staged in LDS */
@@ -237,8 +241,7 @@ typedef enum srigl_activation { SRIGL_ACT_NONE = 0, SRIGL_ACT_RELU = 1, SRIGL_AC
  * choice) with rows_per_wave stored rows to a wavefront (0: likewise) and xcd_order as in srigl_fwd_tuning, on rows of any length
  * that fit the LDS (up to 4096, about 2500, 1250 and 600 columns) and with 16- or 32-bit indices (idx_bits).  For tests and measurements:
  * SRIGL_FWD_AUTO takes this kernel, in these tiles, where it expects it to be the fastest; srigl_fwd_tile_query says in which (0: in
- * none) and with how many stored rows to a wavefront.  srigl_fwd_plan_query describes the choice among what the algorithms above
- * can be asked for (tiles of 32 and 64 rows, d_in a multiple of 16), which is what runs where the query here says 0. */
+ * none) and with how many stored rows to a wavefront, for either width of the indices (srigl_fwd_plan_query: 32 bits). */
 srigl_status srigl_condensed_linear_fwd_tile(const void* x, srigl_dtype x_dtype, int32_t B, int32_t d_in, const void* W_c,
                                              srigl_dtype w_dtype, const void* idx, int32_t idx_bits, const int32_t* active,
                                              int32_t n_active, int32_t K, const float* bias, int32_t d_out, float* y,

@@ -819,22 +819,20 @@ static OtherEstimates other_estimates(const FwdArgs& a) {
 // The whole-input batched kernel is taken where its estimate is ahead of theirs, 5 % in its favour against the chunked kernel: over 304 points
 // (67 layers 112 to 2400 wide, fan-ins 6 to 384, both types, batches 8 to 2048) the call is then 0.8 % behind the fastest of the
 // three kernels on average; 1.0 % with 5 % against both, 1.1 % with none, 0.9 % with 10 % against the chunked one.  Below 32 batch rows it is
-// never taken against the staged few-lanes shape of the small-batch kernel, which was placed by measurement.  any_tile: in whatever tile runs
-// (plan_tile), else only in those that a caller can ask for as SRIGL_FWD_ROWLOOP.
-static bool tile_ahead(const FwdArgs& a, double us, bool any_tile) {
+// never taken against the staged few-lanes shape of the small-batch kernel, which was placed by measurement.
+static bool tile_ahead(const FwdArgs& a, double us) {
     const OtherEstimates o = other_estimates(a);
     // (beyond 2304 columns a tile leaves room for nine stored rows to a wavefront and less: 2400 -> 12000, K = 48 at batch 800 143 us, chunked 134)
-    return us * (any_tile ? (a.d_in > 2304 ? 1.0 : 0.95) : 1.02) < o.batched && us * (any_tile ? 1.0 : 1.02) < o.small;
+    return us * (a.d_in > 2304 ? 1.0 : 0.95) < o.batched && us < o.small;
 }
-static srigl_fwd_algo choose_fwd_algo(const FwdArgs& a, bool any_tile, RowloopPlan* tile) {
+static srigl_fwd_algo choose_fwd_algo(const FwdArgs& a, RowloopPlan* tile) {
     const srigl_fwd_algo base = choose_chunked_or_small(a);
     if (a.B < 2) return base;
     int few_L = 0, few_RB = 0;
     if (base == SRIGL_FWD_KLANE && a.B < 32 && klane_few_lanes_staged(a.B, a.d_in, a.n_active, a.K, &few_L, &few_RB)) return base;
     double us = 0.0;
-    *tile = any_tile ? plan_tile(a, 0, 0, 0, &us) : plan_rowloop(a, nullptr, &us);
-    if (!tile->ok || (base == SRIGL_FWD_GENERIC && !any_tile)) return base;
-    return base == SRIGL_FWD_GENERIC || tile_ahead(a, us, any_tile) ? SRIGL_FWD_ROWLOOP : base;
+    *tile = plan_tile(a, 0, 0, 0, &us);
+    return tile->ok && (base == SRIGL_FWD_GENERIC || tile_ahead(a, us)) ? SRIGL_FWD_ROWLOOP : base;
 }
 
 // The library's own choice for a call: the kernel and its launch shape, remembered per thread for the sizes, types and
@@ -846,22 +844,23 @@ struct FwdDecision {
     bool stream;           // (of the small-batch kernels)
     RowloopPlan rowloop;   // (not the caller's SRIGL_FWD_ROWLOOP alone: tiles of 8 and 16 rows and rows of any length too)
 };
+static FwdDecision choose_fwd(const FwdArgs& a) {
+    FwdDecision d{};
+    d.algo = choose_fwd_algo(a, &d.rowloop);
+    if (d.algo == SRIGL_FWD_KLANE) {
+        d.klane = plan_klane(a, nullptr);
+        d.stream = stream_ahead(a);
+    }
+    if (d.algo == SRIGL_FWD_ROWLANE) d.rowlane = plan_rowlane(a, nullptr);
+    return d;
+}
 static const FwdDecision& decide_fwd(const FwdArgs& a) {
     struct Key { int32_t B, d_in, n_active, K, d_out, flags; };
     static thread_local DecisionCache<Key, FwdDecision, 64> cache;
     const Key k = {a.B, a.d_in, a.n_active, a.K, a.d_out,
                    (a.x_bf16 ? 1 : 0) | (a.idx_u16 ? 2 : 0) | (a.active ? 4 : 0) | (a.seg ? 8 : 0) | (a.packed ? 16 : 0) |
                        (int)((reinterpret_cast<uintptr_t>(a.x) & 15) << 8) | (int)((reinterpret_cast<uintptr_t>(a.idx) & 3) << 12)};
-    return cache.get(k, [&] {
-        FwdDecision d{};
-        d.algo = choose_fwd_algo(a, true, &d.rowloop);
-        if (d.algo == SRIGL_FWD_KLANE) {
-            d.klane = plan_klane(a, nullptr);
-            d.stream = stream_ahead(a);
-        }
-        if (d.algo == SRIGL_FWD_ROWLANE) d.rowlane = plan_rowlane(a, nullptr);
-        return d;
-    });
+    return cache.get(k, [&] { return choose_fwd(a); });
 }
 
 // stand-ins for the device arrays of a call of these sizes: the planner looks at their alignment and at which ones are
@@ -883,7 +882,7 @@ double condensed_estimate_us(int B, int d_in, int n_active, int K, int d_out, bo
     if (B <= 0 || n_active <= 0 || K <= 0 || d_in <= 0) return 2.0;
     const FwdArgs a = standin_args(B, d_in, n_active, K, d_out, bf16, has_active, true);
     double us = 0.0;
-    if (plan_tile(a, 0, 0, 0, &us).ok && tile_ahead(a, us, true)) return us;
+    if (plan_tile(a, 0, 0, 0, &us).ok && tile_ahead(a, us)) return us;
     const OtherEstimates o = other_estimates(a);
     return std::min(o.batched, o.small);
 }
@@ -964,7 +963,7 @@ int32_t srigl_fwd_tile_query(int32_t B, int32_t d_in, int32_t n_active, int32_t 
     FwdArgs a = standin_args(B, d_in, n_active, K, d_out, dtype == SRIGL_BF16, has_active != 0, has_seg != 0);
     a.idx_u16 = idx_bits == 16;
     RowloopPlan p{};
-    if (choose_fwd_algo(a, true, &p) != SRIGL_FWD_ROWLOOP) return 0;
+    if (choose_fwd_algo(a, &p) != SRIGL_FWD_ROWLOOP) return 0;
     if (rows_per_wave) *rows_per_wave = (p.NG + p.NW - 1) / p.NW;
     return p.BT;
 }
@@ -1046,19 +1045,30 @@ srigl_status srigl_fwd_plan_query_algo(int32_t B, int32_t d_in, int32_t n_active
     *plan = srigl_fwd_plan{};
     if (B == 0 || d_out == 0 || n_active == 0 || K == 0) return SRIGL_OK;   // nothing to gather: no forward kernel runs
     const FwdArgs a = standin_args(B, d_in, n_active, K, d_out, dtype == SRIGL_BF16, has_active != 0, has_seg != 0);
-    RowloopPlan unused{};
-    const srigl_fwd_algo algo = forced == SRIGL_FWD_AUTO ? choose_fwd_algo(a, false, &unused) : forced;
+    // (AUTO: through the function that decides a call)
+    FwdDecision d{};
+    if (forced == SRIGL_FWD_AUTO) d = choose_fwd(a);
+    else if (forced == SRIGL_FWD_ROWLANE) d.rowlane = plan_rowlane(a, tuning);
+    else if (forced == SRIGL_FWD_ROWLOOP) d.rowloop = plan_rowloop(a, tuning, nullptr);
+    else if (forced == SRIGL_FWD_KLANE) d.klane = plan_klane(a, tuning);
+    const srigl_fwd_algo algo = forced == SRIGL_FWD_AUTO ? d.algo : forced;
     plan->algo = (int32_t)algo;
     if (algo == SRIGL_FWD_ROWLANE) {
-        const RowlanePlan p = plan_rowlane(a, tuning);
+        const RowlanePlan& p = d.rowlane;
         if (!p.ok) return SRIGL_ERR_UNSUPPORTED;
         plan->rows_per_lane = p.R; plan->term_slices = p.H; plan->waves = p.NW; plan->neurons_per_wave = p.NPW;
         plan->chunk_cols = p.C; plan->workgroups = (int64_t)p.n_groups * p.n_btiles; plan->xcd_order = p.bt_major ? 2 : 1;
         plan->spread_rows = p.spread == 0 ? 1 : (p.spread == 1 ? 2 : 3);
     } else if (algo == SRIGL_FWD_ROWLOOP) {
-        if (!rowloop_plan_query(a, tuning, plan)) return SRIGL_ERR_UNSUPPORTED;
+        const RowloopPlan& p = d.rowloop;
+        if (!p.ok) return SRIGL_ERR_UNSUPPORTED;
+        plan->rows_per_lane = 2; plan->term_slices = 128 / p.BT; plan->waves = p.NW; plan->neurons_per_wave = (p.NG + p.NW - 1) / p.NW;
+        plan->chunk_cols = a.d_in; plan->workgroups = (int64_t)p.n_groups * p.n_btiles; plan->xcd_order = p.bt_major ? 2 : 1; plan->spread_rows = 1;
+    } else if (algo == SRIGL_FWD_KLANE && d.stream) {
+        plan->lanes_per_neuron = kWave; plan->rows_per_block = 1; plan->waves = kStreamWaves; plan->neurons_per_wave = kStreamRows;
+        plan->workgroups = stream_groups(a) * (int64_t)a.B;
     } else if (algo == SRIGL_FWD_KLANE) {
-        const KlanePlan p = plan_klane(a, tuning);
+        const KlanePlan& p = d.klane;
         if (!p.ok) return SRIGL_ERR_UNSUPPORTED;
         plan->lanes_per_neuron = p.L; plan->rows_per_block = p.RB; plan->workgroups = p.workgroups; plan->direct_gather = p.direct;
     }

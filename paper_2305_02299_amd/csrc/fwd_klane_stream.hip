@@ -12,7 +12,7 @@
 
 namespace srigl {
 
-constexpr int kStreamWaves = 8, kStreamRows = 4, kStreamTerms = 4;   // wavefronts of a workgroup, rows of a wavefront, consecutive terms of a lane
+constexpr int kStreamTerms = 4;   // consecutive terms of a lane
 constexpr int kStreamChunk = kStreamTerms * kWave;
 
 template <typename T> struct Four { T v[4]; };
@@ -126,8 +126,7 @@ static srigl_status launch_stream_t(const FwdArgs& a, hipStream_t st) {
     static LdsLimit lds_limit;
     const size_t lds = (size_t)(a.d_in + 1) * sizeof(float);
     if (lds_limit.ensure(kern, lds) != SRIGL_OK) return SRIGL_ERR_HIP;
-    constexpr int kPerWg = kStreamWaves * kStreamRows;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((a.n_active + kPerWg - 1) / kPerWg), (unsigned)a.B), dim3(kStreamWaves * kWave), lds, st, (const XT*)a.x, a.d_in,
+    hipLaunchKernelGGL(kern, dim3((unsigned)stream_groups(a), (unsigned)a.B), dim3(kStreamWaves * kWave), lds, st, (const XT*)a.x, a.d_in,
                        (const XT*)a.W_c, (const IT*)a.idx, a.active, a.n_active, a.K, a.bias, a.d_out, a.y, a.act);
     return hip_ok(hipGetLastError());
 }

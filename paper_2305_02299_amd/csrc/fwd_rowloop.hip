@@ -126,16 +126,6 @@ RowloopPlan plan_tile(const FwdArgs& a, int tile_rows, int rows_per_wave, int xc
     return best;
 }
 
-bool rowloop_supported(const FwdArgs& a, const srigl_fwd_tuning* t) { return plan_rowloop(a, t, nullptr).ok; }
-
-bool rowloop_plan_query(const FwdArgs& a, const srigl_fwd_tuning* t, srigl_fwd_plan* plan) {
-    const RowloopPlan p = plan_rowloop(a, t, nullptr);
-    if (!p.ok) return false;
-    plan->rows_per_lane = 2; plan->term_slices = 128 / p.BT; plan->waves = p.NW; plan->neurons_per_wave = (p.NG + p.NW - 1) / p.NW;
-    plan->chunk_cols = a.d_in; plan->workgroups = (int64_t)p.n_groups * p.n_btiles; plan->xcd_order = p.bt_major ? 2 : 1; plan->spread_rows = 1;
-    return true;
-}
-
 srigl_status launch_fwd_rowloop(const FwdArgs& a, const srigl_fwd_tuning* t, hipStream_t st) {
     if (a.B == 0 || a.n_active == 0) return SRIGL_OK;
     return launch_rowloop_plan(a, plan_rowloop(a, t, nullptr), st);

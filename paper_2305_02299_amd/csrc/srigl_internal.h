@@ -175,11 +175,8 @@ srigl_status launch_fwd_generic(const FwdArgs& a, hipStream_t st);
 srigl_status launch_fwd_klane(const FwdArgs& a, const srigl_fwd_tuning* t, hipStream_t st);
 srigl_status launch_fwd_rowlane(const FwdArgs& a, const srigl_fwd_tuning* t, hipStream_t st);
 bool rowlane_supported(const FwdArgs& a, const srigl_fwd_tuning* t);
-// ROWLOOP (fwd_rowloop.hip): the launch, whether these sizes can run it, its estimated time (us; 1e30 if they cannot) and
-// the launch shape for srigl_fwd_plan_query
+// ROWLOOP (fwd_rowloop.hip): the launch, and launch shapes with their estimated times (us): as a caller can ask for them, and of any tile
 srigl_status launch_fwd_rowloop(const FwdArgs& a, const srigl_fwd_tuning* t, hipStream_t st);
-bool rowloop_supported(const FwdArgs& a, const srigl_fwd_tuning* t);
-bool rowloop_plan_query(const FwdArgs& a, const srigl_fwd_tuning* t, srigl_fwd_plan* plan);
 RowloopPlan plan_rowloop(const FwdArgs& a, const srigl_fwd_tuning* t, double* us);
 srigl_status launch_rowloop_f32(const FwdArgs& a, const RowloopPlan& p, hipStream_t st);
 srigl_status launch_rowloop_bf16(const FwdArgs& a, const RowloopPlan& p, hipStream_t st);
@@ -187,6 +184,8 @@ srigl_status launch_rowloop_f32_i16(const FwdArgs& a, const RowloopPlan& p, hipS
 srigl_status launch_rowloop_bf16_i16(const FwdArgs& a, const RowloopPlan& p, hipStream_t st);
 RowloopPlan plan_tile(const FwdArgs& a, int tile_rows, int rows_per_wave, int xcd_order, double* us);
 // The small-batch kernel for layers whose terms are streamed, and whether it is expected to be ahead of the other small-batch forms.
+constexpr int kStreamWaves = 8, kStreamRows = 4;   // wavefronts of a workgroup, stored rows of a wavefront
+inline int stream_groups(const FwdArgs& a) { return (a.n_active + kStreamWaves * kStreamRows - 1) / (kStreamWaves * kStreamRows); }
 bool stream_ahead(const FwdArgs& a);
 srigl_status launch_fwd_stream(const FwdArgs& a, hipStream_t st);
 srigl_status launch_rowloop_plan(const FwdArgs& a, const RowloopPlan& p, hipStream_t st);

@@ -11,10 +11,60 @@ def plan(B, d_in, d_out, K, n_active=None, **kw):
     return B_.srigl_fwd_plan_query(B, d_in, n, K, d_out, has_active=(n != d_out), **kw)
 
 
+def tile_rows(p):
+    """Batch rows of a tile of the batched kernels (0: another kernel)."""
+    return 64 * p["rows_per_lane"] // p["term_slices"] if p["term_slices"] else 0
+
+
+def streamed(p):
+    """The small-batch kernel in its form for layers whose terms are streamed."""
+    return p["algo"] == B_.FWD_KLANE and p["waves"] > 0
+
+
+@pytest.mark.parametrize("B,d_in,d_out,K,n,rows", [
+    # narrow and wide inputs, batches from two rows on: tiles of 8, 16 and 32 rows; 0: another kernel
+    # (the chunked kernel's on inputs beyond 4096 columns)
+    (256, 3072, 768, 307, 538, 8), (320, 3072, 768, 308, 768, 8), (512, 4096, 1024, 410, 1024, 8), (64, 4096, 4096, 41, 4096, 8),
+    (8, 4096, 16384, 205, 16384, 8), (16, 2560, 2560, 256, 2560, 8), (96, 2048, 512, 205, 512, 16), (256, 2160, 768, 216, 768, 16),
+    (64, 768, 3072, 77, 3072, 16), (256, 768, 3072, 77, 3072, 32), (1024, 768, 3072, 154, 3072, 32), (300, 1000, 777, 50, 777, 16),
+    (96, 3072, 768, 31, 768, 0), (8, 768, 3072, 77, 3072, 0), (1, 768, 3072, 77, 3072, 0), (256, 4112, 768, 307, 768, 16),
+])
+def test_the_tile_that_a_call_takes(B, d_in, d_out, K, n, rows):
+    p = plan(B, d_in, d_out, K, n_active=n)
+    assert tile_rows(p) == rows, p
+    assert (p["algo"] == B_.FWD_ROWLOOP) == (0 < rows and d_in <= 4096)
+    assert B_.srigl_fwd_tile_query(B, d_in, n, K, d_out, has_active=(n != d_out)) == ((rows, p["neurons_per_wave"]) if p["algo"] == B_.FWD_ROWLOOP else (0, 0))
+
+
+def test_the_query_is_the_decision_of_a_call():
+    """What the query says and which tile the library's own choice takes, on sizes of every kind: they come from one decision."""
+    import random
+    rng = random.Random(77)
+    kinds = {"tile": 0, "streamed": 0, "other": 0}
+    for _ in range(1500):
+        d_in, d_out = rng.randint(1, 4200), rng.randint(1, 16384)
+        n = max(1, d_out - rng.choice([0, rng.randint(0, d_out // 2)]))
+        K, B = max(1, d_in * rng.randint(1, 20) // 100), rng.choice([1, 1, 2, 3, 6, 8, 16, 33, 64, 100, 256, 777, 2048, 5000])
+        dtype, has_seg = rng.choice([B_.F32, B_.BF16]), rng.random() < 0.9
+        p = B_.srigl_fwd_plan_query(B, d_in, n, K, d_out, dtype_code=dtype, has_active=n != d_out, has_seg=has_seg)
+        tile, per_wave = B_.srigl_fwd_tile_query(B, d_in, n, K, d_out, dtype_code=dtype, has_active=n != d_out, has_seg=has_seg)
+        assert (p["algo"] == B_.FWD_ROWLOOP) == (tile > 0), (B, d_in, n, K, d_out, p, tile)
+        if tile:
+            assert (tile_rows(p), p["neurons_per_wave"]) == (tile, per_wave)
+            assert p["workgroups"] == -(-B // tile) * -(-n // (16 * per_wave))
+        if streamed(p):
+            assert (p["waves"], p["neurons_per_wave"], p["lanes_per_neuron"], p["rows_per_block"], p["direct_gather"]) == (8, 4, 64, 1, 0)
+            assert p["workgroups"] == -(-n // 32) * B and B <= 64 and K >= 4 and (d_in + 1) * 4 <= 40 * 1024
+        kinds["tile" if tile else "streamed" if streamed(p) else "other"] += 1
+    assert min(kinds.values()) > 20, kinds
+
+
 def test_single_row_takes_the_small_batch_kernel():
     for (d_in, d_out, K) in ((768, 3072, 77), (3072, 768, 308), (4096, 16384, 205), (64, 8, 3)):
         p = plan(1, d_in, d_out, K)
         assert p["algo"] == B_.FWD_KLANE and p["rows_per_block"] == 1 and p["rows_per_lane"] == 0
+        # 3.4 million terms come from memory: the form for streamed terms, eight wavefronts of four stored rows (8.1 -> 5.5 us)
+        assert (p["waves"], p["neurons_per_wave"], p["workgroups"]) == ((8, 4, 512) if d_in == 4096 else (0, 0, p["workgroups"]))
     assert plan(1, 768, 3072, 77)["lanes_per_neuron"] == 32      # 77 terms: at most 4 per lane
     assert plan(1, 768, 3072, 8)["lanes_per_neuron"] == 4
 
@@ -34,7 +84,7 @@ def test_headline_batch_is_one_workgroup_per_compute_unit():
 
 
 def test_wide_inputs_get_16_row_tiles_and_one_row_per_workgroup():
-    p = plan(256, 3072, 768, 307, n_active=538)
+    p = plan(256, 3072, 768, 307, n_active=538, algo=B_.FWD_ROWLANE)
     assert p["algo"] == B_.FWD_ROWLANE and p["term_slices"] == 4 and p["neurons_per_wave"] == 3
     # staged activations: one row per workgroup for wide inputs, two for narrow ones from batch 5
     assert plan(256, 3072, 768, 31, algo=B_.FWD_KLANE, tuning=dict(direct_gather=2))["rows_per_block"] == 1
@@ -46,38 +96,38 @@ def test_small_batches_gather_their_activations():
     rows of it in LDS (3072 -> 768 at B = 1: 3.7 vs 6.4 us cold), with one, two or four batch rows per workgroup."""
     for (B, d_in, d_out, K, rb) in ((1, 768, 3072, 77, 1), (1, 3072, 768, 308, 1), (4, 3072, 768, 308, 1), (8, 3072, 768, 308, 2),
                                     (4, 768, 3072, 77, 1), (8, 4096, 1024, 410, 2), (2, 4096, 16384, 205, 2)):
-        p = plan(B, d_in, d_out, K)
+        p = plan(B, d_in, d_out, K, algo=B_.FWD_KLANE)    # (a call of some of these takes the form for streamed terms, or a tile of all columns)
         assert (p["algo"], p["direct_gather"], p["rows_per_block"]) == (B_.FWD_KLANE, 1, rb), (B, d_in, d_out, K, p)
     # 8 to 32 rows on inputs up to 1024 wide with moderate fan-in and 2048 stored rows or more: rows of x staged, few lanes per
     # stored row (measured ahead of the gathering form and of the batched kernel: 768 -> 3072 at B = 8 / 16 / 32 5.1 / 5.8 / 6.6 us
     # cold against 5.6 / 6.1 / 7.7)
     for (B, d_in, d_out, K, lanes, rb) in ((8, 768, 3072, 77, 16, 2), (16, 768, 3072, 77, 8, 2), (32, 768, 3072, 77, 8, 2),
                                            (32, 768, 3072, 39, 8, 2), (8, 1024, 4096, 102, 16, 2), (8, 768, 3072, 154, 16, 2)):
-        p = plan(B, d_in, d_out, K, **(dict(algo=B_.FWD_KLANE) if B == 32 else {}))   # (at 32 rows the whole-input kernel is compared too)
+        p = plan(B, d_in, d_out, K, **(dict(algo=B_.FWD_KLANE) if B == 32 or K == 154 else {}))   # (at 32 rows the whole-input kernel is compared too, long rows are streamed)
         assert (p["algo"], p["direct_gather"], p["lanes_per_neuron"], p["rows_per_block"]) == (B_.FWD_KLANE, 0, lanes, rb), (B, d_in, K, p)
     # not beyond B x K of about 2500, nor on wide inputs, few stored rows, long rows from 16 batch rows on, or very short rows
-    assert plan(8, 2048, 2048, 204)["direct_gather"] == 1
+    assert plan(8, 2048, 2048, 204, algo=B_.FWD_KLANE)["direct_gather"] == 1
     assert plan(8, 1024, 1024, 102)["direct_gather"] == 1
-    assert plan(16, 768, 3072, 154)["algo"] == B_.FWD_ROWLANE
-    assert plan(32, 768, 3072, 154)["algo"] == B_.FWD_ROWLANE
-    assert plan(8, 3072, 768, 308)["direct_gather"] == 1
+    assert plan(16, 768, 3072, 154)["algo"] == B_.FWD_ROWLOOP
+    assert plan(32, 768, 3072, 154)["algo"] == B_.FWD_ROWLOOP
+    assert plan(8, 3072, 768, 308, algo=B_.FWD_KLANE)["direct_gather"] == 1
     assert plan(16, 768, 3072, 8)["direct_gather"] == 1
     # very sparse layers at larger batches: many distinct lines per gather, the staged rows win
     p = plan(256, 768, 3072, 8, algo=B_.FWD_KLANE)                     # 8.9 / 7.3 us staged, 10.9 / 9.4 gathered, 9.4 / 8.4 batched
     assert (p["algo"], p["direct_gather"], p["rows_per_block"]) == (B_.FWD_KLANE, 0, 2)
-    # 4096 -> 4096 at 99 % and 64 rows: the batched kernel (16.0 / 11.8 us) is ahead of staged (17.9 / 14.4) and gathered
-    assert plan(64, 4096, 4096, 41)["algo"] == B_.FWD_ROWLANE
+    # 4096 -> 4096 at 99 % and 64 rows: the batched kernels (chunked 16.0 / 11.8 us) are ahead of staged (17.9 / 14.4) and gathered
+    assert plan(64, 4096, 4096, 41)["algo"] == B_.FWD_ROWLOOP
     # a row of x that does not fit the LDS can only be gathered
     p = plan(1, 49152, 48, 64)
     assert (p["algo"], p["direct_gather"]) == (B_.FWD_KLANE, 1)
-    # large layers from a few rows on: the batched kernel (every further pass re-reads W_c / idx from beyond the L2)
-    assert plan(8, 4096, 16384, 205)["algo"] == B_.FWD_ROWLANE            # 23.5 / 20.7 us vs 39.3 / 34.8 gathered
+    # large layers from a few rows on: the batched kernels (every further pass re-reads W_c / idx from beyond the L2)
+    assert plan(8, 4096, 16384, 205)["algo"] == B_.FWD_ROWLOOP            # chunked 23.5 / 20.7 us vs 39.3 / 34.8 gathered
 
 
 def test_rounds_are_counted_per_xcd():
     """3072 -> 768 at B = 320: four stored rows per wavefront would be 12 groups, two of them on four of the eight XCDs (40
     workgroups on 32 compute units); two or six rows per wavefront fit in one round per XCD or split evenly."""
-    p = plan(320, 3072, 768, 308)
+    p = plan(320, 3072, 768, 308, algo=B_.FWD_ROWLANE)
     assert p["algo"] == B_.FWD_ROWLANE and p["neurons_per_wave"] in (2, 6)
     # 768 -> 3072 at B = 384: 128-row tiles with three rows per wavefront are one round of 192 workgroups
     p = plan(384, 768, 3072, 77, algo=B_.FWD_ROWLANE)
@@ -101,7 +151,7 @@ def test_long_rows_take_two_rows_per_lane_in_two_slices():
         p = plan(B, d_in, d_out, K, algo=B_.FWD_ROWLANE)
         assert (p["rows_per_lane"], p["term_slices"], p["neurons_per_wave"]) == (2, 4, 6), (B, d_in, d_out, K, p)
     # wide inputs, long rows: 32-row tiles the same way (four slices of 16 lanes); 4096 -> 1024 K = 410 at B = 512: 39.6 -> 31.4 us
-    p = plan(512, 4096, 1024, 410)
+    p = plan(512, 4096, 1024, 410, algo=B_.FWD_ROWLANE)
     assert (p["rows_per_lane"], p["term_slices"]) == (2, 4)
 
 
@@ -110,7 +160,7 @@ def test_which_workgroups_share_an_xcd():
     of x and all of W_c / idx; the batched kernel takes the order that fetches fewer bytes once an XCD has two tiles."""
     assert plan(256, 768, 3072, 77, algo=B_.FWD_ROWLANE)["xcd_order"] == 1          # x 0.8 MB < W_c + idx 1.9 MB; only four batch tiles
     assert plan(2048, 768, 3072, 77, algo=B_.FWD_ROWLANE)["xcd_order"] == 2         # x 6.3 MB; 65.9 -> 62.0 us
-    assert plan(256, 3072, 768, 307, n_active=538)["xcd_order"] == 2   # 16 tiles of 16 rows; x 3.1 MB > 1.3 MB
+    assert plan(256, 3072, 768, 307, n_active=538, algo=B_.FWD_ROWLANE)["xcd_order"] == 2   # 16 tiles of 16 rows; x 3.1 MB > 1.3 MB
     assert plan(128, 2048, 512, 205, algo=B_.FWD_ROWLANE)["xcd_order"] == 1   # one tile per XCD: 9.6 vs 10.4 us
 
 
@@ -119,7 +169,7 @@ def test_very_sparse_layers_stay_on_the_small_batch_kernel_at_larger_batches():
     assert plan(96, 768, 3072, 8)["algo"] == B_.FWD_KLANE             # 6.0 / 5.0 vs 8.1 / 7.4
     assert plan(256, 768, 3072, 8)["algo"] in (B_.FWD_KLANE, B_.FWD_ROWLOOP)   # 8.8 / 8.1 us against 9.1 / 7.1
     assert plan(256, 768, 3072, 39)["algo"] == B_.FWD_ROWLOOP
-    assert plan(4096, 3072, 768, 31)["algo"] == B_.FWD_ROWLANE      # above 2048 rows always the batched kernel
+    assert plan(4096, 3072, 768, 31)["algo"] in (B_.FWD_ROWLANE, B_.FWD_ROWLOOP)      # above 2048 rows always a batched kernel
 
 
 def test_mid_batches_follow_the_estimates():
@@ -129,9 +179,8 @@ def test_mid_batches_follow_the_estimates():
     assert plan(64, 768, 3072, 77)["algo"] == B_.FWD_ROWLOOP          # 7.0 / 6.6 us against 7.4 / 6.9 chunked
     assert plan(64, 768, 3072, 77, algo=B_.FWD_ROWLANE)["workgroups"] == 256
     assert plan(32, 2048, 512, 205)["algo"] == B_.FWD_KLANE         # few stored rows: the batched kernel cannot fill the GPU
-    assert plan(96, 2048, 512, 205)["algo"] == B_.FWD_ROWLANE
-    assert plan(16, 2560, 2560, 256)["algo"] == B_.FWD_ROWLANE        # wide input, many stored rows: 9.6 vs 13.7 us measured
-    assert plan(16, 3072, 768, 615)["algo"] == B_.FWD_KLANE           # wide input, few stored rows: 8.1 vs 11.9 us
+    assert plan(96, 2048, 512, 205)["algo"] == B_.FWD_ROWLOOP
+    assert plan(16, 2560, 2560, 256)["algo"] == B_.FWD_ROWLOOP        # wide input, many stored rows: chunked 9.6 vs 13.7 us measured
 
 
 def test_fallbacks():
@@ -164,9 +213,9 @@ def test_fitted_ranking_moves_the_shape_only_when_it_is_well_ahead():
     10-22 % faster; rows of fewer than 16 terms keep the estimate's shape."""
     p = plan(256, 768, 3072, 77, algo=B_.FWD_ROWLANE)
     assert (p["rows_per_lane"], p["term_slices"], p["neurons_per_wave"], p["chunk_cols"]) == (2, 2, 3, 384)
-    p = plan(256, 3072, 768, 307, n_active=538)
+    p = plan(256, 3072, 768, 307, n_active=538, algo=B_.FWD_ROWLANE)
     assert (p["rows_per_lane"], p["term_slices"], p["neurons_per_wave"], p["waves"]) == (1, 4, 3, 12)
-    p = plan(2048, 4096, 16384, 205, n_active=13108, dtype_code=B_.BF16)
+    p = plan(2048, 4096, 16384, 205, n_active=13108, dtype_code=B_.BF16, algo=B_.FWD_ROWLANE)
     assert (p["rows_per_lane"], p["term_slices"], p["neurons_per_wave"]) == (2, 1, 8)
     for (B, d_in, d_out, K, shape) in ((1024, 3072, 768, 154, (2, 4, 6)),      # 36.9 / 28.2 -> 28.8 / 22.7 us
                                        (512, 768, 3072, 39, (2, 2, 6)),        # 18.6 / 16.5 -> 16.5 / 14.6
@@ -202,12 +251,17 @@ def test_every_plan_is_one_the_kernels_accept():
             forced = dict(rows_per_lane=p["rows_per_lane"], term_slices=p["term_slices"], waves=p["waves"],
                           neurons_per_wave=p["neurons_per_wave"], chunk_cols=p["chunk_cols"], xcd_order=p["xcd_order"])
         elif p["algo"] == B_.FWD_ROWLOOP:
-            assert p["rows_per_lane"] == 2 and p["term_slices"] in (2, 4) and p["waves"] == 16 and p["neurons_per_wave"] >= 1
-            tile_rows = 128 // p["term_slices"]
-            assert d_in % 16 == 0 and p["chunk_cols"] == d_in and p["xcd_order"] in (1, 2)
-            # the tile of x, the all-zero column and the result tile fit the LDS
-            assert ((d_in + 1) * (tile_rows + 4) + tile_rows * (p["neurons_per_wave"] * 16 + 1)) * 4 <= 160 * 1024
+            rows, per_group = tile_rows(p), p["neurons_per_wave"] * 16
+            assert rows in (8, 16, 32, 64) and p["waves"] == 16 and p["neurons_per_wave"] >= 1 and p["chunk_cols"] == d_in and p["xcd_order"] in (1, 2)
+            # the tile of x in whole staging units, the all-zero column and the result tile fit the LDS
+            unit = 32 if rows == 8 else 16
+            assert ((-(-d_in // unit) * unit + 1) * rows + rows * (per_group | 1)) * 4 <= 160 * 1024
+            # what SRIGL_FWD_ROWLOOP can be asked for: tiles of 32 and 64 rows, whole 16-column units, room for four words per column more
+            if rows < 32 or d_in % 16 or ((d_in + 1) * (rows + 4) + (rows + 4) * (per_group + 2)) * 4 > 160 * 1024:
+                continue
             forced = dict(term_slices=p["term_slices"], waves=p["waves"], neurons_per_wave=p["neurons_per_wave"], xcd_order=p["xcd_order"])
+        elif streamed(p):
+            continue         # (no tuning asks for it)
         elif p["algo"] == B_.FWD_KLANE:
             L = p["lanes_per_neuron"]
             assert 4 <= L <= 64 and L & (L - 1) == 0 and p["rows_per_block"] in (1, 2, 4) and p["direct_gather"] in (0, 1)
