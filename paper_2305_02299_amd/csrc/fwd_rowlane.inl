@@ -3,6 +3,7 @@
 #pragma once
 #include <type_traits>
 
+#include "ragged_rows.h"
 #include "srigl_internal.h"
 
 namespace srigl {
@@ -96,7 +97,6 @@ __device__ __forceinline__ void load4(const uint16_t* __restrict__ p, bool vec_o
 // run past the last one starts as many elements earlier (`ragged_shift`), and the values are moved up when they are stored.
 // What a load brings from beyond its own row's end lies in columns no index names.  (Element by element behind branches, as
 // these rows were staged before, the loads went out one round trip after the other: 1000 -> 777 at batch 37 20.6 us.)
-__device__ __forceinline__ int ragged_shift(unsigned e, int total) { return max((int)e - (total - 4), 0); }
 __device__ __forceinline__ void load4_at_element(const float* __restrict__ p, Staged4<float>& out) {
     struct __attribute__((packed, aligned(4))) F4 { float x, y, z, w; };
     const F4 v = *reinterpret_cast<const F4*>(p);
@@ -129,7 +129,7 @@ __device__ __forceinline__ void shift4(Staged4<float>& s, int sh) {
     if (sh & 1) { s.v[0] = s.v[1]; s.v[1] = s.v[2]; s.v[2] = s.v[3]; }
 }
 __device__ __forceinline__ void shift4(Staged4<uint16_t>& s, int sh) {
-    const uint64_t v = (((uint64_t)s.w[1] << 32) | s.w[0]) >> (16 * sh);
+    const uint64_t v = move_halves(((uint64_t)s.w[1] << 32) | s.w[0], sh);
     s.w[0] = (uint32_t)v;
     s.w[1] = (uint32_t)(v >> 32);
 }
@@ -464,7 +464,7 @@ __global__ __launch_bounds__(rowlane_max_threads(R)) void k_fwd_rowlane(const XT
         if (u_col[i] < C) {                                                                                     \
             if (!FAST) {   /* only the last row of x ends behind the last place a load can start at */          \
                 const int sh_ = ragged_shift(g_off[i] / (unsigned)sizeof(XT) + (unsigned)((c) * C), tile_total); \
-                if (tile_total >= 4 && __ballot(sh_ > 0) != 0) shift4(st[i], min(sh_, 3));                       \
+                if (tile_total >= 4 && __ballot(sh_ > 0) != 0) shift4(st[i], sh_);                               \
             }                                                                                                   \
             float* d_ = lds + l_off[i];                                                                         \
             if (H == 4 && R == 1) {   /* stride 16: odd column quads write their pairs in the other order (banks 16 apart) */ \
