@@ -438,6 +438,11 @@ srigl_status srigl_structured_linear_fwd_tile(const void* x, srigl_dtype x_dtype
 srigl_status srigl_structured_split_plan(int32_t B, int32_t d_in, int32_t n_active, int32_t d_out, srigl_dtype dtype, int32_t* splits,
                                          size_t* workspace_bytes);
 
+/* The tile of the library's own choice for these sizes, in one part (may_split 0: srigl_structured_linear_fwd) or in the parts of
+ * srigl_structured_split_plan: a srigl_gemm_tile, or 7 for the 256 x 192 tile of bf16 calls (8 wavefronts of 64x96, 2 LDS stages of 128
+ * bytes), which cannot be asked for; 0 where no product runs.  Host-only. */
+int32_t srigl_structured_tile_query(int32_t B, int32_t d_in, int32_t n_active, int32_t d_out, srigl_dtype dtype, int32_t may_split);
+
 srigl_status srigl_structured_linear_fwd_split(const void* x, srigl_dtype x_dtype, int32_t B, int32_t d_in, const void* Wd,
                                                srigl_dtype w_dtype, const int32_t* active, int32_t n_active, const float* bias,
                                                int32_t d_out, float* y, srigl_gemm_tile tile, int32_t splits, void* workspace,

@@ -22,6 +22,7 @@ REPR_CONDENSED, REPR_STRUCTURED = 0, 1
 ACT_NONE, ACT_RELU, ACT_GELU = 0, 1, 2
 FWD_AUTO, FWD_GENERIC, FWD_KLANE, FWD_ROWLANE, FWD_ROWLOOP = range(5)
 TILE_AUTO, TILE_256x256, TILE_256x256_H, TILE_256x128_W4, TILE_256x128, TILE_128x128, TILE_64x64 = range(7)
+TILE_256x192 = 7   # bf16, the library's own choice only
 BLOCKED_64, BLOCKED_128, BLOCKED_256, BLOCKED_192 = 1, 2, 3, 4
 TILES = {"256x256": TILE_256x256, "256x256_h": TILE_256x256_H, "256x128_w4": TILE_256x128_W4, "256x128": TILE_256x128,
          "128x128": TILE_128x128, "64x64": TILE_64x64}
@@ -34,7 +35,7 @@ EXPORTS = (
     "srigl_structured_linear_fwd_tile", "srigl_structured_split_plan", "srigl_structured_linear_fwd_split", "srigl_choose_representation",
     "srigl_condensed_linear_fwd_act", "srigl_fold_ablated_inputs", "srigl_mask_update_workspace_bytes", "srigl_mask_update",
     "srigl_compact_hidden_layer", "srigl_condensed_mlp_fwd", "srigl_narrow_idx", "srigl_condensed_linear_fwd_idx16", "srigl_csr_linear_fwd", "srigl_fwd_plan_query", "srigl_fwd_plan_query_algo",
-    "srigl_condensed_linear_fwd_tile", "srigl_fwd_tile_query",
+    "srigl_condensed_linear_fwd_tile", "srigl_fwd_tile_query", "srigl_structured_tile_query",
     "srigl_blocked_bytes", "srigl_block_terms", "srigl_blocked_tile", "srigl_blocked_tile_with_copy", "srigl_blocked_linear_fwd",
 )
 
@@ -128,6 +129,8 @@ def _load() -> ctypes.CDLL:
                                                     ctypes.c_int, i32, i32, i32, vp]
     lib.srigl_fwd_tile_query.restype = i32
     lib.srigl_fwd_tile_query.argtypes = [i32, i32, i32, i32, i32, ctypes.c_int, i32, i32, i32, ctypes.POINTER(i32)]
+    lib.srigl_structured_tile_query.restype = i32
+    lib.srigl_structured_tile_query.argtypes = [i32, i32, i32, i32, ctypes.c_int, i32]
     lib.srigl_blocked_bytes.restype = sz
     lib.srigl_blocked_bytes.argtypes = [i32, i32, i32]
     lib.srigl_block_terms.restype = ctypes.c_int
@@ -365,6 +368,11 @@ def srigl_structured_split_plan(B, d_in, n_active, d_out, dtype_code):
     _check(lib.srigl_structured_split_plan(int(B), int(d_in), int(n_active), int(d_out), int(dtype_code), ctypes.byref(n), ctypes.byref(b)),
            "srigl_structured_split_plan")
     return int(n.value), int(b.value)
+
+
+def srigl_structured_tile_query(B, d_in, n_active, d_out, dtype_code, may_split=False) -> int:
+    """Tile of the library's own choice (TILE_* codes, or TILE_256x192, which only that choice takes), in one part or as srigl_structured_split_plan cuts d_in."""
+    return int(lib.srigl_structured_tile_query(int(B), int(d_in), int(n_active), int(d_out), int(dtype_code), int(bool(may_split))))
 
 
 def srigl_structured_linear_fwd_split(x, B, d_in, Wd, active, n_active, bias, d_out, y, workspace, splits=0, tile=None):

@@ -640,6 +640,11 @@ srigl_status srigl_structured_split_plan(int32_t B, int32_t d_in, int32_t n_acti
     return SRIGL_OK;
 }
 
+int32_t srigl_structured_tile_query(int32_t B, int32_t d_in, int32_t n_active, int32_t d_out, srigl_dtype dtype, int32_t may_split) {
+    if (B <= 0 || d_in <= 0 || n_active <= 0 || d_out < n_active || (dtype != SRIGL_F32 && dtype != SRIGL_BF16)) return 0;
+    return choose_gemm(B, n_active, d_in, d_out, dtype == SRIGL_F32, may_split != 0).tile;
+}
+
 srigl_status srigl_structured_linear_fwd_split(const void* x, srigl_dtype x_dtype, int32_t B, int32_t d_in, const void* Wd,
                                                srigl_dtype w_dtype, const int32_t* active, int32_t n_active, const float* bias,
                                                int32_t d_out, float* y, srigl_gemm_tile tile, int32_t splits, void* workspace,

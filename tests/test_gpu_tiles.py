@@ -121,6 +121,7 @@ def test_activation_in_the_epilogue(act):
 def test_structured_library_choice(B, n, d_in, ablated):
     """The shape that only the library's own choice takes, against float64: two orders of one fp32 sum of d_in products differ by at most
     d_in * 2^-23 of the sum of the magnitudes (bf16 products are exact in fp32)."""
+    assert B_.srigl_structured_tile_query(B, d_in, n, n + ablated, B_.BF16) == B_.TILE_256x192
     g = torch.Generator(device="cuda").manual_seed(n)
     x = torch.randn(B, d_in, device="cuda", generator=g).bfloat16()
     Wd = torch.randn(n, d_in, device="cuda", generator=g).bfloat16()
@@ -165,15 +166,22 @@ def test_blocked_rows_that_end_inside_a_piece(d_in, K, tile):
     assert (np.abs(y.cpu().numpy() - want) <= scale * (K + 1) * 2.0 ** -23).all()   # exact products, fp32 sums of K of them
 
 
-@pytest.mark.parametrize("d_in,d_out,n,K,B,dtype,narrow", [
-    (1501, 9000, 8201, 290, 1, "f32", False), (1200, 8200, 8200, 500, 1, "bf16", True), (4096, 16384, 13108, 205, 1, "bf16", True),
-    (3999, 5440, 5440, 143, 3, "f32", True), (3072, 768, 538, 307, 16, "f32", False), (700, 400, 255, 256, 63, "bf16", False),
-    (2200, 3000, 1601, 683, 8, "bf16", False),
+@pytest.mark.parametrize("activation", [B_.ACT_NONE, B_.ACT_RELU])
+@pytest.mark.parametrize("d_in,d_out,n,K,B,dtype,narrow,streamed", [
+    (1501, 9000, 8201, 290, 1, "f32", False, True), (1200, 8200, 8200, 500, 1, "bf16", True, True), (4096, 16384, 13108, 205, 1, "bf16", True, True),
+    (3999, 5440, 5440, 143, 3, "f32", True, True), (3072, 768, 538, 307, 16, "f32", False, True), (700, 400, 255, 256, 63, "bf16", False, True),
+    (2200, 3000, 1601, 683, 3, "bf16", False, True), (3700, 5000, 4001, 683, 1, "f32", False, True),       # three chunks, the last one not full
+    (4000, 4096, 4090, 768, 1, "bf16", True, True), (3000, 3000, 2303, 1030, 2, "f32", True, True),        # three whole ones; five
+    (2200, 3000, 1601, 683, 8, "bf16", False, False),      # (taken by the whole-input batched kernel)
 ])
-def test_streamed_terms_against_the_general_kernel(d_in, d_out, n, K, B, dtype, narrow):
-    """The small-batch kernel for layers whose terms are streamed, at sizes where the library's own choice takes it: rows of one to three chunks of
-    256 terms that end inside a lane's four, wavefronts and workgroups with fewer rows than they have room for, both types and index widths,
-    ablated neurons in front, between and behind; activations that are not finite in a column no row reads."""
+def test_streamed_terms_against_the_general_kernel(d_in, d_out, n, K, B, dtype, narrow, streamed, activation):
+    """The small-batch kernel for layers whose terms are streamed, at sizes where the library's own choice takes it (asked of the plan query): rows of
+    one to five chunks of 256 terms that end inside a lane's four, wavefronts and workgroups with fewer rows than they have room for, both types and
+    index widths, ablated neurons in front, between and behind; activations that are not finite in a column no row reads."""
+    p = B_.srigl_fwd_plan_query(B, d_in, n, K, d_out, B_.F32 if dtype == "f32" else B_.BF16, has_active=n < d_out, has_seg=False)
+    assert (p["algo"] == B_.FWD_KLANE and p["waves"] == 8) == streamed, p
+    if streamed:     # (the query above means 32-bit indices)
+        assert B_.srigl_fwd_tile_query(B, d_in, n, K, d_out, B_.F32 if dtype == "f32" else B_.BF16, 16 if narrow else 32, n < d_out, False) == (0, 0)
     rng = np.random.default_rng(K)
     active = np.sort(rng.permutation(d_out - (2 if n < d_out else 0))[:n] + (1 if n < d_out else 0)).astype(np.int32)
     idx = np.sort(np.argsort(rng.random((n, d_in - 1)), axis=1)[:, :K], axis=1).astype(np.int32)     # (nobody reads the last column)
@@ -184,11 +192,11 @@ def test_streamed_terms_against_the_general_kernel(d_in, d_out, n, K, B, dtype, 
     ix = torch.from_numpy(idx).cuda()
     got = torch.full((B + 2, d_out), 777.0, device="cuda")
     want = torch.full((B, d_out), 777.0, device="cuda")
-    B_.srigl_condensed_linear_fwd(x, B, d_in, W, ix.to(torch.int16) if narrow else ix, act, n, K, bias, d_out, got[1:B + 1], act=B_.ACT_RELU)
-    B_.srigl_condensed_linear_fwd(x, B, d_in, W, ix, act, n, K, bias, d_out, want, algo=B_.FWD_GENERIC)
+    B_.srigl_condensed_linear_fwd(x, B, d_in, W, ix.to(torch.int16) if narrow else ix, act, n, K, bias, d_out, got[1:B + 1], act=activation)
+    B_.srigl_condensed_linear_fwd(x, B, d_in, W, ix, act, n, K, bias, d_out, want, act=activation, algo=B_.FWD_GENERIC)
     scale = torch.full((B, d_out), 1.0, device="cuda") + bias.abs()
     rows = torch.from_numpy(active).cuda().long()
     for b in range(B):
         scale[b, rows] += (W.float().abs() * x[b].float().abs()[ix.long()]).sum(1)
-    assert ((got[1:B + 1] - want.clamp(min=0)).abs() <= scale * (K + 1) * 2.0 ** -23).all()       # two orders of one fp32 sum of K products
+    assert ((got[1:B + 1] - want).abs() <= scale * (K + 1) * 2.0 ** -23).all()       # two orders of one fp32 sum of K products
     assert (got[0] == 777.0).all() and (got[B + 1] == 777.0).all()
