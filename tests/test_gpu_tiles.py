@@ -200,3 +200,30 @@ def test_streamed_terms_against_the_general_kernel(d_in, d_out, n, K, B, dtype, 
         scale[b, rows] += (W.float().abs() * x[b].float().abs()[ix.long()]).sum(1)
     assert ((got[1:B + 1] - want).abs() <= scale * (K + 1) * 2.0 ** -23).all()       # two orders of one fp32 sum of K products
     assert (got[0] == 777.0).all() and (got[B + 1] == 777.0).all()
+
+
+@pytest.mark.parametrize("n,activation,with_bias", [(1100, B_.ACT_NONE, True), (1101, B_.ACT_RELU, True), (1103, B_.ACT_NONE, False)])
+def test_streamed_terms_beside_long_runs_of_ablated_columns(n, activation, with_bias):
+    """Neighbours ablated together: runs of 0 to 700 columns in front of each of a wavefront's four rows, around the ends of wavefronts and workgroups,
+    and behind the last row; every ablated column is its bias (bits), the others as the general kernel has them."""
+    d_in, K, B = 2000, 300, 5
+    runs = {0: 700, 1: 15, 2: 16, 3: 17, 4: 80, 6: 81, 9: 272, 31: 33, 32: 273, 33: 1, 500: 64, n - 1: 300}
+    active = (np.arange(n) + np.cumsum([runs.get(s, 0) for s in range(n)])).astype(np.int32)
+    d_out = int(active[-1]) + 1 + 517
+    p = B_.srigl_fwd_plan_query(B, d_in, n, K, d_out, B_.F32, has_active=True, has_seg=False)
+    assert p["algo"] == B_.FWD_KLANE and p["waves"] == 8, p
+    rng = np.random.default_rng(n)
+    idx = dev(np.sort(np.argsort(rng.random((n, d_in)), axis=1)[:, :K], axis=1).astype(np.int32))
+    W, x = dev(rng.standard_normal((n, K)).astype(np.float32)), dev(rng.standard_normal((B, d_in)).astype(np.float32))
+    bias = dev(rng.standard_normal(d_out).astype(np.float32)) if with_bias else None
+    got, want = torch.full((B + 2, d_out), 777.0, device="cuda"), torch.full((B, d_out), 777.0, device="cuda")
+    B_.srigl_condensed_linear_fwd(x, B, d_in, W, idx, dev(active), n, K, bias, d_out, got[1:B + 1], act=activation)
+    B_.srigl_condensed_linear_fwd(x, B, d_in, W, idx, dev(active), n, K, bias, d_out, want, act=activation, algo=B_.FWD_GENERIC)
+    stored = torch.zeros(d_out, dtype=torch.bool, device="cuda")
+    stored[dev(active).long()] = True
+    assert torch.equal(got[1:B + 1, ~stored], want[:, ~stored])
+    scale = torch.zeros((B, d_out), device="cuda") + (bias.abs() if with_bias else 0)
+    for b in range(B):
+        scale[b, stored] += (W.abs() * x[b].abs()[idx.long()]).sum(1)
+    assert ((got[1:B + 1] - want).abs() <= scale * (K + 1) * 2.0 ** -23).all()       # two orders of one fp32 sum of K products
+    assert (got[0] == 777.0).all() and (got[B + 1] == 777.0).all()
