@@ -791,6 +791,11 @@ static srigl_status launch_rowlane_plan(const FwdArgs& a, const RowlanePlan& p, 
 // The library's own choice of kernel: the smallest of the estimated times of the small-batch kernel (gathered or staged
 // activations) and of the batched kernel in the launch shape it would take.  A single row always takes the small-batch
 // kernel, above 2048 rows the batched kernel always wins.
+// Estimated time (us) of the small-batch kernel in the form that a call takes.
+static double small_estimate_us(const FwdArgs& a) {
+    return stream_ahead(a) ? stream_estimate_us(a) : klane_estimate_us(a.B, a.d_in, a.n_active, a.K);
+}
+
 // The choice between the small-batch kernel, the chunked batched kernel and the fallback.
 static srigl_fwd_algo choose_chunked_or_small(const FwdArgs& a) {
     const int B = a.B, d_in = a.d_in, n_active = a.n_active, K = a.K;
@@ -802,7 +807,7 @@ static srigl_fwd_algo choose_chunked_or_small(const FwdArgs& a) {
     if (B > 1 && B <= 2048) {
         static_assert(kKlaneTerms == 4, "klane_estimate_us assumes 4 terms per lane and request");
         const RowlanePlan rp = plan_rowlane_by_estimate(a, nullptr);   // (the comparison was fitted with this shape and estimate)
-        batched = rp.ok && rowlane_estimate_us(a, rp, true) < klane_estimate_us(B, d_in, n_active, K);
+        batched = rp.ok && rowlane_estimate_us(a, rp, true) < small_estimate_us(a);
     }
     const bool can_batch = rowlane_supported(a, nullptr);
     if (batched && can_batch) return SRIGL_FWD_ROWLANE;
@@ -814,7 +819,7 @@ static srigl_fwd_algo choose_chunked_or_small(const FwdArgs& a) {
 struct OtherEstimates { double batched, small; };
 static OtherEstimates other_estimates(const FwdArgs& a) {
     const RowlanePlan rp = plan_rowlane_by_estimate(a, nullptr);
-    return {rp.ok ? rowlane_estimate_us(a, rp, true) : 1e30, a.B > 2048 && rp.ok ? 1e30 : klane_estimate_us(a.B, a.d_in, a.n_active, a.K)};
+    return {rp.ok ? rowlane_estimate_us(a, rp, true) : 1e30, a.B > 2048 && rp.ok ? 1e30 : small_estimate_us(a)};
 }
 // The whole-input batched kernel is taken where its estimate is ahead of theirs, 5 % in its favour against the chunked kernel: over 304 points
 // (67 layers 112 to 2400 wide, fan-ins 6 to 384, both types, batches 8 to 2048) the call is then 0.8 % behind the fastest of the

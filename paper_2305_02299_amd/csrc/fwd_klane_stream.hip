@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kStreamWaves* kWave) void k_fwd_klane_stream(const 
     if (active == nullptr) return;
     // Ablated columns hold their bias: the run in front of each row's column, and the one behind the last row's.  The 16 lanes of a row write
     // its first 16 columns; longer runs are the whole wavefront's, four loads of the bias in flight.  By 16 lanes, one load after the
-    // other, a run cost 5 ns a column: 1565 -> 7697, K = 140 at two batch rows with 769 neighbours ablated at either end 9.8 us (the gathering
+    // other, a run cost 5 ns a column: 1565 -> 7698, K = 140 at two batch rows with 769 neighbours ablated at either end 9.8 us (the gathering
     // form 6.8), now 5.4; 1528 -> 4680, K = 305 at two with 468 7.9 (5.6), now 5.0.
     constexpr int kOwn = 16;
     auto put = [&](int q, float raw) { yr[q] = act == SRIGL_ACT_NONE ? raw : apply_act(raw, act); };
@@ -158,6 +158,19 @@ bool stream_ahead(const FwdArgs& a) {
     const int chunks = (a.K + kStreamChunk - 1) / kStreamChunk;
     const double terms = (double)a.n_active * a.K * a.B;
     return terms >= 0.8e6 * std::max(2, chunks) && (long long)a.n_active * a.B <= 4 * 256 * kStreamWaves * kStreamRows && 2 * a.K >= chunks * kStreamChunk;
+}
+
+// Estimated time (us), for the comparison with the batched kernels: the columns of x that the workgroups stage, the places that the chunks of all
+// rows take, the chunks after the first, the bytes of the terms, and those of them that the L2s fetch beyond their 32 MB: a batch row's workgroups
+// go round the XCDs from where the row before ended, so that unless their number is a multiple of eight every XCD meets all terms
+// (2834 -> 3423, K = 481, four rows 9.9 us, 7.6 of it without).  Non-negative least squares on the relative error of 272 launches on which stream_ahead holds (300 to 4096 wide,
+// 128 to 16384 stored rows, batches 2 to 64, both types and index widths, random ablation, cached operands): standard deviation 8 %, worst -21 and +24 %.
+double stream_estimate_us(const FwdArgs& a) {
+    const double chunks = (a.K + kStreamChunk - 1) / kStreamChunk;
+    const double bytes = (double)a.n_active * a.K * ((a.x_bf16 ? 2 : 4) + (a.idx_u16 ? 2 : 4));
+    const double fetched = stream_groups(a) % 8 ? bytes * std::min(a.B, 8) : bytes;
+    return 3.27 + 0.449e-6 * stream_groups(a) * a.B * (double)a.d_in + 0.276e-6 * a.n_active * a.B * chunks * kStreamChunk + 0.0131e-6 * bytes +
+           0.162e-6 * std::max(0.0, fetched - 32e6) + 0.41 * (chunks - 1);
 }
 
 srigl_status launch_fwd_stream(const FwdArgs& a, hipStream_t st) {

@@ -12,11 +12,13 @@ static double term_bytes(const FwdArgs& a) { return (double)a.n_active * a.K * (
 // per 16 terms (32 in 8-row tiles) and a constant (another where terms beyond 256 are walked in a loop); the bytes of y; the bytes the XCDs' L2 caches
 // fetch (all of them the one array, each its share of the other).  Non-negative least squares on the relative error of 2600 launches
 // (each tile, shapes within 1.6 times the fastest; 67 layers 112 to 2400 wide, fan-ins 6 to 384, both types, batches 8 to 2048, cached
-// operands; 8-row tiles: 2800 launches, 297 layers 700 to 4096 wide, fan-ins to 806): standard deviation 6.5 to 9 %.  The shape of smallest estimate was 0.6 % behind the best measured one on average over
-// 304 points.
+// operands; 8-row tiles: 2800 launches, 297 layers 700 to 4096 wide, fan-ins to 806): standard deviation 6.5 to 9 %.  The 8-row launches were measured apart from the others and came
+// out 7 % higher: on 1300 later points, where every tile was timed beside the others (300 to 4096 wide, batches 2 to 1200), 0.935 of their estimate at small,
+// middle and large batches alike, so their constants are the fit's times 0.93.  The tile of smallest estimate is then 0.2 % behind the fastest up to 64 batch
+// rows and 0.9 % above (7.9 % and 2.0 % before: 16-row tiles were taken where 8-row ones are ahead, 1280 -> 1008, K = 256, 625 stored at 24, 16-bit indices 6.6 us, 5.8).
 static double rowloop_us(const FwdArgs& a, const RowloopPlan& p) {
     struct Fit { double fixed, round, word, big, step, row, y, fetched, long_row; };
-    static const Fit fits[4] = {{2.817, 2.003, 0.2907e-4, 0.292e-4, 0.0683, 0.0931, 2.549e-6, 0.0338e-6, 0.1623},
+    static const Fit fits[4] = {{2.620, 1.863, 0.2704e-4, 0.272e-4, 0.0635, 0.0866, 2.371e-6, 0.0314e-6, 0.1509},
                                 {2.231, 2.147, 0.2049e-4, 0.585e-4, 0.0545, 0.0423, 2.128e-6, 0.0585e-6, 0.2256},
                                 {3.522, 1.023, 0.1370e-4, 1.2465e-4, 0.0866, 0.0701, 1.613e-6, 0.0430e-6, 0.5675},
                                 {3.131, 1.348, 0.2724e-4, 0.3693e-4, 0.1745, 0.0951, 1.378e-6, 0.0448e-6, 0.0}};

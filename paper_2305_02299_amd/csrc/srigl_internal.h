@@ -187,6 +187,7 @@ RowloopPlan plan_tile(const FwdArgs& a, int tile_rows, int rows_per_wave, int xc
 constexpr int kStreamWaves = 8, kStreamRows = 4;   // wavefronts of a workgroup, stored rows of a wavefront
 inline int stream_groups(const FwdArgs& a) { return (a.n_active + kStreamWaves * kStreamRows - 1) / (kStreamWaves * kStreamRows); }
 bool stream_ahead(const FwdArgs& a);
+double stream_estimate_us(const FwdArgs& a);
 srigl_status launch_fwd_stream(const FwdArgs& a, hipStream_t st);
 srigl_status launch_rowloop_plan(const FwdArgs& a, const RowloopPlan& p, hipStream_t st);
 // Estimated time (us) of the condensed forward call of these sizes in the kernel the library's own choice takes.

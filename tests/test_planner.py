@@ -25,7 +25,7 @@ def streamed(p):
     # narrow and wide inputs, batches from two rows on: tiles of 8, 16 and 32 rows; 0: another kernel
     # (the chunked kernel's on inputs beyond 4096 columns)
     (256, 3072, 768, 307, 538, 8), (320, 3072, 768, 308, 768, 8), (512, 4096, 1024, 410, 1024, 8), (64, 4096, 4096, 41, 4096, 8),
-    (8, 4096, 16384, 205, 16384, 8), (16, 2560, 2560, 256, 2560, 8), (96, 2048, 512, 205, 512, 16), (256, 2160, 768, 216, 768, 16),
+    (8, 4096, 16384, 205, 16384, 8), (16, 2560, 2560, 256, 2560, 8), (96, 2048, 512, 205, 512, 8), (256, 2160, 768, 216, 768, 16),
     (64, 768, 3072, 77, 3072, 16), (256, 768, 3072, 77, 3072, 32), (1024, 768, 3072, 154, 3072, 32), (300, 1000, 777, 50, 777, 16),
     (96, 3072, 768, 31, 768, 0), (8, 768, 3072, 77, 3072, 0), (1, 768, 3072, 77, 3072, 0), (256, 4112, 768, 307, 768, 16),
 ])
@@ -34,6 +34,20 @@ def test_the_tile_that_a_call_takes(B, d_in, d_out, K, n, rows):
     assert tile_rows(p) == rows, p
     assert (p["algo"] == B_.FWD_ROWLOOP) == (0 < rows and d_in <= 4096)
     assert B_.srigl_fwd_tile_query(B, d_in, n, K, d_out, has_active=(n != d_out)) == ((rows, p["neurons_per_wave"]) if p["algo"] == B_.FWD_ROWLOOP else (0, 0))
+
+
+def test_the_streamed_form_is_compared_with_the_tiles_by_its_own_estimate():
+    """us, streamed / gathering / 8-row / 16-row tile.  While the gathering form's estimate stood for both, tiles were taken here."""
+    for (B, d_in, d_out, K, n) in ((24, 1280, 1008, 256, 625),      # 4.7 / 6.4 / 5.8 / 6.6
+                                   (12, 2424, 2331, 169, 2331),     # 6.3 / 8.4 / 6.2 / 8.1 (level with the 8-row tile)
+                                   (8, 3101, 1837, 217, 1837),      # 4.9 / 6.5 / 6.1 / -
+                                   (32, 1204, 583, 216, 583)):      # 5.0 / 6.3 / 5.3 / 6.1
+        p = plan(B, d_in, d_out, K, n_active=n)
+        assert streamed(p) or tile_rows(p) == 8, (B, d_in, K, p)
+        for bits in (16, 32):
+            assert B_.srigl_fwd_tile_query(B, d_in, n, K, d_out, idx_bits=bits, has_active=n != d_out)[0] in (0, 8), (B, d_in, K, bits)
+    assert streamed(plan(24, 1280, 1008, 256, n_active=625)) and streamed(plan(8, 3101, 1837, 217)) and streamed(plan(32, 1204, 583, 216))
+    assert not streamed(plan(6, 2498, 4038, 499, n_active=3231))    # every batch row fetches 13 MB of terms from beyond the L2s: 18.2 / 12.5 / 7.5
 
 
 def test_the_query_is_the_decision_of_a_call():
