@@ -7,6 +7,9 @@ namespace srigl {
 static double x_bytes(const FwdArgs& a) { return (double)a.B * a.d_in * (a.x_bf16 ? 2 : 4); }
 static double term_bytes(const FwdArgs& a) { return (double)a.n_active * a.K * ((a.x_bf16 ? 2 : 4) + (a.idx_u16 ? 2 : 4)); }
 
+// Columns of a tile: whole units of its staging.
+static int tile_columns_of(const FwdArgs& a, int BT) { return BT < 16 ? (a.d_in + 31) / 32 * 32 : (a.d_in + 15) / 16 * 16; }
+
 // Estimated time (us) of a launch shape: per round of workgroups on the busiest XCD a constant, the tile (words staged; beyond 16 K words
 // more from the second round on, when no wavefronts start under its loads any more), and per stored row of a wavefront a step
 // per 16 terms (32 in 8-row tiles) and a constant (another where terms beyond 256 are walked in a loop); the bytes of y; the bytes the XCDs' L2 caches
@@ -16,23 +19,25 @@ static double term_bytes(const FwdArgs& a) { return (double)a.n_active * a.K * (
 // out 7 % higher: on 1300 later points, where every tile was timed beside the others (300 to 4096 wide, batches 2 to 1200), 0.935 of their estimate at small,
 // middle and large batches alike, so their constants are the fit's times 0.93.  The tile of smallest estimate is then 0.2 % behind the fastest up to 64 batch
 // rows and 0.9 % above (7.9 % and 2.0 % before: 16-row tiles were taken where 8-row ones are ahead, 1280 -> 1008, K = 256, 625 stored at 24, 16-bit indices 6.6 us, 5.8).
+// second_pass: workgroups make a second pass over their tile where it has more columns than one pass holds (2048 * wavefronts / rows of
+// the tile: 4096, 2048, 1024 and 512 at 16), another trip to the L2 and back, which later rounds
+// hide behind one another's arithmetic: the step in time at those widths on 2200 and, of 64-row tiles, 108 launches.  With it
+// the tile taken on inputs of 1024 to 2600 columns at batches above 64 is 0.9 % behind the fastest (2.1 % without: 2160 -> 768, K = 216 at 256 in 16-row tiles 9.7 us, 8.2 in 8-row ones).
 static double rowloop_us(const FwdArgs& a, const RowloopPlan& p) {
-    struct Fit { double fixed, round, word, big, step, row, y, fetched, long_row; };
-    static const Fit fits[4] = {{2.620, 1.863, 0.2704e-4, 0.272e-4, 0.0635, 0.0866, 2.371e-6, 0.0314e-6, 0.1509},
-                                {2.231, 2.147, 0.2049e-4, 0.585e-4, 0.0545, 0.0423, 2.128e-6, 0.0585e-6, 0.2256},
-                                {3.522, 1.023, 0.1370e-4, 1.2465e-4, 0.0866, 0.0701, 1.613e-6, 0.0430e-6, 0.5675},
-                                {3.131, 1.348, 0.2724e-4, 0.3693e-4, 0.1745, 0.0951, 1.378e-6, 0.0448e-6, 0.0}};
+    struct Fit { double fixed, round, word, big, step, row, y, fetched, long_row, second_pass; };
+    static const Fit fits[4] = {{2.620, 1.863, 0.2704e-4, 0.272e-4, 0.0635, 0.0866, 2.371e-6, 0.0314e-6, 0.1509, 0.0},
+                                {2.231, 2.147, 0.2049e-4, 0.585e-4, 0.0545, 0.0423, 2.128e-6, 0.0585e-6, 0.2256, 1.4},
+                                {3.522, 1.023, 0.1370e-4, 1.2465e-4, 0.0866, 0.0701, 1.613e-6, 0.0430e-6, 0.5675, 1.1},
+                                {3.131, 1.348, 0.2724e-4, 0.3693e-4, 0.1745, 0.0951, 1.378e-6, 0.0448e-6, 0.0, 0.7}};
     const Fit& f = fits[p.BT == 8 ? 0 : p.BT == 16 ? 1 : p.BT == 32 ? 2 : 3];
     const int steps = a.K <= 256 ? p.ST : p.BT == 8 ? 8 + 2 * ((a.K - 256 + 63) / 64) : 16 + 4 * ((a.K - 256 + 63) / 64);
     const int rows = std::min((p.NG + p.NW - 1) / p.NW, (a.n_active + p.NW - 1) / p.NW);   // of the busiest wavefront
     const double fetched = p.bt_major ? x_bytes(a) + 8 * term_bytes(a) : 8 * x_bytes(a) + term_bytes(a);
     const double words = (double)p.BT * ((a.d_in + 15) / 16 * 16);
-    return f.fixed + p.rounds * (f.round + f.word * words + rows * (f.step * steps + f.row + (a.K > 256 ? f.long_row : 0.0)) * p.NW / 16.0) +
+    const double again = tile_columns_of(a, p.BT) > 2048 / p.BT * p.NW ? f.second_pass : 0.0;
+    return f.fixed + again + p.rounds * (f.round + f.word * words + rows * (f.step * steps + f.row + (a.K > 256 ? f.long_row : 0.0)) * p.NW / 16.0) +
            (p.rounds - 1) * f.big * std::max(0.0, words - 16384) + f.y * a.B * a.d_out + f.fetched * fetched;
 }
-
-// Columns of a tile: whole units of its staging.
-static int tile_columns_of(const FwdArgs& a, int BT) { return BT < 16 ? (a.d_in + 31) / 32 * 32 : (a.d_in + 15) / 16 * 16; }
 
 // Rows per workgroup the result tile (and, with an active list, a column table of twice as many columns) has room for.
 static long long rowloop_room(const FwdArgs& a, size_t tile, int BT) {

@@ -18,8 +18,8 @@
 // columns, K = 216 at 256, in place of the chunked kernel 13.7 -> 9.4; 1000 -> 777, K = 50 at 300 15.8 -> 7.4.)
 // What bounds it: vector instructions (the multiply-adds are half of them) and LDS reads in equal parts, behind a fixed 5 to 6 us of
 // launching 4096 wavefronts, staging the tile and writing y.
-// Inputs of 2500 to 4096 columns, which leave room for 8 batch rows: 32 groups of two lanes, 32 terms to a step, the same reads and
-// instructions per term and row.  In place of the chunked kernel 3072 -> 768, K = 307 at batch 256 16.8 -> 11.1 us, 538 stored at 64 10.6 -> 8.4,
+// Tiles of 8 batch rows (all that inputs of 2500 to 4096 columns leave room for; also taken on narrower ones where the batch is small or ends inside a
+// 16-row tile): 32 groups of two lanes, 32 terms to a step, the same reads and instructions per term and row.  In place of the chunked kernel 3072 -> 768, K = 307 at batch 256 16.8 -> 11.1 us, 538 stored at 64 10.6 -> 8.4,
 // 4096 -> 1024, K = 205 at 512 23.9 -> 19.1, 2816 -> 768 bf16, K = 113 at 1527 35.6 -> 27.6; on 147 points that take it 1.49 times faster on
 // average, none slower.
 // Rows of 64 tiles only pay on inputs up to about 400 columns wide, where they still leave room for a hundred stored rows.
@@ -223,8 +223,8 @@ __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, 
     int e_col[TP];
 
     // A pass stages kStageUnits units per wavefront, 16 columns of all rows under one wave-uniform branch (a lane's row past the end
-    // re-reads the last one and is dropped afterwards), and the first pass, the only one on inputs up to 2048 columns wide with 16
-    // wavefronts, is straight-line code: in a loop whose registers a load of the last turn may still own, or with a branch on every
+    // re-reads the last one and is dropped afterwards), and the first pass, with 16 wavefronts the only one on inputs up to 4096, 2048, 1024 and 512
+    // columns wide in tiles of 8, 16, 32 and 64 rows, is straight-line code: in a loop whose registers a load of the last turn may still own, or with a branch on every
     // load's lanes, the compiler waits for every load in flight before the next one is issued (measured on the staging of this
     // kernel: the six tile loads of a wavefront went out one round trip after the other).
     const float* const bias_src = bias ? bias : reinterpret_cast<const float*>(x);   // never used: entries are 0 without a bias

@@ -25,7 +25,7 @@ def streamed(p):
     # narrow and wide inputs, batches from two rows on: tiles of 8, 16 and 32 rows; 0: another kernel
     # (the chunked kernel's on inputs beyond 4096 columns)
     (256, 3072, 768, 307, 538, 8), (320, 3072, 768, 308, 768, 8), (512, 4096, 1024, 410, 1024, 8), (64, 4096, 4096, 41, 4096, 8),
-    (8, 4096, 16384, 205, 16384, 8), (16, 2560, 2560, 256, 2560, 8), (96, 2048, 512, 205, 512, 8), (256, 2160, 768, 216, 768, 16),
+    (8, 4096, 16384, 205, 16384, 8), (16, 2560, 2560, 256, 2560, 8), (96, 2048, 512, 205, 512, 8), (256, 2160, 768, 216, 768, 8),
     (64, 768, 3072, 77, 3072, 16), (256, 768, 3072, 77, 3072, 32), (1024, 768, 3072, 154, 3072, 32), (300, 1000, 777, 50, 777, 16),
     (96, 3072, 768, 31, 768, 0), (8, 768, 3072, 77, 3072, 0), (1, 768, 3072, 77, 3072, 0), (256, 4112, 768, 307, 768, 16),
 ])
