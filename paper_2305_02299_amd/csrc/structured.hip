@@ -407,27 +407,31 @@ static srigl_gemm_tile choose_tile(int B, int n_active, bool f32) {
     return best;
 }
 
-// bf16: a round of tiles costs a part of its own, a part per 1000 elements of d_in and another that follows how full the rounds are;
-// two 64 x 64 tiles share a compute unit.  Least squares on 79 products with 5 to 20 % of the weights present (200 to 16384 stored
-// rows, batches 48 to 2048, 128- to 4096-wide, half of them with ablated neurons): 7 to 9 % per shape, and the tile of smallest time 0.3 %
-// behind the fastest on average.  (256 x 192 tiles: 9000 rows at batch 2048, d_in 4096, 155 us, 157 in 256 x 128 and 180 in 256 x 256; 5023 at
-// 1696, 1136, 35.7, 48 and 36.)
+// bf16: a round of tiles costs a part of its own, a part per 1000 elements of d_in and another that follows how full the rounds are; two
+// 64 x 64 tiles share a compute unit (up to 256 of them run one to a unit); the bytes of y; ablated neurons' tables; a second launch and the
+// partial sums where d_in is cut.  Non-negative least squares on the relative error of 6258 launches, every shape in one part and in the parts
+// that parts_of gives, of 920 products (128 to 4096 wide, 100 to 16384 stored rows, batches 8 to 2048, up to half of the neurons ablated, 1 to 20 %
+// of the weights present; graphs of 5 to 40 launches): 10 % per shape.  The tile and parts of smallest time are 0.3 % behind the fastest on average on 609
+// products of up to 5 M results (at worst 18 %) and 1.4 % (22 %) on 311 larger ones; 0.5 (23) and 2.7 % (28) with constants fitted to calls from
+// the host, 13 % too high and most on the smallest, which also left the condensed form calls that the product does faster (4096 -> 4096, K = 410 at batch 64: 17.7 us
+// against 13.9).  (256 x 192 tiles: 9000 rows at batch 2048, d_in 4096, 155 us, 157 in 256 x 128 and 180 in 256 x 256; 5023 at 1696, 1136, 35.7, 48 and 36.)
 constexpr int kTile256x192 = 7;   // 8 wavefronts of 64x96, 2 LDS stages of 128 bytes; only the library's choice takes it
-struct Bf16TileModel { int tile, bm, bn; float fixed, round, per_k, per_k_full; };
+struct Bf16TileModel { int tile, bm, bn; float fixed, round, per_k, per_k_full, y, ablated, second, part; };
 static const Bf16TileModel kBf16TileModels[] = {
-    {SRIGL_TILE_256x256, 256, 256, 2.0f, 7.14f, 16.67f, 2.35f},
-    {kTile256x192, 256, 192, 0.1f, 8.24f, 12.88f, 5.28f},
-    {SRIGL_TILE_256x128, 256, 128, 0.7f, 6.74f, 9.90f, 0.41f},
-    {SRIGL_TILE_128x128, 128, 128, 3.3f, 3.88f, 6.74f, 0.0f},
-    {SRIGL_TILE_64x64, 64, 64, 2.0f, 2.42f, 5.67f, 0.0f},
+    {SRIGL_TILE_256x256, 256, 256, 0.71f, 6.96f, 15.62f, 4.62f, 0.69f, 2.06f, 1.71f, 1.82f},
+    {kTile256x192, 256, 192, 0.0f, 7.08f, 12.05f, 5.64f, 0.83f, 1.88f, 0.0f, 0.0f},
+    {SRIGL_TILE_256x128, 256, 128, 1.62f, 4.69f, 8.47f, 2.07f, 0.82f, 1.95f, 1.31f, 2.07f},
+    {SRIGL_TILE_128x128, 128, 128, 3.07f, 2.96f, 5.82f, 1.18f, 0.87f, 1.84f, 1.52f, 2.42f},
+    {SRIGL_TILE_64x64, 64, 64, 2.76f, 1.07f, 5.60f, 0.0f, 1.22f, 1.34f, 1.46f, 3.18f},
 };
-// Time (us) of `splits` parts of the product in a shape, without the bytes of y.
-static double bf16_tiles_us(const Bf16TileModel& m, int splits, int B, int d_in, int n_active) {
+// Time (us) of the product in a shape and `splits` parts.
+static double bf16_tiles_us(const Bf16TileModel& m, int splits, int B, int d_in, int n_active, int d_out) {
     const double d = d_in * 1e-3 / splits;
     const long long tiles = (long long)((B + m.bm - 1) / m.bm) * ((n_active + m.bn - 1) / m.bn);
     const double groups = (double)(splits > 1 ? (tiles + kXcds - 1) / kXcds * kXcds * splits : tiles);
-    if (m.bm == 64) return groups <= 256 ? 5.1 + 4.44 * d : m.fixed + std::ceil(groups / 512) * (m.round + m.per_k * d);
-    return m.fixed + std::ceil(groups / 256) * (m.round + m.per_k * d) + groups / 256 * m.per_k_full * d;
+    const double more = m.y * 1e-6 * B * d_out + (splits > 1 ? m.second + m.part * 1e-6 * splits * B * (double)n_active : n_active < d_out ? m.ablated : 0.0);
+    if (m.bm == 64) return more + (groups <= 256 ? 4.17 + 3.67 * d : m.fixed + std::ceil(groups / 512) * (m.round + m.per_k * d));
+    return more + m.fixed + std::ceil(groups / 256) * (m.round + m.per_k * d) + groups / 256 * m.per_k_full * d;
 }
 
 struct GemmChoice { int tile, splits; double us; };
@@ -445,10 +449,8 @@ static int parts_of(int B, int n_active, int d_in, bool f32, int bm, int bn) {
     return padded >= wg_cap ? 1 : std::min((int)(wg_cap / padded), cap);
 }
 
-// The partial sums are written once and read once; the second launch and a second pipeline fill are 1 us (bf16) and 2.6 (fp32) of
-// the 2.5 and 3.5 that the estimates add, the rest is the host's second launch.  On 78 products with and without parts (64 x 64 tiles, 100 to 6000 stored
-// rows, batches 16 to 512): 4 to 6 us too high while the constants were the first kernel's (1304 rows at batch 80, d_in 1680, bf16: 12.6 us
-// in one part, 9.3 in six).
+// fp32: the partial sums are written once and read once; the second launch and a second pipeline fill are 2.6 us of the 3.5 that the estimate adds, the
+// rest is the host's second launch.  (On 78 products with and without parts, 64 x 64 tiles, 100 to 6000 stored rows, batches 16 to 512.)
 constexpr double kPartsUs = 1.7 * 8.0 / 4.5e6;
 static GemmChoice choose_f32(int B, int n_active, int d_in, int d_out, bool may_split) {
     GemmChoice best{};
@@ -476,14 +478,13 @@ static GemmChoice choose_bf16(int B, int n_active, int d_in, int d_out, bool may
     GemmChoice best{};
     for (const Bf16TileModel& m : kBf16TileModels) {
         if (m.bm > 64 && (long long)m.bm * d_in * 2 >= (1ll << 31)) continue;   // launch_gemm's byte offsets
-        const double one = bf16_tiles_us(m, 1, B, d_in, n_active);
+        const double one = bf16_tiles_us(m, 1, B, d_in, n_active, d_out);
         if (best.tile == 0 || one < best.us) best = {m.tile, 1, one};
         const int s = may_split ? parts_of(B, n_active, d_in, false, m.bm, m.bn) : 1;
         if (s == 1 || m.tile == kTile256x192) continue;
-        const double several = bf16_tiles_us(m, s, B, d_in, n_active) + 2.5 + kPartsUs * s * (double)B * n_active;
+        const double several = bf16_tiles_us(m, s, B, d_in, n_active, d_out);
         if (several < best.us) best = {m.tile, s, several};
     }
-    best.us += 4.0 * (double)B * d_out / 4.5e6 + (best.splits == 1 && n_active < d_out ? 1.3 : 0.0);   // (1.3: the columns' tables)
     return best;
 }
 static GemmChoice choose_gemm(int B, int n_active, int d_in, int d_out, bool f32, bool may_split) {
@@ -558,8 +559,10 @@ srigl_status srigl_densify(const void* W_c, srigl_dtype w_dtype, const int32_t* 
 //                  + 4 B d_out / 4.5e6              (writing the result at HBM speed)
 srigl_representation srigl_choose_representation(int32_t B, int32_t d_in, int32_t n_active, int32_t K, int32_t d_out,
                                                  srigl_dtype dtype, float* est_condensed_us, float* est_structured_us) {
-    // On the same points (bf16) the form taken is 0.2 % slower than the faster one on average, at worst 7 %.  (While the condensed estimate
-    // was the gathering kernels' alone: up to 20 %, and a dense copy of 107 MB on 4096 -> 16384 for what the estimate called 2.7 times.)
+    // bf16: on 920 layers and batches timed in both forms (128 to 4096 wide, batches 8 to 2048) the form taken is 1.1 % slower than the faster one on
+    // average, beyond 10 % on 22 (fan-ins of 1 to 3 at batches above 700, which the tiles' estimates put too low, among them); on 144 points of 16 named layers 0.4 %, at worst 17 %.
+    // (With the constants before, 1.7 % and 0.9 %, beyond 10 % on 48.  While the condensed estimate was the gathering kernels' alone: up to 20 %, and a
+    // dense copy of 107 MB on 4096 -> 16384 for what the estimate called 2.7 times.)
     struct Key { int32_t B, d_in, n_active, K, d_out, dtype; };
     struct Estimates { double cond, stru; };
     static thread_local DecisionCache<Key, Estimates, 64> cache;
@@ -568,7 +571,8 @@ srigl_representation srigl_choose_representation(int32_t B, int32_t d_in, int32_
         v.cond = condensed_estimate_us(B, d_in, n_active, K, d_out, dtype == SRIGL_BF16, n_active < d_out);
         const bool f32 = dtype == SRIGL_F32;
         v.stru = choose_gemm(B > 0 ? B : 1, n_active > 0 ? n_active : 1, d_in, d_out, f32, true).us;
-        if (!f32) v.cond = std::min(v.cond, blocked_estimate_us(B, d_in, n_active, K, d_out));
+        // (1.04: timed beside the products, in the same graphs, the condensed calls take that much longer than the estimates, whatever the batch and the form)
+        if (!f32) v.cond = 1.04 * std::min(v.cond, blocked_estimate_us(B, d_in, n_active, K, d_out));
         if ((d_in * (f32 ? 4 : 2)) % 16 != 0) v.stru = 1e30;   // the matrix-core kernel needs rows of whole 16-byte pieces
         return v;
     });

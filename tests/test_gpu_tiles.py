@@ -115,13 +115,15 @@ def test_activation_in_the_epilogue(act):
     assert np.abs(got - want).max() <= 2e-6 * max(1.0, np.abs(want).max())    # the activation of the same fp32 sums
 
 
-@pytest.mark.parametrize("B,n,d_in,ablated", [
-    (520, 16121, 136, 0), (1000, 8200, 72, 333), (1500, 5401, 264, 57),      # 256 x 192 tiles: rows, columns and depth end inside a tile
+@pytest.mark.parametrize("B,n,d_in,ablated,tile", [
+    (520, 12001, 136, 57, B_.TILE_256x192), (520, 12001, 72, 57, B_.TILE_256x192), (1500, 5401, 264, 57, B_.TILE_256x192),
+    (520, 16121, 520, 0, B_.TILE_256x192),                                     # 256 x 192 tiles: rows, columns and depth end inside a tile
+    (520, 16121, 136, 0, B_.TILE_256x256), (1000, 8200, 72, 333, B_.TILE_256x256),
 ])
-def test_structured_library_choice(B, n, d_in, ablated):
-    """The shape that only the library's own choice takes, against float64: two orders of one fp32 sum of d_in products differ by at most
+def test_structured_library_choice(B, n, d_in, ablated, tile):
+    """The shape that only the library's own choice takes, and its neighbour, against float64: two orders of one fp32 sum of d_in products differ by at most
     d_in * 2^-23 of the sum of the magnitudes (bf16 products are exact in fp32)."""
-    assert B_.srigl_structured_tile_query(B, d_in, n, n + ablated, B_.BF16) == B_.TILE_256x192
+    assert B_.srigl_structured_tile_query(B, d_in, n, n + ablated, B_.BF16) == tile
     g = torch.Generator(device="cuda").manual_seed(n)
     x = torch.randn(B, d_in, device="cuda", generator=g).bfloat16()
     Wd = torch.randn(n, d_in, device="cuda", generator=g).bfloat16()
