@@ -41,7 +41,7 @@ CACHE_BYTES = 256 << 20        # Infinity Cache; the cold loop cycles through >=
 # Bytes per launch between L2 and the fabric (HBM / Infinity Cache) of the forward kernel, from the rocprofv3 --pmc
 # FETCH_SIZE and WRITE_SIZE runs of this script summarised in profiles/fwd_c2_c1_hbm_traffic.md (each counter scaled
 # by what it reads for srigl_copy_bytes on 1 GiB).  Keys: workload and batch.
-MEASURED_TRAFFIC_BYTES = {("c2", 256): 11585229, ("c2", 1): 2103310}
+MEASURED_TRAFFIC_BYTES = {("c2", 256): 11486171, ("c2", 1): 2103308}
 
 
 def log(*a):
