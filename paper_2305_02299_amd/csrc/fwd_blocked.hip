@@ -575,10 +575,11 @@ static double blocked_tile_us(int tile, int B, int n, double columns, int d_in, 
 }
 
 // The tile code of smallest estimate.  The large shapes are also tried for their full rounds of workgroups only, with the stored rows that
-// are left in the shape that suits those, and taken where that promises 8 % (3016 -> 9749 at batch 1765 in 256 and then 64 wide tiles 106 us, 135
-// in one shape; 13108 at 2048, d_in 4096, in 256 and then 192 wide ones, 7 % ahead by the estimate, 215 us against 206: the second
-// launch's start and the power that a full round draws).  On 42 points (600- to 4096-wide, 2500 to 16000 stored rows, batches 600 to 2048)
-// the code taken is 0.8 % behind the fastest of up to 10 on average, 9 % at worst; 1.8 % (28 %) with one shape only.
+// are left in the shape that suits those (3016 -> 9749 at batch 1765 in 256 and then 64 wide tiles 106 us, 135 in one shape).  Two launches take longer
+// than their estimates' sum, 1 % with every neuron stored and 9 % with a fifth of them ablated (the second one's start waits for the first one's last rows
+// and tables), so that they are taken where the sum promises 8 %.  On 256 points (128 products 768- to 4096-wide, 2560 to 16000 stored rows, batches 600 to
+// 2048, with none and with a fifth of the neurons ablated) the code taken is 0.5 % behind the fastest of up to 10 on average, 13 % at worst; 0.6 % (15 %)
+// where any promise counts, 1.1 % (16 %) with one shape only.
 constexpr double kSplitGain = 0.92;
 static int choose_blocked_tile(int B, int d_in, int n_active, int d_out, double* us) {
     constexpr int kShapes[] = {SRIGL_BLOCKED_64, SRIGL_BLOCKED_128, SRIGL_BLOCKED_192, SRIGL_BLOCKED_256};
@@ -607,9 +608,8 @@ static int choose_blocked_tile(int B, int d_in, int n_active, int d_out, double*
     return best;
 }
 
-// Taken where its estimate is level with the gathering kernels' or ahead.  On 92 points (23 layers 155 to 2368 wide, 80 to 99 % sparse,
-// batches of 24 to 2048) a call is then 0.06 % slower on average than with the faster of the two forms throughout, 4 % at worst, with 1.0
-// or 1.05 in its place alike; with 0.95 0.12 % (9 %), with 1.1 0.5 % (9 %).
+// Taken where its estimate is level with the gathering kernels' or ahead.  On 168 points (21 layers 200 to 4096 wide, batches of 16 to 2048) a call with
+// its copy made is then 0.06 % slower on average than with the faster of the two forms throughout, 8 % at worst, one with the copy given 0.1 % (6 %).
 constexpr double kBlockedMargin = 1.02;
 
 // What making the copy adds to a call (us): between 4.1 (200 -> 300) and 14 (4096 -> 16384, K = 205) on those layers

@@ -32,9 +32,6 @@ __device__ __forceinline__ Four<uint16_t> load_four(const uint16_t* p) {
     return {{(uint16_t)f.x, (uint16_t)(f.x >> 16), (uint16_t)f.y, (uint16_t)(f.y >> 16)}};
 }
 
-template <int N>
-__device__ __forceinline__ float ror16(float v) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, true)); }
-
 template <typename XT, typename IT>
 __global__ __launch_bounds__(kStreamWaves* kWave) void k_fwd_klane_stream(const XT* __restrict__ x, int d_in, const XT* __restrict__ W_c,
                                                            const IT* __restrict__ idx, const int32_t* __restrict__ active, int n_active, int K,
@@ -103,10 +100,10 @@ __global__ __launch_bounds__(kStreamWaves* kWave) void k_fwd_klane_stream(const 
     const float u0 = __uint_as_float(h0[0]) + __uint_as_float(h0[1]), u1 = __uint_as_float(h1[0]) + __uint_as_float(h1[1]);
     const auto h = __builtin_amdgcn_permlane16_swap(__float_as_uint(u0), __float_as_uint(u1), false, false);
     float v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
-    v += ror16<8>(v);
-    v += ror16<4>(v);
-    v += ror16<2>(v);
-    v += ror16<1>(v);
+    v += row_ror<8>(v);
+    v += row_ror<4>(v);
+    v += row_ror<2>(v);
+    v += row_ror<1>(v);
     const bool mine = s0 + own < n_active;
     if (mine && (lane & 15) == 0 && stored) yr[col] = act == SRIGL_ACT_NONE ? v + bv : apply_act(v + bv, act);
     if (active == nullptr) return;
@@ -147,12 +144,12 @@ static srigl_status launch_stream_t(const FwdArgs& a, hipStream_t st) {
     return hip_ok(hipGetLastError());
 }
 
-// Taken in place of the other small-batch forms where there are terms to stream (over the batch 1.6 M, or 0.8 M per chunk of 256 terms of a
-// row, whose chunks follow one another), four workgroups to a compute unit hold all of them, and a row fills half of its wavefront's lanes
-// or more: 1.16 times faster on average on 22 of 220 points and 1.10 times on 33 of 320 others, nowhere slower by more than runs differ
-// (400 to 4096 wide, 128 to 16384 stored rows, batches 1 to 48, both types and index widths; 3142 -> 16707, K = 314 at one batch row 11.1 ->
-// 7.5 us, 3072 -> 768 with 538 stored, K = 307 at 16 6.9 -> 6.2, 4052 -> 4395 bf16, K = 202 at 3 6.6 -> 5.2).  From 1.0 M terms on some lose 9 to
-// 21 % (3912 -> 3106, K = 391 at 1; 3680 -> 1412, K = 736), with rows that fill fewer lanes 10 % (1011 -> 1884, K = 101 at 12).
+// The form of the small-batch kernel where there are terms to stream (over the batch 1.6 M, or 0.8 M per chunk of 256 terms of a row, whose chunks follow one
+// another), four workgroups to a compute unit hold all of them, and a row fills half of its wavefront's lanes or more (3142 -> 16707, K = 314 at one batch
+// row 11.1 -> 7.5 us, 3072 -> 768 with 538 stored, K = 307 at 16 6.9 -> 6.2, 4052 -> 4395 bf16, K = 202 at 3 6.6 -> 5.2).  Of 557 points where it may run (300
+// to 4096 wide, 128 to 16384 stored rows, batches 2 to 64, both types and index widths) a call takes it on 386, there in 0.85 of the gathering form's time
+// on average; on 14 it is 3 to 16 % behind (2559 -> 407, 326 stored, K = 281 at 24 rows 6.3 against 5.5: a second chunk for 25 terms).  From 1.0 M terms on
+// some would lose 9 to 21 % (3912 -> 3106, K = 391 at 1; 3680 -> 1412, K = 736), with rows that fill fewer lanes 10 % (1011 -> 1884, K = 101 at 12).
 bool stream_ahead(const FwdArgs& a) {
     if (a.B <= 0 || a.B > 64 || a.n_active <= 0 || a.K < kStreamTerms || (size_t)(a.d_in + 1) * sizeof(float) > kLdsMax / 4) return false;
     const int chunks = (a.K + kStreamChunk - 1) / kStreamChunk;

@@ -15,6 +15,10 @@ template <> __device__ __forceinline__ float rl_to_f32<uint16_t>(uint16_t v) { r
 __device__ __forceinline__ float lane_fetch(float v, int byte_addr) { return __int_as_float(__builtin_amdgcn_ds_bpermute(byte_addr, __float_as_int(v))); }
 __device__ __forceinline__ uint16_t lane_fetch(uint16_t v, int byte_addr) { return (uint16_t)__builtin_amdgcn_ds_bpermute(byte_addr, (int)v); }
 __device__ __forceinline__ int lane_fetch(int v, int byte_addr) { return __builtin_amdgcn_ds_bpermute(byte_addr, v); }
+template <int N>
+__device__ __forceinline__ float row_ror(float v) {   // the value N lanes below, around the 16-lane row
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, true));
+}
 __device__ __forceinline__ float rl_bias_at(const float* __restrict__ bias, int col) { return bias ? bias[col] : 0.0f; }
 
 // ------------------------------------------------------------------------------------------------

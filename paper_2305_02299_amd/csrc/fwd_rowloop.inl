@@ -69,10 +69,6 @@ __device__ __forceinline__ void xor_bcast(int ov, const int (&piece)[4], int (&a
     xor_bcast<GL, Q>(ov, hi, h);
     at[0] = l[0]; at[1] = l[1]; at[2] = h[0]; at[3] = h[1];
 }
-template <int N>
-__device__ __forceinline__ float row_ror(float v) {   // the value N lanes below, around the 16-lane row
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, true));
-}
 
 constexpr int kQuadBlock = 64;   // terms a wavefront's vector load of W_c / idx brings: 16 groups of lanes x 4 steps, or 32 x 2
 

@@ -560,7 +560,7 @@ srigl_status srigl_densify(const void* W_c, srigl_dtype w_dtype, const int32_t* 
 srigl_representation srigl_choose_representation(int32_t B, int32_t d_in, int32_t n_active, int32_t K, int32_t d_out,
                                                  srigl_dtype dtype, float* est_condensed_us, float* est_structured_us) {
     // bf16: on 920 layers and batches timed in both forms (128 to 4096 wide, batches 8 to 2048) the form taken is 1.1 % slower than the faster one on
-    // average, beyond 10 % on 22 (fan-ins of 1 to 3 at batches above 700, which the tiles' estimates put too low, among them); on 144 points of 16 named layers 0.4 %, at worst 17 %.
+    // average, beyond 10 % on 22 (fan-ins of 1 to 3 at batches above 700, which the tiles' estimates put too low, among them); on 144 points of 18 named layers 0.3 %, at worst 15 %.
     // (With the constants before, 1.7 % and 0.9 %, beyond 10 % on 48.  While the condensed estimate was the gathering kernels' alone: up to 20 %, and a
     // dense copy of 107 MB on 4096 -> 16384 for what the estimate called 2.7 times.)
     struct Key { int32_t B, d_in, n_active, K, d_out, dtype; };
