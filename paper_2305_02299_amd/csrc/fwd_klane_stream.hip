@@ -33,7 +33,7 @@ __device__ __forceinline__ Four<uint16_t> load_four(const uint16_t* p) {
 }
 
 template <typename XT, typename IT>
-__global__ __launch_bounds__(kStreamWaves* kWave) void k_fwd_klane_stream(const XT* __restrict__ x, int d_in, const XT* __restrict__ W_c,
+__global__ __launch_bounds__(kStreamWaves* kWave, sizeof(XT) + sizeof(IT) < 8 ? 8 : 6) void k_fwd_klane_stream(const XT* __restrict__ x, int d_in, const XT* __restrict__ W_c,
                                                            const IT* __restrict__ idx, const int32_t* __restrict__ active, int n_active, int K,
                                                            const float* __restrict__ bias, int d_out, float* __restrict__ y, int act) {
     extern __shared__ float xs[];   // the columns, then one of zeros for lanes without a term
@@ -82,14 +82,24 @@ __global__ __launch_bounds__(kStreamWaves* kWave) void k_fwd_klane_stream(const 
         Four<IT> cn[kStreamRows];
         if (k0 + kStreamChunk < K) request(k0 + kStreamChunk, wn, cn);   // on their way behind these
         const int first = k0 + kStreamTerms * lane, at = min(first, K - kStreamTerms);
+        // (the reads of two rows together: left to the compiler they came one at a time, each waited for, in some of its arrangements of this kernel: 3072 -> 448,
+        // K = 492 at eight rows 4.7 us for 4.3)
 #pragma unroll
-        for (int r = 0; r < kStreamRows; ++r)
+        for (int r0 = 0; r0 < kStreamRows; r0 += 2) {
+            float xv[2][kStreamTerms];
 #pragma unroll
-            for (int u = 0; u < kStreamTerms; ++u) {
-                const bool real = at + u >= first;   // (none where first >= K)
-                const unsigned j = real ? min((unsigned)c[r].v[u], (unsigned)d_in - 1u) : (unsigned)d_in;
-                acc[r] = fmaf(real ? rl_to_f32<XT>(w[r].v[u]) : 0.0f, xs[j], acc[r]);
-            }
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int u = 0; u < kStreamTerms; ++u)   // (no real term where first >= K)
+                    xv[r][u] = xs[at + u >= first ? min((unsigned)c[r0 + r].v[u], (unsigned)d_in - 1u) : (unsigned)d_in];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int u = 0; u < kStreamTerms; ++u)
+                    acc[r0 + r] = fmaf(at + u >= first ? rl_to_f32<XT>(w[r0 + r].v[u]) : 0.0f, xv[r][u], acc[r0 + r]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int r = 0; r < kStreamRows; ++r) { w[r] = wn[r]; c[r] = cn[r]; }
     }
@@ -108,29 +118,29 @@ __global__ __launch_bounds__(kStreamWaves* kWave) void k_fwd_klane_stream(const 
     if (mine && (lane & 15) == 0 && stored) yr[col] = act == SRIGL_ACT_NONE ? v + bv : apply_act(v + bv, act);
     if (active == nullptr) return;
     // Ablated columns hold their bias: the run in front of each row's column, and the one behind the last row's.  The 16 lanes of a row write
-    // its first 16 columns; longer runs are the whole wavefront's, four loads of the bias in flight.  By 16 lanes, one load after the
+    // its first 16 columns; longer runs are the whole wavefront's, a load of the bias ahead of each store.  By 16 lanes, one load after the
     // other, a run cost 5 ns a column: 1565 -> 7698, K = 140 at two batch rows with 769 neighbours ablated at either end 9.8 us (the gathering
     // form 6.8), now 5.4; 1528 -> 4680, K = 305 at two with 468 7.9 (5.6), now 5.0.
     constexpr int kOwn = 16;
     auto put = [&](int q, float raw) { yr[q] = act == SRIGL_ACT_NONE ? raw : apply_act(raw, act); };
-    auto fill = [&](int from, int to) {
-        for (int q0 = from + lane; q0 < to; q0 += 4 * kWave) {
-            float b[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) b[u] = rl_bias_at(bias, min(q0 + u * kWave, to - 1));
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (q0 + u * kWave < to) put(q0 + u * kWave, b[u]);
-        }
-    };
     const int from = max(prev + 1, 0), to = mine ? min(col, d_out) : from;
     if (from + (lane & 15) < to) put(from + (lane & 15), rl_bias_at(bias, from + (lane & 15)));
-    if (__any(to - from > kOwn)) {
-#pragma unroll
-        for (int g = 0; g < kStreamRows; ++g)
-            fill(__builtin_amdgcn_readlane(from, 16 * g) + kOwn, __builtin_amdgcn_readlane(to, 16 * g));
+    const bool last = s0 + kStreamRows >= n_active;   // (the last row's column then is that of lane 63: rows past it were clamped to it)
+    if (!last && !__any(to - from > kOwn)) return;
+    const int behind = max(__builtin_amdgcn_readlane(col, kWave - 1) + 1, 0);
+#pragma unroll 1
+    for (int g = 0; g < kStreamRows + (last ? 1 : 0); ++g) {
+        const int lo = g < kStreamRows ? __builtin_amdgcn_readlane(from, 16 * g) + kOwn : behind;
+        const int hi = g < kStreamRows ? __builtin_amdgcn_readlane(to, 16 * g) : d_out;
+        if (lo >= hi) continue;
+        float next = rl_bias_at(bias, min(lo + lane, hi - 1));
+#pragma unroll 1
+        for (int q = lo + lane; q < hi; q += kWave) {
+            const float raw = next;
+            next = rl_bias_at(bias, min(q + kWave, hi - 1));
+            put(q, raw);
+        }
     }
-    if (s0 + kStreamRows >= n_active) fill(max(__builtin_amdgcn_readlane(col, 63) + 1, 0), d_out);   // (the last row's: rows past it were clamped to it)
 }
 
 template <typename XT, typename IT>
