@@ -40,9 +40,12 @@ __global__ __launch_bounds__(kStreamWaves* kWave, sizeof(XT) + sizeof(IT) < 8 ? 
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     constexpr int kThreads = kStreamWaves * kWave;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const XT* const xr = x + (size_t)blockIdx.y * d_in;
-    float* const yr = y + (size_t)blockIdx.y * d_out;
-    const int s0 = (blockIdx.x * kStreamWaves + wv) * kStreamRows;   // (may lie past the last row)
+    // (groups of stored rows, batch rows, 1), or (8, batch rows, groups / 8): consecutive workgroups go to different XCDs
+    const unsigned b = blockIdx.y;
+    const int s0 = (int)((blockIdx.z * 8 + blockIdx.x) * kStreamWaves + wv) * kStreamRows;   // (may lie past the last row)
+    if (s0 - wv * kStreamRows >= n_active) return;   // (the whole workgroup)
+    const XT* const xr = x + (size_t)b * d_in;
+    float* const yr = y + (size_t)b * d_out;
     // after the sums over lanes, 16-lane group g of the wavefront holds row s0 + own (0, 2, 1, 3)
     const int own = ((lane >> 5) | ((lane >> 3) & 2));
 
@@ -98,7 +101,6 @@ __global__ __launch_bounds__(kStreamWaves* kWave, sizeof(XT) + sizeof(IT) < 8 ? 
 #pragma unroll
                 for (int u = 0; u < kStreamTerms; ++u)
                     acc[r0 + r] = fmaf(at + u >= first ? rl_to_f32<XT>(w[r0 + r].v[u]) : 0.0f, xv[r][u], acc[r0 + r]);
-            __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int r = 0; r < kStreamRows; ++r) { w[r] = wn[r]; c[r] = cn[r]; }
@@ -121,6 +123,7 @@ __global__ __launch_bounds__(kStreamWaves* kWave, sizeof(XT) + sizeof(IT) < 8 ? 
     // its first 16 columns; longer runs are the whole wavefront's, a load of the bias ahead of each store.  By 16 lanes, one load after the
     // other, a run cost 5 ns a column: 1565 -> 7698, K = 140 at two batch rows with 769 neighbours ablated at either end 9.8 us (the gathering
     // form 6.8), now 5.4; 1528 -> 4680, K = 305 at two with 468 7.9 (5.6), now 5.0.
+    // (The short runs' bias asked for ahead of the barrier spilled registers: 3 to 13 % slower.)
     constexpr int kOwn = 16;
     auto put = [&](int q, float raw) { yr[q] = act == SRIGL_ACT_NONE ? raw : apply_act(raw, act); };
     const int from = max(prev + 1, 0), to = mine ? min(col, d_out) : from;
@@ -144,13 +147,15 @@ __global__ __launch_bounds__(kStreamWaves* kWave, sizeof(XT) + sizeof(IT) < 8 ? 
 }
 
 template <typename XT, typename IT>
-static srigl_status launch_stream_t(const FwdArgs& a, hipStream_t st) {
+static srigl_status launch_stream_t(const FwdArgs& a, bool by_xcd, hipStream_t st) {
     auto kern = k_fwd_klane_stream<XT, IT>;
     static LdsLimit lds_limit;
     const size_t lds = (size_t)(a.d_in + 1) * sizeof(float);
     if (lds_limit.ensure(kern, lds) != SRIGL_OK) return SRIGL_ERR_HIP;
-    hipLaunchKernelGGL(kern, dim3((unsigned)stream_groups(a), (unsigned)a.B), dim3(kStreamWaves * kWave), lds, st, (const XT*)a.x, a.d_in,
-                       (const XT*)a.W_c, (const IT*)a.idx, a.active, a.n_active, a.K, a.bias, a.d_out, a.y, a.act);
+    const unsigned groups = (unsigned)stream_groups(a);   // (at most 64 batch rows and 32768 rows in all: stream_ahead)
+    const dim3 grid = by_xcd ? dim3(8, (unsigned)a.B, (groups + 7) / 8) : dim3(groups, (unsigned)a.B);
+    hipLaunchKernelGGL(kern, grid, dim3(kStreamWaves * kWave), lds, st, (const XT*)a.x, a.d_in, (const XT*)a.W_c, (const IT*)a.idx, a.active,
+                       a.n_active, a.K, a.bias, a.d_out, a.y, a.act);
     return hip_ok(hipGetLastError());
 }
 
@@ -167,22 +172,32 @@ bool stream_ahead(const FwdArgs& a) {
     return terms >= 0.8e6 * std::max(2, chunks) && (long long)a.n_active * a.B <= 4 * 256 * kStreamWaves * kStreamRows && 2 * a.K >= chunks * kStreamChunk;
 }
 
+static double stream_bytes(const FwdArgs& a) { return (double)a.n_active * a.K * ((a.x_bf16 ? 2 : 4) + (a.idx_u16 ? 2 : 4)); }
+// Whether the grid makes every batch row's workgroup of a group of stored rows go to the same XCD, whose L2 then fetches the group's terms once and no
+// other's; otherwise a batch row's workgroups go round the XCDs from where the row before ended, which comes to the same where the groups are a multiple of
+// eight, and else each meets all terms.  Taken from 2 MB of terms on (level in a loop over one layer up to 4 MB, but two layers' terms then share an L2:
+// 915 -> 2745 -> 915 at 11 rows 13.8 -> 11.7 us; 497 points: 0.90 of the time at 8 to 12 MB, 0.68 beyond 20, 2834 -> 3423, K = 481 at four rows 9.9 -> 7.5 us) where
+// that keeps the XCDs within a ninth of equal work (172 stored rows, six groups, up to 1.3 times slower).
+static bool stream_by_xcd(const FwdArgs& a) {
+    const int groups = stream_groups(a);
+    return groups % 8 != 0 && stream_bytes(a) > 2e6 && 9 * ((groups + 7) / 8 * 8) <= 10 * groups;
+}
+
 // Estimated time (us), for the comparison with the batched kernels: the columns of x that the workgroups stage, the places that the chunks of all
-// rows take, the chunks after the first, the bytes of the terms, and those of them that the L2s fetch beyond their 32 MB: a batch row's workgroups
-// go round the XCDs from where the row before ended, so that unless their number is a multiple of eight every XCD meets all terms
-// (2834 -> 3423, K = 481, four rows 9.9 us, 7.6 of it without).  Non-negative least squares on the relative error of 272 launches on which stream_ahead holds (300 to 4096 wide,
-// 128 to 16384 stored rows, batches 2 to 64, both types and index widths, random ablation, cached operands): standard deviation 8 %, worst -21 and +24 %.
+// rows take, the chunks after the first, and the bytes of the terms that the L2s fetch beyond their 32 MB.  Non-negative least squares on the relative
+// error of 497 launches on which stream_ahead holds (300 to 4096 wide, 128 to 16384 stored rows, batches 2 to 64, both types and index widths,
+// random ablation, cached operands): standard deviation 7.5 %, worst -22 and +21 %.
 double stream_estimate_us(const FwdArgs& a) {
     const double chunks = (a.K + kStreamChunk - 1) / kStreamChunk;
-    const double bytes = (double)a.n_active * a.K * ((a.x_bf16 ? 2 : 4) + (a.idx_u16 ? 2 : 4));
-    const double fetched = stream_groups(a) % 8 ? bytes * std::min(a.B, 8) : bytes;
-    return 3.27 + 0.449e-6 * stream_groups(a) * a.B * (double)a.d_in + 0.276e-6 * a.n_active * a.B * chunks * kStreamChunk + 0.0131e-6 * bytes +
-           0.162e-6 * std::max(0.0, fetched - 32e6) + 0.41 * (chunks - 1);
+    const double bytes = stream_bytes(a), fetched = stream_by_xcd(a) || stream_groups(a) % 8 == 0 ? bytes : bytes * std::min(a.B, 8);
+    return 3.40 + 0.460e-6 * stream_groups(a) * a.B * (double)a.d_in + 0.282e-6 * a.n_active * a.B * chunks * kStreamChunk +
+           0.098e-6 * std::max(0.0, fetched - 32e6) + 0.28 * (chunks - 1);
 }
 
 srigl_status launch_fwd_stream(const FwdArgs& a, hipStream_t st) {
-    if (a.idx_u16) return a.x_bf16 ? launch_stream_t<uint16_t, uint16_t>(a, st) : launch_stream_t<float, uint16_t>(a, st);
-    return a.x_bf16 ? launch_stream_t<uint16_t, int32_t>(a, st) : launch_stream_t<float, int32_t>(a, st);
+    const bool by_xcd = stream_by_xcd(a);
+    if (a.idx_u16) return a.x_bf16 ? launch_stream_t<uint16_t, uint16_t>(a, by_xcd, st) : launch_stream_t<float, uint16_t>(a, by_xcd, st);
+    return a.x_bf16 ? launch_stream_t<uint16_t, int32_t>(a, by_xcd, st) : launch_stream_t<float, int32_t>(a, by_xcd, st);
 }
 
 }  // namespace srigl

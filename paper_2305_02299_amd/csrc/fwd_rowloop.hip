@@ -27,7 +27,7 @@ static double rowloop_us(const FwdArgs& a, const RowloopPlan& p) {
     struct Fit { double fixed, round, word, big, step, row, y, fetched, long_row, second_pass; };
     static const Fit fits[4] = {{2.620, 1.863, 0.2704e-4, 0.272e-4, 0.0635, 0.0866, 2.371e-6, 0.0314e-6, 0.1509, 0.0},
                                 {2.231, 2.147, 0.2049e-4, 0.585e-4, 0.0545, 0.0423, 2.128e-6, 0.0585e-6, 0.2256, 1.4},
-                                {3.522, 1.023, 0.1370e-4, 1.2465e-4, 0.0866, 0.0701, 1.613e-6, 0.0430e-6, 0.5675, 1.1},
+                                {3.522, 1.023, 0.1370e-4, 1.2465e-4, 0.0866, 0.0701, 1.613e-6, 0.0430e-6, 0.5675, 0.6},
                                 {3.131, 1.348, 0.2724e-4, 0.3693e-4, 0.1745, 0.0951, 1.378e-6, 0.0448e-6, 0.0, 0.7}};
     const Fit& f = fits[p.BT == 8 ? 0 : p.BT == 16 ? 1 : p.BT == 32 ? 2 : 3];
     const int steps = a.K <= 256 ? p.ST : p.BT == 8 ? 8 + 2 * ((a.K - 256 + 63) / 64) : 16 + 4 * ((a.K - 256 + 63) / 64);
