@@ -821,14 +821,14 @@ static OtherEstimates other_estimates(const FwdArgs& a) {
     const RowlanePlan rp = plan_rowlane_by_estimate(a, nullptr);
     return {rp.ok ? rowlane_estimate_us(a, rp, true) : 1e30, a.B > 2048 && rp.ok ? 1e30 : small_estimate_us(a)};
 }
-// The whole-input batched kernel is taken where its estimate is ahead of theirs, 5 % in its favour against the chunked kernel: over 304 points
-// (67 layers 112 to 2400 wide, fan-ins 6 to 384, both types, batches 8 to 2048) the call is then 0.8 % behind the fastest of the
-// three kernels on average; 1.0 % with 5 % against both, 1.1 % with none, 0.9 % with 10 % against the chunked one.  Below 32 batch rows it is
-// never taken against the staged few-lanes shape of the small-batch kernel, which was placed by measurement.
+// The whole-input batched kernel is taken where its estimate is ahead of theirs, 5 % in its favour: over 2070 points (100 to 4096 wide, 100 to
+// 16384 stored rows, fan-ins 1 to 800, both types and index widths, batches 2 to 2048) the call is then 1.6 % behind the fastest of the four kernels up to 64
+// batch rows and 2.6 % above; with none against the small-batch kernel 1.7 and 3.3 % (128 -> 6592, K = 6, 4417 stored at 180 10.3 us, 8.6 in a tile),
+// with 8 % 1.8 and 2.4 %.  Below 32 batch rows it is never taken against the staged few-lanes shape of the small-batch kernel, which was placed by measurement.
 static bool tile_ahead(const FwdArgs& a, double us) {
     const OtherEstimates o = other_estimates(a);
     // (beyond 2304 columns a tile leaves room for nine stored rows to a wavefront and less: 2400 -> 12000, K = 48 at batch 800 143 us, chunked 134)
-    return us * (a.d_in > 2304 ? 1.0 : 0.95) < o.batched && us < o.small;
+    return us * (a.d_in > 2304 ? 1.0 : 0.95) < o.batched && 0.95 * us < o.small;
 }
 static srigl_fwd_algo choose_fwd_algo(const FwdArgs& a, RowloopPlan* tile) {
     const srigl_fwd_algo base = choose_chunked_or_small(a);

@@ -162,8 +162,8 @@ static srigl_status launch_stream_t(const FwdArgs& a, bool by_xcd, hipStream_t s
 // The form of the small-batch kernel where there are terms to stream (over the batch 1.6 M, or 0.8 M per chunk of 256 terms of a row, whose chunks follow one
 // another), four workgroups to a compute unit hold all of them, and a row fills half of its wavefront's lanes or more (3142 -> 16707, K = 314 at one batch
 // row 11.1 -> 7.5 us, 3072 -> 768 with 538 stored, K = 307 at 16 6.9 -> 6.2, 4052 -> 4395 bf16, K = 202 at 3 6.6 -> 5.2).  Of 557 points where it may run (300
-// to 4096 wide, 128 to 16384 stored rows, batches 2 to 64, both types and index widths) a call takes it on 386, there in 0.85 of the gathering form's time
-// on average; on 14 it is 3 to 16 % behind (2559 -> 407, 326 stored, K = 281 at 24 rows 6.3 against 5.5: a second chunk for 25 terms).  From 1.0 M terms on
+// to 4096 wide, 128 to 16384 stored rows, batches 2 to 64, both types and index widths) a call takes it on 401, there in 0.86 of the gathering form's time
+// on average; on a few it is 3 to 14 % behind (2559 -> 407, 326 stored, K = 281 at 24 rows 6.2 against 5.4: a second chunk for 25 terms).  From 1.0 M terms on
 // some would lose 9 to 21 % (3912 -> 3106, K = 391 at 1; 3680 -> 1412, K = 736), with rows that fill fewer lanes 10 % (1011 -> 1884, K = 101 at 12).
 bool stream_ahead(const FwdArgs& a) {
     if (a.B <= 0 || a.B > 64 || a.n_active <= 0 || a.K < kStreamTerms || (size_t)(a.d_in + 1) * sizeof(float) > kLdsMax / 4) return false;
