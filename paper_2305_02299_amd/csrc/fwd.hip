@@ -823,7 +823,7 @@ static OtherEstimates other_estimates(const FwdArgs& a) {
 }
 // The whole-input batched kernel is taken where its estimate is ahead of theirs, 5 % in its favour: over 2070 points (100 to 4096 wide, 100 to
 // 16384 stored rows, fan-ins 1 to 800, both types and index widths, batches 2 to 2048) the call is then 1.6 % behind the fastest of the four kernels up to 64
-// batch rows and 2.6 % above; with none against the small-batch kernel 1.7 and 3.3 % (128 -> 6592, K = 6, 4417 stored at 180 10.3 us, 8.6 in a tile),
+// batch rows and 2.6 % above; with none against the small-batch kernel 1.7 and 3.3 % (128 -> 6592, K = 6, 4417 stored at 180 10.3 us, 7.8 in a tile),
 // with 8 % 1.8 and 2.4 %.  Below 32 batch rows it is never taken against the staged few-lanes shape of the small-batch kernel, which was placed by measurement.
 static bool tile_ahead(const FwdArgs& a, double us) {
     const OtherEstimates o = other_estimates(a);
