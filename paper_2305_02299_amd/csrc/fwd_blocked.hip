@@ -432,7 +432,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
     load_list(0);
 #pragma unroll
     for (int q = 0; q < XP; ++q) issue_piece(0, q);
-    fill_table<BN, WGM, NWAVES * 64>(table, cols.lo, cols, n0, p.active, p.bias);
+    fill_table<BN, WGM, NWAVES * 64>(table, cols.base, cols, n0, p.active, p.bias);
     if (!DIRECT) store_x(0);
     wait_loads<0>();
     build(0);

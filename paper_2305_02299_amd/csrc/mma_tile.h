@@ -60,11 +60,12 @@ __device__ __forceinline__ bool tile_of_workgroup(int id, int tiles_m, int tiles
 // ---- epilogue: a tile's sums to their columns of y ----
 // The columns of y that the tile at stored neuron n0 writes: its stored neurons and the ablated ones in front of them (behind the
 // last one too in the last tile) are one contiguous range.
-struct TileColumns { int lo, hi, stored; };
+struct TileColumns { int lo, hi, stored, base; };   // base: where the windows begin, the columns' 128-byte line
 __device__ __forceinline__ TileColumns tile_columns(int n0, int bn, const int32_t* active, int n_active, int d_out) {
     const int cnt = min(bn, n_active - n0);
-    if (!active) return {n0, n0 + cnt - 1, cnt};
-    return {max((n0 > 0) ? active[n0 - 1] + 1 : 0, 0), min((n0 + cnt == n_active) ? d_out - 1 : active[n0 + cnt - 1], d_out - 1), cnt};
+    if (!active) return {n0, n0 + cnt - 1, cnt, n0 & ~31};
+    const int lo = max((n0 > 0) ? active[n0 - 1] + 1 : 0, 0);
+    return {lo, min((n0 + cnt == n_active) ? d_out - 1 : active[n0 + cnt - 1], d_out - 1), cnt, lo & ~31};
 }
 
 // LDS of the epilogue: one 32-row part of each wavefront row's tile at a time, at the rows' final columns (a window of COLS of them;
@@ -94,7 +95,7 @@ __device__ __forceinline__ void fill_table(unsigned char* at, int cc, const Tile
         }
         const int col = active ? active[n0 + s] : n0 + s;
         const int prev = s == 0 ? c.lo - 1 : (active ? active[n0 + s - 1] : n0 + s - 1);
-        place[s] = col >= c.lo && col <= c.hi ? col - c.lo : -1;
+        place[s] = col >= c.lo && col <= c.hi ? col - c.base : -1;
         for (int k = max(prev + 1 - cc, 0); k < min(col - cc, wc); ++k) table[k] = -1;
         if (col >= cc && col - cc < wc) table[col - cc] = s;
         if (s == c.stored - 1)
@@ -113,6 +114,9 @@ __device__ __forceinline__ void fill_table(unsigned char* at, int cc, const Tile
 // With that and the float4 rows a 768 -> 3072 layer in 256 x 256 tiles went from 36.4 to 32.3 us, 4096 -> 16384 at batch 2048 from 297 to
 // 279 in 128 x 128 tiles.  Narrow tiles put 2 or 4 rows into one LDS request (16 or 32 lanes each): with 64 lanes on a row 64 x 64
 // tiles took 11.5 us instead of 9.4 on 768 -> 3072 at batch 128.
+// The windows begin at a 128-byte line of y where its rows do (columns in front of the tile's own are left out): with ablated neurons a tile's first column
+// lies anywhere, and every store of a kilobyte then began and ended in part of a line, which streaming stores do not put together: 4096 -> 16384 with
+// 13108 stored at batch 2048 207 -> 201 us (condensed form 212 -> 208), 1024 -> 16384 with 8192 stored 73 -> 64.  (Plain stores: the first two 203 and 218.)
 // SPOILED: the tile's rows with a sum that is not finite get their bits set in `spoiled` (BM of them, in LDS); what has been written for
 // them is up to the caller to mend.
 template <int BM, int BN, int WGM, int WGN, bool SPOILED, int TM, int TN>
@@ -133,12 +137,13 @@ __device__ __forceinline__ void store_tile(unsigned char* smem, unsigned char* t
     const int* const table = place + BN;
     float* const tbias = reinterpret_cast<float*>(table_at + (size_t)(BN + EL::COLS) * 4);
     if (!have_table) {
-        fill_table<BN, WGM, NWAVES * 64>(table_at, cols.lo, cols, n0, active, bias);
+        fill_table<BN, WGM, NWAVES * 64>(table_at, cols.base, cols, n0, active, bias);
         __syncthreads();
     }
-    for (int cc = cols.lo; cc <= cols.hi; cc += EL::COLS) {
+    for (int cc = cols.base; cc <= cols.hi; cc += EL::COLS) {
         const int wc = min(EL::COLS, cols.hi - cc + 1);
-        if (cc != cols.lo) {
+        const int head = max(cols.lo - cc, 0);   // columns of the first line that are the tile's before
+        if (cc != cols.base) {
             __syncthreads();   // the previous window is done with the tables
             fill_table<BN, WGM, NWAVES * 64>(table_at, cc, cols, n0, active, bias);
             __syncthreads();
@@ -146,7 +151,7 @@ __device__ __forceinline__ void store_tile(unsigned char* smem, unsigned char* t
         if (act != SRIGL_ACT_NONE) {
             __syncthreads();
             for (int k = tid; k < wc; k += NWAVES * 64)
-                if (table[k] < 0) tbias[k] = apply_act(tbias[k], act);
+                if (k >= head && table[k] < 0) tbias[k] = apply_act(tbias[k], act);
             __syncthreads();
         }
         int at[TN];        // this lane's columns in the window
@@ -154,7 +159,7 @@ __device__ __forceinline__ void store_tile(unsigned char* smem, unsigned char* t
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int q = place[wn * WTN + j * 32 + (lane & 31)];
-            at[j] = q < 0 ? -1 : q - (cc - cols.lo);
+            at[j] = q < 0 ? -1 : q - (cc - cols.base);
             if (at[j] >= wc) at[j] = -1;
             badd[j] = tbias[max(at[j], 0)];
         }
@@ -166,11 +171,11 @@ __device__ __forceinline__ void store_tile(unsigned char* smem, unsigned char* t
             for (int j = 0; j < 4; ++j) {
                 const int k = RUN * run + 4 * (lane % LR) + j, in = min(k, wc - 1);
                 flat[run][j] = tbias[in];
-                if (k >= wc || table[in] < 0) gaps |= 1 << (4 * run + j);
+                if (k < head || k >= wc || table[in] < 0) gaps |= 1 << (4 * run + j);
             }
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            if (i > 0 || cc != cols.lo) __syncthreads();   // the rows before have been read
+            if (i > 0 || cc != cols.base) __syncthreads();   // the rows before have been read
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 if (at[j] >= 0) {
@@ -203,7 +208,7 @@ __device__ __forceinline__ void store_tile(unsigned char* smem, unsigned char* t
 #pragma unroll 1
                         for (int q = 0; q < 16; ++q) {
                             const int k = k0 + (q & 3), mq = m + (q >> 2) * RPI, r = mq - m0;
-                            if (k < wc && table[k] >= 0 && mq < B && !(fabsf(t0[(q >> 2) * RPI * PITCH + (q & 3)]) <= 3.4028234e38f))
+                            if (k >= head && k < wc && table[k] >= 0 && mq < B && !(fabsf(t0[(q >> 2) * RPI * PITCH + (q & 3)]) <= 3.4028234e38f))
                                 atomicOr(&spoiled[r >> 5], 1u << (r & 31));
                         }
                     }
@@ -212,7 +217,7 @@ __device__ __forceinline__ void store_tile(unsigned char* smem, unsigned char* t
                         for (int q = 0; q < 16; ++q) {
                             const int k = k0 + (q & 3), mq = m + (q >> 2) * RPI;
                             float* const at_q = t0 + (q >> 2) * RPI * PITCH + (q & 3);
-                            if (k < wc && table[k] >= 0 && mq < B) *at_q = apply_act(*at_q, act);
+                            if (k >= head && k < wc && table[k] >= 0 && mq < B) *at_q = apply_act(*at_q, act);
                         }
 #pragma unroll
                         for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const float4_t*>(t0 + u * RPI * PITCH);
@@ -224,12 +229,12 @@ __device__ __forceinline__ void store_tile(unsigned char* smem, unsigned char* t
                         for (int j = 0; j < 4; ++j) v[u][j] = (gaps >> (4 * run + j)) & 1 ? flat[run][j] : v[u][j];
                         float* const yu = yr + (size_t)(u * RPI) * d_out;
                         if (m + u * RPI < B) {
-                            if (k0 + 4 <= wc) {
+                            if (k0 >= head && k0 + 4 <= wc) {
                                 __builtin_nontemporal_store(v[u], reinterpret_cast<float4_at4_t*>(yu));
                             } else {
 #pragma unroll
-                                for (int j = 0; j < 3; ++j)
-                                    if (k0 + j < wc) yu[j] = v[u][j];
+                                for (int j = 0; j < 4; ++j)
+                                    if (k0 + j >= head && k0 + j < wc) yu[j] = v[u][j];
                             }
                         }
                     }
