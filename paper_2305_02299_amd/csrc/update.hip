@@ -79,6 +79,13 @@ __global__ __launch_bounds__(256) void k_update_init(uint4* __restrict__ head) {
     for (size_t i = blockIdx.x * 256 + threadIdx.x; i < kZeroWords; i += (size_t)gridDim.x * 256) head[i] = z;
 }
 
+// The part of the layer (of `parts`) that workgroup w works on, in every launch that reads the layer: consecutive workgroup ids go round the eight
+// dies, and each of them stays with the same eighth of the layer, which its L2 then still holds from the launch before.
+constexpr unsigned int kDies = 8;
+__device__ __forceinline__ unsigned int part_of_workgroup(unsigned int w, unsigned int workgroups) {
+    return workgroups % kDies ? w : w % kDies * (workgroups / kDies) + w / kDies;
+}
+
 // Four consecutive elements of the flat layer.
 struct Quad {
     uint32_t m;
@@ -112,7 +119,7 @@ __global__ __launch_bounds__(kScanThreads) void k_hist(const float* __restrict__
                                                        unsigned int N, unsigned int n4, UpdateScratch* __restrict__ s) {
     __shared__ __align__(16) unsigned int h[2][kDigits];
     const int t = threadIdx.x;
-    const unsigned int per = (n4 + gridDim.x - 1) / gridDim.x, q0 = min(blockIdx.x * per, n4), q1 = min(q0 + per, n4);
+    const unsigned int per = (n4 + gridDim.x - 1) / gridDim.x, q0 = min(part_of_workgroup(blockIdx.x, gridDim.x) * per, n4), q1 = min(q0 + per, n4);
     Quad q[kQuads];
     if (q0 < q1) load_quads<true>(q, W, mask, grad, q0, q1);
     for (int i = t; i < 2 * kDigits / 4; i += kScanThreads) reinterpret_cast<uint4*>(&h[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
@@ -252,7 +259,7 @@ __global__ __launch_bounds__(kScanThreads) void k_collect(const float* __restric
     __shared__ unsigned long long base[2];
     const int t = threadIdx.x;
     constexpr int selA = PAIR ? 0 : 2;
-    const unsigned int per = (n4 + gridDim.x - 1) / gridDim.x, q0 = min(blockIdx.x * per, n4), q1 = min(q0 + per, n4);
+    const unsigned int per = (n4 + gridDim.x - 1) / gridDim.x, q0 = min(part_of_workgroup(blockIdx.x, gridDim.x) * per, n4), q1 = min(q0 + per, n4);
     Quad q[kQuads];
     if (!PAIR && sum_copies(s->cnt_ablated, t & 63) == 0) return;
     if (q0 < q1) load_quads<PAIR>(q, W, mask, grad, q0, q1);   // (before the counters are waited for)
@@ -679,7 +686,7 @@ __global__ __launch_bounds__(256) void k_row_salient(const float* __restrict__ W
     __shared__ __align__(16) unsigned int gone[kDigits];
     bool ablates = false;
     const int lane = threadIdx.x & 63;
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int r = part_of_workgroup(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
     if (threadIdx.x == 0) { wg_stay = 0; wg_ablated = 0; }
     const size_t row0 = (size_t)r * d_in;
     const bool quads = d_in >= 4;
@@ -781,7 +788,7 @@ __global__ __launch_bounds__(256) void k_row_update(const float* __restrict__ W,
     static_assert(WPR == 1 || WPR == 4, "the workgroup's barrier is the row's");
     __shared__ int part[2][4];
     const int lane = WPR == 1 ? threadIdx.x & 63 : threadIdx.x;
-    const int r = WPR == 1 ? blockIdx.x * 4 + (threadIdx.x >> 6) : blockIdx.x;
+    const int part_no = part_of_workgroup(blockIdx.x, gridDim.x), r = WPR == 1 ? part_no * 4 + (threadIdx.x >> 6) : part_no;
     if (r >= d_out) return;
     const size_t row0 = (size_t)r * d_in;
     const bool quads = NQ > 1 || WPR > 1 || d_in >= 4;
@@ -1015,7 +1022,7 @@ srigl_status srigl_mask_update(const float* W, const uint8_t* mask, const float*
     const unsigned int parts = N < (1u << 24) ? std::min(blocks, 64u) : (unsigned)kWideParts;
     hipLaunchKernelGGL(k_final<true>, dim3(2 * parts), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, d_in, s, candA, candB, cap,
                        (unsigned long long)K_upd, (long long)budget, report);
-    const dim3 row_grid((unsigned)((d_out + 3) / 4));
+    const dim3 row_grid(((unsigned)((d_out + 3) / 4) + kDies - 1) / kDies * kDies);   // (the same number of workgroups on every die)
     hipLaunchKernelGGL(k_row_salient, row_grid, dim3(256), 0, st, W, mask, grad, d_out, d_in, k, gamma_percent, s, remains);
     // (most updates ablate nothing and this launch returns at once: it takes few workgroups, whose start is then all it costs)
     hipLaunchKernelGGL(k_collect<false>, dim3(std::min(blocks, 64u)), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, n4, d_in, (unsigned long long)K_upd, s,
@@ -1023,7 +1030,7 @@ srigl_status srigl_mask_update(const float* W, const uint8_t* mask, const float*
     hipLaunchKernelGGL(k_final<false>, dim3(parts), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, d_in, s, candA, candB, cap,
                        (unsigned long long)K_upd, (long long)budget, report);
 #define SRIGL_ROW_UPDATE(NQ, WPR)                                                                                                      \
-    hipLaunchKernelGGL((k_row_update<NQ, WPR>), WPR == 1 ? row_grid : dim3((unsigned)d_out), dim3(256), 0, st, W, mask, grad, d_out, d_in, remains, \
+    hipLaunchKernelGGL((k_row_update<NQ, WPR>), WPR == 1 ? row_grid : dim3(((unsigned)d_out + kDies - 1) / kDies * kDies), dim3(256), 0, st, W, mask, grad, d_out, d_in, remains, \
                        s, mask_out, W_out)
     const int nq = (d_in + 255) / 256;
     if (nq <= 1) SRIGL_ROW_UPDATE(1, 1);
