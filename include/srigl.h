@@ -111,6 +111,25 @@ srigl_status srigl_condense(const void* W, srigl_dtype w_dtype, const uint8_t* m
                             int32_t* active, uint16_t* seg, void* packed, size_t packed_bytes, void* workspace,
                             size_t workspace_bytes, srigl_report* report_dev, void* stream);
 
+/* srigl_condense in two calls, for callers that wait for the number of stored rows on the host: the first launch can run before the buffers that are sized for
+ * the largest result have been allocated, and on layers up to 8 M elements it leaves the rows' counts in host memory, so that they are there before the
+ * second launch has run.
+ * srigl_condense_count: counts (may be NULL): srigl_condense_count_bytes(d_out, d_in) bytes (0: this layer's call takes none) of pinned host memory that the GPU can
+ *   write, 8-byte aligned; cleared by the call, filled by its launch.  It must stay allocated until all counts are there or the stream has finished.
+ * srigl_condense_counted: reads on from word *from (0 at first); 0 while counts are missing, 1 when *report (host memory) is complete, as srigl_condense reports with
+ *   the cap_rows of the second call.  Host only.
+ * srigl_condense_write: the second launch, on the same stream, with the workspace of the first; results as in srigl_condense; report may be NULL. */
+size_t srigl_condense_count_bytes(int32_t d_out, int32_t d_in);
+
+srigl_status srigl_condense_count(const uint8_t* mask, int32_t d_out, int32_t d_in, int32_t K, void* workspace, size_t workspace_bytes, void* counts,
+                                  size_t counts_bytes, void* stream);
+
+srigl_status srigl_condense_write(const void* W, srigl_dtype w_dtype, const uint8_t* mask, int32_t d_out, int32_t d_in, int32_t K, int32_t cap_rows,
+                                  void* W_c, int32_t* idx, int32_t* active, uint16_t* seg, void* packed, size_t packed_bytes, void* workspace,
+                                  size_t workspace_bytes, srigl_report* report, void* stream);
+
+int32_t srigl_condense_counted(const void* counts, int32_t d_out, int32_t K, int32_t cap_rows, int32_t* from, srigl_report* report);
+
 /* The streaming copy of a condensed layer.  App. E's representation is the two n x k arrays; how they lie in memory
  * for the forward pass is free, and W_c / idx as separate row-major arrays of K = 77, 205, 307 ... words per row leave
  * every row at another alignment, so a lane can fetch only one 4-byte (2-byte) word per load.  The copy holds the same

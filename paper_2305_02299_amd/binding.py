@@ -29,6 +29,7 @@ TILES = {"256x256": TILE_256x256, "256x256_h": TILE_256x256_H, "256x128_w4": TIL
 
 EXPORTS = (
     "srigl_workspace_bytes", "srigl_seg_stride", "srigl_check_fanin", "srigl_condense", "srigl_condense_static",
+    "srigl_condense_count_bytes", "srigl_condense_count", "srigl_condense_counted", "srigl_condense_write",
     "srigl_packed_bytes", "srigl_pack_terms",
     "srigl_condensed_linear_fwd", "srigl_condensed_linear_fwd_algo", "srigl_launch_empty",
     "srigl_copy_bytes", "srigl_status_str", "srigl_densify", "srigl_structured_linear_fwd",
@@ -76,6 +77,14 @@ def _load() -> ctypes.CDLL:
     lib.srigl_condense.argtypes = [vp, ctypes.c_int, vp, i32, i32, i32, i32, vp, vp, vp, vp, vp, sz, vp, sz, vp, vp]
     lib.srigl_condense_static.restype = ctypes.c_int
     lib.srigl_condense_static.argtypes = [vp, ctypes.c_int, vp, i32, i32, i32, i32, vp, vp, vp, vp, vp, sz, vp, vp]
+    lib.srigl_condense_count_bytes.restype = sz
+    lib.srigl_condense_count_bytes.argtypes = [i32, i32]
+    lib.srigl_condense_count.restype = ctypes.c_int
+    lib.srigl_condense_count.argtypes = [vp, i32, i32, i32, vp, sz, vp, sz, vp]
+    lib.srigl_condense_counted.restype = i32
+    lib.srigl_condense_counted.argtypes = [vp, i32, i32, i32, ctypes.POINTER(i32), vp]
+    lib.srigl_condense_write.restype = ctypes.c_int
+    lib.srigl_condense_write.argtypes = [vp, ctypes.c_int, vp, i32, i32, i32, i32, vp, vp, vp, vp, vp, sz, vp, sz, vp, vp]
     lib.srigl_packed_bytes.restype = sz
     lib.srigl_packed_bytes.argtypes = [i32, i32, i32, ctypes.c_int]
     lib.srigl_pack_terms.restype = ctypes.c_int

@@ -9,7 +9,11 @@
 // come from ballots and prefix popcounts (no atomics).
 #include "srigl_internal.h"
 
+#include <algorithm>
+#include <atomic>
+#include <cstring>
 #include <mutex>
+#include <type_traits>
 
 // Scratch of srigl_condense_static (the condense call for callers that cannot allocate): the rows' bits that srigl_condense
 // keeps in its workspace argument.  One copy per GPU, held until the process ends.  The name is a host-side
@@ -217,6 +221,65 @@ __global__ __launch_bounds__(kFlagRows* kWave) void k_row_flags(const uint8_t* _
     }
 }
 
+// The same for a caller that adds the rows up itself: a workgroup goes through `groups` groups of 32 rows, two rows to a wavefront, and leaves a word in host
+// memory, how many of its rows are stored and bad and the first bad one, beside a mark.  Every word is a write of its own over the bus, 20 to 30 ns at its end (with one
+// for every eight rows 384 of them took 7 us on 768 -> 3072), so that there are at most kCountWords.
+constexpr unsigned long long kCounted = 1ull << 63;
+constexpr int kCountWords = 128, kCountRows = 32, kCountWaves = 16;
+__global__ __launch_bounds__(kCountWaves* kWave) void k_row_counts(const uint8_t* __restrict__ mask, int n_rows, int d_in, int K, int groups,
+                                                                 uint32_t* __restrict__ stored, uint32_t* __restrict__ bad,
+                                                                 unsigned long long* __restrict__ to_host) {
+    constexpr int ROWS = kCountRows / kCountWaves, AHEAD = 4;   // rows of a wavefront; loads of each in flight
+    __shared__ int cnt[2][kCountRows];
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x >> 6;
+    unsigned n_stored = 0, n_bad = 0, first_bad = 0;
+    for (int g = 0; g < groups; ++g) {
+        const int group = blockIdx.x * groups + g, r0 = group * kCountRows + wv * ROWS;
+        if (group * kCountRows >= n_rows) break;
+        uint32_t c[ROWS] = {};
+        if (d_in >= kMaskCols) {
+            for (int col0 = 0; col0 < d_in; col0 += AHEAD * kWave * kMaskCols) {
+                MaskPiece p[ROWS][AHEAD];
+#pragma unroll
+                for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u)
+                        if (r0 + i < n_rows && col0 + u * kWave * kMaskCols < d_in)
+                            p[i][u] = load_piece(mask + (size_t)(r0 + i) * d_in, col0 + (u * kWave + lane) * kMaskCols, d_in);
+#pragma unroll
+                for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u)
+                        if (r0 + i < n_rows && col0 + u * kWave * kMaskCols < d_in) c[i] += __popc(kept_bits(p[i][u]));
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i)
+                if (r0 + i < n_rows) c[i] = __popc(kept_bits_short(mask + (size_t)(r0 + i) * d_in, lane, d_in));
+        }
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) {
+            const uint32_t n = wave_prefix(c[i]);
+            if (lane == kWave - 1) cnt[g & 1][wv * ROWS + i] = (int)n;
+        }
+        __syncthreads();   // (two places in turn: one barrier)
+        if (threadIdx.x < kWave) {
+            const int n = lane < kCountRows ? cnt[g & 1][lane] : 0;
+            const uint32_t is_stored = (uint32_t)__ballot(n > 0 && n == K), is_bad = (uint32_t)__ballot(n != 0 && n != K);
+            if (lane == 0) {
+                stored[group] = is_stored;
+                bad[group] = is_bad;
+            }
+            if (is_bad && n_bad == 0) first_bad = g * kCountRows + __builtin_ctz(is_bad);
+            n_stored += __popc(is_stored);
+            n_bad += __popc(is_bad);
+        }
+    }
+    if (threadIdx.x == 0)
+        __hip_atomic_store(&to_host[blockIdx.x], kCounted | (unsigned long long)first_bad << 42 | (unsigned long long)n_bad << 21 | n_stored, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // One wavefront per row: ordered stream compaction of the kept columns.  T = bit container of one weight (uint32_t for fp32,
 // uint16_t for bf16).  The row's kept columns are listed in LDS first (a lane's columns go to consecutive places behind those
 // of the lanes below it), then the lanes take the list's entries in turn, so that idx, W_c, the streaming copy (see
@@ -224,7 +287,7 @@ __global__ __launch_bounds__(kFlagRows* kWave) void k_row_flags(const uint8_t* _
 // gather all run over consecutive terms: three store instructions per 64 terms, where a lane storing its own columns issued
 // three per column position.  What bounds it: the mask a second time and the 128-byte lines of W that hold a kept weight (at
 // 5 % density nearly all of W).  4096 x 16384 bf16, 20 % of the rows ablated: 161 us for the whole call on the GPU before.
-// Workgroup 0 also writes the report.
+// Workgroup 0 also writes the report, if there is one to write.
 template <typename T>
 __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_compact_rows(const T* __restrict__ W, const uint8_t* __restrict__ mask,
                                                                      int d_out, int d_in, int K, int cap_rows,
@@ -256,7 +319,7 @@ __global__ __launch_bounds__(kRowsPerBlock* kWave) void k_compact_rows(const T* 
     auto stored_byte = [&](int r) { return (r >> 3) == (row0 >> 3) ? own_byte : (uint32_t)stored[r >> 3]; };
 
     // bits of the rows [0, row0); workgroup 0 counts all rows, and the bad ones, for the report
-    const bool reports = blockIdx.x == 0;
+    const bool reports = blockIdx.x == 0 && report != nullptr;
     const int upto = reports ? n_words : (row0 + 31) / 32;
     int below = 0, n_bad = 0, first_bad = 0x7fffffff;
     for (int w = tid; w < upto; w += kRowsPerBlock * kWave) {
@@ -447,41 +510,121 @@ srigl_status srigl_check_fanin(const uint8_t* mask, const int32_t* idx, int32_t 
     return hip_ok(hipGetLastError());
 }
 
-static srigl_status condense_core(const void* W, srigl_dtype w_dtype, const uint8_t* mask, int32_t d_out, int32_t d_in, int32_t K,
-                                  int32_t cap_rows, void* W_c, int32_t* idx, int32_t* active, uint16_t* seg, void* packed,
-                                  size_t packed_bytes, void* workspace, srigl_report* report_dev, hipStream_t st) {
-    if (d_out < 0 || d_in < 0 || K < 0 || K > d_in || cap_rows < 0 || report_dev == nullptr) return SRIGL_ERR_INVALID_ARG;
+// What both launches refuse before anything runs.
+static srigl_status check_condense(const void* W, srigl_dtype w_dtype, const uint8_t* mask, int32_t d_out, int32_t d_in, int32_t K, int32_t cap_rows,
+                                   const void* W_c, const int32_t* idx, const int32_t* active, const uint16_t* seg, const void* packed,
+                                   size_t packed_bytes, const void* workspace) {
+    if (d_out < 0 || d_in < 0 || K < 0 || K > d_in || cap_rows < 0) return SRIGL_ERR_INVALID_ARG;
     if (w_dtype != SRIGL_F32 && w_dtype != SRIGL_BF16) return SRIGL_ERR_INVALID_ARG;
     if (d_out > 0 && d_in > 0 && (W == nullptr || mask == nullptr)) return SRIGL_ERR_INVALID_ARG;
     if (cap_rows > 0 && (active == nullptr || (K > 0 && (W_c == nullptr || idx == nullptr)))) return SRIGL_ERR_INVALID_ARG;
     if (seg && K > 65535) return SRIGL_ERR_UNSUPPORTED;
     if (d_out > 0 && workspace == nullptr) return SRIGL_ERR_INVALID_ARG;
-    const PackedLayout pl = packed_layout(K, d_in, w_dtype == SRIGL_BF16);
     if (packed) {
         if (reinterpret_cast<uintptr_t>(packed) % 16 != 0) return SRIGL_ERR_INVALID_ARG;
         if (packed_bytes < srigl_packed_bytes(cap_rows, K, d_in, w_dtype)) return SRIGL_ERR_CAPACITY;
     }
-    // two bits per row in the workspace (8 bytes per row of room)
-    uint8_t* stored = static_cast<uint8_t*>(workspace);
-    uint8_t* bad = stored ? stored + (size_t)(d_out + 127) / 128 * 16 : nullptr;
-    const int flag_blocks = (d_out + kFlagRows - 1) / kFlagRows;
-    if (d_out > 0) hipLaunchKernelGGL(k_row_flags, dim3(flag_blocks), dim3(kFlagRows * kWave), 0, st, mask, d_out, d_in, K, stored, bad);
+    return SRIGL_OK;
+}
+
+// two bits per row in the workspace (8 bytes per row of room)
+static uint8_t* bad_bits(uint8_t* stored, int32_t d_out) { return stored ? stored + (size_t)(d_out + 127) / 128 * 16 : nullptr; }
+
+// How the rows are shared out among k_row_counts' workgroups: groups of 32 to a workgroup, workgroups.
+struct CountShape { int groups, words; };
+static CountShape count_shape(int32_t d_out) {
+    const int all = (d_out + kCountRows - 1) / kCountRows, groups = (all + kCountWords - 1) / kCountWords;
+    return {groups, groups ? (all + groups - 1) / groups : 0};
+}
+
+static void launch_flags(const uint8_t* mask, int32_t d_out, int32_t d_in, int32_t K, void* workspace, unsigned long long* to_host, hipStream_t st) {
+    uint8_t* const stored = static_cast<uint8_t*>(workspace);
+    uint8_t* const bad = bad_bits(stored, d_out);
+    if (d_out <= 0) return;
+    if (to_host) {
+        const CountShape c = count_shape(d_out);
+        hipLaunchKernelGGL(k_row_counts, dim3((unsigned)c.words), dim3(kCountWaves * kWave), 0, st, mask, d_out, d_in, K, c.groups,
+                           reinterpret_cast<uint32_t*>(stored), reinterpret_cast<uint32_t*>(bad), to_host);
+    } else {
+        hipLaunchKernelGGL(k_row_flags, dim3((unsigned)((d_out + kFlagRows - 1) / kFlagRows)), dim3(kFlagRows * kWave), 0, st, mask, d_out, d_in, K, stored, bad);
+    }
+}
+
+static void launch_compact(const void* W, srigl_dtype w_dtype, const uint8_t* mask, int32_t d_out, int32_t d_in, int32_t K, int32_t cap_rows, void* W_c,
+                           int32_t* idx, int32_t* active, uint16_t* seg, void* packed, void* workspace, srigl_report* report, hipStream_t st) {
+    const PackedLayout pl = packed_layout(K, d_in, w_dtype == SRIGL_BF16);
+    const uint8_t* stored = static_cast<const uint8_t*>(workspace);
+    const uint8_t* bad = bad_bits(static_cast<uint8_t*>(workspace), d_out);
     // one row per wavefront; layers of more than 131072 rows several, so that the bits every workgroup reads stay a small part
     int rows_per_block = kRowsPerBlock;
     while ((d_out + rows_per_block - 1) / rows_per_block > 32768) rows_per_block *= 2;
     const int blocks = d_out > 0 ? (d_out + rows_per_block - 1) / rows_per_block : 1;   // (no rows: workgroup 0 writes the report)
     const int list_cap = (K < kBatchCols ? K : kBatchCols) + 1;
     const size_t lds = sizeof(uint16_t) * kRowsPerBlock * (size_t)list_cap;
-    const int ss = srigl_seg_stride(d_in);
-    if (w_dtype == SRIGL_F32)
-        hipLaunchKernelGGL(k_compact_rows<uint32_t>, dim3(blocks), dim3(kRowsPerBlock * kWave), lds, st, static_cast<const uint32_t*>(W), mask, d_out,
-                           d_in, K, cap_rows, stored, bad, static_cast<uint32_t*>(W_c), idx, active, seg, ss,
-                           static_cast<unsigned char*>(packed), pl, rows_per_block, list_cap, report_dev);
-    else
-        hipLaunchKernelGGL(k_compact_rows<uint16_t>, dim3(blocks), dim3(kRowsPerBlock * kWave), lds, st, static_cast<const uint16_t*>(W), mask, d_out,
-                           d_in, K, cap_rows, stored, bad, static_cast<uint16_t*>(W_c), idx, active, seg, ss,
-                           static_cast<unsigned char*>(packed), pl, rows_per_block, list_cap, report_dev);
+    auto launch = [&](auto kern, const auto* weights, auto* out) {
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(kRowsPerBlock * kWave), lds, st, weights, mask, d_out, d_in, K, cap_rows, stored, bad, out, idx, active,
+                           seg, srigl_seg_stride(d_in), static_cast<unsigned char*>(packed), pl, rows_per_block, list_cap, report);
+    };
+    if (w_dtype == SRIGL_F32) launch(k_compact_rows<uint32_t>, static_cast<const uint32_t*>(W), static_cast<uint32_t*>(W_c));
+    else launch(k_compact_rows<uint16_t>, static_cast<const uint16_t*>(W), static_cast<uint16_t*>(W_c));
+}
+
+static srigl_status condense_core(const void* W, srigl_dtype w_dtype, const uint8_t* mask, int32_t d_out, int32_t d_in, int32_t K,
+                                  int32_t cap_rows, void* W_c, int32_t* idx, int32_t* active, uint16_t* seg, void* packed,
+                                  size_t packed_bytes, void* workspace, srigl_report* report_dev, hipStream_t st) {
+    if (report_dev == nullptr) return SRIGL_ERR_INVALID_ARG;
+    if (const srigl_status rc = check_condense(W, w_dtype, mask, d_out, d_in, K, cap_rows, W_c, idx, active, seg, packed, packed_bytes, workspace)) return rc;
+    launch_flags(mask, d_out, d_in, K, workspace, nullptr, st);
+    launch_compact(W, w_dtype, mask, d_out, d_in, K, cap_rows, W_c, idx, active, seg, packed, workspace, report_dev, st);
     return hip_ok(hipGetLastError());
+}
+
+// Layers up to 8 M elements: beyond, the launches on the GPU take longer than the host's part of a call, which is what the counts shorten, and 128 workgroups
+// no longer read the mask as fast as it comes.  2^20 rows: the fields of a word.
+size_t srigl_condense_count_bytes(int32_t d_out, int32_t d_in) {
+    return d_out > 0 && d_in > 0 && d_out <= 1 << 20 && (long long)d_out * d_in <= 8 << 20 ? count_shape(d_out).words * sizeof(unsigned long long) : 0;
+}
+
+srigl_status srigl_condense_count(const uint8_t* mask, int32_t d_out, int32_t d_in, int32_t K, void* workspace, size_t workspace_bytes, void* counts,
+                                  size_t counts_bytes, void* stream) {
+    if (d_out < 0 || d_in < 0 || K < 0 || K > d_in || (d_out > 0 && d_in > 0 && mask == nullptr)) return SRIGL_ERR_INVALID_ARG;
+    if (d_out > 0 && (workspace == nullptr || reinterpret_cast<uintptr_t>(counts) % 8 != 0)) return SRIGL_ERR_INVALID_ARG;
+    const size_t need = srigl_condense_count_bytes(d_out, d_in);
+    if (workspace_bytes < srigl_workspace_bytes(d_out) || (counts && counts_bytes < need)) return SRIGL_ERR_CAPACITY;
+    if (counts && need == 0) return SRIGL_ERR_UNSUPPORTED;
+    if (counts) std::memset(counts, 0, need);
+    std::atomic_thread_fence(std::memory_order_release);
+    launch_flags(mask, d_out, d_in, K, workspace, static_cast<unsigned long long*>(counts), static_cast<hipStream_t>(stream));
+    return hip_ok(hipGetLastError());
+}
+
+srigl_status srigl_condense_write(const void* W, srigl_dtype w_dtype, const uint8_t* mask, int32_t d_out, int32_t d_in, int32_t K, int32_t cap_rows,
+                                  void* W_c, int32_t* idx, int32_t* active, uint16_t* seg, void* packed, size_t packed_bytes, void* workspace,
+                                  size_t workspace_bytes, srigl_report* report, void* stream) {
+    if (d_out >= 0 && workspace_bytes < srigl_workspace_bytes(d_out)) return SRIGL_ERR_CAPACITY;
+    if (const srigl_status rc = check_condense(W, w_dtype, mask, d_out, d_in, K, cap_rows, W_c, idx, active, seg, packed, packed_bytes, workspace)) return rc;
+    launch_compact(W, w_dtype, mask, d_out, d_in, K, cap_rows, W_c, idx, active, seg, packed, workspace, report, static_cast<hipStream_t>(stream));
+    return hip_ok(hipGetLastError());
+}
+
+int32_t srigl_condense_counted(const void* counts, int32_t d_out, int32_t K, int32_t cap_rows, int32_t* from, srigl_report* report) {
+    const unsigned long long* const words = static_cast<const unsigned long long*>(counts);
+    const CountShape c = count_shape(d_out);
+    for (; *from < c.words; ++*from) {
+        const unsigned long long w = __atomic_load_n(&words[*from], __ATOMIC_ACQUIRE);
+        if ((w & kCounted) == 0) return 0;
+        if (*from == 0) {
+            *report = srigl_report{};
+            report->first_bad_row = -1;
+        }
+        const int wrong = (int)((w >> 21) & 0x1fffff);
+        report->n_active += (int)(w & 0x1fffff);
+        report->n_bad_rows += wrong;
+        if (wrong && report->first_bad_row < 0) report->first_bad_row = *from * c.groups * kCountRows + (int)((w >> 42) & 0x1fffff);
+    }
+    report->K = K;
+    report->status = report->n_bad_rows > 0 ? SRIGL_ERR_FANIN : report->n_active > cap_rows ? SRIGL_ERR_CAPACITY : SRIGL_OK;
+    return 1;
 }
 
 srigl_status srigl_condense(const void* W, srigl_dtype w_dtype, const uint8_t* mask, int32_t d_out,

@@ -1,0 +1,65 @@
+"""condense_layer counts its rows from host memory (srigl_condense_count / _counted / _write): sizes at the edges of a group of 32 rows and of what 128 workgroups
+share, against the oracle bit for bit; rows that are wrong in any group; the size from which the second launch's report is read."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth_inputs as si
+from gpu_util import dev, host, oracle_seg
+from paper_2305_02299_amd import binding as B_
+from paper_2305_02299_amd import condense_layer
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d_in,d_out,K,abl,dtype", [
+    (5, 1, 2, 0.0, "f32"), (15, 33, 4, 0.3, "bf16"), (16, 31, 3, 0.0, "f32"), (17, 32, 5, 0.5, "bf16"), (300, 97, 30, 0.9, "f32"),
+    (96, 4096, 9, 0.2, "bf16"), (96, 4097, 9, 0.2, "f32"), (64, 12345, 7, 0.45, "f32"),        # one, two and four groups to a workgroup
+    (4100, 70, 40, 0.1, "f32"), (9000, 40, 900, 0.0, "bf16"),                                  # rows of more than one turn of loads
+    (2048, 4100, 20, 0.1, "bf16"),                                                             # beyond 8 M elements: no counts
+])
+def test_condense_layer_bit_exact(d_in, d_out, K, abl, dtype):
+    L = si.make_layer(d_in, d_out, K, 1, ablate_frac=abl, dtype=dtype, seed=7 * d_out + d_in)
+    W = L.W_bf16 if dtype == "bf16" else L.W
+    W_c, idx, active = oracle.condense(W, L.mask, K)
+    assert (B_.lib.srigl_condense_count_bytes(d_out, d_in) > 0) == (d_out * d_in <= 8 << 20)
+    for _ in range(2):
+        layer = condense_layer(dev(W), dev(L.mask), K)
+        n = len(active)
+        assert layer.n_active == n and (layer.active is None) == (n == d_out)
+        assert np.array_equal(host(layer.idx), idx) and np.array_equal(host(layer.W_c), W_c)
+        assert n == d_out or np.array_equal(host(layer.active), active)
+        assert n == 0 or np.array_equal(host(layer.seg), oracle_seg(idx, d_in))
+        assert n == 0 or np.array_equal(host(layer.packed).reshape(n, -1), oracle.pack_terms(W_c, idx, d_in))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d_out,wrong", [(40, [0]), (40, [39]), (5000, [31, 32]), (5000, [64, 4999]), (5000, [4963])])
+def test_wrong_rows_are_named(d_out, wrong):
+    L = si.make_layer(48, d_out, 6, 1, seed=d_out)
+    for r in wrong:
+        L.mask[r, int(np.flatnonzero(L.mask[r] == 0)[0])] = 1
+    with pytest.raises(B_.SriglError, match="first bad row %d\\)" % wrong[0]) as e:
+        condense_layer(dev(L.W), dev(L.mask), 6)
+    assert e.value.status == B_.ERR_FANIN
+    assert condense_layer(dev(L.W), dev(np.zeros_like(L.mask)), 6).n_active == 0
+
+
+def test_counts_of_several_words():
+    """The host's side on its own: missing words stop it, the fields add up, the report's rows are the layer's."""
+    d_out, mark = 32 * 128 * 2 - 5, 1 << 63                  # 128 words of 64 rows, two groups each
+    words = np.zeros(128, np.uint64)
+    at, report = ctypes.c_int32(0), (ctypes.c_int32 * 8)()
+    ask = lambda cap: B_.lib.srigl_condense_counted(words.ctypes.data, d_out, 6, cap, ctypes.byref(at), report)   # noqa: E731
+    assert ask(d_out) == 0 and at.value == 0
+    words[:100] = mark | 60
+    words[40] = mark | 33 << 42 | 2 << 21 | 58               # two wrong rows, the first its 34th
+    assert ask(d_out) == 0 and at.value == 100
+    words[100:] = mark | 1
+    assert ask(d_out) == 1 and list(report)[:5] == [6, 99 * 60 + 58 + 28, 2, 40 * 64 + 33, B_.ERR_FANIN]
+    at.value, words[40] = 0, mark | 60
+    assert ask(6027) == 1 and list(report)[:5] == [6, 6028, 0, -1, B_.ERR_CAPACITY]
+    at.value = 0
+    assert ask(6028) == 1 and list(report)[:5] == [6, 6028, 0, -1, B_.OK]
