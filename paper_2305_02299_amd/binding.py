@@ -22,7 +22,7 @@ REPR_CONDENSED, REPR_STRUCTURED = 0, 1
 ACT_NONE, ACT_RELU, ACT_GELU = 0, 1, 2
 FWD_AUTO, FWD_GENERIC, FWD_KLANE, FWD_ROWLANE, FWD_ROWLOOP = range(5)
 TILE_AUTO, TILE_256x256, TILE_256x256_H, TILE_256x128_W4, TILE_256x128, TILE_128x128, TILE_64x64 = range(7)
-TILE_256x192 = 7   # bf16, the library's own choice only
+TILE_256x192, TILE_192x192, TILE_128x96, TILE_64x128 = range(7, 11)   # bf16, the library's own choice only
 BLOCKED_64, BLOCKED_128, BLOCKED_256, BLOCKED_192 = 1, 2, 3, 4
 TILES = {"256x256": TILE_256x256, "256x256_h": TILE_256x256_H, "256x128_w4": TILE_256x128_W4, "256x128": TILE_256x128,
          "128x128": TILE_128x128, "64x64": TILE_64x64}
@@ -380,7 +380,7 @@ def srigl_structured_split_plan(B, d_in, n_active, d_out, dtype_code):
 
 
 def srigl_structured_tile_query(B, d_in, n_active, d_out, dtype_code, may_split=False) -> int:
-    """Tile of the library's own choice (TILE_* codes, or TILE_256x192, which only that choice takes), in one part or as srigl_structured_split_plan cuts d_in."""
+    """Tile of the library's own choice (TILE_* codes, those from TILE_256x192 on are taken by that choice only), in one part or as srigl_structured_split_plan cuts d_in."""
     return int(lib.srigl_structured_tile_query(int(B), int(d_in), int(n_active), int(d_out), int(dtype_code), int(bool(may_split))))
 
 

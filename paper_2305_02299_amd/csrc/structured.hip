@@ -415,7 +415,13 @@ static srigl_gemm_tile choose_tile(int B, int n_active, bool f32) {
 // products of up to 5 M results (at worst 18 %) and 1.4 % (22 %) on 311 larger ones; 0.5 (23) and 2.7 % (28) with constants fitted to calls from
 // the host, 13 % too high and most on the smallest, which also left the condensed form calls that the product does faster (4096 -> 4096, K = 410 at batch 64: 17.7 us
 // against 13.9).  (256 x 192 tiles: 9000 rows at batch 2048, d_in 4096, 155 us, 157 in 256 x 128 and 180 in 256 x 256; 5023 at 1696, 1136, 35.7, 48 and 36.)
-constexpr int kTile256x192 = 7;   // 8 wavefronts of 64x96, 2 LDS stages of 128 bytes; only the library's choice takes it
+// The last three shapes are for rounds that the others would leave part empty: 192 x 192 has nine sixteenths of a 256 x 256 tile's work to a round, and 4 wavefronts of
+// 96 x 96 read fewer fragments per multiplication than 8 of 128 x 64 (13108 rows at batch 2048, d_in 4096, 1.6 rounds of 256 x 256: 205 us -> 197 on one card, 207.7 -> 204.3 on another, which the power of the matrix units limits; 11440 at 1500, 89 -> 68); a
+// layer whose 128 x 128 tiles fill three quarters of the chip or a little more than all of it goes into 128 x 96 or 64 x 128 (2335 at 1024, d_in 576, 16.9 -> 13.1; 9012 at 256, 768,
+// 18.5 -> 14.6).  Fitted on 918 products beside the time of the shape taken before, plus 6 %: it takes that much of a promise for one of them, in one part
+// only (cut into parts they were level or up to 19 % behind).  Of 105 out of 1500 random products that came to another shape 85 in one part are 1.11 times faster, the slowest 9 % behind.
+// Shapes that only the library's choice takes: 8 wavefronts of 64x96, 2 LDS stages of 128 bytes; 4 of 96x96, 3 stages; 4 of 32x96, 4; 4 of 32x64, 4
+constexpr int kTile256x192 = 7, kTile192x192 = 8, kTile128x96 = 9, kTile64x128 = 10;
 struct Bf16TileModel { int tile, bm, bn; float fixed, round, per_k, per_k_full, y, ablated, second, part; };
 static const Bf16TileModel kBf16TileModels[] = {
     {SRIGL_TILE_256x256, 256, 256, 0.71f, 6.96f, 15.62f, 4.62f, 0.69f, 2.06f, 1.71f, 1.82f},
@@ -423,6 +429,9 @@ static const Bf16TileModel kBf16TileModels[] = {
     {SRIGL_TILE_256x128, 256, 128, 1.62f, 4.69f, 8.47f, 2.07f, 0.82f, 1.95f, 1.31f, 2.07f},
     {SRIGL_TILE_128x128, 128, 128, 3.07f, 2.96f, 5.82f, 1.18f, 0.87f, 1.84f, 1.52f, 2.42f},
     {SRIGL_TILE_64x64, 64, 64, 2.76f, 1.07f, 5.60f, 0.0f, 1.22f, 1.34f, 1.46f, 3.18f},
+    {kTile192x192, 192, 192, 3.52f, 7.48f, 9.65f, 1.84f, 0.75f, 1.39f, 0.0f, 0.0f},
+    {kTile128x96, 128, 96, 1.59f, 5.88f, 4.85f, 1.38f, 0.61f, 1.27f, 0.0f, 0.0f},
+    {kTile64x128, 64, 128, 2.35f, 2.71f, 4.81f, 0.30f, 1.31f, 1.64f, 0.0f, 0.0f},
 };
 // Time (us) of the product in a shape and `splits` parts.
 static double bf16_tiles_us(const Bf16TileModel& m, int splits, int B, int d_in, int n_active, int d_out) {
@@ -430,7 +439,7 @@ static double bf16_tiles_us(const Bf16TileModel& m, int splits, int B, int d_in,
     const long long tiles = (long long)((B + m.bm - 1) / m.bm) * ((n_active + m.bn - 1) / m.bn);
     const double groups = (double)(splits > 1 ? (tiles + kXcds - 1) / kXcds * kXcds * splits : tiles);
     const double more = m.y * 1e-6 * B * d_out + (splits > 1 ? m.second + m.part * 1e-6 * splits * B * (double)n_active : n_active < d_out ? m.ablated : 0.0);
-    if (m.bm == 64) return more + (groups <= 256 ? 4.17 + 3.67 * d : m.fixed + std::ceil(groups / 512) * (m.round + m.per_k * d));
+    if (m.bn == 64) return more + (groups <= 256 ? 4.17 + 3.67 * d : m.fixed + std::ceil(groups / 512) * (m.round + m.per_k * d));
     return more + m.fixed + std::ceil(groups / 256) * (m.round + m.per_k * d) + groups / 256 * m.per_k_full * d;
 }
 
@@ -444,7 +453,7 @@ struct GemmChoice { int tile, splits; double us; };
 static int parts_of(int B, int n_active, int d_in, bool f32, int bm, int bn) {
     const int stages = (d_in * (f32 ? 4 : 2) + kSlabBytes - 1) / kSlabBytes;
     const long long tiles = (long long)((B + bm - 1) / bm) * ((n_active + bn - 1) / bn), padded = (tiles + kXcds - 1) / kXcds * kXcds;
-    const long long wg_cap = bm == 64 ? 480 : 256;
+    const long long wg_cap = bm == 64 && bn == 64 ? 480 : 256;
     const int cap = std::max(1, std::min(stages / 4, kMaxSplits));
     return padded >= wg_cap ? 1 : std::min((int)(wg_cap / padded), cap);
 }
@@ -477,11 +486,11 @@ static GemmChoice choose_f32(int B, int n_active, int d_in, int d_out, bool may_
 static GemmChoice choose_bf16(int B, int n_active, int d_in, int d_out, bool may_split) {
     GemmChoice best{};
     for (const Bf16TileModel& m : kBf16TileModels) {
-        if (m.bm > 64 && (long long)m.bm * d_in * 2 >= (1ll << 31)) continue;   // launch_gemm's byte offsets
+        if (m.bn > 64 && (long long)std::max(m.bm, m.bn) * d_in * 2 >= (1ll << 31)) continue;   // launch_gemm's byte offsets
         const double one = bf16_tiles_us(m, 1, B, d_in, n_active, d_out);
         if (best.tile == 0 || one < best.us) best = {m.tile, 1, one};
         const int s = may_split ? parts_of(B, n_active, d_in, false, m.bm, m.bn) : 1;
-        if (s == 1 || m.tile == kTile256x192) continue;
+        if (s == 1 || m.tile >= kTile256x192) continue;
         const double several = bf16_tiles_us(m, s, B, d_in, n_active, d_out);
         if (several < best.us) best = {m.tile, s, several};
     }
@@ -499,6 +508,9 @@ template <typename T>
 static srigl_status launch_structured(int tile, const void* x, int B, int d_in, const void* Wd, const int32_t* active, int n_active,
                                       const float* bias, int d_out, float* y, int splits, float* part, hipStream_t st) {
     if constexpr (sizeof(T) == 2) {
+        if (tile == kTile192x192) return launch_gemm<T, 192, 192, 2, 2, 3, 128>(x, B, d_in, Wd, active, n_active, bias, d_out, y, splits, part, st);
+        if (tile == kTile128x96) return launch_gemm<T, 128, 96, 4, 1, 4, 128>(x, B, d_in, Wd, active, n_active, bias, d_out, y, splits, part, st);
+        if (tile == kTile64x128) return launch_gemm<T, 64, 128, 2, 2, 4, 128>(x, B, d_in, Wd, active, n_active, bias, d_out, y, splits, part, st);
         if (tile == kTile256x192) return launch_gemm<T, 256, 192, 4, 2, 2, 128>(x, B, d_in, Wd, active, n_active, bias, d_out, y, splits, part, st);
     }
     switch (tile) {

@@ -1,0 +1,35 @@
+"""The tile shapes that only the library's own choice takes (192 x 192, 128 x 96, 64 x 128), against float64, at sizes where batch rows, stored
+neurons and depth end inside a tile, with and without ablated neurons."""
+import pytest
+import torch
+
+from paper_2305_02299_amd import binding as B_
+
+pytestmark = pytest.mark.gpu
+GUARD = 1024
+
+
+@pytest.mark.parametrize("B,n,d_in,ablated,tile", [
+    (518, 11284, 616, 134, B_.TILE_192x192), (683, 10997, 976, 0, B_.TILE_192x192),
+    (1014, 2980, 120, 107, B_.TILE_128x96), (1125, 2651, 152, 199, B_.TILE_128x96), (348, 6784, 480, 21, B_.TILE_128x96), (1104, 2017, 672, 147, B_.TILE_128x96),
+    (66, 8573, 2096, 0, B_.TILE_64x128), (1152, 1754, 4088, 154, B_.TILE_64x128),
+])
+def test_shapes_of_the_library_choice(B, n, d_in, ablated, tile):
+    """Two orders of one fp32 sum of d_in exact products differ by at most d_in * 2^-23 of the sum of the magnitudes."""
+    d_out = n + ablated
+    assert B_.srigl_structured_tile_query(B, d_in, n, d_out, B_.BF16) == tile
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn(B, d_in, device="cuda", generator=g).bfloat16()
+    Wd = torch.randn(n, d_in, device="cuda", generator=g).bfloat16()
+    bias = torch.randn(d_out, device="cuda", generator=g)
+    active = torch.sort(torch.randperm(d_out, device="cuda", generator=g)[:n]).values
+    flat = torch.full((B * d_out + 2 * GUARD,), 777.0, device="cuda")
+    y = flat[GUARD:GUARD + B * d_out].view(B, d_out)
+    B_.srigl_structured_linear_fwd(x.view(torch.int16), B, d_in, Wd.view(torch.int16), active.int() if ablated else None, n, bias, d_out, y)
+    ref = bias.double().repeat(B, 1)
+    ref[:, active] += x.double() @ Wd.double().t()
+    bound = bias.abs().repeat(B, 1)
+    bound[:, active] += x.float().abs() @ Wd.float().abs().t()
+    worst = ((y - ref).abs() / (bound * (d_in + 1) * 2.0 ** -23)).max().item()
+    assert worst <= 1, worst
+    assert (flat[:GUARD] == 777.0).all() and (flat[GUARD + B * d_out:] == 777.0).all()
