@@ -60,12 +60,15 @@ __device__ __forceinline__ bool tile_of_workgroup(int id, int tiles_m, int tiles
 // ---- epilogue: a tile's sums to their columns of y ----
 // The columns of y that the tile at stored neuron n0 writes: its stored neurons and the ablated ones in front of them (behind the
 // last one too in the last tile) are one contiguous range.
-struct TileColumns { int lo, hi, stored, base; };   // base: where the windows begin, the columns' 128-byte line
-__device__ __forceinline__ TileColumns tile_columns(int n0, int bn, const int32_t* active, int n_active, int d_out) {
+struct TileColumns { int lo, hi, stored, base; };   // base: where the windows begin
+// A tile's first column lies anywhere with ablated neurons.  The windows begin at its 128-byte line of y where all rows of y have lines there and the tile's
+// rows take no more runs of `run` columns (a wavefront's stores of a row; 0: never) for it: 124 -> 6696 at batch 1270, whose rows begin anywhere, 20.9 us from the column and 22.2 from
+// the line; 384 -> 5120 with 3072 stored at batch 288 in 64 x 64 tiles, whose runs are two lines long, 8.0 and 8.4.
+__device__ __forceinline__ TileColumns tile_columns(int n0, int bn, const int32_t* active, int n_active, int d_out, int run) {
     const int cnt = min(bn, n_active - n0);
-    if (!active) return {n0, n0 + cnt - 1, cnt, n0 & ~31};
-    const int lo = max((n0 > 0) ? active[n0 - 1] + 1 : 0, 0);
-    return {lo, min((n0 + cnt == n_active) ? d_out - 1 : active[n0 + cnt - 1], d_out - 1), cnt, lo & ~31};
+    if (!active) return {n0, n0 + cnt - 1, cnt, n0};   // (tiles are multiples of 32 columns)
+    const int lo = max((n0 > 0) ? active[n0 - 1] + 1 : 0, 0), hi = min((n0 + cnt == n_active) ? d_out - 1 : active[n0 + cnt - 1], d_out - 1), line = lo & ~31;
+    return {lo, hi, cnt, run && d_out % 32 == 0 && (hi - line) / run == (hi - lo) / run ? line : lo};
 }
 
 // LDS of the epilogue: one 32-row part of each wavefront row's tile at a time, at the rows' final columns (a window of COLS of them;
@@ -74,6 +77,7 @@ __device__ __forceinline__ TileColumns tile_columns(int n0, int bn, const int32_
 template <int BN, int WGM>
 struct EpiLayout {
     static constexpr int COLS = BN >= 256 ? 512 : 256, ROWS = 32 * WGM, PITCH = COLS + 4;
+    static constexpr int LINE_RUN = BN >= 256 ? 256 : (BN >= 128 ? 128 : 0);   // for tile_columns
     static constexpr size_t TILE_BYTES = (size_t)ROWS * PITCH * 4, TABLE_BYTES = (size_t)BN * 4 + (size_t)COLS * 8;
     static constexpr size_t BYTES = TILE_BYTES + TABLE_BYTES;
 };
@@ -114,8 +118,8 @@ __device__ __forceinline__ void fill_table(unsigned char* at, int cc, const Tile
 // With that and the float4 rows a 768 -> 3072 layer in 256 x 256 tiles went from 36.4 to 32.3 us, 4096 -> 16384 at batch 2048 from 297 to
 // 279 in 128 x 128 tiles.  Narrow tiles put 2 or 4 rows into one LDS request (16 or 32 lanes each): with 64 lanes on a row 64 x 64
 // tiles took 11.5 us instead of 9.4 on 768 -> 3072 at batch 128.
-// The windows begin at a 128-byte line of y where its rows do (columns in front of the tile's own are left out): with ablated neurons a tile's first column
-// lies anywhere, and every store of a kilobyte then began and ended in part of a line, which streaming stores do not put together: 4096 -> 16384 with
+// The windows begin at a 128-byte line of y where that is of use (tile_columns; columns in front of the tile's own are left out): from a column inside of a
+// line on every store of a kilobyte then began and ended in part of a line, which streaming stores do not put together: 4096 -> 16384 with
 // 13108 stored at batch 2048 207 -> 201 us (condensed form 212 -> 208), 1024 -> 16384 with 8192 stored 73 -> 64.  (Plain stores: the first two 203 and 218.)
 // SPOILED: the tile's rows with a sum that is not finite get their bits set in `spoiled` (BM of them, in LDS); what has been written for
 // them is up to the caller to mend.

@@ -345,7 +345,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_structured_gemm(const T* __r
 
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // the re-issued last stages may still be landing in the ring
     __syncthreads();
-    store_tile<BM, BN, WGM, WGN, false>(smem, smem + EpiLayout<BN, WGM>::TILE_BYTES, false, acc, tile_columns(n0, BN, active, n_active, d_out), m0, n0, B,
+    store_tile<BM, BN, WGM, WGN, false>(smem, smem + EpiLayout<BN, WGM>::TILE_BYTES, false, acc, tile_columns(n0, BN, active, n_active, d_out, EpiLayout<BN, WGM>::LINE_RUN), m0, n0, B,
                                     active, bias, d_out, y, SRIGL_ACT_NONE, nullptr);
 }
 
