@@ -73,6 +73,7 @@ __global__ __launch_bounds__(256) void k_bias_broadcast(const float* __restrict_
 // first stages in LDS (fp32, row-major).
 // ------------------------------------------------------------------------------------------------
 constexpr int kKlaneTerms = 4;   // terms a lane keeps in flight per request
+constexpr int kKlaneThreads = 256;
 
 template <int RB, bool GATHER, typename XT, typename IT>
 __global__ __launch_bounds__(256) void k_fwd_klane(const XT* __restrict__ x, int B, int d_in, const XT* __restrict__ W_c,
@@ -84,7 +85,7 @@ __global__ __launch_bounds__(256) void k_fwd_klane(const XT* __restrict__ x, int
     const int tid = threadIdx.x;
     const int q = tid & (L - 1);                      // lane within the neuron's group
     const int grp = tid >> log2L;                     // group within the workgroup
-    const int groups = blockDim.x >> log2L;
+    const int groups = kKlaneThreads >> log2L;
     const int b0 = blockIdx.y * RB;
     const int n_slots = active ? n_active + 1 : n_active;
     const int s_begin = blockIdx.x * rows_per_wg;
@@ -97,13 +98,13 @@ __global__ __launch_bounds__(256) void k_fwd_klane(const XT* __restrict__ x, int
         // four loads per thread in flight before the first of them is converted and stored
 #pragma unroll
         for (int r = 0; r < RB; ++r)
-            for (int j0 = tid; j0 < d_in; j0 += 4 * (int)blockDim.x) {
+            for (int j0 = tid; j0 < d_in; j0 += 4 * kKlaneThreads) {
                 XT v[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = xrow[r][min(j0 + u * (int)blockDim.x, d_in - 1)];
+                for (int u = 0; u < 4; ++u) v[u] = xrow[r][min(j0 + u * kKlaneThreads, d_in - 1)];
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    if (j0 + u * (int)blockDim.x < d_in) xs[r * d_in + j0 + u * (int)blockDim.x] = to_f32<XT>(v[u]);
+                    if (j0 + u * kKlaneThreads < d_in) xs[r * d_in + j0 + u * kKlaneThreads] = to_f32<XT>(v[u]);
             }
         __syncthreads();
     }
@@ -199,7 +200,7 @@ __global__ __launch_bounds__(256) void k_fwd_klane_packed(const XT* __restrict__
     const int tid = threadIdx.x;
     const int q = tid & (L - 1);
     const int grp = tid >> log2L;
-    const int groups = blockDim.x >> log2L;
+    const int groups = kKlaneThreads >> log2L;
     const int b0 = blockIdx.y * RB;
     const int n_slots = active ? n_active + 1 : n_active;
     const int s_begin = blockIdx.x * rows_per_wg;
@@ -217,19 +218,19 @@ __global__ __launch_bounds__(256) void k_fwd_klane_packed(const XT* __restrict__
     PackedUnit<XT, UB> first;
     if (!GATHER) {
         XT v[RB][4];
-        const int j0 = tid;   // this thread's first column; the loop below strides by 4 * blockDim.x
+        const int j0 = tid;   // this thread's first column; the loop below strides by 4 * kKlaneThreads
 #pragma unroll
         for (int r = 0; r < RB; ++r)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[r][u] = xrow[r][min(j0 + u * (int)blockDim.x, d_in - 1)];
+            for (int u = 0; u < 4; ++u) v[r][u] = xrow[r][min(j0 + u * kKlaneThreads, d_in - 1)];
         first.load(unit_at(s_begin + grp, q));
 #pragma unroll
         for (int r = 0; r < RB; ++r)
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                if (j0 + u * (int)blockDim.x < d_in) xs[r * d_in + j0 + u * (int)blockDim.x] = to_f32<XT>(v[r][u]);
+                if (j0 + u * kKlaneThreads < d_in) xs[r * d_in + j0 + u * kKlaneThreads] = to_f32<XT>(v[r][u]);
         for (int r = 0; r < RB; ++r)
-            for (int j = tid + 4 * (int)blockDim.x; j < d_in; j += (int)blockDim.x) xs[r * d_in + j] = to_f32<XT>(xrow[r][j]);
+            for (int j = tid + 4 * kKlaneThreads; j < d_in; j += kKlaneThreads) xs[r * d_in + j] = to_f32<XT>(xrow[r][j]);
         __syncthreads();
     } else {
         first.load(unit_at(s_begin + grp, q));
@@ -351,7 +352,7 @@ static srigl_status launch_klane_t(const FwdArgs& a, int log2L, int rows_per_wg,
     const unsigned gx = (unsigned)((n_slots + rows_per_wg - 1) / rows_per_wg);
     const unsigned gy = (unsigned)((a.B + RB - 1) / RB);
     if (gy > 65535u) return SRIGL_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(256), lds, st, (const XT*)a.x, a.B, a.d_in, (const XT*)a.W_c, (const IT*)a.idx,
+    hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(kKlaneThreads), lds, st, (const XT*)a.x, a.B, a.d_in, (const XT*)a.W_c, (const IT*)a.idx,
                        a.active, a.n_active, a.K, a.bias, a.d_out, a.y, log2L, rows_per_wg, a.act);
     return hip_ok(hipGetLastError());
 }
@@ -367,7 +368,7 @@ static srigl_status launch_klane_packed_t(const FwdArgs& a, int log2L, int rows_
     const unsigned gx = (unsigned)((n_slots + rows_per_wg - 1) / rows_per_wg);
     const unsigned gy = (unsigned)((a.B + RB - 1) / RB);
     if (gy > 65535u) return SRIGL_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(256), lds, st, (const XT*)a.x, a.B, a.d_in, static_cast<const unsigned char*>(a.packed),
+    hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(kKlaneThreads), lds, st, (const XT*)a.x, a.B, a.d_in, static_cast<const unsigned char*>(a.packed),
                        (a.K + 3) / 4, a.active, a.n_active, a.K, a.bias, a.d_out, a.y, log2L, rows_per_wg, a.act);
     return hip_ok(hipGetLastError());
 }

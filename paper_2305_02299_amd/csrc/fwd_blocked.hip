@@ -175,8 +175,8 @@ struct BlockedArgs {
 // else (the gathering kernel: 0.85 ms); with every sum added up by one lane, term after term from memory, 1.3 ms and 23 ms.  (Rewritten
 // operands through the matrix cores once more, four passes, took 2.8 ms for either, and its registers 3 to 7 % of every call.)
 constexpr int kMendRows = 8, kMendAhead = 4;   // rows at a time; loads of 64 terms in flight, for two neurons
-__device__ __forceinline__ void mend_rows(const BlockedArgs& p, unsigned char* smem, int area, float* sums, const uint32_t* spoiled, int bm, int bn, int m0, int n0) {
-    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), waves = blockDim.x >> 6;
+__device__ __forceinline__ void mend_rows(const BlockedArgs& p, unsigned char* smem, int area, float* sums, const uint32_t* spoiled, int bm, int bn, int waves, int m0, int n0) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int stored = min(bn, p.n_active - n0), width = area / (2 * kMendRows) / 64 * 64;
     const int g = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);   // the row whose sum ends up in this lane
     for (int done = 0;; done += kMendRows) {
@@ -196,7 +196,7 @@ __device__ __forceinline__ void mend_rows(const BlockedArgs& p, unsigned char* s
         for (int c0 = 0; c0 < p.d_in; c0 += width) {
             const int cols = min(width, p.d_in - c0);
             __syncthreads();   // the run before has been read (at first: the tile)
-            for (int c = tid; c < cols; c += blockDim.x) {
+            for (int c = tid; c < cols; c += waves * kWave) {
                 uint32_t h[kMendRows];
 #pragma unroll
                 for (int q = 0; q < kMendRows; ++q) h[q] = p.x[(size_t)rows[q] * p.d_in + c0 + c];
@@ -506,7 +506,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
     if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)any) != 0, 0)) {
         constexpr int SUMS = BN * kMendRows * 4, AREA = (int)blocked_table_at<UA, BM, BN, WGM, WGN, CC>() - SUMS;
         wait_loads<0>();   // the stores above have reached memory; the function starts with a barrier
-        mend_rows(p, smem, AREA, reinterpret_cast<float*>(smem + AREA), spoiled, BM, BN, m0, n0);
+        mend_rows(p, smem, AREA, reinterpret_cast<float*>(smem + AREA), spoiled, BM, BN, WGM * WGN, m0, n0);
     }
 }
 

@@ -322,7 +322,7 @@ __global__ __launch_bounds__(rowlane_max_threads(R)) void k_fwd_rowlane(const XT
                                                       int n_active, int K, const float* __restrict__ bias, int d_out,
                                                       float* __restrict__ y, const uint16_t* __restrict__ seg, int seg_stride,
                                                       int C, int n_chunks, int n_btiles, int n_groups, int out_off, int act, int bt_major,
-                                                      const unsigned char* __restrict__ pk, int KS, unsigned div_magic, int spread) {
+                                                      const unsigned char* __restrict__ pk, int KS, unsigned div_magic, int spread, int nw) {
     extern __shared__ float lds[];   // x tile [C + 1][S]; afterwards out tile [BT][NG + 1]
     constexpr int LR = kWave / H;            // lanes per term slice
     constexpr int BT = LR * R;               // batch rows per tile
@@ -367,7 +367,6 @@ __global__ __launch_bounds__(rowlane_max_threads(R)) void k_fwd_rowlane(const XT
     const int tofs = H * (lane & (kBlock - 1)) + lane / LR;   // this lane's term inside a block
     const int lofs = H == 1 ? tofs : (lane & (kBlock * H - 1));   // the term this lane loads
     const int wv_id = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nw = blockDim.x >> 6;
     const int NG = nw * NPW;                 // stored rows (slots) per workgroup
     const int b0 = bt * BT;
     const int n_slots = active ? n_active + 1 : n_active;
@@ -536,7 +535,7 @@ __global__ __launch_bounds__(rowlane_max_threads(R)) void k_fwd_rowlane(const XT
         int* const place_row = keys + 256;                     // row of the workgroup per place (wavefront, its i-th row)
         int* const wave_lo = keys + 384;
         int* const wave_hi = keys + 400;
-        const int t = tid & 127, part = tid >> 7, n_parts = max((int)blockDim.x >> 7, 1);
+        const int t = tid & 127, part = tid >> 7, n_parts = max(nw >> 1, 1);
         if (lane < NPW) keys[wv_id * NPW + lane] = spread_key;
         if (tid < 128) ranks[tid] = 0;
         if (lane == 0) { wave_lo[wv_id] = w_lo; wave_hi[wv_id] = w_hi; }
@@ -585,7 +584,7 @@ __global__ __launch_bounds__(rowlane_max_threads(R)) void k_fwd_rowlane(const XT
         for (int p = 0; p < (MERGE ? 1 : KPRE); ++p)
             request_terms<XT, IT, PKB>(W_c, idx, pk, slot_of(i) * KS + p * TB, MERGE ? lane : lofs, t_last, rw[i][p], ri[i][p]);
     SRIGL_LOAD_BOUNDS()
-    for (int t = tid; t < S; t += blockDim.x) lds[C * S + t] = 0.0f;   // the all-zero column
+    for (int t = tid; t < S; t += nw * kWave) lds[C * S + t] = 0.0f;   // the all-zero column
     SRIGL_STAGE_STORE(0)
     __syncthreads();
 
@@ -692,7 +691,7 @@ __global__ __launch_bounds__(rowlane_max_threads(R)) void k_fwd_rowlane(const XT
         if (span > 0 && span <= kSpanCap && c0 >= 0) {
             int* const tab = reinterpret_cast<int*>(out + BT * OS);
             float* const bsp = reinterpret_cast<float*>(tab + kSpanCap);
-            for (int c = tid; c < span; c += blockDim.x) {
+            for (int c = tid; c < span; c += nw * kWave) {
                 tab[c] = -1;
                 bsp[c] = rl_bias_at(bias, c0 + c);
             }
@@ -764,7 +763,7 @@ static srigl_status launch_rowlane_f(const FwdArgs& a, const RowlanePlan& p, hip
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(p.NW * kWave), p.lds, st, (const XT*)a.x, a.B, a.d_in, (const XT*)a.W_c,
                        (const IT*)a.idx, a.active, a.n_active, a.K, a.bias, a.d_out, a.y, a.seg, a.seg_stride, p.C, p.n_chunks, p.n_btiles,
                        p.n_groups, p.out_off, a.act, p.bt_major, static_cast<const unsigned char*>(a.packed), PKB ? (a.K + 3) / 4 * 4 : a.K,
-                       rowlane_decode_multiplier(blocks, p.bt_major ? p.n_groups : p.n_btiles), p.spread);
+                       rowlane_decode_multiplier(blocks, p.bt_major ? p.n_groups : p.n_btiles), p.spread, p.NW);
     return hip_ok(hipGetLastError());
 }
 

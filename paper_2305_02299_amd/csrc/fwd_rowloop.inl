@@ -112,7 +112,7 @@ template <int GL, int RL, int ST, typename XT, typename IT>
 __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, int B, int d_in, const XT* __restrict__ W_c,
                                                       const IT* __restrict__ idx, const int32_t* __restrict__ active, int n_active,
                                                       int K, const float* __restrict__ bias, int d_out, float* __restrict__ y,
-                                                      int NG, int n_btiles, int n_groups, int out_off, int span_cap, int act, int bt_major) {
+                                                      int NG, int n_btiles, int n_groups, int out_off, int span_cap, int act, int bt_major, int nw) {
     extern __shared__ float lds[];   // x tile [C + 1][S]; result tile [BT][NG | 1]; bias [NG], or bias and column table [span_cap] each
     constexpr int BT = GL * RL;              // batch rows per tile
     constexpr int S = BT;                    // words from column to column
@@ -134,7 +134,6 @@ __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wv_id = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nw = blockDim.x >> 6;
     const int b0 = bt * BT;
     const int sg0 = g * NG;
     const int ng = min(NG, n_active - sg0);   // > 0: n_groups = ceil(n_active / NG)
@@ -198,7 +197,7 @@ __global__ __launch_bounds__(1024) void k_fwd_rowloop(const XT* __restrict__ x, 
     // takes the ablated columns up to d_out), the bias of that run and, per column of it, which row of the result tile holds
     // it, if any.  TP entries per thread wait in registers behind the tile's requests; what is beyond goes through a loop.
     constexpr int TP = 1;
-    const int nthreads = blockDim.x;
+    const int nthreads = nw * kWave;
     float* const out = lds + out_off;
     const int OS = NG | 1;                    // odd stride: conflict-free transposed writes
     float* const bsp = out + BT * OS;         // bias of the workgroup's columns
@@ -448,7 +447,7 @@ static srigl_status launch_rowloop_f(const FwdArgs& a, const RowloopPlan& p, hip
     const long long blocks = p.bt_major ? 8LL * ((p.n_btiles + 7) / 8) * p.n_groups : 8LL * ((p.n_groups + 7) / 8) * p.n_btiles;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(p.NW * kWave), p.lds, st, (const XT*)a.x, a.B, a.d_in, (const XT*)a.W_c,
                        (const IT*)a.idx, a.active, a.n_active, a.K, a.bias, a.d_out, a.y, p.NG, p.n_btiles, p.n_groups, p.out_off,
-                       p.span_cap, a.act, p.bt_major);
+                       p.span_cap, a.act, p.bt_major, p.NW);
     return hip_ok(hipGetLastError());
 }
 

@@ -74,9 +74,10 @@ __device__ __forceinline__ unsigned long long key_large_first(unsigned int mag, 
 __device__ __forceinline__ unsigned int digit_small_first(unsigned int mag) { return (0x7fffffffu - mag) >> (kDigitShift - 32); }
 __device__ __forceinline__ unsigned int digit_large_first(unsigned int mag) { return mag >> (kDigitShift - 32); }
 
+constexpr int kInitBlocks = 64;
 __global__ __launch_bounds__(256) void k_update_init(uint4* __restrict__ head) {
     const uint4 z = {0u, 0u, 0u, 0u};
-    for (size_t i = blockIdx.x * 256 + threadIdx.x; i < kZeroWords; i += (size_t)gridDim.x * 256) head[i] = z;
+    for (size_t i = blockIdx.x * 256 + threadIdx.x; i < kZeroWords; i += (size_t)kInitBlocks * 256) head[i] = z;
 }
 
 // The part of the layer that workgroup w works on, in every launch that reads the layer: consecutive workgroup ids go round the eight dies, and each of
@@ -128,10 +129,10 @@ __device__ __forceinline__ void each_of_quad(const Quad& q, unsigned int base, E
 // Counts the first digits of both selections of step 3.  n4 quads, then the elements [4 n4, N) one by one.  LDS counters: the
 // digits of one wavefront's values spread over some fifty of the 4096, so its adds meet at most a few times per address.
 __global__ __launch_bounds__(kScanThreads) void k_hist(const float* __restrict__ W, const uint8_t* __restrict__ mask, const float* __restrict__ grad,
-                                                       unsigned int N, unsigned int n4, UpdateScratch* __restrict__ s) {
+                                                       unsigned int N, unsigned int n4, unsigned int n_wg, unsigned int per, UpdateScratch* __restrict__ s) {
     __shared__ __align__(16) unsigned int h[2][kDigits];
     const int t = threadIdx.x;
-    const unsigned int per = (n4 + gridDim.x - 1) / gridDim.x, q0 = min(part_of_workgroup(blockIdx.x, gridDim.x) * per, n4), q1 = min(q0 + per, n4);
+    const unsigned int q0 = min(part_of_workgroup(blockIdx.x, n_wg) * per, n4), q1 = min(q0 + per, n4);
     Quad q[kQuads];
     if (q0 < q1) load_quads<true>(q, W, mask, grad, q0, q1);
     for (int i = t; i < 2 * kDigits / 4; i += kScanThreads) reinterpret_cast<uint4*>(&h[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(kScanThreads) void k_hist(const float* __restrict__
         for (int u = 0; u < kQuads; ++u)
             if (b + u * kScanThreads + t < q1) each_of_quad(q[u], 0, element);
     }
-    each_of_tail(N, n4, blockIdx.x * kScanThreads + t, gridDim.x * kScanThreads, [&](unsigned int i) { element(i, mask[i], W[i], grad[i]); });
+    each_of_tail(N, n4, blockIdx.x * kScanThreads + t, n_wg * kScanThreads, [&](unsigned int i) { element(i, mask[i], W[i], grad[i]); });
     __syncthreads();
     // neighbouring lanes add to neighbouring digits (an atomic instruction costs by the lines it touches: with four digits in a
     // row per thread the flush took half of the kernel's 11 us)
@@ -262,7 +263,7 @@ constexpr int kStage = 2048;
 template <bool PAIR>
 __global__ __launch_bounds__(kScanThreads) void k_collect(const float* __restrict__ W, const uint8_t* __restrict__ mask,
                                                           const float* __restrict__ grad, const int* __restrict__ remains, unsigned int N,
-                                                          unsigned int n4, int d_in, unsigned long long K, UpdateScratch* __restrict__ s,
+                                                          unsigned int n4, unsigned int n_wg, unsigned int per, int d_in, unsigned long long K, UpdateScratch* __restrict__ s,
                                                           unsigned long long* __restrict__ candA, unsigned long long* __restrict__ candB,
                                                           unsigned long long cap) {
     __shared__ __align__(16) unsigned long long stage[PAIR ? 2 : 1][kStage];
@@ -271,7 +272,7 @@ __global__ __launch_bounds__(kScanThreads) void k_collect(const float* __restric
     __shared__ unsigned long long base[2];
     const int t = threadIdx.x;
     constexpr int selA = PAIR ? 0 : 2;
-    const unsigned int per = (n4 + gridDim.x - 1) / gridDim.x, q0 = min(part_of_workgroup(blockIdx.x, gridDim.x) * per, n4), q1 = min(q0 + per, n4);
+    const unsigned int q0 = min(part_of_workgroup(blockIdx.x, n_wg) * per, n4), q1 = min(q0 + per, n4);
     Quad q[kQuads];
     if (!PAIR && sum_copies(s->cnt_ablated, t & 63) == 0) return;
     if (q0 < q1) load_quads<PAIR>(q, W, mask, grad, q0, q1);   // (before the counters are waited for)
@@ -353,7 +354,7 @@ __global__ __launch_bounds__(kScanThreads) void k_collect(const float* __restric
         }
         if (++batches % 4 == 0 && b + kQuads * kScanThreads < q1) flush();   // (65536 elements, three percent of which the stage holds)
     }
-    each_of_tail(N, n4, blockIdx.x * kScanThreads + t, gridDim.x * kScanThreads,
+    each_of_tail(N, n4, blockIdx.x * kScanThreads + t, n_wg * kScanThreads,
                  [&](unsigned int i) { element(i, mask[i], W[i], PAIR ? grad[i] : 0.0f); });
     flush();
 #pragma unroll
@@ -548,7 +549,7 @@ __device__ bool finish_wide(SelState& st, int sel, int part, int parts, const fl
 constexpr int kAhead = 4, kDirect = 256;
 template <bool PAIR>
 __global__ __launch_bounds__(kScanThreads) void k_final(const float* __restrict__ W, const uint8_t* __restrict__ mask, const float* __restrict__ grad,
-                                                        const int* __restrict__ remains, unsigned int N, int d_in, UpdateScratch* __restrict__ s,
+                                                        const int* __restrict__ remains, unsigned int N, int d_in, int parts, UpdateScratch* __restrict__ s,
                                                         unsigned long long* candA, unsigned long long* candB, unsigned long long cap,
                                                         unsigned long long K, long long budget, long long* __restrict__ report) {
     __shared__ __align__(16) unsigned int h[kDigits];
@@ -557,7 +558,7 @@ __global__ __launch_bounds__(kScanThreads) void k_final(const float* __restrict_
     __shared__ unsigned long long direct[kDirect];
     __shared__ unsigned int n_direct;
     const int t = threadIdx.x, lane = t & 63;
-    const int sel = PAIR ? (int)blockIdx.x & 1 : 2, part = PAIR ? (int)blockIdx.x >> 1 : (int)blockIdx.x, parts = PAIR ? (int)gridDim.x / 2 : (int)gridDim.x;
+    const int sel = PAIR ? (int)blockIdx.x & 1 : 2, part = PAIR ? (int)blockIdx.x >> 1 : (int)blockIdx.x;   // of `parts` for each selection
     SelState st;
     if (!PAIR) {
         const unsigned int n_ablated = sum_copies(s->cnt_ablated, lane);
@@ -693,13 +694,13 @@ __device__ __forceinline__ void load_row_short(RowQuad& q, const float* __restri
 // atomic per workgroup and counter, spread over copies; read by the launches after this one).  One wavefront per row.  An
 // ablated neuron's weights leave the counts of selection 0.
 __global__ __launch_bounds__(256) void k_row_salient(const float* __restrict__ W, const uint8_t* __restrict__ mask,
-                                                     const float* __restrict__ grad, int d_out, int d_in, int k, int gamma_percent,
+                                                     const float* __restrict__ grad, int d_out, int d_in, unsigned int n_wg, int k, int gamma_percent,
                                                      UpdateScratch* __restrict__ s, int* __restrict__ remains) {
     __shared__ int wg_stay, wg_ablated;
     __shared__ __align__(16) unsigned int gone[kDigits];
     bool ablates = false;
     const int lane = threadIdx.x & 63;
-    const int r = part_of_workgroup(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
+    const int r = part_of_workgroup(blockIdx.x, n_wg) * 4 + (threadIdx.x >> 6);
     if (threadIdx.x == 0) { wg_stay = 0; wg_ablated = 0; }
     const size_t row0 = (size_t)r * d_in;
     const bool quads = d_in >= 4;
@@ -794,14 +795,14 @@ __global__ __launch_bounds__(256) void k_row_salient(const float* __restrict__ W
 // instructions) until a threshold splits off exactly `want`.
 template <int NQ, int WPR>
 __global__ __launch_bounds__(256) void k_row_update(const float* __restrict__ W, const uint8_t* __restrict__ mask, const float* __restrict__ grad,
-                                                    int d_out, int d_in, const int* __restrict__ remains, const UpdateScratch* __restrict__ s,
+                                                    int d_out, int d_in, unsigned int n_wg, const int* __restrict__ remains, const UpdateScratch* __restrict__ s,
                                                     uint8_t* __restrict__ mask_out, float* __restrict__ W_out) {
     constexpr int N = 4 * NQ;
     constexpr bool HOLD = NQ <= 4;   // the weights stay in registers (else they are read again where they are kept)
     static_assert(WPR == 1 || WPR == 4, "the workgroup's barrier is the row's");
     __shared__ int part[2][4];
     const int lane = WPR == 1 ? threadIdx.x & 63 : threadIdx.x;
-    const int part_no = part_of_workgroup(blockIdx.x, gridDim.x), r = WPR == 1 ? part_no * 4 + (threadIdx.x >> 6) : part_no;
+    const int part_no = part_of_workgroup(blockIdx.x, n_wg), r = WPR == 1 ? part_no * 4 + (threadIdx.x >> 6) : part_no;
     if (r >= d_out) return;
     const size_t row0 = (size_t)r * d_in;
     const bool quads = NQ > 1 || WPR > 1 || d_in >= 4;
@@ -1023,32 +1024,35 @@ srigl_status srigl_mask_update(const float* W, const uint8_t* mask, const float*
         hipLaunchKernelGGL(k_update_report_empty, dim3(1), dim3(64), 0, st, report);
         return hip_ok(hipGetLastError());
     }
-    // eight launches, each reading what the ones before it counted
-    hipLaunchKernelGGL(k_update_init, dim3(64), dim3(256), 0, st, reinterpret_cast<uint4*>(s));
+    // Eight launches, each reading what the ones before it counted.  (What a kernel needs to know of its grid is an argument: gridDim, and blockDim, come
+    // with 256 bytes of arguments of the runtime's own, which every launch of the kernel writes.)
+    hipLaunchKernelGGL(k_update_init, dim3(kInitBlocks), dim3(256), 0, st, reinterpret_cast<uint4*>(s));
     // quads of the flat layer (16-byte moves need aligned arrays; rows of any length); at most one workgroup per compute unit
     const bool vec = reinterpret_cast<uintptr_t>(W) % 16 == 0 && reinterpret_cast<uintptr_t>(grad) % 16 == 0 && reinterpret_cast<uintptr_t>(mask) % 4 == 0;
     const unsigned int n4 = vec ? N / 4 : 0;
     unsigned int blocks = (unsigned int)(((unsigned long long)N + 4 * kScanThreads - 1) / (4 * kScanThreads));
     if (blocks > 256) blocks = 256;
-    hipLaunchKernelGGL(k_hist, dim3(blocks), dim3(kScanThreads), 0, st, W, mask, grad, N, n4, s);
-    hipLaunchKernelGGL(k_collect<true>, dim3(blocks), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, n4, d_in, (unsigned long long)K_upd, s,
+    hipLaunchKernelGGL(k_hist, dim3(blocks), dim3(kScanThreads), 0, st, W, mask, grad, N, n4, blocks, (n4 + blocks - 1) / blocks, s);
+    hipLaunchKernelGGL(k_collect<true>, dim3(blocks), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, n4, blocks, (n4 + blocks - 1) / blocks, d_in, (unsigned long long)K_upd, s,
                        candA, candB, cap);
     // Workgroups of k_final that stand by for a selection without a list (otherwise their start is all they cost: 45.0 us with 64, 44.7 with
     // none on 768 x 3072).  With 16 / 32 / 64 of them an update of that layer with zero gradients takes 127 / 92 / 79 us; on 4096 x 4097 64 take
     // 330 us and 256 285, on smaller layers 256 have too little to do each (1953 x 4096: 276, with 64 212).
     const unsigned int parts = N < (1u << 24) ? std::min(blocks, 64u) : (unsigned)kWideParts;
-    hipLaunchKernelGGL(k_final<true>, dim3(2 * parts), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, d_in, s, candA, candB, cap,
+    hipLaunchKernelGGL(k_final<true>, dim3(2 * parts), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, d_in, (int)parts, s, candA, candB, cap,
                        (unsigned long long)K_upd, (long long)budget, report);
     const dim3 row_grid(((unsigned)((d_out + 3) / 4) + kDies - 1) / kDies * kDies);   // (the same number of workgroups on every die)
-    hipLaunchKernelGGL(k_row_salient, row_grid, dim3(256), 0, st, W, mask, grad, d_out, d_in, k, gamma_percent, s, remains);
+    hipLaunchKernelGGL(k_row_salient, row_grid, dim3(256), 0, st, W, mask, grad, d_out, d_in, row_grid.x, k, gamma_percent, s, remains);
     // (most updates ablate nothing and this launch returns at once: it takes few workgroups, whose start is then all it costs)
-    hipLaunchKernelGGL(k_collect<false>, dim3(std::min(blocks, 64u)), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, n4, d_in, (unsigned long long)K_upd, s,
+    const unsigned int few = std::min(blocks, 64u);
+    hipLaunchKernelGGL(k_collect<false>, dim3(few), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, n4, few, (n4 + few - 1) / few, d_in, (unsigned long long)K_upd, s,
                        candA, candB, cap);
-    hipLaunchKernelGGL(k_final<false>, dim3(parts), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, d_in, s, candA, candB, cap,
+    hipLaunchKernelGGL(k_final<false>, dim3(parts), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, d_in, (int)parts, s, candA, candB, cap,
                        (unsigned long long)K_upd, (long long)budget, report);
-#define SRIGL_ROW_UPDATE(NQ, WPR)                                                                                                      \
-    hipLaunchKernelGGL((k_row_update<NQ, WPR>), WPR == 1 ? row_grid : dim3(((unsigned)d_out + kDies - 1) / kDies * kDies), dim3(256), 0, st, W, mask, grad, d_out, d_in, remains, \
-                       s, mask_out, W_out)
+    const dim3 one_row_grid(((unsigned)d_out + kDies - 1) / kDies * kDies);
+#define SRIGL_ROW_UPDATE(NQ, WPR)                                                                                                                    \
+    hipLaunchKernelGGL((k_row_update<NQ, WPR>), WPR == 1 ? row_grid : one_row_grid, dim3(256), 0, st, W, mask, grad, d_out, d_in,                    \
+                       (WPR == 1 ? row_grid : one_row_grid).x, remains, s, mask_out, W_out)
     const int nq = (d_in + 255) / 256;
     if (nq <= 1) SRIGL_ROW_UPDATE(1, 1);
     else if (nq <= 2) SRIGL_ROW_UPDATE(2, 1);
