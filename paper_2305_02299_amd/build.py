@@ -15,6 +15,9 @@ HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # packed fp32 VALU forms stay off for every kernel of this library
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # A kernel's first 16 words of arguments (structs passed by value are not among them) arrive in scalar registers with its wavefronts, instead of by a load that
+    # everything else waits for: 0.15 to 0.4 us a launch, 3072 -> 768 with 538 stored at 16 rows 6.20 -> 5.95 us, 768 -> 3072 at batch 256 8.4 -> 8.25, its update 42.3 -> 41.7
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wno-unused-command-line-argument",
 ]
 
