@@ -458,8 +458,9 @@ srigl_status srigl_structured_split_plan(int32_t B, int32_t d_in, int32_t n_acti
                                          size_t* workspace_bytes);
 
 /* The tile of the library's own choice for these sizes, in one part (may_split 0: srigl_structured_linear_fwd) or in the parts of
- * srigl_structured_split_plan: a srigl_gemm_tile, or 7 for the 256 x 192 tile of bf16 calls (8 wavefronts of 64x96, 2 LDS stages of 128
- * bytes), which cannot be asked for; 0 where no product runs.  Host-only. */
+ * srigl_structured_split_plan: a srigl_gemm_tile, or one of four tiles of bf16 calls that cannot be asked for: 7 = 256 x 192 (8 wavefronts of
+ * 64x96, 2 LDS stages of 128 bytes), 8 = 192 x 192 (4 of 96x96, 3), 9 = 128 x 96 (4 of 32x96, 4), 10 = 64 x 128 (4 of 32x64, 4); 0 where no
+ * product runs.  Host-only. */
 int32_t srigl_structured_tile_query(int32_t B, int32_t d_in, int32_t n_active, int32_t d_out, srigl_dtype dtype, int32_t may_split);
 
 srigl_status srigl_structured_linear_fwd_split(const void* x, srigl_dtype x_dtype, int32_t B, int32_t d_in, const void* Wd,
