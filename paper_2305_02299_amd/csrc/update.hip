@@ -262,10 +262,10 @@ __device__ __forceinline__ unsigned int sum_copies(const unsigned int (&c)[kCoun
 constexpr int kStage = 2048;
 template <bool PAIR>
 __global__ __launch_bounds__(kScanThreads) void k_collect(const float* __restrict__ W, const uint8_t* __restrict__ mask,
-                                                          const float* __restrict__ grad, const int* __restrict__ remains, unsigned int N,
-                                                          unsigned int n4, unsigned int n_wg, unsigned int per, int d_in, unsigned long long K, UpdateScratch* __restrict__ s,
-                                                          unsigned long long* __restrict__ candA, unsigned long long* __restrict__ candB,
-                                                          unsigned long long cap) {
+                                                          const float* __restrict__ grad, UpdateScratch* __restrict__ s, unsigned long long K,
+                                                          unsigned int n4, unsigned int n_wg, unsigned int per, unsigned int N,   // (preloaded)
+                                                          const int* __restrict__ remains, int d_in, unsigned long long* __restrict__ candA,
+                                                          unsigned long long* __restrict__ candB, unsigned long long cap) {
     __shared__ __align__(16) unsigned long long stage[PAIR ? 2 : 1][kStage];
     __shared__ SelState cur[2];
     __shared__ unsigned int n_staged[2];
@@ -548,10 +548,10 @@ __device__ bool finish_wide(SelState& st, int sel, int part, int parts, const fl
 // Step 6's first workgroup also takes the new fan-in from the neuron counters (step 5) and writes the report.
 constexpr int kAhead = 4, kDirect = 256;
 template <bool PAIR>
-__global__ __launch_bounds__(kScanThreads) void k_final(const float* __restrict__ W, const uint8_t* __restrict__ mask, const float* __restrict__ grad,
-                                                        const int* __restrict__ remains, unsigned int N, int d_in, int parts, UpdateScratch* __restrict__ s,
-                                                        unsigned long long* candA, unsigned long long* candB, unsigned long long cap,
-                                                        unsigned long long K, long long budget, long long* __restrict__ report) {
+__global__ __launch_bounds__(kScanThreads) void k_final(UpdateScratch* __restrict__ s, unsigned long long* candA, unsigned long long* candB,
+                                                        unsigned long long cap, unsigned long long K, long long budget, int parts, int d_in,   // (preloaded)
+                                                        const float* __restrict__ W, const uint8_t* __restrict__ mask, const float* __restrict__ grad,
+                                                        const int* __restrict__ remains, unsigned int N, long long* __restrict__ report) {
     __shared__ __align__(16) unsigned int h[kDigits];
     __shared__ unsigned int wave_sum[kScanThreads / 64];
     __shared__ SelState cur;
@@ -1033,22 +1033,22 @@ srigl_status srigl_mask_update(const float* W, const uint8_t* mask, const float*
     unsigned int blocks = (unsigned int)(((unsigned long long)N + 4 * kScanThreads - 1) / (4 * kScanThreads));
     if (blocks > 256) blocks = 256;
     hipLaunchKernelGGL(k_hist, dim3(blocks), dim3(kScanThreads), 0, st, W, mask, grad, N, n4, blocks, (n4 + blocks - 1) / blocks, s);
-    hipLaunchKernelGGL(k_collect<true>, dim3(blocks), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, n4, blocks, (n4 + blocks - 1) / blocks, d_in, (unsigned long long)K_upd, s,
-                       candA, candB, cap);
+    hipLaunchKernelGGL(k_collect<true>, dim3(blocks), dim3(kScanThreads), 0, st, W, mask, grad, s, (unsigned long long)K_upd, n4, blocks,
+                       (n4 + blocks - 1) / blocks, N, remains, d_in, candA, candB, cap);
     // Workgroups of k_final that stand by for a selection without a list (otherwise their start is all they cost: 45.0 us with 64, 44.7 with
     // none on 768 x 3072).  With 16 / 32 / 64 of them an update of that layer with zero gradients takes 127 / 92 / 79 us; on 4096 x 4097 64 take
     // 330 us and 256 285, on smaller layers 256 have too little to do each (1953 x 4096: 276, with 64 212).
     const unsigned int parts = N < (1u << 24) ? std::min(blocks, 64u) : (unsigned)kWideParts;
-    hipLaunchKernelGGL(k_final<true>, dim3(2 * parts), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, d_in, (int)parts, s, candA, candB, cap,
-                       (unsigned long long)K_upd, (long long)budget, report);
+    hipLaunchKernelGGL(k_final<true>, dim3(2 * parts), dim3(kScanThreads), 0, st, s, candA, candB, cap, (unsigned long long)K_upd, (long long)budget,
+                       (int)parts, d_in, W, mask, grad, remains, N, report);
     const dim3 row_grid(((unsigned)((d_out + 3) / 4) + kDies - 1) / kDies * kDies);   // (the same number of workgroups on every die)
     hipLaunchKernelGGL(k_row_salient, row_grid, dim3(256), 0, st, W, mask, grad, d_out, d_in, row_grid.x, k, gamma_percent, s, remains);
     // (most updates ablate nothing and this launch returns at once: it takes few workgroups, whose start is then all it costs)
     const unsigned int few = std::min(blocks, 64u);
-    hipLaunchKernelGGL(k_collect<false>, dim3(few), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, n4, few, (n4 + few - 1) / few, d_in, (unsigned long long)K_upd, s,
-                       candA, candB, cap);
-    hipLaunchKernelGGL(k_final<false>, dim3(parts), dim3(kScanThreads), 0, st, W, mask, grad, remains, N, d_in, (int)parts, s, candA, candB, cap,
-                       (unsigned long long)K_upd, (long long)budget, report);
+    hipLaunchKernelGGL(k_collect<false>, dim3(few), dim3(kScanThreads), 0, st, W, mask, grad, s, (unsigned long long)K_upd, n4, few,
+                       (n4 + few - 1) / few, N, remains, d_in, candA, candB, cap);
+    hipLaunchKernelGGL(k_final<false>, dim3(parts), dim3(kScanThreads), 0, st, s, candA, candB, cap, (unsigned long long)K_upd, (long long)budget,
+                       (int)parts, d_in, W, mask, grad, remains, N, report);
     const dim3 one_row_grid(((unsigned)d_out + kDies - 1) / kDies * kDies);
 #define SRIGL_ROW_UPDATE(NQ, WPR)                                                                                                                    \
     hipLaunchKernelGGL((k_row_update<NQ, WPR>), WPR == 1 ? row_grid : one_row_grid, dim3(256), 0, st, W, mask, grad, d_out, d_in,                    \
