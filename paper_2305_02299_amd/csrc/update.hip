@@ -793,7 +793,7 @@ __global__ __launch_bounds__(256) void k_row_salient(const float* __restrict__ W
 // is ranked by one number (its weight's magnitude if it survives step 6, else its gradient's), equal numbers by column.  The
 // `want`-th largest among the row's candidates is searched by counting (NQ x 4 compares, their ballots counted by scalar
 // instructions) until a threshold splits off exactly `want`.
-template <int NQ, int WPR>
+template <int NQ, int WPR, bool BESIDE>
 __global__ __launch_bounds__(256) void k_row_update(const float* __restrict__ W, const uint8_t* __restrict__ mask, const float* __restrict__ grad,
                                                     int d_out, int d_in, unsigned int n_wg, const int* __restrict__ remains, const UpdateScratch* __restrict__ s,
                                                     uint8_t* __restrict__ mask_out, float* __restrict__ W_out) {
@@ -833,7 +833,7 @@ __global__ __launch_bounds__(256) void k_row_update(const float* __restrict__ W,
         RowQuad in[STEP];
 #pragma unroll
         for (int u = 0; u < STEP; ++u) {
-            if (q0 + u < NQ && (q0 == 0 || stays)) {   // (the first ones beside `stays`, not behind it)
+            if (q0 + u < NQ && ((BESIDE && q0 == 0) || stays)) {   // (BESIDE: the first ones beside `stays`, not behind it)
                 if (quads) load_row_quad(in[u], W, mask, grad, row0 + quad_first(col0(q0 + u), d_in));
                 else load_row_short(in[u], W, mask, grad, row0, d_in);
             }
@@ -1049,10 +1049,13 @@ srigl_status srigl_mask_update(const float* W, const uint8_t* mask, const float*
                        (n4 + few - 1) / few, N, remains, d_in, candA, candB, cap);
     hipLaunchKernelGGL(k_final<false>, dim3(parts), dim3(kScanThreads), 0, st, s, candA, candB, cap, (unsigned long long)K_upd, (long long)budget,
                        (int)parts, d_in, W, mask, grad, remains, N, report);
+    // A row is requested beside the flag that says whether it stays where the layer is still near (real-valued, all rows staying: 1953 x 4096 82.5 us, 83.7
+    // behind the flag); from 8 M elements on the memory's rate counts and rows that don't stay are not read: 4096 x 4096 with a fifth of the rows ablated 137 us -> 132,
+    // 16384 x 4096 549 -> 528, 4096 x 2048 with a tenth 79 either way.
     const dim3 one_row_grid(((unsigned)d_out + kDies - 1) / kDies * kDies);
-#define SRIGL_ROW_UPDATE(NQ, WPR)                                                                                                                    \
-    hipLaunchKernelGGL((k_row_update<NQ, WPR>), WPR == 1 ? row_grid : one_row_grid, dim3(256), 0, st, W, mask, grad, d_out, d_in,                    \
-                       (WPR == 1 ? row_grid : one_row_grid).x, remains, s, mask_out, W_out)
+#define SRIGL_ROW_UPDATE(NQ, WPR)                                                                                                               \
+    hipLaunchKernelGGL((N < (1u << 23) ? k_row_update<NQ, WPR, true> : k_row_update<NQ, WPR, false>), WPR == 1 ? row_grid : one_row_grid,       \
+                       dim3(256), 0, st, W, mask, grad, d_out, d_in, (WPR == 1 ? row_grid : one_row_grid).x, remains, s, mask_out, W_out)
     const int nq = (d_in + 255) / 256;
     if (nq <= 1) SRIGL_ROW_UPDATE(1, 1);
     else if (nq <= 2) SRIGL_ROW_UPDATE(2, 1);
