@@ -76,3 +76,12 @@ def test_selections_without_a_list_on_a_layer_of_256_parts():
     W = np.where(mask != 0, few_magnitudes("mostly one", rng, mask.shape), 0).astype(np.float32)
     info = check(B_, W, mask, np.zeros_like(W), k, d_out * k // 2, 50)
     assert info["n_ablated_now"] > 0
+
+
+@pytest.mark.parametrize("d_out,d_in", [(8191, 1024), (8193, 1024), (32800, 256), (2049, 4097)])
+def test_rows_that_do_not_stay_on_either_side_of_8_m_elements(d_out, d_in):
+    """Up to 2^23 elements the last launch requests a row beside the flag that says whether it stays, beyond behind it."""
+    k = d_in // 20
+    W, mask, g = layer(d_in, d_out, k, d_out, 0.2)
+    g *= np.linspace(0.1, 1.0, d_out, dtype=np.float32)[:, None]
+    check(B_, W, mask, g, k, int(0.3 * mask.sum()), 60)
