@@ -14,6 +14,7 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include "pinned_answer.h"
 #include "srigl.h"
 
 namespace {
@@ -300,57 +301,52 @@ PyObject* condense(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
         int32_t* const ws = static_cast<int32_t*>(active.data_ptr()) + d_out;
         // (from the allocator that pinned tensors come from: nothing here needs the tensor around it)
         const size_t count_bytes = srigl_condense_count_bytes(d_out, d_in);
-        const at::DataPtr pinned = at::globalContext().getPinnedMemoryAllocator(at::kCUDA)->allocate(std::max(count_bytes, sizeof(srigl_report)));
+        at::DataPtr pinned = at::globalContext().getPinnedMemoryAllocator(at::kCUDA)->allocate(std::max(count_bytes, sizeof(srigl_report)));
         void* const counts = count_bytes ? pinned.get() : nullptr;
         srigl_report* const rep = static_cast<srigl_report*>(pinned.get());   // (without counts: the second launch's report)
         constexpr int32_t kPending = -7;
         if (!counts) __atomic_store_n(&rep->status, kPending, __ATOMIC_RELEASE);
         at::Tensor W_c, idx, seg, packed;
         const size_t packed_bytes = srigl_packed_bytes(d_out, K, d_in, wt);
+        const void* const wp = W->data_ptr();
+        const uint8_t* const mp = static_cast<const uint8_t*>(mask->data_ptr());
+        srigl_report report{};
+        int32_t from = 0;
+        // Whatever happens from here on, what the launches still write into the pinned memory is waited for before it is given back.
+        srigl::PinnedAnswer answer(
+            [&] {
+                if (counts) return srigl_condense_counted(counts, d_out, K, d_out, &from, &report) != 0;
+                if (__atomic_load_n(&rep->status, __ATOMIC_ACQUIRE) == kPending) return false;
+                report = *rep;
+                return true;
+            },
+            [&] {
+                try {
+                    return st.query() ? srigl::StreamState::kIdle : srigl::StreamState::kBusy;
+                } catch (...) {
+                    return srigl::StreamState::kUnknown;
+                }
+            },
+            [&] { pinned.release_context(); });
         auto allocate = [&] {
             W_c = fresh({d_out, k}, W->scalar_type(), *W);
             idx = fresh({d_out, k}, at::kInt, *W);
             if (want_seg) seg = fresh({d_out, srigl_seg_stride(d_in)}, at::kShort, *W);
             if (want_packed) packed = fresh({(int64_t)(packed_bytes > 16 ? packed_bytes : 16)}, at::kByte, *W);
         };
+        auto count = [&] { return srigl_condense_count(mp, d_out, d_in, K, ws, ws_bytes, counts, count_bytes, st.stream()); };
+        auto write = [&] {
+            return srigl_condense_write(wp, wt, mp, d_out, d_in, K, d_out, W_c.data_ptr(), static_cast<int32_t*>(idx.data_ptr()), static_cast<int32_t*>(active.data_ptr()),
+                                        want_seg ? static_cast<uint16_t*>(seg.data_ptr()) : nullptr, want_packed ? packed.data_ptr() : nullptr,
+                                        want_packed ? (size_t)packed.numel() : 0, ws, ws_bytes, counts ? nullptr : rep, st.stream());
+        };
         if (!counts) allocate();
-        const uint8_t* const mp = static_cast<const uint8_t*>(mask->data_ptr());
-        check(srigl_condense_count(mp, d_out, d_in, K, ws, ws_bytes, counts, count_bytes, st.stream()), "srigl_condense");
-        // The results are allocated and the second launch is made while the first one runs.  Whatever happens here, what the launches still write
-        // into the pinned memory is waited for before it is given back.
-        srigl_report report{};
-        int32_t from = 0;
-        bool pending = counts != nullptr, answered = false;
-        auto arrived = [&] {
-            if (counts) return srigl_condense_counted(counts, d_out, K, d_out, &from, &report) != 0;
-            if (__atomic_load_n(&rep->status, __ATOMIC_ACQUIRE) == kPending) return false;
-            report = *rep;
-            return true;
-        };
-        auto wait = [&] {
-            if (!pending) return;
-            pending = false;
-            // (the stream is asked now and then, so that the wait ends whatever happened to the launches; asked every 1024 polls it took 6 us of a call's 22)
-            for (unsigned polls = 1; !(answered = arrived()); ++polls) {
-                if (polls % 65536 != 0) continue;
-                bool idle = false;
-                try { idle = st.query(); } catch (...) { return; }
-                if (idle) {
-                    answered = arrived();
-                    return;
-                }
-            }
-        };
-        struct AtEnd { decltype(wait)& f; ~AtEnd() { f(); } } at_end{wait};
-        if (counts) allocate();
-        void *wcp = W_c.data_ptr(), *sgp = want_seg ? seg.data_ptr() : nullptr, *pkp = want_packed ? packed.data_ptr() : nullptr;
-        srigl_status rc;
+        srigl_status rc = counts ? answer.launch(count) : count();
+        if (rc == SRIGL_OK && counts) allocate();
+        bool answered = false;
         Py_BEGIN_ALLOW_THREADS
-        rc = srigl_condense_write(W->data_ptr(), wt, mp, d_out, d_in, K, d_out, wcp, static_cast<int32_t*>(idx.data_ptr()),
-                                  static_cast<int32_t*>(active.data_ptr()), static_cast<uint16_t*>(sgp), pkp, want_packed ? (size_t)packed.numel() : 0,
-                                  ws, ws_bytes, counts ? nullptr : rep, st.stream());
-        if (rc == SRIGL_OK) pending = true;
-        wait();
+        if (rc == SRIGL_OK) rc = counts ? write() : answer.launch(write);
+        answered = answer.wait();
         Py_END_ALLOW_THREADS
         check(rc, "srigl_condense");
         if (!answered) check(SRIGL_ERR_HIP, "srigl_condense");
