@@ -113,6 +113,14 @@ int32_t rows_of(const at::Tensor& x, int32_t d_in) {
     return (int32_t)x.size(0);
 }
 
+// The interpreter's lock released, and taken again at the block's end however it is left.
+struct Unlocked {
+    PyThreadState* const state = PyEval_SaveThread();
+    Unlocked() = default;
+    Unlocked(const Unlocked&) = delete;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 template <typename Body>
 PyObject* guarded(Body body) {
     PyObject* out = nullptr;
@@ -312,42 +320,44 @@ PyObject* condense(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
         const uint8_t* const mp = static_cast<const uint8_t*>(mask->data_ptr());
         srigl_report report{};
         int32_t from = 0;
-        // Whatever happens from here on, what the launches still write into the pinned memory is waited for before it is given back.
-        srigl::PinnedAnswer answer(
-            [&] {
-                if (counts) return srigl_condense_counted(counts, d_out, K, d_out, &from, &report) != 0;
-                if (__atomic_load_n(&rep->status, __ATOMIC_ACQUIRE) == kPending) return false;
-                report = *rep;
-                return true;
-            },
-            [&] {
-                try {
-                    return st.query() ? srigl::StreamState::kIdle : srigl::StreamState::kBusy;
-                } catch (...) {
-                    return srigl::StreamState::kUnknown;
-                }
-            },
-            [&] { pinned.release_context(); });
-        auto allocate = [&] {
-            W_c = fresh({d_out, k}, W->scalar_type(), *W);
-            idx = fresh({d_out, k}, at::kInt, *W);
-            if (want_seg) seg = fresh({d_out, srigl_seg_stride(d_in)}, at::kShort, *W);
-            if (want_packed) packed = fresh({(int64_t)(packed_bytes > 16 ? packed_bytes : 16)}, at::kByte, *W);
-        };
-        auto count = [&] { return srigl_condense_count(mp, d_out, d_in, K, ws, ws_bytes, counts, count_bytes, st.stream()); };
-        auto write = [&] {
-            return srigl_condense_write(wp, wt, mp, d_out, d_in, K, d_out, W_c.data_ptr(), static_cast<int32_t*>(idx.data_ptr()), static_cast<int32_t*>(active.data_ptr()),
-                                        want_seg ? static_cast<uint16_t*>(seg.data_ptr()) : nullptr, want_packed ? packed.data_ptr() : nullptr,
-                                        want_packed ? (size_t)packed.numel() : 0, ws, ws_bytes, counts ? nullptr : rep, st.stream());
-        };
-        if (!counts) allocate();
-        srigl_status rc = counts ? answer.launch(count) : count();
-        if (rc == SRIGL_OK && counts) allocate();
+        srigl_status rc = SRIGL_OK;
         bool answered = false;
-        Py_BEGIN_ALLOW_THREADS
-        if (rc == SRIGL_OK) rc = counts ? write() : answer.launch(write);
-        answered = answer.wait();
-        Py_END_ALLOW_THREADS
+        {
+            const Unlocked unlocked;   // (a launch on a stream whose queue is full waits for room in it)
+            // Whatever happens from here on, what the launches still write into the pinned memory is waited for before it is given back.
+            srigl::PinnedAnswer answer(
+                [&] {
+                    if (counts) return srigl_condense_counted(counts, d_out, K, d_out, &from, &report) != 0;
+                    if (__atomic_load_n(&rep->status, __ATOMIC_ACQUIRE) == kPending) return false;
+                    report = *rep;
+                    return true;
+                },
+                [&] {
+                    try {
+                        return st.query() ? srigl::StreamState::kIdle : srigl::StreamState::kBusy;
+                    } catch (...) {
+                        return srigl::StreamState::kUnknown;
+                    }
+                },
+                [&] { pinned.release_context(); });
+            auto allocate = [&] {
+                W_c = fresh({d_out, k}, W->scalar_type(), *W);
+                idx = fresh({d_out, k}, at::kInt, *W);
+                if (want_seg) seg = fresh({d_out, srigl_seg_stride(d_in)}, at::kShort, *W);
+                if (want_packed) packed = fresh({(int64_t)(packed_bytes > 16 ? packed_bytes : 16)}, at::kByte, *W);
+            };
+            auto count = [&] { return srigl_condense_count(mp, d_out, d_in, K, ws, ws_bytes, counts, count_bytes, st.stream()); };
+            auto write = [&] {
+                return srigl_condense_write(wp, wt, mp, d_out, d_in, K, d_out, W_c.data_ptr(), static_cast<int32_t*>(idx.data_ptr()), static_cast<int32_t*>(active.data_ptr()),
+                                            want_seg ? static_cast<uint16_t*>(seg.data_ptr()) : nullptr, want_packed ? packed.data_ptr() : nullptr,
+                                            want_packed ? (size_t)packed.numel() : 0, ws, ws_bytes, counts ? nullptr : rep, st.stream());
+            };
+            if (!counts) allocate();
+            rc = counts ? answer.launch(count) : count();
+            if (rc == SRIGL_OK && counts) allocate();
+            if (rc == SRIGL_OK) rc = counts ? write() : answer.launch(write);
+            answered = answer.wait();
+        }
         check(rc, "srigl_condense");
         if (!answered) check(SRIGL_ERR_HIP, "srigl_condense");
         if (report.status != SRIGL_OK) {
