@@ -117,7 +117,8 @@ srigl_status srigl_condense(const void* W, srigl_dtype w_dtype, const uint8_t* m
  * srigl_condense_count: counts (may be NULL): srigl_condense_count_bytes(d_out, d_in) bytes (0: this layer's call takes none) of pinned host memory that the GPU can
  *   write, 8-byte aligned; cleared by the call, filled by its launch.  It must stay allocated until all counts are there or the stream has finished.
  * srigl_condense_counted: reads on from word *from (0 at first); 0 while counts are missing, 1 when *report (host memory) is complete, as srigl_condense reports with
- *   the cap_rows of the second call.  Host only.
+ *   the cap_rows of the second call; cap_rows negative: for a second call with active NULL, which stores no rows and reports no capacity.  Without rows (d_out 0)
+ *   counts is not read.  Host only.
  * srigl_condense_write: the second launch, on the same stream, with the workspace of the first; results as in srigl_condense; report may be NULL. */
 size_t srigl_condense_count_bytes(int32_t d_out, int32_t d_in);
 

@@ -609,21 +609,21 @@ srigl_status srigl_condense_write(const void* W, srigl_dtype w_dtype, const uint
 
 int32_t srigl_condense_counted(const void* counts, int32_t d_out, int32_t K, int32_t cap_rows, int32_t* from, srigl_report* report) {
     const unsigned long long* const words = static_cast<const unsigned long long*>(counts);
-    const CountShape c = count_shape(d_out);
+    const CountShape c = count_shape(std::max(d_out, 0));
+    if (*from <= 0) {
+        *report = srigl_report{};
+        report->first_bad_row = -1;
+    }
     for (; *from < c.words; ++*from) {
         const unsigned long long w = __atomic_load_n(&words[*from], __ATOMIC_ACQUIRE);
         if ((w & kCounted) == 0) return 0;
-        if (*from == 0) {
-            *report = srigl_report{};
-            report->first_bad_row = -1;
-        }
         const int wrong = (int)((w >> 21) & 0x1fffff);
         report->n_active += (int)(w & 0x1fffff);
         report->n_bad_rows += wrong;
         if (wrong && report->first_bad_row < 0) report->first_bad_row = *from * c.groups * kCountRows + (int)((w >> 42) & 0x1fffff);
     }
     report->K = K;
-    report->status = report->n_bad_rows > 0 ? SRIGL_ERR_FANIN : report->n_active > cap_rows ? SRIGL_ERR_CAPACITY : SRIGL_OK;
+    report->status = report->n_bad_rows > 0 ? SRIGL_ERR_FANIN : cap_rows >= 0 && report->n_active > cap_rows ? SRIGL_ERR_CAPACITY : SRIGL_OK;
     return 1;
 }
 

@@ -63,3 +63,15 @@ def test_counts_of_several_words():
     assert ask(6027) == 1 and list(report)[:5] == [6, 6028, 0, -1, B_.ERR_CAPACITY]
     at.value = 0
     assert ask(6028) == 1 and list(report)[:5] == [6, 6028, 0, -1, B_.OK]
+    at.value = 0
+    assert ask(0) == 1 and report[4] == B_.ERR_CAPACITY      # room for no rows, with an `active` that they would have gone to
+    at.value = 0
+    assert ask(-1) == 1 and list(report)[:5] == [6, 6028, 0, -1, B_.OK]
+
+
+@pytest.mark.parametrize("d_out", [0, -3])
+@pytest.mark.parametrize("cap", [-1, 0, 5])
+def test_counts_of_no_rows(d_out, cap):
+    at, report = ctypes.c_int32(0), (ctypes.c_int32 * 8)(*range(50, 58))
+    assert B_.lib.srigl_condense_counted(None, d_out, 6, cap, ctypes.byref(at), report) == 1
+    assert list(report) == [6, 0, 0, -1, B_.OK, 0, 0, 0]
