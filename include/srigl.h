@@ -112,8 +112,8 @@ srigl_status srigl_condense(const void* W, srigl_dtype w_dtype, const uint8_t* m
                             size_t workspace_bytes, srigl_report* report_dev, void* stream);
 
 /* srigl_condense in two calls, for callers that wait for the number of stored rows on the host: the first launch can run before the buffers that are sized for
- * the largest result have been allocated, and on layers up to 8 M elements it leaves the rows' counts in host memory, so that they are there before the
- * second launch has run.
+ * the largest result have been allocated, and on layers where that is ahead (srigl_condense_count_bytes) it leaves the rows' counts in host memory, so that they are there
+ * before the second launch has run.
  * srigl_condense_count: counts (may be NULL): srigl_condense_count_bytes(d_out, d_in) bytes (0: this layer's call takes none) of pinned host memory that the GPU can
  *   write, 8-byte aligned; cleared by the call, filled by its launch.  It must stay allocated until all counts are there or the stream has finished.
  * srigl_condense_counted: reads on from word *from (0 at first); 0 while counts are missing, 1 when *report (host memory) is complete, as srigl_condense reports with

@@ -579,10 +579,15 @@ static srigl_status condense_core(const void* W, srigl_dtype w_dtype, const uint
     return hip_ok(hipGetLastError());
 }
 
-// Layers up to 8 M elements: beyond, the launches on the GPU take longer than the host's part of a call, which is what the counts shorten, and 128 workgroups
-// no longer read the mask as fast as it comes.  2^20 rows: the fields of a word.
+// Layers whose rows 128 workgroups count in the 4.5 us that the host gains by it: two groups of 32 rows to a workgroup, and so little to read, all of them together and
+// each by itself, that k_row_flags with a workgroup for every eight rows would not have been done sooner.  Calls of condense_layer with counts beside calls
+// with the second launch's report (us; K = a tenth of d_in): 3072 x 768 13.0 / 16.3, 329 x 128 0.69 of the time, 8192 x 512 0.96, 4096 x 1536 0.97, 2048 x 2048 0.88, 1024 x 3072 0.92,
+// 512 x 4096 0.93, 256 x 5120 0.93; beyond the line 12288 x 256 1.04, 20000 x 24 1.17, 3072 x 2048 0.98, 4096 x 2048 1.08, 2048 x 3072 1.02, 1024 x 4096 1.01, 512 x 6144 1.15, 64 x 16384 1.31.
 size_t srigl_condense_count_bytes(int32_t d_out, int32_t d_in) {
-    return d_out > 0 && d_in > 0 && d_out <= 1 << 20 && (long long)d_out * d_in <= 8 << 20 ? count_shape(d_out).words * sizeof(unsigned long long) : 0;
+    if (d_out <= 0 || d_in <= 0 || d_out > 2 * kCountRows * kCountWords) return 0;
+    const CountShape c = count_shape(d_out);
+    const long long rows_of_one = (long long)kCountRows * c.groups;   // what a workgroup reads by itself takes 42 times as long as its part of what all read
+    return (d_out + 42 * rows_of_one) * d_in <= 8500000 ? c.words * sizeof(unsigned long long) : 0;
 }
 
 srigl_status srigl_condense_count(const uint8_t* mask, int32_t d_out, int32_t d_in, int32_t K, void* workspace, size_t workspace_bytes, void* counts,

@@ -287,9 +287,10 @@ PyObject* mask_update(PyObject*, PyObject* const* a, Py_ssize_t n) {
 }
 
 // condense(W, mask, K, want_seg, want_packed) -> (n_active, W_c, idx, active, seg, packed), every array cut to the stored rows
-// (active: None when no neuron is ablated).  Waits for the rows' counts only, which the first launch writes straight into pinned host
-// memory (no copy launch, no stream synchronisation); the arrays are complete in stream order like any other result.  The results are allocated and the
-// second launch is made while the first one runs (768 -> 3072: 16.4 us a call with the launches behind the allocations and a report from the second one).
+// (active: None when no neuron is ablated).  The arrays are complete in stream order like any other result; only the number of stored rows is waited for, which a
+// launch writes straight into pinned host memory (no copy launch, no stream synchronisation).  Where the library counts rows into host memory
+// (srigl_condense_count_bytes) that is the first launch, and the results are allocated and the second launch is made while it runs (768 -> 3072: 12.5 us a call, 15.7
+// with both launches behind the allocations and the report of the second one, as on the other layers).
 PyObject* condense(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     return guarded([&](PyObject*& out) {
         need(n_args, 5);
@@ -346,16 +347,19 @@ PyObject* condense(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
                 if (want_seg) seg = fresh({d_out, srigl_seg_stride(d_in)}, at::kShort, *W);
                 if (want_packed) packed = fresh({(int64_t)(packed_bytes > 16 ? packed_bytes : 16)}, at::kByte, *W);
             };
-            auto count = [&] { return srigl_condense_count(mp, d_out, d_in, K, ws, ws_bytes, counts, count_bytes, st.stream()); };
-            auto write = [&] {
-                return srigl_condense_write(wp, wt, mp, d_out, d_in, K, d_out, W_c.data_ptr(), static_cast<int32_t*>(idx.data_ptr()), static_cast<int32_t*>(active.data_ptr()),
-                                            want_seg ? static_cast<uint16_t*>(seg.data_ptr()) : nullptr, want_packed ? packed.data_ptr() : nullptr,
-                                            want_packed ? (size_t)packed.numel() : 0, ws, ws_bytes, counts ? nullptr : rep, st.stream());
+            auto write = [&](auto call) {
+                return call(wp, wt, mp, d_out, d_in, K, d_out, W_c.data_ptr(), static_cast<int32_t*>(idx.data_ptr()), static_cast<int32_t*>(active.data_ptr()),
+                            want_seg ? static_cast<uint16_t*>(seg.data_ptr()) : nullptr, want_packed ? packed.data_ptr() : nullptr,
+                            want_packed ? (size_t)packed.numel() : 0, ws, ws_bytes, counts ? nullptr : rep, st.stream());
             };
-            if (!counts) allocate();
-            rc = counts ? answer.launch(count) : count();
-            if (rc == SRIGL_OK && counts) allocate();
-            if (rc == SRIGL_OK) rc = counts ? write() : answer.launch(write);
+            if (counts) {
+                rc = answer.launch([&] { return srigl_condense_count(mp, d_out, d_in, K, ws, ws_bytes, counts, count_bytes, st.stream()); });
+                if (rc == SRIGL_OK) allocate();
+                if (rc == SRIGL_OK) rc = write(srigl_condense_write);
+            } else {
+                allocate();
+                rc = answer.launch([&] { return write(srigl_condense); });
+            }
             answered = answer.wait();
         }
         check(rc, "srigl_condense");

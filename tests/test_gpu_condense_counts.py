@@ -1,5 +1,5 @@
 """condense_layer counts its rows from host memory (srigl_condense_count / _counted / _write): sizes at the edges of a group of 32 rows and of what 128 workgroups
-share, against the oracle bit for bit; rows that are wrong in any group; the size from which the second launch's report is read."""
+share, against the oracle bit for bit; rows that are wrong in any group; the layers on which the second launch's report is read instead."""
 import ctypes
 
 import numpy as np
@@ -16,15 +16,15 @@ from paper_2305_02299_amd import condense_layer
 @pytest.mark.gpu
 @pytest.mark.parametrize("d_in,d_out,K,abl,dtype", [
     (5, 1, 2, 0.0, "f32"), (15, 33, 4, 0.3, "bf16"), (16, 31, 3, 0.0, "f32"), (17, 32, 5, 0.5, "bf16"), (300, 97, 30, 0.9, "f32"),
-    (96, 4096, 9, 0.2, "bf16"), (96, 4097, 9, 0.2, "f32"), (64, 12345, 7, 0.45, "f32"),        # one, two and four groups to a workgroup
-    (4100, 70, 40, 0.1, "f32"), (9000, 40, 900, 0.0, "bf16"),                                  # rows of more than one turn of loads
-    (2048, 4100, 20, 0.1, "bf16"),                                                             # beyond 8 M elements: no counts
+    (96, 4096, 9, 0.2, "bf16"), (96, 4097, 9, 0.2, "f32"), (64, 8192, 7, 0.45, "f32"),         # one and two groups to a workgroup
+    (4100, 70, 40, 0.1, "f32"), (6000, 40, 900, 0.0, "bf16"),                                  # rows of more than one turn of loads
+    (64, 12345, 7, 0.45, "f32"), (9000, 40, 900, 0.0, "bf16"), (2048, 4100, 20, 0.1, "bf16"),  # no counts
 ])
 def test_condense_layer_bit_exact(d_in, d_out, K, abl, dtype):
     L = si.make_layer(d_in, d_out, K, 1, ablate_frac=abl, dtype=dtype, seed=7 * d_out + d_in)
     W = L.W_bf16 if dtype == "bf16" else L.W
     W_c, idx, active = oracle.condense(W, L.mask, K)
-    assert (B_.lib.srigl_condense_count_bytes(d_out, d_in) > 0) == (d_out * d_in <= 8 << 20)
+    assert (B_.lib.srigl_condense_count_bytes(d_out, d_in) > 0) == ((d_in, d_out) not in ((64, 12345), (9000, 40), (2048, 4100)))
     for _ in range(2):
         layer = condense_layer(dev(W), dev(L.mask), K)
         n = len(active)
@@ -45,6 +45,16 @@ def test_wrong_rows_are_named(d_out, wrong):
         condense_layer(dev(L.W), dev(L.mask), 6)
     assert e.value.status == B_.ERR_FANIN
     assert condense_layer(dev(L.W), dev(np.zeros_like(L.mask)), 6).n_active == 0
+
+
+def test_counts_only_where_they_were_measured_ahead():
+    """Layers on either side of the line (d_out, d_in), as calls with counts and with the second launch's report were timed beside each other."""
+    words = lambda d_out, d_in: B_.lib.srigl_condense_count_bytes(d_out, d_in) // 8   # noqa: E731
+    for layer in ((3072, 768), (768, 3072), (329, 128), (8192, 512), (4096, 1536), (2048, 2048), (1024, 3072), (512, 4096), (256, 5120), (16, 6144)):
+        assert 0 < words(*layer) <= 128, layer
+    for layer in ((1048576, 8), (524288, 16), (20000, 24), (12288, 64), (12288, 256), (8193, 64), (8192, 1024), (5120, 1536), (4096, 2048), (2048, 3072), (1024, 4096),
+                  (512, 6144), (256, 8192), (64, 16384), (100, 80000), (32, 262144), (1, 1000000), (0, 5), (5, 0), (-1, 5), (2**31 - 1, 2**31 - 1)):
+        assert words(*layer) == 0, layer
 
 
 def test_counts_of_several_words():
