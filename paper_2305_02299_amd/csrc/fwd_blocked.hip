@@ -428,7 +428,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_fwd_blocked(const BlockedArg
     if (tid < BM / 32) spoiled[tid] = 0u;
 
     // ---- prologue (what the epilogue needs from memory is fetched here too, beside the first requests)
-    const TileColumns cols = tile_columns(n0, BN, p.active, p.n_active, p.d_out, EpiLayout<BN, WGM>::LINE_RUN);
+    const long long inputs = 2ll * p.B * p.d_in + 4ll * p.n_active * p.K;
+    const TileColumns cols = tile_columns(n0, BN, p.active, p.n_active, p.d_out, line_run(p.B, p.d_out, inputs, EpiLayout<BN, WGM>::LINE_RUN, BN >= 256 ? 77.0f : 46.5f));
     load_list(0);
 #pragma unroll
     for (int q = 0; q < XP; ++q) issue_piece(0, q);

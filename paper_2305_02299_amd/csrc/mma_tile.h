@@ -61,7 +61,7 @@ __device__ __forceinline__ bool tile_of_workgroup(int id, int tiles_m, int tiles
 // The columns of y that the tile at stored neuron n0 writes: its stored neurons and the ablated ones in front of them (behind the
 // last one too in the last tile) are one contiguous range.
 struct TileColumns { int lo, hi, stored, base; };   // base: where the windows begin
-// A tile's first column lies anywhere with ablated neurons.  The windows begin at its 128-byte line of y where all rows of y have lines there and the tile's
+// A tile's first column lies anywhere with ablated neurons.  The windows begin at its 128-byte line of y where y is large (line_run), all rows of y have lines there and the tile's
 // rows take no more runs of `run` columns (a wavefront's stores of a row; 0: never) for it: 124 -> 6696 at batch 1270, whose rows begin anywhere, 20.9 us from the column and 22.2 from
 // the line; 384 -> 5120 with 3072 stored at batch 288 in 64 x 64 tiles, whose runs are two lines long, 8.0 and 8.4.
 __device__ __forceinline__ TileColumns tile_columns(int n0, int bn, const int32_t* active, int n_active, int d_out, int run) {
@@ -71,13 +71,24 @@ __device__ __forceinline__ TileColumns tile_columns(int n0, int bn, const int32_
     return {lo, hi, cnt, run && d_out % 32 == 0 && (hi - line) / run == (hi - lo) / run ? line : lo};
 }
 
+// `run` for tile_columns, of a launch that writes y and reads `inputs` bytes.  Windows from the line cost a tile's wavefronts the single stores of a first piece beside those of the
+// last one, 1 us in tiles 128 to 192 wide and 2 in 256 wide ones whatever the size; from the column on, a line of y is written in two parts, which costs nothing
+// while the caches hold it until both are there, and 1 to 8 us on larger results.  The line is taken from where it lost 2 % at most on 354 bf16 products and 300 condensed
+// calls (y 8 to 112 MB, in one buffer or in six by turns): y and half of the inputs (of as much as y of them) 31.5 MB in products in tiles up to 192 wide and 52 in 256 wide ones, 46.5 and 77 in the condensed
+// form.  The way taken is behind the better one by 0.3 % on average, always the line 3.1 %, never 4.  40 -> 10304 with 7463 stored at batch 1027 (42 MB) 17.8 us from the
+// column, 20.1 from the line; 144 -> 13216 with 12680 at 1232 (65 MB) 29.0 and 23.8; 896 -> 12576, K = 179, with 8598 at 1763 (89 MB) 52.1 and 43.9.
+__device__ __forceinline__ int line_run(int B, int d_out, long long inputs, int run, float from_mb) {
+    const long long y = 4ll * B * d_out;
+    return y + min(inputs, y) / 2 >= (long long)(from_mb * 1e6f) ? run : 0;
+}
+
 // LDS of the epilogue: one 32-row part of each wavefront row's tile at a time, at the rows' final columns (a window of COLS of them;
 // most ranges fit one), and the tables: the stored neurons' places in the range, for the window's columns which neuron
 // they are (-1: ablated) and their bias.
 template <int BN, int WGM>
 struct EpiLayout {
     static constexpr int COLS = BN >= 256 ? 512 : 256, ROWS = 32 * WGM, PITCH = COLS + 4;
-    static constexpr int LINE_RUN = BN >= 256 ? 256 : (BN >= 128 ? 128 : 0);   // for tile_columns
+    static constexpr int LINE_RUN = BN >= 256 ? 256 : (BN >= 128 ? 128 : 0);   // for line_run
     static constexpr size_t TILE_BYTES = (size_t)ROWS * PITCH * 4, TABLE_BYTES = (size_t)BN * 4 + (size_t)COLS * 8;
     static constexpr size_t BYTES = TILE_BYTES + TABLE_BYTES;
 };
@@ -118,7 +129,7 @@ __device__ __forceinline__ void fill_table(unsigned char* at, int cc, const Tile
 // With that and the float4 rows a 768 -> 3072 layer in 256 x 256 tiles went from 36.4 to 32.3 us, 4096 -> 16384 at batch 2048 from 297 to
 // 279 in 128 x 128 tiles.  Narrow tiles put 2 or 4 rows into one LDS request (16 or 32 lanes each): with 64 lanes on a row 64 x 64
 // tiles took 11.5 us instead of 9.4 on 768 -> 3072 at batch 128.
-// The windows begin at a 128-byte line of y where that is of use (tile_columns; columns in front of the tile's own are left out): from a column inside of a
+// The windows begin at a 128-byte line of y where that is of use (tile_columns, line_run; columns in front of the tile's own are left out): from a column inside of a
 // line on every store of a kilobyte then began and ended in part of a line, which streaming stores do not put together: 4096 -> 16384 with
 // 13108 stored at batch 2048 207 -> 201 us (condensed form 212 -> 208), 1024 -> 16384 with 8192 stored 73 -> 64.  (Plain stores: the first two 203 and 218.)
 // SPOILED: the tile's rows with a sum that is not finite get their bits set in `spoiled` (BM of them, in LDS); what has been written for

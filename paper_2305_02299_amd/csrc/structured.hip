@@ -345,7 +345,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_structured_gemm(const T* __r
 
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // the re-issued last stages may still be landing in the ring
     __syncthreads();
-    store_tile<BM, BN, WGM, WGN, false>(smem, smem + EpiLayout<BN, WGM>::TILE_BYTES, false, acc, tile_columns(n0, BN, active, n_active, d_out, EpiLayout<BN, WGM>::LINE_RUN), m0, n0, B,
+    const int run = line_run(B, d_out, ((long long)B + n_active) * d_in * (int)sizeof(T), EpiLayout<BN, WGM>::LINE_RUN, BN >= 256 ? 52.0f : 31.5f);
+    store_tile<BM, BN, WGM, WGN, false>(smem, smem + EpiLayout<BN, WGM>::TILE_BYTES, false, acc, tile_columns(n0, BN, active, n_active, d_out, run), m0, n0, B,
                                     active, bias, d_out, y, SRIGL_ACT_NONE, nullptr);
 }
 
