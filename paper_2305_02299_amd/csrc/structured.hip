@@ -420,7 +420,9 @@ static srigl_gemm_tile choose_tile(int B, int n_active, bool f32) {
 // 96 x 96 read fewer fragments per multiplication than 8 of 128 x 64 (13108 rows at batch 2048, d_in 4096, 1.6 rounds of 256 x 256: 205 us -> 197 on one card, 207.7 -> 204.3 on another, which the power of the matrix units limits; 11440 at 1500, 89 -> 68); a
 // layer whose 128 x 128 tiles fill three quarters of the chip or a little more than all of it goes into 128 x 96 or 64 x 128 (2335 at 1024, d_in 576, 16.9 -> 13.1; 9012 at 256, 768,
 // 18.5 -> 14.6).  Fitted on 918 products beside the time of the shape taken before, plus 6 %: it takes that much of a promise for one of them, in one part
-// only (cut into parts they were level or up to 19 % behind).  Of 105 out of 1500 random products that came to another shape 85 in one part are 1.11 times faster, the slowest 9 % behind.
+// only (cut into parts they were level or up to 19 % behind).  Not where they gain nothing on average and lose up to 14 % (left_to_others).  Of 1636 random products that come
+// to one of them without that rule the 1529 that still do take 0.897 of the time before on average; 19 of them are more than 2 % behind, at worst 20 % (64 x 64 tiles of
+// which there are just 282 take 0.8 of the time of their neighbours: 3376 deep, 6007 at 151 rows 25 us, 30 in 64 x 128).
 // Shapes that only the library's choice takes: 8 wavefronts of 64x96, 2 LDS stages of 128 bytes; 4 of 96x96, 3 stages; 4 of 32x96, 4; 4 of 32x64, 4
 constexpr int kTile256x192 = 7, kTile192x192 = 8, kTile128x96 = 9, kTile64x128 = 10;
 struct Bf16TileModel { int tile, bm, bn; float fixed, round, per_k, per_k_full, y, ablated, second, part; };
@@ -442,6 +444,15 @@ static double bf16_tiles_us(const Bf16TileModel& m, int splits, int B, int d_in,
     const double more = m.y * 1e-6 * B * d_out + (splits > 1 ? m.second + m.part * 1e-6 * splits * B * (double)n_active : n_active < d_out ? m.ablated : 0.0);
     if (m.bn == 64) return more + (groups <= 256 ? 4.17 + 3.67 * d : m.fixed + std::ceil(groups / 512) * (m.round + m.per_k * d));
     return more + m.fixed + std::ceil(groups / 256) * (m.round + m.per_k * d) + groups / 256 * m.per_k_full * d;
+}
+
+// Products in which the last two shapes are behind the ones taken before although the estimates promise 6 %: 128 x 96 from 14 MB of results on (with ablated neurons: 256 tiles without any
+// hold 12.6) between 384 and 1152 deep (84 products 2 % faster on average, 32 of them 2 to 14 % slower, where shallower and deeper ones are 5 to 10 % faster);
+// 64 x 128 where 64 x 64 tiles are just more than one to a compute unit and it fills half of them, with more than eight rows of tiles (23 products, level, 8 of them 2 to 6 % slower).
+static bool left_to_others(int tile, int B, int n_active, int d_in, int d_out) {
+    if (tile == kTile128x96) return (long long)B * d_out >= 3500000 && d_in >= 384 && d_in < 1152;
+    if (tile == kTile64x128) return B > 512 && (B + 63ll) / 64 * ((n_active + 63ll) / 64) <= 272;
+    return false;
 }
 
 struct GemmChoice { int tile, splits; double us; };
@@ -488,6 +499,7 @@ static GemmChoice choose_bf16(int B, int n_active, int d_in, int d_out, bool may
     GemmChoice best{};
     for (const Bf16TileModel& m : kBf16TileModels) {
         if (m.bn > 64 && (long long)std::max(m.bm, m.bn) * d_in * 2 >= (1ll << 31)) continue;   // launch_gemm's byte offsets
+        if (left_to_others(m.tile, B, n_active, d_in, d_out)) continue;
         const double one = bf16_tiles_us(m, 1, B, d_in, n_active, d_out);
         if (best.tile == 0 || one < best.us) best = {m.tile, 1, one};
         const int s = may_split ? parts_of(B, n_active, d_in, false, m.bm, m.bn) : 1;

@@ -1,4 +1,4 @@
-"""Which tile of the whole-input batched kernel the library's own choice takes (host arithmetic, no GPU)."""
+"""Which tile of the whole-input batched kernel, and of the bf16 product, the library's own choice takes (host arithmetic, no GPU)."""
 import random
 
 from paper_2305_02299_amd import binding as B_
@@ -30,3 +30,17 @@ def test_every_tile_taken_fits():
             assert tile in (8, 16, 32, 64) and 16 <= d_in and B > 1
             assert ((cols + 1) * tile + tile * (16 * rows | 1)) * 4 <= 160 * 1024
     assert taken > 50
+
+
+def test_shapes_of_bf16_products_that_only_the_choice_takes():
+    """(B, d_in, stored, d_out): products measured behind in 128 x 96 and 64 x 128 go into 128 x 128 and 64 x 64, the ones around them measured ahead stay."""
+    tile = lambda *sizes: B_.srigl_structured_tile_query(*sizes, B_.BF16)   # noqa: E731
+    for sizes in ((314, 544, 7906, 13632), (331, 1120, 7918, 12416), (1127, 456, 2423, 3904), (428, 448, 5660, 8256)):
+        assert tile(*sizes) == B_.TILE_128x128, sizes
+    for sizes in ((616, 2416, 1728, 1728), (1116, 2680, 899, 899), (524, 2976, 1894, 3392)):
+        assert tile(*sizes) == B_.TILE_64x64, sizes
+    for sizes in ((1057, 208, 2196, 4032), (391, 3368, 5960, 11328), (1104, 672, 2017, 2164)):
+        assert tile(*sizes) == B_.TILE_128x96, sizes
+    for sizes in ((1192, 3952, 1026, 1472), (118, 3840, 10524, 10919), (188, 3160, 5494, 5494)):
+        assert tile(*sizes) == B_.TILE_64x128, sizes
+    assert tile(1500, 2048, 11440, 11440) == B_.TILE_192x192
