@@ -85,7 +85,7 @@ __global__ __launch_bounds__(256) void k_update_init(uint4* __restrict__ head) {
 // expensive rows lie together (weights of few magnitudes lose their first rows) do not leave dies without work: signed weights on 1953 x 4096 take 400 us,
 // 412 with one run a die and 400 with no order at all, real-valued ones on 3072 x 768 40.6, 39.8 and 43.4.  (Eight runs: 396, and 768 x 3072
 // 44.4 where four take 42.8 and no order 48.6: a die then meets twice as many pages.)
-constexpr unsigned int kDies = 8, kRuns = 4;
+constexpr unsigned int kRuns = 4;
 __device__ __forceinline__ unsigned int part_of_workgroup(unsigned int w, unsigned int workgroups) {
     if (workgroups % kDies) return w;
     const unsigned int of_die = workgroups / kDies, die = w % kDies, j = w / kDies;
@@ -700,14 +700,15 @@ __global__ __launch_bounds__(256) void k_row_salient(const float* __restrict__ W
     __shared__ __align__(16) unsigned int gone[kDigits];
     bool ablates = false;
     const int lane = threadIdx.x & 63;
-    const int r = part_of_workgroup(blockIdx.x, n_wg) * 4 + (threadIdx.x >> 6);
+    const unsigned int r = part_of_workgroup(blockIdx.x, n_wg) * 4 + (threadIdx.x >> 6);
+    const bool row = is_row(r, d_out);
     if (threadIdx.x == 0) { wg_stay = 0; wg_ablated = 0; }
     const size_t row0 = (size_t)r * d_in;
     const bool quads = d_in >= 4;
     // the row's first kAhead steps are requested before the thresholds are (they do not depend on them)
     constexpr int kAhead = 4;
     RowQuad p[kAhead];
-    if (r < d_out && quads) {
+    if (row && quads) {
 #pragma unroll
         for (int u = 0; u < kAhead; ++u)
             if (256 * u < d_in) load_row_quad(p[u], W, mask, grad, row0 + quad_first(4 * lane + 256 * u, d_in));
@@ -731,7 +732,7 @@ __global__ __launch_bounds__(256) void k_row_salient(const float* __restrict__ W
         element(first + 2, own, (q.m >> 16) & 0xffu, q.w.z, q.g.z);
         element(first + 3, own, q.m >> 24, q.w.w, q.g.w);
     };
-    if (r < d_out) {
+    if (row) {
         if (quads) {
 #pragma unroll
             for (int u = 0; u < kAhead; ++u)
@@ -802,8 +803,8 @@ __global__ __launch_bounds__(256) void k_row_update(const float* __restrict__ W,
     static_assert(WPR == 1 || WPR == 4, "the workgroup's barrier is the row's");
     __shared__ int part[2][4];
     const int lane = WPR == 1 ? threadIdx.x & 63 : threadIdx.x;
-    const int part_no = part_of_workgroup(blockIdx.x, n_wg), r = WPR == 1 ? part_no * 4 + (threadIdx.x >> 6) : part_no;
-    if (r >= d_out) return;
+    const unsigned int part_no = part_of_workgroup(blockIdx.x, n_wg), r = WPR == 1 ? part_no * 4 + (threadIdx.x >> 6) : part_no;
+    if (!is_row(r, d_out)) return;
     const size_t row0 = (size_t)r * d_in;
     const bool quads = NQ > 1 || WPR > 1 || d_in >= 4;
     struct __attribute__((packed, aligned(4))) F4 { float x, y, z, w; };
@@ -1041,7 +1042,7 @@ srigl_status srigl_mask_update(const float* W, const uint8_t* mask, const float*
     const unsigned int parts = N < (1u << 24) ? std::min(blocks, 64u) : (unsigned)kWideParts;
     hipLaunchKernelGGL(k_final<true>, dim3(2 * parts), dim3(kScanThreads), 0, st, s, candA, candB, cap, (unsigned long long)K_upd, (long long)budget,
                        (int)parts, d_in, W, mask, grad, remains, N, report);
-    const dim3 row_grid(((unsigned)((d_out + 3) / 4) + kDies - 1) / kDies * kDies);   // (the same number of workgroups on every die)
+    const dim3 row_grid(row_workgroups(d_out, 4));
     hipLaunchKernelGGL(k_row_salient, row_grid, dim3(256), 0, st, W, mask, grad, d_out, d_in, row_grid.x, k, gamma_percent, s, remains);
     // (most updates ablate nothing and this launch returns at once: it takes few workgroups, whose start is then all it costs)
     const unsigned int few = std::min(blocks, 64u);
@@ -1052,7 +1053,7 @@ srigl_status srigl_mask_update(const float* W, const uint8_t* mask, const float*
     // A row is requested beside the flag that says whether it stays where the layer is still near (real-valued, all rows staying: 1953 x 4096 82.5 us, 83.7
     // behind the flag); from 8 M elements on the memory's rate counts and rows that don't stay are not read: 4096 x 4096 with a fifth of the rows ablated 137 us -> 132,
     // 16384 x 4096 549 -> 528, 4096 x 2048 with a tenth 79 either way.
-    const dim3 one_row_grid(((unsigned)d_out + kDies - 1) / kDies * kDies);
+    const dim3 one_row_grid(row_workgroups(d_out, 1));
 #define SRIGL_ROW_UPDATE(NQ, WPR)                                                                                                               \
     hipLaunchKernelGGL((N < (1u << 23) ? k_row_update<NQ, WPR, true> : k_row_update<NQ, WPR, false>), WPR == 1 ? row_grid : one_row_grid,       \
                        dim3(256), 0, st, W, mask, grad, d_out, d_in, (WPR == 1 ? row_grid : one_row_grid).x, remains, s, mask_out, W_out)

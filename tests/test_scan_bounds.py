@@ -1,5 +1,5 @@
-"""Index arithmetic of the layer-wide passes of a connectivity update at the largest layers the call accepts (fewer than 2^32 elements),
-compiled for the host: every worker ends, and the workers together visit each element once."""
+"""Index arithmetic of the passes of a connectivity update at the largest layers the call accepts (fewer than 2^32 elements), compiled for the
+host: every worker ends, the workers together visit each element once, and places behind the last row are no rows."""
 import os
 import subprocess
 
@@ -25,6 +25,17 @@ int main() {
                 });
                 if (seen != want) { printf("n %u n4 %u worker %u: %llu of %llu\n", n, n4, w, (unsigned long long)seen, (unsigned long long)want); exit(1); }
             }
+        }
+    // rows: every row of the layer has a place in the launch, and no place behind the last row is taken for one
+    for (int32_t d_out : {1, 4, 31, 32, 33, 3072, 0x7fffffe0, 0x7fffffe1, 0x7ffffffd, 0x7fffffff})
+        for (uint32_t each : {1u, 4u}) {
+            const uint64_t places = (uint64_t)srigl::row_workgroups(d_out, each) * each;
+            if (places < (uint64_t)d_out || places >= (uint64_t)d_out + 8 * each || places > 0xffffffffull || srigl::row_workgroups(d_out, each) % 8) {
+                printf("%d rows, %u each: %llu places\n", d_out, each, (unsigned long long)places);
+                return 1;
+            }
+            for (uint64_t r = (uint64_t)d_out > 40 ? d_out - 40 : 0; r < places; ++r)
+                if (srigl::is_row((uint32_t)r, d_out) != (r < (uint64_t)d_out)) { printf("%d rows: row %llu\n", d_out, (unsigned long long)r); return 1; }
         }
     printf("bounds ok\n");
 }
