@@ -85,3 +85,60 @@ def test_counts_of_no_rows(d_out, cap):
     at, report = ctypes.c_int32(0), (ctypes.c_int32 * 8)(*range(50, 58))
     assert B_.lib.srigl_condense_counted(None, d_out, 6, cap, ctypes.byref(at), report) == 1
     assert list(report) == [6, 0, 0, -1, B_.OK, 0, 0, 0]
+
+
+def test_what_the_two_calls_refuse():
+    """Everything is checked before anything is launched, so that the pointers here are only looked at."""
+    at = 1 << 20                                              # (an address that is never read)
+    count = lambda d_out=40, d_in=64, K=6, mask=at, ws=at, ws_bytes=1 << 20, counts=at, size=1024: B_.lib.srigl_condense_count(   # noqa: E731
+        mask, d_out, d_in, K, ws, ws_bytes, counts, size, None)
+    for wrong in (dict(d_out=-1), dict(d_in=-1), dict(K=-1), dict(K=65), dict(mask=None), dict(ws=None), dict(counts=at + 4)):
+        assert count(**wrong) == B_.ERR_INVALID_ARG, wrong
+    assert count(ws_bytes=B_.lib.srigl_workspace_bytes(40) - 1) == B_.ERR_CAPACITY
+    assert count(size=B_.lib.srigl_condense_count_bytes(40, 64) - 1) == B_.ERR_CAPACITY
+    assert count(d_out=20000) == B_.ERR_UNSUPPORTED           # a layer that takes no counts
+    write = lambda dt=0, d_out=40, d_in=64, K=6, cap=40, W=at, mask=at, W_c=at, idx=at, active=at, seg=at, packed=at, pb=1 << 20, ws=at, wb=1 << 20: (   # noqa: E731
+        B_.lib.srigl_condense_write(W, dt, mask, d_out, d_in, K, cap, W_c, idx, active, seg, packed, pb, ws, wb, None, None))
+    for wrong in (dict(dt=7), dict(d_out=-1), dict(K=65), dict(cap=-1), dict(W=None), dict(mask=None), dict(W_c=None), dict(idx=None), dict(active=None), dict(packed=at + 8), dict(ws=None)):
+        assert write(**wrong) == B_.ERR_INVALID_ARG, wrong
+    assert write(wb=B_.lib.srigl_workspace_bytes(40) - 1) == B_.ERR_CAPACITY
+    assert write(pb=B_.lib.srigl_packed_bytes(40, 6, 64, 0) - 1) == B_.ERR_CAPACITY
+    assert write(d_in=70000, K=65536) == B_.ERR_UNSUPPORTED    # positions in seg have 16 bits
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("with_counts", [True, False])
+@pytest.mark.parametrize("cap", [0, 20, 500])
+def test_the_two_calls_by_hand(cap, with_counts):
+    """With counts, or without them and the second launch's report, and with room for fewer rows than are stored, or for none: as srigl_condense."""
+    d_in, d_out, K = 96, 700, 9
+    L = si.make_layer(d_in, d_out, K, 1, ablate_frac=0.25, seed=3)
+    W, mask = dev(L.W), dev(L.mask)
+
+    def arrays():
+        return dict(W_c=torch.full((500, K), 7.0, device="cuda"), idx=torch.full((500, K), 7, dtype=torch.int32, device="cuda"), active=torch.full((500,), 7, dtype=torch.int32, device="cuda"),
+                    seg=torch.full((500, B_.srigl_seg_stride(d_in)), 7, dtype=torch.int16, device="cuda"),
+                    packed=torch.full((B_.lib.srigl_packed_bytes(500, K, d_in, 0),), 7, dtype=torch.uint8, device="cuda"))
+
+    if cap == 500:
+        mask[500:] = 0      # (room for every stored row)
+    ws, stream = B_.new_workspace(d_out), torch.cuda.current_stream().cuda_stream
+    ptr = lambda a: [a[k].data_ptr() for k in ("W_c", "idx", "active", "seg", "packed")] + [a["packed"].numel(), ws.data_ptr(), ws.numel() * ws.element_size()]   # noqa: E731
+    want, want_report = arrays(), torch.full((8,), -9, dtype=torch.int32).pin_memory()
+    assert B_.lib.srigl_condense(W.data_ptr(), 0, mask.data_ptr(), d_out, d_in, K, cap, *ptr(want), want_report.data_ptr(), stream) == B_.OK
+    torch.cuda.synchronize()
+    got, report = arrays(), torch.full((8,), -9, dtype=torch.int32).pin_memory()
+    size = B_.lib.srigl_condense_count_bytes(d_out, d_in)
+    counts = torch.full((size // 8,), -1, dtype=torch.int64).pin_memory()
+    ws.fill_(-1)
+    assert B_.lib.srigl_condense_count(mask.data_ptr(), d_out, d_in, K, ws.data_ptr(), ws.numel() * ws.element_size(), counts.data_ptr() if with_counts else None,
+                                       size if with_counts else 0, stream) == B_.OK
+    assert B_.lib.srigl_condense_write(W.data_ptr(), 0, mask.data_ptr(), d_out, d_in, K, cap, *ptr(got), None if with_counts else report.data_ptr(), stream) == B_.OK
+    torch.cuda.synchronize()
+    if with_counts:
+        at = ctypes.c_int32(0)
+        assert B_.lib.srigl_condense_counted(counts.data_ptr(), d_out, K, cap, ctypes.byref(at), ctypes.cast(report.data_ptr(), ctypes.c_void_p)) == 1
+    assert torch.equal(report, want_report) and report[4] == (B_.OK if cap == 500 else B_.ERR_CAPACITY)
+    assert all(torch.equal(got[k], want[k]) for k in got)
+    filled = min(cap, int(report[1]))
+    assert (got["active"][filled:] == 7).all() and (got["idx"][filled:] == 7).all()

@@ -33,3 +33,24 @@ def test_shapes_of_the_library_choice(B, n, d_in, ablated, tile):
     worst = ((y - ref).abs() / (bound * (d_in + 1) * 2.0 ** -23)).max().item()
     assert worst <= 1, worst
     assert (flat[:GUARD] == 777.0).all() and (flat[GUARD + B * d_out:] == 777.0).all()
+
+
+@pytest.mark.parametrize("B,n,d_in,ablated,tile", [(1104, 2017, 672, 147, B_.TILE_128x96), (1152, 1754, 4088, 154, B_.TILE_64x128)])
+def test_without_a_bias_and_with_values_that_are_not_finite(B, n, d_in, ablated, tile):
+    """A row of x or of the weights that holds one spoils its own results only, as in 64 bits; ablated neurons without a bias are zero."""
+    d_out = n + ablated
+    assert B_.srigl_structured_tile_query(B, d_in, n, d_out, B_.BF16) == tile
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x, Wd = torch.randn(B, d_in, device="cuda", generator=g).bfloat16(), torch.randn(n, d_in, device="cuda", generator=g).bfloat16()
+    x[5, 3], x[-1, -1], Wd[100, 7] = float("inf"), float("nan"), float("-inf")
+    active = torch.sort(torch.randperm(d_out, device="cuda", generator=g)[:n]).values
+    y = torch.full((B, d_out), 777.0, device="cuda")
+    B_.srigl_structured_linear_fwd(x.view(torch.int16), B, d_in, Wd.view(torch.int16), active.int(), n, None, d_out, y)
+    ref, got = x.double() @ Wd.double().t(), y[:, active]
+    ok = torch.isfinite(ref)
+    assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(torch.isinf(got), torch.isinf(ref)) and (got[torch.isinf(ref)] == ref[torch.isinf(ref)]).all()
+    bound = x.double().abs() @ Wd.double().abs().t()
+    assert ((got - ref).abs()[ok] <= bound[ok] * (d_in + 1) * 2.0 ** -23).all()
+    gone = torch.ones(d_out, dtype=torch.bool, device="cuda")
+    gone[active] = False
+    assert (y[:, gone] == 0).all()

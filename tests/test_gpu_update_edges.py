@@ -78,9 +78,9 @@ def test_selections_without_a_list_on_a_layer_of_256_parts():
     assert info["n_ablated_now"] > 0
 
 
-@pytest.mark.parametrize("d_out,d_in", [(8191, 1024), (8193, 1024), (32800, 256), (2049, 4097)])
+@pytest.mark.parametrize("d_out,d_in", [(8191, 1024), (8193, 1024), (32800, 256), (16400, 512), (10930, 768), (4100, 2048), (2735, 3072), (2049, 4097), (1030, 8192)])
 def test_rows_that_do_not_stay_on_either_side_of_8_m_elements(d_out, d_in):
-    """Up to 2^23 elements the last launch requests a row beside the flag that says whether it stays, beyond behind it."""
+    """Up to 2^23 elements the last launch requests a row beside the flag that says whether it stays, beyond behind it (every number of columns a lane holds)."""
     k = d_in // 20
     W, mask, g = layer(d_in, d_out, k, d_out, 0.2)
     g *= np.linspace(0.1, 1.0, d_out, dtype=np.float32)[:, None]
