@@ -15,8 +15,10 @@ HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # packed fp32 VALU forms stay off for every kernel of this library
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # A kernel's first 16 words of arguments (structs passed by value are not among them) arrive in scalar registers with its wavefronts, instead of by a load that
-    # everything else waits for: 0.15 to 0.4 us a launch, 3072 -> 768 with 538 stored at 16 rows 6.20 -> 5.95 us, 768 -> 3072 at batch 256 8.4 -> 8.25, its update 42.3 -> 41.7
+    # A kernel's first words of arguments (structs passed by value are not among them) arrive in scalar registers with its wavefronts, instead of by a load that
+    # everything else waits for.  16 is what is asked for; a wavefront has 16 registers for it and two hold the pointer to the arguments, so that 14 words come, or 13 where a
+    # pointer would be split.  0.15 to 0.4 us a launch: 4096 -> 16384 bf16 at one row 5.47 -> 5.25 us, 768 -> 3072 at batch 256 8.41 -> 8.14, its update 42.3 -> 41.7, 3072 -> 768 with 538
+    # stored at 16 rows 6.26 -> 6.00 (level on another card)
     "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wno-unused-command-line-argument",
 ]

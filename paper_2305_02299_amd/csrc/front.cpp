@@ -289,7 +289,7 @@ PyObject* mask_update(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // condense(W, mask, K, want_seg, want_packed) -> (n_active, W_c, idx, active, seg, packed), every array cut to the stored rows
 // (active: None when no neuron is ablated).  The arrays are complete in stream order like any other result; only the number of stored rows is waited for, which a
 // launch writes straight into pinned host memory (no copy launch, no stream synchronisation).  Where the library counts rows into host memory
-// (srigl_condense_count_bytes) that is the first launch, and the results are allocated and the second launch is made while it runs (768 -> 3072: 12.5 us a call, 15.7
+// (srigl_condense_count_bytes) that is the first launch, and the results are allocated and the second launch is made while it runs (768 -> 3072: 12.9 us a call, 16.2
 // with both launches behind the allocations and the report of the second one, as on the other layers).
 PyObject* condense(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     return guarded([&](PyObject*& out) {

@@ -81,10 +81,13 @@ __global__ __launch_bounds__(256) void k_update_init(uint4* __restrict__ head) {
 }
 
 // The part of the layer that workgroup w works on, in every launch that reads the layer: consecutive workgroup ids go round the eight dies, and each of
-// them stays with the same eighth of the layer, which its L2 then still holds from the launch before.  A die's eighth is four runs, so that contents whose
-// expensive rows lie together (weights of few magnitudes lose their first rows) do not leave dies without work: signed weights on 1953 x 4096 take 400 us,
-// 412 with one run a die and 400 with no order at all, real-valued ones on 3072 x 768 40.6, 39.8 and 43.4.  (Eight runs: 396, and 768 x 3072
-// 44.4 where four take 42.8 and no order 48.6: a die then meets twice as many pages.)
+// them stays with the same eighth of the layer.  (What a die keeps of it between launches the counters do not say: under them, one launch at a time, k_row_salient misses its L2 on
+// 167 of 185 thousand requests with this order and on 168 without.)  A die's eighth is four runs, so that contents whose
+// expensive rows lie together (weights of few magnitudes lose their first rows) do not leave dies without work.  Whole updates against ones with no order (and results
+// not yet streamed): real-valued contents 0.83 to 0.95 of the time (3072 x 768 43.8 -> 40.6 us, 4096 x 1024 61.4 -> 51.2, 1953 x 4096 87.9 -> 81.9), few magnitudes 0.97 to
+// 1.03, 1.05 at worst (signed weights on 4096 x 1024 185 -> 187, 1953 x 4096 351 -> 345; mostly ones on 1024 x 4096 200 -> 207).  One run a die: signed weights another 1 to 3 % slower.
+// Eight runs: those 0.94 to 0.99 of four, but real-valued ones 1.01 to 1.06 (a die then meets twice as many pages); eight on layers of 4 to 7 M elements only: signed weights on
+// 4096 x 1024 178, real-valued ones 51.7, and the choice itself 0.5 to 1 us on every other layer.
 constexpr unsigned int kRuns = 4;
 __device__ __forceinline__ unsigned int part_of_workgroup(unsigned int w, unsigned int workgroups) {
     if (workgroups % kDies) return w;
@@ -543,8 +546,8 @@ __device__ bool finish_wide(SelState& st, int sel, int part, int parts, const fl
 // it all and the others return at once; without one they share the work (finish_wide).  One workgroup runs the code for a list once, so its
 // length counts: with the list held in registers and every loop unrolled over it, fetching the instructions took most of 10 us.  12-bit
 // digits until at most kDirect keys share the prefix (step 3: the first of them from k_collect's counters, which is enough on
-// real-valued contents), which are then ranked against each other.  (Eight loads ahead instead of four: 6.1 us instead of 5.6, for
-// the same reason.)
+// real-valued contents), which are then ranked against each other.  (Eight loads ahead instead of four, for
+// the same reason: updates of 4096 x 1024 52.1 us instead of 50.9, 1953 x 4096 83.7 instead of 81.9, smaller ones level.)
 // Step 6's first workgroup also takes the new fan-in from the neuron counters (step 5) and writes the report.
 constexpr int kAhead = 4, kDirect = 256;
 template <bool PAIR>
