@@ -114,8 +114,8 @@ srigl_status srigl_condense(const void* W, srigl_dtype w_dtype, const uint8_t* m
 /* srigl_condense in two calls, for callers that wait for the number of stored rows on the host: the first launch can run before the buffers that are sized for
  * the largest result have been allocated, and on layers where that is ahead (srigl_condense_count_bytes) it leaves the rows' counts in host memory, so that they are there
  * before the second launch has run.
- * srigl_condense_count: counts (may be NULL): srigl_condense_count_bytes(d_out, d_in) bytes (0: this layer's call takes none) of pinned host memory that the GPU can
- *   write, 8-byte aligned; cleared by the call, filled by its launch.  It must stay allocated until all counts are there or the stream has finished.
+ * srigl_condense_count: counts (may be NULL): srigl_condense_count_bytes(d_out, d_in) bytes (0: on this layer the call is not ahead with them; up to 8 M elements and 2^20 rows it
+ *   takes 1024 all the same) of pinned host memory that the GPU can write, 8-byte aligned; cleared by the call, filled by its launch.  It must stay allocated until all counts are there or the stream has finished.
  * srigl_condense_counted: reads on from word *from (0 at first); 0 while counts are missing, 1 when *report (host memory) is complete, as srigl_condense reports with
  *   the cap_rows of the second call; cap_rows negative: for a second call with active NULL, which stores no rows and reports no capacity.  Without rows (d_out 0)
  *   counts is not read.  Host only.

@@ -590,11 +590,14 @@ size_t srigl_condense_count_bytes(int32_t d_out, int32_t d_in) {
     return (d_out + 42 * rows_of_one) * d_in <= 8500000 ? c.words * sizeof(unsigned long long) : 0;
 }
 
+// The layers whose rows k_row_counts counts when it is asked to: 2^20 rows are the fields of a word.
+static bool counts_fit(int32_t d_out, int32_t d_in) { return d_out > 0 && d_in > 0 && d_out <= 1 << 20 && (long long)d_out * d_in <= 8 << 20; }
+
 srigl_status srigl_condense_count(const uint8_t* mask, int32_t d_out, int32_t d_in, int32_t K, void* workspace, size_t workspace_bytes, void* counts,
                                   size_t counts_bytes, void* stream) {
     if (d_out < 0 || d_in < 0 || K < 0 || K > d_in || (d_out > 0 && d_in > 0 && mask == nullptr)) return SRIGL_ERR_INVALID_ARG;
     if (d_out > 0 && (workspace == nullptr || reinterpret_cast<uintptr_t>(counts) % 8 != 0)) return SRIGL_ERR_INVALID_ARG;
-    const size_t need = srigl_condense_count_bytes(d_out, d_in);
+    const size_t need = counts_fit(d_out, d_in) ? count_shape(d_out).words * sizeof(unsigned long long) : 0;
     if (workspace_bytes < srigl_workspace_bytes(d_out) || (counts && counts_bytes < need)) return SRIGL_ERR_CAPACITY;
     if (counts && need == 0) return SRIGL_ERR_UNSUPPORTED;
     if (counts) std::memset(counts, 0, need);

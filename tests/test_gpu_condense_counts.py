@@ -96,7 +96,7 @@ def test_what_the_two_calls_refuse():
         assert count(**wrong) == B_.ERR_INVALID_ARG, wrong
     assert count(ws_bytes=B_.lib.srigl_workspace_bytes(40) - 1) == B_.ERR_CAPACITY
     assert count(size=B_.lib.srigl_condense_count_bytes(40, 64) - 1) == B_.ERR_CAPACITY
-    assert count(d_out=20000) == B_.ERR_UNSUPPORTED           # a layer that takes no counts
+    assert count(d_out=200000, ws_bytes=1 << 24) == B_.ERR_UNSUPPORTED   # 12.8 M elements
     write = lambda dt=0, d_out=40, d_in=64, K=6, cap=40, W=at, mask=at, W_c=at, idx=at, active=at, seg=at, packed=at, pb=1 << 20, ws=at, wb=1 << 20: (   # noqa: E731
         B_.lib.srigl_condense_write(W, dt, mask, d_out, d_in, K, cap, W_c, idx, active, seg, packed, pb, ws, wb, None, None))
     for wrong in (dict(dt=7), dict(d_out=-1), dict(K=65), dict(cap=-1), dict(W=None), dict(mask=None), dict(W_c=None), dict(idx=None), dict(active=None), dict(packed=at + 8), dict(ws=None)):
@@ -142,3 +142,20 @@ def test_the_two_calls_by_hand(cap, with_counts):
     assert all(torch.equal(got[k], want[k]) for k in got)
     filled = min(cap, int(report[1]))
     assert (got["active"][filled:] == 7).all() and (got["idx"][filled:] == 7).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d_out,d_in", [(20000, 48), (1 << 20, 5), (40, 9000)])
+def test_counts_of_layers_that_are_not_ahead_with_them(d_out, d_in):
+    """Several groups to a workgroup, up to 256 of them, and rows of several turns."""
+    mask = torch.zeros((d_out, d_in), dtype=torch.uint8, device="cuda")
+    mask[:, :4] = 1
+    mask[d_out // 3:d_out // 2] = 0
+    mask[d_out - 2, 4] = 1                                      # a row of five
+    ws, counts = B_.new_workspace(d_out), torch.full((128,), -1, dtype=torch.int64).pin_memory()
+    assert B_.lib.srigl_condense_count_bytes(d_out, d_in) == 0
+    assert B_.lib.srigl_condense_count(mask.data_ptr(), d_out, d_in, 4, ws.data_ptr(), ws.numel(), counts.data_ptr(), 1024, torch.cuda.current_stream().cuda_stream) == B_.OK
+    torch.cuda.synchronize()
+    at, report = ctypes.c_int32(0), (ctypes.c_int32 * 8)()
+    assert B_.lib.srigl_condense_counted(counts.data_ptr(), d_out, 4, d_out, ctypes.byref(at), report) == 1
+    assert list(report)[:5] == [4, d_out - (d_out // 2 - d_out // 3) - 1, 1, d_out - 2, B_.ERR_FANIN]
